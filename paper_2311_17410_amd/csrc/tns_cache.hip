@@ -65,10 +65,21 @@ __global__ void __launch_bounds__(256) k_rebuild_map(const int32_t* __restrict__
 
 // Lookup of the batch against the cache as it is before the update; accesses are recorded.  A thread takes
 // kLookupUnroll ids, one grid width apart, and runs each dependent step for all of them before the next.
+//
+// Feature ids follow a power law, so thousands of lanes record an access of the same entry, and a device-wide atomic
+// on one word completes about every 20 ns here whatever the rest of the chip does (batch of 2^20 Zipf(1.05) ids, LFU:
+// 60 K accesses of the hottest entry, 1150 us for this kernel alone and as long for the row gather beside it).  The
+// accesses are therefore combined per workgroup first, in an LDS hash table twice the size of its ids (linear
+// probing: it never fills), and one atomic per distinct entry of the workgroup goes to memory.  The same table holds
+// the smallest batch position of every missed id.
 constexpr int kLookupUnroll = 4;
+constexpr int kLookupTable = 2 * 256 * kLookupUnroll;      // power of two
+constexpr int32_t kFreeKey = INT_MIN;                      // hits: slot >= 0; misses: -1 - id > INT_MIN
 __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_t num_ids, int64_t B,
                                                 const int32_t* __restrict__ ids, int32_t* __restrict__ slots,
                                                 uint8_t* __restrict__ hit, Ctl* ctl) {
+    __shared__ int32_t s_key[kLookupTable], s_val[kLookupTable];
+    __shared__ int32_t s_hits, s_misses;
     if (blockIdx.x == 0) {          // scalars of this update
         if (threadIdx.x == 0) { ctl->prefix = 0; ctl->mask = 0; ctl->remaining = 0; ctl->m = 0; ctl->n_unique = 0; }
 #pragma unroll
@@ -85,7 +96,23 @@ __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_
         s[u] = c.slot_of[in_range ? id[u] : 0];
         if (!in_range) s[u] = -2;                         // -2: id out of range
     }
-    unsigned long long h = 0, m = 0;
+    for (int i = threadIdx.x; i < kLookupTable; i += 256) s_key[i] = kFreeKey;
+    if (threadIdx.x == 0) { s_hits = 0; s_misses = 0; }
+    __syncthreads();
+    // entry of `key` in the table; a value starts at 0 (hits count up) and misses keep INT_MAX - (smallest position)
+    // as a maximum, so that both start at the same neutral value
+    auto entry_of = [&](int32_t key) -> int {
+        uint32_t e = ((uint32_t)key * 2654435761u) >> 16;
+        while (true) {
+            e &= kLookupTable - 1;
+            const int32_t k = atomicCAS(&s_key[e], kFreeKey, key);
+            if (k == kFreeKey || k == key) return (int)e;
+            ++e;
+        }
+    };
+    for (int i = threadIdx.x; i < kLookupTable; i += 256) s_val[i] = 0;
+    __syncthreads();
+    int32_t h = 0, m = 0;
 #pragma unroll
     for (int u = 0; u < kLookupUnroll; ++u) {
         const int64_t b = b0 + (int64_t)u * stride;
@@ -94,10 +121,10 @@ __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_
             if (s[u] >= 0) {
                 is_hit = 1;
                 if (policy == TNS_CACHE_LRU) c.touched[s[u]] = 1;
-                else if (policy == TNS_CACHE_LFU) atomicAdd(&c.score[s[u]], 1);
+                else if (policy == TNS_CACHE_LFU) atomicAdd(&s_val[entry_of(s[u])], 1);
             } else if (s[u] == -1) {
                 is_miss = 1;
-                atomicMin(&c.first_idx[id[u]], (int32_t)b);   // first occurrence of a missed id
+                atomicMax(&s_val[entry_of(-1 - id[u])], INT_MAX - (int32_t)b);   // first occurrence of a missed id
             }
             slots[b] = s[u];
             if (hit) hit[b] = (uint8_t)is_hit;
@@ -106,9 +133,19 @@ __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_
         m += __popcll(__ballot(is_miss));
     }
     if ((threadIdx.x & (kWave - 1)) == 0) {
-        unsigned long long* mine = c.counters + (size_t)((blockIdx.x * 4 + (threadIdx.x >> 6)) % kStripes) * 3;
-        if (h) atomicAdd(&mine[0], h);
-        if (m) atomicAdd(&mine[1], m);
+        atomicAdd(&s_hits, h);
+        atomicAdd(&s_misses, m);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kLookupTable; i += 256) {
+        const int32_t key = s_key[i];
+        if (key == kFreeKey) continue;
+        if (key >= 0) atomicAdd(&c.score[key], s_val[i]);
+        else atomicMin(&c.first_idx[-1 - key], INT_MAX - s_val[i]);
+    }
+    if (threadIdx.x < 2) {
+        const int32_t v = threadIdx.x == 0 ? s_hits : s_misses;
+        if (v) atomicAdd(&c.counters[(size_t)(blockIdx.x % kStripes) * 3 + threadIdx.x], (unsigned long long)v);
     }
 }
 
