@@ -51,6 +51,7 @@ struct SampleArgs {
     int32_t wide_offsets;  // edge array has 2^31 or more entries: 64-bit positions in LDS
     int32_t first_ticket;  // 0; tests of the chained scan's bounded wait pass 1: tile 0 then never exists
     int32_t scan_ready;    // scan_ws is already cleared (multi-hop: one clearing launch for all hops)
+    int32_t no_deleted;    // no edge of the store has been deleted
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
     uint32_t* err_flag;    // where a chained scan whose bounded wait ran out reports it (null: the error word of scan_ws)
 };
@@ -79,6 +80,8 @@ size_t compact_workspace_bytes(int64_t Q);
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream);
 // The same for a store in the prefix layout (tns_kernels_prefix.hip); launch_sample forwards to it.
 hipError_t launch_sample_prefix(const SampleArgs& a, hipStream_t stream);
+// The same with sixteen lanes per query (tns_kernels_team.hip); launch_sample forwards to it by the batch size.
+hipError_t launch_sample_team(const SampleArgs& a, hipStream_t stream);
 // Clears the chained scan's state for `num_tiles` tiles before a fused launch (kernel, capturable).
 hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t stream);
 hipError_t launch_compact(const CompactArgs& a, hipStream_t stream);

@@ -1,0 +1,409 @@
+// gfx950 sampling kernel for small batches (default layout, no deleted edges): Algorithm 1 of the paper (section 4.2), the padded write and the padding removal of section 5 fused in,
+// with sixteen lanes working on one query.
+//
+// tns_sample_kernel gives every lane a query of its own, which keeps the most independent reads in flight once a
+// batch fills the chip.  A batch that does not fill it is bound by the length of one wave's program instead: with 64
+// queries per wave the search and the gather are 16 and 10 unrolled loads with their address arithmetic, fetched once
+// from a cold instruction cache (1024 queries: 16 us, of which 3.5 us each in the walk, the search and the gather).
+// Here a team of sixteen lanes holds one query in registers, every step is one instruction for the whole query, and
+// the program is short:
+//   node      eight lanes read the node line, lane b then holds the record of the b-th oldest block
+//   window    a node's blocks, concatenated, are one chronological sequence; its candidates are a range [L, R) of
+//             it.  Each end is the block that contains it (ballot over the records, or sixteen-way search over a
+//             directory run) and the position inside (sixteen-way search over the block's timestamps: one round for
+//             blocks of up to 16 edges, four for 8192)
+//   gather    lane j takes slot j: its rank (newest first, or its own pick), the block that holds it, the edge.
+//             Under the uniform policy the f picks of a query are resolved side by side instead of one after the
+//             other.
+// What bounds it is the chain of dependent reads (query, node, search, edge, look-back) and, as every workgroup takes
+// a ticket, 18 ns per tile.  Measured beside tns_sample_kernel, fan-out 10, in us per call: see the rule in launch_sample.
+#include <type_traits>
+
+#include "../../include/tns.h"
+#include "tns_device.h"
+#include "tns_kernels.h"
+
+namespace tns {
+namespace {
+
+constexpr int kTeam = 16;
+constexpr int kTeamsPerWave = kWave / kTeam;
+constexpr int64_t kComputeUnits = 256;
+constexpr int kTileWaves = 16;       // 64 queries per workgroup at least: the workspace holds one tile state per 64 queries
+
+// For each of CH independent ranges: number of leading items of [0, n) for which qual(u, i) holds (the items for which
+// it holds come first), found by the team together: sixteen probes a round, the rounds of all ranges side by side.
+// n is the same in all lanes of a team; called by the whole wave.
+template <int CH, class Qual>
+__device__ __forceinline__ void team_partition(int32_t (&n)[CH], int32_t (&lo)[CH], int lane, const Qual& qual) {
+    const int j = lane & (kTeam - 1), shift = lane & ~(kTeam - 1);
+    bool any = false;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        lo[u] = 0;
+        any = any || n[u] > 0;
+    }
+    while (__ballot(any)) {
+        bool ok[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int32_t s = (n[u] + kTeam - 1) / kTeam;
+            ok[u] = n[u] > 0 && qual(u, lo[u] + min((j + 1) * s - 1, n[u] - 1));
+        }
+        any = false;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int32_t s = (n[u] + kTeam - 1) / kTeam;
+            const int32_t cnt = __popcll((__ballot(ok[u]) >> shift) & 0xffffull);
+            // the first cnt probes qualify, the next one does not: the answer is less than s items further on
+            const int32_t step = min(cnt * s, n[u]);
+            lo[u] += step;
+            n[u] = max(min(s - 1, n[u] - step), 0);
+            any = any || n[u] > 0;
+        }
+    }
+}
+
+// CH: queries per team, all steps of which run side by side; ROUNDS: of sixteen slots
+template <int POLICY, bool INCL, int CH, int ROUNDS>
+__global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) tns_sample_team_kernel(const SampleArgs p) {
+    constexpr int kTileQueries = kTileWaves * kTeamsPerWave * CH;
+    __shared__ int64_t s_tile_base;
+    __shared__ int32_t s_wave_sum[kTileWaves];
+    __shared__ int32_t s_arrived;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x >> 6;
+    const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
+    const int32_t f = p.fanout;
+    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    // later hops are launched for the most queries they can have: workgroups beyond the actual number leave at once
+    if ((int64_t)blockIdx.x * kTileQueries >= Q) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
+            p.rowptr[0] = 0;
+            if (p.total_out) *p.total_out = 0;
+        }
+        return;
+    }
+    ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
+    if (threadIdx.x == 0) {
+        // tiles are numbered in the order workgroups start
+        s_tile_base = (int64_t)atomicAdd(&ws->ticket, 1u);
+        s_arrived = 0;
+    }
+    __syncthreads();
+    const int64_t tile = s_tile_base;
+    __syncthreads();
+    // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
+    const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
+
+    // ---- the queries and their nodes ---------------------------------------------------------
+    float te[CH], tb[CH];
+    int32_t v[CH];
+    int64_t nidx[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        const int64_t q = q0 + u * kTeamsPerWave;
+        v[u] = -1; te[u] = 0.0f; tb[u] = 0.0f;
+        if (q < Q) {
+            v[u] = p.targets[q];
+            te[u] = p.t_end[q];
+            if (p.t_start) tb[u] = p.t_start[q];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        if (!p.t_start) tb[u] = p.delta == INFINITY ? -INFINITY : te[u] - p.delta;
+        nidx[u] = (uint32_t)v[u] < (uint64_t)p.num_nodes && !(te[u] != te[u]) && !(tb[u] != tb[u]) ? v[u] : -1;
+        if (q0 + u * kTeamsPerWave >= Q) nidx[u] = -1;
+    }
+    if (p.inst_rowptr) {
+        // instance b owns queries inst_rowptr[b] .. inst_rowptr[b+1]-1
+        int32_t n[CH], b[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) n[u] = q0 + u * kTeamsPerWave < Q ? p.num_instances : 0;
+        team_partition<CH>(n, b, lane, [&](int u, int32_t i) { return p.inst_rowptr[i + 1] <= q0 + u * kTeamsPerWave; });
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            if (b[u] >= p.num_instances) nidx[u] = -1;
+            if (nidx[u] >= 0) nidx[u] += (int64_t)b[u] * p.num_nodes;
+        }
+    }
+    u32x4 piece[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        piece[u] = u32x4{0u, 0u, 0u, 0u};
+        if (nidx[u] >= 0 && j < 8) piece[u] = *(reinterpret_cast<const u32x4*>(p.nodes + nidx[u]) + j);
+    }
+    int32_t nb_in[CH], nb_long[CH];     // blocks in the node line / in the directory run (one of them is 0)
+    uint32_t dline[CH];                 // start of the run in units of kDirAlign records
+    BlockRec rec[CH];                   // lane b: record of the b-th oldest block
+    int32_t cum[CH];                    // lane b: edges in the older blocks
+    int32_t piv[CH];                    // long lists: lane b: edges in the blocks before the (b * piv_step)-th
+    bool any_long = false;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        int32_t nb = __shfl((int)piece[u].x, team0, kWave);
+        dline[u] = (uint32_t)__shfl((int)piece[u].z, team0, kWave);
+        if (__shfl((int)piece[u].w, team0, kWave) & 1) nb = 0;                       // deleted node: no blocks
+        if (nb > kInlineBlocks && (int64_t)dline[u] * kDirAlign + nb > p.num_dir) nb = 0;
+        nb_in[u] = nb > kInlineBlocks ? 0 : nb;
+        nb_long[u] = nb - nb_in[u];
+        any_long = any_long || nb_long[u] > 0;
+        const int src = team0 + max(nb_in[u] - j, 0);          // inline records are stored newest first
+        rec[u].t_min = __uint_as_float((uint32_t)__shfl((int)piece[u].x, src, kWave));
+        rec[u].t_max = __uint_as_float((uint32_t)__shfl((int)piece[u].y, src, kWave));
+        rec[u].off_lo = (uint32_t)__shfl((int)piece[u].z, src, kWave);
+        rec[u].size_hi = (uint32_t)__shfl((int)piece[u].w, src, kWave);
+        const int32_t size = j < nb_in[u] ? rec_size(rec[u]) : 0;
+        cum[u] = size;
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+            const int32_t w = __shfl_up(cum[u], d, kTeam);
+            if (j >= d) cum[u] += w;
+        }
+        cum[u] -= size;
+        piv[u] = 0;
+        if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
+    }
+    any_long = __ballot(any_long) != 0;
+
+    // ---- the window [L, R) in a node's sequence of edges --------------------------------------
+    // index of the first edge with ts >= x (STRICT: ts > x)
+    auto first_at = [&](const float (&x)[CH], int32_t (&at)[CH], auto strict) {
+        constexpr bool STRICT = decltype(strict)::value;
+        auto before = [&](int u, float t) { return STRICT ? t <= x[u] : t < x[u]; };
+        int32_t b[CH], n[CH], base[CH], size[CH], pos[CH];
+        int64_t off[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) b[u] = __popcll((__ballot(j < nb_in[u] && before(u, rec[u].t_max)) >> team0) & 0xffffull);
+        if (any_long) {
+            int32_t bl[CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) n[u] = nb_long[u];
+            team_partition<CH>(n, bl, lane, [&](int u, int32_t i) { return before(u, p.dir[(int64_t)dline[u] * kDirAlign + i].t_max); });
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+                if (nb_long[u] > 0) b[u] = bl[u];
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int32_t nb = nb_in[u] + nb_long[u], bb = max(min(b[u], nb - 1), 0);
+            const int src = team0 + (nb_in[u] > 0 ? bb : 0);
+            BlockRec r;
+            r.t_min = __shfl(rec[u].t_min, src, kWave);
+            r.off_lo = (uint32_t)__shfl((int)rec[u].off_lo, src, kWave);
+            r.size_hi = (uint32_t)__shfl((int)rec[u].size_hi, src, kWave);
+            base[u] = __shfl(cum[u], src, kWave);
+            if (nb_long[u] > 0) {
+                r = p.dir[(int64_t)dline[u] * kDirAlign + bb];
+                base[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + bb];
+            }
+            size[u] = rec_size(r);
+            off[u] = rec_off(r);
+            // the block's newest edge is not before x: one item less to search
+            n[u] = (b[u] < nb && before(u, r.t_min)) ? size[u] - 1 : 0;
+        }
+        team_partition<CH>(n, pos, lane, [&](int u, int32_t i) { return before(u, __uint_as_float(p.edges[slot_word(off[u] + i)])); });
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int32_t nb = nb_in[u] + nb_long[u];
+            at[u] = nb <= 0 ? 0 : base[u] + (b[u] >= nb ? size[u] : pos[u]);
+        }
+    };
+    int32_t R[CH], L[CH], c[CH], k[CH];
+    first_at(te, R, std::integral_constant<bool, INCL>{});
+    bool windowed = false;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        L[u] = 0;
+        windowed = windowed || tb[u] > -INFINITY;
+    }
+    if (__ballot(windowed)) first_at(tb, L, std::false_type{});
+
+    // ---- dense offsets inside the workgroup -----------------------------------------------------
+    int32_t excl_in_wave[CH], wave_total = 0;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        c[u] = max(R[u] - L[u], 0);
+        k[u] = min(c[u], f);
+        const int32_t k0 = __shfl(k[u], 0, kWave), k1 = __shfl(k[u], 16, kWave), k2 = __shfl(k[u], 32, kWave), k3 = __shfl(k[u], 48, kWave);
+        excl_in_wave[u] = wave_total + (lane >= 16 ? k0 : 0) + (lane >= 32 ? k1 : 0) + (lane >= 48 ? k2 : 0);
+        wave_total += k0 + k1 + k2 + k3;
+    }
+    int is_last = 0;
+    if (lane == 0) {
+        s_wave_sum[wave] = wave_total;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        is_last = __hip_atomic_fetch_add(&s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == kTileWaves - 1;
+    }
+    is_last = __shfl(is_last, 0, kWave);
+    int32_t wg_total = 0;
+    if (is_last) {
+        // the wave that arrives last publishes the tile total at once, so that later tiles can look past this one
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        for (int i = 0; i < kTileWaves; ++i) wg_total += s_wave_sum[i];
+        if (lane == 0 && tile > 0)
+            __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // ---- slots: rank -> block -> edge -----------------------------------------------------------
+    Edge e[CH][ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        int32_t g[CH], cb[CH], lo[CH], hi[CH];
+        BlockRec rb[CH];
+        const int32_t slot_no = r * kTeam + j;
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            e[u][r].ts = 0.0f; e[u][r].nbr = -1; e[u][r].eid = -1;
+            any = any || slot_no < k[u];
+        }
+        if (!__ballot(any)) continue;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            g[u] = R[u] - 1 - slot_no;                // newest first; so too when all candidates are taken
+            if (POLICY == 1 && slot_no < k[u] && c[u] > f)
+                g[u] = L[u] + (int32_t)pick_rank(p.seed, p.qid_base + q0 + u * kTeamsPerWave, f, slot_no, (uint64_t)c[u]);
+            // newest inline block that starts at or before g
+            int32_t b = -1;
+#pragma unroll
+            for (int t = 0; t < kInlineBlocks; ++t) b += (t < nb_in[u] && __shfl(cum[u], team0 + t, kWave) <= g[u]) ? 1 : 0;
+            const int src = team0 + max(b, 0);
+            rb[u].off_lo = (uint32_t)__shfl((int)rec[u].off_lo, src, kWave);
+            rb[u].size_hi = (uint32_t)__shfl((int)rec[u].size_hi, src, kWave);
+            cb[u] = __shfl(cum[u], src, kWave);
+        }
+        if (any_long) {
+            bool more = false;
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                const int32_t piv_step = (nb_long[u] + kTeam - 1) / kTeam;
+                int32_t lo16 = 0;
+#pragma unroll
+                for (int d = kTeam / 2; d >= 1; d >>= 1) {
+                    const int32_t t = lo16 + d;
+                    const int32_t w = __shfl(piv[u], team0 + t, kWave);
+                    if (t * piv_step < nb_long[u] && w <= g[u]) lo16 = t;
+                }
+                lo[u] = lo16 * piv_step;
+                hi[u] = slot_no < k[u] ? min(lo[u] + piv_step, nb_long[u]) : lo[u];
+                more = more || hi[u] - lo[u] > 1;
+            }
+            while (__ballot(more)) {
+                more = false;
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    const int32_t mid = lo[u] + ((hi[u] - lo[u]) >> 1);
+                    if (hi[u] - lo[u] > 1) {
+                        if ((int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + mid] <= g[u]) lo[u] = mid; else hi[u] = mid;
+                    }
+                    more = more || hi[u] - lo[u] > 1;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+                if (nb_long[u] > 0 && slot_no < k[u]) {
+                    rb[u] = p.dir[(int64_t)dline[u] * kDirAlign + lo[u]];
+                    cb[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + lo[u]];
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+            if (slot_no < k[u]) e[u][r] = *reinterpret_cast<const Edge*>(p.edges + slot_word(rec_off(rb[u]) + (g[u] - cb[u])));
+    }
+
+    // ---- outputs --------------------------------------------------------------------------------
+    if (is_last) {
+        const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
+        if (lane == 0) {
+            __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_tile_base = excl;
+        }
+    }
+    if (p.out_nbr) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int64_t q = q0 + u * kTeamsPerWave;
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                const int32_t slot_no = r * kTeam + j;
+                if (q < Q && slot_no < f) {
+                    const int64_t o = q * f + slot_no;
+                    __builtin_nontemporal_store(e[u][r].nbr, &p.out_nbr[o]);
+                    __builtin_nontemporal_store(e[u][r].eid, &p.out_eid[o]);
+                    __builtin_nontemporal_store(e[u][r].ts, &p.out_ts[o]);
+                }
+            }
+        }
+    }
+    lds_barrier();
+    int64_t wave_row = s_tile_base;
+    for (int i = 0; i < wave; ++i) wave_row += s_wave_sum[i];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+        const int64_t q = q0 + u * kTeamsPerWave;
+        const int64_t row = wave_row + excl_in_wave[u];
+        if (q >= Q) continue;
+        if (j == 0) {
+            p.rowptr[q] = row;
+            if (p.out_count) p.out_count[q] = k[u];
+            if (q == Q - 1) {
+                // The last query's tile has looked back over every other tile.  If any wait ran into its bound the
+                // dense rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
+                __threadfence();
+                const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                const int64_t tot = bad ? 0 : row + k[u];
+                p.rowptr[Q] = tot;
+                if (p.total_out) *p.total_out = tot;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const int32_t slot_no = r * kTeam + j;
+            if (slot_no < k[u]) {
+                p.cmp_nbr[row + slot_no] = e[u][r].nbr;
+                p.cmp_eid[row + slot_no] = e[u][r].eid;
+                p.cmp_ts[row + slot_no] = e[u][r].ts;
+            }
+        }
+    }
+}
+
+template <int POLICY, bool INCL, int CH, int ROUNDS>
+hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
+    constexpr int64_t kTileQueries = kTileWaves * kTeamsPerWave * CH;
+    const int64_t grid = (a.Q + kTileQueries - 1) / kTileQueries;
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (!a.scan_ready) {
+        // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
+        const hipError_t e = launch_scan_init(a, grid + 1, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (grid <= 0) return hipGetLastError();
+    SampleArgs b = a;
+    if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
+    hipLaunchKernelGGL((tns_sample_team_kernel<POLICY, INCL, CH, ROUNDS>), dim3((unsigned)grid), dim3(kTileWaves * kWave), 0, stream, b);
+    return hipGetLastError();
+}
+
+template <int POLICY, bool INCL>
+hipError_t launch_team_p(const SampleArgs& a, hipStream_t stream) {
+    constexpr int kAllRounds = 4;
+    static_assert(kAllRounds * kTeam >= TNS_MAX_FANOUT, "rounds cover the largest fan-out");
+    // Queries per team: one while the batch gives a compute unit no more than one workgroup (16384 queries: 12.5 us
+    // against 13.2 with two per team, power-law ids 14.3 / 17.9), two beyond (32768: 15.6 against 18.9, 65536: 23.6 /
+    // 30.7; tickets are taken at 18 ns each, and a tile is then 128 queries).
+    const bool one = a.Q <= kComputeUnits * (int64_t)(kTileWaves * kTeamsPerWave);
+    if (a.fanout > kTeam) return one ? launch_team_t<POLICY, INCL, 1, kAllRounds>(a, stream) : launch_team_t<POLICY, INCL, 2, kAllRounds>(a, stream);
+    return one ? launch_team_t<POLICY, INCL, 1, 1>(a, stream) : launch_team_t<POLICY, INCL, 2, 1>(a, stream);
+}
+
+}  // namespace
+
+hipError_t launch_sample_team(const SampleArgs& a, hipStream_t stream) {
+    if (a.policy == 0) return a.inclusive_end ? launch_team_p<0, true>(a, stream) : launch_team_p<0, false>(a, stream);
+    return a.inclusive_end ? launch_team_p<1, true>(a, stream) : launch_team_p<1, false>(a, stream);
+}
+
+}  // namespace tns

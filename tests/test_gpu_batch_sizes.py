@@ -1,0 +1,55 @@
+"""A batch may be run in pieces of any size: the pieces (sixteen lanes per query) and the whole (a query per lane) must
+give the oracle's result bit for bit, on nodes with no edge, with inline block lists and with long directory runs."""
+import numpy as np
+import pytest
+
+from paper_2311_17410_amd import workloads as W
+from _harness import assert_same, gpu_sample
+
+pytestmark = pytest.mark.gpu
+
+PIECES = [1, 3, 4, 63, 64, 65, 127, 128, 129, 1024, 16384, 16385, 32700]       # edges of the tiles and of the dispatch
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2311_17410_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("fanout,incl,tau,ties", [(10, 0, 8192, False), (16, 1, 48, True), (17, 0, 5, False), (64, 1, 1, True), (1, 0, 48, True)])
+def test_pieces_equal_whole(B, oracle_lib, policy, fanout, incl, tau, ties):
+    import torch
+    rng = np.random.default_rng(fanout * 7 + policy)
+    nodes, n = 3000, 60_000
+    src = (rng.zipf(1.2, n) % (nodes - 5)).astype(np.int32)
+    dst = rng.integers(0, nodes, n, dtype=np.int32)
+    ts = np.sort(rng.integers(0, n // 20, n) if ties else rng.standard_normal(n)).astype(np.float32)
+    plan = B.Plan(nodes, fanout, policy=policy, block_threshold=tau, inclusive_end=incl, seed=9, flags=B.TNS_FLAG_DEVICE_INGEST)
+    bounds = list(range(0, n, 1500)) + [n]
+    d = [torch.from_numpy(a).cuda() for a in (src, dst, ts)]
+    for lo, hi in zip(bounds[:-1], bounds[1:]):
+        plan.add_edges_device(d[0][lo:hi], d[1][lo:hi], d[2][lo:hi])
+    st = W.Stream(nodes, src, dst, ts, 1500)
+    Q = 1 + sum(PIECES) + 300
+    targets, t_start, t_end = W.random_queries(3, st, Q)
+    adj = oracle_lib.Adjacency(nodes, src, dst, ts, batch_rowptr=bounds)
+    assert Q > 1 << 16                                   # the whole takes the other kernel
+    for tb in (None, t_start):
+        ref = adj.sample(targets, tb, t_end, fanout, policy=policy, inclusive_end=incl, seed=9)
+        assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, "whole")
+        lo = 0
+        for size in PIECES + [Q - sum(PIECES)]:
+            hi = lo + size
+            part = oracle_lib.Sampled(size, fanout)
+            for name in ("nbr", "eid", "ts", "count"):
+                setattr(part, name, getattr(ref, name)[lo:hi])
+            got = gpu_sample(plan, targets[lo:hi], None if tb is None else tb[lo:hi], t_end[lo:hi], query_id_base=lo)
+            assert_same(got, part, oracle_lib, f"piece {lo}..{hi}")
+            lo = hi
+    adj.close()
+    plan.close()
