@@ -47,6 +47,30 @@ __device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v, int lane) {
     return v;
 }
 
+// Instance of query q, one of the wave's 64 consecutive queries from q0 on: instance b owns queries rowptr[b] ..
+// rowptr[b + 1] - 1.  The wave finds the instance of its first query together, 64 probes a round (two dependent reads
+// for 256 instances where a binary search per lane makes eight), and only a wave whose queries lie in several instances
+// searches on from there lane by lane.  num_instances for a q beyond the last instance.
+__device__ __forceinline__ int32_t instance_of(const int64_t* __restrict__ rowptr, int32_t num_instances, int64_t q0, int64_t q,
+                                               int64_t Q, int lane) {
+    int32_t first = 0, n = num_instances;
+    while (n > 0) {
+        const int32_t s = (n - 1) / kWave + 1;
+        const bool past = rowptr[1 + first + (int32_t)min((int64_t)(lane + 1) * s - 1, (int64_t)n - 1)] <= q0;
+        const int32_t cnt = __popcll(__ballot(past));
+        const int32_t step = (int32_t)min((int64_t)cnt * s, (int64_t)n);
+        first += step;
+        n = max(min(s - 1, n - step), 0);
+    }
+    if (first >= num_instances || rowptr[first + 1] >= min(q0 + kWave, Q)) return first;
+    int32_t lo = first, hi = num_instances;
+    while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (rowptr[mid + 1] <= q) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
 constexpr int kCoopGroup = 16;        // lanes per query in the cooperative search (recent policy, fan-out <= 16)
 constexpr int kGatherChunk = 10;      // gather iterations whose loads are issued together (8 and 5 measured slower)
 

@@ -64,6 +64,16 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
     const int wave = threadIdx.x >> 6;
     const int waves_per_wg = blockDim.x >> 6;
 
+    // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
+    // have none leave before they take a ticket (18 ns each)
+    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
+            p.rowptr[0] = 0;
+            if (p.total_out) *p.total_out = 0;
+        }
+        return;
+    }
     int64_t tile;
     if (FUSED) {
         // tiles are numbered in the order workgroups start
@@ -81,12 +91,6 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
-    // number of queries: the host's bound, or fewer when the count lives on the device (later hops)
-    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
-    if (FUSED && Q <= 0 && tile == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
-        p.rowptr[0] = 0;
-        if (p.total_out) *p.total_out = 0;
-    }
 
     Walk<POLICY, INCL, pos_t> w;
     w.f = f;
@@ -98,6 +102,7 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
     w.tb = 0.0f;
     int32_t n_nodes = 0;
     int64_t nidx = -1;           // index of the target's entry in the node table, -1: no walk
+    const int32_t inst = p.inst_rowptr ? instance_of(p.inst_rowptr, p.num_instances, q0, q, Q, lane) : 0;
     if (q < Q) {
         const int32_t v = __builtin_nontemporal_load(&p.targets[q]);
         w.te = __builtin_nontemporal_load(&p.t_end[q]);
@@ -105,14 +110,8 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
         int64_t nbase = 0;
         bool ok = (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
         if (p.inst_rowptr) {
-            // instance b owns queries inst_rowptr[b] .. inst_rowptr[b+1]-1
-            int32_t lo = 0, hi = p.num_instances;
-            while (lo < hi) {
-                const int32_t mid = lo + ((hi - lo) >> 1);
-                if (p.inst_rowptr[mid + 1] <= q) lo = mid + 1; else hi = mid;
-            }
-            ok = ok && lo < p.num_instances;
-            nbase = (int64_t)lo * p.num_nodes;
+            ok = ok && inst < p.num_instances;
+            nbase = (int64_t)inst * p.num_nodes;
         }
         if (ok) nidx = nbase + v;
     }

@@ -12,7 +12,7 @@
 // How the wave reads it.  Every 128-byte line is fetched exactly once and nothing is read twice:
 //   * node lines: eight lanes per line, 16 bytes each, handed to the owning lane through LDS; the lane
 //     counts the qualifying slots of its own line in registers (eight compares, no search loop);
-//   * extension lines: the requests of a wave are compacted, sixteen lanes serve one request, lane j
+//   * extension lines: the requests of a wave are compacted, ten lanes serve one request, lane j
 //     loads the 12-byte edge of slot j; two ballots give the window ends inside the line, and the lanes
 //     whose edges are selected write them straight into the query's result row in LDS;
 //   * result rows (f edges per query, newest first up to a rotation that makes the row position of an
@@ -41,10 +41,14 @@ __device__ __forceinline__ int ceil_log2_outcomes(int n) { return n <= 0 ? 0 : 3
 // window end (all of them if open_end) and not before its window start the newest `cap` are written into
 // the lane's result row, the newest at row position (from_f ? f - a : 0), a = how many are taken.
 //
-// The requests are compacted; sixteen lanes serve one request, lane j loads the 12-byte edge of slot j.
+// The requests are compacted; ten lanes serve one request, lane j loads the 12-byte edge of slot j.  The kernel is bound
+// by the instructions it issues, and this is where most of them were: an instruction serves six requests (with sixteen
+// lanes each it served four), and the steps of a batch that have no request are skipped (uniform branches).  2640 vector instructions per wave before;
+// 2^22 edges and queries, fan-out 10, without the padding removal: 391 -> 328 us, with it 497 -> 480.
 // A request's parameters stay in the registers of the lane that made it and reach the serving lanes by
 // shuffles; LDS only holds who made request number r (one byte) and, afterwards, its two counts.
-constexpr int kBatch = 8;             // load instructions issued together = 32 requests
+constexpr int kReqs = kWave / kSlotsPerLine;      // requests per load instruction
+constexpr int kBatch = 6;             // load instructions issued together = 36 requests
 struct ExtBatch {
     Edge ed[kBatch];
     uint32_t par[kBatch];             // owner | n << 8 | cap << 16 | from_f << 24 | open_end << 25 | valid << 31
@@ -52,36 +56,41 @@ struct ExtBatch {
 
 __device__ __forceinline__ void ext_issue(ExtBatch& x, const uint32_t* __restrict__ lines, const unsigned char* owner_of, int b0,
                                           int total, int lane, uint32_t my_line, uint32_t my_par) {
-    const int g = lane >> 4, j = lane & 15;
+    const int g = lane / kSlotsPerLine, j = lane - g * kSlotsPerLine;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
-        const int req = b0 + i * 4 + g;
-        const bool valid = req < total;
-        const int owner = valid ? (int)owner_of[req] : lane;
-        const uint32_t line = (uint32_t)__shfl((int)my_line, owner, kWave);
-        // (every lane takes part in the shuffles: a lane that sat one out could not be read by the others)
-        const uint32_t par = (uint32_t)__shfl((int)my_par, owner, kWave);
-        x.par[i] = valid ? (par | 0x80000000u) : 0u;
+        x.par[i] = 0u;
         x.ed[i].ts = 0.0f; x.ed[i].nbr = -1; x.ed[i].eid = -1;
-        if (valid && j < (int)((x.par[i] >> 8) & 0xffu))
-            x.ed[i] = *reinterpret_cast<const Edge*>(lines + (uint64_t)line * 32u + (uint32_t)(3 * j));
+        if (b0 + i * kReqs < total) {
+            const int req = b0 + i * kReqs + g;
+            const bool valid = g < kReqs && req < total;
+            const int owner = valid ? (int)owner_of[req] : lane;
+            const uint32_t line = (uint32_t)__shfl((int)my_line, owner, kWave);
+            // (every lane takes part in the shuffles: a lane that sat one out could not be read by the others)
+            const uint32_t par = (uint32_t)__shfl((int)my_par, owner, kWave);
+            x.par[i] = valid ? (par | 0x80000000u) : 0u;
+            if (j < (int)((x.par[i] >> 8) & 0xffu))
+                x.ed[i] = *reinterpret_cast<const Edge*>(lines + (uint64_t)line * 32u + (uint32_t)(3 * j));
+        }
     }
 }
 
 template <bool INCL>
 __device__ __forceinline__ void ext_process(const ExtBatch& x, unsigned char* result_of, uint32_t* rows, int rs, int f, int b0,
-                                            int lane, float my_te, float my_tb) {
-    const int g = lane >> 4, j = lane & 15;
+                                            int total, int lane, float my_te, float my_tb) {
+    const int g = lane / kSlotsPerLine, j = lane - g * kSlotsPerLine;
+    constexpr uint32_t kLineMask = (1u << kSlotsPerLine) - 1u;
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
+        if (b0 + i * kReqs >= total) break;
         const bool valid = (x.par[i] >> 31) != 0;
         const int nn = (int)((x.par[i] >> 8) & 0xffu), cp = (int)((x.par[i] >> 16) & 0xffu);
         const bool in = valid && j < nn;
         const float qe = __shfl(my_te, (int)(x.par[i] & 0xffu), kWave), qb = __shfl(my_tb, (int)(x.par[i] & 0xffu), kWave);
         const bool before = in && (((x.par[i] >> 25) & 1u) || (INCL ? (x.ed[i].ts <= qe) : (x.ed[i].ts < qe)));
         const bool early = in && x.ed[i].ts < qb;
-        const int r = __popcll((__ballot(before) >> (g * 16)) & 0xffffull);
-        const int l = __popcll((__ballot(early) >> (g * 16)) & 0xffffull);
+        const int r = __popc((uint32_t)(__ballot(before) >> (g * kSlotsPerLine)) & kLineMask);
+        const int l = __popc((uint32_t)(__ballot(early) >> (g * kSlotsPerLine)) & kLineMask);
         const int lo_sel = max(l, r - cp);
         const int a = max(r - lo_sel, 0);
         const int base = ((x.par[i] >> 24) & 1u) ? f - a : 0;
@@ -91,7 +100,7 @@ __device__ __forceinline__ void ext_process(const ExtBatch& x, unsigned char* re
             dst[1] = (uint32_t)x.ed[i].nbr;
             dst[2] = (uint32_t)x.ed[i].eid;
         }
-        if (valid && j == 0) result_of[b0 + i * 4 + g] = (unsigned char)(r | (l << 4));
+        if (valid && j == 0) result_of[b0 + i * kReqs + g] = (unsigned char)(r | (l << 4));
     }
 }
 
@@ -179,6 +188,17 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
     const int wave = threadIdx.x >> 6;
     const int waves_per_wg = blockDim.x >> 6;
 
+    // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
+    // have none leave before they take a ticket (18 ns each; two hops from 2^20 roots with a window, most of the
+    // second hop's workgroups empty: 820 -> 563 us together with the line requests above)
+    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
+            p.rowptr[0] = 0;
+            if (p.total_out) *p.total_out = 0;
+        }
+        return;
+    }
     int64_t tile;
     if (FUSED) {
         ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
@@ -195,12 +215,6 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
-    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
-    if (FUSED && Q <= 0 && tile == 0 && threadIdx.x == 0) {
-        p.rowptr[0] = 0;
-        if (p.total_out) *p.total_out = 0;
-    }
-
     unsigned char* const my_lds = smem + (size_t)wave * chunk;
     uint32_t* const rows = reinterpret_cast<uint32_t*>(my_lds);
     const uint32_t* __restrict__ lines = p.edges;
@@ -208,6 +222,7 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
     // ---- the query and its node ------------------------------------------------------------
     float te = 0.0f, tb = 0.0f;
     int64_t nidx = -1;
+    const int32_t inst = p.inst_rowptr ? instance_of(p.inst_rowptr, p.num_instances, q0, q, Q, lane) : 0;
     if (q < Q) {
         const int32_t v = __builtin_nontemporal_load(&p.targets[q]);
         te = __builtin_nontemporal_load(&p.t_end[q]);
@@ -215,13 +230,8 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
         int64_t nbase = 0;
         bool ok = (uint32_t)v < (uint64_t)p.num_nodes && !(te != te) && !(tb != tb);
         if (p.inst_rowptr) {
-            int32_t lo = 0, hi = p.num_instances;
-            while (lo < hi) {
-                const int32_t mid = lo + ((hi - lo) >> 1);
-                if (p.inst_rowptr[mid + 1] <= q) lo = mid + 1; else hi = mid;
-            }
-            ok = ok && lo < p.num_instances;
-            nbase = (int64_t)lo * p.num_nodes;
+            ok = ok && inst < p.num_instances;
+            nbase = (int64_t)inst * p.num_nodes;
         }
         if (ok) nidx = nbase + v;
     }
@@ -355,11 +365,11 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
             }
         } else if (total1 > 0) {
             wave_lds_sync();
-            ext_process<INCL>(xb, result_of, rows, rs, f, 0, lane, te, tb);
+            ext_process<INCL>(xb, result_of, rows, rs, f, 0, total1, lane, te, tb);
 #pragma unroll 1
-            for (int b0 = 4 * kBatch; b0 < total1; b0 += 4 * kBatch) {
+            for (int b0 = kReqs * kBatch; b0 < total1; b0 += kReqs * kBatch) {
                 ext_issue(xb, lines, owner_of, b0, total1, lane, line1, par1);
-                ext_process<INCL>(xb, result_of, rows, rs, f, b0, lane, te, tb);
+                ext_process<INCL>(xb, result_of, rows, rs, f, b0, total1, lane, te, tb);
             }
             wave_lds_sync();
             if (need1) {
@@ -398,9 +408,9 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
                 const uint32_t line2 = need2 ? ext_line(e - 1) : 0u;
                 const uint32_t par2 = (uint32_t)lane | ((uint32_t)kSlotsPerLine << 8) | ((uint32_t)(f - k) << 16) | (1u << 25);
 #pragma unroll 1
-                for (int b0 = 0; b0 < total2; b0 += 4 * kBatch) {
+                for (int b0 = 0; b0 < total2; b0 += kReqs * kBatch) {
                     ext_issue(xb, lines, owner_of, b0, total2, lane, line2, par2);
-                    ext_process<INCL>(xb, result_of, rows, rs, f, b0, lane, te, tb);
+                    ext_process<INCL>(xb, result_of, rows, rs, f, b0, total2, lane, te, tb);
                 }
                 wave_lds_sync();
                 if (need2) {
