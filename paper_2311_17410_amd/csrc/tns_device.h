@@ -79,6 +79,34 @@ constexpr int kGatherChunk = 10;      // gather iterations whose loads are issue
 template <typename pos_t> struct index_of { using type = uint64_t; };
 template <> struct index_of<int32_t> { using type = uint32_t; };
 
+// slot_word as a position entry: where entries are 32 bits wide every slot index is below 2^30, and the division by
+// the slots per line is one 32-bit multiplication instead of a 64-bit one.
+template <typename pos_t>
+__device__ __forceinline__ pos_t slot_pos(int64_t s) {
+    if (sizeof(pos_t) == 8) return (pos_t)slot_word(s);
+    const uint32_t u = (uint32_t)s, line = u / (uint32_t)kSlotsPerLine;
+    return (pos_t)(line * 32u + (u - line * (uint32_t)kSlotsPerLine) * 3u);
+}
+template <typename pos_t>
+__device__ __forceinline__ float time_at(const uint32_t* __restrict__ edges, int64_t slot) {      // Edge::ts is the first word
+    return __uint_as_float(edges[(typename index_of<pos_t>::type)slot_pos<pos_t>(slot)]);
+}
+
+// Number of leading items of [lo, lo + n) for which qual holds (they come first), by one lane with three reads in
+// flight: half as many dependent round trips as a binary search.  Stops once at most `rest` items are undecided: lo
+// is then moved past the decided ones and n is what is left.
+template <class Qual>
+__device__ __forceinline__ void narrow4(int32_t& lo, int32_t& n, int32_t rest, const Qual& qual) {
+    while (n > rest) {
+        const int32_t i1 = n >> 2, i2 = n >> 1, i3 = (int32_t)((3 * (int64_t)n) >> 2);
+        const bool b1 = qual(lo + i1), b2 = qual(lo + i2), b3 = qual(lo + i3);
+        const int32_t skip = b3 ? i3 + 1 : (b2 ? i2 + 1 : (b1 ? i1 + 1 : 0));
+        const int32_t end = !b1 ? i1 : (!b2 ? i2 : (!b3 ? i3 : n));
+        lo += skip;
+        n = end - skip;
+    }
+}
+
 // State of one lane's walk over the blocks of its target node, newest block first
 // (Algorithm 1).  `t` numbers the blocks in visiting order.
 template <int POLICY, bool INCL, typename pos_t>
@@ -105,7 +133,7 @@ struct Walk {
         int32_t lo = 0, hi = n;
         while (lo < hi) {
             const int32_t mid = lo + ((hi - lo) >> 1);
-            const float t = __uint_as_float(edges[slot_word(off + mid)]);   // Edge::ts is the first word
+            const float t = time_at<pos_t>(edges, off + mid);
             ++n_probes;
             const bool ge = STRICT ? (t > x) : (t >= x);
             if (ge) hi = mid; else lo = mid + 1;
@@ -129,7 +157,7 @@ struct Walk {
             int32_t lo = 0;
             while (hi - lo > group) {
                 const int32_t mid = lo + ((hi - lo) >> 1);
-                const float tm = __uint_as_float(edges[slot_word(off + mid)]);
+                const float tm = time_at<pos_t>(edges, off + mid);
                 ++n_probes;
                 const bool ge = INCL ? (tm > te) : (tm >= te);
                 if (ge) hi = mid; else lo = mid + 1;
@@ -158,7 +186,7 @@ struct Walk {
                 const int32_t id = (int32_t)edges[slot_word(off + i) + 2];
                 ++n_probes;
                 if (id < 0) continue;
-                if (k < f) s_pos[k++] = (pos_t)slot_word(off + i);
+                if (k < f) s_pos[k++] = slot_pos<pos_t>(off + i);
                 ++cnt;
                 if (POLICY == 0 && k >= f) break;
             }
@@ -169,7 +197,7 @@ struct Walk {
             }
         } else if (cnt > 0) {
             const int32_t take = min(f - k, cnt);
-            for (int32_t j = 0; j < take; ++j) s_pos[k + j] = (pos_t)slot_word(off + hi - 1 - j);
+            for (int32_t j = 0; j < take; ++j) s_pos[k + j] = slot_pos<pos_t>(off + hi - 1 - j);
             k += take > 0 ? take : 0;
             if (POLICY == 1) {
                 if (t_first < 0) { t_first = t; hi_first = hi; }
@@ -205,7 +233,7 @@ struct Walk {
                 if ((int32_t)edges[slot_word(off + i) + 2] < 0) continue;
                 for (int32_t j = 0; j < f; ++j) {
                     const int64_t sv = (int64_t)s_pos[j];
-                    if (sv < 0 && -(sv + 1) - cum == cnt) s_pos[j] = (pos_t)slot_word(off + i);
+                    if (sv < 0 && -(sv + 1) - cum == cnt) s_pos[j] = slot_pos<pos_t>(off + i);
                 }
                 ++cnt;
             }
@@ -214,7 +242,7 @@ struct Walk {
                 const int64_t sv = (int64_t)s_pos[j];
                 if (sv < 0) {
                     const int64_t rr = -(sv + 1) - cum;
-                    if (rr < cnt) s_pos[j] = (pos_t)slot_word(off + hi - 1 - rr);
+                    if (rr < cnt) s_pos[j] = slot_pos<pos_t>(off + hi - 1 - rr);
                 }
             }
         }

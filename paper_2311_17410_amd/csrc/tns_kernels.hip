@@ -163,6 +163,47 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
 #pragma unroll
         for (int j = 0; j < kInlineBlocks; ++j) L[j] = line[1 + j];
     }
+    auto before_end = [&](float t) { return INCL ? t <= w.te : t < w.te; };
+    // inline list without deleted edges: candidates per block (newest block first), the blocks that contain the window's
+    // end and start, and what is left of the searches in them
+    bool flat = false;
+    int32_t cnt[kInlineBlocks];
+    int32_t end_block = -1, cut_new = 0, start_block = -1, b_lo = 0, b_n = 0;
+    int64_t b_off = 0;
+    // Candidates of an inline list once b_lo, the edges of start_block before the window's start, is known.  `inside`:
+    // edges of end_block before the window's end (recent policy: 0, that block is dealt with after its search).
+    auto count_flat = [&](int32_t inside) {
+        int32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < kInlineBlocks; ++j) {
+            if (j == end_block) {
+                cut_new = cnt[j] - inside;
+                cnt[j] = inside;
+            }
+            if (j == start_block) cnt[j] = max(cnt[j] - b_lo, 0);
+            c += cnt[j];
+        }
+        return c;
+    };
+    // Slots 0 .. k-1 from the candidates counted, every slot finding its block among the register counts.
+    auto fill_flat = [&](int32_t c, int32_t k) {
+#pragma unroll 1
+        for (int32_t i = 0; i < k; ++i) {
+            int32_t rr = i;               // from the newest candidate
+            if (POLICY == 1 && c > f) rr = c - 1 - (int32_t)pick_rank(p.seed, p.qid_base + q, f, i, (uint64_t)c);
+            BlockRec r = {};
+            int32_t back = -1;            // slots between the picked edge and the end of its block
+#pragma unroll
+            for (int j = 0; j < kInlineBlocks; ++j) {
+                if (back < 0 && rr < cnt[j]) {
+                    back = rr + (j == end_block ? cut_new : 0);
+                    r.off_lo = L[j].z; r.size_hi = L[j].w;
+                }
+                rr -= cnt[j];
+            }
+            w.s_pos[i] = slot_pos<pos_t>(rec_off(r) + rec_size(r) - 1 - back);
+        }
+    };
     // uniform policy, long list without deleted edges: the run and the candidates [L, R) of the node's sequence
     int32_t long_nb = 0, long_L = 0, long_R = 0;
     uint32_t long_dir = 0;
@@ -170,54 +211,27 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
         {
             ++n_nodes;
             const int32_t nb = (hd.w & 1) ? 0 : (int32_t)hd.x;      // deleted node: no blocks
-            if (POLICY == 1 && !COUNT && nb > 0 && nb <= kInlineBlocks && !(hd.w & 2)) {
-                // Uniform policy on an inline list without deleted edges.  At most one block contains the window end
-                // and at most one its start: their searches are written once, not per block.  The candidates of every
-                // block are then counted in registers and every slot finds its block there (2^22 edges and queries of uniform
-                // ids, fan-out 10: 485 -> 449 us per call).
-                auto before = [&](float t) { return INCL ? t <= w.te : t < w.te; };      // inside the window's end
-                int32_t cnt[kInlineBlocks], hi_size = 0, lo_size = 0;
-                int64_t hi_off = 0, lo_off = 0;
+            if (!COUNT && (POLICY == 1 || gshift >= 0) && nb > 0 && nb <= kInlineBlocks && !(hd.w & 2)) {
+                // Inline list without deleted edges.  At most one block contains the window end and at most one its
+                // start; the others count as a whole or not at all.  Recent policy: the two searches are left to the
+                // wave, narrowed to kCoopGroup slots each.  One search each instead of one per block of the unrolled walk:
+                // 256 graphs of 2^16 edges in one call, windowed, 1.98 -> 1.75 ms; 2^20 queries over uniform ids 116 -> 109 us.
+                flat = true;
 #pragma unroll
                 for (int j = 0; j < kInlineBlocks; ++j) {
                     const BlockRec r = as_rec(L[j]);
-                    const bool in = j < nb && before(r.t_min) && !(w.tb > r.t_max);
+                    const bool in = j < nb && before_end(r.t_min) && !(w.tb > r.t_max);
                     cnt[j] = in ? rec_size(r) : 0;
-                    if (in && !before(r.t_max)) { hi_off = rec_off(r); hi_size = rec_size(r); }
-                    if (in && w.tb > r.t_min) { lo_off = rec_off(r); lo_size = rec_size(r); }
+                    if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_n = rec_size(r); end_block = j; }
+                    if (in && w.tb > r.t_min) { b_off = rec_off(r); b_n = rec_size(r); start_block = j; }
                 }
-                const int32_t cut_new = hi_size > 0 ? hi_size - w.template first_not_before<INCL>(hi_off, hi_size, w.te) : 0;
-                const int32_t cut_old = lo_size > 0 ? w.template first_not_before<false>(lo_off, lo_size, w.tb) : 0;
-                int32_t c = 0;
-#pragma unroll
-                for (int j = 0; j < kInlineBlocks; ++j) {
-                    const BlockRec r = as_rec(L[j]);
-                    if (cnt[j] > 0) {
-                        if (!before(r.t_max)) cnt[j] -= cut_new;
-                        if (w.tb > r.t_min) cnt[j] -= cut_old;
-                        cnt[j] = max(cnt[j], 0);
-                    }
-                    c += cnt[j];
-                }
-                w.c = c;
-                w.k = min(c, f);
-                for (int32_t i = 0; i < w.k; ++i) {
-                    int32_t rr = c <= f ? i : c - 1 - (int32_t)pick_rank(p.seed, p.qid_base + q, f, i, (uint64_t)c);   // from the newest
-                    uint32_t off_lo = 0, size_hi = 0;
-                    int32_t back = -1;         // slots between the picked edge and the end of its block's candidates
-                    bool cut = false;
-#pragma unroll
-                    for (int j = 0; j < kInlineBlocks; ++j) {
-                        if (back < 0 && rr < cnt[j]) {
-                            back = rr;
-                            off_lo = L[j].z; size_hi = L[j].w;
-                            cut = !before(__uint_as_float(L[j].y));
-                        }
-                        rr -= cnt[j];
-                    }
-                    BlockRec r;
-                    r.off_lo = off_lo; r.size_hi = size_hi;
-                    w.s_pos[i] = (pos_t)slot_word(rec_off(r) + rec_size(r) - (cut ? cut_new : 0) - 1 - back);
+                const int32_t rest = POLICY == 1 ? 0 : kCoopGroup;
+                narrow4(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+                narrow4(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                if (POLICY == 1) {
+                    const int32_t c = count_flat(w.d_lo);
+                    w.k = min(c, f);
+                    fill_flat(c, w.k);
                 }
             } else if (nb > 0 && nb <= kInlineBlocks) {
                 bool go = true;
@@ -245,19 +259,32 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
                     // index in the sequence of the first edge with ts >= x (STRICT: ts > x)
                     auto first_at = [&](float x, auto strict) -> int64_t {
                         constexpr bool STRICT = decltype(strict)::value;
-                        int32_t lo = 0, hi = nb;          // first block whose newest edge is not before x
-                        while (lo < hi) {
-                            const int32_t mid = lo + ((hi - lo) >> 1);
-                            const float tm = d[mid].t_max;
-                            ++w.n_blocks;
-                            if (STRICT ? (tm > x) : (tm >= x)) hi = mid; else lo = mid + 1;
+                        auto before = [&](float t) { return STRICT ? t <= x : t < x; };
+                        int32_t lo = 0;                   // first block whose newest edge is not before x
+                        if (!FUSED) {
+                            int32_t hi = nb;
+                            while (lo < hi) {
+                                const int32_t mid = lo + ((hi - lo) >> 1);
+                                ++w.n_blocks;
+                                if (before(d[mid].t_max)) lo = mid + 1; else hi = mid;
+                            }
+                        } else {
+                            int32_t n = nb;
+                            narrow4(lo, n, 0, [&](int32_t i) { return before(d[i].t_max); });
                         }
                         if (lo == nb) return (int64_t)cum[nb - 1] + rec_size(d[nb - 1]);
                         const BlockRec r = d[lo];
                         ++w.n_blocks;
                         int32_t pos = 0;
-                        if (!(STRICT ? (r.t_min > x) : (r.t_min >= x)))
-                            pos = w.template first_not_before<STRICT>(rec_off(r), rec_size(r), x);
+                        if (before(r.t_min)) {
+                            const int64_t off = rec_off(r);
+                            if (!FUSED) {
+                                pos = w.template first_not_before<STRICT>(off, rec_size(r), x);
+                            } else {
+                                int32_t n = rec_size(r) - 1;          // the newest edge is not before x
+                                narrow4(pos, n, 0, [&](int32_t i) { return before(time_at<pos_t>(p.edges, off + i)); });
+                            }
+                        }
                         return (int64_t)cum[lo] + pos;
                     };
                     const int64_t R = first_at(w.te, std::integral_constant<bool, INCL>{});
@@ -282,12 +309,17 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
                     const BlockRec* __restrict__ d = p.dir + d0;
                     // newest block that starts before the window end (binary search instead of
                     // stepping through the newer blocks one by one)
-                    int32_t lo = 0, hi = nb;
-                    while (lo < hi) {
-                        const int32_t mid = lo + ((hi - lo) >> 1);
-                        const float tm = d[mid].t_min;
-                        ++w.n_blocks;
-                        if (INCL ? (tm > w.te) : (tm >= w.te)) hi = mid; else lo = mid + 1;
+                    int32_t lo = 0;
+                    if (!FUSED) {
+                        int32_t hi = nb;
+                        while (lo < hi) {
+                            const int32_t mid = lo + ((hi - lo) >> 1);
+                            ++w.n_blocks;
+                            if (before_end(d[mid].t_min)) lo = mid + 1; else hi = mid;
+                        }
+                    } else {
+                        int32_t n = nb;
+                        narrow4(lo, n, 0, [&](int32_t i) { return before_end(d[i].t_min); });
                     }
                     const int32_t j0 = lo - 1;
                     bool go = true;
@@ -304,7 +336,9 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
     // Uniform policy, picks on long lists: one (query, slot) per lane, kResolve of them side by side, each a binary
     // search over the run's prefix counts.  Neighbouring lanes search the same run, so an instruction touches a dozen
     // lines instead of 64, and the dependent reads of a query's picks overlap instead of following one another
-    // (2^23 edges with Zipf(1.1) ids, 2^23 queries, fan-out 10: 2.26 -> 1.92 ms per call).
+    // (2^23 edges with Zipf(1.1) ids, 2^23 queries, fan-out 10: 2.26 -> 1.92 ms per call).  In the fused kernel, where
+    // few waves are resident, the searches over directory runs and their blocks keep three reads in flight and make half
+    // the round trips (1.92 -> 1.85 ms); without the scan the plain binary searches are faster (1.53 against 1.59).
     if (POLICY == 1 && !COUNT && __ballot(long_nb > 0)) {
         constexpr int kResolve = 5;
         pos_t* const rows = reinterpret_cast<pos_t*>(my_lds);
@@ -331,7 +365,7 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
                 }
             }
             // newest block that starts at or before g: it is among the n blocks from lo on
-            while (__ballot(any)) {
+            while (!FUSED && __ballot(any)) {
                 any = false;
                 uint32_t v[kResolve];
 #pragma unroll
@@ -350,6 +384,30 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
                     any = any || n[i] > 1;
                 }
             }
+            while (FUSED && __ballot(any)) {      // three reads per search in flight
+                any = false;
+                uint32_t v1[kResolve], v2[kResolve], v3[kResolve];
+#pragma unroll
+                for (int i = 0; i < kResolve; ++i) {
+                    v1[i] = v2[i] = v3[i] = 0;
+                    if (n[i] > 1) {
+                        const uint32_t* __restrict__ run = p.dir_cum + ((int64_t)line[i] * kDirAlign + lo[i]);
+                        v1[i] = run[(n[i] + 3) >> 2]; v2[i] = run[n[i] >> 1]; v3[i] = run[(3 * (int64_t)n[i]) >> 2];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < kResolve; ++i) {
+                    if (n[i] > 1) {
+                        const int32_t i1 = (n[i] + 3) >> 2, i2 = n[i] >> 1, i3 = (int32_t)((3 * (int64_t)n[i]) >> 2);
+                        const bool u1 = (int32_t)v1[i] <= g[i], u2 = (int32_t)v2[i] <= g[i], u3 = (int32_t)v3[i] <= g[i];
+                        const int32_t from = u3 ? i3 : (u2 ? i2 : (u1 ? i1 : 0));
+                        const int32_t to = !u1 ? i1 : (!u2 ? i2 : (!u3 ? i3 : n[i]));
+                        lo[i] += from;
+                        n[i] = max(to - from, 1);
+                    }
+                    any = any || n[i] > 1;
+                }
+            }
             BlockRec r[kResolve];
             uint32_t cb[kResolve];
 #pragma unroll
@@ -362,55 +420,71 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
             }
 #pragma unroll
             for (int i = 0; i < kResolve; ++i)
-                if (n[i] > 0) rows[dst[i]] = (pos_t)slot_word(rec_off(r[i]) + (g[i] - (int32_t)cb[i]));
+                if (n[i] > 0) rows[dst[i]] = slot_pos<pos_t>(rec_off(r[i]) + (g[i] - (int32_t)cb[i]));
         }
     }
     // Recent policy, stage 1 of the cooperative part: finish the searches the lanes left open.
     // A group of 16 lanes serves one query: lane j of the group reads the timestamp of slot j of
     // the query's search window; the number of qualifying slots comes from a ballot.  All loads are
-    // issued before the first result is used, so the wave pays the memory latency once.
+    // issued before the first result is used, so the wave pays the memory latency once (twice with window starts).
     int32_t h = 0;               // edges of the searched block that lie before the window end
     if (POLICY == 0 && gshift >= 0) {
         constexpr int G = kCoopGroup, groups = kWave / G;
         unsigned char* extra = my_lds + (size_t)kWave * stride * sizeof(pos_t);
         // per query: window start (40-bit slot index) with the window size in the upper bits,
-        // the window end time, and the result
+        // the time searched for, and the result
         uint2* s_q = reinterpret_cast<uint2*>(extra);
-        float* s_te = reinterpret_cast<float*>(extra + (size_t)kWave * sizeof(uint2));
+        float* s_t = reinterpret_cast<float*>(extra + (size_t)kWave * sizeof(uint2));
         int32_t* s_h = reinterpret_cast<int32_t*>(extra + (size_t)kWave * (sizeof(uint2) + sizeof(float)));
-        const int64_t win0 = w.d_off + w.d_lo;
-        s_q[lane] = make_uint2((uint32_t)(win0 & 0xffffffffll), ((uint32_t)(win0 >> 32) & 0xffu) | ((uint32_t)w.d_n << 8));
-        s_te[lane] = w.te;
-        wave_lds_sync();
         const int g = lane / G, j = lane % G;
-        float tj[G];
+        auto describe = [&](int64_t slot0, int32_t n, float t) {
+            s_q[lane] = make_uint2((uint32_t)(slot0 & 0xffffffffll), ((uint32_t)(slot0 >> 32) & 0xffu) | ((uint32_t)n << 8));
+            s_t[lane] = t;
+            wave_lds_sync();
+        };
+        // slots of every query's window that lie before the time searched for
+        auto count_before = [&](auto closed) {
+            float t[G];
 #pragma unroll
-        for (int it = 0; it < G; ++it) {
-            const uint2 d = s_q[it * groups + g];
-            tj[it] = 0.0f;
-            if (j < (int32_t)(d.y >> 8)) {
-                const auto w = (typename index_of<pos_t>::type)slot_word((((int64_t)(d.y & 0xffu)) << 32 | d.x) + j);
-                tj[it] = __uint_as_float(p.edges[w]);
+            for (int it = 0; it < G; ++it) {
+                const uint2 d = s_q[it * groups + g];
+                t[it] = 0.0f;
+                if (j < (int32_t)(d.y >> 8)) t[it] = time_at<pos_t>(p.edges, (((int64_t)(d.y & 0xffu)) << 32 | d.x) + j);
             }
-        }
 #pragma unroll
-        for (int it = 0; it < G; ++it) {
-            const int32_t n = (int32_t)(s_q[it * groups + g].y >> 8);
-            const float teq = s_te[it * groups + g];
-            const bool qual = j < n && (INCL ? (tj[it] <= teq) : (tj[it] < teq));
-            const uint64_t m = __ballot(qual);
-            if (j == 0) s_h[it * groups + g] = __popcll((m >> (g * G)) & ((1ull << G) - 1));
+            for (int it = 0; it < G; ++it) {
+                const int32_t n = (int32_t)(s_q[it * groups + g].y >> 8);
+                const float x = s_t[it * groups + g];
+                const uint64_t m = __ballot(j < n && (decltype(closed)::value ? t[it] <= x : t[it] < x));
+                if (j == 0) s_h[it * groups + g] = __popcll((m >> (g * G)) & ((1ull << G) - 1));
+            }
+            wave_lds_sync();
+            return s_h[lane];
+        };
+        if (__ballot(b_n > 0)) {
+            describe(b_off + b_lo, b_n, w.tb);
+            b_lo += count_before(std::false_type{});
+            wave_lds_sync();
         }
-        wave_lds_sync();
-        if (w.d_off >= 0) h = w.d_lo + s_h[lane];
+        if (flat) {
+            // the blocks older than the one with the window's end; that one's edges are put in front below
+            const int32_t c = count_flat(0);
+            w.k = min(c, f);
+            fill_flat(c, w.k);
+        }
+        describe(w.d_off + w.d_lo, w.d_n, w.te);
+        const int32_t found = count_before(std::integral_constant<bool, INCL>{});
+        if (w.d_off >= 0) h = w.d_lo + found;
     }
-    const int32_t k = POLICY == 0 ? min(f, h + w.k) : w.k;
-    if (POLICY == 0 && h > 0) {
-        // The first min(h, f) slots come from the block whose search the wave finished (newest
+    // candidates of that block: those before the window's start, where it lies in the same block, do not count
+    const int32_t h_cnt = flat && start_block == end_block ? max(h - b_lo, 0) : h;
+    const int32_t k = POLICY == 0 ? min(f, h_cnt + w.k) : w.k;
+    if (POLICY == 0 && h_cnt > 0) {
+        // The first min(h_cnt, f) slots come from the block whose search the wave finished (newest
         // first); the positions recorded from older blocks move up behind them.
-        const int32_t hh = min(h, f);
+        const int32_t hh = min(h_cnt, f);
         for (int32_t j = k - 1; j >= hh; --j) w.s_pos[j] = w.s_pos[j - hh];
-        for (int32_t j = 0; j < hh; ++j) w.s_pos[j] = (pos_t)slot_word(w.d_off + h - 1 - j);
+        for (int32_t j = 0; j < hh; ++j) w.s_pos[j] = slot_pos<pos_t>(w.d_off + h - 1 - j);
     }
     if (COUNT) {
         // totals of what this launch reads: node entries, block records, timestamp probes, edges

@@ -498,8 +498,7 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
             const int64_t w0 = shfl64(win0, src);
             tj[it] = 0.0f;
             if (j < __shfl(my_n, src, kWave)) {
-                const auto wi = (typename index_of<pos_t>::type)slot_word(w0 + j);
-                tj[it] = __uint_as_float(lines[wi]);
+                tj[it] = time_at<pos_t>(lines, w0 + j);
             }
         }
 #pragma unroll
@@ -520,7 +519,7 @@ __global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArg
         if (POLICY == 0 && h > 0) {
             const int32_t hh = min(h, f);
             for (int32_t j = k - 1; j >= hh; --j) wk.s_pos[j] = wk.s_pos[j - hh];
-            for (int32_t j = 0; j < hh; ++j) wk.s_pos[j] = (pos_t)slot_word(wk.d_off + h - 1 - j);
+            for (int32_t j = 0; j < hh; ++j) wk.s_pos[j] = slot_pos<pos_t>(wk.d_off + h - 1 - j);
         }
         n_blocks += wk.n_blocks;
         n_probes += wk.n_probes;
