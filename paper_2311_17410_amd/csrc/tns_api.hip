@@ -374,7 +374,7 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     a.used_lines = plan->d_edges.used;
     a.cap_lines = plan->d_edges.cap;
     a.used_dir = plan->d_dir.used;
-    a.cap_dir = plan->d_dir.cap;
+    a.cap_dir = std::min(plan->d_dir.cap, plan->d_dir_cum.cap);
     a.tau = plan->cfg.block_threshold;
     a.sizing = plan->cfg.sizing;
     a.workspace = ds.ws.ptr;
@@ -390,6 +390,9 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     }
     hipError_t e = fast ? tns::ingest_plan_fast(a, stream) : tns::ingest_plan(a, stream);
     if (e != hipSuccess) return fail_hip(e, "launching the ingestion planning kernels");
+    // The apply phase is queued behind the plan at once: the device need not wait for this thread to see the plan (some
+    // 16 us), and the kernel does nothing unless the batch can be applied as it is, which is decided again below.
+    if (a.host_status && (e = tns::ingest_apply(a, 0, true, stream)) != hipSuccess) return fail_hip(e, "launching the ingestion kernels");
     tns::IngestStatus st;
     bool polled = false;
     if (a.host_status) {
@@ -400,7 +403,12 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
         const auto t0 = std::chrono::steady_clock::now();
         int spins = 0;
         while (*seq_word != a.seq) {
-            if ((++spins & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
+            if ((++spins & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
+                // the stream was busy: once its work is done the record is here (the device's own copy is not read
+                // then, the apply phase has made it ready for the next batch)
+                if ((e = hipStreamSynchronize(stream)) != hipSuccess) return fail_hip(e, "waiting for the ingestion plan");
+                break;
+            }
         }
         if (*seq_word == a.seq) {
             std::atomic_thread_fence(std::memory_order_acquire);
@@ -432,6 +440,7 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     }
     if (st.num_segments < 1 || st.num_segments > m || st.total_lines < 0 || st.total_dir < 0)
         return fail(TNS_EHIP, "inconsistent plan from the ingestion kernels");
+    const bool applied = fast && polled && tns::ingest_may_apply(st, a);       // by the kernel queued behind the plan
     const int64_t lines_after = plan->d_edges.used + st.total_lines;
     const int64_t dir_after = plan->d_dir.used + st.total_dir;
     if (lines_after > tns::kMaxEdgeOffset / tns::kSlotsPerLine) return fail(TNS_ESIZE, "edge array would exceed 2^39 slots");
@@ -445,9 +454,9 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     a.cap_lines = plan->d_edges.cap;
     a.cap_dir = std::min(plan->d_dir.cap, plan->d_dir_cum.cap);
 
-    // The apply kernels are not waited for: the store changes in stream order, and an internal error they might
+    // The apply phase is not waited for: the store changes in stream order, and an internal error it might
     // raise (a pool too small, which the sizes above rule out) is reported by the next read of the status record.
-    e = tns::ingest_apply(a, st.num_segments, fast, stream);
+    if (!applied) e = tns::ingest_apply(a, st.num_segments, fast, stream);
     if (e != hipSuccess) return fail_hip(e, "launching the ingestion kernels");
     plan->d_edges.used = lines_after;
     plan->d_dir.used = dir_after;

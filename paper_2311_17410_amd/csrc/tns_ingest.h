@@ -65,7 +65,18 @@ struct IngestArgs {
     IngestStatus* host_status;
     unsigned long long* host_seq;
     unsigned long long seq;
+    int64_t* go;          // set by ingest_plan_fast: number of segments for an apply phase queued behind the plan, 0: not to run
 };
+
+// Whether a planned batch can be applied as it is: no error, in time order, room in the pools.  The plan's last thread
+// and the host decide by the same rule.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline bool ingest_may_apply(const IngestStatus& st, const IngestArgs& a) {
+    return st.err_word == ~0ull && !st.unsorted && !st.internal && st.num_segments >= 1 && st.num_segments <= a.m && st.total_lines >= 0 &&
+           st.total_dir >= 0 && st.total_lines <= a.cap_lines - a.used_lines && st.total_dir <= a.cap_dir - a.used_dir;
+}
 
 constexpr int64_t kMaxDeviceBatch = kMaxBlockEdges;   // one new block always takes the rest of a node's share
 
@@ -75,13 +86,14 @@ size_t ingest_workspace_bytes(int64_t m);
 // against what is stored, and compute what every node needs (edge lines, directory records).
 // Changes nothing in the store.  The host then reads *status, makes room, and runs phase 2.
 hipError_t ingest_plan(const IngestArgs& a, hipStream_t stream);
-// The same phase in five launches for batches of stream size (at most 2^21 edges, at most 2^24 nodes) that
+// The same phase in five launches (one for up to 4096 edges) for batches of stream size (at most 2^21 edges, at most 2^24 nodes) that
 // arrive in time order: it sorts by source only and reports status->unsorted when the batch was not in time
 // order, in which case the caller runs ingest_plan instead.  Expects *status reset (ingest_apply leaves it so).
 bool ingest_fast_ok(int64_t m, int64_t num_nodes);
 hipError_t ingest_plan_fast(const IngestArgs& a, hipStream_t stream);
-// Phase 2: update node entries and block records, write the edges (num_segments as read from *status; `fast`:
-// the plan came from ingest_plan_fast).  Its first kernel resets *status for the next batch, except the sticky
+// Phase 2: update node entries and block records, write the edges (num_segments as read from *status, or 0: as left by
+// ingest_plan_fast with a host record, queued right behind it and without effect unless ingest_may_apply; `fast`:
+// the plan came from ingest_plan_fast), in one launch.  It resets *status for the next batch, except the sticky
 // `internal` word, which the next read of *status reports.
 hipError_t ingest_apply(const IngestArgs& a, int64_t num_segments, bool fast, hipStream_t stream);
 

@@ -53,3 +53,40 @@ def test_pieces_equal_whole(B, oracle_lib, policy, fanout, incl, tau, ties):
             lo = hi
     adj.close()
     plan.close()
+
+
+@pytest.mark.parametrize("batch", [2, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("nodes", [1, 700, 1 << 17])
+def test_ingestion_batches_around_the_small_plan(B, oracle_lib, batch, nodes):
+    import torch
+    rng = np.random.default_rng(batch + nodes)
+    n = 4 * batch + 1
+    src = rng.integers(0, nodes, n, dtype=np.int32)
+    src[rng.random(n) < 0.3] = nodes - 1
+    dst = rng.integers(0, nodes, n, dtype=np.int32)
+    ts = np.sort(rng.integers(0, n // 2, n)).astype(np.float32)
+    eid = rng.permutation(n).astype(np.int32)
+    ts[2 * batch], ts[3 * batch - 1] = ts[3 * batch - 1], ts[2 * batch]           # the third batch is not in time order
+    plan = B.Plan(nodes, 10, block_threshold=48, flags=B.TNS_FLAG_DEVICE_INGEST)
+    bs = oracle_lib.BlockStore(nodes, 48, 0)
+    d = [torch.from_numpy(a).cuda() for a in (src, dst, ts, eid)]
+    bounds = list(range(0, n, batch)) + [n]
+    for lo, hi in zip(bounds[:-1], bounds[1:]):
+        plan.add_edges_device(*(a[lo:hi] for a in d))
+    bs.add_stream(src, dst, ts, batch)
+    ref, got = bs.stats(), plan.stats()
+    for name in ("num_blocks", "wasted_slots", "max_list_len"):
+        assert got[name] == ref[name], name
+    st = W.Stream(nodes, src, dst, ts, batch)
+    targets, t_start, t_end = W.random_queries(5, st, 3000)
+    adj = oracle_lib.Adjacency(nodes, src, dst, ts, batch_rowptr=bounds)
+    want = adj.sample(targets, t_start, t_end, 10)
+    out = gpu_sample(plan, targets, t_start, t_end)
+    out["eid"] = np.where(out["eid"] >= 0, np.argsort(eid)[np.maximum(out["eid"], 0)], -1).astype(np.int32)   # back to stream positions
+    for name in ("count", "nbr", "eid", "ts"):
+        assert np.array_equal(out[name], getattr(want, name)), name
+    adj.close()
+    with pytest.raises(B.TnsError):                                # a rejected batch changes nothing
+        plan.add_edges_device(torch.full((batch,), nodes, dtype=torch.int32, device="cuda"), d[1][:batch], d[2][-1].repeat(batch))
+    assert plan.stats()["num_edges"] == n
+    plan.close()
