@@ -90,3 +90,46 @@ def test_ingestion_batches_around_the_small_plan(B, oracle_lib, batch, nodes):
         plan.add_edges_device(torch.full((batch,), nodes, dtype=torch.int32, device="cuda"), d[1][:batch], d[2][-1].repeat(batch))
     assert plan.stats()["num_edges"] == n
     plan.close()
+
+
+def test_stores_built_one_after_another_by_two_threads(B, oracle_lib):
+    # memory of a closed plan is kept for the next one: plans of two threads, each on a stream of its own, of changing
+    # sizes, must not see each other's (or an earlier plan's) data
+    import threading
+    import torch
+    rng = np.random.default_rng(8)
+    nodes, n = 2000, 40_000
+    src, dst = (rng.integers(0, nodes, n, dtype=np.int32) for _ in range(2))
+    ts = np.sort(rng.standard_normal(n)).astype(np.float32)
+    sizes = (n, 3000, 20_000, 500, n)
+    want = {}
+    for m in sizes:
+        adj = oracle_lib.Adjacency(nodes, src[:m], dst[:m], ts[:m])
+        want[m] = adj.sample(src[:m], None, ts[:m], 10)
+        adj.close()
+    errors = []
+
+    def work(shift):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                d = [torch.from_numpy(a).cuda() for a in (src, dst, ts)]
+                for i in range(10):
+                    m = sizes[(i + shift) % len(sizes)]
+                    plan = B.Plan(nodes, 10, flags=B.TNS_FLAG_DEVICE_INGEST)
+                    for lo in range(0, m, 2500):
+                        hi = min(lo + 2500, m)
+                        plan.add_edges_device(*(a[lo:hi] for a in d))
+                    out = plan.run(d[0][:m], None, d[2][:m])
+                    torch.cuda.current_stream().synchronize()
+                    for name in ("nbr", "eid", "ts"):
+                        assert np.array_equal(out[name].cpu().numpy().reshape(m, 10), getattr(want[m], name)), (i, m, name)
+                    plan.close()
+        except Exception as e:       # noqa: BLE001 -- reported by the test's own thread
+            errors.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
