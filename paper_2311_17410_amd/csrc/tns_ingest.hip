@@ -345,7 +345,7 @@ __device__ __forceinline__ void plan_segment(const IngestArgs& a, uint32_t v, ui
         else cap = max(rest, min((int64_t)nd.degree + take, (int64_t)a.tau));   // b_v = min(deg(v), tau)
         cap = min(cap, kMaxBlockEdges);
         P.cap = (int32_t)cap;
-        P.nbn = (int32_t)((rest + cap - 1) / cap);
+        P.nbn = (int32_t)(((uint32_t)rest + (uint32_t)cap - 1u) / (uint32_t)cap);       // both below 2^24
         if (cap < kSlotsPerLine && ax.slab_line) {
             P.k0 = min(P.nbn, (kSlotsPerLine - ax.slab_used) / (int32_t)cap);
             P.slab_slot = (int64_t)(ax.slab_line - 1) * kSlotsPerLine + ax.slab_used;
@@ -919,9 +919,10 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
 // The whole plan in one workgroup for batches of at most kSmallBatch edges (a mini-batch of a stream): such a batch
 // spends its time in the five dependent launches above.  Sort by (source, arrival) in LDS, segments, plans and the two
 // scans follow each other behind barriers; nothing is read back from memory in between, and the record goes to the host
-// from here.  A bitonic network of 2048 keys is 66 steps of one compare per thread; 2000 edges 31 us in all, against
+// from here.  A bitonic network of 2048 keys is 66 steps of one compare per thread; 2000 edges 30 us in all, against
 // 36 us in the five kernels and the gaps between them (64 batches of 2000 edges, each sampled, with the apply phase
-// queued behind the plan: 5.76 -> 4.25 ms).
+// queued behind the plan: 5.76 -> 3.82 ms, 0.3 of it by the memory kept between plans).  Keeping the keys in registers and
+// exchanging them by shuffles gave nothing.
 template <int ITEMS /* keys per thread */>
 __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val,
                                                      int64_t* __restrict__ head_excl, int32_t* __restrict__ seg_start,
@@ -931,7 +932,9 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
     __shared__ uint64_t s_key[N];
     __shared__ int32_t s_start[N + 1];
     __shared__ int64_t s_wave[kWaves];
+    __shared__ unsigned long long s_totals[2];
     const int t = threadIdx.x, m = (int)a.m;
+    if (t < 2) s_totals[t] = 0;
     int32_t touched = 0;
     // keys: (source, batch position), all different, so the order is that of a stable sort by source
 #pragma unroll
@@ -1007,39 +1010,35 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
         }
     }
     __syncthreads();
-    // plans; a thread owns ITEMS consecutive segments
-    int64_t lines[ITEMS], dirs[ITEMS], blocks = 0, slots = 0, my_lines = 0, my_dirs = 0, all_lines, all_dirs;
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int sgm = t * ITEMS + j;
-        int64_t b = 0, sl = 0;
-        lines[j] = dirs[j] = 0;
+    // plans, 1024 segments at a time (a loop, not unrolled: the program is fetched once from a cold instruction cache,
+    // and its length is what this kernel costs)
+    int64_t all_lines = 0, all_dirs = 0, blocks = 0, slots = 0;
+#pragma unroll 1
+    for (int64_t sgm = t; sgm - t < nseg; sgm += 1024) {
+        int64_t lines = 0, dirs = 0, b = 0, sl = 0, tot_lines, tot_dirs;
         if (sgm < nseg) {
             const int p0 = s_start[sgm];
             const uint64_t k0 = s_key[p0];
             SegPlan P{};
-            plan_segment(a, (uint32_t)(k0 >> 32), (uint32_t)k0, s_start[sgm + 1] - p0, P, lines[j], dirs[j], b, sl);
+            plan_segment(a, (uint32_t)(k0 >> 32), (uint32_t)k0, s_start[sgm + 1] - p0, P, lines, dirs, b, sl);
             plan[sgm] = P;
         }
         blocks += b;
         slots += sl;
-        my_lines += lines[j];
-        my_dirs += dirs[j];
-    }
-    int64_t line0 = block_exclusive_scan<kWaves>(my_lines, s_wave, all_lines);
-    int64_t dir0 = block_exclusive_scan<kWaves>(my_dirs, s_wave, all_dirs);
-    int64_t all_blocks, all_slots;
-    (void)block_exclusive_scan<kWaves>(blocks, s_wave, all_blocks);
-    (void)block_exclusive_scan<kWaves>(slots, s_wave, all_slots);
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int sgm = t * ITEMS + j;
+        const int64_t line0 = block_exclusive_scan<kWaves>(lines, s_wave, tot_lines);
+        const int64_t dir0 = block_exclusive_scan<kWaves>(dirs, s_wave, tot_dirs);
         if (sgm < nseg) {
-            lines_base[sgm] = line0;
-            dir_base[sgm] = dir0;
+            lines_base[sgm] = all_lines + line0;
+            dir_base[sgm] = all_dirs + dir0;
         }
-        line0 += lines[j];
-        dir0 += dirs[j];
+        all_lines += tot_lines;
+        all_dirs += tot_dirs;
+    }
+    blocks = wave_sum64(blocks);
+    slots = wave_sum64(slots);
+    if ((t & (kWave - 1)) == 0) {
+        atomicAdd(&s_totals[0], (unsigned long long)blocks);
+        atomicAdd(&s_totals[1], (unsigned long long)slots);
     }
     __syncthreads();                 // every thread's reports have been performed
     if (t == 0) {
@@ -1047,8 +1046,8 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
         st->num_segments = nseg;
         st->total_lines = all_lines;
         st->total_dir = all_dirs;
-        st->new_blocks = (unsigned long long)all_blocks;
-        st->new_slots = (unsigned long long)all_slots;
+        st->new_blocks = s_totals[0];
+        st->new_slots = s_totals[1];
         if (a.host_status) {
             __threadfence();
             hand_over(a);
