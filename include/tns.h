@@ -364,7 +364,9 @@ TNS_API int tns_hbm_probe_mix(int32_t nontemporal, void *d_dst, size_t write_byt
                               void *hip_stream);
 
 /* Release the plan (the dynamic graph object of section 5's interface), its host store and its device
-   memory.  NULL is allowed. */
+   memory, after the device's queued work is done.  NULL is allowed.  Up to 256 MiB of device memory per process are
+   kept for plans created next and given back once unused for two seconds, at the library's next release or request of
+   device memory, or when an allocation of the library fails. */
 TNS_API int tns_destroy(tns_plan *plan);
 
 /* Static description of a status code. */
