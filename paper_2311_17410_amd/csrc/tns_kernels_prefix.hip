@@ -176,8 +176,10 @@ __device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_ma
     wave_lds_sync();
 }
 
+// Uniform policy: workgroups of at most eight waves, three of them per compute unit (80 registers; at 85, with two of
+// them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459).
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
-__global__ void __launch_bounds__(1024) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_magic,
+__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_magic,
                                                                  const int32_t gshift, const uint32_t chunk,
                                                                  const uint32_t rows_bytes) {
     extern __shared__ __align__(16) unsigned char smem[];
