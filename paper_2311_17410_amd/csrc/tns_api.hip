@@ -754,7 +754,6 @@ static int fill_sample_args(tns_plan* plan, int64_t Q, const int32_t* d_targets,
     a.policy = plan->cfg.policy;
     a.inclusive_end = plan->cfg.inclusive_end;
     a.xcd_remap = (plan->cfg.flags & TNS_FLAG_NO_XCD_REMAP) ? 0 : 1;
-    a.no_deleted = plan->deleted_edges ? 0 : 1;
     a.first_ticket = (plan->cfg.flags & TNS_TEST_FLAG_LOST_TILE) ? 1 : 0;
     const int64_t edge_lines = plan->pstore ? plan->d_lines.used : plan->d_edges.used;
     a.wide_offsets = (edge_lines * 32 >= (int64_t(1) << 31) || (plan->cfg.flags & TNS_FLAG_WIDE_POSITIONS)) ? 1 : 0;   // word indices beyond int32

@@ -1,5 +1,5 @@
-// gfx950 sampling kernel for small batches (default layout, no deleted edges): Algorithm 1 of the paper (section 4.2), the padded write and the padding removal of section 5 fused in,
-// with sixteen lanes working on one query.
+// gfx950 sampling kernel for small batches (default layout): Algorithm 1 of the paper (section 4.2), the padded write and
+// the padding removal of section 5 fused in, with sixteen lanes working on one query.
 //
 // tns_sample_kernel gives every lane a query of its own, which keeps the most independent reads in flight once a
 // batch fills the chip.  A batch that does not fill it is bound by the length of one wave's program instead: with 64
@@ -15,6 +15,8 @@
 //   gather    lane j takes slot j: its rank (newest first, or its own pick), the block that holds it, the edge.
 //             Under the uniform policy the f picks of a query are resolved side by side instead of one after the
 //             other.
+//   deleted   a node whose flags say that edges of it are deleted has its candidates looked at, sixteen side by side.
+//             The flag is read here and not on the host: a captured call may be replayed after a deletion.
 // What bounds it is the chain of dependent reads (query, node, search, edge, look-back) and, as every workgroup takes
 // a ticket, 18 ns per tile.  Measured beside tns_sample_kernel, fan-out 10, in us per call: see the rule in launch_sample.
 #include <type_traits>
@@ -139,12 +141,16 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     BlockRec rec[CH];                   // lane b: record of the b-th oldest block
     int32_t cum[CH];                    // lane b: edges in the older blocks
     int32_t piv[CH];                    // long lists: lane b: edges in the blocks before the (b * piv_step)-th
-    bool any_long = false;
+    bool holes[CH];                     // some edges of the node are deleted
+    bool any_long = false, any_holes = false;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         int32_t nb = __shfl((int)piece[u].x, team0, kWave);
         dline[u] = (uint32_t)__shfl((int)piece[u].z, team0, kWave);
-        if (__shfl((int)piece[u].w, team0, kWave) & 1) nb = 0;                       // deleted node: no blocks
+        const int32_t flags = __shfl((int)piece[u].w, team0, kWave);
+        if (flags & 1) nb = 0;                                                       // deleted node: no blocks
+        holes[u] = (flags & 2) != 0;
+        any_holes = any_holes || holes[u];
         if (nb > kInlineBlocks && (int64_t)dline[u] * kDirAlign + nb > p.num_dir) nb = 0;
         nb_in[u] = nb > kInlineBlocks ? 0 : nb;
         nb_long[u] = nb - nb_in[u];
@@ -166,6 +172,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
+    any_holes = __ballot(any_holes) != 0;
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -220,11 +227,54 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     }
     if (__ballot(windowed)) first_at(tb, L, std::false_type{});
 
+#pragma unroll
+    for (int u = 0; u < CH; ++u) c[u] = max(R[u] - L[u], 0);
+
+    // ---- nodes with deleted edges: which candidates are there ------------------------------------
+    // Whether edge g of the node's sequence is there, for the lanes that ask; called by the whole wave.
+    auto present = [&](int u, int32_t g, bool ask) {
+        int32_t b = -1;
+#pragma unroll 1
+        for (int t = 0; t < kInlineBlocks; ++t) b += (t < nb_in[u] && __shfl(cum[u], team0 + t, kWave) <= g) ? 1 : 0;
+        const int src = team0 + max(b, 0);
+        BlockRec r;
+        r.off_lo = (uint32_t)__shfl((int)rec[u].off_lo, src, kWave);
+        r.size_hi = (uint32_t)__shfl((int)rec[u].size_hi, src, kWave);
+        int32_t before = __shfl(cum[u], src, kWave);
+        if (!ask) return false;
+        if (nb_long[u] > 0) {
+            const int64_t d0 = (int64_t)dline[u] * kDirAlign;
+            int32_t lo = 0, n = nb_long[u];
+            while (n > 1) {
+                const int32_t half = n >> 1;
+                const bool up = (int32_t)p.dir_cum[d0 + lo + half] <= g;
+                lo += up ? half : 0;
+                n = up ? n - half : half;
+            }
+            r = p.dir[d0 + lo];
+            before = (int32_t)p.dir_cum[d0 + lo];
+        }
+        return (int32_t)p.edges[slot_word(rec_off(r) + (g - before)) + 2] >= 0;      // the edge id word
+    };
+    if (any_holes) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            int32_t at = R[u], n = 0;           // newest first; the recent policy needs no more than f of them
+            bool go = holes[u] && c[u] > 0;
+            while (__ballot(go)) {
+                const int32_t g = at - 1 - j;
+                n += __popcll((__ballot(present(u, g, go && g >= L[u])) >> team0) & 0xffffull);
+                at -= kTeam;
+                go = go && at > L[u] && (POLICY == 1 || n < f);
+            }
+            if (holes[u]) c[u] = n;
+        }
+    }
+
     // ---- dense offsets inside the workgroup -----------------------------------------------------
     int32_t excl_in_wave[CH], wave_total = 0;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
-        c[u] = max(R[u] - L[u], 0);
         k[u] = min(c[u], f);
         const int32_t k0 = __shfl(k[u], 0, kWave), k1 = __shfl(k[u], 16, kWave), k2 = __shfl(k[u], 32, kWave), k3 = __shfl(k[u], 48, kWave);
         excl_in_wave[u] = wave_total + (lane >= 16 ? k0 : 0) + (lane >= 32 ? k1 : 0) + (lane >= 48 ? k2 : 0);
@@ -265,6 +315,27 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
             g[u] = R[u] - 1 - slot_no;                // newest first; so too when all candidates are taken
             if (POLICY == 1 && slot_no < k[u] && c[u] > f)
                 g[u] = L[u] + (int32_t)pick_rank(p.seed, p.qid_base + q0 + u * kTeamsPerWave, f, slot_no, (uint64_t)c[u]);
+            if (any_holes) {
+                // g so far counts the candidates that are there; its edge is the one with that many newer ones
+                const int32_t newer = POLICY == 1 && c[u] > f ? c[u] - 1 - (g[u] - L[u]) : slot_no;
+                int32_t at = R[u], n = 0;
+                bool go = holes[u] && slot_no < k[u];
+                while (true) {
+                    const uint64_t open = __ballot(go);
+                    if (!open) break;
+                    const int32_t i = at - 1 - j;
+                    uint32_t there = (uint32_t)(__ballot(present(u, i, ((open >> team0) & 0xffffull) != 0 && i >= L[u])) >> team0) & 0xffffu;
+                    const int32_t cnt = __popc(there);
+                    if (go && newer < n + cnt) {
+                        for (int32_t s = newer - n; s > 0; --s) there &= there - 1;
+                        g[u] = at - 1 - (__ffs((int)there) - 1);
+                        go = false;
+                    }
+                    n += cnt;
+                    at -= kTeam;
+                    go = go && at > L[u];
+                }
+            }
             // newest inline block that starts at or before g
             int32_t b = -1;
 #pragma unroll
