@@ -73,6 +73,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[kTileWaves];
     __shared__ int32_t s_arrived;
+    __shared__ int32_t s_seq[kTileWaves][CH][kTeamsPerWave][ROUNDS * kTeam];      // nodes with deleted edges: the slots' edges
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
@@ -139,18 +140,15 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     int32_t nb_in[CH], nb_long[CH];     // blocks in the node line / in the directory run (one of them is 0)
     uint32_t dline[CH];                 // start of the run in units of kDirAlign records
     BlockRec rec[CH];                   // lane b: record of the b-th oldest block
-    int32_t cum[CH];                    // lane b: edges in the older blocks
+    int32_t cum[CH];                    // lane b: edges in the older blocks; last lane of the team: the node's flags
     int32_t piv[CH];                    // long lists: lane b: edges in the blocks before the (b * piv_step)-th
-    bool holes[CH];                     // some edges of the node are deleted
-    bool any_long = false, any_holes = false;
+    bool any_long = false;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         int32_t nb = __shfl((int)piece[u].x, team0, kWave);
         dline[u] = (uint32_t)__shfl((int)piece[u].z, team0, kWave);
         const int32_t flags = __shfl((int)piece[u].w, team0, kWave);
         if (flags & 1) nb = 0;                                                       // deleted node: no blocks
-        holes[u] = (flags & 2) != 0;
-        any_holes = any_holes || holes[u];
         if (nb > kInlineBlocks && (int64_t)dline[u] * kDirAlign + nb > p.num_dir) nb = 0;
         nb_in[u] = nb > kInlineBlocks ? 0 : nb;
         nb_long[u] = nb - nb_in[u];
@@ -167,12 +165,11 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
             const int32_t w = __shfl_up(cum[u], d, kTeam);
             if (j >= d) cum[u] += w;
         }
-        cum[u] -= size;
+        cum[u] = j == kTeam - 1 ? flags : cum[u] - size;
         piv[u] = 0;
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
-    any_holes = __ballot(any_holes) != 0;
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -243,7 +240,9 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         int32_t before = __shfl(cum[u], src, kWave);
         if (!ask) return false;
         if (nb_long[u] > 0) {
-            const int64_t d0 = (int64_t)dline[u] * kDirAlign;
+            uint32_t run = dline[u];
+            asm volatile("" : "+v"(run));      // an address of its own: one shared with the searches would be kept in registers all along
+            const int64_t d0 = (int64_t)run * kDirAlign;
             int32_t lo = 0, n = nb_long[u];
             while (n > 1) {
                 const int32_t half = n >> 1;
@@ -256,19 +255,50 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         }
         return (int32_t)p.edges[slot_word(rec_off(r) + (g - before)) + 2] >= 0;      // the edge id word
     };
+    bool any_holes = false;             // of the wave's nodes
+#pragma unroll
+    for (int u = 0; u < CH; ++u) any_holes = any_holes || (j == kTeam - 1 && (cum[u] & 2));
+    any_holes = __ballot(any_holes) != 0;
     if (any_holes) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            int32_t at = R[u], n = 0;           // newest first; the recent policy needs no more than f of them
-            bool go = holes[u] && c[u] > 0;
+            const bool holes = __shfl(cum[u], team0 + kTeam - 1, kWave) & 2;
+            // how many of the candidates are there; the recent policy needs no more than f of them
+            int32_t at = R[u], n = 0;
+            bool go = holes && c[u] > 0;
             while (__ballot(go)) {
-                const int32_t g = at - 1 - j;
-                n += __popcll((__ballot(present(u, g, go && g >= L[u])) >> team0) & 0xffffull);
+                n += __popcll((__ballot(present(u, at - 1 - j, go && at - 1 - j >= L[u])) >> team0) & 0xffffull);
                 at -= kTeam;
                 go = go && at > L[u] && (POLICY == 1 || n < f);
             }
-            if (holes[u]) c[u] = n;
+            if (holes) c[u] = n;
+            // the slots' edges: each the one with a given number of newer ones that are there
+#pragma unroll 1
+            for (int32_t slot_no = j; slot_no < ROUNDS * kTeam; slot_no += kTeam) {
+                int32_t newer = slot_no, g = R[u] - 1 - slot_no;
+                go = holes && slot_no < min(c[u], f);
+                if (POLICY == 1 && go && c[u] > f)
+                    newer = c[u] - 1 - (int32_t)pick_rank(p.seed, p.qid_base + q0 + u * kTeamsPerWave, f, slot_no, (uint64_t)c[u]);
+                at = R[u];
+                n = 0;
+                while (true) {
+                    const uint64_t open = (__ballot(go) >> team0) & 0xffffull;
+                    if (!__ballot(open != 0)) break;
+                    uint32_t there = (uint32_t)(__ballot(present(u, at - 1 - j, open != 0 && at - 1 - j >= L[u])) >> team0) & 0xffffu;
+                    const int32_t cnt = __popc(there);
+                    if (go && newer < n + cnt) {
+                        for (int32_t s = newer - n; s > 0; --s) there &= there - 1;
+                        g = at - __ffs((int)there);
+                        go = false;
+                    }
+                    n += cnt;
+                    at -= kTeam;
+                    go = go && at > L[u];
+                }
+                s_seq[wave][u][lane >> 4][slot_no] = g;
+            }
         }
+        wave_lds_sync();
     }
 
     // ---- dense offsets inside the workgroup -----------------------------------------------------
@@ -315,27 +345,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
             g[u] = R[u] - 1 - slot_no;                // newest first; so too when all candidates are taken
             if (POLICY == 1 && slot_no < k[u] && c[u] > f)
                 g[u] = L[u] + (int32_t)pick_rank(p.seed, p.qid_base + q0 + u * kTeamsPerWave, f, slot_no, (uint64_t)c[u]);
-            if (any_holes) {
-                // g so far counts the candidates that are there; its edge is the one with that many newer ones
-                const int32_t newer = POLICY == 1 && c[u] > f ? c[u] - 1 - (g[u] - L[u]) : slot_no;
-                int32_t at = R[u], n = 0;
-                bool go = holes[u] && slot_no < k[u];
-                while (true) {
-                    const uint64_t open = __ballot(go);
-                    if (!open) break;
-                    const int32_t i = at - 1 - j;
-                    uint32_t there = (uint32_t)(__ballot(present(u, i, ((open >> team0) & 0xffffull) != 0 && i >= L[u])) >> team0) & 0xffffu;
-                    const int32_t cnt = __popc(there);
-                    if (go && newer < n + cnt) {
-                        for (int32_t s = newer - n; s > 0; --s) there &= there - 1;
-                        g[u] = at - 1 - (__ffs((int)there) - 1);
-                        go = false;
-                    }
-                    n += cnt;
-                    at -= kTeam;
-                    go = go && at > L[u];
-                }
-            }
+            if (any_holes && (__shfl(cum[u], team0 + kTeam - 1, kWave) & 2)) g[u] = s_seq[wave][u][lane >> 4][slot_no];
             // newest inline block that starts at or before g
             int32_t b = -1;
 #pragma unroll
