@@ -1,0 +1,98 @@
+"""The kernel with a query per lane serves batches above 2^16 queries (2^15 for small fan-outs): its parity at the edge of
+that rule, with 64-bit positions, over instances of uneven and no size, and its bounded wait."""
+import time
+
+import numpy as np
+import pytest
+
+from paper_2311_17410_amd import workloads as W
+from _harness import assert_same, build_plan, gpu_sample, oracle_sample
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2311_17410_amd import binding
+    binding.lib()
+    return binding
+
+
+def mixed_stream(seed, num_nodes, n, batch, ties):
+    """Nodes of every size: none, a few edges, inline lists, and hubs of long lists."""
+    rng = np.random.default_rng(seed)
+    src = (rng.zipf(1.3, n) % max(num_nodes - 3, 1)).astype(np.int32)
+    ts = np.sort(rng.integers(0, max(n // 10, 2), n) if ties else rng.standard_normal(n)).astype(np.float32)
+    return W.Stream(num_nodes, src, rng.integers(0, num_nodes, n, dtype=np.int32), ts, batch)
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("fanout,Q", [(5, 1 << 15), (5, (1 << 15) + 1), (7, (1 << 15) + 1), (8, 1 << 16), (8, (1 << 16) + 1)])
+def test_both_sides_of_the_rule(B, oracle_lib, policy, fanout, Q):
+    st = mixed_stream(1, 2000, 20_000, 900, ties=False)
+    wl = W.Workload("mixed", 0, [st], fanout=fanout, tau=48)
+    plan = build_plan(B, wl, policy, seed=3)
+    targets, t_start, t_end = W.random_queries(2, st, Q)
+    adjs = [oracle_lib.Adjacency(st.num_nodes, st.src, st.dst, st.ts)]
+    for tb in (None, t_start):
+        ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, policy, 0, 3, adjs=adjs)
+        assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, f"start={tb is not None}")
+    plan.close()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("fanout,tau,incl,ties", [(1, 48, 0, True), (3, 16, 1, True), (10, 5, 0, False), (10, 8192, 1, True),
+                                                  (16, 1, 0, True), (20, 48, 0, False), (64, 48, 1, True)])
+def test_large_batches_with_64_bit_positions(B, oracle_lib, wide, policy, fanout, tau, incl, ties):
+    st = mixed_stream(fanout + policy, 500, 12_000, 700, ties)
+    wl = W.Workload("mixed", 0, [st], fanout=fanout, tau=tau)
+    plan = build_plan(B, wl, policy, incl, seed=8, flags=B.TNS_FLAG_WIDE_POSITIONS if wide else 0)
+    targets, t_start, t_end = W.random_queries(44, st, (1 << 16) + 77)
+    adjs = [oracle_lib.Adjacency(st.num_nodes, st.src, st.dst, st.ts)]
+    for tb in (t_start, None):
+        ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, policy, incl, 8, adjs=adjs)
+        assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, f"start={tb is not None}")
+        got = gpu_sample(plan, targets, tb, t_end, compact=False)
+        assert_same(got, ref, None, f"without the padding removal, start={tb is not None}")
+    plan.close()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("policy", [0, 1])
+def test_uneven_instances(B, oracle_lib, wide, policy, layout):
+    rng = np.random.default_rng(5)
+    I, nodes = 150, 40
+    streams = [mixed_stream(100 + i, nodes, int(rng.integers(1, 400)), 64, ties=i % 2 == 0) for i in range(I)]
+    wl = W.Workload("instances", 0, streams, fanout=10, tau=16)
+    plan = build_plan(B, wl, policy, seed=4, flags=B.TNS_FLAG_WIDE_POSITIONS if wide else 0)
+    adjs = [oracle_lib.Adjacency(s.num_nodes, s.src, s.dst, s.ts) for s in streams]
+    # several instances inside a wave, none, exactly a wave, several tiles; small and large batches
+    for sizes in (rng.choice([0, 1, 2, 7, 63, 64, 65, 300], I), np.where(np.arange(I) % 3 == 0, 0, rng.integers(1, 1400, I))):
+        if sizes.sum() > 20_000:
+            sizes[-1] += max(0, (1 << 16) + 5 - int(sizes.sum()))
+        rowptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+        parts = [W.random_queries(int(i), s, int(m)) for i, (s, m) in enumerate(zip(streams, sizes))]
+        targets, t_start, t_end = (np.concatenate([q[k] for q in parts]) for k in range(3))
+        for tb in (None, t_start):
+            ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, rowptr, 10, policy, 0, 4, adjs=adjs)
+            assert_same(gpu_sample(plan, targets, tb, t_end, rowptr), ref, oracle_lib, f"Q={len(targets)} start={tb is not None}")
+    plan.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_bounded_wait_ends(B, layout, policy):
+    # as in test_gpu_parity.py: the tile tickets start at 1, so tile 0 never exists and the look-back ends by its bound
+    import torch
+    st = W.tiny_stream(17, 70_000, 500, 4096, ties=False)
+    plan = build_plan(B, W.Workload("tiny", 0, [st], fanout=10, tau=48), policy, flags=B.TNS_TEST_FLAG_LOST_TILE)
+    d_t, d_e = torch.from_numpy(st.src).cuda(), torch.from_numpy(st.ts).cuda()
+    t0 = time.time()
+    out = plan.run(d_t, None, d_e)
+    torch.cuda.synchronize()
+    assert time.time() - t0 < 60
+    assert plan.status(out["workspace"]), "the time-out must be reported"
+    assert int(out["rowptr"][-1].item()) == 0, "after a time-out the dense total reads 0"
+    plan.close()
