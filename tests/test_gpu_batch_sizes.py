@@ -133,3 +133,30 @@ def test_stores_built_one_after_another_by_two_threads(B, oracle_lib):
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("m", [1, 64, 2048, 2049, 4096, 4097, 20_000, 100_000])
+def test_an_edge_out_of_order_is_found_wherever_its_node_lies(B, m):
+    # one wave of the plan meets the node whose newest edge is younger than the batch; the host must hear of it every
+    # time, of the smallest such node where there are several, and the store must stay as it was
+    import torch
+    nodes = m + 3
+    late = sorted({0, m // 3, m // 2, m - 1})
+    plan = B.Plan(nodes, 4, flags=B.TNS_FLAG_DEVICE_INGEST)
+    ids = torch.tensor(late, dtype=torch.int32, device="cuda")
+    plan.add_edges_device(ids, ids, torch.full((len(late),), 100.0, device="cuda"))
+    src = torch.arange(m, dtype=torch.int32, device="cuda")
+    ts = torch.linspace(1.0, 2.0, m, device="cuda")
+    shuffled = src[torch.randperm(m, device="cuda")]
+    for rep in range(10):
+        for v in late:
+            part = torch.where(torch.isin(src, ids) & (src != v), nodes - 1, src)       # `v` alone is late
+            with pytest.raises(B.TnsError, match=f"node {v} would receive") as e:
+                plan.add_edges_device(part, part, ts)
+            assert e.value.status == B.TNS_EORDER
+        with pytest.raises(B.TnsError, match="node 0 would receive"):
+            plan.add_edges_device(shuffled, shuffled, ts)
+    assert plan.stats()["num_edges"] == len(late)
+    out = plan.run(src, None, torch.full((m,), 1000.0, device="cuda"))
+    assert torch.equal(torch.nonzero(out["count"])[:, 0].int(), ids)
+    plan.close()
