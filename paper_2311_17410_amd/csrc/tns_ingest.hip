@@ -563,7 +563,10 @@ constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
 constexpr int kSegItems = 4;                            // positions per thread in k_fast_segments
 constexpr int kPlanThreads = 1024;                      // k_fast_plan: one segment per thread, 1024 per tile
-constexpr int64_t kSmallBatch = 4096;                   // batches planned by one workgroup (k_small_plan)
+// Batches planned by one workgroup (k_small_plan).  us per batch with it / with the five kernels: 2^18 nodes 600 edges
+// 41.8 / 43.3, 2000 52.2 / 51.0, 3000 73.2 / 51.9, 4096 81.5 / 52.0; power-law ids 600 38.8 / 45.8, 2000 44.6 / 58.5, 3000
+// 63.2 / 60.8, 4096 67.5 / 60.2; a single node 2000 37.6 / 62.6.
+constexpr int64_t kSmallBatch = 2048;
 constexpr uint32_t kInternalStore = 1u;                 // IngestStatus::internal: a node entry is not what the builder writes
 constexpr uint32_t kInternalScan = 8u;                  // IngestStatus::internal: a chained scan's bounded wait ran out
 
@@ -929,12 +932,11 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
 // 36 us in the five kernels and the gaps between them (64 batches of 2000 edges, each sampled, with the apply phase
 // queued behind the plan: 5.76 -> 3.82 ms, 0.3 of it by the memory kept between plans).  Keeping the keys in registers and
 // exchanging them by shuffles gave nothing.
-template <int ITEMS /* keys per thread */>
 __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val,
                                                      int64_t* __restrict__ head_excl, int32_t* __restrict__ seg_start,
                                                      SegPlan* __restrict__ plan, int64_t* __restrict__ lines_base,
                                                      int64_t* __restrict__ dir_base) {
-    constexpr int N = 1024 * ITEMS, kWaves = 1024 / kWave;
+    constexpr int N = (int)kSmallBatch, ITEMS = N / 1024 /* keys per thread */, kWaves = 1024 / kWave;
     __shared__ uint64_t s_key[N];
     __shared__ int32_t s_start[N + 1];
     __shared__ int64_t s_wave[kWaves];
@@ -1232,12 +1234,8 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
     IngestArgs a = args;
     a.go = c.sums;
     if (a.m <= kSmallBatch) {
-        if (a.m <= 2048)
-            hipLaunchKernelGGL(k_small_plan<2>, dim3(1), dim3(1024), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start, c.plan,
-                               c.lines_base, c.dir_base);
-        else
-            hipLaunchKernelGGL(k_small_plan<4>, dim3(1), dim3(1024), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start, c.plan,
-                               c.lines_base, c.dir_base);
+        hipLaunchKernelGGL(k_small_plan, dim3(1), dim3(1024), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start, c.plan,
+                           c.lines_base, c.dir_base);
         return hipGetLastError();
     }
     const int bins = 1 << bits;
