@@ -567,7 +567,6 @@ constexpr int kPlanThreads = 1024;                      // k_fast_plan: one segm
 // 41.8 / 43.3, 2000 52.2 / 51.0, 3000 73.2 / 51.9, 4096 81.5 / 52.0; power-law ids 600 38.8 / 45.8, 2000 44.6 / 58.5, 3000
 // 63.2 / 60.8, 4096 67.5 / 60.2; a single node 2000 37.6 / 62.6.
 constexpr int64_t kSmallBatch = 2048;
-constexpr uint32_t kInternalStore = 1u;                 // IngestStatus::internal: a node entry is not what the builder writes
 constexpr uint32_t kInternalScan = 8u;                  // IngestStatus::internal: a chained scan's bounded wait ran out
 
 
@@ -957,7 +956,7 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
             else if (a.eid && a.eid[i] < 0) report(a.status, TNS_EINVAL, i);
             if (i > 0 && before > ts) atomicOr(&a.status->unsorted, 1u);
             k = ((uint64_t)(uint32_t)v << 32) | (uint32_t)i;
-            // brings the node's entry and builder state into the L2 while the keys are sorted (neither is negative)
+            // brings the node's entry and builder state into the L2 while the keys are sorted
             if ((uint64_t)(uint32_t)v < (uint64_t)a.num_nodes) touched |= a.nodes[a.node_base + v].nblocks | a.aux[a.node_base + v].tail_cap;
         }
         s_key[i] = k;
@@ -985,7 +984,7 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
             }
         }
     }
-    if (touched < 0) atomicOr(&a.status->internal, kInternalStore);
+    asm volatile("" ::"v"(touched));          // the loads' only use
     // segments; a thread owns ITEMS consecutive sorted positions
     uint64_t k[ITEMS];
     int h[ITEMS];
