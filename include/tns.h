@@ -364,9 +364,10 @@ TNS_API int tns_hbm_probe_mix(int32_t nontemporal, void *d_dst, size_t write_byt
                               void *hip_stream);
 
 /* Release the plan (the dynamic graph object of section 5's interface), its host store and its device
-   memory, after the device's queued work is done.  NULL is allowed.  Up to 256 MiB of device memory per process are
-   kept for plans created next and given back once unused for two seconds, at the library's next release or request of
-   device memory, or when an allocation of the library fails. */
+   memory, after the device's queued work is done.  Up to 256 MiB of device memory per process are kept for plans created
+   next.  They are given back once unused for two seconds, at the library's next release or request of a store's memory;
+   when an allocation of the library finds no memory left; and, all of it at once, by this call with NULL, which is
+   allowed at any time. */
 TNS_API int tns_destroy(tns_plan *plan);
 
 /* Static description of a status code. */

@@ -12,6 +12,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/tns.h"
@@ -47,10 +48,12 @@ namespace {
 
 // Device memory of destroyed and outgrown stores, kept for the next one.  A program that rebuilds its store per epoch or
 // per round otherwise spends its time in hipMalloc and hipFree, which map and unmap the memory (some 3 us per MiB to free;
-// a store of 3.2 M edges built in 32 batches, each sampled: 5.66 -> 4.23 ms a pass with the pool).  At most kHold bytes are held per process; a block that
-// has lain unused for kKeepFor is given back at the next release or request, all of a device's blocks when an
-// allocation fails.  Blocks are released only after the device's queued work is done, so a block can be handed to any
-// stream.  Safe with several threads.
+// a store of 3.2 M edges built in 32 batches, each sampled: 5.66 -> 4.23 ms a pass with the pool).  At most kHold bytes
+// are held per process (three stores of that size with what they have outgrown); a block that has lain unused for kKeepFor
+// (longer than any such loop leaves it) is given back at the next release or request, all blocks by tns_destroy(NULL), all
+// of a device's when an allocation of the library fails there.  A request takes a block of up to half more than it needs,
+// the factor by which stores grow.  Blocks are released only after the device's queued work is done, so a block can be
+// handed to any stream.  Safe with several threads; no memory is freed under the lock.
 class DevicePool {
 public:
     static constexpr size_t kHold = size_t(256) << 20, kRound = size_t(4) << 10;
@@ -60,32 +63,33 @@ public:
     hipError_t take(void** p, size_t bytes, size_t* got) {
         bytes = std::max(kRound, (bytes + kRound - 1) / kRound * kRound);
         int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+        const hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
+        give_back(Clock::now() - kKeepFor, -1);
         {
             std::lock_guard<std::mutex> lock(mutex_);
-            give_back(now() - kKeepFor, -1);
             size_t best = blocks_.size();
             for (size_t i = 0; i < blocks_.size(); ++i)
                 if (blocks_[i].dev == dev && blocks_[i].bytes >= bytes && blocks_[i].bytes <= bytes + bytes / 2 &&
                     (best == blocks_.size() || blocks_[i].bytes < blocks_[best].bytes))
                     best = i;
             if (best < blocks_.size()) {
-                *p = blocks_[best].ptr;
                 *got = blocks_[best].bytes;
-                held_ -= blocks_[best].bytes;
-                blocks_.erase(blocks_.begin() + (std::ptrdiff_t)best);
+                *p = remove(best);
                 return hipSuccess;
             }
         }
         *got = bytes;
-        e = hipMalloc(p, bytes);
-        if (e != hipErrorOutOfMemory) return e;
+        return allocate(p, bytes);
+    }
+
+    // memory that is not kept afterwards; if there is none left, the blocks held on this device are given back first
+    hipError_t allocate(void** p, size_t bytes) {
+        const hipError_t e = hipMalloc(p, bytes);
+        int dev = 0;
+        if (e != hipErrorOutOfMemory || hipGetDevice(&dev) != hipSuccess) return e;
         (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> lock(mutex_);
-            give_back(now(), dev);
-        }
+        give_back(Clock::time_point::max(), dev);
         return hipMalloc(p, bytes);
     }
 
@@ -96,15 +100,34 @@ public:
             (void)hipFree(p);
             return;
         }
-        std::lock_guard<std::mutex> lock(mutex_);
-        give_back(now() - kKeepFor, -1);
-        while (held_ + bytes > kHold) free_oldest();
-        try {
-            blocks_.push_back(Block{p, bytes, dev, now()});
-            held_ += bytes;
-        } catch (const std::bad_alloc&) {
-            (void)hipFree(p);
-        }
+        give_back(Clock::now() - kKeepFor, -1);
+        void* drop = nullptr;
+        do {
+            drop = nullptr;
+            std::lock_guard<std::mutex> lock(mutex_);
+            if (held_ + bytes > kHold) {
+                drop = remove(0);          // in the order of their release
+            } else {
+                try {
+                    blocks_.push_back(Block{p, bytes, dev, Clock::now()});
+                    held_ += bytes;
+                    p = nullptr;
+                } catch (const std::bad_alloc&) {
+                    drop = std::exchange(p, nullptr);
+                }
+            }
+        } while (free_block(drop) && p);
+    }
+
+    // frees the blocks released up to `until`, of one device or (dev < 0) of all
+    void give_back(std::chrono::steady_clock::time_point until, int dev) {
+        void* drop = nullptr;
+        do {
+            drop = nullptr;
+            std::lock_guard<std::mutex> lock(mutex_);
+            for (size_t i = 0; i < blocks_.size() && !drop; ++i)
+                if (blocks_[i].since <= until && (dev < 0 || blocks_[i].dev == dev)) drop = remove(i);
+        } while (free_block(drop));
     }
 
 private:
@@ -115,23 +138,15 @@ private:
         int dev;
         Clock::time_point since;
     };
-    static Clock::time_point now() { return Clock::now(); }
-    void free_oldest() {
-        (void)hipFree(blocks_.front().ptr);          // in the order of their release
-        held_ -= blocks_.front().bytes;
-        blocks_.erase(blocks_.begin());
+    static bool free_block(void* p) {
+        if (p) (void)hipFree(p);
+        return p != nullptr;
     }
-    // frees the blocks released before `until`, of one device or (dev < 0) of all
-    void give_back(Clock::time_point until, int dev) {
-        for (size_t i = 0; i < blocks_.size();) {
-            if (blocks_[i].since <= until && (dev < 0 || blocks_[i].dev == dev)) {
-                (void)hipFree(blocks_[i].ptr);
-                held_ -= blocks_[i].bytes;
-                blocks_.erase(blocks_.begin() + (std::ptrdiff_t)i);
-            } else {
-                ++i;
-            }
-        }
+    void* remove(size_t i) {
+        void* p = blocks_[i].ptr;
+        held_ -= blocks_[i].bytes;
+        blocks_.erase(blocks_.begin() + (std::ptrdiff_t)i);
+        return p;
     }
     std::mutex mutex_;
     std::vector<Block> blocks_;
@@ -143,6 +158,12 @@ DevicePool& device_pool() {
     static DevicePool* pool = new (room) DevicePool();      // never destroyed: the HIP runtime may be gone by then
     return *pool;
 }
+
+}  // namespace
+
+hipError_t tns::device_malloc(void** p, size_t bytes) { return device_pool().allocate(p, bytes); }
+
+namespace {
 
 template <class T>
 struct DeviceArray {
@@ -281,7 +302,7 @@ int ensure_device_store(tns_plan* plan, hipStream_t stream) {
     hipError_t e = hipMemsetAsync(plan->d_nodes.ptr, 0, (size_t)total_nodes * sizeof(tns::NodeLine), stream);
     if (e == hipSuccess) e = hipMemsetAsync(ds.aux.ptr, 0, (size_t)total_nodes * sizeof(tns::NodeAux), stream);
     tns::IngestStatus* st = nullptr;
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&st), sizeof(tns::IngestStatus));
+    if (e == hipSuccess) e = tns::device_malloc(reinterpret_cast<void**>(&st), sizeof(tns::IngestStatus));
     if (e == hipSuccess && !ds.h_status) {
         e = hipHostMalloc(reinterpret_cast<void**>(&ds.h_status), 2 * sizeof(tns::IngestStatus), hipHostMallocMapped | hipHostMallocCoherent);
         if (e == hipSuccess) {
@@ -330,7 +351,7 @@ struct DeviceTemp {
     T* ptr = nullptr;
     ~DeviceTemp() { if (ptr) (void)hipFree(ptr); }
     hipError_t upload(const T* host, int64_t n, hipStream_t stream) {
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&ptr), (size_t)std::max<int64_t>(n, 1) * sizeof(T));
+        hipError_t e = tns::device_malloc(reinterpret_cast<void**>(&ptr), (size_t)std::max<int64_t>(n, 1) * sizeof(T));
         if (e == hipSuccess && n > 0) e = hipMemcpyAsync(ptr, host, (size_t)n * sizeof(T), hipMemcpyHostToDevice, stream);
         return e;
     }
@@ -1150,7 +1171,10 @@ int64_t tns_node_blocks(const tns_plan* plan, int32_t instance, int32_t node, in
 
 int tns_destroy(tns_plan* plan) {
     g_err.clear();
-    if (!plan) return TNS_OK;
+    if (!plan) {
+        device_pool().give_back(std::chrono::steady_clock::time_point::max(), -1);
+        return TNS_OK;
+    }
     if (plan->d_nodes.ptr || plan->d_dir.ptr || plan->d_edges.ptr || plan->d_lines.ptr) {
         DeviceGuard guard(plan->cfg.device);
         plan->d_lines.release();

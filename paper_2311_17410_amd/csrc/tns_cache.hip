@@ -650,7 +650,7 @@ int tns_cache_create(const tns_cache_config* cfg, tns_cache** out) {
                             {(void**)&c->st.touched, (size_t)C * 4}, {(void**)&c->st.rows, (size_t)C * cfg->dim * 4},
                             {(void**)&c->st.counters, kStripes * 3 * 8},        {(void**)&c->st.ring, 8}};
     for (const Alloc& a : allocs) {
-        const hipError_t e = hipMalloc(a.p, a.bytes);
+        const hipError_t e = tns::device_malloc(a.p, a.bytes);
         if (e != hipSuccess) {
             tns_cache_destroy(c);
             return fail_hip(e, "allocating the cache");

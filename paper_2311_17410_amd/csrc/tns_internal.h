@@ -11,6 +11,10 @@ int fail(int code, const std::string& msg);
 int fail_hip(hipError_t e, const char* what);
 void clear_error();
 
+// hipMalloc on the current device.  If there is no memory left, what the library holds there for plans created next is
+// given back first.
+hipError_t device_malloc(void** p, size_t bytes);
+
 // Switches to a device for the lifetime of the object and restores the caller's.
 class DeviceGuard {
 public:

@@ -1,0 +1,73 @@
+"""Host paths around the kernels, without a GPU: the library runs in a process of its own on tests/fake_hip.c (device
+memory with a limit, kernels that do nothing)."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_set_limit.argtypes, fake.fake_used.restype = [C.c_size_t], C.c_size_t
+sys.modules["torch"] = None                     # the binding does without it; its runtime stays out of the process
+sys.path.insert(0, sys.argv[2])
+from paper_2311_17410_amd import binding as B, cache_binding as KB
+MiB = 1 << 20
+def plan_of(mib):                               # a device-built store whose node table and builder state take `mib`
+    p = B.Plan(mib * MiB // 216, 10, flags=B.TNS_FLAG_DEVICE_INGEST)      # 144 bytes a node, and room to grow by half
+    B.tns_commit(p.handle)
+    return p
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "fake_hip.c")])
+
+    def go(body):
+        p = subprocess.run([sys.executable, "-c", PRELUDE + body, so, ROOT], capture_output=True, text=True, timeout=120)
+        assert p.returncode == 0, p.stdout + p.stderr
+    return go
+
+
+def test_memory_kept_for_the_next_plan(run):
+    run("""
+p = plan_of(100); in_use = fake.fake_used(); p.close()
+assert 100 * MiB <= fake.fake_used() <= in_use            # kept
+n = fake.fake_allocations(); p = plan_of(100)
+assert fake.fake_allocations() - n <= 1                   # and used again (the status record is not kept)
+p.close()
+for mib in (300, 200, 150, 250): plan_of(mib).close()
+assert fake.fake_used() <= 256 * MiB                      # bounded
+B.tns_destroy(None)
+assert fake.fake_used() == 0                              # given back
+""")
+
+
+def test_kept_memory_is_given_back_to_a_cache(run):
+    run("""
+fake.fake_set_limit(300 * MiB)
+plan_of(180).close()
+assert fake.fake_used() > 150 * MiB
+c = KB.Cache(1000, 400_000, 128, KB.TNS_CACHE_LRU, 0.2)   # 195 MiB of rows
+""")
+
+
+def test_kept_memory_is_given_back_to_a_larger_plan(run):
+    run("""
+fake.fake_set_limit(300 * MiB)
+plan_of(180).close()
+p = plan_of(200)
+try:
+    plan_of(200)
+    raise SystemExit("200 + 200 MiB of 300")
+except B.TnsError as e:
+    assert e.status == B.TNS_ENOMEM
+p.close()
+plan_of(200)
+""")
