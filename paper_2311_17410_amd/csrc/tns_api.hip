@@ -200,6 +200,7 @@ struct DeviceStore {
                                                 // sequence word; the device can write both (mapped, coherent)
     tns::IngestStatus* h_status_dev = nullptr;  // the same memory as the device addresses it
     unsigned long long seq = 0;                 // batches planned by the short pipeline
+    bool lost = false;                          // whether the last batch was applied is not known: no further one is taken
     std::vector<tns::InstanceTotals> totals;   // per instance: edges, blocks, slots, running edge id, deleted
 };
 
@@ -474,6 +475,7 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     if (m == 0) return TNS_OK;
     if (m > tns::kMaxDeviceBatch) return fail(TNS_ESIZE, "batch larger than 2^24-1 edges: split it");
     DeviceStore& ds = *plan->dev;
+    if (ds.lost) return fail(TNS_ESTATE, "an earlier batch failed and may have been applied in part: create a new plan");
     tns::InstanceTotals& tot = ds.totals[(size_t)instance];
     if (!d_eid && tot.next_eid + m > (int64_t)INT32_MAX) return fail(TNS_ESIZE, "running edge id would exceed 2^31-1");
 
@@ -528,24 +530,27 @@ int tns_add_edges_device(tns_plan* plan, int32_t instance, const int32_t* d_src,
     bool polled = false;
     if (a.host_status) {
         // The plan's last workgroup writes the record into host memory and then the batch's sequence number: picked
-        // up here by polling, which is some 20 us sooner than a copy and a wait for the stream.  The wait is bounded;
-        // past the bound (or with an internal error in the record) the ordinary read-back takes over.
+        // up here by polling, which is some 20 us sooner than a copy and a wait for the stream.  The wait is bounded; past
+        // the bound the stream is waited for.  With an internal error in the record (then nothing is applied) the
+        // ordinary read-back takes over and clears it.
         const volatile unsigned long long* seq_word = reinterpret_cast<const volatile unsigned long long*>(ds.h_status + 1);
         const auto t0 = std::chrono::steady_clock::now();
         int spins = 0;
         while (*seq_word != a.seq) {
             if ((++spins & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) {
-                // the stream was busy: once its work is done the record is here (the device's own copy is not read
-                // then, the apply phase has made it ready for the next batch)
-                if ((e = hipStreamSynchronize(stream)) != hipSuccess) return fail_hip(e, "waiting for the ingestion plan");
+                // the stream was busy: once its work is done the record is here.  The device's own copy cannot stand in
+                // for it: the apply phase, if it ran, has made that ready for the next batch.
+                if ((e = hipStreamSynchronize(stream)) != hipSuccess || *seq_word != a.seq) {
+                    ds.lost = true;
+                    return e != hipSuccess ? fail_hip(e, "waiting for the ingestion plan")
+                                           : fail(TNS_EHIP, "the ingestion plan did not reach the host (internal error)");
+                }
                 break;
             }
         }
-        if (*seq_word == a.seq) {
-            std::atomic_thread_fence(std::memory_order_acquire);
-            st = *ds.h_status;
-            polled = st.internal == 0;
-        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        st = *ds.h_status;
+        polled = st.internal == 0;
     }
     if (!polled && (rc = read_status(plan, stream, st, "waiting for the ingestion plan"))) return rc;
     if (fast && st.unsorted && st.err_word == ~0ull) {

@@ -491,8 +491,8 @@ __device__ __forceinline__ void apply_edge(const IngestArgs& a, const uint64_t* 
                                            const SegPlan* __restrict__ plan, const int64_t* __restrict__ lines_base, int64_t p) {
     if (p >= a.m) return;
     if (p == 0) {
-        // the host has read the plan; the record is made ready for the next batch here, so that the next
-        // plan needs no launch of its own for it (`internal` stays: it is reported by the next read-back)
+        // The host has read the record or has a copy of it (hand_over), and it is made ready for the next batch here, so
+        // that the next plan needs no launch of its own for it (`internal` stays: it is reported by the next read-back).
         IngestStatus* st = a.status;
         st->err_word = ~0ull;
         st->unsorted = 0;

@@ -160,3 +160,37 @@ def test_an_edge_out_of_order_is_found_wherever_its_node_lies(B, m):
     out = plan.run(src, None, torch.full((m,), 1000.0, device="cuda"))
     assert torch.equal(torch.nonzero(out["count"])[:, 0].int(), ids)
     plan.close()
+
+
+@pytest.mark.parametrize("m", [700, 5000])
+def test_batches_behind_a_busy_stream(B, oracle_lib, m):
+    # the host gives up polling for a batch's plan after 2 ms and waits for the stream: same store, same refusals
+    import torch
+    rng = np.random.default_rng(m)
+    nodes, n = 400, 6 * m
+    src, dst = (rng.integers(0, nodes, n, dtype=np.int32) for _ in range(2))
+    ts = np.sort(rng.standard_normal(n)).astype(np.float32)
+    ts[3 * m:4 * m] = rng.permutation(ts[3 * m:4 * m])                     # this batch is not in time order
+    d = [torch.from_numpy(a).cuda() for a in (src, dst, ts)]
+    plan = B.Plan(nodes, 10, flags=B.TNS_FLAG_DEVICE_INGEST)
+    block = torch.zeros(1 << 28, dtype=torch.float32, device="cuda")
+    other = torch.empty_like(block)
+
+    def busy():                    # some 15 ms of copies
+        for _ in range(40):
+            other.copy_(block)
+
+    for lo in range(0, n, m):
+        busy()
+        plan.add_edges_device(*(a[lo:lo + m] for a in d))
+        busy()
+        with pytest.raises(B.TnsError) as e:                               # older than what is stored
+            plan.add_edges_device(d[0][lo:lo + m], d[1][lo:lo + m], d[2][lo:lo + m] - 100.0)
+        assert e.value.status == B.TNS_EORDER
+    assert plan.stats()["num_edges"] == n
+    st = W.Stream(nodes, src, dst, ts, m)
+    targets, t_start, t_end = W.random_queries(5, st, 3000)
+    adj = oracle_lib.Adjacency(nodes, src, dst, ts, batch_rowptr=list(range(0, n + 1, m)))
+    assert_same(gpu_sample(plan, targets, t_start, t_end), adj.sample(targets, t_start, t_end, 10), oracle_lib, "store")
+    adj.close()
+    plan.close()

@@ -71,3 +71,20 @@ except B.TnsError as e:
 p.close()
 plan_of(200)
 """)
+
+
+@pytest.mark.parametrize("m", [100, 5000])
+def test_a_plan_that_never_reaches_the_host_is_an_error(run, m):
+    # the kernels do nothing here, so the record with the batch's plan does not come; whether the queued apply phase ran
+    # is then not known, and the store takes no further batch
+    run(f"""
+p = plan_of(1)
+src = C.create_string_buffer(4 * {m})
+for status, text in ((B.TNS_EHIP, "did not reach the host"), (B.TNS_ESTATE, "create a new plan")):
+    try:
+        B.tns_add_edges_device(p.handle, 0, C.addressof(src), C.addressof(src), C.addressof(src), None, {m}, 0)
+        raise SystemExit("accepted")
+    except B.TnsError as e:
+        assert e.status == status and text in str(e), str(e)
+assert p.stats()["num_edges"] == 0
+""")
