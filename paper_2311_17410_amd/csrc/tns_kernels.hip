@@ -780,10 +780,11 @@ hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     // Small batches go to the kernel with sixteen lanes per query.  us per call with that kernel / with a query per
     // lane (store of 2^22 edges, fan-out 10): uniform ids, recent 1024 queries 12.4 / 16.9, 65536 23.6 / 27.8, 131072
     // 42.0 / 31.3; power-law ids, recent, windowed 12.8 / 35.2, 40.3 / 50.8, 83.5 / 59.7; power-law ids, uniform policy
-    // 11.9 / 37.2, 34.3 / 55.2, 62.9 / 66.2.  With fewer than 8 slots half of a team has nothing to gather and the limit is
-    // lower: fan-out 1, power-law ids, recent, windowed 32768 queries 24.5 / 27.5, 65536 39.0 / 31.1; fan-out 5, 24.8 / 30.6,
-    // 38.9 / 35.0.
-    const int64_t team_max_queries = int64_t(1) << (a.fanout < 8 ? 15 : 16);
+    // 11.9 / 37.2, 34.3 / 55.2, 62.9 / 66.2.  With fewer than 8 slots half of a team has nothing to gather, and the limit
+    // stays below 2^16, where the workgroups of the other kernel take a second wave and it halves its tickets.  Mean over six
+    // stores and three windows of the time with the teams over the time without: fan-out 1, recent 61000 queries 0.86, 65536
+    // 1.08, uniform 1.01, 1.32; fan-out 5 0.83, 1.03, 0.95, 1.17; fan-out 7 0.80, 1.01, 0.91, 1.09.
+    const int64_t team_max_queries = (int64_t(1) << 16) - (a.fanout < 8 ? 1 : 0);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;
     const bool wide = a.wide_offsets != 0;

@@ -1,4 +1,4 @@
-"""The kernel with a query per lane serves batches above 2^16 queries (2^15 for small fan-outs): its parity at the edge of
+"""The kernel with a query per lane serves batches above 2^16 queries (from there on with small fan-outs): its parity at the edge of
 that rule, with 64-bit positions, over instances of uneven and no size, and its bounded wait."""
 import time
 
@@ -29,7 +29,7 @@ def mixed_stream(seed, num_nodes, n, batch, ties):
 
 
 @pytest.mark.parametrize("policy", [0, 1])
-@pytest.mark.parametrize("fanout,Q", [(5, 1 << 15), (5, (1 << 15) + 1), (7, (1 << 15) + 1), (8, 1 << 16), (8, (1 << 16) + 1)])
+@pytest.mark.parametrize("fanout,Q", [(5, (1 << 16) - 1), (5, 1 << 16), (7, 1 << 16), (8, 1 << 16), (8, (1 << 16) + 1)])
 def test_both_sides_of_the_rule(B, oracle_lib, policy, fanout, Q):
     st = mixed_stream(1, 2000, 20_000, 900, ties=False)
     wl = W.Workload("mixed", 0, [st], fanout=fanout, tau=48)
