@@ -257,10 +257,10 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Workgroup barrier for data exchanged through LDS only.  __syncthreads() also orders global memory: on
-// gfx9 that is a wait for EVERY outstanding vector memory operation of the wave, stores included, and a
-// store is only done when the L2 has taken it (microseconds under load).  Here the wave waits for its
-// LDS operations and meets the others; its stores stay in flight.
+// Workgroup barrier for data exchanged through LDS only: the wave waits for its LDS operations and meets the others, its
+// stores stay in flight (a store is only done when the L2 has taken it, microseconds under load).  __syncthreads() is a
+// fence for global memory as well.  How much of a wave's traffic it waits for is left to the compiler: nothing that needs
+// other waves' stores or atomics performed may rely on either.
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
