@@ -107,6 +107,17 @@ __device__ __forceinline__ void narrow4(int32_t& lo, int32_t& n, int32_t rest, c
     }
 }
 
+// The same with one read in flight.
+template <class Qual>
+__device__ __forceinline__ void narrow2(int32_t& lo, int32_t& n, int32_t rest, const Qual& qual) {
+    while (n > rest) {
+        const int32_t half = n >> 1;
+        const bool up = qual(lo + half);
+        lo += up ? half + 1 : 0;
+        n = up ? n - half - 1 : half;
+    }
+}
+
 // State of one lane's walk over the blocks of its target node, newest block first
 // (Algorithm 1).  `t` numbers the blocks in visiting order.
 template <int POLICY, bool INCL, typename pos_t>

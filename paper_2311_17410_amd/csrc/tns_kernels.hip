@@ -49,10 +49,12 @@ __global__ void __launch_bounds__(256) tns_scan_clear(uint64_t* ws, int64_t word
 
 // FUSED: also removes the padding in the same pass (rowptr and dense arrays), with the tile
 // offsets obtained from a chained scan over the workgroups.
+// Without the scan, recent policy: seven waves per SIMD (72 registers; with six of them 80 and the reads in flight across
+// the host link were too few: 2^24 Zipf(1.1) edges on the host, one query each, 32.0 -> 30.8 ms; in HBM 2^22 queries over
+// blocks of up to 8192 edges 416 -> 372 us, 2^20 over uniform ids 95 -> 97).
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
-__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_kernel(const SampleArgs p, const int32_t stride,
-                                                                          const uint32_t f_magic, const int32_t gshift,
-                                                                          const uint32_t chunk) {
+__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : (POLICY == 0 && !COUNT ? 7 : 6))
+tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_magic, const int32_t gshift, const uint32_t chunk) {
     // LDS: one chunk per wave.  First the staging area of the node lines (3 KiB), later, in the same bytes,
     // the wave's rows of selected positions and, behind them, the descriptors of the cooperative search.
     constexpr bool COOP_NODE = !COUNT;
@@ -226,8 +228,15 @@ __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6) tns_sample_
                     if (in && w.tb > r.t_min) { b_off = rec_off(r); b_n = rec_size(r); start_block = j; }
                 }
                 const int32_t rest = POLICY == 1 ? 0 : kCoopGroup;
-                narrow4(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
-                narrow4(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                // (without the scan and recent policy one read at a time: of three in flight two are more traffic, 32.0 -> 31.5
+                // ms across the host link)
+                if (FUSED || POLICY == 1) {
+                    narrow4(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+                    narrow4(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                } else {
+                    narrow2(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+                    narrow2(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                }
                 if (POLICY == 1) {
                     const int32_t c = count_flat(w.d_lo);
                     w.k = min(c, f);
