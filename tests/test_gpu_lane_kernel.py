@@ -60,6 +60,30 @@ def test_large_batches_with_64_bit_positions(B, oracle_lib, wide, policy, fanout
     plan.close()
 
 
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("fanout", [1, 9, 10, 11, 17])
+def test_degrees_around_the_line_boundaries(B, oracle_lib, policy, fanout, layout):
+    # nodes of 0 to 71 edges with ties, queried at, just before and just after every time, in one large batch
+    rng = np.random.default_rng(fanout)
+    num_nodes = 72
+    src = rng.permutation(np.repeat(np.arange(num_nodes, dtype=np.int32), np.arange(num_nodes)))
+    ts = np.sort(rng.integers(0, 300, len(src))).astype(np.float32)
+    st = W.Stream(num_nodes, src, rng.integers(0, num_nodes, len(src), dtype=np.int32), ts, 37)
+    wl = W.Workload("degrees", 0, [st], fanout=fanout, tau=48)
+    times = np.unique(ts)
+    at = np.concatenate([times, np.nextafter(times, np.float32(-np.inf)), np.nextafter(times, np.float32(np.inf)), [-1.0, 1e9]]).astype(np.float32)
+    targets, t_end = (a.ravel() for a in np.meshgrid(np.arange(num_nodes, dtype=np.int32), at))
+    targets, t_end = (np.ascontiguousarray(np.resize(a, max(len(a), (1 << 16) + 9))) for a in (targets, t_end))
+    t_start = (t_end - np.float32(40.0)).astype(np.float32)
+    adjs = [oracle_lib.Adjacency(num_nodes, src, st.dst, ts)]
+    for incl in (0, 1):
+        plan = build_plan(B, wl, policy, incl, seed=9)
+        for tb in (None, t_start):
+            ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, policy, incl, 9, adjs=adjs)
+            assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, f"incl={incl} start={tb is not None}")
+        plan.close()
+
+
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("policy", [0, 1])
 def test_uneven_instances(B, oracle_lib, wide, policy, layout):

@@ -81,10 +81,11 @@ def test_degrees_around_the_line_boundaries(B, oracle_lib, policy, f):
 @pytest.mark.parametrize("policy", [0, 1])
 @pytest.mark.parametrize("f", [3, 10, 20])
 def test_64_bit_edge_positions(B, oracle_lib, policy, f):
-    # the kernels keep 64-bit positions once the edge array passes 8 GiB; forced here on a small store
+    # the kernels with a query per lane (batches above 2^16 queries, calls without the padding removal) keep 64-bit
+    # positions once the edge array passes 8 GiB; forced here on a small store
     st = W.tiny_stream(43, 5000, 31, 300, ties=True)
     wl = wl_of(st, fanout=f, tau=16)
-    targets, t_start, t_end = W.random_queries(44, st, 2000 + 3)
+    targets, t_start, t_end = W.random_queries(44, st, (1 << 16) + 3)
     plan = build_plan(B, wl, policy, 0, seed=8, flags=B.TNS_FLAG_WIDE_POSITIONS)
     for tb in (t_start, None):
         got = gpu_sample(plan, targets, tb, t_end)
