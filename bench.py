@@ -330,9 +330,8 @@ def main() -> int:
         total_k = int(r.out["rowptr"][-1].item())
         assert total_k == bm["n_edges"], (total_k, bm["n_edges"])
         ms = sum(ev) / len(ev)
-        kname = ("tns_sample_prefix_kernel" if layout == "prefix" else "tns_sample_kernel") + " (padding removal fused)"
-        if args.placement != "hbm":
-            kname = "tns_sample_kernel + tns_compact kernels"
+        kname = "tns_sample_prefix_kernel" if layout == "prefix" else ("tns_sample_recent_kernel" if args.policy == "recent" else "tns_sample_kernel")
+        kname += " (padding removal fused)" if args.placement == "hbm" else " + tns_compact kernels"
         key = f"{wl.name}:{args.policy}:{layout}"
         tr = measured_traffic(key) if plain else None
         fig = {"layout": layout, "wall_ms_per_step": wall_ms, "ms_per_launch": ms, "ms_per_launch_median": sorted(ev)[len(ev) // 2],

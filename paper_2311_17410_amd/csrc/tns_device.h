@@ -28,6 +28,11 @@ __device__ __forceinline__ uint32_t div_by(uint32_t s, uint32_t f, uint32_t magi
     return f == 1 ? s : __umulhi(s, magic);
 }
 
+// Query of the wave that flat slot s of its 64 f slots belongs to: floor(s / f) for s < 2^12, f <= 64 (a 24-bit product
+// with ceil(2^18 / f): the error s * (f - 1) / 2^18 stays below 1 / f).
+__host__ __device__ inline uint32_t slot_multiplier(int32_t f) { return ((1u << 18) + (uint32_t)f - 1u) / (uint32_t)f; }
+__device__ __forceinline__ uint32_t query_of_slot(uint32_t s, uint32_t f_mul) { return __umul24(s, f_mul) >> 18; }
+
 // Rank in [0, c) for slot j of query qid: splitmix64 output function on the counter
 // seed + G * (qid * f + j + 1), top 32 bits scaled by multiply-shift.
 __device__ __forceinline__ uint64_t pick_rank(uint64_t seed, int64_t qid, int32_t f, int32_t j, uint64_t c) {
@@ -71,8 +76,27 @@ __device__ __forceinline__ int32_t instance_of(const int64_t* __restrict__ rowpt
     return lo;
 }
 
+// A value that is the same in all lanes of the wave, as the compiler cannot know: addresses formed from it are a scalar
+// base and a 32-bit offset per lane, where 64-bit additions per lane and access were a third of the output stage's
+// instructions.
+__device__ __forceinline__ int32_t wave_uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t wave_uniform(int64_t v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v & 0xffffffffll));
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// The value of one lane, the same lane for the whole wave.
+__device__ __forceinline__ int32_t wave_read(int32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ int64_t wave_read(int64_t v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v & 0xffffffffll), lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 constexpr int kCoopGroup = 16;        // lanes per query in the cooperative search (recent policy, fan-out <= 16)
 constexpr int kGatherChunk = 10;      // gather iterations whose loads are issued together (8 and 5 measured slower)
+constexpr int kGatherGroup = 5;       // of which so many are prepared side by side (every fan-out in use is a multiple)
 
 // Unsigned index type of the same width as the LDS position entries: with a 32-bit index the edge
 // load is addressed as base + 32-bit offset, one register per address.
@@ -120,7 +144,9 @@ __device__ __forceinline__ void narrow2(int32_t& lo, int32_t& n, int32_t rest, c
 
 // State of one lane's walk over the blocks of its target node, newest block first
 // (Algorithm 1).  `t` numbers the blocks in visiting order.
-template <int POLICY, bool INCL, typename pos_t>
+// SLOTS (recent policy): an entry of s_pos is not the edge's word index but its slot plus the entry's number, as the
+// block tables of tns_kernels_recent.hip hold them.
+template <int POLICY, bool INCL, typename pos_t, bool SLOTS = false>
 struct Walk {
     float tb, te;                 // window [tb, te) or [tb, te]
     int32_t f;
@@ -197,7 +223,7 @@ struct Walk {
                 const int32_t id = (int32_t)edges[slot_word(off + i) + 2];
                 ++n_probes;
                 if (id < 0) continue;
-                if (k < f) s_pos[k++] = slot_pos<pos_t>(off + i);
+                if (k < f) { s_pos[k] = SLOTS ? (pos_t)(off + i + k) : slot_pos<pos_t>(off + i); ++k; }
                 ++cnt;
                 if (POLICY == 0 && k >= f) break;
             }
@@ -208,7 +234,7 @@ struct Walk {
             }
         } else if (cnt > 0) {
             const int32_t take = min(f - k, cnt);
-            for (int32_t j = 0; j < take; ++j) s_pos[k + j] = slot_pos<pos_t>(off + hi - 1 - j);
+            for (int32_t j = 0; j < take; ++j) s_pos[k + j] = SLOTS ? (pos_t)(off + hi - 1 + k) : slot_pos<pos_t>(off + hi - 1 - j);
             k += take > 0 ? take : 0;
             if (POLICY == 1) {
                 if (t_first < 0) { t_first = t; hi_first = hi; }
@@ -294,7 +320,7 @@ struct GatherRegs {
 // BRANCHY: each load sits in its own branch instead (uniform policy: every slot of a query lies in another
 // line and the variant below measured slower there, C5 step 35.4 against 31.2 ms).
 template <typename pos_t, bool BRANCHY = false>
-__device__ __forceinline__ void gather_load(GatherRegs& g, const SampleArgs& p, uint32_t f_magic, int32_t stride,
+__device__ __forceinline__ void gather_load(GatherRegs& g, const SampleArgs& p, uint32_t f_mul, int32_t stride,
                                             const pos_t* __restrict__ w_pos, int lane, int32_t it0, int32_t k) {
     const int32_t f = p.fanout;
     // The loads are unconditional (an empty slot reads the first edge of the array and drops it) and all
@@ -307,7 +333,7 @@ __device__ __forceinline__ void gather_load(GatherRegs& g, const SampleArgs& p, 
             g.nbr[i] = -1; g.eid[i] = -1; g.ts[i] = 0.0f;
             if (it0 + i < f) {
                 const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
-                const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+                const uint32_t ql = query_of_slot(s, f_mul);
                 const int32_t j = (int32_t)(s - ql * (uint32_t)f);
                 const int32_t kq = __shfl(k, (int)ql, kWave);
                 if (j < kq) {
@@ -327,7 +353,7 @@ __device__ __forceinline__ void gather_load(GatherRegs& g, const SampleArgs& p, 
         raw[i].ts = 0.0f; raw[i].nbr = -1; raw[i].eid = -1;
         if (it0 + i < f) {          // uniform over the wave
             const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+            const uint32_t ql = query_of_slot(s, f_mul);
             const int32_t j = (int32_t)(s - ql * (uint32_t)f);
             const int32_t kq = __shfl(k, (int)ql, kWave);
             filled[i] = j < kq;
@@ -355,41 +381,155 @@ __device__ __forceinline__ void gather_load(GatherRegs& g, const SampleArgs& p, 
 }
 
 // padded rows: slots of queries below Q, empty slots get the sentinels
-__device__ __forceinline__ void store_padded(const GatherRegs& g, const SampleArgs& p, uint32_t f_magic, int lane,
-                                             int32_t it0, int64_t q0, int64_t Q) {
+__device__ __forceinline__ void store_padded(const GatherRegs& g, const SampleArgs& p, int lane, int32_t it0, int64_t q0, int64_t Q) {
     if (!p.out_nbr) return;      // dense-only run: the padded rows are not materialised
     const int32_t f = p.fanout;
-    const int64_t out0 = q0 * f;
+    const int64_t out0 = q0 * f + (int64_t)it0 * kWave;
+    int32_t* const nbr = p.out_nbr + out0;
+    int32_t* const eid = p.out_eid + out0;
+    float* const ts = p.out_ts + out0;
+    const int32_t limit = (int32_t)min((int64_t)kWave, Q - q0) * f - it0 * kWave;       // slots from out0 on
+    // (the test per store is kept although a full tile needs none: all stores in one run were slower under the uniform
+    // policy, 2^22 queries 417 -> 460 us)
 #pragma unroll
     for (int i = 0; i < kGatherChunk; ++i) {
-        if (it0 + i < f) {
-            const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
-            if (q0 + (int64_t)ql < Q) {
-                __builtin_nontemporal_store(g.nbr[i], &p.out_nbr[out0 + s]);
-                __builtin_nontemporal_store(g.eid[i], &p.out_eid[out0 + s]);
-                __builtin_nontemporal_store(g.ts[i], &p.out_ts[out0 + s]);
-            }
+        const uint32_t s = (uint32_t)(i * kWave + lane);
+        if ((int32_t)s < limit) {
+            __builtin_nontemporal_store(g.nbr[i], &nbr[s]);
+            __builtin_nontemporal_store(g.eid[i], &eid[s]);
+            __builtin_nontemporal_store(g.ts[i], &ts[s]);
         }
     }
 }
 
-// dense copy: `row` = where the lane's own query starts; consecutive lanes write consecutive entries
-__device__ __forceinline__ void store_dense(const GatherRegs& g, const SampleArgs& p, uint32_t f_magic, int lane,
-                                            int32_t it0, int64_t row) {
+// dense copy: `row0` = where the wave's first query starts, `excl` = where the lane's own query starts from there;
+// consecutive lanes write consecutive entries
+__device__ __forceinline__ void store_dense(const GatherRegs& g, const SampleArgs& p, uint32_t f_mul, int lane,
+                                            int32_t it0, int64_t row0, int32_t excl) {
     const int32_t f = p.fanout;
+    int32_t* const nbr = p.cmp_nbr + row0;
+    int32_t* const eid = p.cmp_eid + row0;
+    float* const ts = p.cmp_ts + row0;
+    uint32_t at[kGatherChunk];
+#pragma unroll
+    for (int i = 0; i < kGatherChunk; ++i) {      // (all shuffles first; beyond the last slot their result is not used)
+        const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
+        const uint32_t ql = query_of_slot(s, f_mul);
+        at[i] = (uint32_t)__shfl(excl, (int)ql, kWave) + (s - ql * (uint32_t)f);
+    }
 #pragma unroll
     for (int i = 0; i < kGatherChunk; ++i) {
-        if (it0 + i < f) {
-            const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
-            const int32_t j = (int32_t)(s - ql * (uint32_t)f);
-            const int64_t rowq = shfl64(row, (int)ql);
-            if (g.eid[i] >= 0) {
-                p.cmp_nbr[rowq + j] = g.nbr[i];
-                p.cmp_eid[rowq + j] = g.eid[i];
-                p.cmp_ts[rowq + j] = g.ts[i];
+        if (g.eid[i] >= 0) {
+            nbr[at[i]] = g.nbr[i];
+            eid[at[i]] = g.eid[i];
+            ts[at[i]] = g.ts[i];
+        }
+    }
+}
+
+// ---- a workgroup's tile and the padding removal fused into sampling --------------------------------------
+
+// Tiles are numbered in the order workgroups start, so that a tile only ever waits for tiles that have started.
+__device__ __forceinline__ int64_t take_tile(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived) {
+    if (threadIdx.x == 0) {
+        *s_tile_base = (int64_t)atomicAdd(&static_cast<ScanWorkspace*>(p.scan_ws)->ticket, 1u);
+        *s_arrived = 0;
+    }
+    __syncthreads();
+    const int64_t tile = wave_uniform(*s_tile_base);
+    __syncthreads();
+    return tile;
+}
+
+// Output stage of a fused kernel: chained scan over the workgroup tiles for the dense offsets, padded rows, dense rows and
+// rowptr.  k: the lane's filled slots; load(g, it0): the wave's slots from it0 * 64 on into registers.
+// CHAIN_FIRST (recent policy): the look-back reads come before the wave's padded stores (a load result can only be waited
+// for together with every store issued before it, and a store takes microseconds to be taken).  Uniform policy: the other
+// order measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
+template <bool CHAIN_FIRST, class Load>
+__device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_wave_sum, int32_t* s_arrived,
+                                             int64_t tile, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
+                                             uint32_t f_mul, const Load& load) {
+    ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
+    const int32_t f = p.fanout;
+    const int32_t inc = wave_inclusive_scan(k, lane);
+    auto publish_total = [&](int32_t wg_total) {
+        // the tile total is published at once, so that later tiles can look past this one
+        if (lane == 0 && tile > 0)
+            __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto chain = [&](int32_t wg_total) {      // one wave: look back for the tile's offset, publish the prefix
+        const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
+        if (lane == 0) {
+            __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *s_tile_base = excl;
+        }
+    };
+    auto write_rowptr = [&](int64_t row0) {
+        if (q0 + lane < Q) {
+            __builtin_nontemporal_store(row0 + (inc - k), &p.rowptr[q0 + lane]);
+            if (q0 + lane == Q - 1) {
+                // The last query's tile has looked back over every other tile.  If any wait ran into its bound the dense
+                // rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
+                __threadfence();
+                const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+                const int64_t tot = bad ? 0 : row0 + inc;
+                p.rowptr[Q] = tot;
+                if (p.total_out) *p.total_out = tot;
             }
+        }
+    };
+    auto row_of_wave = [&]() {
+        int32_t off = 0;
+        for (int i = 0; i < wave; ++i) off += s_wave_sum[i];
+        return wave_uniform(*s_tile_base + off);
+    };
+    GatherRegs g;
+    if (f <= kGatherChunk) {
+        // No barrier between a wave's searches and its gather (the lines the searches fetched are then still in the L2): the
+        // waves count themselves in, and the one that arrives last adds up the tile total and publishes it.  Every wave
+        // gathers (one batch of loads) and writes its padded rows, the gathered edges stay in registers; the last wave then
+        // looks back for the tile's offset (the earlier tiles have had the time of a gather to publish their totals), and
+        // only the dense copy waits for it.
+        int is_last = 0;
+        if (lane == kWave - 1) {
+            s_wave_sum[wave] = inc;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            is_last = __hip_atomic_fetch_add(s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == waves_per_wg - 1;
+        }
+        is_last = __shfl(is_last, kWave - 1, kWave);
+        int32_t wg_total = 0;
+        if (is_last) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
+            publish_total(wg_total);
+        }
+        wave_lds_sync();      // what the load reads from LDS was written by this wave's own lanes
+        load(g, 0);
+        if (CHAIN_FIRST && is_last) chain(wg_total);
+        store_padded(g, p, lane, 0, q0, Q);
+        if (!CHAIN_FIRST && is_last) chain(wg_total);
+        lds_barrier();
+        const int64_t row0 = row_of_wave();
+        write_rowptr(row0);
+        store_dense(g, p, f_mul, lane, 0, row0, inc - k);
+    } else {
+        // larger fan-outs: offset first, then gather in batches and write both
+        if (lane == kWave - 1) s_wave_sum[wave] = inc;
+        __syncthreads();
+        if (wave == 0) {
+            int32_t wg_total = 0;
+            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
+            publish_total(wg_total);
+            chain(wg_total);
+        }
+        __syncthreads();
+        const int64_t row0 = row_of_wave();
+        write_rowptr(row0);
+        for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
+            load(g, it0);
+            store_padded(g, p, lane, it0, q0, Q);
+            store_dense(g, p, f_mul, lane, it0, row0, inc - k);
         }
     }
 }

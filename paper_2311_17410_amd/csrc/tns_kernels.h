@@ -77,6 +77,8 @@ size_t compact_workspace_bytes(int64_t Q);
 
 // Both only enqueue kernels on `stream`; they return the first launch error.
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream);
+// The same under the recent policy, a query per lane (tns_kernels_recent.hip); launch_sample forwards to it.
+hipError_t launch_sample_recent(const SampleArgs& a, hipStream_t stream);
 // The same for a store in the prefix layout (tns_kernels_prefix.hip); launch_sample forwards to it.
 hipError_t launch_sample_prefix(const SampleArgs& a, hipStream_t stream);
 // The same with sixteen lanes per query (tns_kernels_team.hip); launch_sample forwards to it by the batch size.

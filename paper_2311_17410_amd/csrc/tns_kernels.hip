@@ -1,5 +1,6 @@
 // gfx950 kernels: temporal neighbourhood sampling (Algorithm 1 of the paper, section 4.2) over
-// the block store of section 4.1, and removal of the padding (section 5).
+// the block store of section 4.1 with a query per lane, uniform policy (the recent policy has a kernel of its own,
+// tns_kernels_recent.hip) and the counting pass of both, and removal of the padding (section 5).
 //
 // Thread mapping.  The paper runs one thread per sampled neighbour with the f threads of a
 // target adjacent.  On a 64-wide wavefront with dependent random reads (node entry -> block
@@ -8,12 +9,12 @@
 //   * the walk runs one query per lane (64 independent chains per wave);
 //   * the node entries are fetched by the wave together, eight lanes per 128-byte line, and
 //     handed to their lanes through LDS;
-//   * each lane leaves the edge positions it selected in LDS (the paper stages candidate
-//     positions in shared memory for uniform sampling; here both policies do);
-//   * the in-block search of the window end (recent policy) and the gather of the selected edges
-//     are done by the whole wave, all loads of a phase issued before the first result is used:
-//     lane l handles flat slot it*64+l of the wave's 64*f slots, so every store instruction
-//     covers 256 consecutive bytes of each output array;
+//   * each lane leaves the edge positions it selected in LDS, as the paper stages candidate
+//     positions in shared memory for uniform sampling; picks on long lists are resolved by the
+//     wave, one (query, slot) per lane;
+//   * the gather of the selected edges is done by the whole wave, all loads of a phase issued
+//     before the first result is used: lane l handles flat slot it*64+l of the wave's 64*f slots,
+//     so every store instruction covers 256 consecutive bytes of each output array;
 //   * with the dense outputs requested, the workgroups pass their dense offsets along a chain
 //     (single-pass scan over tiles) and write the dense rows from registers.
 #include "tns_kernels.h"
@@ -49,21 +50,19 @@ __global__ void __launch_bounds__(256) tns_scan_clear(uint64_t* ws, int64_t word
 
 // FUSED: also removes the padding in the same pass (rowptr and dense arrays), with the tile
 // offsets obtained from a chained scan over the workgroups.
-// Without the scan, recent policy: seven waves per SIMD (72 registers; with six of them 80 and the reads in flight across
-// the host link were too few: 2^24 Zipf(1.1) edges on the host, one query each, 32.0 -> 30.8 ms; in HBM 2^22 queries over
-// blocks of up to 8192 edges 416 -> 372 us, 2^20 over uniform ids 95 -> 97).
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
-__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : (POLICY == 0 && !COUNT ? 7 : 6))
-tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_magic, const int32_t gshift, const uint32_t chunk) {
+__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6)
+tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
+    static_assert(POLICY == 1 || (COUNT && !FUSED), "the recent policy is sampled by tns_sample_recent_kernel");
     // LDS: one chunk per wave.  First the staging area of the node lines (3 KiB), later, in the same bytes,
-    // the wave's rows of selected positions and, behind them, the descriptors of the cooperative search.
+    // the wave's rows of selected positions.
     constexpr bool COOP_NODE = !COUNT;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;      // fused: waves of the tile that have finished their searches
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
+    const int wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
@@ -76,20 +75,8 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
         }
         return;
     }
-    int64_t tile;
-    if (FUSED) {
-        // tiles are numbered in the order workgroups start
-        ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
-        if (threadIdx.x == 0) {
-            s_tile_base = (int64_t)atomicAdd(&ws->ticket, 1u);
-            s_arrived = 0;
-        }
-        __syncthreads();
-        tile = s_tile_base;
-        __syncthreads();
-    } else {
-        tile = p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-    }
+    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
+                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -99,7 +86,7 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
     unsigned char* const my_lds = smem + (size_t)wave * chunk;
     w.s_pos = reinterpret_cast<pos_t*>(my_lds) + (size_t)lane * stride;
     w.edges = p.edges;
-    w.group = (POLICY == 0 && gshift >= 0) ? (1 << gshift) : 0;
+    w.group = POLICY == 0 && f <= kCoopGroup ? kCoopGroup : 0;      // (the byte model counts a search as narrowed and finished together)
     w.te = 0.0f;
     w.tb = 0.0f;
     int32_t n_nodes = 0;
@@ -166,14 +153,13 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
         for (int j = 0; j < kInlineBlocks; ++j) L[j] = line[1 + j];
     }
     auto before_end = [&](float t) { return INCL ? t <= w.te : t < w.te; };
-    // inline list without deleted edges: candidates per block (newest block first), the blocks that contain the window's
-    // end and start, and what is left of the searches in them
-    bool flat = false;
+    // inline list without deleted edges: candidates per block (newest block first) and the blocks that contain the window's
+    // end and start
     int32_t cnt[kInlineBlocks];
     int32_t end_block = -1, cut_new = 0, start_block = -1, b_lo = 0, b_n = 0;
     int64_t b_off = 0;
-    // Candidates of an inline list once b_lo, the edges of start_block before the window's start, is known.  `inside`:
-    // edges of end_block before the window's end (recent policy: 0, that block is dealt with after its search).
+    // Candidates of an inline list once b_lo, the edges of start_block before the window's start, and `inside`, the edges
+    // of end_block before the window's end, are known.
     auto count_flat = [&](int32_t inside) {
         int32_t c = 0;
 #pragma unroll
@@ -192,7 +178,7 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
 #pragma unroll 1
         for (int32_t i = 0; i < k; ++i) {
             int32_t rr = i;               // from the newest candidate
-            if (POLICY == 1 && c > f) rr = c - 1 - (int32_t)pick_rank(p.seed, p.qid_base + q, f, i, (uint64_t)c);
+            if (c > f) rr = c - 1 - (int32_t)pick_rank(p.seed, p.qid_base + q, f, i, (uint64_t)c);
             BlockRec r = {};
             int32_t back = -1;            // slots between the picked edge and the end of its block
 #pragma unroll
@@ -213,12 +199,10 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
         {
             ++n_nodes;
             const int32_t nb = (hd.w & 1) ? 0 : (int32_t)hd.x;      // deleted node: no blocks
-            if (!COUNT && (POLICY == 1 || gshift >= 0) && nb > 0 && nb <= kInlineBlocks && !(hd.w & 2)) {
+            if (!COUNT && nb > 0 && nb <= kInlineBlocks && !(hd.w & 2)) {
                 // Inline list without deleted edges.  At most one block contains the window end and at most one its
-                // start; the others count as a whole or not at all.  Recent policy: the two searches are left to the
-                // wave, narrowed to kCoopGroup slots each.  One search each instead of one per block of the unrolled walk:
-                // 256 graphs of 2^16 edges in one call, windowed, 1.98 -> 1.75 ms; 2^20 queries over uniform ids 116 -> 109 us.
-                flat = true;
+                // start; the others count as a whole or not at all.  One search each instead of one per block of the unrolled
+                // walk: 256 graphs of 2^16 edges in one call, windowed, 1.98 -> 1.75 ms.
 #pragma unroll
                 for (int j = 0; j < kInlineBlocks; ++j) {
                     const BlockRec r = as_rec(L[j]);
@@ -227,21 +211,11 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
                     if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_n = rec_size(r); end_block = j; }
                     if (in && w.tb > r.t_min) { b_off = rec_off(r); b_n = rec_size(r); start_block = j; }
                 }
-                const int32_t rest = POLICY == 1 ? 0 : kCoopGroup;
-                // (without the scan and recent policy one read at a time: of three in flight two are more traffic, 32.0 -> 31.5
-                // ms across the host link)
-                if (FUSED || POLICY == 1) {
-                    narrow4(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
-                    narrow4(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
-                } else {
-                    narrow2(w.d_lo, w.d_n, rest, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
-                    narrow2(b_lo, b_n, rest, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
-                }
-                if (POLICY == 1) {
-                    const int32_t c = count_flat(w.d_lo);
-                    w.k = min(c, f);
-                    fill_flat(c, w.k);
-                }
+                narrow4(w.d_lo, w.d_n, 0, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+                narrow4(b_lo, b_n, 0, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                const int32_t c = count_flat(w.d_lo);
+                w.k = min(c, f);
+                fill_flat(c, w.k);
             } else if (nb > 0 && nb <= kInlineBlocks) {
                 bool go = true;
 #pragma unroll
@@ -360,7 +334,7 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
                 lo[i] = 0; n[i] = 0; g[i] = 0; line[i] = 0; dst[i] = 0;
                 if (it0 + i < f) {
                     const uint32_t s = (uint32_t)((it0 + i) * kWave + lane);
-                    const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+                    const uint32_t ql = query_of_slot(s, f_mul);
                     const int32_t j = (int32_t)(s - ql * (uint32_t)f);
                     const int32_t nbq = __shfl(long_nb, (int)ql, kWave), Lq = __shfl(long_L, (int)ql, kWave), Rq = __shfl(long_R, (int)ql, kWave);
                     line[i] = (uint32_t)__shfl((int)long_dir, (int)ql, kWave);
@@ -432,68 +406,12 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
                 if (n[i] > 0) rows[dst[i]] = slot_pos<pos_t>(rec_off(r[i]) + (g[i] - (int32_t)cb[i]));
         }
     }
-    // Recent policy, stage 1 of the cooperative part: finish the searches the lanes left open.
-    // A group of 16 lanes serves one query: lane j of the group reads the timestamp of slot j of
-    // the query's search window; the number of qualifying slots comes from a ballot.  All loads are
-    // issued before the first result is used, so the wave pays the memory latency once (twice with window starts).
-    int32_t h = 0;               // edges of the searched block that lie before the window end
-    if (POLICY == 0 && gshift >= 0) {
-        constexpr int G = kCoopGroup, groups = kWave / G;
-        unsigned char* extra = my_lds + (size_t)kWave * stride * sizeof(pos_t);
-        // per query: window start (40-bit slot index) with the window size in the upper bits,
-        // the time searched for, and the result
-        uint2* s_q = reinterpret_cast<uint2*>(extra);
-        float* s_t = reinterpret_cast<float*>(extra + (size_t)kWave * sizeof(uint2));
-        int32_t* s_h = reinterpret_cast<int32_t*>(extra + (size_t)kWave * (sizeof(uint2) + sizeof(float)));
-        const int g = lane / G, j = lane % G;
-        auto describe = [&](int64_t slot0, int32_t n, float t) {
-            s_q[lane] = make_uint2((uint32_t)(slot0 & 0xffffffffll), ((uint32_t)(slot0 >> 32) & 0xffu) | ((uint32_t)n << 8));
-            s_t[lane] = t;
-            wave_lds_sync();
-        };
-        // slots of every query's window that lie before the time searched for
-        auto count_before = [&](auto closed) {
-            float t[G];
-#pragma unroll
-            for (int it = 0; it < G; ++it) {
-                const uint2 d = s_q[it * groups + g];
-                t[it] = 0.0f;
-                if (j < (int32_t)(d.y >> 8)) t[it] = time_at<pos_t>(p.edges, (((int64_t)(d.y & 0xffu)) << 32 | d.x) + j);
-            }
-#pragma unroll
-            for (int it = 0; it < G; ++it) {
-                const int32_t n = (int32_t)(s_q[it * groups + g].y >> 8);
-                const float x = s_t[it * groups + g];
-                const uint64_t m = __ballot(j < n && (decltype(closed)::value ? t[it] <= x : t[it] < x));
-                if (j == 0) s_h[it * groups + g] = __popcll((m >> (g * G)) & ((1ull << G) - 1));
-            }
-            wave_lds_sync();
-            return s_h[lane];
-        };
-        if (__ballot(b_n > 0)) {
-            describe(b_off + b_lo, b_n, w.tb);
-            b_lo += count_before(std::false_type{});
-            wave_lds_sync();
-        }
-        if (flat) {
-            // the blocks older than the one with the window's end; that one's edges are put in front below
-            const int32_t c = count_flat(0);
-            w.k = min(c, f);
-            fill_flat(c, w.k);
-        }
-        describe(w.d_off + w.d_lo, w.d_n, w.te);
-        const int32_t found = count_before(std::integral_constant<bool, INCL>{});
-        if (w.d_off >= 0) h = w.d_lo + found;
-    }
-    // candidates of that block: those before the window's start, where it lies in the same block, do not count
-    const int32_t h_cnt = flat && start_block == end_block ? max(h - b_lo, 0) : h;
-    const int32_t k = POLICY == 0 ? min(f, h_cnt + w.k) : w.k;
-    if (POLICY == 0 && h_cnt > 0) {
-        // The first min(h_cnt, f) slots come from the block whose search the wave finished (newest
-        // first); the positions recorded from older blocks move up behind them.
-        const int32_t hh = min(h_cnt, f);
-        for (int32_t j = k - 1; j >= hh; --j) w.s_pos[j] = w.s_pos[j - hh];
-        for (int32_t j = 0; j < hh; ++j) w.s_pos[j] = slot_pos<pos_t>(w.d_off + h - 1 - j);
+    int32_t k = w.k;
+    if (COUNT && POLICY == 0 && w.d_off >= 0) {
+        // the slots of the window's last block that the search left open
+        int32_t h = w.d_lo;
+        for (int32_t i = 0; i < w.d_n; ++i) h += before_end(time_at<pos_t>(p.edges, w.d_off + w.d_lo + i)) ? 1 : 0;
+        k = min(f, h + w.k);
     }
     if (COUNT) {
         // totals of what this launch reads: node entries, block records, timestamp probes, edges
@@ -509,101 +427,15 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mag
     }
     const pos_t* __restrict__ w_pos = reinterpret_cast<const pos_t*>(my_lds);
 
+    auto load = [&](GatherRegs& g, int32_t it0) { gather_load<pos_t, POLICY == 1>(g, p, f_mul, stride, w_pos, lane, it0, k); };
     if (FUSED) {
-        // Chained scan over the workgroup tiles for the dense offsets.
-        ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
-        const int32_t inc = wave_inclusive_scan(k, lane);
-        auto publish_total = [&](int32_t wg_total) {
-            // the tile total is published at once, so that later tiles can look past this one
-            if (lane == 0 && tile > 0)
-                __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        auto chain = [&](int32_t wg_total) {      // one wave: look back for the tile's offset, publish the prefix
-            const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
-            if (lane == 0) {
-                __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                s_tile_base = excl;
-            }
-        };
-        auto write_rowptr = [&](int64_t row) {
-            if (q < Q) {
-                __builtin_nontemporal_store(row, &p.rowptr[q]);
-                if (q == Q - 1) {
-                    // The last query's tile has looked back over every other tile.  If any wait ran into
-                    // its bound the dense rows are not valid: the total then reads 0, so that a hop chained
-                    // to this one has no queries.
-                    __threadfence();
-                    const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                    const int64_t tot = bad ? 0 : row + k;
-                    p.rowptr[Q] = tot;
-                    if (p.total_out) *p.total_out = tot;
-                }
-            }
-        };
-        auto offset_of_wave = [&]() {
-            int32_t off = 0;
-            for (int i = 0; i < wave; ++i) off += s_wave_sum[i];
-            return off;
-        };
-        GatherRegs g;
-        if (f <= kGatherChunk) {
-            // No barrier between a wave's searches and its gather (the lines the searches fetched are
-            // then still in the L2): the waves count themselves in, and the one that arrives last
-            // adds up the tile total and publishes it.  Every wave gathers (one batch of loads) and
-            // writes its padded rows, the gathered edges stay in registers; the last wave then looks
-            // back for the tile's offset (the earlier tiles have had the time of a gather to publish
-            // their totals), and only the dense copy waits for it.
-            int is_last = 0;
-            if (lane == kWave - 1) {
-                s_wave_sum[wave] = inc;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                is_last = __hip_atomic_fetch_add(&s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == waves_per_wg - 1;
-            }
-            is_last = __shfl(is_last, kWave - 1, kWave);
-            int32_t wg_total = 0;
-            if (is_last) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-                publish_total(wg_total);
-            }
-            wave_lds_sync();      // the positions were written by this wave's own lanes
-            gather_load<pos_t, POLICY == 1>(g, p, f_magic, stride, w_pos, lane, 0, k);
-            // Recent policy: the look-back reads come before this wave's stores (a load result can only be
-            // waited for together with every store issued before it).  Uniform policy: the other order
-            // measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
-            if (is_last && POLICY == 0) chain(wg_total);
-            store_padded(g, p, f_magic, lane, 0, q0, Q);
-            if (is_last && POLICY != 0) chain(wg_total);
-            lds_barrier();
-            const int64_t row = s_tile_base + offset_of_wave() + (inc - k);
-            write_rowptr(row);
-            store_dense(g, p, f_magic, lane, 0, row);
-        } else {
-            // larger fan-outs: offset first, then gather in batches and write both
-            if (lane == kWave - 1) s_wave_sum[wave] = inc;
-            __syncthreads();
-            int32_t wg_total = 0;
-            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-            if (wave == 0) {
-                publish_total(wg_total);
-                chain(wg_total);
-            }
-            __syncthreads();
-            const int64_t row = s_tile_base + offset_of_wave() + (inc - k);
-            write_rowptr(row);
-            for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
-                gather_load<pos_t, POLICY == 1>(g, p, f_magic, stride, w_pos, lane, it0, k);
-                store_padded(g, p, f_magic, lane, it0, q0, Q);
-                store_dense(g, p, f_magic, lane, it0, row);
-            }
-        }
+        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         wave_lds_sync();
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
-            gather_load<pos_t, POLICY == 1>(g, p, f_magic, stride, w_pos, lane, it0, k);
-            store_padded(g, p, f_magic, lane, it0, q0, Q);
+            load(g, it0);
+            store_padded(g, p, lane, it0, q0, Q);
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
@@ -734,17 +566,12 @@ template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
 hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
     const int32_t stride = a.fanout | 1;                                    // odd: conflict-free per-lane rows
     const size_t per_wave = (size_t)kWave * stride * sizeof(pos_t);
-    // The fused variant uses large workgroups under the recent policy: one chained-scan step per 1024
-    // queries keeps the rate at which tiles publish their totals low enough for the look-back to keep
-    // up.  Under the uniform policy the waves of a tile finish far apart (two walks, per-lane searches)
-    // and wait for each other before the dense copy, so small tiles win there (C5: 36.5 ms with 16
-    // waves, 32.6 with 8, 31.3 with 4, 34.1 with 2).
-    // recent policy with fan-out <= 16: the wave finishes the in-block searches together
-    // (16 more bytes of LDS per query); otherwise each lane searches alone
-    int32_t gshift = (POLICY == 0 && a.fanout <= kCoopGroup) ? 4 : -1;
-    // per wave: position rows + search descriptors, and at least the 3 KiB in which the node lines are staged first
-    const size_t chunk = std::max<size_t>(per_wave + (gshift >= 0 ? (size_t)kWave * 16 : 0), COUNT ? 0 : 3072);
-    int waves = (int)std::min<size_t>(FUSED ? (POLICY == 1 ? 4 : 16) : 4, std::max<size_t>(1, (62u << 10) / chunk));
+    // per wave: the position rows, and at least the 3 KiB in which the node lines are staged first
+    const size_t chunk = std::max<size_t>(per_wave, COUNT ? 0 : 3072);
+    // With the padding removal fused in, a workgroup is a tile of the chained scan.  Under the uniform policy the waves of a
+    // tile finish far apart (searches and picks) and wait for each other before the dense copy, so small tiles win (C5:
+    // 36.5 ms with 16 waves, 32.6 with 8, 31.3 with 4, 34.1 with 2).
+    int waves = (int)std::min<size_t>(4, std::max<size_t>(1, (62u << 10) / chunk));
     // small batches: smaller workgroups, so that the queries spread over the compute units instead of
     // queueing at the address units of a few
     while (waves > 1 && (a.Q + (int64_t)waves * kWave - 1) / ((int64_t)waves * kWave) < 512) waves >>= 1;
@@ -761,7 +588,7 @@ hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
     SampleArgs b = a;
     if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
     hipLaunchKernelGGL((tns_sample_kernel<POLICY, INCL, pos_t, COUNT, FUSED>), dim3((unsigned)grid), dim3(waves * kWave),
-                       lds, stream, b, stride, magic_for(a.fanout), gshift, (uint32_t)chunk);
+                       lds, stream, b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
     return hipGetLastError();
 }
 
@@ -803,8 +630,8 @@ hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
           : (wide ? launch_sample_t<POL, false, int64_t, CNT, FUS>(a, stream)                \
                   : launch_sample_t<POL, false, int32_t, CNT, FUS>(a, stream)))
     if (a.counters) return a.policy == 0 ? TNS_DISPATCH(0, true, false) : TNS_DISPATCH(1, true, false);
-    if (a.scan_ws) return a.policy == 0 ? TNS_DISPATCH(0, false, true) : TNS_DISPATCH(1, false, true);
-    return a.policy == 0 ? TNS_DISPATCH(0, false, false) : TNS_DISPATCH(1, false, false);
+    if (a.policy == 0) return launch_sample_recent(a, stream);
+    return a.scan_ws ? TNS_DISPATCH(1, false, true) : TNS_DISPATCH(1, false, false);
 #undef TNS_DISPATCH
 }
 

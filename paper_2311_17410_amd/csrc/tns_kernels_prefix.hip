@@ -107,7 +107,7 @@ __device__ __forceinline__ void ext_process(const ExtBatch& x, unsigned char* re
 // Output stage, fan-outs up to ten: every query's edges are in its result row by now (fast-path queries at a
 // rotated row position, queries that walked at position j after walked_gather).  info = k | rot << 8 of the
 // lane's own query.  No memory loads here: the stores that follow go out back to back.
-__device__ __forceinline__ void rows_load(GatherRegs& g, const SampleArgs& p, uint32_t f_magic, const uint32_t* rows,
+__device__ __forceinline__ void rows_load(GatherRegs& g, const SampleArgs& p, uint32_t f_mul, const uint32_t* rows,
                                           int rs, int lane, int32_t info) {
     const int32_t f = p.fanout;
 #pragma unroll
@@ -115,7 +115,7 @@ __device__ __forceinline__ void rows_load(GatherRegs& g, const SampleArgs& p, ui
         g.nbr[i] = -1; g.eid[i] = -1; g.ts[i] = 0.0f;
         if (i < f) {
             const uint32_t s = (uint32_t)(i * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+            const uint32_t ql = query_of_slot(s, f_mul);
             const int32_t j = (int32_t)(s - ql * (uint32_t)f);
             const int32_t inf = __shfl(info, (int)ql, kWave);
             if (j < (inf & 0xff)) {
@@ -135,7 +135,7 @@ __device__ __forceinline__ void rows_load(GatherRegs& g, const SampleArgs& p, ui
 // and puts them into the rows, slot j at row position j, where rows_load expects them.  All positions
 // are read before the first edge is written, so the two may overlap in the row.
 template <typename pos_t>
-__device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_magic, uint32_t* rows, int rs, int lane,
+__device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_mul, uint32_t* rows, int rs, int lane,
                                               int32_t winfo /* walked ? k : 0 of the lane's own query */) {
     const int32_t f = p.fanout;
     bool filled[kGatherChunk];
@@ -146,7 +146,7 @@ __device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_ma
         raw[i].ts = 0.0f; raw[i].nbr = -1; raw[i].eid = -1;
         if (i < f) {
             const uint32_t s = (uint32_t)(i * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+            const uint32_t ql = query_of_slot(s, f_mul);
             const int32_t j = (int32_t)(s - ql * (uint32_t)f);
             filled[i] = j < __shfl(winfo, (int)ql, kWave);
             const uint64_t m = __ballot(filled[i]);       // empty slots read what the first filled one reads
@@ -165,7 +165,7 @@ __device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_ma
     for (int i = 0; i < kGatherChunk; ++i) {
         if (i < f && filled[i]) {
             const uint32_t s = (uint32_t)(i * kWave + lane);
-            const uint32_t ql = div_by(s, (uint32_t)f, f_magic);
+            const uint32_t ql = query_of_slot(s, f_mul);
             const int32_t j = (int32_t)(s - ql * (uint32_t)f);
             uint32_t* dst = rows + ql * (uint32_t)rs + 3 * j;
             dst[0] = __float_as_uint(raw[i].ts);
@@ -179,7 +179,7 @@ __device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_ma
 // Uniform policy: workgroups of at most eight waves, three of them per compute unit (80 registers; at 85, with two of
 // them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459).
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
-__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_magic,
+__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_mul,
                                                                  const int32_t gshift, const uint32_t chunk,
                                                                  const uint32_t rows_bytes) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
+    const int wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
@@ -201,19 +201,8 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         }
         return;
     }
-    int64_t tile;
-    if (FUSED) {
-        ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
-        if (threadIdx.x == 0) {
-            s_tile_base = (int64_t)atomicAdd(&ws->ticket, 1u);
-            s_arrived = 0;
-        }
-        __syncthreads();
-        tile = s_tile_base;
-        __syncthreads();
-    } else {
-        tile = p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
-    }
+    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
+                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -544,105 +533,24 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
     const int32_t pstride = (int32_t)(rs * 4 / (int)sizeof(pos_t));     // row stride in positions
     const pos_t* __restrict__ w_pos = reinterpret_cast<const pos_t*>(rows);
     wave_lds_sync();      // rows were written by this wave's own lanes
-    if (row_path && __ballot(walked && k > 0)) walked_gather<pos_t>(p, f_magic, rows, rs, lane, walked ? k : 0);
+    if (row_path && __ballot(walked && k > 0)) walked_gather<pos_t>(p, f_mul, rows, rs, lane, walked ? k : 0);
 
     // ---- outputs --------------------------------------------------------------------------------------
+    auto load = [&](GatherRegs& g, int32_t it0) {
+        if (row_path) rows_load(g, p, f_mul, rows, rs, lane, info);
+        else gather_load<pos_t, POLICY == 1>(g, p, f_mul, pstride, w_pos, lane, it0, k);      // positions in the rows
+    };
     if (FUSED) {
-        ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
-        const int32_t inc = wave_inclusive_scan(k, lane);
-        auto publish_total = [&](int32_t wg_total) {
-            // the tile total is published at once, so that later tiles can look past this one
-            if (lane == 0 && tile > 0)
-                __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        auto chain = [&](int32_t wg_total) {      // one wave: look back for the tile's offset, publish the prefix
-            const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
-            if (lane == 0) {
-                __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                s_tile_base = excl;
-            }
-        };
-        auto write_rowptr = [&](int64_t row) {
-            if (q < Q) {
-                __builtin_nontemporal_store(row, &p.rowptr[q]);
-                if (q == Q - 1) {
-                    __threadfence();
-                    const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                    const int64_t tot = bad ? 0 : row + k;
-                    p.rowptr[Q] = tot;
-                    if (p.total_out) *p.total_out = tot;
-                }
-            }
-        };
-        auto offset_of_wave = [&]() {
-            int32_t off = 0;
-            for (int i = 0; i < wave; ++i) off += s_wave_sum[i];
-            return off;
-        };
-        GatherRegs g;
-        if (f <= kGatherChunk) {
-            // as in the other kernel: the waves count themselves in, the last one publishes the tile total,
-            // every wave writes its padded rows, then the last wave looks back and only the dense copy waits
-            int is_last = 0;
-            if (lane == kWave - 1) {
-                s_wave_sum[wave] = inc;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                is_last = __hip_atomic_fetch_add(&s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == waves_per_wg - 1;
-            }
-            is_last = __shfl(is_last, kWave - 1, kWave);
-            int32_t wg_total = 0;
-            if (is_last) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-                publish_total(wg_total);
-            }
-            if (row_path) rows_load(g, p, f_magic, rows, rs, lane, info);
-            else gather_load<pos_t, POLICY == 1>(g, p, f_magic, pstride, w_pos, lane, 0, k);
-            // Recent policy: the look-back reads come before this wave's stores (a load result can only be
-            // waited for together with every store issued before it, and a store takes microseconds to be
-            // taken).  Uniform policy: the other order measured faster, as in the other kernel.
-            if (is_last && POLICY == 0) chain(wg_total);
-            store_padded(g, p, f_magic, lane, 0, q0, Q);
-            if (is_last && POLICY != 0) chain(wg_total);
-            lds_barrier();
-            const int64_t row = s_tile_base + offset_of_wave() + (inc - k);
-            write_rowptr(row);
-            store_dense(g, p, f_magic, lane, 0, row);
-        } else {
-            if (lane == kWave - 1) s_wave_sum[wave] = inc;
-            __syncthreads();
-            int32_t wg_total = 0;
-            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-            if (wave == 0) {
-                publish_total(wg_total);
-                chain(wg_total);
-            }
-            __syncthreads();
-            const int64_t row = s_tile_base + offset_of_wave() + (inc - k);
-            write_rowptr(row);
-            for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {      // larger fan-outs: positions in the rows
-                gather_load<pos_t, POLICY == 1>(g, p, f_magic, pstride, w_pos, lane, it0, k);
-                store_padded(g, p, f_magic, lane, it0, q0, Q);
-                store_dense(g, p, f_magic, lane, it0, row);
-            }
-        }
+        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
-        if (row_path) {
-            rows_load(g, p, f_magic, rows, rs, lane, info);
-            store_padded(g, p, f_magic, lane, 0, q0, Q);
-        } else {
-            for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
-                gather_load<pos_t, POLICY == 1>(g, p, f_magic, pstride, w_pos, lane, it0, k);
-                store_padded(g, p, f_magic, lane, it0, q0, Q);
-            }
+        for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
+            load(g, it0);
+            store_padded(g, p, lane, it0, q0, Q);
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
 }
-
-inline uint32_t magic_of(int32_t f) { return f <= 1 ? 0u : (uint32_t)(((uint64_t(1) << 32) + (uint64_t)f - 1) / (uint64_t)f); }
 
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
 hipError_t launch_prefix_t(const SampleArgs& a, hipStream_t stream) {
@@ -680,7 +588,7 @@ hipError_t launch_prefix_t(const SampleArgs& a, hipStream_t stream) {
     auto kern = tns_sample_prefix_kernel<POLICY, INCL, pos_t, COUNT, FUSED>;
     SampleArgs b = a;
     if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b, rs, magic_of(f), gshift, (uint32_t)chunk,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b, rs, slot_multiplier(f), gshift, (uint32_t)chunk,
                        (uint32_t)rows_bytes);
     return hipGetLastError();
 }

@@ -1,0 +1,359 @@
+// gfx950 sampling kernel for the recent policy over the default layout, batches that fill the chip: Algorithm 1 of the
+// paper (section 4.2), the padded write, and the padding removal of section 5 fused in when the dense outputs are wanted.
+//
+// One query per lane, as in tns_kernels.hip (64 independent chains of dependent reads per wave).  What paces the kernel is
+// the length of a wave's program, not the memory: time stamps in it, for 2^16 queries over each of 256 graphs with a
+// window, gave 3.4 us for the node lines and 9.9 for the searches, the positions and the waits between them, and 7 of
+// every 27 us a wave spent waiting for the slowest one of its tile.  So the steps are arranged to be short and free of
+// waits on one another:
+//   node      the wave fetches the 128-byte node lines together, eight lanes per line, and hands them over through LDS
+//   blocks    each lane finds, among its up to seven records in registers, the blocks that count as a whole, the one with
+//             the window's end and the one with its start
+//   search    the lanes that have such a block ask for its timestamps; requests of both kinds are numbered over the wave
+//             and served together, sixteen lanes per request and 32 requests in flight, so that steps nobody needs cost
+//             nothing and a window costs no second round trip
+//   table     each lane leaves in LDS, per block, where its newest candidate lies, and the number of candidates before each
+//             block packed into bytes: nothing per slot and no loop over slots
+//   gather    lane l takes flat slot it * 64 + l of the wave's 64 f slots, finds the slot's block by comparing all bytes
+//             at once, and loads the edge; five such loads are prepared side by side
+// Against the kernel in which every lane wrote its slots' positions itself, after two rounds of searches for all 64 queries:
+// 256 graphs of 2^16 queries, windowed, 1737 -> 1502 us; 2^22 queries over uniform ids 426 -> 372; 2^26 6624 -> 6236, which is
+// 6 TB/s of lines and rows and what the memory gives.
+// Nodes with long lists (directory runs) or with deleted edges take the walk of Algorithm 1 lane by lane instead; their
+// row of the table holds one entry per slot.
+#include <algorithm>
+#include <type_traits>
+
+#include "tns_device.h"
+#include "tns_kernels.h"
+
+namespace tns {
+namespace {
+
+constexpr int kRequestBatch = 8;                                   // search loads in flight: 32 requests
+constexpr int kGroups = kWave / kCoopGroup;                        // requests per search load
+constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes of the packed counts, and their compare bit
+
+// What the gathering lanes need to know about a query.  Byte i - 1 of `lo` (i = 1..3) and i - 4 of `hi` (i = 4..6): 64
+// minus the candidates before block i (at most 64): added to a slot number of 0..63 it reaches 64 where the slot lies in
+// block i or an older one.  Top byte of `lo`: filled slots; of `hi`: 1 if the row holds an entry per slot.
+struct SlotHead { uint32_t lo, hi; };
+
+template <bool INCL, typename pos_t, bool FUSED>
+__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6)
+tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int64_t s_tile_base;
+    __shared__ int32_t s_wave_sum[16];
+    __shared__ int32_t s_arrived;      // fused: waves of the tile that have finished their searches
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = wave_uniform((int32_t)(threadIdx.x >> 6));
+    const int waves_per_wg = blockDim.x >> 6;
+
+    // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
+    // have none leave before they take a ticket (18 ns each)
+    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
+            p.rowptr[0] = 0;
+            if (p.total_out) *p.total_out = 0;
+        }
+        return;
+    }
+    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
+                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
+    const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
+    const int64_t q = q0 + lane;
+    const int32_t f = p.fanout;
+    // LDS of the wave: the staging area of the node lines (4 KiB); later, in the same bytes, the rows of the table and
+    // behind them the search requests and their results, whose place the slot heads take
+    unsigned char* const my_lds = smem + (size_t)wave * chunk;
+    pos_t* const rows = reinterpret_cast<pos_t*>(my_lds);
+    uint4* const requests = reinterpret_cast<uint4*>(my_lds + (size_t)kWave * stride * sizeof(pos_t));
+    SlotHead* const heads = reinterpret_cast<SlotHead*>(requests);
+    unsigned char* const found = reinterpret_cast<unsigned char*>(requests + 2 * kWave);
+
+    Walk<0, INCL, pos_t, true> w;
+    w.f = f;
+    w.s_pos = rows + (size_t)lane * stride;
+    w.edges = p.edges;
+    w.group = kCoopGroup;
+    w.te = 0.0f;
+    w.tb = 0.0f;
+    const int32_t inst = p.inst_rowptr ? instance_of(p.inst_rowptr, p.num_instances, q0, q, Q, lane) : 0;
+    uint32_t node = ~0u;               // the target's entry in the node table (a table of 2^32 lines does not exist)
+    if (q < Q) {
+        const int32_t v = __builtin_nontemporal_load(&p.targets[q0 + lane]);
+        w.te = __builtin_nontemporal_load(&p.t_end[q0 + lane]);
+        w.tb = p.t_start ? p.t_start[q0 + lane] : (p.delta == INFINITY ? -INFINITY : w.te - p.delta);
+        bool ok = (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
+        if (p.inst_rowptr) ok = ok && inst < p.num_instances;
+        if (ok) node = (uint32_t)(inst * p.num_nodes + v);
+    }
+    // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
+    uint4 hd = make_uint4(0u, 0u, 0u, 0u);
+    uint4 L[kInlineBlocks];
+    {
+        // Eight lanes fetch one query's line with one instruction (16 bytes each), eight queries per instruction; the
+        // pieces reach their owner through LDS.  One request per line lets the loads carry the non-temporal hint: a
+        // node line is used once and should not push edge lines out of the L2.
+        const int piece = lane & 7, sub = lane >> 3;
+        const unsigned char* const table = reinterpret_cast<const unsigned char*>(p.nodes) + piece * 16;
+        uint32_t src[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) src[i] = (uint32_t)__shfl((int)node, i * 8 + sub, kWave);
+        u32x4 R[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)       // (a query without a node reads the first line and drops it: no load sits in a branch)
+            R[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(table + (uint64_t)(src[i] == ~0u ? 0u : src[i]) * 128u));
+        // in two rounds of 32 queries; 16-byte pieces are swizzled by the query number so that neither the writes nor
+        // the reads collide on banks
+        u32x4 P[8];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ql = i * 8 + sub;
+                *reinterpret_cast<u32x4*>(my_lds + ql * 128 + ((piece ^ (ql & 7)) << 4)) = R[r * 4 + i];
+            }
+            wave_lds_sync();
+            if ((lane >> 5) == r) {
+                const int ql = lane & 31;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) P[j] = *reinterpret_cast<const u32x4*>(my_lds + ql * 128 + ((j ^ (ql & 7)) << 4));
+            }
+            wave_lds_sync();
+        }
+        if (node != ~0u) hd = make_uint4(P[0].x, P[0].y, P[0].z, P[0].w);
+#pragma unroll
+        for (int j = 0; j < kInlineBlocks; ++j) L[j] = make_uint4(P[1 + j].x, P[1 + j].y, P[1 + j].z, P[1 + j].w);
+    }
+    auto before_end = [&](float t) { return INCL ? t <= w.te : t < w.te; };
+    const int32_t nb = (hd.w & 1) ? 0 : (int32_t)hd.x;              // deleted node: no blocks
+    const bool flat = nb <= kInlineBlocks && !(hd.w & 2);
+    // ---- blocks: inline list without deleted edges -----------------------------------------------------
+    // At most one block contains the window's end and at most one its start; the others count as a whole or not at all.
+    // Of those two the first and the last edge are known to lie on different sides, the slots between are searched.
+    int32_t cnt[kInlineBlocks];        // candidates
+    pos_t end_slot[kInlineBlocks];     // slot behind the newest one
+    int32_t end_block = -1, start_block = -1, b_lo = 0, b_n = 0;
+    int64_t b_off = 0;
+#pragma unroll
+    for (int j = 0; j < kInlineBlocks; ++j) {
+        const BlockRec r = as_rec(L[j]);
+        const bool in = flat && j < nb && before_end(r.t_min) && !(w.tb > r.t_max);
+        const int32_t size = rec_size(r);
+        cnt[j] = in ? size : 0;
+        end_slot[j] = (pos_t)(rec_off(r) + size);
+        if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_lo = 1; w.d_n = size - 2; end_block = j; }
+        if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; }
+    }
+    if (!flat) {
+        // ---- long lists, nodes with deleted edges: Algorithm 1 block by block --------------------------
+        if (nb <= kInlineBlocks) {
+            bool go = true;
+#pragma unroll 1
+            for (int32_t j = 0; j < nb && go; ++j) go = w.step(p.nodes[node].rec[j], j);
+        } else {
+            // all records of the node, oldest first, in one run of the directory; the newest block that starts before the
+            // window end is searched for instead of stepping through the newer ones one by one
+            const int64_t d0 = (int64_t)hd.z * kDirAlign;
+            if (d0 + nb <= p.num_dir) {
+                const BlockRec* __restrict__ d = p.dir + d0;
+                int32_t lo = 0, n = nb;
+                if (FUSED) narrow4(lo, n, 0, [&](int32_t i) { return before_end(d[i].t_min); });
+                else narrow2(lo, n, 0, [&](int32_t i) { return before_end(d[i].t_min); });
+                bool go = true;
+                for (int32_t j = lo - 1; j >= 0 && go; --j) go = w.step(d[j], lo - 1 - j);
+            }
+        }
+    } else if (FUSED) {
+        narrow4(w.d_lo, w.d_n, kCoopGroup, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+        narrow4(b_lo, b_n, kCoopGroup, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+    } else {
+        // (without the scan one read at a time: of three in flight two are more traffic, 32.0 -> 31.5 ms across the host link)
+        narrow2(w.d_lo, w.d_n, kCoopGroup, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+        narrow2(b_lo, b_n, kCoopGroup, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+    }
+    // ---- search ------------------------------------------------------------------------------------------
+    // A request: the edge line and the position in it where at most 16 slots start, their number, the time; sixteen lanes
+    // read the timestamps of one request side by side and a ballot counts those before the time.
+    const uint64_t ask_end = __ballot(w.d_n > 0), ask_start = __ballot(b_n > 0);
+    const int num_end = __popcll(ask_end), num_requests = num_end + __popcll(ask_start);
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int my_end = __popcll(ask_end & below), my_start = num_end + __popcll(ask_start & below);
+    if (num_requests > 0) {
+        auto request = [&](int r, int64_t slot0, int32_t n, float t, uint32_t closed) {
+            const uint64_t line = sizeof(pos_t) == 8 ? (uint64_t)slot0 / (uint32_t)kSlotsPerLine : (uint32_t)slot0 / (uint32_t)kSlotsPerLine;
+            const uint32_t at = (uint32_t)slot0 - (uint32_t)line * (uint32_t)kSlotsPerLine;
+            requests[r] = make_uint4((uint32_t)line, __float_as_uint(t), at | (uint32_t)n << 8 | closed << 16, 0u);
+        };
+        if (w.d_n > 0) request(my_end, w.d_off + w.d_lo, w.d_n, w.te, INCL ? 1u : 0u);
+        if (b_n > 0) request(my_start, b_off + b_lo, b_n, w.tb, 0u);
+        wave_lds_sync();
+        const int g = lane / kCoopGroup, j = lane % kCoopGroup;
+#pragma unroll 1
+        for (int r0 = 0; r0 < num_requests; r0 += kRequestBatch * kGroups) {
+            uint32_t par[kRequestBatch];
+            float at[kRequestBatch], t[kRequestBatch];
+#pragma unroll
+            for (int i = 0; i < kRequestBatch; ++i) {
+                // (beyond the last request: the last one again, its lines are on their way anyway)
+                const uint4 d = requests[min(r0 + i * kGroups + g, num_requests - 1)];
+                par[i] = d.z;
+                at[i] = __uint_as_float(d.y);
+                const uint32_t s = (d.z & 0xffu) + (uint32_t)min(j, (int)((d.z >> 8) & 0xffu) - 1);     // below 25
+                const uint32_t lines = (s * 205u) >> 11;                                                 // s / kSlotsPerLine
+                t[i] = __uint_as_float(p.edges[(uint64_t)d.x * 32u + (3u * s + 2u * lines)]);
+            }
+#pragma unroll
+            for (int i = 0; i < kRequestBatch; ++i) {
+                const bool first = j < (int)((par[i] >> 8) & 0xffu) && (t[i] < at[i] || (INCL && (par[i] >> 16) && t[i] == at[i]));
+                const uint32_t c = (uint32_t)__popc((uint32_t)(__ballot(first) >> (g * kCoopGroup)) & 0xffffu);
+                found[min(r0 + i * kGroups + g, num_requests - 1)] = (unsigned char)c;
+            }
+        }
+        wave_lds_sync();
+    }
+    int32_t h = w.d_lo;                // edges of the block with the window's end that lie before it
+    if (w.d_n > 0) h += found[my_end];
+    if (b_n > 0) b_lo += found[my_start];
+    wave_lds_sync();                   // the heads take the place of the requests
+    // ---- table -------------------------------------------------------------------------------------------
+    int32_t k;
+    SlotHead head{kFlagBytes, kFlagBytes};
+    if (flat) {
+        pos_t* const row = rows + (size_t)lane * stride;
+        int32_t cum = 0;
+        uint32_t before[kInlineBlocks];
+#pragma unroll
+        for (int j = 0; j < kInlineBlocks; ++j) {
+            pos_t e = end_slot[j];
+            int32_t c = cnt[j];
+            if (j == end_block) { e += (pos_t)(h - c); c = h; }
+            if (j == start_block) c = max(c - b_lo, 0);
+            before[j] = (uint32_t)min(cum, kWave);
+            row[j] = e - 1 + (pos_t)cum;               // minus the slot's number: where its edge lies
+            cum += c;
+        }
+        k = min(cum, f);
+        head.lo -= before[1] | before[2] << 8 | before[3] << 16;
+        head.hi -= before[4] | before[5] << 8 | before[6] << 16;
+    } else {
+        // the first hh slots come from the block whose search the wave finished (newest first); the entries recorded
+        // from older blocks move up behind them
+        const int32_t hh = w.d_off >= 0 ? min(h, f) : 0;
+        k = min(f, hh + w.k);
+        for (int32_t j = k - 1; j >= hh; --j) w.s_pos[j] = w.s_pos[j - hh] + (pos_t)hh;
+        for (int32_t j = 0; j < hh; ++j) w.s_pos[j] = (pos_t)(w.d_off + h - 1);
+        head.hi |= 1u << 24;
+    }
+    head.lo |= (uint32_t)k << 24;
+    heads[lane] = head;
+    wave_lds_sync();
+    // ---- gather and outputs --------------------------------------------------------------------------------
+    // Slots [it0 * 64, (it0 + kGatherChunk) * 64) of the wave, prepared in groups of kGatherGroup.  An empty slot reads what
+    // the first filled one of its instruction reads (one request for both; a fixed address instead would make one memory
+    // channel everybody's).
+    auto load = [&](GatherRegs& g, int32_t it0) {
+        bool filled[kGatherChunk];
+        Edge raw[kGatherChunk];
+#pragma unroll
+        for (int i0 = 0; i0 < kGatherChunk; i0 += kGatherGroup) {
+            if (it0 + i0 >= f) {                       // uniform over the wave
+#pragma unroll
+                for (int i = i0; i < i0 + kGatherGroup; ++i) { filled[i] = false; raw[i] = Edge{0.0f, -1, -1}; }
+                continue;
+            }
+            SlotHead sh[kGatherGroup];
+            uint32_t ql[kGatherGroup], no[kGatherGroup];
+            pos_t e[kGatherGroup];
+#pragma unroll
+            for (int u = 0; u < kGatherGroup; ++u) {
+                const uint32_t s = (uint32_t)((it0 + i0 + u) * kWave + lane);
+                ql[u] = min(query_of_slot(s, f_mul), (uint32_t)kWave - 1u);      // (the last group may reach beyond the last slot)
+                no[u] = s - ql[u] * (uint32_t)f;
+                sh[u] = heads[ql[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kGatherGroup; ++u) {
+                const uint32_t each = no[u] * 0x010101u;
+                uint32_t b = (uint32_t)(__popc((each + sh[u].lo) & kFlagBytes) + __popc((each + sh[u].hi) & kFlagBytes));
+                if (sh[u].hi >> 24) b = no[u];
+                filled[i0 + u] = no[u] < (sh[u].lo >> 24);
+                e[u] = rows[ql[u] * (uint32_t)stride + (filled[i0 + u] ? b : 0u)];
+            }
+#pragma unroll
+            for (int u = 0; u < kGatherGroup; ++u) {
+                const uint64_t m = __ballot(filled[i0 + u]);
+                const pos_t own = e[u] - (pos_t)no[u];
+                const pos_t other = m ? wave_read(own, __builtin_ctzll(m)) : (pos_t)0;
+                const auto pos = (typename index_of<pos_t>::type)slot_pos<pos_t>(filled[i0 + u] ? own : other);
+                raw[i0 + u] = *reinterpret_cast<const Edge*>(p.edges + pos);
+            }
+        }
+        // every load of the batch has returned before the first store is issued: the stores that follow then go out back
+        // to back without waiting for one another
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0) only
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kGatherChunk; ++i) {
+            g.nbr[i] = filled[i] ? raw[i].nbr : -1;
+            g.eid[i] = filled[i] ? raw[i].eid : -1;
+            g.ts[i] = filled[i] ? raw[i].ts : 0.0f;
+        }
+    };
+    if (FUSED) {
+        fused_output<true>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+    } else {
+        GatherRegs g;
+        for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
+            load(g, it0);
+            store_padded(g, p, lane, it0, q0, Q);
+        }
+    }
+    if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
+}
+
+template <bool INCL, typename pos_t, bool FUSED>
+hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
+    const int32_t stride = std::max(a.fanout, kInlineBlocks) | 1;                // odd: conflict-free per-lane rows
+    // per wave: the table, the requests and their results; at least the 4 KiB in which the node lines are staged first
+    const size_t chunk = std::max<size_t>((((size_t)kWave * stride * sizeof(pos_t) + 15) & ~size_t(15)) + 2 * kWave * (sizeof(uint4) + 1), 4096);
+    // The fused variant uses large workgroups: one chained-scan step per 1024 queries keeps the rate at which tiles publish
+    // their totals low enough for the look-back to keep up.
+    int waves = FUSED ? 16 : 4;
+    while (waves > 1 && (size_t)waves * chunk > (size_t)(159u << 10)) --waves;
+    // small batches: smaller workgroups, so that the queries spread over the compute units instead of queueing at the
+    // address units of a few
+    while (waves > 1 && (a.Q + (int64_t)waves * kWave - 1) / ((int64_t)waves * kWave) < 512) waves >>= 1;
+    const int64_t per_wg = (int64_t)waves * kWave;
+    const int64_t grid = (a.Q + per_wg - 1) / per_wg;
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (FUSED && !a.scan_ready) {
+        // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
+        const hipError_t e = launch_scan_init(a, grid + 1, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (grid <= 0) return hipGetLastError();
+    SampleArgs b = a;
+    if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
+    hipLaunchKernelGGL((tns_sample_recent_kernel<INCL, pos_t, FUSED>), dim3((unsigned)grid), dim3(waves * kWave), chunk * waves, stream,
+                       b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_sample_recent(const SampleArgs& a, hipStream_t stream) {
+    const bool fused = a.scan_ws != nullptr;
+    if (a.inclusive_end) {
+        if (a.wide_offsets) return fused ? launch_recent_t<true, int64_t, true>(a, stream) : launch_recent_t<true, int64_t, false>(a, stream);
+        return fused ? launch_recent_t<true, int32_t, true>(a, stream) : launch_recent_t<true, int32_t, false>(a, stream);
+    }
+    if (a.wide_offsets) return fused ? launch_recent_t<false, int64_t, true>(a, stream) : launch_recent_t<false, int64_t, false>(a, stream);
+    return fused ? launch_recent_t<false, int32_t, true>(a, stream) : launch_recent_t<false, int32_t, false>(a, stream);
+}
+
+}  // namespace tns

@@ -26,6 +26,7 @@ CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 PROBE_BYTES = 1 << 30
 
 _SAMPLE = re.compile(r"tns_sample(_prefix)?_kernel<(\d), (true|false), (int|long), (true|false), (true|false)>")
+_RECENT = re.compile(r"tns_sample_recent_kernel<(true|false), (int|long), (true|false)>")
 _PROBE = re.compile(r"tns_probe_kernel<(\d), (true|false)>")
 
 
@@ -67,6 +68,9 @@ def short_name(kernel: str):
         name = f"tns_sample{m.group(1) or ''}_kernel<{m.group(2)},{m.group(3)},{m.group(4)},{m.group(5)},{m.group(6)}>"
         fused_step = m.group(5) == "false" and m.group(6) == "true"
         return name, (f"{policy}:{layout}" if fused_step else None)
+    m = _RECENT.search(kernel)
+    if m:
+        return f"tns_sample_recent_kernel<{m.group(1)},{m.group(2)},{m.group(3)}>", ("recent:blocks" if m.group(3) == "true" else None)
     m = _PROBE.search(kernel)
     if m:
         return f"tns_probe_kernel<{m.group(1)},{m.group(2)}>", None

@@ -120,3 +120,29 @@ def test_bounded_wait_ends(B, layout, policy):
     assert plan.status(out["workspace"]), "the time-out must be reported"
     assert int(out["rowptr"][-1].item()) == 0, "after a time-out the dense total reads 0"
     plan.close()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("fanout,incl", [(1, 0), (6, 1), (10, 0), (11, 0), (16, 1), (33, 0), (64, 0)])
+def test_windows_inside_blocks_of_every_size(B, oracle_lib, wide, fanout, incl):
+    # node v gets a block of v + 1 edges per batch (one per batch: fixed sizing would merge them), so that both window ends
+    # fall into blocks of 1 to 40 slots at every position: all lanes of a wave then have two searches, 128 requests, some of
+    # one slot, some of more than sixteen; times repeat
+    nodes, batches = 40, 5
+    rng = np.random.default_rng(fanout)
+    src = np.concatenate([rng.permutation(np.repeat(np.arange(nodes, dtype=np.int32), np.arange(1, nodes + 1))) for _ in range(batches)])
+    batch = len(src) // batches
+    ts = np.sort(rng.integers(0, len(src) // 3, len(src))).astype(np.float32)
+    st = W.Stream(nodes, src, rng.integers(0, nodes, len(src), dtype=np.int32), ts, batch)
+    wl = W.Workload("blocks", 0, [st], fanout=fanout, tau=1)
+    plan = build_plan(B, wl, 0, incl, flags=B.TNS_FLAG_WIDE_POSITIONS if wide else 0)
+    Q = (1 << 16) + 65
+    targets = (np.arange(Q) % nodes).astype(np.int32)
+    t_end = rng.uniform(-2, len(src) // 3 + 2, Q).astype(np.float32)
+    t_end[::3] = np.round(t_end[::3])
+    t_start = np.round(t_end - rng.uniform(0, len(src) // 6, Q)).astype(np.float32)
+    adjs = [oracle_lib.Adjacency(nodes, src, st.dst, ts)]
+    for tb in (t_start, None):
+        ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, 0, incl, 0, adjs=adjs)
+        assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, f"start={tb is not None}")
+    plan.close()
