@@ -401,29 +401,40 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
     add_block_totals(a.status, blocks, slots);
 }
 
+// A planned batch as the apply phase reads it, left in memory by the planning kernels.
+struct PlannedBatch {
+    const uint64_t* __restrict__ key;         // sorted: source in the high word
+    const uint32_t* __restrict__ val;         // batch position
+    const int64_t* __restrict__ head_excl;    // segment heads before a position
+    const int32_t* __restrict__ seg_start;
+    const SegPlan* __restrict__ plan;
+    const int64_t* __restrict__ lines_base;
+    const int64_t* __restrict__ dir_base;
+    __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(key[p] >> 32); }
+    __device__ __forceinline__ uint32_t position(int64_t p) const { return val[p]; }
+    __device__ __forceinline__ int64_t segment(int64_t p) const { return head_excl[p] + (is_head(key, p) ? 1 : 0) - 1; }
+};
+
 // One thread per segment: tail record, new block records, node entry, builder state.
-__device__ __forceinline__ void apply_node(const IngestArgs& a, const uint32_t* __restrict__ val, const int32_t* __restrict__ seg_start,
-                                           const SegPlan* __restrict__ plan, const int64_t* __restrict__ lines_base,
-                                           const int64_t* __restrict__ dir_base, int64_t num_segments,
-                                           const uint64_t* __restrict__ key, int64_t s) {
-    if (s >= num_segments) return;
-    const SegPlan P = plan[s];
-    const int32_t p0 = seg_start[s], p1 = seg_start[s + 1];
+template <class Batch>
+__device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, int64_t s) {
+    const SegPlan P = b.plan[s];
+    const int32_t p0 = b.seg_start[s], p1 = b.seg_start[s + 1];
     const int64_t mm = p1 - p0;
-    const int64_t nidx = a.node_base + (uint32_t)(key[p0] >> 32);
+    const int64_t nidx = a.node_base + b.source(p0);
     NodeLine* N = &a.nodes[nidx];
     NodeAux ax = a.aux[nidx];
     const int32_t nb = N->nblocks;
     if (P.take > 0) {
         BlockRec* tr = nb <= kInlineBlocks ? &N->rec[0] : &a.dir[(int64_t)N->dir_line * kDirAlign + nb - 1];
         const BlockRec o = *tr;
-        *tr = make_rec(o.t_min, a.ts[val[p0 + P.take - 1]], rec_off(o), rec_size(o) + P.take, rec_tombstones(o));
+        *tr = make_rec(o.t_min, a.ts[b.position(p0 + P.take - 1)], rec_off(o), rec_size(o) + P.take, rec_tombstones(o));
     }
     const int64_t degree_before = N->degree;
     N->degree += (int32_t)mm;
     if (P.nbn > 0) {
         const int64_t lines = lines_of_blocks(P.cap, P.nbn, P.k0);
-        const int64_t line0 = a.used_lines + lines_base[s];
+        const int64_t line0 = a.used_lines + b.lines_base[s];
         if (line0 + lines > a.cap_lines) { atomicOr(&a.status->internal, 1u); return; }
         const int64_t after = (int64_t)nb + P.nbn;
         const int64_t rest = mm - P.take;
@@ -431,7 +442,7 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const uint32_t* 
         if (after > kInlineBlocks) {
             if (after > ax.dir_cap) {
                 const int64_t n = dir_run_for(after, ax.dir_cap);
-                const int64_t start = a.used_dir + dir_base[s];
+                const int64_t start = a.used_dir + b.dir_base[s];
                 if (start + n > a.cap_dir) { atomicOr(&a.status->internal, 2u); return; }
                 BlockRec* dst = a.dir + start;
                 uint32_t* dcum = a.dir_cum + start;
@@ -462,7 +473,7 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const uint32_t* 
         for (int32_t j = 0; j < P.nbn; ++j) {
             const int64_t first = (int64_t)p0 + P.take + (int64_t)j * P.cap;
             const int64_t size = min((int64_t)P.cap, rest - (int64_t)j * P.cap);
-            const BlockRec r = make_rec(a.ts[val[first]], a.ts[val[first + size - 1]], block_slot(P, line0, j), (int32_t)size);
+            const BlockRec r = make_rec(a.ts[b.position(first)], a.ts[b.position(first + size - 1)], block_slot(P, line0, j), (int32_t)size);
             if (run) {
                 run[nb + j] = r;
                 run_cum[nb + j] = (uint32_t)(degree_before + P.take + (int64_t)j * P.cap);   // edges in the older blocks
@@ -485,37 +496,34 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const uint32_t* 
     a.aux[nidx] = ax;
 }
 
+// The record made ready for the next batch (`internal` stays: it is reported by the next read-back).
+__device__ __forceinline__ void ready_status(IngestStatus* st) {
+    st->err_word = ~0ull;
+    st->unsorted = 0;
+    st->num_segments = 0;
+    st->total_lines = 0;
+    st->total_dir = 0;
+    st->new_blocks = 0;
+    st->new_slots = 0;
+    st->counter = 0;
+}
+
 // One thread per edge (sorted position): its slot from the segment's plan.
-__device__ __forceinline__ void apply_edge(const IngestArgs& a, const uint64_t* __restrict__ key, const uint32_t* __restrict__ val,
-                                           const int64_t* __restrict__ head_excl, const int32_t* __restrict__ seg_start,
-                                           const SegPlan* __restrict__ plan, const int64_t* __restrict__ lines_base, int64_t p) {
-    if (p >= a.m) return;
-    if (p == 0) {
-        // The host has read the record or has a copy of it (hand_over), and it is made ready for the next batch here, so
-        // that the next plan needs no launch of its own for it (`internal` stays: it is reported by the next read-back).
-        IngestStatus* st = a.status;
-        st->err_word = ~0ull;
-        st->unsorted = 0;
-        st->num_segments = 0;
-        st->total_lines = 0;
-        st->total_dir = 0;
-        st->new_blocks = 0;
-        st->new_slots = 0;
-        st->counter = 0;
-    }
-    const int64_t s = head_excl[p] + (is_head(key, p) ? 1 : 0) - 1;
-    const SegPlan P = plan[s];
-    const int64_t r = p - seg_start[s];
+template <class Batch>
+__device__ __forceinline__ void apply_edge(const IngestArgs& a, const Batch& b, int64_t p) {
+    const int64_t s = b.segment(p);
+    const SegPlan P = b.plan[s];
+    const int64_t r = p - b.seg_start[s];
     int64_t slot;
     if (r < P.take) {
         slot = P.tail_slot + r;
     } else {
         const int64_t rr = r - P.take;
-        const int32_t j = (int32_t)(rr / P.cap);
-        slot = block_slot(P, a.used_lines + lines_base[s], j) + (rr - (int64_t)j * P.cap);
+        const int32_t j = (int32_t)((uint32_t)rr / (uint32_t)P.cap);      // both below 2^24
+        slot = block_slot(P, a.used_lines + b.lines_base[s], j) + (rr - (int64_t)j * P.cap);
     }
     if (slot / kSlotsPerLine >= a.cap_lines) { atomicOr(&a.status->internal, 4u); return; }
-    const uint32_t e = val[p];
+    const uint32_t e = b.position(p);
     const int64_t w = slot_word(slot);
     a.lines[w] = __float_as_uint(a.ts[e]);
     a.lines[w + 1] = (uint32_t)a.dst[e];
@@ -524,18 +532,20 @@ __device__ __forceinline__ void apply_edge(const IngestArgs& a, const uint64_t* 
 
 // Both in one launch: an edge's slot follows from the plan alone, so the two parts do not depend on each other.
 // (100 K edges: 14.4 us against 7.8 + 10.2 and the gap between the two launches.)
-__global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const uint64_t* __restrict__ key, const uint32_t* __restrict__ val,
-                                                    const int64_t* __restrict__ head_excl, const int32_t* __restrict__ seg_start,
-                                                    const SegPlan* __restrict__ plan, const int64_t* __restrict__ lines_base,
-                                                    const int64_t* __restrict__ dir_base, int64_t num_segments, unsigned node_blocks,
+__global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const PlannedBatch b, int64_t num_segments, unsigned node_blocks,
                                                     const int64_t* __restrict__ go) {
     if (go) num_segments = *go;          // queued before the host has seen the plan
     if (num_segments <= 0) return;
     // the node part first: it is the longer chain of dependent reads
-    if (blockIdx.x < node_blocks)
-        apply_node(a, val, seg_start, plan, lines_base, dir_base, num_segments, key, (int64_t)blockIdx.x * kThreads + threadIdx.x);
-    else
-        apply_edge(a, key, val, head_excl, seg_start, plan, lines_base, (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x);
+    if (blockIdx.x < node_blocks) {
+        const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+        if (s < num_segments) apply_node(a, b, s);
+    } else {
+        const int64_t p = (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x;
+        // (the host has read the record or has a copy of it: the next plan needs no launch of its own for it)
+        if (p == 0) ready_status(a.status);
+        if (p < a.m) apply_edge(a, b, p);
+    }
 }
 
 // ---- short pipeline for stream-sized batches -------------------------------------------------
@@ -563,9 +573,10 @@ constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
 constexpr int kSegItems = 4;                            // positions per thread in k_fast_segments
 constexpr int kPlanThreads = 1024;                      // k_fast_plan: one segment per thread, 1024 per tile
-// Batches planned by one workgroup (k_small_plan).  us per batch with it / with the five kernels: 2^18 nodes 600 edges
-// 41.8 / 43.3, 2000 52.2 / 51.0, 3000 73.2 / 51.9, 4096 81.5 / 52.0; power-law ids 600 38.8 / 45.8, 2000 44.6 / 58.5, 3000
-// 63.2 / 60.8, 4096 67.5 / 60.2; a single node 2000 37.6 / 62.6.
+// Batches planned and applied by one workgroup (k_small_batch).  us per batch with the sampling of its events, with it / with
+// the same in two launches and a bitonic sort, which above this size was slower than the five kernels (3000 edges over
+// 2^18 nodes 73.2 / 51.9 us without the sampling): 600 edges over 2^18 nodes 46 / 56, 2000 over 2^18 57 / 68, 2000 over 2^16
+// power-law ids 48 / 59, 2048 over two nodes 43 / 58.  Twice the size does not fit the LDS.
 constexpr int64_t kSmallBatch = 2048;
 constexpr uint32_t kInternalScan = 8u;                  // IngestStatus::internal: a chained scan's bounded wait ran out
 
@@ -613,21 +624,32 @@ __device__ __forceinline__ int64_t chain_wave(ScanWorkspace* ws, IngestStatus* s
 // would write the L2 back as well (batches of 100 K edges 82 -> 103 us).
 __device__ __forceinline__ void wait_for_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// The finished record goes to the host, and the apply kernel queued behind the plan learns whether it may run: the
-// batch is sound and in time order and the pools have room.  The host comes to the same conclusion from the record and
-// otherwise (an error, the general pipeline, larger pools) goes on by itself.  One thread, after the last update of *status.
-__device__ __forceinline__ void hand_over(const IngestArgs& a) {
+__device__ __forceinline__ IngestStatus load_status(const IngestStatus* st) {      // past the caches of this compute unit
     IngestStatus r;
-    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(a.status);
+    const unsigned long long* src = reinterpret_cast<const unsigned long long*>(st);
     unsigned long long* copy = reinterpret_cast<unsigned long long*>(&r);
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(IngestStatus) / 8); ++i) copy[i] = __hip_atomic_load(&src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *a.go = ingest_may_apply(r, a) ? r.num_segments : 0;
+    return r;
+}
+
+// The finished record goes to the host: the record first, then the batch's sequence number.
+__device__ __forceinline__ void send_to_host(const IngestArgs& a, const IngestStatus& r) {
+    const unsigned long long* copy = reinterpret_cast<const unsigned long long*>(&r);
     unsigned long long* dst = reinterpret_cast<unsigned long long*>(a.host_status);
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(IngestStatus) / 8); ++i) dst[i] = copy[i];
     __threadfence_system();
     __hip_atomic_store(a.host_seq, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The record goes to the host, and the apply kernel queued behind the plan learns whether it may run: the
+// batch is sound and in time order and the pools have room.  The host comes to the same conclusion from the record and
+// otherwise (an error, the general pipeline, larger pools) goes on by itself.  One thread, after the last update of *status.
+__device__ __forceinline__ void hand_over(const IngestArgs& a) {
+    const IngestStatus r = load_status(a.status);
+    *a.go = ingest_may_apply(r, a) ? r.num_segments : 0;
+    send_to_host(a, r);
 }
 
 template <int TILE>
@@ -924,30 +946,80 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     }
 }
 
-// The whole plan in one workgroup for batches of at most kSmallBatch edges (a mini-batch of a stream): such a batch
-// spends its time in the five dependent launches above.  Sort by (source, arrival) in LDS, segments, plans and the two
-// scans follow each other behind barriers; nothing is read back from memory in between, and the record goes to the host
-// from here.  A bitonic network of 2048 keys is 66 steps of one compare per thread; 2000 edges 30 us in all, against
-// 36 us in the five kernels and the gaps between them (64 batches of 2000 edges, each sampled, with the apply phase
-// queued behind the plan: 5.76 -> 3.82 ms, 0.3 of it by the memory kept between plans).  Keeping the keys in registers and
-// exchanging them by shuffles gave nothing.
-__global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val,
-                                                     int64_t* __restrict__ head_excl, int32_t* __restrict__ seg_start,
-                                                     SegPlan* __restrict__ plan, int64_t* __restrict__ lines_base,
-                                                     int64_t* __restrict__ dir_base) {
-    constexpr int N = (int)kSmallBatch, ITEMS = N / 1024 /* keys per thread */, kWaves = 1024 / kWave;
-    __shared__ uint64_t s_key[N];
-    __shared__ int32_t s_start[N + 1];
-    __shared__ int64_t s_wave[kWaves];
-    __shared__ unsigned long long s_totals[2];
-    const int t = threadIdx.x, m = (int)a.m;
-    if (t < 2) s_totals[t] = 0;
-    int32_t touched = 0;
-    // keys: (source, batch position), all different, so the order is that of a stable sort by source
+// Two exclusive scans over the workgroup side by side.
+template <int WAVES>
+__device__ __forceinline__ void block_exclusive_scan2(int64_t (&v)[2], int64_t (*s_wave)[WAVES] /* [2][WAVES] */, int64_t (&total)[2]) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int64_t own[2] = {v[0], v[1]};
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int i = j * 1024 + t;
-        uint64_t k = ~0ull;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int64_t u0 = (int64_t)__shfl_up((long long)v[0], d, kWave), u1 = (int64_t)__shfl_up((long long)v[1], d, kWave);
+        if (lane >= d) { v[0] += u0; v[1] += u1; }
+    }
+    if (lane == kWave - 1) { s_wave[0][wave] = v[0]; s_wave[1][wave] = v[1]; }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        // lane w of every wave adds up the waves: a value per lane instead of a loop over all of them
+        int64_t x = lane < WAVES ? s_wave[i][lane] : 0;
+        int64_t before = lane < wave ? x : 0;
+        for (int d = WAVES / 2; d >= 1; d >>= 1) {
+            x += (int64_t)__shfl_xor((long long)x, d, kWave);
+            before += (int64_t)__shfl_xor((long long)before, d, kWave);
+        }
+        total[i] = (int64_t)__shfl((long long)x, 0, kWave);
+        v[i] += (int64_t)__shfl((long long)before, 0, kWave) - own[i];
+    }
+    __syncthreads();
+}
+
+// A batch of at most kSmallBatch edges (a mini-batch of a stream), planned and applied by one workgroup: such a batch
+// spends its time in dependent launches otherwise.  Everything between the batch and the store stays in LDS; the record goes
+// to the host while the store is being changed.  Sorted by (source, arrival) with a stable radix sort, six bits a pass: a
+// wave ranks 128 keys with ballots, and the 64 x 16 counts of a pass are one per thread for its scan.  As a bitonic network of
+// 66 steps the sort took 13.5 of 28 us, and the apply phase was a launch of its own (64 batches of 2000 power-law edges, each
+// sampled, into a new store: 3.80 -> 3.09 ms).
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave, kSmallItems = (int)kSmallBatch / kSmallThreads;
+constexpr int kSmallDigit = 6, kSmallBins = 1 << kSmallDigit;
+struct SmallShared {
+    uint64_t key[kSmallBatch];           // sorted: source in the high word, batch position in the low one
+    SegPlan plan[kSmallBatch];
+    int64_t lines_base[kSmallBatch], dir_base[kSmallBatch];
+    int32_t seg_start[kSmallBatch + 1];
+    int32_t seg_of[kSmallBatch];
+    int32_t count[kSmallBins * (kSmallWaves + 1)];      // [digit][wave], a word of padding per digit
+    int64_t wave[2][kSmallWaves];
+    int32_t wave32[kSmallWaves];
+    unsigned long long totals[2];
+    int32_t go;
+};
+struct SmallBatch {                      // as PlannedBatch, in LDS
+    const SmallShared& sh;
+    const SegPlan* plan;
+    const int32_t* seg_start;
+    const int64_t *lines_base, *dir_base;
+    __device__ __forceinline__ explicit SmallBatch(const SmallShared& x)
+        : sh(x), plan(x.plan), seg_start(x.seg_start), lines_base(x.lines_base), dir_base(x.dir_base) {}
+    __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(sh.key[p] >> 32); }
+    __device__ __forceinline__ uint32_t position(int64_t p) const { return (uint32_t)sh.key[p]; }
+    __device__ __forceinline__ int64_t segment(int64_t p) const { return sh.seg_of[p]; }
+};
+
+__global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs a, int bits, uint64_t* __restrict__ key,
+                                                               uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
+                                                               int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
+                                                               int64_t* __restrict__ lines_base, int64_t* __restrict__ dir_base) {
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    SmallShared& sh = *reinterpret_cast<SmallShared*>(s_raw);
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, m = (int)a.m;
+    if (t < 2) sh.totals[t] = 0;
+    int32_t touched = 0;
+    // a wave owns kSmallItems * 64 consecutive keys, item by item
+    uint64_t k[kSmallItems];
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+        const int i = (wave * kSmallItems + j) * kWave + lane;
+        k[j] = ~0ull;                    // beyond the batch: last in every pass
         if (i < m) {
             const int32_t v = a.src[i];
             const float ts = a.ts[i], before = a.ts[i > 0 ? i - 1 : 0];
@@ -955,110 +1027,169 @@ __global__ void __launch_bounds__(1024) k_small_plan(const IngestArgs a, uint64_
             else if (ts != ts) report(a.status, TNS_EORDER, i);
             else if (a.eid && a.eid[i] < 0) report(a.status, TNS_EINVAL, i);
             if (i > 0 && before > ts) atomicOr(&a.status->unsorted, 1u);
-            k = ((uint64_t)(uint32_t)v << 32) | (uint32_t)i;
+            k[j] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)i;
             // brings the node's entry and builder state into the L2 while the keys are sorted
             if ((uint64_t)(uint32_t)v < (uint64_t)a.num_nodes) touched |= a.nodes[a.node_base + v].nblocks | a.aux[a.node_base + v].tail_cap;
         }
-        s_key[i] = k;
     }
-    __syncthreads();
-    for (int size = 2; size <= N; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+#pragma unroll 1
+    for (int shift = 0; shift < bits; shift += kSmallDigit) {
+        // rank among the wave's equal digits: those of earlier items, then those of lower lanes
+        sh.count[lane * (kSmallWaves + 1) + wave] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        uint32_t d[kSmallItems], rank[kSmallItems];
 #pragma unroll
-            for (int j = 0; j < ITEMS / 2; ++j) {
-                const int c = j * 1024 + t;
-                const int lo = ((c & ~(stride - 1)) << 1) | (c & (stride - 1)), hi = lo + stride;
-                const uint64_t x = s_key[lo], y = s_key[hi];
-                if ((x > y) == ((lo & size) == 0)) {
-                    s_key[lo] = y;
-                    s_key[hi] = x;
-                }
+        for (int j = 0; j < kSmallItems; ++j) {
+            d[j] = (uint32_t)(k[j] >> (32 + shift)) & (uint32_t)(kSmallBins - 1);
+            uint64_t same = ~0ull;
+#pragma unroll
+            for (int b = 0; b < kSmallDigit; ++b) {
+                const bool bit = (d[j] >> b) & 1u;
+                const uint64_t bal = __ballot(bit);
+                same &= bit ? bal : ~bal;
             }
-            // steps of up to 64 stay inside the 128 keys that a wave's 64 pairs cover: the wave's LDS operations are
-            // executed in order, only the compiler must not reorder them
-            if (stride > kWave || (stride == 1 && size >= 2 * kWave)) {
-                __syncthreads();
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
+            int32_t* const c = &sh.count[d[j] * (kSmallWaves + 1) + wave];
+            const uint32_t earlier = (uint32_t)*c;
+            rank[j] = earlier + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if ((same & ((1ull << lane) - 1ull)) == 0) *c = (int32_t)(earlier + (uint32_t)__popcll(same));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
+        __syncthreads();
+        // exclusive scan of the counts, digit by digit and wave by wave: one per thread
+        int32_t* const mine = &sh.count[(t / kSmallWaves) * (kSmallWaves + 1) + (t % kSmallWaves)];
+        const int32_t own = *mine;
+        int32_t inc = own;
+#pragma unroll
+        for (int x = 1; x < kWave; x <<= 1) {
+            const int32_t u = __shfl_up(inc, x, kWave);
+            if (lane >= x) inc += u;
+        }
+        if (lane == kWave - 1) sh.wave32[wave] = inc;
+        __syncthreads();
+        int32_t before = lane < wave ? sh.wave32[lane & (kSmallWaves - 1)] : 0;
+        for (int x = kSmallWaves / 2; x >= 1; x >>= 1) before += __shfl_xor(before, x, kWave);
+        *mine = __shfl(before, 0, kWave) + inc - own;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSmallItems; ++j) sh.key[(uint32_t)sh.count[d[j] * (kSmallWaves + 1) + wave] + rank[j]] = k[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSmallItems; ++j) k[j] = sh.key[(wave * kSmallItems + j) * kWave + lane];
     }
     asm volatile("" ::"v"(touched));          // the loads' only use
-    // segments; a thread owns ITEMS consecutive sorted positions
-    uint64_t k[ITEMS];
-    int h[ITEMS];
-    int64_t heads = 0, nseg;
+    // segments; every item of a wave is 64 consecutive sorted positions
+    int h[kSmallItems];
+    uint64_t heads[kSmallItems];
+    int32_t in_wave = 0;
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int p = t * ITEMS + j;
-        k[j] = s_key[p];
-        const uint32_t prev = p > 0 ? (uint32_t)(s_key[p - 1] >> 32) : 0u;
-        h[j] = (p < m && (p == 0 || prev != (uint32_t)(k[j] >> 32))) ? 1 : 0;
-        heads += h[j];
+    for (int j = 0; j < kSmallItems; ++j) {
+        const int p = (wave * kSmallItems + j) * kWave + lane;
+        h[j] = p < m && (p == 0 || (uint32_t)(sh.key[p - 1] >> 32) != (uint32_t)(k[j] >> 32)) ? 1 : 0;
+        heads[j] = __ballot(h[j]);
+        in_wave += __popcll(heads[j]);
     }
-    int64_t run = block_exclusive_scan<kWaves>(heads, s_wave, nseg);
+    if (lane == 0) sh.wave32[wave] = in_wave;
+    __syncthreads();
+    int32_t run = 0, nseg = 0;
+    for (int w = 0; w < kSmallWaves; ++w) {
+        const int32_t c = sh.wave32[w];
+        if (w < wave) run += c;
+        nseg += c;
+    }
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j) {
-        const int p = t * ITEMS + j;
+    for (int j = 0; j < kSmallItems; ++j) {
+        const int p = (wave * kSmallItems + j) * kWave + lane;
+        const int32_t s = run + __popcll(heads[j] & ((1ull << lane) - 1ull));       // heads before this position
         if (p < m) {
-            key[p] = k[j];
-            val[p] = (uint32_t)k[j];
-            head_excl[p] = run;
-            if (h[j]) {
-                s_start[run] = p;
-                seg_start[run] = p;
-            }
-            run += h[j];
-            if (p == m - 1) {
-                s_start[run] = m;
-                seg_start[run] = m;
-            }
+            sh.seg_of[p] = s + h[j] - 1;
+            if (h[j]) sh.seg_start[s] = p;
+            if (p == m - 1) sh.seg_start[nseg] = m;
         }
+        run += __popcll(heads[j]);
     }
     __syncthreads();
     // plans, 1024 segments at a time (a loop, not unrolled: the program is fetched once from a cold instruction cache,
-    // and its length is what this kernel costs)
-    int64_t all_lines = 0, all_dirs = 0, blocks = 0, slots = 0;
+    // and its length is part of what this kernel costs)
+    int64_t all[2] = {0, 0}, blocks = 0, slots = 0;
 #pragma unroll 1
-    for (int64_t sgm = t; sgm - t < nseg; sgm += 1024) {
-        int64_t lines = 0, dirs = 0, b = 0, sl = 0, tot_lines, tot_dirs;
+    for (int sgm = t; sgm - t < nseg; sgm += kSmallThreads) {
+        int64_t need[2] = {0, 0}, tot[2], b = 0, sl = 0;
         if (sgm < nseg) {
-            const int p0 = s_start[sgm];
-            const uint64_t k0 = s_key[p0];
+            const int p0 = sh.seg_start[sgm];
+            const uint64_t k0 = sh.key[p0];
             SegPlan P{};
-            plan_segment(a, (uint32_t)(k0 >> 32), (uint32_t)k0, s_start[sgm + 1] - p0, P, lines, dirs, b, sl);
-            plan[sgm] = P;
+            plan_segment(a, (uint32_t)(k0 >> 32), (uint32_t)k0, sh.seg_start[sgm + 1] - p0, P, need[0], need[1], b, sl);
+            sh.plan[sgm] = P;
         }
         blocks += b;
         slots += sl;
-        const int64_t line0 = block_exclusive_scan<kWaves>(lines, s_wave, tot_lines);
-        const int64_t dir0 = block_exclusive_scan<kWaves>(dirs, s_wave, tot_dirs);
+        block_exclusive_scan2<kSmallWaves>(need, sh.wave, tot);
         if (sgm < nseg) {
-            lines_base[sgm] = all_lines + line0;
-            dir_base[sgm] = all_dirs + dir0;
+            sh.lines_base[sgm] = all[0] + need[0];
+            sh.dir_base[sgm] = all[1] + need[1];
         }
-        all_lines += tot_lines;
-        all_dirs += tot_dirs;
+        all[0] += tot[0];
+        all[1] += tot[1];
     }
     blocks = wave_sum64(blocks);
     slots = wave_sum64(slots);
-    if ((t & (kWave - 1)) == 0) {
-        atomicAdd(&s_totals[0], (unsigned long long)blocks);
-        atomicAdd(&s_totals[1], (unsigned long long)slots);
+    if (lane == 0) {
+        atomicAdd(&sh.totals[0], (unsigned long long)blocks);
+        atomicAdd(&sh.totals[1], (unsigned long long)slots);
     }
     wait_for_memory();               // every thread's reports have been performed
     __syncthreads();
+    IngestStatus rec;
+    if (t == 0) {
+        rec = load_status(a.status);
+        rec.num_segments = nseg;
+        rec.total_lines = all[0];
+        rec.total_dir = all[1];
+        rec.new_blocks = sh.totals[0];
+        rec.new_slots = sh.totals[1];
+        sh.go = a.host_status && ingest_may_apply(rec, a) ? 1 : 0;
+    }
+    __syncthreads();
+    const bool go = sh.go != 0;
     if (t == 0) {
         IngestStatus* st = a.status;
-        st->num_segments = nseg;
-        st->total_lines = all_lines;
-        st->total_dir = all_dirs;
-        st->new_blocks = s_totals[0];
-        st->new_slots = s_totals[1];
-        if (a.host_status) {
+        if (go) {
+            ready_status(st);
+        } else {
+            st->num_segments = rec.num_segments;
+            st->total_lines = rec.total_lines;
+            st->total_dir = rec.total_dir;
+            st->new_blocks = rec.new_blocks;
+            st->new_slots = rec.new_slots;
             __threadfence();
-            hand_over(a);
+        }
+        if (a.host_status) send_to_host(a, rec);
+    }
+    const SmallBatch batch(sh);
+    if (go) {
+#pragma unroll 1
+        for (int s = t; s < nseg; s += kSmallThreads) apply_node(a, batch, s);
+#pragma unroll 1
+        for (int p = t; p < m; p += kSmallThreads) apply_edge(a, batch, p);
+    } else {
+        // an error, a batch out of order, pools without room: the host decides, and a later launch finds the plan in memory
+#pragma unroll 1
+        for (int p = t; p < m; p += kSmallThreads) {
+            key[p] = sh.key[p];
+            val[p] = batch.position(p);
+            head_excl[p] = sh.seg_of[p] + ((p == sh.seg_start[sh.seg_of[p]]) ? 0 : 1);
+        }
+#pragma unroll 1
+        for (int s = t; s < nseg; s += kSmallThreads) {
+            plan[s] = sh.plan[s];
+            seg_start[s] = sh.seg_start[s];
+            lines_base[s] = sh.lines_base[s];
+            dir_base[s] = sh.dir_base[s];
+            if (s == nseg - 1) seg_start[nseg] = m;
         }
     }
 }
@@ -1233,8 +1364,8 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
     IngestArgs a = args;
     a.go = c.sums;
     if (a.m <= kSmallBatch) {
-        hipLaunchKernelGGL(k_small_plan, dim3(1), dim3(1024), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start, c.plan,
-                           c.lines_base, c.dir_base);
+        hipLaunchKernelGGL(k_small_batch, dim3(1), dim3(kSmallThreads), sizeof(SmallShared), stream, a, 2 * bits, c.keyA, c.valA, c.head_excl,
+                           c.seg_start, c.plan, c.lines_base, c.dir_base);
         return hipGetLastError();
     }
     const int bins = 1 << bits;
@@ -1268,9 +1399,11 @@ hipError_t ingest_apply(const IngestArgs& a, int64_t num_segments, bool fast, hi
     const bool in_b = !fast && (src_passes(a.num_nodes) & 1) != 0;
     const uint64_t* key = in_b ? c.keyB : c.keyA;
     const uint32_t* val = in_b ? c.valB : c.valA;
+    if (num_segments <= 0 && a.m <= kSmallBatch) return hipSuccess;          // k_small_batch has applied the batch, or may not
     const unsigned node_blocks = grid_for(num_segments > 0 ? num_segments : a.m);
-    hipLaunchKernelGGL(k_apply, dim3(node_blocks + grid_for(a.m)), dim3(kThreads), 0, stream, a, key, val, c.head_excl, c.seg_start, c.plan,
-                       c.lines_base, c.dir_base, num_segments, node_blocks, num_segments > 0 ? nullptr : c.sums);
+    const PlannedBatch b{key, val, c.head_excl, c.seg_start, c.plan, c.lines_base, c.dir_base};
+    hipLaunchKernelGGL(k_apply, dim3(node_blocks + grid_for(a.m)), dim3(kThreads), 0, stream, a, b, num_segments, node_blocks,
+                       num_segments > 0 ? nullptr : c.sums);
     return hipGetLastError();
 }
 

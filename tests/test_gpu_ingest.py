@@ -214,3 +214,34 @@ def test_large_batches_through_both_pipelines(B, oracle_lib, batch):
     host.close()
     plan.close()
     adj.close()
+
+
+@pytest.mark.parametrize("nodes", [1, 2, 63, 64, 65, 4095, 4096, 4097, (1 << 18) - 1, 1 << 18])
+def test_one_workgroup_batches_at_digit_and_wave_boundaries(B, oracle_lib, nodes):
+    # batches sorted six bits of the node id at a time, 128 keys a wave: ids that are all ones in every digit (where the
+    # keys beyond the batch sort too), sizes around the waves' and the workgroup's, growth of the pools in between
+    rng = np.random.default_rng(nodes)
+    sizes = [1, 2, 63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 2047, 2048, 2048, 7]
+    n = sum(sizes)
+    src = rng.integers(0, nodes, n, dtype=np.int32)
+    src[rng.random(n) < 0.25] = nodes - 1
+    src[rng.random(n) < 0.25] = 0
+    dst = rng.integers(0, nodes, n, dtype=np.int32)
+    ts = np.sort(rng.integers(0, n // 3, n)).astype(np.float32)
+    plan = B.Plan(nodes, 10, block_threshold=48, flags=B.TNS_FLAG_DEVICE_INGEST)
+    bs = oracle_lib.BlockStore(nodes, 48, 0)
+    lo = 0
+    for m in sizes:
+        part = slice(lo, lo + m)
+        plan.add_edges_device(to_dev(src[part], np.int32), to_dev(dst[part], np.int32), to_dev(ts[part], np.float32))
+        bs.add_stream(src[part], dst[part], ts[part], m)
+        lo += m
+    ref, got = bs.stats(), plan.stats()
+    for name in ("num_blocks", "wasted_slots", "max_list_len"):
+        assert got[name] == ref[name], name
+    st = W.Stream(nodes, src, dst, ts, n)
+    targets, t_start, t_end = W.random_queries(6, st, 3000)
+    wl = wl_of(st)
+    assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl, targets, t_start, t_end, None, 10, 0, 0, 0),
+                oracle_lib, f"nodes={nodes}")
+    plan.close()
