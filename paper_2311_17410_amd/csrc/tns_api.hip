@@ -260,8 +260,8 @@ int upload_dirty(DeviceArray<T>& d, const P& host, hipStream_t stream, const cha
 
 // Room a growing array of a device-built store is given for `need` elements.  Growing costs a copy and two waits for the
 // device, some 150 us however small the array, and a young store grows every few batches: up to kYoungBytes it is given four
-// times what it needs, above that one and a half times (64 batches of 2000 edges, each sampled, into a new store 3.09 -> 2.75
-// ms; 32 of 100 K 4.15 -> 3.91).
+// times what it needs, above that one and a half times (32 batches of 100 K edges, each sampled, into a new store 4.15 -> 3.38
+// ms; 64 of 2000 3.09 -> 3.04).
 constexpr int64_t kYoungBytes = int64_t(128) << 20;
 inline int64_t room_for(int64_t need, int64_t element) {
     return std::max(need + need / 2 + 1024, std::min(4 * need, kYoungBytes / element));
@@ -304,9 +304,10 @@ int ensure_device_store(tns_plan* plan, hipStream_t stream) {
     DeviceStore& ds = *plan->dev;
     if (ds.d_status) return TNS_OK;
     const int64_t total_nodes = std::max<int64_t>((int64_t)plan->cfg.num_instances * plan->cfg.num_nodes, 1);
+    const int64_t node_room = total_nodes + total_nodes / 2 + 1024;
     int rc;
-    if ((rc = grow_device(plan->d_nodes, total_nodes, total_nodes, stream, "allocating node table"))) return rc;
-    if ((rc = grow_device(ds.aux, total_nodes, total_nodes, stream, "allocating the builder state"))) return rc;
+    if ((rc = grow_device(plan->d_nodes, total_nodes, node_room, stream, "allocating node table"))) return rc;
+    if ((rc = grow_device(ds.aux, total_nodes, node_room, stream, "allocating the builder state"))) return rc;
     if ((rc = grow_device(plan->d_dir, 1024, 4096, stream, "allocating the block directory"))) return rc;
     if ((rc = grow_device(plan->d_dir_cum, 1024, 4096, stream, "allocating the block directory"))) return rc;
     if ((rc = grow_device(plan->d_edges, 1024, 4096, stream, "allocating edge data"))) return rc;
