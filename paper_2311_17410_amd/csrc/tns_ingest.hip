@@ -551,28 +551,28 @@ __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const Pl
 // ---- short pipeline for stream-sized batches -------------------------------------------------
 //
 // A batch of the size streams are ingested in (the paper's 100 K edges) spends its time in launches,
-// not in memory traffic, so the planning phase above (about 40 dependent launches) is cut to five
+// not in memory traffic, so the planning phase above (about 40 dependent launches) is cut to four
 // for batches that fit kFastMaxBatch and arrive in time order, the usual case for a stream:
 //   k_fast_keys      validation, keys, and every tile's histogram of the first digit;
 //   k_fast_scatter   x 2: stable radix pass over one half of the source id's bits.  Every tile adds
 //                    up the histograms of the tiles before it by itself (at most kFastMaxTiles rows, read
 //                    from the L2), so a pass needs no separate scan launch and no tile waits for another;
 //                    the first pass also counts the second digit per destination tile for the second pass;
-//   k_fast_segments  segment heads, their numbering (chained scan over tiles) and the segment starts;
-//   k_fast_plan      the per-segment plan and the pool offsets (two chained scans) in one launch.
+//   k_fast_plan      segment heads and numbers, the per-segment plan and the pool offsets (chained scans) in one launch.
 // Time order is assumed, not known: k_fast_keys sets `unsorted` as the general pipeline does, and
 // the host, which reads the status before anything is changed, then runs the general pipeline instead.
 // keys per sort tile: small batches take smaller tiles so that they still spread over the compute units, large ones
-// larger tiles so that the table of tile histograms every tile reads stays short (measured: 2^14 edges 0.071 / 0.090 ms
-// with 1024 / 4096 keys per tile, 2^17 edges 0.117 / 0.125 ms with 2048 / 4096, 2^20 edges 0.635 / 0.538 ms)
+// larger tiles so that the table of tile histograms every tile reads stays short (us per batch with the sampling of its
+// events, 1024 / 2048 / 4096 keys per tile: 10^5 edges 91 / 93 / -, 2 * 10^5 power-law ids 167 / 174 / 190, 2^18 167 / 168 /
+// 173, 3 * 10^5 233 / 237 / 238, 2^19 392 / 402 / 389)
 constexpr int kFastTileMax = 4096;
-inline int fast_tile_keys(int64_t m) { return m <= (int64_t(1) << 16) ? 1024 : (m <= (int64_t(1) << 17) ? 2048 : kFastTileMax); }
+inline int fast_tile_keys(int64_t m) { return m <= (int64_t(1) << 17) ? 1024 : (m <= (int64_t(1) << 18) ? 2048 : kFastTileMax); }
 constexpr int kScatThreads = 512;                       // the radix passes: 8 waves x 8 keys per lane on the same tiles
+constexpr int kScatGroups = 4;                          // parts of the table of tile histograms that are added up side by side
 constexpr int kFastMaxTiles = 512;
 constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^21 edges
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
-constexpr int kSegItems = 4;                            // positions per thread in k_fast_segments
-constexpr int kPlanThreads = 1024;                      // k_fast_plan: one segment per thread, 1024 per tile
+constexpr int kPlanThreads = 512;                       // k_fast_plan: one sorted position per thread, 512 per tile
 // Batches planned and applied by one workgroup (k_small_batch).  us per batch with the sampling of its events, with it / with
 // the same in two launches and a bitonic sort, which above this size was slower than the five kernels (3000 edges over
 // 2^18 nodes 73.2 / 51.9 us without the sampling): 600 edges over 2^18 nodes 46 / 56, 2000 over 2^18 57 / 68, 2000 over 2^16
@@ -646,17 +646,18 @@ __device__ __forceinline__ void send_to_host(const IngestArgs& a, const IngestSt
 // The record goes to the host, and the apply kernel queued behind the plan learns whether it may run: the
 // batch is sound and in time order and the pools have room.  The host comes to the same conclusion from the record and
 // otherwise (an error, the general pipeline, larger pools) goes on by itself.  One thread, after the last update of *status.
-__device__ __forceinline__ void hand_over(const IngestArgs& a) {
-    const IngestStatus r = load_status(a.status);
+__device__ __forceinline__ void hand_over(const IngestArgs& a, const IngestStatus& r) {
     *a.go = ingest_may_apply(r, a) ? r.num_segments : 0;
     send_to_host(a, r);
 }
 
+constexpr int kPlanScans = 4;
+struct PlanScans { ScanWorkspace* ws[kPlanScans]; };      // of k_fast_plan
+
 template <int TILE>
 __global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val,
                                                         uint32_t* __restrict__ hist1, uint32_t* __restrict__ hist2, int bits,
-                                                        ScanWorkspace* seg_scan, ScanWorkspace* lines_scan, ScanWorkspace* dir_scan,
-                                                        int seg_tiles, int plan_tiles) {
+                                                        const PlanScans scans, int plan_tiles) {
     extern __shared__ uint32_t s_hist[];     // [bins]
     const int bins = 1 << bits;
     for (int b = threadIdx.x; b < bins; b += kThreads) s_hist[b] = 0;
@@ -697,16 +698,15 @@ __global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint
         row2[b] = 0;                      // filled by the first scatter pass
     }
     if (blockIdx.x == 0) {
-        // tickets, error words and tile states of the three chained scans that follow
-        for (int i = threadIdx.x; i < seg_tiles + 1; i += kThreads) seg_scan->status[i] = 0;
+        // tickets, error words and tile states of the plan's chained scans
         for (int i = threadIdx.x; i < plan_tiles + 1; i += kThreads) {
-            lines_scan->status[i] = 0;
-            dir_scan->status[i] = 0;
+            for (ScanWorkspace* w : scans.ws) w->status[i] = 0;
         }
         if (threadIdx.x == 0) {
-            seg_scan->ticket = 0; seg_scan->error = 0;
-            lines_scan->ticket = 0; lines_scan->error = 0; lines_scan->pad[0] = 0;      // pad[0]: plan workgroups that are done
-            dir_scan->ticket = 0; dir_scan->error = 0;
+            for (ScanWorkspace* w : scans.ws) {
+                w->ticket = 0;
+                w->error = 0;
+            }
         }
     }
 }
@@ -729,60 +729,62 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
     const int tile = blockIdx.x;
     const uint32_t mask = (uint32_t)(bins - 1);
 
-    // keys with this digit in earlier tiles, and in all tiles: thread t owns `per` consecutive digits and reads
-    // their counts of every tile (16-byte loads when it owns four or more)
+    // the tile's keys are requested first: nothing before the ranking needs them, and they arrive while the table is read
+    constexpr int kScatItems = TILE / kScatThreads;
+    const int64_t wbase = (int64_t)tile * TILE + (int64_t)wave * (kScatItems * kWave);
+    uint64_t k_[kScatItems];
+    uint32_t v_[kScatItems], r_[kScatItems];
+#pragma unroll
+    for (int j = 0; j < kScatItems; ++j) {
+        const int64_t i = min(wbase + (int64_t)j * kWave + lane, m - 1);   // clamped: no load sits in a branch
+        k_[j] = kin[i];
+        v_[j] = vin[i];
+    }
+    // keys with this digit in earlier tiles, and in all tiles.  A thread adds up four digits (16-byte loads) of every
+    // group-th tile, eight rows in flight: the rows come from the L2, and with all 49 rows of a batch of 100 K to itself a
+    // thread spent seven round trips here (16.5 us a pass, 11.2 in the second, which counts nothing for a next one).
+    const int quads = bins / 4, groups = min(kScatGroups, max(1, kScatThreads / quads));
+    uint32_t* const part_before = s_cnt;                       // [groups][bins] each, in the waves' rows for now
+    uint32_t* const part_all = s_cnt + (size_t)groups * bins;
+    for (int x = t; x < quads * groups; x += kScatThreads) {
+        const int q = x % quads, grp = x / quads;
+        uint4 before = make_uint4(0, 0, 0, 0), all = make_uint4(0, 0, 0, 0);
+        for (int r0 = grp; r0 < tiles; r0 += 8 * groups) {
+            uint4 c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = *reinterpret_cast<const uint4*>(hist + (size_t)min(r0 + u * groups, tiles - 1) * bins + 4 * q);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int r = r0 + u * groups;
+                if (r < tiles) { all.x += c[u].x; all.y += c[u].y; all.z += c[u].z; all.w += c[u].w; }
+                if (r < tile) { before.x += c[u].x; before.y += c[u].y; before.z += c[u].z; before.w += c[u].w; }
+            }
+        }
+        *reinterpret_cast<uint4*>(part_before + (size_t)grp * bins + 4 * q) = before;
+        *reinterpret_cast<uint4*>(part_all + (size_t)grp * bins + 4 * q) = all;
+    }
+    __syncthreads();
+    // thread t owns `per` consecutive digits
     const int per = bins >= kScatThreads ? bins / kScatThreads : 1;
     int64_t mine = 0;
-    if (per >= 4) {
-        for (int k = 0; k < per; k += 4) {
-            const int b = t * per + k;
-            uint4 before = make_uint4(0, 0, 0, 0), all = make_uint4(0, 0, 0, 0);
-            // eight rows are requested before the first is added up: the rows come from the L2 and a thread
-            // that waited for each in turn would spend the whole pass here
-            for (int r0 = 0; r0 < tiles; r0 += 8) {
-                uint4 c[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int r = min(r0 + u, tiles - 1);
-                    c[u] = *reinterpret_cast<const uint4*>(hist + (size_t)r * bins + b);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int r = r0 + u;
-                    if (r < tiles) { all.x += c[u].x; all.y += c[u].y; all.z += c[u].z; all.w += c[u].w; }
-                    if (r < tile) { before.x += c[u].x; before.y += c[u].y; before.z += c[u].z; before.w += c[u].w; }
-                }
-            }
-            s_off[b] = before.x; s_off[b + 1] = before.y; s_off[b + 2] = before.z; s_off[b + 3] = before.w;
-            s_cnt[b] = all.x; s_cnt[b + 1] = all.y; s_cnt[b + 2] = all.z; s_cnt[b + 3] = all.w;   // parked in the first
-            mine += (int64_t)all.x + all.y + all.z + all.w;                                        // wave's row for now
+    for (int i = 0; i < per; ++i) {
+        const int b = t * per + i;
+        if (b >= bins) break;
+        uint32_t before = 0, all = 0;
+        for (int g = 0; g < groups; ++g) {
+            before += part_before[(size_t)g * bins + b];
+            all += part_all[(size_t)g * bins + b];
         }
-    } else {
-        for (int k = 0; k < per; ++k) {
-            const int b = t * per + k;
-            if (b >= bins) break;
-            uint32_t before = 0, all = 0;
-            for (int r0 = 0; r0 < tiles; r0 += 8) {
-                uint32_t c[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) c[u] = hist[(size_t)min(r0 + u, tiles - 1) * bins + b];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (r0 + u < tiles) all += c[u];
-                    if (r0 + u < tile) before += c[u];
-                }
-            }
-            s_off[b] = before;
-            s_cnt[b] = all;
-            mine += all;
-        }
+        s_off[b] = before;
+        part_all[b] = all;             // the first group's: this thread's alone from here on
+        mine += all;
     }
     int64_t total;
     int64_t run = block_exclusive_scan<kScatThreads / kWave>(mine, s_wave, total);       // keys with a smaller digit than this thread's first
     for (int k = 0; k < per; ++k) {
         const int b = t * per + k;
         if (b >= bins) break;
-        const uint32_t all = s_cnt[b];
+        const uint32_t all = part_all[b];
         s_off[b] += (uint32_t)run;
         run += all;
     }
@@ -790,17 +792,7 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
     for (int i = t; i < bins * (kScatThreads / kWave); i += kScatThreads) s_cnt[i] = 0;
     __syncthreads();
 
-    constexpr int kScatItems = TILE / kScatThreads;
-    const int64_t wbase = (int64_t)tile * TILE + (int64_t)wave * (kScatItems * kWave);
-    uint64_t k_[kScatItems];
-    uint32_t v_[kScatItems], r_[kScatItems];
     uint32_t* my_cnt = s_cnt + (size_t)wave * bins;
-#pragma unroll
-    for (int j = 0; j < kScatItems; ++j) {       // all loads of the tile first
-        const int64_t i = min(wbase + (int64_t)j * kWave + lane, m - 1);   // clamped: no load sits in a branch
-        k_[j] = kin[i];
-        v_[j] = vin[i];
-    }
 #pragma unroll
     for (int j = 0; j < kScatItems; ++j) {
         const int64_t i = wbase + (int64_t)j * kWave + lane;
@@ -847,102 +839,117 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
     }
 }
 
-// Sorted keys -> segment heads, head_excl[p] = number of heads before position p, seg_start[s] = first
-// position of segment s (and m after the last), status->num_segments.
-__global__ void __launch_bounds__(kThreads) k_fast_segments(const uint64_t* __restrict__ key, int64_t m, int64_t* __restrict__ head_excl,
-                                                            int32_t* __restrict__ seg_start, ScanWorkspace* ws, IngestStatus* st) {
-    __shared__ int64_t s_wave[kThreads / kWave];
-    __shared__ int64_t s_tile, s_excl;
-    if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&ws->ticket, 1u);
-    __syncthreads();
-    const int64_t tile = s_tile;
-    const int64_t p0 = (tile * kThreads + threadIdx.x) * kSegItems;
-    int h[kSegItems];
-    int64_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < kSegItems; ++j) {
-        const int64_t p = p0 + j;
-        h[j] = (p < m && is_head(key, p)) ? 1 : 0;
-        mine += h[j];
-    }
-    int64_t total;
-    int64_t run = block_exclusive_scan(mine, s_wave, total);
-    if (threadIdx.x < kWave) {
-        const int64_t excl = chain_wave(ws, st, tile, total, threadIdx.x);
-        if (threadIdx.x == 0) s_excl = excl;
-    }
-    __syncthreads();
-    run += s_excl;
-#pragma unroll
-    for (int j = 0; j < kSegItems; ++j) {
-        const int64_t p = p0 + j;
-        if (p >= m) break;
-        head_excl[p] = run;
-        if (h[j]) seg_start[run] = (int32_t)p;
-        run += h[j];
-        if (p == m - 1) {
-            seg_start[run] = (int32_t)m;
-            st->num_segments = run;
-        }
-    }
-}
-
-// The per-segment plan and, in the same launch, every segment's offset into the edge-line and directory pools.
+// Segments, the per-segment plan, and every segment's number and offset into the edge-line and directory pools, in one launch.
+// A thread per sorted position; those at a segment's first edge plan it.  Four chained scans run side by side in the first
+// four waves: segments and new blocks (at most 2^21 of each in a batch, one in the upper half of the value), edge lines,
+// directory records, new slots.  The last tile's sums are the batch's, and it hands the record over without anybody being
+// counted in.  What it costs is its chain of dependent reads (position, node, tail of a long list, look-back, record): 10^5
+// edges 6.5 us for the segments and 21 for their plan as two launches with atomics for the totals.  512 positions a tile: 256
+// and 1024 were both slower somewhere (10^4 edges over 2^16 nodes 54 / 56 / 59 us a batch with 256 / 512 / 1024, 2 * 10^5
+// power-law ids 194 / 185 / 184).  32 batches of 10^5 edges, each sampled, into a new store: 3380 -> 2930 us together with
+// the table of tile histograms read four rows side by side (k_fast_scatter).
 __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, const uint64_t* __restrict__ key,
-                                                            const uint32_t* __restrict__ val, const int32_t* __restrict__ seg_start,
-                                                            SegPlan* __restrict__ plan, int64_t* __restrict__ lines_base,
-                                                            int64_t* __restrict__ dir_base, const ScanWorkspace* seg_scan,
-                                                            ScanWorkspace* lines_scan, ScanWorkspace* dir_scan, int plan_tiles) {
+                                                            const uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
+                                                            int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
+                                                            int64_t* __restrict__ lines_base, int64_t* __restrict__ dir_base,
+                                                            const PlanScans scans, int plan_tiles) {
     constexpr int kWaves = kPlanThreads / kWave;
-    __shared__ int64_t s_wave[kWaves];
-    __shared__ int64_t s_tile, s_excl_lines, s_excl_dir;
-    if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&lines_scan->ticket, 1u);
+    __shared__ int64_t s_tile, s_excl[kPlanScans], s_sum[kPlanScans][kWaves];
+    __shared__ int32_t s_heads[kWaves], s_end;
+    __shared__ int32_t s_start[kPlanThreads + 1];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    if (t == 0) s_tile = (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
     __syncthreads();
-    const int64_t tile = s_tile;
-    // a time-out of the segment numbering leaves seg_start incomplete: nothing may be read through it
-    const bool ok = seg_scan->error == 0;
-    const int64_t nseg = ok ? a.status->num_segments : 0;
-    const int64_t s = tile * kPlanThreads + threadIdx.x;
-    int64_t lines = 0, dirs = 0, blocks = 0, slots = 0;
-    if (s < nseg) {
-        SegPlan P{};
-        const int32_t p0 = seg_start[s];
-        plan_segment(a, (uint32_t)(key[p0] >> 32), val[p0], seg_start[s + 1] - p0, P, lines, dirs, blocks, slots);
-        plan[s] = P;
-    }
-    int64_t tot_lines, tot_dir;
-    const int64_t in_lines = block_exclusive_scan<kWaves>(lines, s_wave, tot_lines);
-    const int64_t in_dir = block_exclusive_scan<kWaves>(dirs, s_wave, tot_dir);
-    // the two look-backs run side by side in the first two waves
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (wave < 2) {
-        const int64_t excl = chain_wave(wave == 0 ? lines_scan : dir_scan, a.status, tile, wave == 0 ? tot_lines : tot_dir, lane);
-        if (lane == 0) *(wave == 0 ? &s_excl_lines : &s_excl_dir) = excl;
-    }
-    __syncthreads();
-    if (s < a.m) {
-        lines_base[s] = s_excl_lines + in_lines;
-        dir_base[s] = s_excl_dir + in_dir;
-    }
-    if (tile == plan_tiles - 1 && threadIdx.x == 0) {
-        a.status->total_lines = s_excl_lines + tot_lines;
-        a.status->total_dir = s_excl_dir + tot_dir;
-    }
-    add_block_totals<kWaves>(a.status, blocks, slots);
-    if (a.host_status) {
-        // The workgroup that finishes last hands the record to the host.  Every thread's updates of the record (an edge
-        // found out of order, a scan that timed out) have been performed when its workgroup counts itself in.  The copy
-        // reads past the caches of this compute unit.
-        wait_for_memory();
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __threadfence();
-            const uint32_t before = atomicAdd(&lines_scan->pad[0], 1u);
-            if (before == (uint32_t)plan_tiles - 1u) {
-                __threadfence();
-                hand_over(a);
-            }
+    const int64_t tile = s_tile, p0 = tile * kPlanThreads, p = p0 + t;
+    const uint64_t k = p < a.m ? key[p] : 0, before = p > 0 && p < a.m ? key[p - 1] : 0;
+    const bool head = p < a.m && (p == 0 || (uint32_t)(k >> 32) != (uint32_t)(before >> 32));
+    if (wave == kWaves - 1) {
+        // where the tile's last segment ends: beyond the tile by at most a batch, found 64 positions at a time
+        int64_t lo = min(p0 + kPlanThreads, a.m), n = a.m - lo;
+        const uint32_t last = (uint32_t)(key[lo - 1] >> 32);
+        while (n > 0) {
+            // the first 64 positions in the first round (most segments are short), then 64-way
+            const int64_t s = lo == p0 + kPlanThreads && n > kWave ? 1 : (n + kWave - 1) / kWave;
+            const int64_t at = lo + min((int64_t)(lane + 1) * s - 1, n - 1);
+            const int cnt = __popcll(__ballot((uint32_t)(key[at] >> 32) == last));
+            const int64_t step = min((int64_t)cnt * s, n);
+            lo += step;
+            n = cnt == kWave ? n - step : max(min(s - 1, n - step), (int64_t)0);
         }
+        if (lane == 0) s_end = (int32_t)lo;
+    }
+    const uint64_t heads = __ballot(head);
+    if (lane == 0) s_heads[wave] = __popcll(heads);
+    __syncthreads();
+    int32_t local = __popcll(heads & ((1ull << lane) - 1ull)), num_heads = 0;       // heads of the tile before this position
+    for (int w = 0; w < kWaves; ++w) {
+        const int32_t c = s_heads[w];
+        if (w < wave) local += c;
+        num_heads += c;
+    }
+    if (head) s_start[local] = (int32_t)p;
+    if (t == 0) s_start[num_heads] = s_end;
+    __syncthreads();
+    SegPlan P{};
+    int64_t lines = 0, dirs = 0, blocks = 0, slots = 0;
+    if (head) plan_segment(a, (uint32_t)(k >> 32), val[p], s_start[local + 1] - p, P, lines, dirs, blocks, slots);
+    // exclusive sums of the scans' values over the workgroup
+    int64_t v[kPlanScans] = {((int64_t)(head ? 1 : 0) << 32) | blocks, lines, dirs, slots}, total[kPlanScans];
+#pragma unroll
+    for (int i = 0; i < kPlanScans; ++i) {
+        const int64_t own = v[i];
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int64_t u = (int64_t)__shfl_up((long long)v[i], d, kWave);
+            if (lane >= d) v[i] += u;
+        }
+        if (lane == kWave - 1) s_sum[i][wave] = v[i];
+        v[i] -= own;
+    }
+    wait_for_memory();               // this thread's reports have been performed before its tile's totals are published
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPlanScans; ++i) {
+        total[i] = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            const int64_t x = s_sum[i][w];
+            if (w < wave) v[i] += x;
+            total[i] += x;
+        }
+    }
+    if (wave < kPlanScans) {
+        const int64_t excl = chain_wave(scans.ws[wave], a.status, tile,
+                                        wave == 0 ? total[0] : (wave == 1 ? total[1] : (wave == 2 ? total[2] : total[3])), lane);
+        if (lane == 0) s_excl[wave] = excl;
+        wait_for_memory();           // a time-out's report likewise
+    }
+    __syncthreads();
+    const int64_t seg = (v[0] + s_excl[0]) >> 32;
+    if (p < a.m) head_excl[p] = seg;
+    // (after a chained scan's time-out the sums are short and nothing is applied: the stores stay within the batch)
+    if (head && seg < a.m) {
+        seg_start[seg] = (int32_t)p;
+        plan[seg] = P;
+        lines_base[seg] = v[1] + s_excl[1];
+        dir_base[seg] = v[2] + s_excl[2];
+    }
+    if (tile == plan_tiles - 1 && t == 0) {
+        // every earlier tile has published, and reported what it had to before that: the record is complete
+        const int64_t nseg = (s_excl[0] + total[0]) >> 32;
+        if (nseg <= a.m) seg_start[nseg] = (int32_t)a.m;
+        IngestStatus rec = load_status(a.status);
+        rec.num_segments = nseg;
+        rec.total_lines = s_excl[1] + total[1];
+        rec.total_dir = s_excl[2] + total[2];
+        rec.new_blocks = (unsigned long long)((s_excl[0] + total[0]) & 0xffffffffll);
+        rec.new_slots = (unsigned long long)(s_excl[3] + total[3]);
+        IngestStatus* st = a.status;
+        st->num_segments = rec.num_segments;
+        st->total_lines = rec.total_lines;
+        st->total_dir = rec.total_dir;
+        st->new_blocks = rec.new_blocks;
+        st->new_slots = rec.new_slots;
+        if (a.host_status) hand_over(a, rec);
     }
 }
 
@@ -1257,8 +1264,8 @@ struct Carve {
     int nblk;
     // short pipeline (batches of at most kFastMaxBatch edges)
     uint32_t* tile_hist[2];        // [tiles][bins] per radix pass
-    ScanWorkspace *seg_scan, *lines_scan, *dir_scan;
-    int fast_tiles, seg_tiles, plan_tiles;
+    PlanScans scans;
+    int fast_tiles, plan_tiles;
     size_t bytes;
 };
 
@@ -1284,13 +1291,11 @@ Carve carve(void* ws, int64_t m) {
     c.plan = reinterpret_cast<SegPlan*>(take(mm * sizeof(SegPlan)));
     if (m <= kFastMaxBatch) {
         c.fast_tiles = (int)((mm + fast_tile_keys(m) - 1) / fast_tile_keys(m));
-        c.seg_tiles = (int)((mm + kThreads * kSegItems - 1) / (kThreads * kSegItems));
         c.plan_tiles = (int)((mm + kPlanThreads - 1) / kPlanThreads);
         for (int p2 = 0; p2 < 2; ++p2)
             c.tile_hist[p2] = reinterpret_cast<uint32_t*>(take((size_t)c.fast_tiles * (size_t(1) << kFastMaxBits) * 4));
-        c.seg_scan = reinterpret_cast<ScanWorkspace*>(take(sizeof(ScanWorkspace) + (size_t)(c.seg_tiles + 1) * 8));
-        c.lines_scan = reinterpret_cast<ScanWorkspace*>(take(sizeof(ScanWorkspace) + (size_t)(c.plan_tiles + 1) * 8));
-        c.dir_scan = reinterpret_cast<ScanWorkspace*>(take(sizeof(ScanWorkspace) + (size_t)(c.plan_tiles + 1) * 8));
+        for (ScanWorkspace*& w : c.scans.ws)
+            w = reinterpret_cast<ScanWorkspace*>(take(sizeof(ScanWorkspace) + (size_t)(c.plan_tiles + 1) * 8));
     }
     c.bytes = o;
     return c;
@@ -1352,7 +1357,7 @@ int fast_digit_bits(int64_t m, int64_t num_nodes) {
     int bits = 0;
     while (bits < 32 && (int64_t(1) << bits) < num_nodes) ++bits;
     if (bits > 2 * kFastMaxBits) return 0;
-    return std::max(1, (bits + 1) / 2);
+    return std::max(2, (bits + 1) / 2);            // (at least four bins: a table row is read 16 bytes at a time)
 }
 
 bool ingest_fast_ok(int64_t m, int64_t num_nodes) { return fast_digit_bits(m, num_nodes) > 0; }
@@ -1373,8 +1378,7 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
 #define TNS_FAST_SORT(TILE)                                                                                                          \
     do {                                                                                                                             \
         hipLaunchKernelGGL((k_fast_keys<TILE>), dim3((unsigned)c.fast_tiles), dim3(kThreads), (size_t)bins * 4, stream, a, c.keyA,  \
-                           c.valA, c.tile_hist[0], c.tile_hist[1], bits, c.seg_scan, c.lines_scan, c.dir_scan, c.seg_tiles,          \
-                           c.plan_tiles);                                                                                            \
+                           c.valA, c.tile_hist[0], c.tile_hist[1], bits, c.scans, c.plan_tiles);                                     \
         hipLaunchKernelGGL((k_fast_scatter<TILE>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, c.keyA, c.valA,    \
                            c.keyB, c.valB, a.m, 32, bits, c.fast_tiles, c.tile_hist[0], c.tile_hist[1], 32 + bits);                  \
         hipLaunchKernelGGL((k_fast_scatter<TILE>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, c.keyB, c.valB,    \
@@ -1386,10 +1390,8 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
         default: TNS_FAST_SORT(kFastTileMax); break;
     }
 #undef TNS_FAST_SORT
-    hipLaunchKernelGGL(k_fast_segments, dim3((unsigned)c.seg_tiles), dim3(kThreads), 0, stream, c.keyA, a.m, c.head_excl, c.seg_start,
-                       c.seg_scan, a.status);
-    hipLaunchKernelGGL(k_fast_plan, dim3((unsigned)c.plan_tiles), dim3(kPlanThreads), 0, stream, a, c.keyA, c.valA, c.seg_start, c.plan,
-                       c.lines_base, c.dir_base, c.seg_scan, c.lines_scan, c.dir_scan, c.plan_tiles);
+    hipLaunchKernelGGL(k_fast_plan, dim3((unsigned)c.plan_tiles), dim3(kPlanThreads), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start,
+                       c.plan, c.lines_base, c.dir_base, c.scans, c.plan_tiles);
     return hipGetLastError();
 }
 

@@ -245,3 +245,31 @@ def test_one_workgroup_batches_at_digit_and_wave_boundaries(B, oracle_lib, nodes
     assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl, targets, t_start, t_end, None, 10, 0, 0, 0),
                 oracle_lib, f"nodes={nodes}")
     plan.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1, 510])
+def test_segments_across_tiles_of_the_plan(B, oracle_lib, shift):
+    # batches planned 512 sorted positions at a time: segments that end just before, at and after a tile's end, that fill
+    # several tiles (their end is searched for 64-way), and the same again on what the first batch left
+    rng = np.random.default_rng(shift)
+    lengths = [shift, 1, 511, 512, 513, 1, 63, 64, 65, 447, 1, 5000, 1, 2, 40_000, 1023, 1025, 70_000, 3]
+    src = np.concatenate([np.full(c, v, np.int32) for v, c in enumerate(lengths)])
+    m, nodes, batches = len(src), len(lengths), 3
+    src = np.concatenate([rng.permutation(src) for _ in range(batches)])
+    n = len(src)
+    dst = rng.integers(0, nodes, n, dtype=np.int32)
+    ts = np.sort(rng.integers(0, n // 4, n)).astype(np.float32)
+    st = W.Stream(nodes, src, dst, ts, m)
+    wl = wl_of(st)
+    plan = device_plan(B, wl)
+    bs = oracle_lib.BlockStore(nodes, 48, 0)
+    bs.add_stream(src, dst, ts, m)
+    ref, got = bs.stats(), plan.stats()
+    for name in ("num_blocks", "wasted_slots", "max_list_len"):
+        assert got[name] == ref[name], name
+    targets, t_start, t_end = W.random_queries(7, st, 3000)
+    for policy in (0, 1):
+        plan.set_sampler(10, policy, 0, 4)
+        assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl, targets, t_start, t_end, None, 10, policy, 0, 4),
+                    oracle_lib, f"policy={policy}")
+    plan.close()
