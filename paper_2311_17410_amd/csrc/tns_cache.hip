@@ -9,8 +9,10 @@
 #include <cmath>
 #include <cstdint>
 #include <new>
+#include <type_traits>
 
 #include "../../include/tns_cache.h"
+#include "tns_chain.h"
 #include "tns_internal.h"
 
 using tns::DeviceGuard;
@@ -37,6 +39,8 @@ struct Ctl {
     int32_t remaining;                    // how many entries are still to be taken among keys equal to the threshold
     int32_t m;                            // entries replaced by this update
     int32_t n_unique;                     // distinct missed ids of the batch
+    int32_t now;                          // LRU: number of this update; 0 otherwise
+    int64_t ring;                         // FIFO: slot of the first entry replaced by this update
     // state after each pass of the radix select (index p = after p passes; 0 = nothing decided) and the histogram
     // each pass fills: a pass's digit is picked by the kernel that follows it, in every workgroup's prologue
     uint32_t sel_prefix[kPasses + 1], sel_mask[kPasses + 1];
@@ -48,11 +52,14 @@ struct CacheState {
     int32_t* slot_of;    // [num_ids]   slot of a cached id, -1 otherwise
     int32_t* first_idx;  // [num_ids]   scratch: first batch position of a missed id (kNoIndex between fetches)
     int32_t* id_of;      // [capacity]  id held by a slot, -1 if empty
-    int32_t* score;      // [capacity]  recent score (LRU) / access count (LFU)
-    int32_t* touched;    // [capacity]  LRU: accessed by the current batch
+    // [capacity]  LFU: access count.  LRU: the number of the update that last accessed the entry; its recent score is that
+    // minus the number of the latest update, so that no update has to decrement every score (all arithmetic modulo 2^32).
+    int32_t* score;
+    int32_t* updates;    // LRU: number of updates so far; 0 otherwise
     float* rows;         // [capacity * dim]
     unsigned long long* counters;  // [kStripes][3]: hits, misses, replaced (striped: one hot word would serialise the batch)
     int64_t* ring;       // FIFO position
+    int64_t capacity;
 };
 
 __global__ void __launch_bounds__(256) k_fill_i32(int32_t* p, int64_t n, int32_t v) {
@@ -82,17 +89,20 @@ __global__ void __launch_bounds__(256) k_rebuild_map(const int32_t* __restrict__
 constexpr int kLookupUnroll = 4;
 constexpr int kLookupTable = 2 * 256 * kLookupUnroll;      // power of two
 constexpr int32_t kFreeKey = INT_MIN;                      // hits: slot >= 0; misses: -1 - id > INT_MIN
-__global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_t num_ids, int64_t B,
+__global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, int64_t num_ids, int64_t B,
                                                 const int32_t* __restrict__ ids, int32_t* __restrict__ slots,
-                                                uint8_t* __restrict__ hit, Ctl* ctl) {
+                                                uint8_t* __restrict__ hit, Ctl* ctl, tns::ScanWorkspace* chain) {
     __shared__ int32_t s_key[kLookupTable], s_val[kLookupTable];
     __shared__ int32_t s_hits, s_misses;
+    const int32_t now = policy == TNS_CACHE_LRU ? (int32_t)((uint32_t)*c.updates + 1u) : 0;
     if (blockIdx.x == 0) {          // scalars of this update
-        if (threadIdx.x == 0) { ctl->prefix = 0; ctl->mask = 0; ctl->remaining = 0; ctl->m = 0; ctl->n_unique = 0; }
+        if (threadIdx.x == 0) { ctl->now = now; ctl->prefix = 0; ctl->mask = 0; ctl->remaining = 0; ctl->m = 0; ctl->n_unique = 0; }
         int4* const all = reinterpret_cast<int4*>(&ctl->hist[0][0]);
 #pragma unroll
         for (int i = 0; i < kPasses * kBins / 4 / 256; ++i) all[i * 256 + threadIdx.x] = make_int4(0, 0, 0, 0);
+        if (chain && threadIdx.x == 1) { chain->ticket = 0; chain->error = 0; }
     }
+    if (chain && threadIdx.x == 0) chain->status[blockIdx.x] = 0;      // a workgroup here and a tile of the chain are both 1024 ids
     const int64_t stride = (int64_t)gridDim.x * 256;
     const int64_t b0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int32_t id[kLookupUnroll], s[kLookupUnroll];
@@ -128,7 +138,7 @@ __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_
         if (b < B) {
             if (s[u] >= 0) {
                 is_hit = 1;
-                if (policy == TNS_CACHE_LRU) c.touched[s[u]] = 1;
+                if (policy == TNS_CACHE_LRU) c.score[s[u]] = now;
                 else if (policy == TNS_CACHE_LFU) atomicAdd(&s_val[entry_of(s[u])], 1);
             } else if (s[u] == -1) {
                 is_miss = 1;
@@ -157,29 +167,27 @@ __global__ void __launch_bounds__(256) k_lookup(CacheState c, int policy, int64_
     }
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 // out[b] = cached row or row of the backing store; VEC floats per thread, rows stay coalesced
 // The slot comes from the id map directly (the threads of a row read the same two words), so the gather does not
 // wait for the lookup kernel, which records the accesses for the update beside it.  A thread moves kGatherUnroll
 // pieces, one grid width apart, and runs each dependent step (id, slot, row, store) for all of them before the next:
 // the kernel is a copy, and a copy on this machine is bound by how much each compute unit has in flight.
 constexpr int kGatherUnroll = 8;
-template <int VEC>
-__global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
-                                                int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
-                                                const int32_t* __restrict__ slot_of, float* __restrict__ out) {
+template <int VEC, int THREADS, typename idx_t>
+__device__ __forceinline__ void gather_body(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
+                                            int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
+                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, int64_t bid, int64_t nb) {
     const int32_t per_row = dim / VEC;
     const int64_t total = B * per_row;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t stride = nb * THREADS;
+    const int64_t t0 = bid * THREADS + threadIdx.x;
     int64_t b[kGatherUnroll];
     int32_t col[kGatherUnroll], id[kGatherUnroll], s[kGatherUnroll];
 #pragma unroll
     for (int u = 0; u < kGatherUnroll; ++u) {
-        const int64_t t = min(t0 + (int64_t)u * stride, total - 1);      // clamped: no load sits in a branch
-        b[u] = t / per_row;
-        col[u] = (int32_t)(t - b[u] * per_row) * VEC;
+        const idx_t t = (idx_t)min(t0 + (int64_t)u * stride, total - 1);      // clamped: no load sits in a branch
+        b[u] = (int64_t)(t / (idx_t)per_row);
+        col[u] = (int32_t)(t - (idx_t)b[u] * (idx_t)per_row) * VEC;
         id[u] = ids[b[u]];
     }
 #pragma unroll
@@ -190,38 +198,25 @@ __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, 
     }
     // the output and the rows of the backing store are touched once (non-temporal); the cached rows are
     // what should stay in the L2
-    if (VEC == 4) {
-        f32x4 v[kGatherUnroll];
+    typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    vec_t v[kGatherUnroll];
 #pragma unroll
-        for (int u = 0; u < kGatherUnroll; ++u) {
-            const float* src = s[u] >= 0 ? rows + (int64_t)s[u] * dim + col[u] : store + (int64_t)(s[u] == -1 ? id[u] : 0) * dim + col[u];
-            v[u] = s[u] >= 0 ? *reinterpret_cast<const f32x4*>(src) : __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src));
-            if (s[u] == -2) v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int u = 0; u < kGatherUnroll; ++u)
-            if (t0 + (int64_t)u * stride < total) __builtin_nontemporal_store(v[u], reinterpret_cast<f32x4*>(out + b[u] * dim + col[u]));
-    } else {
-        float v[kGatherUnroll];
-#pragma unroll
-        for (int u = 0; u < kGatherUnroll; ++u) {
-            const float* src = s[u] >= 0 ? rows + (int64_t)s[u] * dim + col[u] : store + (int64_t)(s[u] == -1 ? id[u] : 0) * dim + col[u];
-            v[u] = s[u] >= 0 ? *src : __builtin_nontemporal_load(src);
-            if (s[u] == -2) v[u] = 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kGatherUnroll; ++u)
-            if (t0 + (int64_t)u * stride < total) __builtin_nontemporal_store(v[u], out + b[u] * dim + col[u]);
+    for (int u = 0; u < kGatherUnroll; ++u) {
+        const float* src = s[u] >= 0 ? rows + (int64_t)s[u] * dim + col[u] : store + (int64_t)(s[u] == -1 ? id[u] : 0) * dim + col[u];
+        v[u] = s[u] >= 0 ? *reinterpret_cast<const vec_t*>(src) : __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(src));
+        if (s[u] == -2) v[u] = vec_t(0.f);
     }
+#pragma unroll
+    for (int u = 0; u < kGatherUnroll; ++u)
+        if (t0 + (int64_t)u * stride < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out + b[u] * dim + col[u]));
 }
 
-// LRU: every score is decremented, accessed entries are reset to 0
-__global__ void __launch_bounds__(256) k_lru_scores(int32_t* __restrict__ score, int32_t* __restrict__ touched, int64_t capacity) {
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s < capacity) {
-        score[s] = touched[s] ? 0 : score[s] - 1;
-        touched[s] = 0;
-    }
+// idx_t: an unsigned type that holds the number of pieces
+template <int VEC, typename idx_t>
+__global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
+                                                int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
+                                                const int32_t* __restrict__ slot_of, float* __restrict__ out) {
+    gather_body<VEC, 256, idx_t>(rows, store, dim, B, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
 }
 
 // ---- compaction of flagged elements in three launches -------------------------------------------
@@ -368,7 +363,8 @@ struct NewIds {
 
 // ---- victims: the m entries with the lowest (score, slot) --------------------------------------
 
-__device__ __forceinline__ uint32_t score_key(int32_t score) { return (uint32_t)score ^ 0x80000000u; }   // unsigned order = signed order
+// unsigned order = signed order of the scores
+__device__ __forceinline__ uint32_t score_key(int32_t stored, int32_t now) { return ((uint32_t)stored - (uint32_t)now) ^ 0x80000000u; }
 
 // Radix select of the m-th smallest key.  A pass is one launch that histograms the digit over the entries whose
 // decided high bits match; the digit in which the remaining-th smallest key falls is picked by the NEXT kernel, by
@@ -420,13 +416,10 @@ __device__ __forceinline__ SelState select_pick(Ctl* ctl, int pass /* 1..kPasses
     return out;
 }
 
-// Histogram of pass `pass` (0-based).  LRU_UPDATE (pass 0 under LRU): the scores are brought up to date on the way
-// (every score decremented, entries accessed by the batch reset to 0); that pass does not know yet whether
-// anything will be replaced and histograms regardless.  `bid` / `nb`: this workgroup's index and the number of
-// workgroups that share the pass (the kernel may hold other work in its other workgroups).
-template <bool LRU_UPDATE>
-__device__ __forceinline__ void select_hist_body(int32_t* __restrict__ score, int32_t* __restrict__ touched, int64_t capacity,
-                                                 int pass, Ctl* ctl, int64_t bid, int64_t nb) {
+// Histogram of pass `pass` (0-based); pass 0 does not know yet whether anything will be replaced and histograms
+// regardless.  `bid` / `nb`: this workgroup's index and the number of workgroups that share the pass (the kernel may hold
+// other work in its other workgroups).
+__device__ __forceinline__ void select_hist_body(const int32_t* __restrict__ score, int64_t capacity, int pass, Ctl* ctl, int64_t bid, int64_t nb) {
     __shared__ int32_t s_h[kBins];
     uint32_t prefix = 0, mask = 0;
     if (pass > 0) {
@@ -435,6 +428,7 @@ __device__ __forceinline__ void select_hist_body(int32_t* __restrict__ score, in
         prefix = st.prefix;
         mask = st.mask;
     }
+    const int32_t now = ctl->now;
     const int shift = digit_shift(pass);
     const uint32_t dmask = digit_mask(pass);
 #pragma unroll
@@ -445,13 +439,7 @@ __device__ __forceinline__ void select_hist_body(int32_t* __restrict__ score, in
         bool take = false;
         uint32_t d = 0;
         if (s < capacity) {
-            int32_t sc = score[s];
-            if (LRU_UPDATE) {
-                sc = touched[s] ? 0 : sc - 1;
-                score[s] = sc;
-                touched[s] = 0;
-            }
-            const uint32_t k = score_key(sc);
+            const uint32_t k = score_key(score[s], now);
             take = (k & mask) == prefix;
             d = (k >> shift) & dmask;
         }
@@ -474,10 +462,8 @@ __device__ __forceinline__ void select_hist_body(int32_t* __restrict__ score, in
     }
 }
 
-template <bool LRU_UPDATE>
-__global__ void __launch_bounds__(256) k_select_hist(int32_t* __restrict__ score, int32_t* __restrict__ touched, int64_t capacity,
-                                                     int pass, Ctl* ctl) {
-    select_hist_body<LRU_UPDATE>(score, touched, capacity, pass, ctl, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(256) k_select_hist(const int32_t* __restrict__ score, int64_t capacity, int pass, Ctl* ctl) {
+    select_hist_body(score, capacity, pass, ctl, blockIdx.x, gridDim.x);
 }
 
 // The victims in ascending slot order: every entry below the threshold key and the first `remaining`
@@ -487,13 +473,13 @@ struct Victims {
     const Ctl* ctl;
     int32_t* victims;
     __device__ int64_t count_with(int64_t s, uint32_t t) const {
-        const uint32_t k = score_key(score[s]);
+        const uint32_t k = score_key(score[s], ctl->now);
         return k < t ? (int64_t(1) << 32) : (k == t ? 1 : 0);
     }
     __device__ int64_t count(int64_t s) const { return ctl->m <= 0 ? 0 : count_with(s, ctl->prefix); }
     __device__ void emit(int64_t s, int64_t before) const {
         const int64_t below_before = before >> 32, eq_before = before & 0xffffffffll, rem = ctl->remaining;
-        const bool below = score_key(score[s]) < ctl->prefix;
+        const bool below = score_key(score[s], ctl->now) < ctl->prefix;
         if (below || eq_before < rem) victims[below_before + (eq_before < rem ? eq_before : rem)] = (int32_t)s;
     }
     __device__ void total(int64_t) const {}
@@ -522,22 +508,249 @@ __global__ void __launch_bounds__(256) k_victims_tile_sums(const Victims f, Ctl*
 // Two independent pieces of the update in one launch (the chain of short launches is what the update costs):
 // workgroups [0, tiles) collect the distinct missed ids (which also fixes m), the other `hb` workgroups run pass 0
 // of the radix select over the scores, which depends on the lookup only.
-template <bool LRU_UPDATE>
 __global__ void __launch_bounds__(256) k_newids_collect_hist0(const NewIds f, int64_t n, const int64_t* __restrict__ sums, int64_t tiles,
-                                                              int32_t* __restrict__ score, int32_t* __restrict__ touched,
-                                                              int64_t capacity, Ctl* ctl, int64_t hb) {
+                                                              const int32_t* __restrict__ score, int64_t capacity, Ctl* ctl, int64_t hb) {
     if ((int64_t)blockIdx.x < tiles) flag_collect_body<NewIds, true>(f, n, sums, blockIdx.x, tiles);
-    else select_hist_body<LRU_UPDATE>(score, touched, capacity, 0, ctl, (int64_t)blockIdx.x - tiles, hb);
+    else select_hist_body(score, capacity, 0, ctl, (int64_t)blockIdx.x - tiles, hb);
 }
 
-__global__ void __launch_bounds__(256) k_fifo_victims(int64_t capacity, int32_t max_replace, int64_t* ring, const Ctl* ctl,
-                                                      int32_t* __restrict__ victims) {
-    const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    const int32_t m = ctl->m;
-    const int64_t r = *ring;
-    if (i < m) victims[i] = (int32_t)((r + i) % capacity);
+// ---- the update in one launch: FIFO, and caches of up to kOneGroupEntries entries ------------------
+//
+// What bounds the fetch of a batch of some ten thousand rows is the number of launches that wait for one another: tile sums
+// of the missed ids, their collection, three histogram passes, tile sums of the victims, their collection, and two
+// events around them.  Here one launch holds all of it, beside the gather.  A workgroup per 1024 ids of the batch counts its
+// first occurrences of missed ids and learns from a chained scan over the workgroups what comes before it; the one with
+// the last tile then knows the number of entries to replace and selects the victims by itself, every score in a
+// register of one of its 1024 threads.  The scores are requested before its ids and arrive meanwhile.
+// The threshold, the m-th lowest score, is found by counting the scores below a bound (1.3 us each for 42 K entries):
+// the bound rises from the lowest score in steps that grow fourfold and is then bisected.  Victims are the oldest or
+// rarest entries and lie within a few values of the lowest, so that one to six counts are usual; any 32-bit scores take at most
+// 16 and 32.  (A histogram in LDS has all its lanes adding to a handful of words.)  One workgroup issues about an
+// instruction per SIMD every four cycles, so 44 scores per thread make the instructions per score what counts: the victims are
+// stored in 2.5 us where the equal ones are all taken or all left, by one comparison; with both compared for
+// every score and counted in a pass of their own they took 9.  Time stamps, batch of 66600 of which 8388 are replaced: new ids
+// known at 8 us, threshold at 15, victims stored at 18.
+// 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO: 66600 ids 71 / 74 / 61 -> 34 / 36 / 32, 16000 ids 67 / 67 / 60
+// -> 22 / 19 / 16, 600 ids 69 / 67 / 60 -> 16 / 15 / 13.
+constexpr int kOneGroup = 1024, kOneGroupWaves = kOneGroup / kWave;
+constexpr int kItems = 64, kItemStep = 8;                         // scores per thread, and per uniform branch
+// Where the line lies: a large gather saturates the memory, and the chain of dependent reads of the tiles beside it then
+// takes longer than the short launches do on a stream of their own.  Us per fetch, LRU / LFU / FIFO, this form and the
+// other: 262144 rows of 172 floats (11 M pieces of 16 bytes) 97 / 118 / 97 and 116 / 132 / 102, 524288 rows (23 M) 174 / 214 / 171 and
+// 169 / 194 / 162; rows of 173 floats, LRU, 66600 (12 M pieces of 4 bytes) 47 and 71, 262144 (45 M) 151 and 119; 2^20 rows of
+// 32 floats (8 M) 96 and 113.
+constexpr int64_t kGatherWithin = int64_t(1) << 24, kOneLaunchIds = int64_t(1) << 20;
+constexpr int64_t kOneGroupEntries = (int64_t)kOneGroup * kItems;
+
+// set bits of `mask` below this lane
+__device__ __forceinline__ int32_t lanes_before(uint64_t mask) {
+    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
-__global__ void k_fifo_advance(int64_t capacity, int64_t* ring, const Ctl* ctl) { *ring = (*ring + ctl->m) % capacity; }
+
+__device__ __forceinline__ int32_t fifo_slot(int64_t ring, int64_t i, int64_t capacity) {
+    const int64_t s = ring + i;                // ring < capacity, i < capacity
+    return (int32_t)(s >= capacity ? s - capacity : s);
+}
+
+// Number of keys below `bound` in the workgroup, and in this wave.  `s_cnt`: two rows, used in turn, so that one barrier serves.
+__device__ __forceinline__ int32_t count_below(const uint32_t (&key)[kItems], int items, uint32_t bound, int32_t (*s_cnt)[kOneGroupWaves],
+                                               int round, int32_t& of_wave) {
+    int32_t n = 0;
+#pragma unroll
+    for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+        if (i0 < items) {                       // uniform
+            uint64_t below[kItemStep];
+#pragma unroll
+            for (int u = 0; u < kItemStep; ++u) below[u] = __ballot(key[i0 + u] < bound);
+            __builtin_amdgcn_sched_barrier(0);   // the comparisons back to back, none waits for the count of the one before
+#pragma unroll
+            for (int u = 0; u < kItemStep; ++u) n += __popcll(below[u]);
+        }
+    }
+    of_wave = n;
+    int32_t* const row = s_cnt[round & 1];
+    if ((threadIdx.x & (kWave - 1)) == 0) row[threadIdx.x / kWave] = n;
+    __syncthreads();
+    n = 0;
+#pragma unroll
+    for (int w = 0; w < kOneGroupWaves; ++w) n += row[w];
+    return __builtin_amdgcn_readfirstlane(n);
+}
+
+// Distinct missed ids of tile `tile` in the order of their first occurrence, behind those of the tiles before it.
+// Returns their number up to and including this tile.
+__device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile) {
+    __shared__ int32_t s_w[kOneGroupWaves];
+    __shared__ int64_t s_excl;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t b = tile * kOneGroup + threadIdx.x;
+    const uint64_t first = __ballot(b < B && f.count(b));
+    if (lane == 0) s_w[wave] = __popcll(first);
+    __syncthreads();
+    int32_t total = 0, before = 0;
+#pragma unroll
+    for (int w = 0; w < kOneGroupWaves; ++w) {
+        const int32_t n = s_w[w];
+        before += w < wave ? n : 0;
+        total += n;
+    }
+    if (wave == 0) {
+        if (lane == 0 && tile > 0)
+            __hip_atomic_store(&chain->status[tile], tns::kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int64_t excl = tile > 0 ? tns::lookback_exclusive(chain, &chain->error, tile, lane) : 0;
+        if (lane == 0) {
+            __hip_atomic_store(&chain->status[tile], tns::kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_excl = excl;
+        }
+    }
+    __syncthreads();
+    const int64_t excl = s_excl;
+    if ((first >> lane) & 1) f.emit(b, excl + before + lanes_before(first));
+    return excl + total;
+}
+
+// Entries to replace once the last tile knows the number of distinct missed ids.  If a wait of the chained scan ever ran
+// into its bound that number is not to be trusted, and nothing is replaced.
+__device__ __forceinline__ int32_t entries_to_replace(const NewIds& f, int64_t n_unique, tns::ScanWorkspace* chain) {
+    __shared__ int32_t s_m;
+    if (threadIdx.x == 0) {
+        // (whoever reports an error does so before it publishes what the look-back has read)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const bool bad = __hip_atomic_load(&chain->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        f.total(bad ? 0 : n_unique);
+        s_m = f.ctl->m;
+    }
+    __syncthreads();
+    return s_m;
+}
+
+__device__ __forceinline__ void last_tile(const CacheState& c, const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile,
+                                          int32_t* __restrict__ victims) {
+    __shared__ int32_t s_cnt[2][kOneGroupWaves];
+    __shared__ uint32_t s_min[kOneGroupWaves];
+    __shared__ int32_t s_below[kOneGroupWaves], s_equal[kOneGroupWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    // a wave holds `items` times 64 consecutive scores: the lanes of a ballot are in slot order
+    const int32_t C = (int32_t)c.capacity;
+    const int items = (C + kOneGroup * kItemStep - 1) / (kOneGroup * kItemStep) * kItemStep;
+    const int32_t base = wave * items * kWave + lane;
+    uint32_t key[kItems];                      // beyond the last entry: the highest, below no bound
+#pragma unroll
+    for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+        if (i0 >= items) continue;             // uniform
+#pragma unroll
+        for (int i = i0; i < i0 + kItemStep; ++i) key[i] = (uint32_t)c.score[min(base + i * kWave, C - 1)];
+    }
+    const int32_t now = f.ctl->now;
+#pragma unroll
+    for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+        if (i0 >= items) continue;
+#pragma unroll
+        for (int i = i0; i < i0 + kItemStep; ++i) key[i] = base + i * kWave < C ? score_key((int32_t)key[i], now) : ~0u;
+    }
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile);
+    const int32_t m = __builtin_amdgcn_readfirstlane(entries_to_replace(f, n_unique, chain));
+    if (m <= 0) return;
+    uint32_t lowest = ~0u;
+#pragma unroll
+    for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+        if (i0 >= items) continue;
+#pragma unroll
+        for (int i = i0; i < i0 + kItemStep; ++i) lowest = min(lowest, key[i]);
+    }
+    for (int d = kWave / 2; d >= 1; d >>= 1) lowest = min(lowest, (uint32_t)__shfl_xor((int)lowest, d, kWave));
+    if (lane == 0) s_min[wave] = lowest;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kOneGroupWaves; ++w) lowest = min(lowest, s_min[w]);
+    // the m-th lowest key is in [lo, hi); below lo lie below_lo keys, of_lo of them this wave's, and of_hi of this wave's below hi
+    uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lowest), hi = 1ull << 32, step = 1;
+    int32_t below_lo = 0, of_lo = 0, of_hi = max(min(C - wave * items * kWave, items * kWave), 0);
+    int round = 0;
+    while (hi - lo > 1) {
+        const bool rising = hi == 1ull << 32 && lo + step < hi;      // (at most sixteen times, then never again)
+        const uint64_t at = rising ? lo + step : lo + ((hi - lo) >> 1);
+        int32_t of_wave;
+        const int32_t n = count_below(key, items, (uint32_t)at, s_cnt, round++, of_wave);
+        if (n >= m) { hi = at; of_hi = of_wave; }
+        else { lo = at; below_lo = n; of_lo = of_wave; step *= rising ? 4 : 1; }
+    }
+    const uint32_t threshold = (uint32_t)lo;
+    const int32_t rem = m - below_lo;          // to take among keys equal to the threshold, lowest slots first
+    if (lane == 0) { s_below[wave] = of_lo; s_equal[wave] = of_hi - of_lo; }
+    __syncthreads();
+    int32_t below_before = 0, equal_before = 0;
+    for (int w = 0; w < wave; ++w) { below_before += s_below[w]; equal_before += s_equal[w]; }
+    // victims in slot order: every key below the threshold and the first `rem` equal to it, of which `quota` fall to this wave
+    const int32_t quota = __builtin_amdgcn_readfirstlane(min(max(rem - equal_before, 0), of_hi - of_lo));
+    int32_t at = __builtin_amdgcn_readfirstlane(below_before + min(equal_before, rem));
+    if ((quota == 0 || quota == of_hi - of_lo) && threshold != ~0u) {
+        // none or all of its equal ones, as in every wave but one: a single bound
+        const uint32_t bound = quota ? threshold + 1u : threshold;
+#pragma unroll
+        for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+            if (i0 >= items) continue;
+#pragma unroll
+            for (int i = i0; i < i0 + kItemStep; ++i) {
+                const bool take = key[i] < bound;
+                const uint64_t mask = __ballot(take);
+                if (take) victims[(uint32_t)(at + lanes_before(mask))] = base + i * kWave;
+                at += __popcll(mask);
+            }
+        }
+    } else {
+        int32_t left = quota;
+#pragma unroll
+        for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+            if (i0 >= items) continue;
+#pragma unroll
+            for (int i = i0; i < i0 + kItemStep; ++i) {
+                const int32_t s = base + i * kWave;
+                const bool equal = key[i] == threshold && s < C;
+                const uint64_t equals = __ballot(equal);
+                const bool take = key[i] < threshold || (equal && lanes_before(equals) < left);
+                const uint64_t mask = __ballot(take);
+                if (take) victims[(uint32_t)(at + lanes_before(mask))] = s;
+                at += __popcll(mask);
+                left = max(left - (int32_t)__popcll(equals), 0);
+            }
+        }
+    }
+}
+
+// FIFO: the entries this update replaces start at ctl->ring
+__device__ __forceinline__ void fifo_advance(int64_t capacity, int64_t* ring, Ctl* ctl, int32_t m) {
+    const int64_t r = *ring;
+    ctl->ring = r;
+    *ring = (r + m) % capacity;
+}
+__global__ void k_fifo_advance(int64_t capacity, int64_t* ring, Ctl* ctl) { fifo_advance(capacity, ring, ctl, ctl->m); }
+
+// GATHER: floats per piece of the gathered rows
+template <bool SELECT, int GATHER>
+__global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const NewIds f, int64_t B, int64_t tiles, tns::ScanWorkspace* chain,
+                                                      int32_t* __restrict__ victims, const float* __restrict__ store, int32_t dim,
+                                                      int64_t num_ids, float* __restrict__ out) {
+    __shared__ int64_t s_tile;
+    if ((int64_t)blockIdx.x >= tiles) {
+        gather_body<GATHER, kOneGroup, uint32_t>(c.rows, store, dim, B, num_ids, f.ids, c.slot_of, out, (int64_t)blockIdx.x - tiles,
+                                                 (int64_t)gridDim.x - tiles);
+        return;
+    }
+    // tiles are numbered in the order workgroups start, so that a tile only waits for tiles that have started
+    if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&chain->ticket, 1u);
+    __syncthreads();
+    const int64_t tile = s_tile;
+    if (SELECT && tile == tiles - 1) {
+        last_tile(c, f, B, chain, tile, victims);
+        return;
+    }
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile);
+    if (!SELECT && tile == tiles - 1) {
+        const int32_t m = entries_to_replace(f, n_unique, chain);
+        if (threadIdx.x == 0) fifo_advance(c.capacity, c.ring, f.ctl, m);
+    }
+}
 
 // one wave per replaced entry: maps, score, row copy from the backing store
 __device__ __forceinline__ void insert_body(const CacheState& c, int policy, int32_t dim, const float* __restrict__ store,
@@ -546,13 +759,13 @@ __device__ __forceinline__ void insert_body(const CacheState& c, int policy, int
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t i = bid * 4 + (threadIdx.x >> 6);
     if (i >= ctl->m) return;
-    const int32_t s = victims[i], id = new_ids[i];
+    const int32_t s = policy == TNS_CACHE_FIFO ? fifo_slot(ctl->ring, i, c.capacity) : victims[i], id = new_ids[i];
     if (lane == 0) {
         const int32_t old = c.id_of[s];
         if (old >= 0) c.slot_of[old] = -1;
         c.id_of[s] = id;
         c.slot_of[id] = s;
-        c.score[s] = policy == TNS_CACHE_LFU ? 1 : 0;
+        c.score[s] = policy == TNS_CACHE_LFU ? 1 : ctl->now;
         if (i == 0) atomicAdd(&c.counters[2], (unsigned long long)ctl->m);
     }
     const float* __restrict__ src = store + (int64_t)id * dim;
@@ -570,6 +783,7 @@ __global__ void __launch_bounds__(256) k_insert_clear(CacheState c, int policy, 
         insert_body(c, policy, dim, store, new_ids, victims, ctl, blockIdx.x);
     } else {
         const int64_t b = ((int64_t)blockIdx.x - insert_blocks) * 256 + threadIdx.x;
+        if (b == 0) *c.updates = ctl->now;
         if (b < B && slots[b] == -1) c.first_idx[ids[b]] = kNoIndex;
     }
 }
@@ -608,6 +822,7 @@ struct Workspace {
     Ctl* ctl;
     int32_t *slots, *new_ids, *victims;
     int64_t* sums;
+    tns::ScanWorkspace* chain;
     size_t bytes;
 };
 Workspace carve(const tns_cache* c, int64_t B, void* base) {
@@ -621,6 +836,7 @@ Workspace carve(const tns_cache* c, int64_t B, void* base) {
     w.new_ids = reinterpret_cast<int32_t*>(take((size_t)std::max(c->max_replace, 1) * 4));
     w.victims = reinterpret_cast<int32_t*>(take((size_t)std::max(c->max_replace, 1) * 4));
     w.sums = reinterpret_cast<int64_t*>(take((size_t)(std::max(B, cap) / kScanTile + 2) * 8));
+    w.chain = reinterpret_cast<tns::ScanWorkspace*>(take(sizeof(tns::ScanWorkspace) + (size_t)(B / kScanTile + 1) * 8));
     w.bytes = off;
     return w;
 }
@@ -642,12 +858,13 @@ int tns_cache_create(const tns_cache_config* cfg, tns_cache** out) {
     tns_cache* c = new (std::nothrow) tns_cache();
     if (!c) return fail(TNS_ENOMEM, "host allocation failed");
     c->cfg = *cfg;
+    c->st.capacity = cfg->capacity;
     c->max_replace = (int32_t)std::floor(cfg->lambda * (float)cfg->capacity);
     const int64_t N = cfg->num_ids, C = cfg->capacity;
     struct Alloc { void** p; size_t bytes; };
     const Alloc allocs[] = {{(void**)&c->st.slot_of, (size_t)N * 4}, {(void**)&c->st.first_idx, (size_t)N * 4},
                             {(void**)&c->st.id_of, (size_t)C * 4},   {(void**)&c->st.score, (size_t)C * 4},
-                            {(void**)&c->st.touched, (size_t)C * 4}, {(void**)&c->st.rows, (size_t)C * cfg->dim * 4},
+                            {(void**)&c->st.updates, 4},             {(void**)&c->st.rows, (size_t)C * cfg->dim * 4},
                             {(void**)&c->st.counters, kStripes * 3 * 8},        {(void**)&c->st.ring, 8}};
     for (const Alloc& a : allocs) {
         const hipError_t e = tns::device_malloc(a.p, a.bytes);
@@ -667,7 +884,7 @@ int tns_cache_create(const tns_cache_config* cfg, tns_cache** out) {
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(N)), dim3(256), 0, nullptr, c->st.first_idx, N, kNoIndex);
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(C)), dim3(256), 0, nullptr, c->st.id_of, C, -1);
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(C)), dim3(256), 0, nullptr, c->st.score, C, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(C)), dim3(256), 0, nullptr, c->st.touched, C, 0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, nullptr, c->st.updates, 1, 0);
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(kStripes * 6)), dim3(256), 0, nullptr, reinterpret_cast<int32_t*>(c->st.counters), kStripes * 6, 0);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, nullptr, reinterpret_cast<int32_t*>(c->st.ring), 2, 0);
     hipError_t e = hipMemsetAsync(c->st.rows, 0, (size_t)C * cfg->dim * 4, nullptr);
@@ -708,74 +925,66 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
     const int64_t C = cache->cfg.capacity, N = cache->cfg.num_ids;
     const int32_t maxrep = cache->max_replace;
 
-    // Two chains that only meet at the insertion.  The caller's stream gathers the rows (bound by memory bandwidth;
-    // each row's threads look the slot up themselves).  The cache's own stream runs the lookup proper (hit flags,
-    // counters, recorded accesses, first occurrence of every missed id) and the update (scores, distinct misses,
-    // victims: many short kernels over the score vector).  Both only read the maps and rows; the insertion changes
-    // them and waits for both.
-    const bool select = maxrep > 0 && policy != TNS_CACHE_FIFO;
-    hipStream_t us = cache->side;
-    {
+    // The rows are gathered (bound by memory bandwidth; each row's threads look the slot up themselves) beside the update:
+    // lookup proper (hit flags, counters, recorded accesses, first occurrence of every missed id), distinct misses, scores,
+    // victims.  Both only read the maps and rows; the insertion changes them and waits for both.
+    const bool vec4 = dim % 4 == 0 && ((reinterpret_cast<uintptr_t>(store) | reinterpret_cast<uintptr_t>(d_out)) & 15) == 0;
+    const int64_t pieces = B * (dim / (vec4 ? 4 : 1));
+    // One launch for all but the lookup and the insertion, on the caller's stream; see kGatherWithin.
+    const bool one_launch = (policy == TNS_CACHE_FIFO || C <= kOneGroupEntries) && pieces <= kGatherWithin && B <= kOneLaunchIds;
+    const int64_t tiles_b = (B + kScanTile - 1) / kScanTile;
+    const NewIds nf{st.first_idx, d_ids, w.slots, maxrep, w.new_ids, w.ctl};
+    // Otherwise the caller's stream gathers and the update, a chain of launches, runs on a stream of the cache's own.
+    hipStream_t us = one_launch ? stream : cache->side;
+    if (!one_launch) {
         hipError_t ef = hipEventRecord(cache->forked, stream);
         if (ef == hipSuccess) ef = hipStreamWaitEvent(us, cache->forked, 0);
         if (ef != hipSuccess) return fail_hip(ef, "forking the cache update");
+        const dim3 grid(blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll));
+        auto gather = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, st.rows, store, dim, B, N, d_ids, st.slot_of, d_out); };
+        if (pieces >> 32) vec4 ? gather(k_gather<4, uint64_t>) : gather(k_gather<1, uint64_t>);
+        else vec4 ? gather(k_gather<4, uint32_t>) : gather(k_gather<1, uint32_t>);
     }
-    const bool vec4 = dim % 4 == 0 && ((reinterpret_cast<uintptr_t>(store) | reinterpret_cast<uintptr_t>(d_out)) & 15) == 0;
-    if (vec4)
-        hipLaunchKernelGGL(k_gather<4>, dim3(blocks_for((B * (dim / 4) + kGatherUnroll - 1) / kGatherUnroll)), dim3(256), 0, stream, st.rows, store, dim, B, N, d_ids,
-                           st.slot_of, d_out);
-    else
-        hipLaunchKernelGGL(k_gather<1>, dim3(blocks_for((B * dim + kGatherUnroll - 1) / kGatherUnroll)), dim3(256), 0, stream, st.rows, store, dim, B, N, d_ids,
-                           st.slot_of, d_out);
-
-    hipLaunchKernelGGL(k_lookup, dim3(blocks_for((B + kLookupUnroll - 1) / kLookupUnroll)), dim3(256), 0, us, st, policy, N, B, d_ids,
-                       w.slots, d_hit, w.ctl);
-    // LRU: every score is decremented and the accessed entries are reset; done on the way by the first
-    // pass of the victim selection when there is one
-    if (policy == TNS_CACHE_LRU && !select)
-        hipLaunchKernelGGL(k_lru_scores, dim3(blocks_for(C)), dim3(256), 0, us, st.score, st.touched, C);
-    if (maxrep > 0) {
-        const NewIds nf{st.first_idx, d_ids, w.slots, maxrep, w.new_ids, w.ctl};
+    hipLaunchKernelGGL(k_lookup, dim3((unsigned)tiles_b), dim3(256), 0, us, st, policy, N, B, d_ids, w.slots, d_hit, w.ctl,
+                       one_launch ? w.chain : nullptr);
+    if (one_launch) {
+        const int64_t gather_blocks = blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll, kOneGroup);
+        auto update = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_b + gather_blocks)), dim3(kOneGroup), 0, us, st, nf, B, tiles_b, w.chain, w.victims,
+                               store, dim, N, d_out);
+        };
+        if (policy == TNS_CACHE_FIFO) vec4 ? update(k_update<false, 4>) : update(k_update<false, 1>);
+        else vec4 ? update(k_update<true, 4>) : update(k_update<true, 1>);
+    } else if (maxrep > 0 && policy == TNS_CACHE_FIFO) {
+        compact_flagged(nf, B, w.sums, us);
+        hipLaunchKernelGGL(k_fifo_advance, dim3(1), dim3(1), 0, us, C, st.ring, w.ctl);
+    } else if (maxrep > 0) {
         // few workgroups for the histograms: they are added to one global one with atomics
         const unsigned hb = (unsigned)std::min<int64_t>(blocks_for(C), 256);
-        const int64_t tiles_b = (B + kScanTile - 1) / kScanTile;
-        const bool lru = policy == TNS_CACHE_LRU;
-        if (select && tiles_b <= kFoldTiles) {
+        if (tiles_b <= kFoldTiles) {
             // distinct missed ids: tile sums, then the collect kernel, which shares its launch with pass 0 of the selection
             hipLaunchKernelGGL((k_flag_tile_sums<NewIds>), dim3((unsigned)tiles_b), dim3(256), 0, us, nf, B, w.sums);
-            if (lru)
-                hipLaunchKernelGGL((k_newids_collect_hist0<true>), dim3((unsigned)tiles_b + hb), dim3(256), 0, us, nf, B, w.sums, tiles_b,
-                                   st.score, st.touched, C, w.ctl, (int64_t)hb);
-            else
-                hipLaunchKernelGGL((k_newids_collect_hist0<false>), dim3((unsigned)tiles_b + hb), dim3(256), 0, us, nf, B, w.sums, tiles_b,
-                                   st.score, st.touched, C, w.ctl, (int64_t)hb);
+            hipLaunchKernelGGL(k_newids_collect_hist0, dim3((unsigned)tiles_b + hb), dim3(256), 0, us, nf, B, w.sums, tiles_b, st.score, C, w.ctl,
+                               (int64_t)hb);
         } else {
             compact_flagged(nf, B, w.sums, us);
-            if (select) {
-                if (lru) hipLaunchKernelGGL(k_select_hist<true>, dim3(hb), dim3(256), 0, us, st.score, st.touched, C, 0, w.ctl);
-                else hipLaunchKernelGGL(k_select_hist<false>, dim3(hb), dim3(256), 0, us, st.score, st.touched, C, 0, w.ctl);
-            }
+            hipLaunchKernelGGL(k_select_hist, dim3(hb), dim3(256), 0, us, st.score, C, 0, w.ctl);
         }
-        if (policy == TNS_CACHE_FIFO) {
-            hipLaunchKernelGGL(k_fifo_victims, dim3(blocks_for(maxrep)), dim3(256), 0, us, C, maxrep, st.ring, w.ctl, w.victims);
-            hipLaunchKernelGGL(k_fifo_advance, dim3(1), dim3(1), 0, us, C, st.ring, w.ctl);
+        // the passes after the first: each picks the digit of the pass before it in its prologue
+        for (int pass = 1; pass < kPasses; ++pass)
+            hipLaunchKernelGGL(k_select_hist, dim3(hb), dim3(256), 0, us, st.score, C, pass, w.ctl);
+        // victims in slot order; the tile-sum kernel picks the last digit first
+        const Victims vf{st.score, w.ctl, w.victims};
+        const int64_t tiles_c = (C + kScanTile - 1) / kScanTile;
+        hipLaunchKernelGGL(k_victims_tile_sums, dim3((unsigned)tiles_c), dim3(256), 0, us, vf, w.ctl, C, w.sums);
+        if (tiles_c <= kFoldTiles) {
+            hipLaunchKernelGGL((k_flag_collect<Victims, true>), dim3((unsigned)tiles_c), dim3(256), 0, us, vf, C, w.sums);
         } else {
-            // the passes after the first: each picks the digit of the pass before it in its prologue
-            for (int pass = 1; pass < kPasses; ++pass)
-                hipLaunchKernelGGL(k_select_hist<false>, dim3(hb), dim3(256), 0, us, st.score, st.touched, C, pass, w.ctl);
-            // victims in slot order; the tile-sum kernel picks the last digit first
-            const Victims vf{st.score, w.ctl, w.victims};
-            const int64_t tiles_c = (C + kScanTile - 1) / kScanTile;
-            hipLaunchKernelGGL(k_victims_tile_sums, dim3((unsigned)std::max<int64_t>(tiles_c, 1)), dim3(256), 0, us, vf, w.ctl, C, w.sums);
-            if (tiles_c <= kFoldTiles) {
-                hipLaunchKernelGGL((k_flag_collect<Victims, true>), dim3((unsigned)std::max<int64_t>(tiles_c, 1)), dim3(256), 0, us, vf, C, w.sums);
-            } else {
-                hipLaunchKernelGGL((k_flag_scan_sums<Victims>), dim3(1), dim3(1024), 0, us, vf, w.sums, tiles_c);
-                hipLaunchKernelGGL((k_flag_collect<Victims, false>), dim3((unsigned)tiles_c), dim3(256), 0, us, vf, C, w.sums);
-            }
+            hipLaunchKernelGGL((k_flag_scan_sums<Victims>), dim3(1), dim3(1024), 0, us, vf, w.sums, tiles_c);
+            hipLaunchKernelGGL((k_flag_collect<Victims, false>), dim3((unsigned)tiles_c), dim3(256), 0, us, vf, C, w.sums);
         }
     }
-    {
+    if (!one_launch) {
         hipError_t ej = hipEventRecord(cache->joined, us);
         if (ej == hipSuccess) ej = hipStreamWaitEvent(stream, cache->joined, 0);
         if (ej != hipSuccess) return fail_hip(ej, "joining the cache update");
@@ -818,9 +1027,12 @@ int tns_cache_save(tns_cache* cache, void* hip_stream, int32_t* h_id_of, int32_t
     hipError_t e = hipMemcpyAsync(h_id_of, cache->st.id_of, (size_t)C * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(h_score, cache->st.score, (size_t)C * 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(h_rows, cache->st.rows, (size_t)C * cache->cfg.dim * 4, hipMemcpyDeviceToHost, s);
+    int32_t updates = 0;
+    if (e == hipSuccess) e = hipMemcpyAsync(&updates, cache->st.updates, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(h_ring, cache->st.ring, 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "saving the cache");
+    for (int64_t i = 0; i < C; ++i) h_score[i] = (int32_t)((uint32_t)h_score[i] - (uint32_t)updates);
     return TNS_OK;
 }
 
@@ -841,7 +1053,7 @@ int tns_cache_restore(tns_cache* cache, void* hip_stream, const int32_t* h_id_of
     if (e == hipSuccess) e = hipMemcpyAsync(cache->st.ring, &ring, 8, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return fail_hip(e, "restoring the cache");
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(N)), dim3(256), 0, s, cache->st.slot_of, N, -1);
-    hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(C)), dim3(256), 0, s, cache->st.touched, C, 0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, cache->st.updates, 1, 0);
     hipLaunchKernelGGL(k_rebuild_map, dim3(blocks_for(C)), dim3(256), 0, s, cache->st.id_of, C, N, cache->st.slot_of);
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "restoring the cache");
@@ -854,7 +1066,7 @@ int tns_cache_destroy(tns_cache* cache) {
     {
         DeviceGuard guard(cache->cfg.device);
         void* ptrs[] = {cache->st.slot_of, cache->st.first_idx, cache->st.id_of, cache->st.score,
-                        cache->st.touched, cache->st.rows,      cache->st.counters, cache->st.ring};
+                        cache->st.updates, cache->st.rows,      cache->st.counters, cache->st.ring};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
         if (cache->forked) (void)hipEventDestroy(cache->forked);

@@ -149,3 +149,30 @@ def test_fetch_replayed_from_a_hip_graph(KB):
                 assert np.array_equal(st["score"], ref.score), (policy, rep)
         del graph
         gpu.close()
+
+
+@pytest.mark.parametrize("policy", [CO.LRU, CO.LFU])
+@pytest.mark.parametrize("cap", [1, 255, 4097, 40_001, 65_535, 65_536, 65_537])
+def test_victims_among_scores_of_any_size(KB, policy, cap):
+    # one workgroup holds the scores of up to 65536 entries and searches for the threshold: capacities around its chunks
+    # and its end, scores close together, spread over 32 bits and at their extremes, replacement of one entry up to all
+    import torch
+    dev = torch.device("cuda", 0)
+    rng = np.random.default_rng(900 + cap)
+    n, dim = 2 * cap + 10, 3
+    store = rng.standard_normal((n, dim)).astype(np.float32)
+    d_store = torch.from_numpy(store).to(dev)
+    spreads = [(-6, 0), (0, 2 ** 20), (-(2 ** 31) + 8, 2 ** 31 - 8), (2 ** 31 - 12, 2 ** 31 - 8), (5, 6)]
+    for lam in (0.2, 1.0):
+        ref, gpu = CO.VectorCache(n, cap, dim, policy, lam), KB.Cache(n, cap, dim, policy, lam)
+        for it, (lo, hi) in enumerate(spreads):
+            ref.score[:] = rng.integers(lo, hi, cap)
+            gpu.restore(dict(id_of=ref.id_of, score=ref.score, rows=ref.data, ring=0))
+            for b in (1, 1500, 1024, min(2 * cap, 90_000) + 1):
+                ids = rng.integers(0, n, b).astype(np.int32)
+                out, hit = gpu.fetch(torch.from_numpy(ids).to(dev), d_store)
+                r_out, r_hit = ref.fetch(ids, store)
+                assert np.array_equal(out.cpu().numpy(), r_out) and np.array_equal(hit.cpu().numpy().astype(bool), r_hit), (lam, it, b)
+                st = gpu.save()
+                assert np.array_equal(st["id_of"], ref.id_of) and np.array_equal(st["score"], ref.score), (lam, it, b)
+        gpu.close()
