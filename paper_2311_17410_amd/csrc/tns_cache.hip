@@ -173,6 +173,7 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
 // pieces, one grid width apart, and runs each dependent step (id, slot, row, store) for all of them before the next:
 // the kernel is a copy, and a copy on this machine is bound by how much each compute unit has in flight.
 constexpr int kGatherUnroll = 8;
+// idx_t: a type that holds the number of pieces
 template <int VEC, int THREADS, typename idx_t>
 __device__ __forceinline__ void gather_body(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                             int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
@@ -211,12 +212,11 @@ __device__ __forceinline__ void gather_body(const float* __restrict__ rows, cons
         if (t0 + (int64_t)u * stride < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out + b[u] * dim + col[u]));
 }
 
-// idx_t: an unsigned type that holds the number of pieces
-template <int VEC, typename idx_t>
+template <int VEC>
 __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                                 int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
                                                 const int32_t* __restrict__ slot_of, float* __restrict__ out) {
-    gather_body<VEC, 256, idx_t>(rows, store, dim, B, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
+    gather_body<VEC, 256, int64_t>(rows, store, dim, B, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
 }
 
 // ---- compaction of flagged elements in three launches -------------------------------------------
@@ -942,8 +942,7 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
         if (ef != hipSuccess) return fail_hip(ef, "forking the cache update");
         const dim3 grid(blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll));
         auto gather = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, st.rows, store, dim, B, N, d_ids, st.slot_of, d_out); };
-        if (pieces >> 32) vec4 ? gather(k_gather<4, uint64_t>) : gather(k_gather<1, uint64_t>);
-        else vec4 ? gather(k_gather<4, uint32_t>) : gather(k_gather<1, uint32_t>);
+        vec4 ? gather(k_gather<4>) : gather(k_gather<1>);
     }
     hipLaunchKernelGGL(k_lookup, dim3((unsigned)tiles_b), dim3(256), 0, us, st, policy, N, B, d_ids, w.slots, d_hit, w.ctl,
                        one_launch ? w.chain : nullptr);
