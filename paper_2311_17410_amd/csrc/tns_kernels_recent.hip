@@ -69,7 +69,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     // behind them the search requests and their results, whose place the slot heads take
     unsigned char* const my_lds = smem + (size_t)wave * chunk;
     pos_t* const rows = reinterpret_cast<pos_t*>(my_lds);
-    uint4* const requests = reinterpret_cast<uint4*>(my_lds + (size_t)kWave * stride * sizeof(pos_t));
+    SearchRequest* const requests = reinterpret_cast<SearchRequest*>(my_lds + (size_t)kWave * stride * sizeof(pos_t));
     SlotHead* const heads = reinterpret_cast<SlotHead*>(requests);
     unsigned char* const found = reinterpret_cast<unsigned char*>(requests + 2 * kWave);
 
@@ -176,39 +176,29 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         narrow2(b_lo, b_n, kCoopGroup, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
     }
     // ---- search ------------------------------------------------------------------------------------------
-    // A request: the edge line and the position in it where at most 16 slots start, their number, the time; sixteen lanes
-    // read the timestamps of one request side by side and a ballot counts those before the time.
+    // Sixteen lanes read the timestamps of one request side by side and a ballot counts those before its time.
     const uint64_t ask_end = __ballot(w.d_n > 0), ask_start = __ballot(b_n > 0);
     const int num_end = __popcll(ask_end), num_requests = num_end + __popcll(ask_start);
     const uint64_t below = (1ull << lane) - 1ull;
     const int my_end = __popcll(ask_end & below), my_start = num_end + __popcll(ask_start & below);
     if (num_requests > 0) {
-        auto request = [&](int r, int64_t slot0, int32_t n, float t, uint32_t closed) {
-            const uint64_t line = sizeof(pos_t) == 8 ? (uint64_t)slot0 / (uint32_t)kSlotsPerLine : (uint32_t)slot0 / (uint32_t)kSlotsPerLine;
-            const uint32_t at = (uint32_t)slot0 - (uint32_t)line * (uint32_t)kSlotsPerLine;
-            requests[r] = make_uint4((uint32_t)line, __float_as_uint(t), at | (uint32_t)n << 8 | closed << 16, 0u);
-        };
-        if (w.d_n > 0) request(my_end, w.d_off + w.d_lo, w.d_n, w.te, INCL ? 1u : 0u);
-        if (b_n > 0) request(my_start, b_off + b_lo, b_n, w.tb, 0u);
+        if (w.d_n > 0) requests[my_end] = make_request<pos_t>(w.d_off + w.d_lo, w.d_n, w.te, INCL);
+        if (b_n > 0) requests[my_start] = make_request<pos_t>(b_off + b_lo, b_n, w.tb, false);
         wave_lds_sync();
         const int g = lane / kCoopGroup, j = lane % kCoopGroup;
 #pragma unroll 1
         for (int r0 = 0; r0 < num_requests; r0 += kRequestBatch * kGroups) {
-            uint32_t par[kRequestBatch];
-            float at[kRequestBatch], t[kRequestBatch];
+            SearchRequest d[kRequestBatch];
+            float t[kRequestBatch];
 #pragma unroll
             for (int i = 0; i < kRequestBatch; ++i) {
                 // (beyond the last request: the last one again, its lines are on their way anyway)
-                const uint4 d = requests[min(r0 + i * kGroups + g, num_requests - 1)];
-                par[i] = d.z;
-                at[i] = __uint_as_float(d.y);
-                const uint32_t s = (d.z & 0xffu) + (uint32_t)min(j, (int)((d.z >> 8) & 0xffu) - 1);     // below 25
-                const uint32_t lines = (s * 205u) >> 11;                                                 // s / kSlotsPerLine
-                t[i] = __uint_as_float(p.edges[(uint64_t)d.x * 32u + (3u * s + 2u * lines)]);
+                d[i] = requests[min(r0 + i * kGroups + g, num_requests - 1)];
+                t[i] = __uint_as_float(p.edges[request_word<pos_t>(d[i], j)]);
             }
 #pragma unroll
             for (int i = 0; i < kRequestBatch; ++i) {
-                const bool first = j < (int)((par[i] >> 8) & 0xffu) && (t[i] < at[i] || (INCL && (par[i] >> 16) && t[i] == at[i]));
+                const bool first = j < request_slots(d[i]) && (t[i] < d[i].t || (INCL && request_closed(d[i]) && t[i] == d[i].t));
                 const uint32_t c = (uint32_t)__popc((uint32_t)(__ballot(first) >> (g * kCoopGroup)) & 0xffffu);
                 found[min(r0 + i * kGroups + g, num_requests - 1)] = (unsigned char)c;
             }
@@ -320,7 +310,7 @@ template <bool INCL, typename pos_t, bool FUSED>
 hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     const int32_t stride = std::max(a.fanout, kInlineBlocks) | 1;                // odd: conflict-free per-lane rows
     // per wave: the table, the requests and their results; at least the 4 KiB in which the node lines are staged first
-    const size_t chunk = std::max<size_t>((((size_t)kWave * stride * sizeof(pos_t) + 15) & ~size_t(15)) + 2 * kWave * (sizeof(uint4) + 1), 4096);
+    const size_t chunk = std::max<size_t>((((size_t)kWave * stride * sizeof(pos_t) + 15) & ~size_t(15)) + 2 * kWave * (sizeof(SearchRequest) + 1), 4096);
     // The fused variant uses large workgroups: one chained-scan step per 1024 queries keeps the rate at which tiles publish
     // their totals low enough for the look-back to keep up.
     int waves = FUSED ? 16 : 4;

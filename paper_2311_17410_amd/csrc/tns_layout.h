@@ -91,6 +91,34 @@ TNS_HD int64_t slot_word(int64_t s) {
     return line * 32 + (s - line * kSlotsPerLine) * 3;
 }
 
+// Search request of the sampling kernel for the recent policy: up to sixteen consecutive slots whose timestamps are
+// compared with one time by as many lanes.
+struct alignas(16) SearchRequest {
+    uint32_t line;      // edge line of the first slot, low 32 bits
+    float t;            // the time searched for
+    uint32_t range;     // bits 0-7: position of the first slot in its line; bits 8-15: number of slots; bit 16: slots at the time
+                        // count too; bits 17-31: upper bits of the line (2^39 slots are more than 2^32 lines)
+    uint32_t unused;
+};
+// pos_t (32 or 64 bits): a type that holds every word index of the edge array
+template <typename pos_t>
+TNS_HD SearchRequest make_request(int64_t slot0, int32_t n, float t, bool closed) {
+    const uint64_t line = sizeof(pos_t) == 8 ? (uint64_t)slot0 / (uint32_t)kSlotsPerLine : (uint32_t)slot0 / (uint32_t)kSlotsPerLine;
+    const uint32_t at = (uint32_t)slot0 - (uint32_t)line * (uint32_t)kSlotsPerLine;
+    return SearchRequest{(uint32_t)line, t, at | (uint32_t)n << 8 | (closed ? 1u << 16 : 0u) | (uint32_t)(line >> 32) << 17, 0u};
+}
+TNS_HD int32_t request_slots(const SearchRequest& r) { return (int32_t)((r.range >> 8) & 0xffu); }
+TNS_HD bool request_closed(const SearchRequest& r) { return ((r.range >> 16) & 1u) != 0; }
+// word index of the timestamp in slot j of a request (of the last one for a j beyond it)
+template <typename pos_t>
+TNS_HD uint64_t request_word(const SearchRequest& r, int32_t j) {
+    const int32_t last = request_slots(r) - 1;
+    const uint32_t s = (r.range & 0xffu) + (uint32_t)(j < last ? j : last);      // below 25
+    const uint32_t lines = (s * 205u) >> 11;                                     // s / kSlotsPerLine
+    const uint64_t line = sizeof(pos_t) == 8 ? (uint64_t)(r.range >> 17) << 32 | r.line : r.line;
+    return line * 32u + (3u * s + 2u * lines);
+}
+
 // ---- prefix layout (TNS_FLAG_PREFIX_LAYOUT) ------------------------------------------------------
 //
 // A second placement of the same logical structure (node table, chronological block lists, block
