@@ -859,7 +859,8 @@ int tns_cache_create(const tns_cache_config* cfg, tns_cache** out) {
     if (!c) return fail(TNS_ENOMEM, "host allocation failed");
     c->cfg = *cfg;
     c->st.capacity = cfg->capacity;
-    c->max_replace = (int32_t)std::floor(cfg->lambda * (float)cfg->capacity);
+    // (from 2^24 on a capacity may round up on its way to 32 bits; the victims are distinct entries)
+    c->max_replace = (int32_t)std::min(std::floor((double)(cfg->lambda * (float)cfg->capacity)), (double)cfg->capacity);
     const int64_t N = cfg->num_ids, C = cfg->capacity;
     struct Alloc { void** p; size_t bytes; };
     const Alloc allocs[] = {{(void**)&c->st.slot_of, (size_t)N * 4}, {(void**)&c->st.first_idx, (size_t)N * 4},

@@ -8,12 +8,14 @@
 
 static size_t used, limit = (size_t)1 << 40;
 static int allocations, launches;
+static uint64_t grid_xy;                        /* of the latest launch */
 struct head { size_t bytes, pad[31]; };
 
 void fake_set_limit(size_t bytes) { limit = bytes; }
 size_t fake_used(void) { return used; }
 int fake_allocations(void) { return allocations; }
 int fake_launches(void) { return launches; }
+unsigned fake_grid(void) { return (unsigned)grid_xy; }
 
 int hipMalloc(void **p, size_t n) {
     struct head *h;
@@ -42,7 +44,8 @@ int hipLaunchKernel(const void *f, uint64_t gxy, uint32_t gz, uint64_t bxy, uint
     return 0;
 }
 int __hipPushCallConfiguration(uint64_t gxy, uint32_t gz, uint64_t bxy, uint32_t bz, size_t lds, void *stream) {
-    (void)gxy; (void)gz; (void)bxy; (void)bz; (void)lds; (void)stream;
+    (void)gz; (void)bxy; (void)bz; (void)lds; (void)stream;
+    grid_xy = gxy;
     return 0;
 }
 int __hipPopCallConfiguration(void *grid, void *block, size_t *lds, void **stream) {

@@ -88,3 +88,15 @@ for status, text in ((B.TNS_EHIP, "did not reach the host"), (B.TNS_ESTATE, "cre
         assert e.status == status and text in str(e), str(e)
 assert p.stats()["num_edges"] == 0
 """)
+
+
+@pytest.mark.parametrize("capacity", [7, 40_000, (1 << 26) + 12])
+def test_no_more_entries_are_replaced_than_the_cache_has(run, capacity):
+    # lambda 1 and a capacity that rounds up to 2^26 + 16 in 32 bits: the insertion, which ends a fetch, has a wave per entry
+    # that may be replaced, four a workgroup, and a workgroup for the batch
+    run(f"""
+c = KB.tns_cache_create(1000, {capacity}, 1, KB.TNS_CACHE_FIFO, 1.0)
+KB.tns_cache_fetch(c, 100, 256, 256, 256, 0, 256, KB.tns_cache_workspace(c, 100))      # (the kernels do nothing)
+assert fake.fake_grid() == ({capacity} + 3) // 4 + 1, fake.fake_grid()
+KB.tns_cache_destroy(c)
+""")
