@@ -14,6 +14,7 @@
 #include "../../include/tns_cache.h"
 #include "tns_chain.h"
 #include "tns_internal.h"
+#include "tns_test_hooks.h"
 
 using tns::DeviceGuard;
 using tns::fail;
@@ -91,7 +92,8 @@ constexpr int kLookupTable = 2 * 256 * kLookupUnroll;      // power of two
 constexpr int32_t kFreeKey = INT_MIN;                      // hits: slot >= 0; misses: -1 - id > INT_MIN
 __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, int64_t num_ids, int64_t B,
                                                 const int32_t* __restrict__ ids, int32_t* __restrict__ slots,
-                                                uint8_t* __restrict__ hit, Ctl* ctl, tns::ScanWorkspace* chain) {
+                                                uint8_t* __restrict__ hit, Ctl* ctl, tns::ScanWorkspace* chain,
+                                                uint32_t first_ticket) {
     __shared__ int32_t s_key[kLookupTable], s_val[kLookupTable];
     __shared__ int32_t s_hits, s_misses;
     const int32_t now = policy == TNS_CACHE_LRU ? (int32_t)((uint32_t)*c.updates + 1u) : 0;
@@ -100,7 +102,7 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
         int4* const all = reinterpret_cast<int4*>(&ctl->hist[0][0]);
 #pragma unroll
         for (int i = 0; i < kPasses * kBins / 4 / 256; ++i) all[i * 256 + threadIdx.x] = make_int4(0, 0, 0, 0);
-        if (chain && threadIdx.x == 1) { chain->ticket = 0; chain->error = 0; }
+        if (chain && threadIdx.x == 1) chain->ticket = first_ticket;
     }
     if (chain && threadIdx.x == 0) chain->status[blockIdx.x] = 0;      // a workgroup here and a tile of the chain are both 1024 ids
     const int64_t stride = (int64_t)gridDim.x * 256;
@@ -540,6 +542,7 @@ constexpr int kItems = 64, kItemStep = 8;                         // scores per 
 // 169 / 194 / 162; rows of 173 floats, LRU, 66600 (12 M pieces of 4 bytes) 47 and 71, 262144 (45 M) 151 and 119; 2^20 rows of
 // 32 floats (8 M) 96 and 113.
 constexpr int64_t kGatherWithin = int64_t(1) << 24, kOneLaunchIds = int64_t(1) << 20;
+constexpr uint32_t kNoWait = 1u << 31;                            // bit of the tickets of tiles that do not wait for one another (tests)
 constexpr int64_t kOneGroupEntries = (int64_t)kOneGroup * kItems;
 
 // set bits of `mask` below this lane
@@ -578,8 +581,10 @@ __device__ __forceinline__ int32_t count_below(const uint32_t (&key)[kItems], in
 }
 
 // Distinct missed ids of tile `tile` in the order of their first occurrence, behind those of the tiles before it.
-// Returns their number up to and including this tile.
-__device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile) {
+// Returns their number up to and including this tile.  What a tile learns from the chained scan it could count by itself, and
+// does so if the tiles before it have not reported within the bound of its wait (or `wait` is false, in tests): every update
+// is made, however late a tile is.
+__device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile, bool wait) {
     __shared__ int32_t s_w[kOneGroupWaves];
     __shared__ int64_t s_excl;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -594,30 +599,40 @@ __device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, t
         before += w < wave ? n : 0;
         total += n;
     }
+    auto publish = [&](int64_t before_tile) {
+        __hip_atomic_store(&chain->status[tile], tns::kStPrefix | (uint64_t)(before_tile + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (wave == 0) {
         if (lane == 0 && tile > 0)
             __hip_atomic_store(&chain->status[tile], tns::kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t excl = tile > 0 ? tns::lookback_exclusive(chain, &chain->error, tile, lane) : 0;
+        int64_t excl = 0;
+        if (tile > 0 && !(wait && tns::lookback(chain, tile, lane, excl))) excl = -1;
         if (lane == 0) {
-            __hip_atomic_store(&chain->status[tile], tns::kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_excl = excl;
+            if (excl >= 0) publish(excl);
         }
     }
     __syncthreads();
-    const int64_t excl = s_excl;
+    int64_t excl = s_excl;
+    if (excl < 0) {                            // uniform
+        int32_t n = 0;
+        for (int64_t i = threadIdx.x; i < tile * kOneGroup; i += kOneGroup) n += (int32_t)f.count(i);
+        for (int d = kWave / 2; d >= 1; d >>= 1) n += __shfl_xor(n, d, kWave);
+        if (lane == 0) s_w[wave] = n;
+        __syncthreads();
+        excl = 0;
+        for (int w = 0; w < kOneGroupWaves; ++w) excl += s_w[w];
+        if (threadIdx.x == 0) publish(excl);
+    }
     if ((first >> lane) & 1) f.emit(b, excl + before + lanes_before(first));
     return excl + total;
 }
 
-// Entries to replace once the last tile knows the number of distinct missed ids.  If a wait of the chained scan ever ran
-// into its bound that number is not to be trusted, and nothing is replaced.
-__device__ __forceinline__ int32_t entries_to_replace(const NewIds& f, int64_t n_unique, tns::ScanWorkspace* chain) {
+// Entries to replace, once the last tile knows the number of distinct missed ids.
+__device__ __forceinline__ int32_t entries_to_replace(const NewIds& f, int64_t n_unique) {
     __shared__ int32_t s_m;
     if (threadIdx.x == 0) {
-        // (whoever reports an error does so before it publishes what the look-back has read)
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const bool bad = __hip_atomic_load(&chain->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-        f.total(bad ? 0 : n_unique);
+        f.total(n_unique);
         s_m = f.ctl->m;
     }
     __syncthreads();
@@ -625,7 +640,7 @@ __device__ __forceinline__ int32_t entries_to_replace(const NewIds& f, int64_t n
 }
 
 __device__ __forceinline__ void last_tile(const CacheState& c, const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile,
-                                          int32_t* __restrict__ victims) {
+                                          int32_t* __restrict__ victims, bool wait) {
     __shared__ int32_t s_cnt[2][kOneGroupWaves];
     __shared__ uint32_t s_min[kOneGroupWaves];
     __shared__ int32_t s_below[kOneGroupWaves], s_equal[kOneGroupWaves];
@@ -648,8 +663,8 @@ __device__ __forceinline__ void last_tile(const CacheState& c, const NewIds& f, 
 #pragma unroll
         for (int i = i0; i < i0 + kItemStep; ++i) key[i] = base + i * kWave < C ? score_key((int32_t)key[i], now) : ~0u;
     }
-    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile);
-    const int32_t m = __builtin_amdgcn_readfirstlane(entries_to_replace(f, n_unique, chain));
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait);
+    const int32_t m = __builtin_amdgcn_readfirstlane(entries_to_replace(f, n_unique));
     if (m <= 0) return;
     uint32_t lowest = ~0u;
 #pragma unroll
@@ -731,23 +746,24 @@ template <bool SELECT, int GATHER>
 __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const NewIds f, int64_t B, int64_t tiles, tns::ScanWorkspace* chain,
                                                       int32_t* __restrict__ victims, const float* __restrict__ store, int32_t dim,
                                                       int64_t num_ids, float* __restrict__ out) {
-    __shared__ int64_t s_tile;
+    __shared__ uint32_t s_ticket;
     if ((int64_t)blockIdx.x >= tiles) {
         gather_body<GATHER, kOneGroup, uint32_t>(c.rows, store, dim, B, num_ids, f.ids, c.slot_of, out, (int64_t)blockIdx.x - tiles,
                                                  (int64_t)gridDim.x - tiles);
         return;
     }
     // tiles are numbered in the order workgroups start, so that a tile only waits for tiles that have started
-    if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&chain->ticket, 1u);
+    if (threadIdx.x == 0) s_ticket = atomicAdd(&chain->ticket, 1u);
     __syncthreads();
-    const int64_t tile = s_tile;
+    const int64_t tile = s_ticket & ~kNoWait;
+    const bool wait = !(s_ticket & kNoWait);
     if (SELECT && tile == tiles - 1) {
-        last_tile(c, f, B, chain, tile, victims);
+        last_tile(c, f, B, chain, tile, victims, wait);
         return;
     }
-    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile);
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait);
     if (!SELECT && tile == tiles - 1) {
-        const int32_t m = entries_to_replace(f, n_unique, chain);
+        const int32_t m = entries_to_replace(f, n_unique);
         if (threadIdx.x == 0) fifo_advance(c.capacity, c.ring, f.ctl, m);
     }
 }
@@ -815,6 +831,7 @@ struct tns_cache {
     // forked from and joined back into the caller's stream with these events
     hipStream_t side = nullptr;
     hipEvent_t forked = nullptr, joined = nullptr;
+    uint32_t first_ticket = 0;       // of the tiles of an update
 };
 
 namespace {
@@ -946,7 +963,7 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
         vec4 ? gather(k_gather<4>) : gather(k_gather<1>);
     }
     hipLaunchKernelGGL(k_lookup, dim3((unsigned)tiles_b), dim3(256), 0, us, st, policy, N, B, d_ids, w.slots, d_hit, w.ctl,
-                       one_launch ? w.chain : nullptr);
+                       one_launch ? w.chain : nullptr, cache->first_ticket);
     if (one_launch) {
         const int64_t gather_blocks = blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll, kOneGroup);
         auto update = [&](auto kernel) {
@@ -1059,6 +1076,8 @@ int tns_cache_restore(tns_cache* cache, void* hip_stream, const int32_t* h_id_of
     if (e != hipSuccess) return fail_hip(e, "restoring the cache");
     return TNS_OK;
 }
+
+TNS_API void tns_test_cache_no_wait(tns_cache* cache) { cache->first_ticket = kNoWait; }
 
 int tns_cache_destroy(tns_cache* cache) {
     tns::clear_error();

@@ -16,7 +16,7 @@ constexpr int kChainWave = 64;
 // Workspace layout: word 0 = tile ticket, word 1 = error flag, then one 64-bit status per tile:
 // bits 62-63 = state (0 not ready, 1 tile total, 2 inclusive prefix), bits 0-61 = value.
 // Tiles take their index from the ticket, so a tile only ever waits for tiles that have
-// already started; the wait is bounded and sets the error flag if the bound is ever hit.
+// already started; the wait is bounded (lookback_exclusive sets the error flag if the bound is ever hit).
 constexpr uint64_t kStTotal = 1ull << 62, kStPrefix = 2ull << 62, kStMask = 3ull << 62;
 constexpr int kSpinLimit = 1 << 22;
 
@@ -33,9 +33,10 @@ __device__ __forceinline__ int64_t shfl64(int64_t v, int src) {
     return ((int64_t)hi << 32) | (uint32_t)lo;
 }
 
-// Sum of the totals of all tiles before `tile` (called by one whole wave).
-__device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_t* err_flag, int64_t tile, int lane) {
-    int64_t excl = 0;
+// Sum of the totals of all tiles before `tile` (called by one whole wave).  False if a tile had not reported after
+// kSpinLimit polls: `excl` is then too small.
+__device__ __forceinline__ bool lookback(ScanWorkspace* ws, int64_t tile, int lane, int64_t& excl) {
+    excl = 0;
     int64_t idx = tile - 1;
     int spins = 0;
     bool fresh = true;              // new window: every lane reads its tile's state
@@ -54,23 +55,28 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
         const int first = is_prefix ? __builtin_ctzll(is_prefix) : kChainWave;             // nearest tile with a full prefix
         const uint64_t needed = first >= kChainWave - 1 ? ~0ull : ((2ull << first) - 1);    // lanes 0..first
         if (not_ready & needed) {
-            if (++spins > kSpinLimit) {
-                // reported before this tile publishes anything, so that whoever builds on its (wrong)
-                // prefix can see the flag
-                if (lane == 0) atomicExch(err_flag, 1u);
-                __threadfence();
-                return excl;
-            }
+            if (++spins > kSpinLimit) return false;
             __builtin_amdgcn_s_sleep(16);      // ~0.4 us between polls: late tiles are late by microseconds
             continue;
         }
         int64_t v = (lane <= first) ? (int64_t)(st & ~kStMask) : 0;
         for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kChainWave);
         excl += v;
-        if (first < kChainWave) return excl;
+        if (first < kChainWave) return true;
         idx -= kChainWave;
         fresh = true;
     }
+}
+
+// The same for a scan that cannot do without the tiles before this one: a wait that runs out is reported in *err_flag,
+// before this tile publishes anything, so that whoever builds on its (wrong) prefix can see the flag.
+__device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_t* err_flag, int64_t tile, int lane) {
+    int64_t excl;
+    if (!lookback(ws, tile, lane, excl)) {
+        if (lane == 0) atomicExch(err_flag, 1u);
+        __threadfence();
+    }
+    return excl;
 }
 
 }  // namespace

@@ -1,7 +1,13 @@
-// Hooks for the library's own tests: accepted in tns_config.flags but not part of the public header.
+// Hooks for the library's own tests, not part of the public headers.
 #pragma once
 
-// Test of the fused kernel's bounded wait: the tile tickets start at 1, so the first tile's predecessor
+#include "../../include/tns_cache.h"
+
+// Test of what a cache update does when the tiles of its chained scan do not hear from one another: no tile of this
+// cache's updates waits for those before it, as after a bounded wait that ran out.
+extern "C" TNS_API void tns_test_cache_no_wait(tns_cache* cache);
+
+// Accepted in tns_config.flags.  Test of the fused kernel's bounded wait: the tile tickets start at 1, so the first tile's predecessor
 // never reports.  Every kernel still ends (after the bound, about two seconds); tns_run_status then
 // reports the time-out and the dense outputs are not valid.
 #define TNS_TEST_FLAG_LOST_TILE 64

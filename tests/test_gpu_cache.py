@@ -17,13 +17,15 @@ def KB():
     return cache_binding
 
 
-def run_sequence(KB, policy, n, cap, dim, lam, batches, seed, check_state_every=1):
+def run_sequence(KB, policy, n, cap, dim, lam, batches, seed, check_state_every=1, prepare=None):
     import torch
     dev = torch.device("cuda", 0)
     store = np.random.default_rng(seed).standard_normal((n, dim)).astype(np.float32)
     d_store = torch.from_numpy(store).to(dev)
     ref = CO.VectorCache(n, cap, dim, policy, lam)
     gpu = KB.Cache(n, cap, dim, policy, lam)
+    if prepare:
+        prepare(gpu)
     for it, ids in enumerate(batches):
         ids = np.asarray(ids, np.int32)
         out, hit = gpu.fetch(torch.from_numpy(ids).to(dev), d_store)
@@ -176,3 +178,17 @@ def test_victims_among_scores_of_any_size(KB, policy, cap):
                 st = gpu.save()
                 assert np.array_equal(st["id_of"], ref.id_of) and np.array_equal(st["score"], ref.score), (lam, it, b)
         gpu.close()
+
+
+@pytest.mark.parametrize("policy", [CO.LRU, CO.LFU, CO.FIFO])
+def test_tiles_that_do_not_hear_from_one_another(KB, policy):
+    # the update of a batch numbers its missed ids with a chained scan over tiles of 1024 ids; no tile of this cache waits for
+    # the others, as after a wait that ran into its bound: the update must be made all the same
+    import ctypes
+    no_wait = KB.lib().tns_test_cache_no_wait
+    no_wait.argtypes, no_wait.restype = [ctypes.c_void_p], None
+    rng = np.random.default_rng(60 + policy)
+    n, cap = 50_000, 9_000
+    sizes = (1, 1024, 1025, 2048, 5000, 70_001)
+    gpu, *_ = run_sequence(KB, policy, n, cap, 5, 0.5, [rng.integers(0, n, b) for b in sizes], 9, prepare=lambda c: no_wait(c._h))
+    gpu.close()
