@@ -137,6 +137,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     int32_t cnt[kInlineBlocks];        // candidates
     pos_t end_slot[kInlineBlocks];     // slot behind the newest one
     int32_t end_block = -1, start_block = -1, b_lo = 0, b_n = 0;
+    int32_t newer = 0, whole = 0;      // edges of the blocks newer than the one with the start that count as a whole
     int64_t b_off = 0;
 #pragma unroll
     for (int j = 0; j < kInlineBlocks; ++j) {
@@ -146,8 +147,15 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         cnt[j] = in ? size : 0;
         end_slot[j] = (pos_t)(rec_off(r) + size);
         if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_lo = 1; w.d_n = size - 2; end_block = j; }
-        if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; }
+        if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; newer = whole; }
+        whole += in && before_end(r.t_max) ? size : 0;
     }
+    // Where the newer blocks fill the slots, the one with the start is not searched; the walk of Algorithm 1 does not come to it
+    // either.  (2^20 queries over power-law ids, window of a quarter of the time span, fan-out 20, padded rows only: edge data on the
+    // host 2.51 -> 1.77 ms, in HBM 153 -> 139 us.)
+    auto start_matters = [&]() {
+        if (newer + (end_block != start_block ? w.d_lo : 0) >= f) b_n = 0;
+    };
     if (!flat) {
         // ---- long lists, nodes with deleted edges: Algorithm 1 block by block --------------------------
         if (nb <= kInlineBlocks) {
@@ -169,10 +177,12 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         }
     } else if (FUSED) {
         narrow4(w.d_lo, w.d_n, kCoopGroup, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+        start_matters();
         narrow4(b_lo, b_n, kCoopGroup, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
     } else {
         // (without the scan one read at a time: of three in flight two are more traffic, 32.0 -> 31.5 ms across the host link)
         narrow2(w.d_lo, w.d_n, kCoopGroup, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
+        start_matters();
         narrow2(b_lo, b_n, kCoopGroup, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
     }
     // ---- search ------------------------------------------------------------------------------------------
@@ -313,8 +323,18 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     const size_t chunk = std::max<size_t>((((size_t)kWave * stride * sizeof(pos_t) + 15) & ~size_t(15)) + 2 * kWave * (sizeof(SearchRequest) + 1), 4096);
     // The fused variant uses large workgroups: one chained-scan step per 1024 queries keeps the rate at which tiles publish
     // their totals low enough for the look-back to keep up.
+    constexpr size_t kLds = 159u << 10;
     int waves = FUSED ? 16 : 4;
-    while (waves > 1 && (size_t)waves * chunk > (size_t)(159u << 10)) --waves;
+    while (waves > 1 && (size_t)waves * chunk > kLds) --waves;
+    if (!FUSED) {
+        // Larger fan-outs: smaller workgroups where a quarter more waves then fit a compute unit's LDS.  (2^20 queries, padded rows
+        // only, power-law ids, windowed: fan-out 32, 12 waves as 3 x 4 197 us, 15 as 5 x 3 189; fan-out 20, where 7 x 3 would be 21
+        // instead of 20, 139 and 147.)
+        const int four = waves;
+        auto resident = [&](int n) { return (int)(kLds / (n * chunk)) * n; };
+        for (int n = four - 1; n >= 1; --n)
+            if (resident(n) * 4 >= resident(four) * 5 && resident(n) > resident(waves)) waves = n;
+    }
     // small batches: smaller workgroups, so that the queries spread over the compute units instead of queueing at the
     // address units of a few
     while (waves > 1 && (a.Q + (int64_t)waves * kWave - 1) / ((int64_t)waves * kWave) < 512) waves >>= 1;

@@ -146,3 +146,35 @@ def test_windows_inside_blocks_of_every_size(B, oracle_lib, wide, fanout, incl):
         ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, 0, incl, 0, adjs=adjs)
         assert_same(gpu_sample(plan, targets, tb, t_end), ref, oracle_lib, f"start={tb is not None}")
     plan.close()
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("fanout", [1, 10, 20, 32, 33, 64])
+def test_padded_rows_only_where_the_window_start_may_not_matter(B, oracle_lib, wide, fanout):
+    # without the dense outputs; four to eight blocks of v + 1 edges per node v, queried at and around every time with windows of
+    # all lengths: the blocks before the one with the window's start hold fewer than, exactly and more than the fan-out.  The
+    # fan-outs give workgroups of four, three, two and one wave
+    nodes = 36
+    rng = np.random.default_rng(fanout)
+    src = np.concatenate([rng.permutation(np.repeat(np.arange(b % 2, nodes, 1 + b % 2, dtype=np.int32), np.arange(b % 2, nodes, 1 + b % 2) + 1))
+                          for b in range(8)])
+    sizes = [int((np.arange(b % 2, nodes, 1 + b % 2) + 1).sum()) for b in range(8)]
+    ts = np.sort(rng.integers(0, len(src) // 2, len(src))).astype(np.float32)
+    dst = rng.integers(0, nodes, len(src), dtype=np.int32)
+    st = W.Stream(nodes, src, dst, ts, len(src))
+    wl = W.Workload("starts", 0, [st], fanout=fanout, tau=1)
+    plan = B.Plan(nodes, fanout, block_threshold=1, flags=B.TNS_FLAG_WIDE_POSITIONS if wide else 0)
+    lo = 0
+    for m in sizes:
+        plan.add_edges(src[lo:lo + m], dst[lo:lo + m], ts[lo:lo + m])
+        lo += m
+    plan.commit()
+    Q = (1 << 17) + 65
+    targets = rng.integers(0, nodes, Q, dtype=np.int32)
+    t_end = ts[rng.integers(0, len(ts), Q)] + rng.integers(-1, 2, Q).astype(np.float32)
+    t_start = (t_end - rng.integers(0, len(src) // 2, Q)).astype(np.float32)
+    adjs = [oracle_lib.Adjacency(nodes, src, dst, ts)]
+    for tb in (t_start, None):
+        ref = oracle_sample(oracle_lib, wl, targets, tb, t_end, None, fanout, 0, 0, 0, adjs=adjs)
+        assert_same(gpu_sample(plan, targets, tb, t_end, compact=False), ref, None, f"start={tb is not None}")
+    plan.close()
