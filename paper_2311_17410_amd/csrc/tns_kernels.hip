@@ -613,14 +613,14 @@ hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t 
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     if (a.prefix_layout) return launch_sample_prefix(a, stream);
-    // Small batches go to the kernel with sixteen lanes per query.  us per call with that kernel / with a query per
-    // lane (store of 2^22 edges, fan-out 10): uniform ids, recent 1024 queries 12.4 / 16.9, 65536 23.6 / 27.8, 131072
-    // 42.0 / 31.3; power-law ids, recent, windowed 12.8 / 35.2, 40.3 / 50.8, 83.5 / 59.7; power-law ids, uniform policy
-    // 11.9 / 37.2, 34.3 / 55.2, 62.9 / 66.2.  With fewer than 8 slots half of a team has nothing to gather, and the limit
-    // stays below 2^16, where the workgroups of the other kernel take a second wave and it halves its tickets.  Mean over six
-    // stores and three windows of the time with the teams over the time without: fan-out 1, recent 61000 queries 0.86, 65536
-    // 1.08, uniform 1.01, 1.32; fan-out 5 0.83, 1.03, 0.95, 1.17; fan-out 7 0.80, 1.01, 0.91, 1.09.
-    const int64_t team_max_queries = (int64_t(1) << 16) - (a.fanout < 8 ? 1 : 0);
+    // Small batches go to the kernel with sixteen lanes per query.  us per call with that kernel / with a query per lane, mean
+    // over six stores (uniform and power-law ids, 2^18 to 2^24 edges) with and without a window: recent policy, fan-out 10, 1024
+    // queries 12.5 / 14.9, 32768 19.6 / 23.2, 61000 29.5 / 31.2, 65536 30.1 / 25.6, 131072 57.2 / 29.2; uniform policy 12.7 / 18.0,
+    // 20.1 / 27.8, 29.8 / 36.1, 30.5 / 31.6, 58.0 / 37.4.  At 2^16 the workgroups of the other kernel take a second wave and it halves
+    // its tickets: only under the uniform policy, and with at least 8 slots (with fewer half of a team has nothing to gather), are
+    // the teams still faster there.  Time with them over the time without at 61000 and 65536 queries: recent, fan-out 1 0.97,
+    // 1.25, fan-out 7 0.95, 1.19, fan-out 20 0.97, 1.16; uniform 0.98, 1.27, 0.88, 1.06, 0.80, 0.94.
+    const int64_t team_max_queries = (int64_t(1) << 16) - (a.policy == 0 || a.fanout < 8 ? 1 : 0);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;
     const bool wide = a.wide_offsets != 0;
