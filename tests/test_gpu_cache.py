@@ -116,41 +116,58 @@ def test_random_configuration(KB, seed):
     gpu.close()
 
 
-def test_fetch_replayed_from_a_hip_graph(KB):
-    # the fetch forks part of its work onto a stream of the cache's own and joins it again; captured once and
-    # replayed, every replay must behave like one more fetch of the same batch (state and rows checked each time)
+# A fetch is three launches on the caller's stream, or (caches of more than 65536 entries under LRU and LFU, more than 2^20
+# ids, more than 2^24 pieces of rows) forks its update onto a stream of the cache's own and joins it again.
+@pytest.mark.parametrize("policy,n,cap,dim,b", [(CO.LRU, 5000, 400, 20, 3000), (CO.LFU, 5000, 400, 20, 3000), (CO.FIFO, 5000, 400, 20, 3000),
+                                                (CO.LRU, 300_000, 70_000, 20, 30_000), (CO.LFU, 300_000, 70_000, 20, 30_000),
+                                                (CO.FIFO, 60_000, 5000, 4, (1 << 20) + 1)])
+def test_fetch_replayed_from_a_hip_graph(KB, policy, n, cap, dim, b):
+    # captured once and replayed, every replay must behave like one more fetch of the same batch (state and rows checked
+    # each time)
     import torch
     dev = torch.device("cuda", 0)
     rng = np.random.default_rng(77)
-    n, cap, dim = 5000, 400, 20
     store = rng.standard_normal((n, dim)).astype(np.float32)
     d_store = torch.from_numpy(store).to(dev)
-    ids = (rng.zipf(1.1, 3000) % n).astype(np.int32)
+    ids = (rng.zipf(1.1, b) % n).astype(np.int32)
     d_ids = torch.from_numpy(ids).to(dev)
-    for policy in (CO.LRU, CO.LFU, CO.FIFO):
-        ref = CO.VectorCache(n, cap, dim, policy, 0.2)
-        gpu = KB.Cache(n, cap, dim, policy, 0.2)
-        out = torch.empty((len(ids), dim), dtype=torch.float32, device=dev)
-        hit = torch.empty(len(ids), dtype=torch.uint8, device=dev)
-        gpu.fetch(d_ids, d_store, out, hit)                     # eager once (also allocates the workspace)
-        ref.fetch(ids, store)
+    ref = CO.VectorCache(n, cap, dim, policy, 0.2)
+    gpu = KB.Cache(n, cap, dim, policy, 0.2)
+    out = torch.empty((len(ids), dim), dtype=torch.float32, device=dev)
+    hit = torch.empty(len(ids), dtype=torch.uint8, device=dev)
+    gpu.fetch(d_ids, d_store, out, hit)                     # eager once (also allocates the workspace)
+    ref.fetch(ids, store)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        gpu.fetch(d_ids, d_store, out, hit)
+    for rep in range(3):
+        out.zero_()
+        assert float(d_store.sum().item()) == float(d_store.sum().item())     # unrelated eager work and a sync
+        graph.replay()
         torch.cuda.synchronize()
-        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
-        with torch.cuda.graph(graph, stream=side):
-            gpu.fetch(d_ids, d_store, out, hit)
-        for rep in range(3):
-            out.zero_()
-            assert float(d_store.sum().item()) == float(d_store.sum().item())     # unrelated eager work and a sync
-            graph.replay()
-            torch.cuda.synchronize()
-            r_out, r_hit = ref.fetch(ids, store)
-            assert np.array_equal(out.cpu().numpy(), r_out) and np.array_equal(hit.cpu().numpy().astype(bool), r_hit), (policy, rep)
-            st = gpu.save()
-            assert np.array_equal(st["id_of"], ref.id_of), (policy, rep)
-            if policy != CO.FIFO:
-                assert np.array_equal(st["score"], ref.score), (policy, rep)
-        del graph
-        gpu.close()
+        r_out, r_hit = ref.fetch(ids, store)
+        assert np.array_equal(out.cpu().numpy(), r_out) and np.array_equal(hit.cpu().numpy().astype(bool), r_hit), rep
+        st = gpu.save()
+        assert np.array_equal(st["id_of"], ref.id_of), rep
+        if policy != CO.FIFO:
+            assert np.array_equal(st["score"], ref.score), rep
+    del graph
+    gpu.close()
+
+
+@pytest.mark.parametrize("policy,cap,dim,b", [
+    (CO.FIFO, 3000, 4, 1 << 20), (CO.FIFO, 3000, 4, (1 << 20) + 1),       # ids on either side of the line, the ring goes round
+    (CO.LRU, 3000, 4, 1 << 20), (CO.LFU, 3000, 4, (1 << 20) + 1),
+    (CO.LRU, 3000, 64, 1 << 18), (CO.FIFO, 3000, 256, 1 << 18), (CO.FIFO, 3000, 256, (1 << 18) + 1),     # 2^24 pieces and one row more
+    (CO.FIFO, 3000, 17, 1_000_000), (CO.LRU, 3000, 17, 986_895), (CO.LRU, 3000, 17, 986_896),           # pieces of one float
+    (CO.LRU, 65_536, 8, 90_000), (CO.LRU, 65_537, 8, 90_000), (CO.LFU, 70_000, 172, 90_000), (CO.LFU, 70_000, 7, 90_000)])
+def test_both_sides_of_the_lines_between_the_two_forms(KB, policy, cap, dim, b):
+    rng = np.random.default_rng(cap + dim)
+    n = 100_000
+    batches = [rng.zipf(1.05, b) % n, rng.integers(0, n, b), rng.zipf(1.05, 1 + b // 3) % n, rng.integers(-3, n + 3, b)]
+    gpu, *_ = run_sequence(KB, policy, n, cap, dim, 0.5, batches, 5)
+    gpu.close()
 
 
 @pytest.mark.parametrize("policy", [CO.LRU, CO.LFU])
