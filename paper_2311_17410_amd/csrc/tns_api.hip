@@ -261,7 +261,9 @@ int upload_dirty(DeviceArray<T>& d, const P& host, hipStream_t stream, const cha
 // Room a growing array of a device-built store is given for `need` elements.  Growing costs a copy and two waits for the
 // device, some 150 us however small the array, and a young store grows every few batches: up to kYoungBytes it is given four
 // times what it needs, above that one and a half times (32 batches of 100 K edges, each sampled, into a new store 4.15 -> 3.38
-// ms; 64 of 2000 3.09 -> 3.04).
+// ms; 64 of 2000 3.09 -> 3.04).  It costs memory: up to kYoungBytes for the edge data and as much for the records and a quarter for
+// their counts.  What a closed plan leaves with the pool stays within kHold (after that store 246 MiB, with half more than
+// needed each time 234), and so does the time the next request after an idle spell takes to free it (1.8 to 2.2 ms for both).
 constexpr int64_t kYoungBytes = int64_t(128) << 20;
 inline int64_t room_for(int64_t need, int64_t element) {
     return std::max(need + need / 2 + 1024, std::min(4 * need, kYoungBytes / element));
@@ -848,7 +850,8 @@ static int run_impl(tns_plan* plan, int64_t Q, const int32_t* d_targets, const f
     // One pass: sampling with the padding removal fused in.  With the edge data in host memory the reads
     // cross the host link and what counts is how many of them are in flight: the plain sampling kernel
     // keeps more waves resident than the fused one, so the two steps are run one after the other
-    // (C3, edge data on the host: 29.0 + 0.9 ms against 46.9 ms fused).  A store with deleted edges also takes the
+    // (2^20 queries over power-law ids, recent policy, fan-out 10, edge data on the host 1.46 ms against 2.59 fused, everything on
+    // the host 2.42 against 3.55).  A store with deleted edges also takes the
     // two steps: a block with deleted edges is scanned candidate by candidate, a hub query under the uniform policy
     // can then take long, and in the fused kernel every later tile's bounded wait would be running meanwhile.
     const bool fuse = want_cmp && !plan->d_edges.on_host && !plan->deleted_edges;

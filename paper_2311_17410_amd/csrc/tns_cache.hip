@@ -172,8 +172,10 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
 // out[b] = cached row or row of the backing store; VEC floats per thread, rows stay coalesced
 // The slot comes from the id map directly (the threads of a row read the same two words), so the gather does not
 // wait for the lookup kernel, which records the accesses for the update beside it.  A thread moves kGatherUnroll
-// pieces, one grid width apart, and runs each dependent step (id, slot, row, store) for all of them before the next:
-// the kernel is a copy, and a copy on this machine is bound by how much each compute unit has in flight.
+// pieces, one grid width apart: the kernel is a copy, and a copy on this machine is bound by how much each compute unit has
+// in flight.  As compiled, seven pieces run each dependent step (id, slot, row) together, the first one's three reads
+// follow in the branch of its store, and every store waits for its own row: 4.1 TB/s for 2^20 rows of 172 floats, where the
+// library's copy kernels reach 4.3 (a store right behind each load) to 6.1.
 constexpr int kGatherUnroll = 8;
 // idx_t: a type that holds the number of pieces
 template <int VEC, int THREADS, typename idx_t>
@@ -199,14 +201,13 @@ __device__ __forceinline__ void gather_body(const float* __restrict__ rows, cons
         s[u] = slot_of[in_range ? id[u] : 0];
         if (!in_range) s[u] = -2;                                         // -1: not cached, -2: id out of range
     }
-    // the output and the rows of the backing store are touched once (non-temporal); the cached rows are
-    // what should stay in the L2
+    // the output is touched once (non-temporal); the cached rows are what should stay in the L2
     typedef float vec_t __attribute__((ext_vector_type(VEC)));
     vec_t v[kGatherUnroll];
 #pragma unroll
     for (int u = 0; u < kGatherUnroll; ++u) {
         const float* src = s[u] >= 0 ? rows + (int64_t)s[u] * dim + col[u] : store + (int64_t)(s[u] == -1 ? id[u] : 0) * dim + col[u];
-        v[u] = s[u] >= 0 ? *reinterpret_cast<const vec_t*>(src) : __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(src));
+        v[u] = *reinterpret_cast<const vec_t*>(src);
         if (s[u] == -2) v[u] = vec_t(0.f);
     }
 #pragma unroll

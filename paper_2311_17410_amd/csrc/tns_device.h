@@ -94,9 +94,13 @@ __device__ __forceinline__ int64_t wave_read(int64_t v, int lane) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-constexpr int kCoopGroup = 16;        // lanes per query in the cooperative search (recent policy, fan-out <= 16)
+constexpr int kCoopGroup = 16;        // lanes per query in the cooperative search (recent policy)
 constexpr int kGatherChunk = 10;      // gather iterations whose loads are issued together (8 and 5 measured slower)
-constexpr int kGatherGroup = 5;       // of which so many are prepared side by side (every fan-out in use is a multiple)
+// ... of which so many are prepared side by side (recent policy).  The last group of a fan-out that is no multiple prepares up
+// to four iterations without a slot and re-reads a line in them.  A test around each load instead: 2^20 queries over power-law
+// ids, fan-out 1 101.4 -> 100.3 us, 6 112.1 -> 111.6, 16 158 -> 157, but 10 120.0 -> 121.2 and 2^26 queries 6231 -> 6259; edge data
+// on the host, any fan-out, no difference.
+constexpr int kGatherGroup = 5;
 
 // Unsigned index type of the same width as the LDS position entries: with a 32-bit index the edge
 // load is addressed as base + 32-bit offset, one register per address.
@@ -305,8 +309,6 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 
-// Word index of the edge in slot j of a query: the first hq slots come from the block whose
-// search the wave finished (newest first), the others from the positions the lane recorded.
 // The wave's cooperative gather: its 64*f slots in flat order, lane l handles slot it*64 + l, so
 // consecutive lanes read consecutive edges of one query (12-byte loads within one or two lines)
 // and every store instruction covers 256 consecutive bytes of an output array.  The loads of up to

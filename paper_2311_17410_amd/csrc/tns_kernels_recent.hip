@@ -2,9 +2,9 @@
 // paper (section 4.2), the padded write, and the padding removal of section 5 fused in when the dense outputs are wanted.
 //
 // One query per lane, as in tns_kernels.hip (64 independent chains of dependent reads per wave).  What paces the kernel is
-// the length of a wave's program, not the memory: time stamps in it, for 2^16 queries over each of 256 graphs with a
-// window, gave 3.4 us for the node lines and 9.9 for the searches, the positions and the waits between them, and 7 of
-// every 27 us a wave spent waiting for the slowest one of its tile.  So the steps are arranged to be short and free of
+// the length of a wave's program, not the memory: time stamps in the kernel before this one, for 2^16 queries over each of 256
+// graphs with a window, gave 3.4 us for the node lines and 9.9 for the searches, the positions and the waits between them, and
+// 7 of every 27 us a wave spent waiting for the slowest one of its tile.  So the steps are arranged to be short and free of
 // waits on one another:
 //   node      the wave fetches the 128-byte node lines together, eight lanes per line, and hands them over through LDS
 //   blocks    each lane finds, among its up to seven records in registers, the blocks that count as a whole, the one with
@@ -17,8 +17,7 @@
 //   gather    lane l takes flat slot it * 64 + l of the wave's 64 f slots, finds the slot's block by comparing all bytes
 //             at once, and loads the edge; five such loads are prepared side by side
 // Against the kernel in which every lane wrote its slots' positions itself, after two rounds of searches for all 64 queries:
-// 256 graphs of 2^16 queries, windowed, 1737 -> 1502 us; 2^22 queries over uniform ids 426 -> 372; 2^26 6624 -> 6236, which is
-// 6 TB/s of lines and rows and what the memory gives.
+// 256 graphs of 2^16 queries, windowed, 1737 -> 1502 us; 2^22 queries over uniform ids 426 -> 372; 2^26 6624 -> 6236.
 // Nodes with long lists (directory runs) or with deleted edges take the walk of Algorithm 1 lane by lane instead; their
 // row of the table holds one entry per slot.
 #include <algorithm>
@@ -39,6 +38,9 @@ constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes 
 // block i or an older one.  Top byte of `lo`: filled slots; of `hi`: 1 if the row holds an entry per slot.
 struct SlotHead { uint32_t lo, hi; };
 
+// Registers: fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
+// positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
+// all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
 template <bool INCL, typename pos_t, bool FUSED>
 __global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6)
 tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {

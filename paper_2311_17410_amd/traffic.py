@@ -168,7 +168,8 @@ def main(argv=None) -> int:
              f"  python3 -m paper_2311_17410_amd.traffic --kt gpurun_out/prof/kt --fetch gpurun_out/prof/fetch --write gpurun_out/prof/write "
              f"--workload {args.workload} --json profiles/traffic.json --summary profiles/{os.path.basename(args.summary)}", "",
              "Template arguments of the sampling kernels: <policy (0 recent, 1 uniform), inclusive window end, position type,",
-             "counting pass (byte model), padding removal fused>.  <p,false,int,false,true> is the timed step.", "",
+             "counting pass (byte model), padding removal fused>; of tns_sample_recent_kernel (default layout, recent policy):",
+             "<inclusive window end, position type, padding removal fused>.  <p,false,int,false,true> and <false,int,true> are the timed steps.", "",
              "kernel trace (ms per dispatch): name, dispatches, avg, min, max"]
     for k in sorted(trace):
         v = trace[k]
