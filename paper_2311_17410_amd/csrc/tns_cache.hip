@@ -533,8 +533,9 @@ __global__ void __launch_bounds__(256) k_newids_collect_hist0(const NewIds f, in
 // stored in 2.5 us where the equal ones are all taken or all left, by one comparison; with both compared for
 // every score and counted in a pass of their own they took 9.  Time stamps, batch of 66600 of which 8388 are replaced: new ids
 // known at 8 us, threshold at 15, victims stored at 18.
-// 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO: 66600 ids 71 / 74 / 61 -> 34 / 36 / 32, 16000 ids 67 / 67 / 60
-// -> 22 / 19 / 16, 600 ids 69 / 67 / 60 -> 16 / 15 / 13.
+// 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO, one cache again and again: 66600 ids 71 / 74 / 61 -> 34 / 36 / 32, 16000 ids 67 / 67 / 60
+// -> 22 / 19 / 16, 600 ids 69 / 67 / 60 -> 16 / 15 / 13.  Three caches in turn, so that their rows come from memory: 66600 ids
+// 83 / 84 / 65 -> 41 / 44 / 40.
 constexpr int kOneGroup = 1024, kOneGroupWaves = kOneGroup / kWave;
 constexpr int kItems = 64, kItemStep = 8;                         // scores per thread, and per uniform branch
 // Where the line lies: a large gather saturates the memory, and the chain of dependent reads of the tiles beside it then
