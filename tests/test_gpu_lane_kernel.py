@@ -1,4 +1,4 @@
-"""The kernel with a query per lane serves batches above 2^16 queries (from there on with small fan-outs): its parity at the edge of
+"""The kernel with a query per lane serves batches above 2^16 queries (from there on under the recent policy and with small fan-outs): its parity at the edge of
 that rule, with 64-bit positions, over instances of uneven and no size, and its bounded wait."""
 import time
 
