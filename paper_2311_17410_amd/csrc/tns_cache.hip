@@ -425,13 +425,13 @@ __device__ __forceinline__ SelState select_pick(Ctl* ctl, int pass /* 1..kPasses
 __device__ __forceinline__ void select_hist_body(const int32_t* __restrict__ score, int64_t capacity, int pass, Ctl* ctl, int64_t bid, int64_t nb) {
     __shared__ int32_t s_h[kBins];
     uint32_t prefix = 0, mask = 0;
+    const int32_t now = ctl->now;              // (read here, beside what the pick reads)
     if (pass > 0) {
         if (ctl->m <= 0) return;
         const SelState st = select_pick(ctl, pass, bid == 0);
         prefix = st.prefix;
         mask = st.mask;
     }
-    const int32_t now = ctl->now;
     const int shift = digit_shift(pass);
     const uint32_t dmask = digit_mask(pass);
 #pragma unroll
@@ -776,15 +776,17 @@ __device__ __forceinline__ void insert_body(const CacheState& c, int policy, int
                                             int64_t bid) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t i = bid * 4 + (threadIdx.x >> 6);
-    if (i >= ctl->m) return;
+    // (the scalars are read before the first store: a load behind stores is only waited for together with them)
+    const int32_t m = ctl->m, now = ctl->now;
+    if (i >= m) return;
     const int32_t s = policy == TNS_CACHE_FIFO ? fifo_slot(ctl->ring, i, c.capacity) : victims[i], id = new_ids[i];
     if (lane == 0) {
         const int32_t old = c.id_of[s];
         if (old >= 0) c.slot_of[old] = -1;
         c.id_of[s] = id;
         c.slot_of[id] = s;
-        c.score[s] = policy == TNS_CACHE_LFU ? 1 : ctl->now;
-        if (i == 0) atomicAdd(&c.counters[2], (unsigned long long)ctl->m);
+        c.score[s] = policy == TNS_CACHE_LFU ? 1 : now;
+        if (i == 0) atomicAdd(&c.counters[2], (unsigned long long)m);
     }
     const float* __restrict__ src = store + (int64_t)id * dim;
     float* __restrict__ dst = c.rows + (int64_t)s * dim;
