@@ -16,6 +16,8 @@
 //             block packed into bytes: nothing per slot and no loop over slots
 //   gather    lane l takes flat slot it * 64 + l of the wave's 64 f slots, finds the slot's block by comparing all bytes
 //             at once, and loads the edge; five such loads are prepared side by side
+// (Only loads that have a request are issued, and the queries are requested before their instance is searched for: 2^23 queries
+// 688 -> 668 us windowed, 728 -> 713 without, 2^26 6235 -> 6200.)
 // Against the kernel in which every lane wrote its slots' positions itself, after two rounds of searches for all 64 queries:
 // 256 graphs of 2^16 queries, windowed, 1737 -> 1502 us; 2^22 queries over uniform ids 426 -> 372; 2^26 6624 -> 6236.
 // Nodes with long lists (directory runs) or with deleted edges take the walk of Algorithm 1 lane by lane instead; their
@@ -82,16 +84,19 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     w.group = kCoopGroup;
     w.te = 0.0f;
     w.tb = 0.0f;
-    const int32_t inst = p.inst_rowptr ? instance_of(p.inst_rowptr, p.num_instances, q0, q, Q, lane) : 0;
-    uint32_t node = ~0u;               // the target's entry in the node table (a table of 2^32 lines does not exist)
-    if (q < Q) {
-        const int32_t v = __builtin_nontemporal_load(&p.targets[q0 + lane]);
+    // (the queries are requested before the reads that find their instance: two or three dependent ones)
+    const bool have = q < Q;
+    int32_t v = -1;
+    if (have) {
+        v = __builtin_nontemporal_load(&p.targets[q0 + lane]);
         w.te = __builtin_nontemporal_load(&p.t_end[q0 + lane]);
-        w.tb = p.t_start ? p.t_start[q0 + lane] : (p.delta == INFINITY ? -INFINITY : w.te - p.delta);
-        bool ok = (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
-        if (p.inst_rowptr) ok = ok && inst < p.num_instances;
-        if (ok) node = (uint32_t)(inst * p.num_nodes + v);
+        if (p.t_start) w.tb = p.t_start[q0 + lane];
     }
+    const int32_t inst = p.inst_rowptr ? instance_of(p.inst_rowptr, p.num_instances, q0, q, Q, lane) : 0;
+    if (!p.t_start) w.tb = p.delta == INFINITY ? -INFINITY : w.te - p.delta;
+    bool ok = have && (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
+    if (p.inst_rowptr) ok = ok && inst < p.num_instances;
+    const uint32_t node = ok ? (uint32_t)(inst * p.num_nodes + v) : ~0u;      // the target's entry in the node table (a table of 2^32 lines does not exist)
     // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -204,12 +209,14 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
             float t[kRequestBatch];
 #pragma unroll
             for (int i = 0; i < kRequestBatch; ++i) {
+                if (r0 + i * kGroups >= num_requests) break;       // uniform: a load without a request costs its address cycles
                 // (beyond the last request: the last one again, its lines are on their way anyway)
                 d[i] = requests[min(r0 + i * kGroups + g, num_requests - 1)];
                 t[i] = __uint_as_float(p.edges[request_word<pos_t>(d[i], j)]);
             }
 #pragma unroll
             for (int i = 0; i < kRequestBatch; ++i) {
+                if (r0 + i * kGroups >= num_requests) break;
                 const bool first = j < request_slots(d[i]) && (t[i] < d[i].t || (INCL && request_closed(d[i]) && t[i] == d[i].t));
                 const uint32_t c = (uint32_t)__popc((uint32_t)(__ballot(first) >> (g * kCoopGroup)) & 0xffffu);
                 found[min(r0 + i * kGroups + g, num_requests - 1)] = (unsigned char)c;
