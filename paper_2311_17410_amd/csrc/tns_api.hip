@@ -980,8 +980,16 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
     size_t scan = 0;
     for (int h = 0; h < num_hops; ++h) scan += tns::compact_workspace_bytes(caps[h]);
     int64_t* header = reinterpret_cast<int64_t*>(scan_ws + scan);
-    {
-        const hipError_t e = tns::launch_scan_clear(d_workspace, kStatusBytes + scan, stream);
+    // One launch clears the regions of the hops that are too large to do without: from the first of them on (hops do not get
+    // smaller), with the status word if that is the first hop; otherwise the first hop leaves the word as it should be.
+    int first_cleared = 0;
+    if (Q > 0)
+        while (first_cleared < num_hops && caps[first_cleared] <= tns::tagged_queries(fanouts[first_cleared])) ++first_cleared;
+    if (first_cleared < num_hops) {
+        unsigned char* from = scan_ws;
+        for (int h = 0; h < first_cleared; ++h) from += tns::compact_workspace_bytes(caps[h]);
+        if (first_cleared == 0) from = static_cast<unsigned char*>(d_workspace);
+        const hipError_t e = tns::launch_scan_clear(from, (size_t)(scan_ws + scan - from), stream);
         if (e != hipSuccess) return fail_hip(e, "clearing the chained-scan workspace");
     }
     a.err_flag = static_cast<uint32_t*>(d_workspace) + 1;   // every hop reports a time-out in the same word
@@ -998,7 +1006,7 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
         a.out_count = b.count;
         a.total_out = total;
         a.scan_ws = scan_ws;                                    // sampling with the padding removal fused in
-        a.scan_ready = Q > 0 ? 1 : 0;                           // cleared above, together with the other hops' regions
+        a.scan_ready = Q > 0 && h >= first_cleared ? 1 : 0;     // cleared above, together with the other hops' regions
         scan_ws += tns::compact_workspace_bytes(caps[h]);
         a.rowptr = b.rowptr;
         a.cmp_nbr = b.cmp_nbr;

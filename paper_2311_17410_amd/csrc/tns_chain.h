@@ -23,7 +23,8 @@ constexpr int kSpinLimit = 1 << 22;
 struct ScanWorkspace {
     uint32_t ticket;
     uint32_t error;
-    uint32_t pad[62];
+    uint64_t launches;    // tagged chain
+    uint32_t pad[60];
     uint64_t status[1];   // [number of tiles]
 };
 
@@ -78,6 +79,103 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
     }
     return excl;
 }
+
+// ---- the same for a small grid, without a launch that clears the state and without tickets --------------------------
+//
+// A batch of a few hundred tiles is bound by latency: the clearing launch is 2.5 us of it, and tickets, atomics on one word,
+// are taken at 18 ns each (14 us for the 782 tiles of 10^5 queries).  Here a tile's word carries a tag next to the total, and
+// a word with another tag has not been written yet, whatever the workspace held before.  The tag is made from a key that the
+// host draws anew for every launch, and, because a captured launch is replayed with the same key, from two counters in the
+// workspace that every launch moves on: one in its head and one before the tiles' words.  Two, because a kernel that clears
+// its state overwrites the second (and a caller may clear the head): for the words of an earlier replay to be taken for new
+// ones both would have to be set back and the words kept.  The last tile moves the counters on, when it has heard from every
+// other tile, which has then read them.  Memory that by chance holds the tag of a launch: one word in 2^48.
+//
+// Every tile reads the totals of all tiles before it, four words per lane at a time; there are no prefixes to wait for.  Tiles
+// are numbered as the workgroups are, which start in that order, and the grid is not larger than what the chip holds at once
+// (tagged_queries), so that a tile that waits keeps no earlier one from starting; the wait is bounded all the same.
+// us per call, 2^21 edges, fan-out 10, tickets and clearing launch / this, recent policy, uniform ids: 65537 queries 22.6 /
+// 13.4, 10^5 27.8 / 15.7, 2 * 10^5 37.0 / 25.3, 2^18 - 1 36.9 / 29.2; power-law ids 26.7 / 17.8, 32.5 / 20.5, 40.8 / 28.7, 38.0 / 30.5; uniform
+// policy, power-law ids 38.8 / 32.0, 49.3 / 38.9, 66.8 / 58.0, 77.9 / 66.4; prefix layout, recent 32.4 / 23.5, 37.4 / 25.5, 44.7 /
+// 32.6, 41.2 / 35.5.  Both forms in one kernel, chosen at run time, cost the large batches of the prefix layout 1 to 4 %.
+constexpr int kTagShift = 16;                         // a tile's total is below 2^16
+__host__ __device__ inline uint64_t mix64(uint64_t z) {      // splitmix64's output function
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+__host__ __device__ inline uint64_t chain_tag(uint64_t key, uint64_t in_head, uint64_t before_tiles) {
+    return mix64(key + in_head * 0x9E3779B97F4A7C15ull + mix64(before_tiles + 1)) >> kTagShift;
+}
+
+// Where the words of a tagged chain are: status[0] is the second counter, tile t's word is status[t + 1].
+struct TaggedChain {
+    ScanWorkspace* ws;
+    uint64_t in_head, before_tiles, tag;
+    __device__ __forceinline__ void request(void* scan_ws) {
+        ws = static_cast<ScanWorkspace*>(scan_ws);
+        in_head = __hip_atomic_load(&ws->launches, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before_tiles = __hip_atomic_load(&ws->status[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // once the counters have arrived; they are the same in all lanes and need not stay in registers of each
+    __device__ __forceinline__ void settle(uint64_t key) {
+        auto uniform = [](uint64_t v) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+            return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32 | lo;
+        };
+        in_head = uniform(in_head);
+        before_tiles = uniform(before_tiles);
+        tag = chain_tag(key, in_head, before_tiles);
+    }
+    __device__ __forceinline__ void publish(int64_t tile, int32_t total) const {
+        __hip_atomic_store(&ws->status[tile + 1], tag << kTagShift | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // what an error word holds after a wait of this launch ran out
+    __device__ __forceinline__ uint32_t mark() const { return (uint32_t)tag | 1u; }
+    // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.
+    __device__ __forceinline__ int64_t exclusive(uint32_t* err_flag, int64_t tile, int lane) const {
+        int64_t sum = 0;
+        int spins = 0;
+        for (int64_t t0 = 0; t0 < tile; t0 += 4 * kChainWave) {
+            uint64_t w[4];
+            while (true) {
+                bool ready = true;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t t = t0 + i * kChainWave + lane;
+                    w[i] = tag << kTagShift;
+                    if (t < tile) w[i] = __hip_atomic_load(&ws->status[t + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ready = ready && w[i] >> kTagShift == tag;
+                if (!__ballot(!ready)) break;
+                if (++spins > kSpinLimit) {
+                    if (lane == 0) atomicExch(err_flag, mark());
+                    __threadfence();
+                    return 0;
+                }
+                if (spins < 16) __builtin_amdgcn_s_sleep(2);
+                else __builtin_amdgcn_s_sleep(16);
+            }
+            int64_t v = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & ((1ull << kTagShift) - 1ull));
+            sum += v;
+        }
+        for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kChainWave);
+        return sum;
+    }
+    // The end of the launch, by one lane that knows that every tile has published: true if a wait of this launch ran out.
+    // An error word that holds anything else is made 0 (it held whatever the workspace did).
+    __device__ __forceinline__ bool close(uint32_t* err_flag) const {
+        __threadfence();
+        const bool bad = __hip_atomic_load(err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark();
+        if (!bad) __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ws->launches, in_head + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ws->status[0], before_tiles + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return bad;
+    }
+};
 
 }  // namespace
 }  // namespace tns

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "tns_chain.h"
 #include "tns_kernels.h"
@@ -431,51 +432,86 @@ __device__ __forceinline__ void store_dense(const GatherRegs& g, const SampleArg
 
 // ---- a workgroup's tile and the padding removal fused into sampling --------------------------------------
 
-// Tiles are numbered in the order workgroups start, so that a tile only ever waits for tiles that have started.
-__device__ __forceinline__ int64_t take_tile(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived) {
-    if (threadIdx.x == 0) {
-        *s_tile_base = (int64_t)atomicAdd(&static_cast<ScanWorkspace*>(p.scan_ws)->ticket, 1u);
-        *s_arrived = 0;
+// How a kernel numbers its tiles and learns the dense entries of the tiles before one.
+enum Scan : int {
+    kNoScan,      // padded rows only
+    kTickets,     // tiles numbered in the order workgroups start: a tile only ever waits for tiles that have started
+    kTags,        // small grids (TaggedChain)
+};
+template <int SCAN>
+struct TileChain {
+    static constexpr bool kTagged = SCAN == kTags;
+    TaggedChain tags;
+    int64_t tile;
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived) {
+        if (threadIdx.x == 0) *s_arrived = 0;
+        if (kTagged) {
+            tags.request(p.scan_ws);
+            tile = (int64_t)blockIdx.x + p.first_ticket;
+            __syncthreads();
+        } else {
+            if (threadIdx.x == 0) *s_tile_base = (int64_t)atomicAdd(&static_cast<ScanWorkspace*>(p.scan_ws)->ticket, 1u);
+            __syncthreads();
+            tile = wave_uniform(*s_tile_base);
+            __syncthreads();
+        }
     }
-    __syncthreads();
-    const int64_t tile = wave_uniform(*s_tile_base);
-    __syncthreads();
-    return tile;
-}
+    __device__ __forceinline__ void settle(const SampleArgs& p) {
+        if (kTagged) tags.settle(p.chain_key);
+    }
+    __device__ __forceinline__ ScanWorkspace* ws(const SampleArgs& p) const { return static_cast<ScanWorkspace*>(p.scan_ws); }
+    // one wave, at once, so that later tiles can look past this one
+    __device__ __forceinline__ void publish_total(const SampleArgs& p, int32_t total, int lane) const {
+        if (lane != 0) return;
+        if (kTagged) tags.publish(tile, total);
+        else if (tile > 0) __hip_atomic_store(&ws(p)->status[tile], kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // one wave: the dense entries of the tiles before this one
+    __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
+        if (kTagged) return tags.exclusive(p.err_flag, tile, lane);
+        const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane) : 0;
+        if (lane == 0)
+            __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return excl;
+    }
+    // by the last query's lane, whose tile has looked back over every other one: true if any wait ran into its bound
+    __device__ __forceinline__ bool failed(const SampleArgs& p) const {
+        if (kTagged) return tags.close(p.err_flag);
+        __threadfence();
+        return __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    }
+};
+// Padded rows only: tiles in the order of the workgroups, or a contiguous range per XCD.
+template <>
+struct TileChain<kNoScan> {
+    int64_t tile;
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t*, int32_t*)
+        : tile(p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) {}
+    __device__ __forceinline__ void settle(const SampleArgs&) {}
+};
 
 // Output stage of a fused kernel: chained scan over the workgroup tiles for the dense offsets, padded rows, dense rows and
 // rowptr.  k: the lane's filled slots; load(g, it0): the wave's slots from it0 * 64 on into registers.
 // CHAIN_FIRST (recent policy): the look-back reads come before the wave's padded stores (a load result can only be waited
 // for together with every store issued before it, and a store takes microseconds to be taken).  Uniform policy: the other
 // order measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
-template <bool CHAIN_FIRST, class Load>
+template <bool CHAIN_FIRST, class Chain, class Load>
 __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_wave_sum, int32_t* s_arrived,
-                                             int64_t tile, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
+                                             const Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
                                              uint32_t f_mul, const Load& load) {
-    ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
     const int32_t f = p.fanout;
     const int32_t inc = wave_inclusive_scan(k, lane);
-    auto publish_total = [&](int32_t wg_total) {
-        // the tile total is published at once, so that later tiles can look past this one
-        if (lane == 0 && tile > 0)
-            __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto chain = [&](int32_t wg_total) {      // one wave: look back for the tile's offset, publish the prefix
-        const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
-        if (lane == 0) {
-            __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *s_tile_base = excl;
-        }
+    auto chain = [&](int32_t wg_total) {
+        const int64_t excl = tc.look_back(p, wg_total, lane);
+        if (lane == 0) *s_tile_base = excl;
     };
     auto write_rowptr = [&](int64_t row0) {
         if (q0 + lane < Q) {
             __builtin_nontemporal_store(row0 + (inc - k), &p.rowptr[q0 + lane]);
             if (q0 + lane == Q - 1) {
-                // The last query's tile has looked back over every other tile.  If any wait ran into its bound the dense
-                // rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
-                __threadfence();
-                const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                const int64_t tot = bad ? 0 : row0 + inc;
+                // If any wait ran into its bound the dense rows are not valid: the total then reads 0, so that a hop
+                // chained to this one has no queries.
+                const int64_t tot = tc.failed(p) ? 0 : row0 + inc;
                 p.rowptr[Q] = tot;
                 if (p.total_out) *p.total_out = tot;
             }
@@ -504,7 +540,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         if (is_last) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
             for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-            publish_total(wg_total);
+            tc.publish_total(p, wg_total, lane);
         }
         wave_lds_sync();      // what the load reads from LDS was written by this wave's own lanes
         load(g, 0);
@@ -522,7 +558,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         if (wave == 0) {
             int32_t wg_total = 0;
             for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
-            publish_total(wg_total);
+            tc.publish_total(p, wg_total, lane);
             chain(wg_total);
         }
         __syncthreads();
@@ -534,6 +570,31 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
             store_dense(g, p, f_mul, lane, it0, row0, inc - k);
         }
     }
+}
+
+// Launches `grid` workgroups of a kernel with a query per lane in the form that the batch asks for.
+template <bool FUSED, class Launch>
+hipError_t launch_tiles(const SampleArgs& a, int64_t grid, hipStream_t stream, const Launch& launch) {
+    SampleArgs b = a;
+    if (!FUSED) {
+        if (grid > 0) launch(std::integral_constant<int, kNoScan>{}, b);
+        return hipGetLastError();
+    }
+    if constexpr (FUSED) {
+        if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
+        if (grid > 0 && a.Q <= tagged_queries(a.fanout)) {
+            b.chain_key = new_chain_key();
+            launch(std::integral_constant<int, kTags>{}, b);
+            return hipGetLastError();
+        }
+        if (!a.scan_ready) {
+            // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
+            const hipError_t e = launch_scan_init(a, grid + 1, stream);
+            if (e != hipSuccess) return e;
+        }
+        if (grid > 0) launch(std::integral_constant<int, kTickets>{}, b);
+    }
+    return hipGetLastError();
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -21,6 +21,7 @@
 #include "tns_device.h"
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 namespace tns {
@@ -50,9 +51,10 @@ __global__ void __launch_bounds__(256) tns_scan_clear(uint64_t* ws, int64_t word
 
 // FUSED: also removes the padding in the same pass (rowptr and dense arrays), with the tile
 // offsets obtained from a chained scan over the workgroups.
-template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
-__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6)
+template <int POLICY, bool INCL, typename pos_t, bool COUNT, int SCAN>
+__global__ void __launch_bounds__(SCAN ? 1024 : 256, SCAN ? 4 : 6)
 tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
+    constexpr bool FUSED = SCAN != kNoScan;
     static_assert(POLICY == 1 || (COUNT && !FUSED), "the recent policy is sampled by tns_sample_recent_kernel");
     // LDS: one chunk per wave.  First the staging area of the node lines (3 KiB), later, in the same bytes,
     // the wave's rows of selected positions.
@@ -66,7 +68,7 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
-    // have none leave before they take a ticket (18 ns each)
+    // have none leave before they take a ticket
     const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
     if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
@@ -75,8 +77,9 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul
         }
         return;
     }
-    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
-                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
+    TileChain<SCAN> tc(p, &s_tile_base, &s_arrived);
+    const int64_t tile = tc.tile;
+    if (FUSED && tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -106,6 +109,7 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul
         }
         if (ok) nidx = nbase + v;
     }
+    tc.settle(p);
     // the node's 128-byte line: header + the records of up to 7 blocks, newest first
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -430,8 +434,8 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul
     const pos_t* __restrict__ w_pos = reinterpret_cast<const pos_t*>(my_lds);
 
     auto load = [&](GatherRegs& g, int32_t it0) { gather_load<pos_t, POLICY == 1>(g, p, f_mul, stride, w_pos, lane, it0, k); };
-    if (FUSED) {
-        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+    if constexpr (FUSED) {
+        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         wave_lds_sync();
         GatherRegs g;
@@ -580,18 +584,12 @@ hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (FUSED && !a.scan_ready) {
-        // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
-        const hipError_t e = launch_scan_init(a, grid + 1, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (grid <= 0) return hipGetLastError();
     const size_t lds = chunk * waves;
-    SampleArgs b = a;
-    if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
-    hipLaunchKernelGGL((tns_sample_kernel<POLICY, INCL, pos_t, COUNT, FUSED>), dim3((unsigned)grid), dim3(waves * kWave),
-                       lds, stream, b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
-    return hipGetLastError();
+    auto launch = [&](auto scan, const SampleArgs& b) {
+        hipLaunchKernelGGL((tns_sample_kernel<POLICY, INCL, pos_t, COUNT, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds,
+                           stream, b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
+    };
+    return launch_tiles<FUSED>(a, grid, stream, launch);
 }
 
 }  // namespace
@@ -613,16 +611,21 @@ hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t 
     return hipGetLastError();
 }
 
+uint64_t new_chain_key() {
+    static std::atomic<uint64_t> launches{0};
+    return mix64(0x9E3779B97F4A7C15ull * (launches.fetch_add(1, std::memory_order_relaxed) + 1));
+}
+
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     if (a.prefix_layout) return launch_sample_prefix(a, stream);
-    // Small batches go to the kernel with sixteen lanes per query.  us per call with that kernel / with a query per lane, mean
-    // over six stores (uniform and power-law ids, 2^18 to 2^24 edges) with and without a window: recent policy, fan-out 10, 1024
-    // queries 12.5 / 14.9, 32768 19.6 / 23.2, 61000 29.5 / 31.2, 65536 30.1 / 25.6, 131072 57.2 / 29.2; uniform policy 12.7 / 18.0,
-    // 20.1 / 27.8, 29.8 / 36.1, 30.5 / 31.6, 58.0 / 37.4.  At 2^16 the workgroups of the other kernel take a second wave and it halves
-    // its tickets: only under the uniform policy, and with at least 8 slots (with fewer half of a team has nothing to gather), are
-    // the teams still faster there.  Time with them over the time without at 61000 and 65536 queries: recent, fan-out 1 0.97,
-    // 1.25, fan-out 7 0.95, 1.19, fan-out 20 0.97, 1.16; uniform 0.98, 1.27, 0.88, 1.06, 0.80, 0.94.
-    const int64_t team_max_queries = (int64_t(1) << 16) - (a.policy == 0 || a.fanout < 8 ? 1 : 0);
+    // Small batches go to the kernel with sixteen lanes per query: up to one workgroup of it per compute unit, or two where
+    // every lane of a team has a slot to gather.  us per call with that kernel / with a query per lane over 2^21 edges, both
+    // without tickets and clearing launch: recent policy, fan-out 10, uniform ids, 16384 queries 9.4 / 9.5 (the host's 9.2),
+    // 32768 10.6 / 10.8, 49152 14.8 / 11.8, 65536 15.1 / 12.9, power-law ids 9.4 / 13.7, 14.8 / 15.2, 21.6 / 16.1, 22.3 / 17.3; fan-out 64,
+    // 65536 27.8 / 33.0 and 46.4 / 40.2.  Uniform policy, fan-out 10, uniform ids 9.2 / 11.7, 11.6 / 12.8, 16.2 / 14.1, 16.4 / 15.5,
+    // power-law ids 10.2 / 21.6, 17.5 / 25.2, 24.9 / 29.2, 25.7 / 32.3; fan-out 5, 32768 11.1 / 10.6 and 16.4 / 18.6, 65536
+    // 16.0 / 12.2 and 23.6 / 23.3.
+    const int64_t team_max_queries = int64_t(1) << ((a.policy == 0 ? a.fanout <= 32 : a.fanout < 8) ? 15 : 16);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;
     const bool wide = a.wide_offsets != 0;

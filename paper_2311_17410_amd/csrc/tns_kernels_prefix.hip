@@ -23,6 +23,7 @@
 // the prefix, then the prefix's lines as blocks of their own, the node's own line from registers.  They
 // leave edge positions in their row and the output stage loads those edges from memory.
 #include <algorithm>
+#include <type_traits>
 
 #include "tns_device.h"
 #include "tns_kernels.h"
@@ -178,10 +179,11 @@ __device__ __forceinline__ void walked_gather(const SampleArgs& p, uint32_t f_mu
 
 // Uniform policy: workgroups of at most eight waves, three of them per compute unit (80 registers; at 85, with two of
 // them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459).
-template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>
+template <int POLICY, bool INCL, typename pos_t, bool COUNT, int SCAN>
 __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_mul,
                                                                  const int32_t gshift, const uint32_t chunk,
                                                                  const uint32_t rows_bytes) {
+    constexpr bool FUSED = SCAN != kNoScan;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
@@ -201,8 +203,9 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         }
         return;
     }
-    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
-                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
+    TileChain<SCAN> tc(p, &s_tile_base, &s_arrived);
+    const int64_t tile = tc.tile;
+    if (FUSED && tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -226,6 +229,7 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         }
         if (ok) nidx = nbase + v;
     }
+    tc.settle(p);
     // ---- node lines: eight lanes per line, handed over through LDS ------------------------------------
     uint32_t w[3 * kInlineSlots];     // the eight edge slots of the node's own line
     uint32_t h_degree, h_meta, h_ext0, h_ext12, h_fence0, h_fence1, h_fence2, h_dir;   // the node entry
@@ -540,8 +544,8 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         if (row_path) rows_load(g, p, f_mul, rows, rs, lane, info);
         else gather_load<pos_t, POLICY == 1>(g, p, f_mul, pstride, w_pos, lane, it0, k);      // positions in the rows
     };
-    if (FUSED) {
-        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+    if constexpr (FUSED) {
+        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
@@ -579,18 +583,12 @@ hipError_t launch_prefix_t(const SampleArgs& a, hipStream_t stream) {
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (FUSED && !a.scan_ready) {
-        const hipError_t e = launch_scan_init(a, grid + 1, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (grid <= 0) return hipGetLastError();
     const size_t lds = chunk * waves;
-    auto kern = tns_sample_prefix_kernel<POLICY, INCL, pos_t, COUNT, FUSED>;
-    SampleArgs b = a;
-    if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b, rs, slot_multiplier(f), gshift, (uint32_t)chunk,
-                       (uint32_t)rows_bytes);
-    return hipGetLastError();
+    auto launch = [&](auto scan, const SampleArgs& b) {
+        hipLaunchKernelGGL((tns_sample_prefix_kernel<POLICY, INCL, pos_t, COUNT, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave),
+                           lds, stream, b, rs, slot_multiplier(f), gshift, (uint32_t)chunk, (uint32_t)rows_bytes);
+    };
+    return launch_tiles<FUSED>(a, grid, stream, launch);
 }
 
 }  // namespace

@@ -43,9 +43,10 @@ struct SlotHead { uint32_t lo, hi; };
 // Registers: fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
 // positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
 // all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
-template <bool INCL, typename pos_t, bool FUSED>
-__global__ void __launch_bounds__(FUSED ? 1024 : 256, FUSED ? 4 : 6)
+template <bool INCL, typename pos_t, int SCAN>
+__global__ void __launch_bounds__(SCAN ? 1024 : 256, SCAN ? 4 : 6)
 tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
+    constexpr bool FUSED = SCAN != kNoScan;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
@@ -55,7 +56,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
-    // have none leave before they take a ticket (18 ns each)
+    // have none leave before they take a ticket
     const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
     if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
@@ -64,8 +65,9 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         }
         return;
     }
-    const int64_t tile = FUSED ? take_tile(p, &s_tile_base, &s_arrived)
-                               : (p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x);
+    TileChain<SCAN> tc(p, &s_tile_base, &s_arrived);
+    const int64_t tile = tc.tile;
+    if (FUSED && tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -97,6 +99,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     bool ok = have && (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
     if (p.inst_rowptr) ok = ok && inst < p.num_instances;
     const uint32_t node = ok ? (uint32_t)(inst * p.num_nodes + v) : ~0u;      // the target's entry in the node table (a table of 2^32 lines does not exist)
+    tc.settle(p);
     // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -313,8 +316,8 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
             g.ts[i] = filled[i] ? raw[i].ts : 0.0f;
         }
     };
-    if (FUSED) {
-        fused_output<true>(p, &s_tile_base, s_wave_sum, &s_arrived, tile, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+    if constexpr (FUSED) {
+        fused_output<true>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
@@ -350,17 +353,12 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (FUSED && !a.scan_ready) {
-        // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
-        const hipError_t e = launch_scan_init(a, grid + 1, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (grid <= 0) return hipGetLastError();
-    SampleArgs b = a;
-    if (FUSED && !b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
-    hipLaunchKernelGGL((tns_sample_recent_kernel<INCL, pos_t, FUSED>), dim3((unsigned)grid), dim3(waves * kWave), chunk * waves, stream,
-                       b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
-    return hipGetLastError();
+    const size_t lds = chunk * waves;
+    auto launch = [&](auto scan, const SampleArgs& b) {
+        hipLaunchKernelGGL((tns_sample_recent_kernel<INCL, pos_t, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b,
+                           stride, slot_multiplier(a.fanout), (uint32_t)chunk);
+    };
+    return launch_tiles<FUSED>(a, grid, stream, launch);
 }
 
 }  // namespace

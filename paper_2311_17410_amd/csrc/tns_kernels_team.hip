@@ -17,8 +17,10 @@
 //             other.
 //   deleted   a node whose flags say that edges of it are deleted has its candidates looked at, sixteen side by side.
 //             The flag is read here and not on the host: a captured call may be replayed after a deletion.
-// What bounds it is the chain of dependent reads (query, node, search, edge, look-back) and, as every workgroup takes
-// a ticket, 18 ns per tile.  Measured beside tns_sample_kernel, fan-out 10, in us per call: see the rule in launch_sample.
+// What bounds it is the chain of dependent reads (query, node, search, edge, look-back).  Its tiles tag what they publish
+// instead of having the scan state cleared by a launch before it and tickets taken (TaggedChain): 1024 queries 11.3 -> 8.2 us
+// per call, two hops from 600 and 4000 roots 17.9 -> 14.8 and 26.9 -> 23.0.  Measured beside the kernels with a query per
+// lane: see the rule in launch_sample.
 #include <type_traits>
 
 #include "../../include/tns.h"
@@ -87,15 +89,12 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         }
         return;
     }
-    ScanWorkspace* ws = static_cast<ScanWorkspace*>(p.scan_ws);
-    if (threadIdx.x == 0) {
-        // tiles are numbered in the order workgroups start
-        s_tile_base = (int64_t)atomicAdd(&ws->ticket, 1u);
-        s_arrived = 0;
-    }
+    const int64_t tile = (int64_t)blockIdx.x + p.first_ticket;
+    if (tile * kTileQueries >= Q) return;      // (tests whose tiles start at 1)
+    if (threadIdx.x == 0) s_arrived = 0;
     __syncthreads();
-    const int64_t tile = s_tile_base;
-    __syncthreads();
+    TaggedChain chain;
+    chain.request(p.scan_ws);
     // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
     const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
 
@@ -170,6 +169,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
+    chain.settle(p.chain_key);
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -322,8 +322,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         // the wave that arrives last publishes the tile total at once, so that later tiles can look past this one
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         for (int i = 0; i < kTileWaves; ++i) wg_total += s_wave_sum[i];
-        if (lane == 0 && tile > 0)
-            __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)wg_total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) chain.publish(tile, wg_total);
     }
 
     // ---- slots: rank -> block -> edge -----------------------------------------------------------
@@ -396,11 +395,8 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
 
     // ---- outputs --------------------------------------------------------------------------------
     if (is_last) {
-        const int64_t excl = tile > 0 ? lookback_exclusive(ws, p.err_flag, tile, lane) : 0;
-        if (lane == 0) {
-            __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + wg_total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_tile_base = excl;
-        }
+        const int64_t excl = chain.exclusive(p.err_flag, tile, lane);
+        if (lane == 0) s_tile_base = excl;
     }
     if (p.out_nbr) {
 #pragma unroll
@@ -432,9 +428,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
             if (q == Q - 1) {
                 // The last query's tile has looked back over every other tile.  If any wait ran into its bound the
                 // dense rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
-                __threadfence();
-                const bool bad = __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-                const int64_t tot = bad ? 0 : row + k[u];
+                const int64_t tot = chain.close(p.err_flag) ? 0 : row + k[u];
                 p.rowptr[Q] = tot;
                 if (p.total_out) *p.total_out = tot;
             }
@@ -454,15 +448,12 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
 template <int POLICY, bool INCL, int CH, int ROUNDS>
 hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
     constexpr int64_t kTileQueries = kTileWaves * kTeamsPerWave * CH;
+    static_assert(kTileQueries * ROUNDS * kTeam < (1 << kTagShift), "a tile's total lies below the tag");
     const int64_t grid = (a.Q + kTileQueries - 1) / kTileQueries;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (!a.scan_ready) {
-        // one state more than tiles: the workspace has it, and a test that starts the tickets at 1 uses it
-        const hipError_t e = launch_scan_init(a, grid + 1, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (grid <= 0) return hipGetLastError();
+    if (grid <= 0) return a.scan_ready ? hipGetLastError() : launch_scan_init(a, 1, stream);
     SampleArgs b = a;
+    b.chain_key = new_chain_key();
     if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
     hipLaunchKernelGGL((tns_sample_team_kernel<POLICY, INCL, CH, ROUNDS>), dim3((unsigned)grid), dim3(kTileWaves * kWave), 0, stream, b);
     return hipGetLastError();
@@ -474,7 +465,7 @@ hipError_t launch_team_p(const SampleArgs& a, hipStream_t stream) {
     static_assert(kAllRounds * kTeam >= TNS_MAX_FANOUT, "rounds cover the largest fan-out");
     // Queries per team: one while the batch gives a compute unit no more than one workgroup (16384 queries: 12.5 us
     // against 13.2 with two per team, power-law ids 14.3 / 17.9), two beyond (32768: 15.6 against 18.9, 65536: 23.6 /
-    // 30.7; tickets are taken at 18 ns each, and a tile is then 128 queries).
+    // 30.7, both with tickets).
     const bool one = a.Q <= kComputeUnits * (int64_t)(kTileWaves * kTeamsPerWave);
     if (a.fanout > kTeam) return one ? launch_team_t<POLICY, INCL, 1, kAllRounds>(a, stream) : launch_team_t<POLICY, INCL, 2, kAllRounds>(a, stream);
     return one ? launch_team_t<POLICY, INCL, 1, 1>(a, stream) : launch_team_t<POLICY, INCL, 2, 1>(a, stream);
