@@ -1,5 +1,6 @@
-// gfx950 sampling kernel for the recent policy over the default layout, batches that fill the chip: Algorithm 1 of the
-// paper (section 4.2), the padded write, and the padding removal of section 5 fused in when the dense outputs are wanted.
+// gfx950 sampling kernel for the recent policy, batches that fill the chip, over the default layout, and batches of any size over
+// the prefix layout: Algorithm 1 of the paper (section 4.2), the padded write, and the padding removal of section 5 fused in
+// when the dense outputs are wanted.
 //
 // One query per lane, as in tns_kernels.hip (64 independent chains of dependent reads per wave).  What paces the kernel is
 // the length of a wave's program, not the memory: time stamps in the kernel before this one, for 2^16 queries over each of 256
@@ -20,6 +21,13 @@
 // 688 -> 668 us windowed, 728 -> 713 without, 2^26 6235 -> 6200.)
 // Against the kernel in which every lane wrote its slots' positions itself, after two rounds of searches for all 64 queries:
 // 256 graphs of 2^16 queries, windowed, 1737 -> 1502 us; 2^22 queries over uniform ids 426 -> 372; 2^26 6624 -> 6236.
+// Prefix layout: the lines of a node's prefix are blocks like any other (the node's own line, whose times the lane has, and up to
+// three extension lines indexed by the fences), and up to three blocks outside the prefix are read from the directory beside
+// them.  The kernel before, in which the lines' requests were served by ten lanes each and every edge was written to a result row
+// in LDS, issued 1900 vector instructions per wave and sent every node with a block outside the prefix on the walk, which held up
+// its whole tile: two hops from 2^20 roots, windowed, dense rows only 533 -> 402 us, 10^6 queries 122 -> 96, 2^22 412 -> 340, 2^26 5990
+// -> 5530, 10^5 25.5 -> 15.  Node lines are read without the non-temporal hint, as the gather comes back for their edges (with it
+// 419, 110 and 6070 us).
 // Nodes with long lists (directory runs) or with deleted edges take the walk of Algorithm 1 lane by lane instead; their
 // row of the table holds one entry per slot.
 #include <algorithm>
@@ -31,6 +39,7 @@
 namespace tns {
 namespace {
 
+constexpr int kPrefixBigBlocks = kInlineBlocks - 1 - kPrefixExtLines;      // blocks outside the prefix that a lane holds like inline ones
 constexpr int kRequestBatch = 8;                                   // search loads in flight: 32 requests
 constexpr int kGroups = kWave / kCoopGroup;                        // requests per search load
 constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes of the packed counts, and their compare bit
@@ -43,7 +52,7 @@ struct SlotHead { uint32_t lo, hi; };
 // Registers: fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
 // positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
 // all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
-template <bool INCL, typename pos_t, int SCAN>
+template <bool PREFIX, bool INCL, typename pos_t, int SCAN>
 __global__ void __launch_bounds__(SCAN ? 1024 : 256, SCAN ? 4 : 6)
 tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
     constexpr bool FUSED = SCAN != kNoScan;
@@ -101,24 +110,27 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     const uint32_t node = ok ? (uint32_t)(inst * p.num_nodes + v) : ~0u;      // the target's entry in the node table (a table of 2^32 lines does not exist)
     tc.settle(p);
     // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
-    uint4 hd = make_uint4(0u, 0u, 0u, 0u);
-    uint4 L[kInlineBlocks];
+    u32x4 P[8];
     {
         // Eight lanes fetch one query's line with one instruction (16 bytes each), eight queries per instruction; the
-        // pieces reach their owner through LDS.  One request per line lets the loads carry the non-temporal hint: a
-        // node line is used once and should not push edge lines out of the L2.
+        // pieces reach their owner through LDS.  (In the prefix layout the gather comes back to the line.)
         const int piece = lane & 7, sub = lane >> 3;
-        const unsigned char* const table = reinterpret_cast<const unsigned char*>(p.nodes) + piece * 16;
+        const unsigned char* const table = (PREFIX ? reinterpret_cast<const unsigned char*>(p.edges) : reinterpret_cast<const unsigned char*>(p.nodes)) + piece * 16;
         uint32_t src[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) src[i] = (uint32_t)__shfl((int)node, i * 8 + sub, kWave);
         u32x4 R[8];
+        // (a query without a node reads the first line and drops it: no load sits in a branch)
+        auto line_of = [&](int i) { return reinterpret_cast<const u32x4*>(table + (uint64_t)(src[i] == ~0u ? 0u : src[i]) * 128u); };
+        if (PREFIX) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)       // (a query without a node reads the first line and drops it: no load sits in a branch)
-            R[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(table + (uint64_t)(src[i] == ~0u ? 0u : src[i]) * 128u));
+            for (int i = 0; i < 8; ++i) R[i] = *line_of(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) R[i] = __builtin_nontemporal_load(line_of(i));
+        }
         // in two rounds of 32 queries; 16-byte pieces are swizzled by the query number so that neither the writes nor
         // the reads collide on banks
-        u32x4 P[8];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
 #pragma unroll
@@ -134,31 +146,98 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
             }
             wave_lds_sync();
         }
-        if (node != ~0u) hd = make_uint4(P[0].x, P[0].y, P[0].z, P[0].w);
-#pragma unroll
-        for (int j = 0; j < kInlineBlocks; ++j) L[j] = make_uint4(P[1 + j].x, P[1 + j].y, P[1 + j].z, P[1 + j].w);
     }
     auto before_end = [&](float t) { return INCL ? t <= w.te : t < w.te; };
-    const int32_t nb = (hd.w & 1) ? 0 : (int32_t)hd.x;              // deleted node: no blocks
-    const bool flat = nb <= kInlineBlocks && !(hd.w & 2);
-    // ---- blocks: inline list without deleted edges -----------------------------------------------------
+    // ---- blocks: short lists without deleted edges ------------------------------------------------------
     // At most one block contains the window's end and at most one its start; the others count as a whole or not at all.
-    // Of those two the first and the last edge are known to lie on different sides, the slots between are searched.
-    int32_t cnt[kInlineBlocks];        // candidates
+    // Of those two the slots on whose side something is known already are not searched.
+    int32_t cnt[kInlineBlocks];        // candidates, newest block first
     pos_t end_slot[kInlineBlocks];     // slot behind the newest one
     int32_t end_block = -1, start_block = -1, b_lo = 0, b_n = 0;
     int32_t newer = 0, whole = 0;      // edges of the blocks newer than the one with the start that count as a whole
     int64_t b_off = 0;
-#pragma unroll
-    for (int j = 0; j < kInlineBlocks; ++j) {
-        const BlockRec r = as_rec(L[j]);
-        const bool in = flat && j < nb && before_end(r.t_min) && !(w.tb > r.t_max);
-        const int32_t size = rec_size(r);
+    // block j; t_max: a time that no edge of it is after; undecided: slots to search where a time lies inside
+    // the block (its first edge is known to be on the near side)
+    auto block = [&](int j, bool there, float t_min, float t_max, int64_t off, int32_t size, int32_t undecided) {
+        const bool in = there && before_end(t_min) && !(w.tb > t_max);
         cnt[j] = in ? size : 0;
-        end_slot[j] = (pos_t)(rec_off(r) + size);
-        if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_lo = 1; w.d_n = size - 2; end_block = j; }
-        if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; newer = whole; }
-        whole += in && before_end(r.t_max) ? size : 0;
+        end_slot[j] = (pos_t)(off + size);
+        if (in && !before_end(t_max)) { w.d_off = off; w.d_lo = 1; w.d_n = undecided; end_block = j; }
+        if (in && w.tb > t_min) { b_off = off; b_lo = 1; b_n = undecided; start_block = j; newer = whole; }
+        whole += in && before_end(t_max) ? size : 0;
+    };
+    bool flat;
+    int32_t nb = 0;                    // list length (default layout); blocks outside the prefix
+    uint32_t dir_line;
+    if constexpr (!PREFIX) {
+        uint4 hd = make_uint4(0u, 0u, 0u, 0u);
+        uint4 L[kInlineBlocks];
+#pragma unroll
+        for (int j = 0; j < kInlineBlocks; ++j) L[j] = make_uint4(P[1 + j].x, P[1 + j].y, P[1 + j].z, P[1 + j].w);
+        if (node != ~0u) hd = make_uint4(P[0].x, P[0].y, P[0].z, P[0].w);
+        nb = (hd.w & 1) ? 0 : (int32_t)hd.x;                           // deleted node: no blocks
+        dir_line = hd.z;
+        flat = nb <= kInlineBlocks && !(hd.w & 2);
+#pragma unroll
+        for (int j = 0; j < kInlineBlocks; ++j) {
+            const BlockRec r = as_rec(L[j]);
+            const bool in = flat && j < nb && before_end(r.t_min) && !(w.tb > r.t_max);
+            const int32_t size = rec_size(r);
+            cnt[j] = in ? size : 0;
+            end_slot[j] = (pos_t)(rec_off(r) + size);
+            // (of a block's slots, the first and the last one lie on different sides of a time inside it)
+            if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_lo = 1; w.d_n = size - 2; end_block = j; }
+            if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; newer = whole; }
+            whole += in && before_end(r.t_max) ? size : 0;
+        }
+    } else {
+        // Up to three blocks outside the prefix, newest first, then the extension lines and the node's own line as blocks: their
+        // time index is the fences, so that a line's latest time is only known not to be after the next fence.
+        const int32_t degree = (int32_t)P[6].x;
+        const uint32_t meta = P[6].y;
+        const bool alive = node != ~0u && !(meta & 1u) && degree > 0;
+        nb = alive ? pmeta_big_blocks(meta) : 0;
+        dir_line = P[7].w;
+        flat = nb <= kPrefixBigBlocks && !(alive && (meta & 2u));
+        const int32_t fill = alive && flat ? min(degree, pmeta_prefix_slots(meta)) : 0;       // edges stored in the prefix
+        const float fence[kPrefixExtLines + 1] = {__uint_as_float(P[7].x), __uint_as_float(P[7].y), __uint_as_float(P[7].z), INFINITY};
+        float after = INFINITY;        // the oldest block outside the prefix
+        if (__ballot(nb > 0)) {
+            const bool read = flat && nb > 0 && (int64_t)dir_line * kDirAlign + nb <= p.num_dir;
+            BlockRec big[kPrefixBigBlocks];
+#pragma unroll
+            for (int j = 0; j < kPrefixBigBlocks; ++j) {
+                big[j] = BlockRec{};
+                if (read && j < nb) big[j] = p.dir[(int64_t)dir_line * kDirAlign + (nb - 1 - j)];
+            }
+#pragma unroll
+            for (int j = 0; j < kPrefixBigBlocks; ++j) {
+                const bool there = read && j < nb;
+                if (there) after = big[j].t_min;
+                block(j, there, big[j].t_min, big[j].t_max, rec_off(big[j]), rec_size(big[j]), rec_size(big[j]) - 2);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPrefixBigBlocks; ++j) { cnt[j] = 0; end_slot[j] = 0; }
+        }
+#pragma unroll
+        for (int x = kPrefixExtLines - 1; x >= 0; --x) {
+            const int32_t size = min(fill - kInlineSlots - kSlotsPerLine * x, kSlotsPerLine);
+            const float next = x + 1 < kPrefixExtLines && size == kSlotsPerLine && fill > kInlineSlots + kSlotsPerLine * (x + 1) ? fence[x + 1] : after;
+            const uint32_t line = x == 0 ? P[6].z : P[6].w + (uint32_t)(x - 1);
+            block(kInlineBlocks - 2 - x, size > 0, fence[x], next, (int64_t)line * kSlotsPerLine, size, size - 1);
+        }
+        // the node's own line: its times are here
+        const float own[kInlineSlots] = {__uint_as_float(P[0].x), __uint_as_float(P[0].w), __uint_as_float(P[1].z), __uint_as_float(P[2].y),
+                                         __uint_as_float(P[3].x), __uint_as_float(P[3].w), __uint_as_float(P[4].z), __uint_as_float(P[5].y)};
+        int32_t before = 0, early = 0;
+#pragma unroll
+        for (int i = 0; i < kInlineSlots; ++i) {
+            before += i < fill && before_end(own[i]) ? 1 : 0;
+            early += i < fill && own[i] < w.tb ? 1 : 0;
+        }
+        cnt[kInlineBlocks - 1] = max(before - early, 0);
+        end_slot[kInlineBlocks - 1] = (pos_t)((int64_t)node * kSlotsPerLine + before);
     }
     // Where the newer blocks fill the slots, the one with the start is not searched; the walk of Algorithm 1 does not come to it
     // either.  (2^20 queries over power-law ids, window of a quarter of the time span, fan-out 20, padded rows only: edge data on the
@@ -168,14 +247,38 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     };
     if (!flat) {
         // ---- long lists, nodes with deleted edges: Algorithm 1 block by block --------------------------
-        if (nb <= kInlineBlocks) {
+        if (PREFIX) {
+            // the blocks outside the prefix, then the prefix line by line
+            const uint32_t* __restrict__ own = p.edges + (uint64_t)node * 32u;
+            const uint32_t meta = own[kNodeHdrWord + 1];
+            const int32_t fill = min((int32_t)own[kNodeHdrWord], pmeta_prefix_slots(meta));
+            const int64_t d0 = (int64_t)dir_line * kDirAlign;
+            const BlockRec* __restrict__ d = p.dir + d0;
+            const bool dir_ok = nb > 0 && d0 + nb <= p.num_dir;
+            int32_t lo = 0, n = dir_ok ? nb : 0, t = 0;
+            narrow2(lo, n, 0, [&](int32_t i) { return before_end(d[i].t_min); });
+            bool go = true;
+#pragma unroll 1
+            for (int32_t j = lo - 1; j >= 0 && go; --j, ++t) go = w.step(d[j], t);
+            float after = dir_ok ? d[0].t_min : INFINITY;
+#pragma unroll 1
+            for (int32_t x = kPrefixExtLines - 1; x >= -1 && go; --x) {
+                // extension line x, or the node's own line
+                const int32_t first = x < 0 ? 0 : kInlineSlots + kSlotsPerLine * x, size = min(fill - first, x < 0 ? kInlineSlots : kSlotsPerLine);
+                if (size <= 0) continue;
+                const float t_min = __uint_as_float(x < 0 ? own[0] : own[kNodeHdrWord + 4 + x]);
+                const uint32_t line = x < 0 ? node : (x == 0 ? own[kNodeHdrWord + 2] : own[kNodeHdrWord + 3] + (uint32_t)(x - 1));
+                go = w.step(make_rec(t_min, after, (int64_t)line * kSlotsPerLine, size, (meta & 2u) != 0), t++);
+                after = t_min;
+            }
+        } else if (nb <= kInlineBlocks) {
             bool go = true;
 #pragma unroll 1
             for (int32_t j = 0; j < nb && go; ++j) go = w.step(p.nodes[node].rec[j], j);
         } else {
             // all records of the node, oldest first, in one run of the directory; the newest block that starts before the
             // window end is searched for instead of stepping through the newer ones one by one
-            const int64_t d0 = (int64_t)hd.z * kDirAlign;
+            const int64_t d0 = (int64_t)dir_line * kDirAlign;
             if (d0 + nb <= p.num_dir) {
                 const BlockRec* __restrict__ d = p.dir + d0;
                 int32_t lo = 0, n = nb;
@@ -328,7 +431,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
 }
 
-template <bool INCL, typename pos_t, bool FUSED>
+template <bool PREFIX, bool INCL, typename pos_t, bool FUSED>
 hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     const int32_t stride = std::max(a.fanout, kInlineBlocks) | 1;                // odd: conflict-free per-lane rows
     // per wave: the table, the requests and their results; at least the 4 KiB in which the node lines are staged first
@@ -355,7 +458,7 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = chunk * waves;
     auto launch = [&](auto scan, const SampleArgs& b) {
-        hipLaunchKernelGGL((tns_sample_recent_kernel<INCL, pos_t, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b,
+        hipLaunchKernelGGL((tns_sample_recent_kernel<PREFIX, INCL, pos_t, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b,
                            stride, slot_multiplier(a.fanout), (uint32_t)chunk);
     };
     return launch_tiles<FUSED>(a, grid, stream, launch);
@@ -365,12 +468,12 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
 
 hipError_t launch_sample_recent(const SampleArgs& a, hipStream_t stream) {
     const bool fused = a.scan_ws != nullptr;
-    if (a.inclusive_end) {
-        if (a.wide_offsets) return fused ? launch_recent_t<true, int64_t, true>(a, stream) : launch_recent_t<true, int64_t, false>(a, stream);
-        return fused ? launch_recent_t<true, int32_t, true>(a, stream) : launch_recent_t<true, int32_t, false>(a, stream);
-    }
-    if (a.wide_offsets) return fused ? launch_recent_t<false, int64_t, true>(a, stream) : launch_recent_t<false, int64_t, false>(a, stream);
-    return fused ? launch_recent_t<false, int32_t, true>(a, stream) : launch_recent_t<false, int32_t, false>(a, stream);
+#define TNS_DISPATCH(PRE, INC)                                                                                                          \
+    (a.wide_offsets ? (fused ? launch_recent_t<PRE, INC, int64_t, true>(a, stream) : launch_recent_t<PRE, INC, int64_t, false>(a, stream)) \
+                    : (fused ? launch_recent_t<PRE, INC, int32_t, true>(a, stream) : launch_recent_t<PRE, INC, int32_t, false>(a, stream)))
+    if (a.prefix_layout) return a.inclusive_end ? TNS_DISPATCH(true, true) : TNS_DISPATCH(true, false);
+    return a.inclusive_end ? TNS_DISPATCH(false, true) : TNS_DISPATCH(false, false);
+#undef TNS_DISPATCH
 }
 
 }  // namespace tns
