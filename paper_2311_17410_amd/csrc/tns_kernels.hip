@@ -115,17 +115,23 @@ tns_sample_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul
     uint4 L[kInlineBlocks];
     if (COOP_NODE) {
         // Eight lanes fetch one query's line with one instruction (16 bytes each), eight queries per
-        // instruction; the pieces reach their owner through LDS.  One request per line lets the loads
-        // carry the non-temporal hint: a node line is used once and should not push edge lines out
-        // of the L2.
+        // instruction; the pieces reach their owner through LDS.
         unsigned char* stage = my_lds;
         const int piece = lane & 7, sub = lane >> 3;
+        int64_t src[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) src[i] = shfl64(nidx, i * 8 + sub);
         u32x4 R[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t src = shfl64(nidx, i * 8 + sub);
-            R[i] = u32x4{0u, 0u, 0u, 0u};
-            if (src >= 0) R[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.nodes + src) + piece);
+        for (int i = 0; i < 8; ++i) R[i] = u32x4{0u, 0u, 0u, 0u};
+        if (p.keep_nodes) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (src[i] >= 0) R[i] = *(reinterpret_cast<const u32x4*>(p.nodes + src[i]) + piece);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (src[i] >= 0) R[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.nodes + src[i]) + piece);
         }
         u32x4 P[8];
         // through LDS in three rounds of 24, 24 and 16 queries (3 KiB of staging); 16-byte pieces are

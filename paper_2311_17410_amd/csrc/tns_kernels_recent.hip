@@ -122,7 +122,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         u32x4 R[8];
         // (a query without a node reads the first line and drops it: no load sits in a branch)
         auto line_of = [&](int i) { return reinterpret_cast<const u32x4*>(table + (uint64_t)(src[i] == ~0u ? 0u : src[i]) * 128u); };
-        if (PREFIX) {
+        if (PREFIX || p.keep_nodes) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) R[i] = *line_of(i);
         } else {
