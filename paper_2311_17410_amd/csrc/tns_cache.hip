@@ -173,27 +173,40 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
 // The slot comes from the id map directly (the threads of a row read the same two words), so the gather does not
 // wait for the lookup kernel, which records the accesses for the update beside it.  A thread moves kGatherUnroll
 // pieces, one grid width apart: the kernel is a copy, and a copy on this machine is bound by how much each compute unit has
-// in flight.  As compiled, seven pieces run each dependent step (id, slot, row) together, the first one's three reads
-// follow in the branch of its store, and every store waits for its own row: 4.1 TB/s for 2^20 rows of 172 floats, where the
-// library's copy kernels reach 4.3 (a store right behind each load) to 6.1.
+// in flight.  The row of a piece is found by a multiplication; with 64-bit divisions eight pieces took 849 vector
+// instructions and 90 registers (five waves per SIMD), now 233 and 61 (eight).  2^20 rows of 172 floats: Zipf ids 353 -> 342 us,
+// consecutive rows 281 -> 272, any of 2^24 rows 380 -> 370: of what a copy reaches, the rest is rows that begin and end inside
+// lines and lie anywhere.
 constexpr int kGatherUnroll = 8;
-// idx_t: a type that holds the number of pieces
-template <int VEC, int THREADS, typename idx_t>
+
+// Row of piece t where a row has `per_row` of them, for t < 2^31: floor(t / per_row) = t * mul >> shift, with mul =
+// ceil(2^shift / per_row) and 2^(shift - 31) >= per_row, so that the product's error stays below 1 / per_row.
+struct RowOf {
+    uint32_t mul, shift, per_row;
+    __device__ __forceinline__ uint32_t operator()(uint32_t t) const { return (uint32_t)(((uint64_t)t * mul) >> shift); }
+};
+RowOf row_of(int32_t per_row) {
+    uint32_t s = 0;
+    while ((int64_t(1) << s) < per_row) ++s;
+    const uint64_t p = uint64_t(1) << (31 + s);
+    return RowOf{(uint32_t)((p + (uint64_t)per_row - 1) / (uint64_t)per_row), 31 + s, (uint32_t)per_row};
+}
+constexpr int64_t kGatherPieces = int64_t(1) << 31;       // of one launch
+
+template <int VEC, int THREADS>
 __device__ __forceinline__ void gather_body(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
-                                            int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
-                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, int64_t bid, int64_t nb) {
-    const int32_t per_row = dim / VEC;
-    const int64_t total = B * per_row;
-    const int64_t stride = nb * THREADS;
-    const int64_t t0 = bid * THREADS + threadIdx.x;
-    int64_t b[kGatherUnroll];
-    int32_t col[kGatherUnroll], id[kGatherUnroll], s[kGatherUnroll];
+                                            uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
+                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid, uint32_t nb) {
+    const uint32_t stride = nb * THREADS;
+    const uint32_t t0 = bid * THREADS + threadIdx.x;
+    uint32_t col[kGatherUnroll];
+    int32_t id[kGatherUnroll], s[kGatherUnroll];
 #pragma unroll
     for (int u = 0; u < kGatherUnroll; ++u) {
-        const idx_t t = (idx_t)min(t0 + (int64_t)u * stride, total - 1);      // clamped: no load sits in a branch
-        b[u] = (int64_t)(t / (idx_t)per_row);
-        col[u] = (int32_t)(t - (idx_t)b[u] * (idx_t)per_row) * VEC;
-        id[u] = ids[b[u]];
+        const uint32_t t = min(t0 + (uint32_t)u * stride, total - 1);      // clamped: no load sits in a branch
+        const uint32_t b = row(t);
+        col[u] = (t - b * row.per_row) * VEC;
+        id[u] = ids[b];
     }
 #pragma unroll
     for (int u = 0; u < kGatherUnroll; ++u) {
@@ -206,20 +219,33 @@ __device__ __forceinline__ void gather_body(const float* __restrict__ rows, cons
     vec_t v[kGatherUnroll];
 #pragma unroll
     for (int u = 0; u < kGatherUnroll; ++u) {
-        const float* src = s[u] >= 0 ? rows + (int64_t)s[u] * dim + col[u] : store + (int64_t)(s[u] == -1 ? id[u] : 0) * dim + col[u];
-        v[u] = *reinterpret_cast<const vec_t*>(src);
-        if (s[u] == -2) v[u] = vec_t(0.f);
+        const float* const from = s[u] >= 0 ? rows : store;
+        const uint32_t r = s[u] >= 0 ? (uint32_t)s[u] : (s[u] == -1 ? (uint32_t)id[u] : 0u);
+        v[u] = *reinterpret_cast<const vec_t*>(from + ((uint64_t)r * (uint32_t)dim + col[u]));
     }
+    // Every row piece has arrived before the first store is issued (what a copy reaches in the two orders: tns_probe.hip).
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u)
-        if (t0 + (int64_t)u * stride < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out + b[u] * dim + col[u]));
+    for (int u = 0; u < kGatherUnroll; ++u) {
+        float x = v[u][0];
+        asm volatile("" : "+v"(x));         // (the compiler would otherwise move the first load into the branch of its store)
+        v[u][0] = x;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0) only
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kGatherUnroll; ++u) {
+        const uint32_t t = t0 + (uint32_t)u * stride;
+        if (s[u] == -2) v[u] = vec_t(0.f);
+        if (t < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out) + t);
+    }
 }
 
 template <int VEC>
 __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
-                                                int64_t B, int64_t num_ids, const int32_t* __restrict__ ids,
+                                                uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
                                                 const int32_t* __restrict__ slot_of, float* __restrict__ out) {
-    gather_body<VEC, 256, int64_t>(rows, store, dim, B, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
+    gather_body<VEC, 256>(rows, store, dim, total, row, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
 }
 
 // ---- compaction of flagged elements in three launches -------------------------------------------
@@ -747,11 +773,11 @@ __global__ void k_fifo_advance(int64_t capacity, int64_t* ring, Ctl* ctl) { fifo
 template <bool SELECT, int GATHER>
 __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const NewIds f, int64_t B, int64_t tiles, tns::ScanWorkspace* chain,
                                                       int32_t* __restrict__ victims, const float* __restrict__ store, int32_t dim,
-                                                      int64_t num_ids, float* __restrict__ out) {
+                                                      uint32_t pieces, const RowOf row, int64_t num_ids, float* __restrict__ out) {
     __shared__ uint32_t s_ticket;
     if ((int64_t)blockIdx.x >= tiles) {
-        gather_body<GATHER, kOneGroup, uint32_t>(c.rows, store, dim, B, num_ids, f.ids, c.slot_of, out, (int64_t)blockIdx.x - tiles,
-                                                 (int64_t)gridDim.x - tiles);
+        gather_body<GATHER, kOneGroup>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out, blockIdx.x - (uint32_t)tiles,
+                                       gridDim.x - (uint32_t)tiles);
         return;
     }
     // tiles are numbered in the order workgroups start, so that a tile only waits for tiles that have started
@@ -770,41 +796,60 @@ __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const 
     }
 }
 
-// one wave per replaced entry: maps, score, row copy from the backing store
+// One wave per replaced entry: maps, score, row copy from the backing store.  What bounds it is the chain of dependent reads,
+// so the entry's slot and id are requested beside the number of entries, and its row, in pieces of VEC floats, before anything
+// is stored (a load behind stores is only waited for together with them).  Fetch of 66600 rows of 172 floats 33.1 -> 31.9 us.
+template <int VEC>
 __device__ __forceinline__ void insert_body(const CacheState& c, int policy, int32_t dim, const float* __restrict__ store,
                                             const int32_t* __restrict__ new_ids, const int32_t* __restrict__ victims, const Ctl* ctl,
-                                            int64_t bid) {
+                                            int64_t bid, int32_t max_replace) {
+    typedef float vec_t __attribute__((ext_vector_type(VEC)));
+    constexpr int kAhead = 16 / VEC;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t i = bid * 4 + (threadIdx.x >> 6);
-    // (the scalars are read before the first store: a load behind stores is only waited for together with them)
-    const int32_t m = ctl->m, now = ctl->now;
+    const int64_t i = bid * 4 + (threadIdx.x >> 6), at = min(i, (int64_t)max_replace - 1);
+    const int32_t m = ctl->m, now = ctl->now, id = new_ids[at];
+    const int32_t s = policy == TNS_CACHE_FIFO ? fifo_slot(ctl->ring, at, c.capacity) : victims[at];
     if (i >= m) return;
-    const int32_t s = policy == TNS_CACHE_FIFO ? fifo_slot(ctl->ring, i, c.capacity) : victims[i], id = new_ids[i];
-    if (lane == 0) {
-        const int32_t old = c.id_of[s];
-        if (old >= 0) c.slot_of[old] = -1;
-        c.id_of[s] = id;
-        c.slot_of[id] = s;
-        c.score[s] = policy == TNS_CACHE_LFU ? 1 : now;
-        if (i == 0) atomicAdd(&c.counters[2], (unsigned long long)m);
+    const int32_t pieces = dim / VEC;
+    const vec_t* __restrict__ src = reinterpret_cast<const vec_t*>(store + (int64_t)id * dim);
+    vec_t* __restrict__ dst = reinterpret_cast<vec_t*>(c.rows + (int64_t)s * dim);
+    const int32_t old = c.id_of[s];
+    for (int32_t k0 = 0; k0 < pieces; k0 += kAhead * kWave) {
+        vec_t v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (k0 + u * kWave >= pieces) break;             // uniform
+            v[u] = src[min(k0 + u * kWave + lane, pieces - 1)];
+        }
+        if (k0 == 0 && lane == 0) {
+            if (old >= 0) c.slot_of[old] = -1;
+            c.id_of[s] = id;
+            c.slot_of[id] = s;
+            c.score[s] = policy == TNS_CACHE_LFU ? 1 : now;
+            if (i == 0) atomicAdd(&c.counters[2], (unsigned long long)m);
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (k0 + u * kWave >= pieces) break;
+            if (k0 + u * kWave + lane < pieces) dst[k0 + u * kWave + lane] = v[u];
+        }
     }
-    const float* __restrict__ src = store + (int64_t)id * dim;
-    float* __restrict__ dst = c.rows + (int64_t)s * dim;
-    for (int32_t k = lane; k < dim; k += kWave) dst[k] = src[k];
 }
 
 // The insertion (workgroups [0, insert_blocks)) and the clearing of the batch's first-occurrence marks (the rest),
 // which touch different arrays, in one launch at the end of the fetch.
+template <int VEC>
 __global__ void __launch_bounds__(256) k_insert_clear(CacheState c, int policy, int32_t dim, const float* __restrict__ store,
                                                       const int32_t* __restrict__ new_ids, const int32_t* __restrict__ victims,
-                                                      const Ctl* ctl, int64_t insert_blocks, int64_t B,
+                                                      const Ctl* ctl, int64_t insert_blocks, int32_t max_replace, int64_t B,
                                                       const int32_t* __restrict__ ids, const int32_t* __restrict__ slots) {
     if ((int64_t)blockIdx.x < insert_blocks) {
-        insert_body(c, policy, dim, store, new_ids, victims, ctl, blockIdx.x);
+        insert_body<VEC>(c, policy, dim, store, new_ids, victims, ctl, blockIdx.x, max_replace);
     } else {
-        const int64_t b = ((int64_t)blockIdx.x - insert_blocks) * 256 + threadIdx.x;
+        const int64_t b = ((int64_t)blockIdx.x - insert_blocks) * 256 + threadIdx.x, at = min(b, B - 1);
+        const int32_t slot = slots[at], id = ids[at];
         if (b == 0) *c.updates = ctl->now;
-        if (b < B && slots[b] == -1) c.first_idx[ids[b]] = kNoIndex;
+        if (b < B && slot == -1) c.first_idx[id] = kNoIndex;
     }
 }
 
@@ -951,7 +996,9 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
     // lookup proper (hit flags, counters, recorded accesses, first occurrence of every missed id), distinct misses, scores,
     // victims.  Both only read the maps and rows; the insertion changes them and waits for both.
     const bool vec4 = dim % 4 == 0 && ((reinterpret_cast<uintptr_t>(store) | reinterpret_cast<uintptr_t>(d_out)) & 15) == 0;
-    const int64_t pieces = B * (dim / (vec4 ? 4 : 1));
+    const int32_t per_row = dim / (vec4 ? 4 : 1);
+    const int64_t pieces = B * per_row;
+    const RowOf row = row_of(per_row);
     // One launch for all but the lookup and the insertion, on the caller's stream; see kGatherWithin.
     const bool one_launch = (policy == TNS_CACHE_FIFO || C <= kOneGroupEntries) && pieces <= kGatherWithin && B <= kOneLaunchIds;
     const int64_t tiles_b = (B + kScanTile - 1) / kScanTile;
@@ -962,9 +1009,17 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
         hipError_t ef = hipEventRecord(cache->forked, stream);
         if (ef == hipSuccess) ef = hipStreamWaitEvent(us, cache->forked, 0);
         if (ef != hipSuccess) return fail_hip(ef, "forking the cache update");
-        const dim3 grid(blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll));
-        auto gather = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, st.rows, store, dim, B, N, d_ids, st.slot_of, d_out); };
-        vec4 ? gather(k_gather<4>) : gather(k_gather<1>);
+        // (a launch numbers its pieces with 31 bits, and has a whole number of rows)
+        const int64_t step = kGatherPieces / per_row;
+        for (int64_t b0 = 0; b0 < B; b0 += step) {
+            const int64_t n = std::min(step, B - b0) * per_row;
+            const dim3 grid(blocks_for((n + kGatherUnroll - 1) / kGatherUnroll));
+            auto gather = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, st.rows, store, dim, (uint32_t)n, row, N, d_ids + b0, st.slot_of,
+                                   d_out + b0 * dim);
+            };
+            vec4 ? gather(k_gather<4>) : gather(k_gather<1>);
+        }
     }
     hipLaunchKernelGGL(k_lookup, dim3((unsigned)tiles_b), dim3(256), 0, us, st, policy, N, B, d_ids, w.slots, d_hit, w.ctl,
                        one_launch ? w.chain : nullptr, cache->first_ticket);
@@ -972,7 +1027,7 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
         const int64_t gather_blocks = blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll, kOneGroup);
         auto update = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_b + gather_blocks)), dim3(kOneGroup), 0, us, st, nf, B, tiles_b, w.chain, w.victims,
-                               store, dim, N, d_out);
+                               store, dim, (uint32_t)pieces, row, N, d_out);
         };
         if (policy == TNS_CACHE_FIFO) vec4 ? update(k_update<false, 4>) : update(k_update<false, 1>);
         else vec4 ? update(k_update<true, 4>) : update(k_update<true, 1>);
@@ -1013,8 +1068,11 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
     // the insertion, and the clearing of this batch's first-occurrence marks for the next one, in one launch
     {
         const int64_t ib = maxrep > 0 ? (int64_t)blocks_for(maxrep, 4) : 0;
-        hipLaunchKernelGGL(k_insert_clear, dim3((unsigned)(ib + blocks_for(B))), dim3(256), 0, stream, st, policy, dim, store, w.new_ids,
-                           w.victims, w.ctl, ib, B, d_ids, w.slots);
+        auto insert = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(ib + blocks_for(B))), dim3(256), 0, stream, st, policy, dim, store, w.new_ids, w.victims,
+                               w.ctl, ib, maxrep, B, d_ids, w.slots);
+        };
+        dim % 4 == 0 && (reinterpret_cast<uintptr_t>(store) & 15) == 0 ? insert(k_insert_clear<4>) : insert(k_insert_clear<1>);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e, "launching the cache kernels");

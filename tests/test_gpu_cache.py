@@ -209,3 +209,23 @@ def test_tiles_that_do_not_hear_from_one_another(KB, policy):
     sizes = (1, 1024, 1025, 2048, 5000, 70_001)
     gpu, *_ = run_sequence(KB, policy, n, cap, 5, 0.5, [rng.integers(0, n, b) for b in sizes], 9, prepare=lambda c: no_wait(c._h))
     gpu.close()
+
+
+@pytest.mark.parametrize("policy", [CO.LRU, CO.LFU, CO.FIFO])
+@pytest.mark.parametrize("dim", [1, 173, 1028, 4100])
+def test_rows_of_every_width_and_updates_that_fall_short(KB, policy, dim):
+    # rows of one piece, of no whole number of 16-byte pieces, and of more than the insertion and the gather hold at once; updates
+    # that replace as many entries as allowed, fewer (most ids cached, or a batch of a few ids repeated), one and none
+    rng = np.random.default_rng(dim + policy)
+    n, cap = 2000, 300
+    sizes = [500, 61, 60, 59, 400, 1, 700]
+    batches = [rng.integers(0, n, b) for b in sizes]
+    batches += [np.concatenate([batches[-1], rng.integers(0, n, k)]) for k in (0, 1, 20)] + [np.repeat(rng.integers(0, n, 7), 40)]
+    run_sequence(KB, policy, n, cap, dim, 0.2, batches, 6)[0].close()
+
+
+@pytest.mark.parametrize("rows", [24384, 24385, 24386, 49000])
+def test_rows_gathered_beside_lookup_and_update(KB, rows):
+    # 43 pieces a row: 2^20 pieces end inside row 24385
+    rng = np.random.default_rng(rows)
+    run_sequence(KB, CO.LRU, 60_000, 2000, 172, 0.2, [rng.zipf(1.1, rows) % 60_000 for _ in range(3)], 8)[0].close()
