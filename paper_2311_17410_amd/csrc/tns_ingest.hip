@@ -308,19 +308,33 @@ __device__ __forceinline__ const BlockRec* tail_of(const IngestArgs& a, const No
     return &a.dir[(int64_t)nd.dir_line * kDirAlign + nd.nblocks - 1];
 }
 
-// What one segment (the batch's edges p0..p1 of one source node, sorted) needs: how many edges the tail block
-// still takes, the new blocks' capacity and number, the edge lines and directory records to reserve.
-// v: the node, first: batch position of its earliest edge, mm: their number.
-__device__ __forceinline__ void plan_segment(const IngestArgs& a, uint32_t v, uint32_t first, int64_t mm, SegPlan& P, int64_t& lines,
-                                             int64_t& dirs, int64_t& blocks, int64_t& slots) {
+// What planning a segment reads of its node: the entry's header and its newest inline record, which lie side by side, the builder
+// state, and the time of the segment's first edge.  All of it is requested at once, so that the plan is two dependent round trips,
+// not four, and k_fast_plan requests it before the segment's length is known.
+struct SegNode {
+    uint4 h, r0;
+    NodeAux ax;
+    float t_first;
+};
+__device__ __forceinline__ void load_segment_node(const IngestArgs& a, uint32_t v, uint32_t first, SegNode& n) {
     if ((uint64_t)v >= (uint64_t)a.num_nodes) return;      // out-of-range ids were reported with the keys
     const int64_t nidx = a.node_base + v;
-    // the node entry's header and its newest inline record lie side by side: both are requested at once, with the
-    // builder state and the segment's first timestamp, so that the plan is two dependent round trips, not four
-    const uint4 h = *reinterpret_cast<const uint4*>(&a.nodes[nidx]);
-    const uint4 r0 = *(reinterpret_cast<const uint4*>(&a.nodes[nidx]) + 1);
-    const NodeAux ax = a.aux[nidx];
-    const float t_first = a.ts[first];
+    n.h = *reinterpret_cast<const uint4*>(&a.nodes[nidx]);
+    n.r0 = *(reinterpret_cast<const uint4*>(&a.nodes[nidx]) + 1);
+    n.ax = a.aux[nidx];
+    n.t_first = a.ts[first];
+}
+
+// What one segment (the batch's edges p0..p1 of one source node, sorted) needs: how many edges the tail block
+// still takes, the new blocks' capacity and number, the edge lines and directory records to reserve.
+// v: the node, mm: the number of edges.
+__device__ __forceinline__ void plan_segment(const IngestArgs& a, uint32_t v, const SegNode& n, int64_t mm, SegPlan& P, int64_t& lines,
+                                             int64_t& dirs, int64_t& blocks, int64_t& slots) {
+    if ((uint64_t)v >= (uint64_t)a.num_nodes) return;
+    const int64_t nidx = a.node_base + v;
+    const uint4 h = n.h, r0 = n.r0;
+    const NodeAux ax = n.ax;
+    const float t_first = n.t_first;
     NodeLine nd;
     nd.nblocks = (int32_t)h.x; nd.degree = (int32_t)h.y; nd.dir_line = h.z;
     int64_t room = 0;
@@ -392,7 +406,9 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
         if (s < a.status->num_segments) {
             SegPlan P{};
             const int32_t p0 = seg_start[s];
-            plan_segment(a, (uint32_t)(key[p0] >> 32), val[p0], seg_start[s + 1] - p0, P, lines, dirs, blocks, slots);
+            SegNode n{};
+            load_segment_node(a, (uint32_t)(key[p0] >> 32), val[p0], n);
+            plan_segment(a, (uint32_t)(key[p0] >> 32), n, seg_start[s + 1] - p0, P, lines, dirs, blocks, slots);
             plan[s] = P;
         }
         need_lines[s] = lines;
@@ -508,9 +524,13 @@ __device__ __forceinline__ void ready_status(IngestStatus* st) {
     st->counter = 0;
 }
 
-// One thread per edge (sorted position): its slot from the segment's plan.
+// One thread per edge (sorted position): what is stored, and its slot from the segment's plan.
+struct EdgeWords { uint32_t ts, nbr, eid; };
+__device__ __forceinline__ EdgeWords load_edge(const IngestArgs& a, uint32_t e) {
+    return EdgeWords{__float_as_uint(a.ts[e]), (uint32_t)a.dst[e], (uint32_t)(a.eid ? a.eid[e] : (int32_t)(a.eid_base + (int64_t)e))};
+}
 template <class Batch>
-__device__ __forceinline__ void apply_edge(const IngestArgs& a, const Batch& b, int64_t p) {
+__device__ __forceinline__ void apply_edge(const IngestArgs& a, const Batch& b, int64_t p, const EdgeWords& edge) {
     const int64_t s = b.segment(p);
     const SegPlan P = b.plan[s];
     const int64_t r = p - b.seg_start[s];
@@ -523,11 +543,10 @@ __device__ __forceinline__ void apply_edge(const IngestArgs& a, const Batch& b, 
         slot = block_slot(P, a.used_lines + b.lines_base[s], j) + (rr - (int64_t)j * P.cap);
     }
     if (slot / kSlotsPerLine >= a.cap_lines) { atomicOr(&a.status->internal, 4u); return; }
-    const uint32_t e = b.position(p);
     const int64_t w = slot_word(slot);
-    a.lines[w] = __float_as_uint(a.ts[e]);
-    a.lines[w + 1] = (uint32_t)a.dst[e];
-    a.lines[w + 2] = (uint32_t)(a.eid ? a.eid[e] : (int32_t)(a.eid_base + (int64_t)e));
+    a.lines[w] = edge.ts;
+    a.lines[w + 1] = edge.nbr;
+    a.lines[w + 2] = edge.eid;
 }
 
 // Both in one launch: an edge's slot follows from the plan alone, so the two parts do not depend on each other.
@@ -544,7 +563,7 @@ __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const Pl
         const int64_t p = (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x;
         // (the host has read the record or has a copy of it: the next plan needs no launch of its own for it)
         if (p == 0) ready_status(a.status);
-        if (p < a.m) apply_edge(a, b, p);
+        if (p < a.m) apply_edge(a, b, p, load_edge(a, b.position(p)));
     }
 }
 
@@ -573,6 +592,7 @@ constexpr int kFastMaxTiles = 512;
 constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^21 edges
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
 constexpr int kPlanThreads = 512;                       // k_fast_plan: one sorted position per thread, 512 per tile
+constexpr int kPlanResident = 512;                      // of its tiles, two per compute unit
 // Batches planned and applied by one workgroup (k_small_batch).  us per batch with the sampling of its events, with it / with
 // the same in two launches and a bitonic sort, which above this size was slower than the five kernels (3000 edges over
 // 2^18 nodes 73.2 / 51.9 us without the sampling): 600 edges over 2^18 nodes 46 / 56, 2000 over 2^18 57 / 68, 2000 over 2^16
@@ -847,7 +867,8 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
 // edges 6.5 us for the segments and 21 for their plan as two launches with atomics for the totals.  512 positions a tile: 256
 // and 1024 were both slower somewhere (10^4 edges over 2^16 nodes 54 / 56 / 59 us a batch with 256 / 512 / 1024, 2 * 10^5
 // power-law ids 194 / 185 / 184).  32 batches of 10^5 edges, each sampled, into a new store: 3380 -> 2930 us together with
-// the table of tile histograms read four rows side by side (k_fast_scatter).
+// the table of tile histograms read four rows side by side (k_fast_scatter); with the nodes requested before the segments' lengths
+// are known, no tickets up to kPlanResident tiles, and the apply kernel's edges requested beside their segments 2490 -> 2390.
 __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, const uint64_t* __restrict__ key,
                                                             const uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
                                                             int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
@@ -858,11 +879,15 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     __shared__ int32_t s_heads[kWaves], s_end;
     __shared__ int32_t s_start[kPlanThreads + 1];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    if (t == 0) s_tile = (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
+    // tiles are numbered in the order workgroups start or, where the chip holds all of them at once, as the workgroups are (a ticket
+    // is an atomic on one word, 18 ns each)
+    if (t == 0) s_tile = plan_tiles <= kPlanResident ? (int64_t)blockIdx.x : (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
     __syncthreads();
     const int64_t tile = s_tile, p0 = tile * kPlanThreads, p = p0 + t;
     const uint64_t k = p < a.m ? key[p] : 0, before = p > 0 && p < a.m ? key[p - 1] : 0;
     const bool head = p < a.m && (p == 0 || (uint32_t)(k >> 32) != (uint32_t)(before >> 32));
+    SegNode node{};
+    if (head) load_segment_node(a, (uint32_t)(k >> 32), val[p], node);
     if (wave == kWaves - 1) {
         // where the tile's last segment ends: beyond the tile by at most a batch, found 64 positions at a time
         int64_t lo = min(p0 + kPlanThreads, a.m), n = a.m - lo;
@@ -892,7 +917,7 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     __syncthreads();
     SegPlan P{};
     int64_t lines = 0, dirs = 0, blocks = 0, slots = 0;
-    if (head) plan_segment(a, (uint32_t)(k >> 32), val[p], s_start[local + 1] - p, P, lines, dirs, blocks, slots);
+    if (head) plan_segment(a, (uint32_t)(k >> 32), node, s_start[local + 1] - p, P, lines, dirs, blocks, slots);
     // exclusive sums of the scans' values over the workgroup
     int64_t v[kPlanScans] = {((int64_t)(head ? 1 : 0) << 32) | blocks, lines, dirs, slots}, total[kPlanScans];
 #pragma unroll
@@ -985,7 +1010,8 @@ __device__ __forceinline__ void block_exclusive_scan2(int64_t (&v)[2], int64_t (
 // to the host while the store is being changed.  Sorted by (source, arrival) with a stable radix sort, six bits a pass: a
 // wave ranks 128 keys with ballots, and the 64 x 16 counts of a pass are one per thread for its scan.  As a bitonic network of
 // 66 steps the sort took 13.5 of 28 us, and the apply phase was a launch of its own (64 batches of 2000 power-law edges, each
-// sampled, into a new store: 3.80 -> 3.09 ms).
+// sampled, into a new store: 3.80 -> 3.09 ms).  Every thread has two edges and up to two segments; their reads are requested together,
+// before the loops that use them one after the other, and the edges' words while the nodes are changed (the same: 2.86 -> 2.66 ms).
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave, kSmallItems = (int)kSmallBatch / kSmallThreads;
 constexpr int kSmallDigit = 6, kSmallBins = 1 << kSmallDigit;
 struct SmallShared {
@@ -1020,23 +1046,35 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
     SmallShared& sh = *reinterpret_cast<SmallShared*>(s_raw);
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, m = (int)a.m;
     if (t < 2) sh.totals[t] = 0;
-    int32_t touched = 0;
-    // a wave owns kSmallItems * 64 consecutive keys, item by item
+    // a wave owns kSmallItems * 64 consecutive keys, item by item; the items' reads are requested together
     uint64_t k[kSmallItems];
+    int32_t v[kSmallItems], e[kSmallItems], touched[2 * kSmallItems];
+    float ts[kSmallItems], before[kSmallItems];
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+        const int i = min((wave * kSmallItems + j) * kWave + lane, m - 1);
+        v[j] = a.src[i];
+        ts[j] = a.ts[i];
+        before[j] = a.ts[i > 0 ? i - 1 : 0];
+        e[j] = a.eid ? a.eid[i] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+        // brings the node's entry and builder state into the L2 while the keys are sorted
+        const int64_t nidx = a.node_base + ((uint64_t)(uint32_t)v[j] < (uint64_t)a.num_nodes ? v[j] : 0);
+        touched[2 * j] = a.nodes[nidx].nblocks;
+        touched[2 * j + 1] = a.aux[nidx].tail_cap;
+    }
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int i = (wave * kSmallItems + j) * kWave + lane;
         k[j] = ~0ull;                    // beyond the batch: last in every pass
         if (i < m) {
-            const int32_t v = a.src[i];
-            const float ts = a.ts[i], before = a.ts[i > 0 ? i - 1 : 0];
-            if ((uint64_t)(uint32_t)v >= (uint64_t)a.num_nodes) report(a.status, TNS_ERANGE, i);
-            else if (ts != ts) report(a.status, TNS_EORDER, i);
-            else if (a.eid && a.eid[i] < 0) report(a.status, TNS_EINVAL, i);
-            if (i > 0 && before > ts) atomicOr(&a.status->unsorted, 1u);
-            k[j] = ((uint64_t)(uint32_t)v << 32) | (uint32_t)i;
-            // brings the node's entry and builder state into the L2 while the keys are sorted
-            if ((uint64_t)(uint32_t)v < (uint64_t)a.num_nodes) touched |= a.nodes[a.node_base + v].nblocks | a.aux[a.node_base + v].tail_cap;
+            if ((uint64_t)(uint32_t)v[j] >= (uint64_t)a.num_nodes) report(a.status, TNS_ERANGE, i);
+            else if (ts[j] != ts[j]) report(a.status, TNS_EORDER, i);
+            else if (e[j] < 0) report(a.status, TNS_EINVAL, i);
+            if (i > 0 && before[j] > ts[j]) atomicOr(&a.status->unsorted, 1u);
+            k[j] = ((uint64_t)(uint32_t)v[j] << 32) | (uint32_t)i;
         }
     }
 #pragma unroll 1
@@ -1087,7 +1125,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
 #pragma unroll
         for (int j = 0; j < kSmallItems; ++j) k[j] = sh.key[(wave * kSmallItems + j) * kWave + lane];
     }
-    asm volatile("" ::"v"(touched));          // the loads' only use
+#pragma unroll
+    for (int j = 0; j < 2 * kSmallItems; ++j) asm volatile("" ::"v"(touched[j]));          // the loads' only use
     // segments; every item of a wave is 64 consecutive sorted positions
     int h[kSmallItems];
     uint64_t heads[kSmallItems];
@@ -1122,6 +1161,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
     // plans, 1024 segments at a time (a loop, not unrolled: the program is fetched once from a cold instruction cache,
     // and its length is part of what this kernel costs)
     int64_t all[2] = {0, 0}, blocks = 0, slots = 0;
+    SegNode node[kSmallItems] = {};      // requested for all of them first
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j) {
+        const int sgm = t + j * kSmallThreads;
+        if (sgm < nseg) {
+            const uint64_t k0 = sh.key[sh.seg_start[sgm]];
+            load_segment_node(a, (uint32_t)(k0 >> 32), (uint32_t)k0, node[j]);
+        }
+    }
+    static_assert(kSmallItems == 2, "the loop takes the next node's place");
 #pragma unroll 1
     for (int sgm = t; sgm - t < nseg; sgm += kSmallThreads) {
         int64_t need[2] = {0, 0}, tot[2], b = 0, sl = 0;
@@ -1129,7 +1178,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
             const int p0 = sh.seg_start[sgm];
             const uint64_t k0 = sh.key[p0];
             SegPlan P{};
-            plan_segment(a, (uint32_t)(k0 >> 32), (uint32_t)k0, sh.seg_start[sgm + 1] - p0, P, need[0], need[1], b, sl);
+            plan_segment(a, (uint32_t)(k0 >> 32), node[0], sh.seg_start[sgm + 1] - p0, P, need[0], need[1], b, sl);
             sh.plan[sgm] = P;
         }
         blocks += b;
@@ -1141,6 +1190,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
         }
         all[0] += tot[0];
         all[1] += tot[1];
+        node[0] = node[1];
     }
     blocks = wave_sum64(blocks);
     slots = wave_sum64(slots);
@@ -1178,10 +1228,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
     }
     const SmallBatch batch(sh);
     if (go) {
+        EdgeWords edge[kSmallItems] = {};      // on their way while the nodes are changed
+#pragma unroll
+        for (int j = 0; j < kSmallItems; ++j)
+            if (t + j * kSmallThreads < m) edge[j] = load_edge(a, batch.position(t + j * kSmallThreads));
 #pragma unroll 1
         for (int s = t; s < nseg; s += kSmallThreads) apply_node(a, batch, s);
 #pragma unroll 1
-        for (int p = t; p < m; p += kSmallThreads) apply_edge(a, batch, p);
+        for (int p = t; p < m; p += kSmallThreads) {
+            apply_edge(a, batch, p, edge[0]);
+            edge[0] = edge[1];
+        }
     } else {
         // an error, a batch out of order, pools without room: the host decides, and a later launch finds the plan in memory
 #pragma unroll 1

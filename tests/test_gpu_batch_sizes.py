@@ -92,6 +92,35 @@ def test_ingestion_batches_around_the_small_plan(B, oracle_lib, batch, nodes):
     plan.close()
 
 
+@pytest.mark.parametrize("batch", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+def test_ingestion_batches_around_the_plan_without_tickets(B, oracle_lib, batch):
+    # 512 and 513 tiles of sorted positions; a node of a tenth of every batch spans dozens of them
+    import torch
+    rng = np.random.default_rng(batch)
+    n, nodes = 2 * batch, 30_000
+    src = rng.integers(0, nodes, n, dtype=np.int32)
+    src[rng.random(n) < 0.1] = nodes // 2
+    dst = rng.integers(0, nodes, n, dtype=np.int32)
+    ts = np.sort(rng.random(n)).astype(np.float32)
+    plan = B.Plan(nodes, 10, block_threshold=48, flags=B.TNS_FLAG_DEVICE_INGEST)
+    bs = oracle_lib.BlockStore(nodes, 48, 0)
+    d = [torch.from_numpy(a).cuda() for a in (src, dst, ts)]
+    for lo in (0, batch):
+        plan.add_edges_device(*(a[lo:lo + batch] for a in d))
+    bs.add_stream(src, dst, ts, batch)
+    ref, got = bs.stats(), plan.stats()
+    for name in ("num_blocks", "wasted_slots", "max_list_len"):
+        assert got[name] == ref[name], name
+    st = W.Stream(nodes, src, dst, ts, batch)
+    targets, t_start, t_end = W.random_queries(5, st, 3000)
+    targets[:50] = nodes // 2
+    adj = oracle_lib.Adjacency(nodes, src, dst, ts)
+    for tb in (None, t_start):
+        assert_same(gpu_sample(plan, targets, tb, t_end), adj.sample(targets, tb, t_end, 10), oracle_lib, f"start={tb is not None}")
+    adj.close()
+    plan.close()
+
+
 def test_stores_built_one_after_another_by_two_threads(B, oracle_lib):
     # memory of a closed plan is kept for the next one: plans of two threads, each on a stream of its own, of changing
     # sizes, must not see each other's (or an earlier plan's) data
