@@ -216,6 +216,7 @@ struct tns_plan {
     DeviceArray<tns::BlockRec> d_dir;
     DeviceArray<uint32_t> d_dir_cum;            // per directory record: the node's edges in older blocks
     DeviceArray<tns::EdgeLine> d_edges;
+    int32_t defer_spins = tns::kDeferSpins;
     bool committed = false;
     bool deleted_edges = false;                 // some edge has been deleted: blocks with deleted edges are scanned candidate by candidate
 };
@@ -799,6 +800,7 @@ static int fill_sample_args(tns_plan* plan, int64_t Q, const int32_t* d_targets,
     // 2^17 nodes 185 / 180, 2^18 363 / 367, 2^19 722 / 766, 2^20 1439 / 1499.
     a.keep_nodes = plan->cfg.num_nodes <= (int64_t(1) << 17) || a.num_dir * 16 >= plan->cfg.num_nodes * plan->cfg.num_instances ? 1 : 0;
     a.xcd_remap = (plan->cfg.flags & TNS_FLAG_NO_XCD_REMAP) ? 0 : 1;
+    a.defer_spins = plan->defer_spins;
     a.first_ticket = (plan->cfg.flags & TNS_TEST_FLAG_LOST_TILE) ? 1 : 0;
     const int64_t edge_lines = plan->pstore ? plan->d_lines.used : plan->d_edges.used;
     a.wide_offsets = (edge_lines * 32 >= (int64_t(1) << 31) || (plan->cfg.flags & TNS_FLAG_WIDE_POSITIONS)) ? 1 : 0;   // word indices beyond int32
@@ -949,6 +951,8 @@ int tns_workspace_khop(const tns_plan* plan, int32_t num_hops, const int32_t* fa
     *bytes = kStatusBytes + scan + khop_header_bytes(num_hops, plan->cfg.num_instances);
     return TNS_OK;
 }
+
+void tns_test_defer(tns_plan* plan) { plan->defer_spins = 0; }
 
 int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float delta, int64_t Q,
                  const int32_t* d_targets, const float* d_t_start, const float* d_t_end, const int64_t* d_inst_rowptr,

@@ -24,7 +24,8 @@ struct ScanWorkspace {
     uint32_t ticket;
     uint32_t error;
     uint64_t launches;    // tagged chain
-    uint32_t pad[60];
+    uint64_t deferred;    // tagged chain: the tag of a launch in which a tile has left its dense rows to the last one
+    uint32_t pad[58];
     uint64_t status[1];   // [number of tiles]
 };
 
@@ -89,16 +90,21 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
 // workspace that every launch moves on: one in its head and one before the tiles' words.  Two, because a kernel that clears
 // its state overwrites the second (and a caller may clear the head): for the words of an earlier replay to be taken for new
 // ones both would have to be set back and the words kept.  The last tile moves the counters on, when it has heard from every
-// other tile, which has then read them.  Memory that by chance holds the tag of a launch: one word in 2^48.
+// other tile, which has then read them.  Memory that by chance holds the tag of a launch: one word in 2^47.
 //
 // Every tile reads the totals of all tiles before it, four words per lane at a time; there are no prefixes to wait for.  Tiles
-// are numbered as the workgroups are, which start in that order, and the grid is not larger than what the chip holds at once
-// (tagged_queries), so that a tile that waits keeps no earlier one from starting; the wait is bounded all the same.
+// are numbered as the workgroups are, which every XCD starts in that order.  Alone a launch cannot hold itself up, but XCDs
+// start the workgroups of two queues in either order: waiting tiles of two launches could each fill an XCD that the other one's
+// earlier tiles need.  So only the last tile waits for as long as it takes.  Any other one that has waited for kDeferSpins (about
+// two milliseconds, hundreds of times what a tile takes) leaves its dense rows out and makes room, and the last tile's workgroup
+// samples it again when all totals are there.  What waits is then one workgroup per launch.
 // us per call, 2^21 edges, fan-out 10, tickets and clearing launch / this, recent policy, uniform ids: 65537 queries 22.6 /
 // 13.4, 10^5 27.8 / 15.7, 2 * 10^5 37.0 / 25.3, 2^18 - 1 36.9 / 29.2; power-law ids 26.7 / 17.8, 32.5 / 20.5, 40.8 / 28.7, 38.0 / 30.5; uniform
 // policy, power-law ids 38.8 / 32.0, 49.3 / 38.9, 66.8 / 58.0, 77.9 / 66.4; prefix layout, recent 32.4 / 23.5, 37.4 / 25.5, 44.7 /
-// 32.6, 41.2 / 35.5.  Both forms in one kernel, chosen at run time, cost the large batches of the prefix layout 1 to 4 %.
-constexpr int kTagShift = 16;                         // a tile's total is below 2^16
+// 32.6, 41.2 / 35.5 (the second figures without tiles that make room).  Both forms in one kernel, chosen at run time, cost the large batches of the prefix layout 1 to 4 %.
+constexpr int kTotalBits = 16;                        // a tile's total is below 2^16
+constexpr int kTagShift = kTotalBits + 1;             // between them: the tile has left its dense rows to the last one
+constexpr uint64_t kDeferredBit = uint64_t(1) << kTotalBits;
 __host__ __device__ inline uint64_t mix64(uint64_t z) {      // splitmix64's output function
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
@@ -112,6 +118,14 @@ __host__ __device__ inline uint64_t chain_tag(uint64_t key, uint64_t in_head, ui
 struct TaggedChain {
     ScanWorkspace* ws;
     uint64_t in_head, before_tiles, tag;
+    int32_t* s_more;         // LDS: 1 if tiles have left their dense rows to this one, the last
+    bool last_wg;            // the workgroup of the last tile
+    bool again = false;      // which samples other tiles again
+    int64_t last_tile = 0;
+    __device__ __forceinline__ void start(bool is_last_tile, int32_t* more) {
+        last_wg = is_last_tile;
+        s_more = more;
+    }
     __device__ __forceinline__ void request(void* scan_ws) {
         ws = static_cast<ScanWorkspace*>(scan_ws);
         in_head = __hip_atomic_load(&ws->launches, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -125,17 +139,21 @@ struct TaggedChain {
         };
         in_head = uniform(in_head);
         before_tiles = uniform(before_tiles);
-        tag = chain_tag(key, in_head, before_tiles);
+        if (!again) tag = chain_tag(key, in_head, before_tiles);
     }
     __device__ __forceinline__ void publish(int64_t tile, int32_t total) const {
+        if (again) return;
         __hip_atomic_store(&ws->status[tile + 1], tag << kTagShift | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // what an error word holds after a wait of this launch ran out
     __device__ __forceinline__ uint32_t mark() const { return (uint32_t)tag | 1u; }
-    // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.
-    __device__ __forceinline__ int64_t exclusive(uint32_t* err_flag, int64_t tile, int lane) const {
+    // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.  -1: the tile has
+    // waited for long enough and leaves its dense rows to the last one.  It says so before its last look: either that look finds
+    // what was missing, or the last tile, which goes on once nothing is missing, finds the note.
+    __device__ __forceinline__ int64_t exclusive(uint32_t* err_flag, int64_t tile, int lane, int defer_spins) const {
         int64_t sum = 0;
         int spins = 0;
+        bool noted = false;
         for (int64_t t0 = 0; t0 < tile; t0 += 4 * kChainWave) {
             uint64_t w[4];
             while (true) {
@@ -149,17 +167,28 @@ struct TaggedChain {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ready = ready && w[i] >> kTagShift == tag;
                 if (!__ballot(!ready)) break;
+                if (noted) return -1;
                 if (++spins > kSpinLimit) {
                     if (lane == 0) atomicExch(err_flag, mark());
                     __threadfence();
                     return 0;
+                }
+                if (!last_wg && spins > defer_spins) {
+                    if (lane == 0) {
+                        __hip_atomic_fetch_or(&ws->status[tile + 1], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __threadfence();
+                        __hip_atomic_store(&ws->deferred, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    __threadfence();
+                    noted = true;
+                    continue;
                 }
                 if (spins < 16) __builtin_amdgcn_s_sleep(2);
                 else __builtin_amdgcn_s_sleep(16);
             }
             int64_t v = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & ((1ull << kTagShift) - 1ull));
+            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & (kDeferredBit - 1ull));
             sum += v;
         }
         for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kChainWave);
@@ -169,13 +198,44 @@ struct TaggedChain {
     // An error word that holds anything else is made 0 (it held whatever the workspace did).
     __device__ __forceinline__ bool close(uint32_t* err_flag) const {
         __threadfence();
+        const uint64_t left = __hip_atomic_load(&ws->deferred, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool bad = __hip_atomic_load(err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark();
+        if (left == tag && !bad) *s_more = 1;
         if (!bad) __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ws->launches, in_head + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ws->status[0], before_tiles + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return bad;
     }
+    // After a tile, by the whole workgroup: true if there is another one for it to sample, again and now with its dense rows.
+    __device__ __forceinline__ bool next(int64_t& tile, int32_t* s_arrived, int lane) {
+        if (!last_wg) return false;
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(*s_more)) return false;
+        const int64_t last = again ? last_tile : tile;
+        int64_t t0 = again ? tile + 1 : 0;
+        uint64_t found = 0;
+        for (; t0 < last; t0 += kChainWave) {
+            uint64_t w = 0;
+            if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            found = __ballot(w >> kTagShift == tag && (w & kDeferredBit));
+            if (found) break;
+        }
+        if (!found) return false;
+        last_tile = last;
+        again = true;
+        tile = t0 + __builtin_ctzll(found);
+        if (threadIdx.x == 0) *s_arrived = 0;
+        __syncthreads();
+        return true;
+    }
 };
+
+// At the start of every tile of a workgroup that may have several: nothing that follows from these is worth a register between them.
+__device__ __forceinline__ void new_tile(int& lane, int& wave) {
+    asm volatile("" : "+v"(lane), "+v"(wave));
+    lane &= kChainWave - 1;
+    wave &= 15;
+}
 
 }  // namespace
 }  // namespace tns

@@ -432,6 +432,14 @@ __device__ __forceinline__ void store_dense(const GatherRegs& g, const SampleArg
 
 // ---- a workgroup's tile and the padding removal fused into sampling --------------------------------------
 
+// The kernel's first argument, for a tile of a workgroup that may have several: what is read through this is read anew for every tile.
+// (As ordinary arguments the loop's invariants fill the scalar registers: 100 to 700 moves to vector registers and back per kernel.)
+__device__ __forceinline__ const SampleArgs& arguments_anew() {
+    auto* p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const SampleArgs*)p;
+}
+
 // How a kernel numbers its tiles and learns the dense entries of the tiles before one.
 enum Scan : int {
     kNoScan,      // padded rows only
@@ -443,11 +451,12 @@ struct TileChain {
     static constexpr bool kTagged = SCAN == kTags;
     TaggedChain tags;
     int64_t tile;
-    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived) {
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t Q, int64_t* s_tile_base, int32_t* s_arrived, int32_t* s_more) {
         if (threadIdx.x == 0) *s_arrived = 0;
         if (kTagged) {
-            tags.request(p.scan_ws);
             tile = (int64_t)blockIdx.x + p.first_ticket;
+            if (threadIdx.x == 0) *s_more = 0;
+            tags.start((tile + 1) * blockDim.x >= Q, s_more);
             __syncthreads();
         } else {
             if (threadIdx.x == 0) *s_tile_base = (int64_t)atomicAdd(&static_cast<ScanWorkspace*>(p.scan_ws)->ticket, 1u);
@@ -455,6 +464,10 @@ struct TileChain {
             tile = wave_uniform(*s_tile_base);
             __syncthreads();
         }
+    }
+    // (for every tile, inside the loop: the compiler waits before a loop for what was requested before it)
+    __device__ __forceinline__ void request(const SampleArgs& p) {
+        if (kTagged) tags.request(p.scan_ws);
     }
     __device__ __forceinline__ void settle(const SampleArgs& p) {
         if (kTagged) tags.settle(p.chain_key);
@@ -466,9 +479,14 @@ struct TileChain {
         if (kTagged) tags.publish(tile, total);
         else if (tile > 0) __hip_atomic_store(&ws(p)->status[tile], kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // one wave: the dense entries of the tiles before this one
+    // by the whole workgroup, after a tile: true if it has another one to sample
+    __device__ __forceinline__ bool next(int32_t* s_arrived, int lane) {
+        if (!kTagged) return false;
+        return tags.next(tile, s_arrived, lane);
+    }
+    // one wave: the dense entries of the tiles before this one; -1 (kTags): the tile writes no dense rows
     __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
-        if (kTagged) return tags.exclusive(p.err_flag, tile, lane);
+        if (kTagged) return tags.exclusive(p.err_flag, tile, lane, p.defer_spins);
         const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane) : 0;
         if (lane == 0)
             __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -485,9 +503,11 @@ struct TileChain {
 template <>
 struct TileChain<kNoScan> {
     int64_t tile;
-    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t*, int32_t*)
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t, int64_t*, int32_t*, int32_t*)
         : tile(p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) {}
+    __device__ __forceinline__ void request(const SampleArgs&) {}
     __device__ __forceinline__ void settle(const SampleArgs&) {}
+    __device__ __forceinline__ bool next(int32_t*, int) const { return false; }
 };
 
 // Output stage of a fused kernel: chained scan over the workgroup tiles for the dense offsets, padded rows, dense rows and
@@ -520,7 +540,8 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
     auto row_of_wave = [&]() {
         int32_t off = 0;
         for (int i = 0; i < wave; ++i) off += s_wave_sum[i];
-        return wave_uniform(*s_tile_base + off);
+        const int64_t base = *s_tile_base;
+        return wave_uniform(Chain::kTagged && base < 0 ? base : base + off);
     };
     GatherRegs g;
     if (f <= kGatherChunk) {
@@ -549,6 +570,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         if (!CHAIN_FIRST && is_last) chain(wg_total);
         lds_barrier();
         const int64_t row0 = row_of_wave();
+        if (Chain::kTagged && row0 < 0) return;
         write_rowptr(row0);
         store_dense(g, p, f_mul, lane, 0, row0, inc - k);
     } else {
@@ -563,11 +585,12 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         }
         __syncthreads();
         const int64_t row0 = row_of_wave();
-        write_rowptr(row0);
+        const bool dense = !Chain::kTagged || row0 >= 0;
+        if (dense) write_rowptr(row0);
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
             load(g, it0);
             store_padded(g, p, lane, it0, q0, Q);
-            store_dense(g, p, f_mul, lane, it0, row0, inc - k);
+            if (dense) store_dense(g, p, f_mul, lane, it0, row0, inc - k);
         }
     }
 }

@@ -592,7 +592,9 @@ constexpr int kFastMaxTiles = 512;
 constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^21 edges
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
 constexpr int kPlanThreads = 512;                       // k_fast_plan: one sorted position per thread, 512 per tile
-constexpr int kPlanResident = 512;                      // of its tiles, two per compute unit
+// Most tiles that go without tickets: a quarter of the two per compute unit that the chip holds at once.  XCDs start the workgroups
+// of two queues in either order, and a process has four hardware queues: launches that fit side by side cannot hold one another up.
+constexpr int kPlanResident = 128;
 // Batches planned and applied by one workgroup (k_small_batch).  us per batch with the sampling of its events, with it / with
 // the same in two launches and a bitonic sort, which above this size was slower than the five kernels (3000 edges over
 // 2^18 nodes 73.2 / 51.9 us without the sampling): 600 edges over 2^18 nodes 46 / 56, 2000 over 2^18 57 / 68, 2000 over 2^16
@@ -868,7 +870,7 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
 // and 1024 were both slower somewhere (10^4 edges over 2^16 nodes 54 / 56 / 59 us a batch with 256 / 512 / 1024, 2 * 10^5
 // power-law ids 194 / 185 / 184).  32 batches of 10^5 edges, each sampled, into a new store: 3380 -> 2930 us together with
 // the table of tile histograms read four rows side by side (k_fast_scatter); with the nodes requested before the segments' lengths
-// are known, no tickets up to kPlanResident tiles, and the apply kernel's edges requested beside their segments 2490 -> 2390.
+// are known and the apply kernel's edges requested beside their segments, 2860 -> 2570 together with the sampling's smaller launches.
 __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, const uint64_t* __restrict__ key,
                                                             const uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
                                                             int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
@@ -879,8 +881,8 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     __shared__ int32_t s_heads[kWaves], s_end;
     __shared__ int32_t s_start[kPlanThreads + 1];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    // tiles are numbered in the order workgroups start or, where the chip holds all of them at once, as the workgroups are (a ticket
-    // is an atomic on one word, 18 ns each)
+    // tiles are numbered in the order workgroups start or, where they are few enough, as the workgroups are (a ticket is an atomic
+    // on one word, 18 ns each)
     if (t == 0) s_tile = plan_tiles <= kPlanResident ? (int64_t)blockIdx.x : (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
     __syncthreads();
     const int64_t tile = s_tile, p0 = tile * kPlanThreads, p = p0 + t;

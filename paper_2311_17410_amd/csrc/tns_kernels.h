@@ -9,6 +9,8 @@
 
 namespace tns {
 
+constexpr int kDeferSpins = 2048;      // about two milliseconds
+
 struct SampleArgs {
     // store (device)
     const NodeLine* nodes;
@@ -51,6 +53,7 @@ struct SampleArgs {
     int32_t keep_nodes;    // node lines are likely to be read again soon: no non-temporal hint on them
     int32_t wide_offsets;  // edge array has 2^31 or more entries: 64-bit positions in LDS
     int32_t first_ticket;  // 0; tests of the chained scan's bounded wait pass 1: tile 0 then never exists
+    int32_t defer_spins;   // small grids: rounds of waiting after which a tile leaves its dense rows to the last one (kDeferSpins; tests: 0)
     int32_t scan_ready;    // scan_ws is already cleared (multi-hop: one clearing launch for all hops that need it)
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
     uint64_t chain_key;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)

@@ -21,7 +21,7 @@ __device__ __forceinline__ int ceil_log2_outcomes(int n) { return n <= 0 ? 0 : 3
 // Uniform policy: workgroups of at most eight waves, three of them per compute unit (80 registers; at 85, with two of
 // them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459).
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, int SCAN>
-__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs p, const int32_t rs, const uint32_t f_mul,
+__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs args, const int32_t rs, const uint32_t f_mul,
                                                                  const int32_t gshift, const uint32_t chunk) {
     constexpr bool FUSED = SCAN != kNoScan;
     static_assert(POLICY == 1 || (COUNT && !FUSED), "the recent policy is sampled by tns_sample_recent_kernel");
@@ -29,23 +29,33 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = wave_uniform((int32_t)(threadIdx.x >> 6));
+    __shared__ int32_t s_more;
+    int lane = threadIdx.x & (kWave - 1), wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
     // have none leave before they take a ticket
-    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    const int64_t Q = args.Q_dev ? min(args.Q, *args.Q_dev) : args.Q;
     if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
-            p.rowptr[0] = 0;
-            if (p.total_out) *p.total_out = 0;
+            args.rowptr[0] = 0;
+            if (args.total_out) *args.total_out = 0;
         }
         return;
     }
-    TileChain<SCAN> tc(p, &s_tile_base, &s_arrived);
-    const int64_t tile = tc.tile;
-    if (FUSED && tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
+    TileChain<SCAN> tc(args, Q, &s_tile_base, &s_arrived, &s_more);
+    if (FUSED && tc.tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
+sample_tile:
+    if (SCAN == kTags) {
+        new_tile(lane, wave);
+        wave = wave_uniform(wave);
+    }
+    const SampleArgs& p = [&]() -> const SampleArgs& {
+        if constexpr (SCAN == kTags) return arguments_anew();
+        else return args;
+    }();
+    tc.request(p);
+    const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -267,6 +277,7 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
+    if (tc.next(&s_arrived, lane)) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>

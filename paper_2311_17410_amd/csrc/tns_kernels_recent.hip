@@ -49,34 +49,45 @@ constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes 
 // block i or an older one.  Top byte of `lo`: filled slots; of `hi`: 1 if the row holds an entry per slot.
 struct SlotHead { uint32_t lo, hi; };
 
-// Registers: fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
+// Registers: small grids up to 128 and some scratch, because the workgroup of the last tile may sample others again (a loop around
+// the kernel; they have one or two waves per SIMD, four at most).  Otherwise, fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
 // positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
 // all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
 template <bool PREFIX, bool INCL, typename pos_t, int SCAN>
 __global__ void __launch_bounds__(SCAN ? 1024 : 256, SCAN ? 4 : 6)
-tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
+tns_sample_recent_kernel(const SampleArgs args, const int32_t stride, const uint32_t f_mul, const uint32_t chunk) {
     constexpr bool FUSED = SCAN != kNoScan;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;      // fused: waves of the tile that have finished their searches
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = wave_uniform((int32_t)(threadIdx.x >> 6));
+    __shared__ int32_t s_more;
+    int lane = threadIdx.x & (kWave - 1), wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
     // number of queries: the host's bound, or fewer when the count lives on the device (later hops); workgroups that
     // have none leave before they take a ticket
-    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    const int64_t Q = args.Q_dev ? min(args.Q, *args.Q_dev) : args.Q;
     if (FUSED && (int64_t)blockIdx.x * blockDim.x >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
-            p.rowptr[0] = 0;
-            if (p.total_out) *p.total_out = 0;
+            args.rowptr[0] = 0;
+            if (args.total_out) *args.total_out = 0;
         }
         return;
     }
-    TileChain<SCAN> tc(p, &s_tile_base, &s_arrived);
-    const int64_t tile = tc.tile;
-    if (FUSED && tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
+    TileChain<SCAN> tc(args, Q, &s_tile_base, &s_arrived, &s_more);
+    if (FUSED && tc.tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
+sample_tile:
+    if (SCAN == kTags) {
+        new_tile(lane, wave);
+        wave = wave_uniform(wave);
+    }
+    const SampleArgs& p = [&]() -> const SampleArgs& {
+        if constexpr (SCAN == kTags) return arguments_anew();
+        else return args;
+    }();
+    tc.request(p);
+    const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
     const int32_t f = p.fanout;
@@ -429,6 +440,7 @@ tns_sample_recent_kernel(const SampleArgs p, const int32_t stride, const uint32_
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
+    if (tc.next(&s_arrived, lane)) goto sample_tile;
 }
 
 template <bool PREFIX, bool INCL, typename pos_t, bool FUSED>

@@ -18,8 +18,9 @@
 //   deleted   a node whose flags say that edges of it are deleted has its candidates looked at, sixteen side by side.
 //             The flag is read here and not on the host: a captured call may be replayed after a deletion.
 // What bounds it is the chain of dependent reads (query, node, search, edge, look-back).  Its tiles tag what they publish
-// instead of having the scan state cleared by a launch before it and tickets taken (TaggedChain): 1024 queries 11.3 -> 8.2 us
-// per call, two hops from 600 and 4000 roots 17.9 -> 14.8 and 26.9 -> 23.0.  Measured beside the kernels with a query per
+// instead of having the scan state cleared by a launch before it and tickets taken (TaggedChain): 1024 queries 11.9 -> 8.5 us
+// per call, two hops from 600 and 4000 roots 17.3 -> 15.2 and 27.6 -> 24.5 (14.7 and 23.0 if every tile waited for as long as it takes,
+// which launches on several streams could do for good: TaggedChain).  Measured beside the kernels with a query per
 // lane: see the rule in launch_sample.
 #include <type_traits>
 
@@ -70,31 +71,34 @@ __device__ __forceinline__ void team_partition(int32_t (&n)[CH], int32_t (&lo)[C
 
 // CH: queries per team, all steps of which run side by side; ROUNDS: of sixteen slots
 template <int POLICY, bool INCL, int CH, int ROUNDS>
-__global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) tns_sample_team_kernel(const SampleArgs p) {
+__global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) tns_sample_team_kernel(const SampleArgs args) {
     constexpr int kTileQueries = kTileWaves * kTeamsPerWave * CH;
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[kTileWaves];
-    __shared__ int32_t s_arrived;
+    __shared__ int32_t s_arrived, s_more;
     __shared__ int32_t s_seq[kTileWaves][CH][kTeamsPerWave][ROUNDS * kTeam];      // nodes with deleted edges: the slots' edges
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
-    const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
-    const int32_t f = p.fanout;
-    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int32_t f = args.fanout;
+    const int64_t Q = args.Q_dev ? min(args.Q, *args.Q_dev) : args.Q;
     // later hops are launched for the most queries they can have: workgroups beyond the actual number leave at once
     if ((int64_t)blockIdx.x * kTileQueries >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
-            p.rowptr[0] = 0;
-            if (p.total_out) *p.total_out = 0;
+            args.rowptr[0] = 0;
+            if (args.total_out) *args.total_out = 0;
         }
         return;
     }
-    const int64_t tile = (int64_t)blockIdx.x + p.first_ticket;
+    int64_t tile = (int64_t)blockIdx.x + args.first_ticket;
     if (tile * kTileQueries >= Q) return;      // (tests whose tiles start at 1)
-    if (threadIdx.x == 0) s_arrived = 0;
+    if (threadIdx.x == 0) s_arrived = s_more = 0;
     __syncthreads();
     TaggedChain chain;
-    chain.request(p.scan_ws);
+    chain.start((tile + 1) * kTileQueries >= Q, &s_more);
+sample_tile:
+    new_tile(lane, wave);
+    const SampleArgs& p = arguments_anew();
+    chain.request(p.scan_ws);      // (inside the loop: the compiler waits before a loop for what was requested before it)
+    const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
     // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
     const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
 
@@ -395,7 +399,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
 
     // ---- outputs --------------------------------------------------------------------------------
     if (is_last) {
-        const int64_t excl = chain.exclusive(p.err_flag, tile, lane);
+        const int64_t excl = chain.exclusive(p.err_flag, tile, lane, p.defer_spins);
         if (lane == 0) s_tile_base = excl;
     }
     if (p.out_nbr) {
@@ -416,15 +420,17 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     }
     lds_barrier();
     int64_t wave_row = s_tile_base;
+    const bool dense = wave_row >= 0;      // (or the last tile's workgroup writes them)
     for (int i = 0; i < wave; ++i) wave_row += s_wave_sum[i];
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         const int64_t q = q0 + u * kTeamsPerWave;
         const int64_t row = wave_row + excl_in_wave[u];
         if (q >= Q) continue;
+        if (j == 0 && p.out_count) p.out_count[q] = k[u];
+        if (!dense) continue;
         if (j == 0) {
             p.rowptr[q] = row;
-            if (p.out_count) p.out_count[q] = k[u];
             if (q == Q - 1) {
                 // The last query's tile has looked back over every other tile.  If any wait ran into its bound the
                 // dense rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
@@ -443,12 +449,13 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
             }
         }
     }
+    if (chain.next(tile, &s_arrived, lane)) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, int CH, int ROUNDS>
 hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
     constexpr int64_t kTileQueries = kTileWaves * kTeamsPerWave * CH;
-    static_assert(kTileQueries * ROUNDS * kTeam < (1 << kTagShift), "a tile's total lies below the tag");
+    static_assert(kTileQueries * ROUNDS * kTeam < (1 << kTotalBits), "a tile's total lies below the tag");
     const int64_t grid = (a.Q + kTileQueries - 1) / kTileQueries;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (grid <= 0) return a.scan_ready ? hipGetLastError() : launch_scan_init(a, 1, stream);

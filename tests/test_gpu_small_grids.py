@@ -148,3 +148,64 @@ def test_a_tile_that_never_reports(B, Q):
     assert not sound.status(out["workspace"]) and int(out["rowptr"][-1].item()) == total > 0
     lost.close()
     sound.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("Q,fanout,instances", [(1, 10, 1), (130, 3, 1), (4000, 64, 1), (16_500, 10, 1), (30_001, 20, 1), (40_000, 5, 3), (100_000, 10, 1), (60_000, 64, 1),
+                                                ((1 << 18) - 1, 10, 1)])
+def test_tiles_that_leave_their_dense_rows_to_the_last(B, oracle_lib, policy, Q, fanout, instances, layout):
+    # a tile that does not find the totals before it at once makes room; the last tile's workgroup samples it again
+    import ctypes
+
+    import torch
+    rng = np.random.default_rng(Q)
+    sts = []
+    for _ in range(instances):
+        src = (rng.zipf(1.3, 30_000) % 3000).astype(np.int32)
+        sts.append(W.Stream(3000, src, rng.integers(0, 3000, 30_000, dtype=np.int32), np.sort(rng.standard_normal(30_000)).astype(np.float32), 1500))
+    wl = W.Workload("mixed", 0, sts, fanout=fanout, tau=48)
+    plan = build_plan(B, wl, policy, seed=6)
+    defer = B.lib().tns_test_defer
+    defer.argtypes, defer.restype = [ctypes.c_void_p], None
+    defer(plan.handle)
+    per = Q // instances
+    parts = [W.random_queries(Q + i, st, per) for i, st in enumerate(sts)]
+    targets, t_end = (np.concatenate([x[j] for x in parts]) for j in (0, 2))
+    inst = np.arange(instances + 1, dtype=np.int64) * per if instances > 1 else None
+    Q = per * instances
+    ref = oracle_sample(oracle_lib, wl, targets, None, t_end, inst, fanout, policy, 0, 6)
+    d = lambda a: None if a is None else torch.from_numpy(a).cuda()  # noqa: E731
+    args = (d(targets), None, d(t_end), d(inst))
+    out = plan.run(*args)
+    for i in range(4):
+        for n in ("rowptr", "cmp_eid", "count", "eid"):
+            out[n].fill_(-3)
+        plan.run(*args, out=out)
+        torch.cuda.synchronize()
+        assert not plan.status(out["workspace"])
+        assert_same(results(out, Q, fanout), ref, oracle_lib, f"call {i}")
+    plan.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_four_streams(B, oracle_lib, policy):
+    # four queues with launches that together are larger than the chip, each with its own workspace and queries, none waiting for another
+    import torch
+    fanout, Q, streams = 10, 200_000, [torch.cuda.Stream() for _ in range(4)]
+    st, wl, plan = store(B, fanout, policy)
+    adjs = [oracle_lib.Adjacency(st.num_nodes, st.src, st.dst, st.ts)]
+    queries = [W.random_queries(50 + i, st, Q) for i in range(4)]
+    on_device = [(torch.from_numpy(t).cuda(), torch.from_numpy(e).cuda()) for t, _, e in queries]
+    outs = [plan.run(t, None, e) for t, e in on_device]
+    for o in outs:
+        o["rowptr"].fill_(-3)
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for s, (t, e), o in zip(streams, on_device, outs):
+            with torch.cuda.stream(s):
+                plan.run(t, None, e, out=o)
+    torch.cuda.synchronize()
+    for (t, _, e), o in zip(queries, outs):
+        assert not plan.status(o["workspace"])
+        assert_same(results(o, Q, fanout), oracle_sample(oracle_lib, wl, t, None, e, None, fanout, policy, 0, 6, adjs=adjs), oracle_lib, "streams")
+    plan.close()
