@@ -180,6 +180,7 @@ struct TaggedChain {
                         __hip_atomic_store(&ws->deferred, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                     __threadfence();
+                    __builtin_amdgcn_wave_barrier();      // no lane looks before the note is made
                     noted = true;
                     continue;
                 }
@@ -207,25 +208,33 @@ struct TaggedChain {
         return bad;
     }
     // After a tile, by the whole workgroup: true if there is another one for it to sample, again and now with its dense rows.
-    __device__ __forceinline__ bool next(int64_t& tile, int32_t* s_arrived, int lane) {
+    // One wave looks for it: a tile's note may come between two waves' looks (it then writes its rows itself), and the waves
+    // of a workgroup must go on with one tile.  s_tile, s_arrived: in LDS, of the tile that is done.
+    __device__ __forceinline__ bool next(int64_t& tile, int64_t* s_tile, int32_t* s_arrived, int lane) {
         if (!last_wg) return false;
         __syncthreads();
-        if (!__builtin_amdgcn_readfirstlane(*s_more)) return false;
         const int64_t last = again ? last_tile : tile;
-        int64_t t0 = again ? tile + 1 : 0;
-        uint64_t found = 0;
-        for (; t0 < last; t0 += kChainWave) {
-            uint64_t w = 0;
-            if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            found = __ballot(w >> kTagShift == tag && (w & kDeferredBit));
-            if (found) break;
+        if (threadIdx.x < kChainWave) {
+            uint64_t found = 0;
+            int64_t t0 = again ? tile + 1 : 0;
+            if (!*s_more) t0 = last;
+            for (; t0 < last; t0 += kChainWave) {
+                uint64_t w = 0;
+                if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                found = __ballot(w >> kTagShift == tag && (w & kDeferredBit));
+                if (found) break;
+            }
+            if (lane == 0) {
+                *s_tile = found ? t0 + __builtin_ctzll(found) : -1;
+                *s_arrived = 0;
+            }
         }
-        if (!found) return false;
+        __syncthreads();
+        const int64_t t = *s_tile;
+        if (__builtin_amdgcn_readfirstlane((int)(t < 0))) return false;
         last_tile = last;
         again = true;
-        tile = t0 + __builtin_ctzll(found);
-        if (threadIdx.x == 0) *s_arrived = 0;
-        __syncthreads();
+        tile = t;
         return true;
     }
 };

@@ -480,9 +480,9 @@ struct TileChain {
         else if (tile > 0) __hip_atomic_store(&ws(p)->status[tile], kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // by the whole workgroup, after a tile: true if it has another one to sample
-    __device__ __forceinline__ bool next(int32_t* s_arrived, int lane) {
+    __device__ __forceinline__ bool next(int64_t* s_tile_base, int32_t* s_arrived, int lane) {
         if (!kTagged) return false;
-        return tags.next(tile, s_arrived, lane);
+        return tags.next(tile, s_tile_base, s_arrived, lane);
     }
     // one wave: the dense entries of the tiles before this one; -1 (kTags): the tile writes no dense rows
     __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
@@ -507,7 +507,7 @@ struct TileChain<kNoScan> {
         : tile(p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) {}
     __device__ __forceinline__ void request(const SampleArgs&) {}
     __device__ __forceinline__ void settle(const SampleArgs&) {}
-    __device__ __forceinline__ bool next(int32_t*, int) const { return false; }
+    __device__ __forceinline__ bool next(int64_t*, int32_t*, int) const { return false; }
 };
 
 // Output stage of a fused kernel: chained scan over the workgroup tiles for the dense offsets, padded rows, dense rows and

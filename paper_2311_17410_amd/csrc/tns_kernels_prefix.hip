@@ -277,7 +277,7 @@ sample_tile:
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
-    if (tc.next(&s_arrived, lane)) goto sample_tile;
+    if (tc.next(&s_tile_base, &s_arrived, lane)) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>

@@ -449,7 +449,7 @@ sample_tile:
             }
         }
     }
-    if (chain.next(tile, &s_arrived, lane)) goto sample_tile;
+    if (chain.next(tile, &s_tile_base, &s_arrived, lane)) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, int CH, int ROUNDS>
