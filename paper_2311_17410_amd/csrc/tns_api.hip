@@ -990,10 +990,11 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
     size_t scan = 0;
     for (int h = 0; h < num_hops; ++h) scan += tns::compact_workspace_bytes(caps[h]);
     int64_t* header = reinterpret_cast<int64_t*>(scan_ws + scan);
-    // One launch clears the regions of the hops that are too large to do without: from the first of them on (hops do not get
-    // smaller), with the status word if that is the first hop; otherwise the first hop leaves the word as it should be.
+    // One launch clears the regions of the hops that cannot do without: all of them in a call that may be replayed, otherwise those
+    // from the first on that is too large (hops do not get smaller); with the status word if that is the first hop, which otherwise
+    // leaves the word as it should be.
     int first_cleared = 0;
-    if (Q > 0)
+    if (Q > 0 && !tns::may_be_replayed(stream))
         while (first_cleared < num_hops && caps[first_cleared] <= tns::tagged_queries(fanouts[first_cleared])) ++first_cleared;
     if (first_cleared < num_hops) {
         unsigned char* from = scan_ws;
@@ -1016,7 +1017,7 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
         a.out_count = b.count;
         a.total_out = total;
         a.scan_ws = scan_ws;                                    // sampling with the padding removal fused in
-        a.scan_ready = Q > 0 && h >= first_cleared ? 1 : 0;     // cleared above, together with the other hops' regions
+        a.scan_ready = Q > 0 ? 1 : 0;                           // cleared above where it has to be
         scan_ws += tns::compact_workspace_bytes(caps[h]);
         a.rowptr = b.rowptr;
         a.cmp_nbr = b.cmp_nbr;

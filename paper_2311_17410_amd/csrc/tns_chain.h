@@ -23,9 +23,8 @@ constexpr int kSpinLimit = 1 << 22;
 struct ScanWorkspace {
     uint32_t ticket;
     uint32_t error;
-    uint64_t launches;    // tagged chain
     uint64_t deferred;    // tagged chain: the tag of a launch in which a tile has left its dense rows to the last one
-    uint32_t pad[58];
+    uint32_t pad[60];
     uint64_t status[1];   // [number of tiles]
 };
 
@@ -85,12 +84,9 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
 //
 // A batch of a few hundred tiles is bound by latency: the clearing launch is 2.5 us of it, and tickets, atomics on one word,
 // are taken at 18 ns each (14 us for the 782 tiles of 10^5 queries).  Here a tile's word carries a tag next to the total, and
-// a word with another tag has not been written yet, whatever the workspace held before.  The tag is made from a key that the
-// host draws anew for every launch, and, because a captured launch is replayed with the same key, from two counters in the
-// workspace that every launch moves on: one in its head and one before the tiles' words.  Two, because a kernel that clears
-// its state overwrites the second (and a caller may clear the head): for the words of an earlier replay to be taken for new
-// ones both would have to be set back and the words kept.  The last tile moves the counters on, when it has heard from every
-// other tile, which has then read them.  Memory that by chance holds the tag of a launch: one word in 2^47.
+// a word with another tag has not been written yet, whatever the workspace held before.  The host draws a tag anew for every
+// launch.  A captured launch is replayed with the tag it has, over words that the replay before may have left, so that there the
+// state is cleared by a launch of its own (may_be_replayed).  Memory that by chance holds the tag of a launch: one word in 2^47.
 //
 // Every tile reads the totals of all tiles before it, four words per lane at a time; there are no prefixes to wait for.  Tiles
 // are numbered as the workgroups are, which every XCD starts in that order.  Alone a launch cannot hold itself up, but XCDs
@@ -105,19 +101,11 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
 constexpr int kTotalBits = 16;                        // a tile's total is below 2^16
 constexpr int kTagShift = kTotalBits + 1;             // between them: the tile has left its dense rows to the last one
 constexpr uint64_t kDeferredBit = uint64_t(1) << kTotalBits;
-__host__ __device__ inline uint64_t mix64(uint64_t z) {      // splitmix64's output function
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-__host__ __device__ inline uint64_t chain_tag(uint64_t key, uint64_t in_head, uint64_t before_tiles) {
-    return mix64(key + in_head * 0x9E3779B97F4A7C15ull + mix64(before_tiles + 1)) >> kTagShift;
-}
 
-// Where the words of a tagged chain are: status[0] is the second counter, tile t's word is status[t + 1].
+// Tile t's word is status[t].
 struct TaggedChain {
     ScanWorkspace* ws;
-    uint64_t in_head, before_tiles, tag;
+    uint64_t tag;
     int32_t* s_more;         // LDS: 1 if tiles have left their dense rows to this one, the last
     bool last_wg;            // the workgroup of the last tile
     bool again = false;      // which samples other tiles again
@@ -126,24 +114,14 @@ struct TaggedChain {
         last_wg = is_last_tile;
         s_more = more;
     }
-    __device__ __forceinline__ void request(void* scan_ws) {
+    // for every tile of a workgroup
+    __device__ __forceinline__ void use(void* scan_ws, uint64_t launch_tag) {
         ws = static_cast<ScanWorkspace*>(scan_ws);
-        in_head = __hip_atomic_load(&ws->launches, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        before_tiles = __hip_atomic_load(&ws->status[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // once the counters have arrived; they are the same in all lanes and need not stay in registers of each
-    __device__ __forceinline__ void settle(uint64_t key) {
-        auto uniform = [](uint64_t v) {
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-            return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32 | lo;
-        };
-        in_head = uniform(in_head);
-        before_tiles = uniform(before_tiles);
-        if (!again) tag = chain_tag(key, in_head, before_tiles);
+        tag = launch_tag;
     }
     __device__ __forceinline__ void publish(int64_t tile, int32_t total) const {
         if (again) return;
-        __hip_atomic_store(&ws->status[tile + 1], tag << kTagShift | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ws->status[tile], tag << kTagShift | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // what an error word holds after a wait of this launch ran out
     __device__ __forceinline__ uint32_t mark() const { return (uint32_t)tag | 1u; }
@@ -162,7 +140,7 @@ struct TaggedChain {
                 for (int i = 0; i < 4; ++i) {
                     const int64_t t = t0 + i * kChainWave + lane;
                     w[i] = tag << kTagShift;
-                    if (t < tile) w[i] = __hip_atomic_load(&ws->status[t + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (t < tile) w[i] = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ready = ready && w[i] >> kTagShift == tag;
@@ -175,7 +153,7 @@ struct TaggedChain {
                 }
                 if (!last_wg && spins > defer_spins) {
                     if (lane == 0) {
-                        __hip_atomic_fetch_or(&ws->status[tile + 1], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_fetch_or(&ws->status[tile], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         __threadfence();
                         __hip_atomic_store(&ws->deferred, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
@@ -203,8 +181,6 @@ struct TaggedChain {
         const bool bad = __hip_atomic_load(err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark();
         if (left == tag && !bad) *s_more = 1;
         if (!bad) __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&ws->launches, in_head + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&ws->status[0], before_tiles + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return bad;
     }
     // After a tile, by the whole workgroup: true if there is another one for it to sample, again and now with its dense rows.
@@ -220,7 +196,7 @@ struct TaggedChain {
             if (!*s_more) t0 = last;
             for (; t0 < last; t0 += kChainWave) {
                 uint64_t w = 0;
-                if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 found = __ballot(w >> kTagShift == tag && (w & kDeferredBit));
                 if (found) break;
             }

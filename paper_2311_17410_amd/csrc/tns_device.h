@@ -465,12 +465,9 @@ struct TileChain {
             __syncthreads();
         }
     }
-    // (for every tile, inside the loop: the compiler waits before a loop for what was requested before it)
-    __device__ __forceinline__ void request(const SampleArgs& p) {
-        if (kTagged) tags.request(p.scan_ws);
-    }
-    __device__ __forceinline__ void settle(const SampleArgs& p) {
-        if (kTagged) tags.settle(p.chain_key);
+    // for every tile of a workgroup
+    __device__ __forceinline__ void use(const SampleArgs& p) {
+        if (kTagged) tags.use(p.scan_ws, p.chain_tag);
     }
     __device__ __forceinline__ ScanWorkspace* ws(const SampleArgs& p) const { return static_cast<ScanWorkspace*>(p.scan_ws); }
     // one wave, at once, so that later tiles can look past this one
@@ -505,8 +502,7 @@ struct TileChain<kNoScan> {
     int64_t tile;
     __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t, int64_t*, int32_t*, int32_t*)
         : tile(p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) {}
-    __device__ __forceinline__ void request(const SampleArgs&) {}
-    __device__ __forceinline__ void settle(const SampleArgs&) {}
+    __device__ __forceinline__ void use(const SampleArgs&) {}
     __device__ __forceinline__ bool next(int64_t*, int32_t*, int) const { return false; }
 };
 
@@ -606,7 +602,8 @@ hipError_t launch_tiles(const SampleArgs& a, int64_t grid, hipStream_t stream, c
     if constexpr (FUSED) {
         if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
         if (grid > 0 && a.Q <= tagged_queries(a.fanout)) {
-            b.chain_key = new_chain_key();
+            const hipError_t e = ready_tags(b, grid, stream);
+            if (e != hipSuccess) return e;
             launch(std::integral_constant<int, kTags>{}, b);
             return hipGetLastError();
         }

@@ -54,9 +54,9 @@ struct SampleArgs {
     int32_t wide_offsets;  // edge array has 2^31 or more entries: 64-bit positions in LDS
     int32_t first_ticket;  // 0; tests of the chained scan's bounded wait pass 1: tile 0 then never exists
     int32_t defer_spins;   // small grids: rounds of waiting after which a tile leaves its dense rows to the last one (kDeferSpins; tests: 0)
-    int32_t scan_ready;    // scan_ws is already cleared (multi-hop: one clearing launch for all hops that need it)
+    int32_t scan_ready;    // scan_ws is as this launch needs it (multi-hop: one clearing launch for all hops that need it)
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
-    uint64_t chain_key;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)
+    uint64_t chain_tag;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)
     uint32_t* err_flag;    // where a chained scan whose bounded wait ran out reports it (null: the error word of scan_ws)
 };
 
@@ -91,7 +91,10 @@ hipError_t launch_sample_team(const SampleArgs& a, hipStream_t stream);
 // Most queries of a call with fan-out f whose tiles need no cleared scan state (TaggedChain in tns_chain.h): as many as the
 // chip holds at once, sixteen waves per compute unit or what the LDS of a wave's result rows allows.
 constexpr int64_t tagged_queries(int32_t f) { return int64_t(1) << (f <= 12 ? 18 : (f <= 32 ? 17 : 16)); }
-uint64_t new_chain_key();      // another one for every launch
+// Draws the tag of such a launch, another one every time, and clears the state where may_be_replayed() says so.
+hipError_t ready_tags(SampleArgs& a, int64_t tiles, hipStream_t stream);
+// What is launched on the stream is being captured: it may run again as it is.
+bool may_be_replayed(hipStream_t stream);
 // Clears the chained scan's state for `num_tiles` tiles before a fused launch (kernel, capturable).
 hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t stream);
 hipError_t launch_compact(const CompactArgs& a, hipStream_t stream);

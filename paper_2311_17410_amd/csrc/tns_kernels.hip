@@ -20,8 +20,11 @@
 #include "tns_kernels.h"
 #include "tns_device.h"
 
+#include <unistd.h>
+
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <type_traits>
 
 namespace tns {
@@ -88,7 +91,7 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.request(p);
+    tc.use(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -119,7 +122,6 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
-    tc.settle(p);
     // the node's 128-byte line: header + the records of up to 7 blocks, newest first
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -628,9 +630,25 @@ hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t 
     return hipGetLastError();
 }
 
-uint64_t new_chain_key() {
-    static std::atomic<uint64_t> launches{0};
-    return mix64(0x9E3779B97F4A7C15ull * (launches.fetch_add(1, std::memory_order_relaxed) + 1));
+bool may_be_replayed(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();      // (no answer, for instance the legacy stream during a capture: the launch reports what is wrong)
+    return true;
+}
+
+hipError_t ready_tags(SampleArgs& a, int64_t tiles, hipStream_t stream) {
+    // splitmix64 from a start of its own: another copy of the library may have left tags in memory that this one is given
+    auto start = []() { return (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)getpid() << 40; };
+    static std::atomic<uint64_t> state{start()};
+    do {
+        uint64_t z = state.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        a.chain_tag = (z ^ (z >> 31)) >> kTagShift;
+    } while (a.chain_tag == 0);      // (what a cleared word holds)
+    // one state more than tiles: the workspace has it, and a test whose tiles start at 1 uses it
+    return !a.scan_ready && may_be_replayed(stream) ? launch_scan_init(a, tiles + 1, stream) : hipSuccess;
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {

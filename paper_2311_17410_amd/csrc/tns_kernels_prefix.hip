@@ -54,7 +54,7 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.request(p);
+    tc.use(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -79,7 +79,6 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
-    tc.settle(p);
     // ---- node lines: eight lanes per line, handed over through LDS ------------------------------------
     uint32_t w[3 * kInlineSlots];     // the eight edge slots of the node's own line
     uint32_t h_degree, h_meta, h_ext0, h_ext12, h_fence0, h_fence1, h_fence2, h_dir;   // the node entry

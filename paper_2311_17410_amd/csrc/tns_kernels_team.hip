@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
 sample_tile:
     new_tile(lane, wave);
     const SampleArgs& p = arguments_anew();
-    chain.request(p.scan_ws);      // (inside the loop: the compiler waits before a loop for what was requested before it)
+    chain.use(p.scan_ws, p.chain_tag);
     const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
     // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
     const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
@@ -173,7 +173,6 @@ sample_tile:
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
-    chain.settle(p.chain_key);
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -460,8 +459,9 @@ hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (grid <= 0) return a.scan_ready ? hipGetLastError() : launch_scan_init(a, 1, stream);
     SampleArgs b = a;
-    b.chain_key = new_chain_key();
     if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
+    const hipError_t e = ready_tags(b, grid, stream);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((tns_sample_team_kernel<POLICY, INCL, CH, ROUNDS>), dim3((unsigned)grid), dim3(kTileWaves * kWave), 0, stream, b);
     return hipGetLastError();
 }

@@ -7,7 +7,7 @@
 #include <string.h>
 
 static size_t used, limit = (size_t)1 << 40;
-static int allocations, launches;
+static int allocations, launches, capturing;
 static uint64_t grid_xy;                        /* of the latest launch */
 struct head { size_t bytes, pad[31]; };
 
@@ -16,6 +16,8 @@ size_t fake_used(void) { return used; }
 int fake_allocations(void) { return allocations; }
 int fake_launches(void) { return launches; }
 unsigned fake_grid(void) { return (unsigned)grid_xy; }
+
+void fake_capture(int on) { capturing = on; }      /* 2: hipStreamIsCapturing has no answer */
 
 int hipMalloc(void **p, size_t n) {
     struct head *h;
@@ -64,3 +66,4 @@ int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; *e = NULL; return 0; }
 int hipEventDestroy(void *e) { (void)e; return 0; }
 int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }
+int hipStreamIsCapturing(void *s, int *status) { (void)s; *status = capturing == 1; return capturing == 2 ? 906 : 0; }      /* hipErrorStreamCaptureImplicit */

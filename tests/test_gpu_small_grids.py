@@ -129,6 +129,60 @@ def test_replays_between_other_calls(B, oracle_lib, policy, layout):
     plan.close()
 
 
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("Q", [9600, 100_000])
+def test_replays_over_what_an_earlier_one_left(B, oracle_lib, policy, Q, layout):
+    # a captured call and a captured pair of hops, replayed with new queries: before every replay the workspace is made byte for byte
+    # what the first replay left, with its tile totals (other work may put any part of it back, and leave the rest)
+    import torch
+    fanout, roots = 10, 700
+    st, wl, plan = store(B, fanout, policy)
+    adjs = [oracle_lib.Adjacency(st.num_nodes, st.src, st.dst, st.ts)]
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    targets, _, t_end = W.random_queries(1, st, Q)
+    d_t, d_e = d(targets), d(t_end)
+    out = plan.run(d_t, None, d_e)
+    hops, ws_hops = plan.run_khop([fanout, 4], d_t[:roots], None, d_e[:roots])
+    names = [n for n, _ in B.tns_hop_buffers._fields_]
+    ptrs = [{n: h[n].data_ptr() for n in names} for h in hops]
+
+    def call():
+        plan.run(d_t, None, d_e, out=out)
+        B.tns_run_khop(plan.handle, [fanout, 4], float("inf"), roots, d_t.data_ptr(), 0, d_e.data_ptr(), 0, 0, ptrs, ws_hops.data_ptr(), ws_hops.numel(),
+                       torch.cuda.current_stream().cuda_stream)
+
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    graph.replay()
+    torch.cuda.synchronize()
+    left = out["workspace"].clone(), ws_hops.clone()
+    for i in range(6):
+        t, _, e = W.random_queries(100 + i, st, Q)
+        d_t.copy_(d(t))
+        d_e.copy_(d(e))
+        for a in (out["rowptr"], out["cmp_eid"], *(h[n] for h in hops for n in ("rowptr", "cmp_eid"))):
+            a.fill_(-3)
+        out["workspace"].copy_(left[0])
+        ws_hops.copy_(left[1])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert not plan.status(out["workspace"]) and not plan.status(ws_hops), i
+        ref = oracle_sample(oracle_lib, wl, t, None, e, None, fanout, policy, 0, 6, adjs=adjs)
+        assert_same(results(out, Q, fanout), ref, oracle_lib, f"replay {i}")
+        eager, _ = plan.run_khop([fanout, 4], d_t[:roots], None, d_e[:roots])
+        for h, want in zip(hops, eager):
+            q = roots if h is hops[0] else int(hops[0]["rowptr"][-1].item())
+            assert torch.equal(h["rowptr"][:q + 1], want["rowptr"][:q + 1]), i
+            rows = int(want["rowptr"][q].item())
+            for n in ("cmp_nbr", "cmp_eid", "cmp_ts"):
+                assert torch.equal(h[n][:rows], want[n][:rows]), (i, n)
+    plan.close()
+
+
 @pytest.mark.parametrize("Q", [700, 40_000, 300_000])
 def test_a_tile_that_never_reports(B, Q):
     # tile 0 does not exist: the waits run out, the time-out is reported and the next sound call clears the report

@@ -100,3 +100,24 @@ KB.tns_cache_fetch(c, 100, 256, 256, 256, 0, 256, KB.tns_cache_workspace(c, 100)
 assert fake.fake_grid() == ({capacity} + 3) // 4 + 1, fake.fake_grid()
 KB.tns_cache_destroy(c)
 """)
+
+
+@pytest.mark.parametrize("queries,fanout,policy,flags", [(1, 10, 0, 0), (20_000, 10, 1, 0), (1 << 18, 10, 0, 0), (1 << 17, 20, 1, 0), (5000, 10, 0, 128),
+                                                         (1 << 16, 40, 1, 128)])
+def test_the_scan_state_of_a_captured_call_is_cleared(run, queries, fanout, policy, flags):
+    # a captured call runs again as it is, over what the replay before left: batches that otherwise need no cleared state get a
+    # launch that clears it (one for all hops)
+    run(f"""
+p = B.Plan(1000, {fanout}, policy={policy}, flags={flags})
+B.tns_commit(p.handle)
+def launches(capture):
+    fake.fake_capture(capture)
+    n = fake.fake_launches()
+    B.tns_run(p.handle, {queries}, 256, 0, 256, 0, 0, 256, 256, 256, 256, 256, 256, 256, 256, 256, B.tns_workspace(p.handle, {queries}), 0)
+    m = fake.fake_launches()
+    hop = dict.fromkeys([n for n, _ in B.tns_hop_buffers._fields_], 256)
+    B.tns_run_khop(p.handle, [{fanout}, 1], float("inf"), {max(1, queries // fanout)}, 256, 0, 256, 0, 0, [hop, hop], 256,
+                   B.tns_workspace_khop(p.handle, [{fanout}, 1], {max(1, queries // fanout)}), 0)
+    return m - n, fake.fake_launches() - m
+assert launches(0) == (1, 2) and launches(1) == (2, 3) and launches(2) == (2, 3) and launches(0) == (1, 2)
+""")

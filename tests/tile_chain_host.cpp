@@ -10,10 +10,10 @@ static int try_once(uint32_t seed) {
     std::mt19937 rng(seed);
     const int tiles = 1 + (int)(rng() % 8), spins = (int)(rng() % 3);
     const int resident = tiles < 2 ? 1 : 2 + (int)(rng() % (unsigned)(tiles - 1));
-    std::vector<uint64_t> words(64 + tiles + 2);
+    std::vector<uint64_t> words(64 + tiles);
     for (uint64_t& w : words) w = rng() % 2 ? 0 : (uint64_t)rng() << 32 | rng();
     auto* ws = reinterpret_cast<ScanWorkspace*>(words.data());
-    const uint64_t key = mix64(seed + 1);
+    const uint64_t tag = ((uint64_t)rng() << 32 | rng()) >> kTagShift;
     std::vector<int> count(tiles * sim::kWaves);
     for (int& c : count) c = (int)(rng() % 900);
     std::vector<int64_t> row(tiles * sim::kWaves, -3);
@@ -28,8 +28,7 @@ static int try_once(uint32_t seed) {
         TaggedChain chain;
         chain.start(tile == tiles - 1, &g.more);
         do {
-            chain.request(ws);
-            chain.settle(key);
+            chain.use(ws, tag);
             int last = 0;
             if (lane == 0) {
                 g.wave_sum[wave] = count[tile * sim::kWaves + wave];
