@@ -952,7 +952,7 @@ int tns_workspace_khop(const tns_plan* plan, int32_t num_hops, const int32_t* fa
     return TNS_OK;
 }
 
-void tns_test_defer(tns_plan* plan) { plan->defer_spins = 0; }
+void tns_test_defer(tns_plan* plan) { plan->defer_spins = -1; }
 
 int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float delta, int64_t Q,
                  const int32_t* d_targets, const float* d_t_start, const float* d_t_end, const int64_t* d_inst_rowptr,

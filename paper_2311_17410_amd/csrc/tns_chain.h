@@ -23,7 +23,7 @@ constexpr int kSpinLimit = 1 << 22;
 struct ScanWorkspace {
     uint32_t ticket;
     uint32_t error;
-    uint64_t deferred;    // tagged chain: the tag of a launch in which a tile has left its dense rows to the last one
+    uint64_t sampled_again;   // tagged chain: tiles, counted on from whatever this held (read by tests)
     uint32_t pad[60];
     uint64_t status[1];   // [number of tiles]
 };
@@ -86,81 +86,82 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
 // are taken at 18 ns each (14 us for the 782 tiles of 10^5 queries).  Here a tile's word carries a tag next to the total, and
 // a word with another tag has not been written yet, whatever the workspace held before.  The host draws a tag anew for every
 // launch.  A captured launch is replayed with the tag it has, over words that the replay before may have left, so that there the
-// state is cleared by a launch of its own (may_be_replayed).  Memory that by chance holds the tag of a launch: one word in 2^47.
+// state is cleared by a launch of its own (may_be_replayed).  Memory that by chance holds the tag of a launch: one word in 2^44.
 //
 // Every tile reads the totals of all tiles before it, four words per lane at a time; there are no prefixes to wait for.  Tiles
-// are numbered as the workgroups are, which every XCD starts in that order.  Alone a launch cannot hold itself up, but XCDs
-// start the workgroups of two queues in either order: waiting tiles of two launches could each fill an XCD that the other one's
-// earlier tiles need.  So only the last tile waits for as long as it takes.  Any other one that has waited for kDeferSpins (about
-// two milliseconds, hundreds of times what a tile takes) leaves its dense rows out and makes room, and the last tile's workgroup
-// samples it again when all totals are there.  What waits is then one workgroup per launch.
+// are numbered as the workgroups are, and a tile may find that one before it has not even started: other work can hold an XCD for
+// any time, and waiting tiles of two launches could each fill an XCD that the other one's earlier tiles need.  So a tile waits for
+// tiles that have started, which publish without waiting for anything, and no more than about two milliseconds (kDeferSpins,
+// hundreds of times what a tile takes) for one that has not.  Then it makes room: it leaves its dense rows out, notes that in its
+// word, and asks the nearest missing tile, in that tile's word, to see to it.  What a word held is what publishing it returns, so that
+// either the request is seen, or whoever asks sees that there is nothing to wait for any more.  A workgroup that was asked has either
+// made room itself and asked a tile further back, or nothing is missing before its tile and before those that asked it: it
+// samples the noted tiles up to the first missing one again, beside others that do the same.  The last tile, if it makes room,
+// first leaves the end of the call as it would be if a tile never reported.  What that can cost: 10^5 queries over power-law ids with
+// 770 of their tiles sampled again, most of them by one workgroup, took 5.5 ms (7 us a tile) instead of 17 us.
 // us per call, 2^21 edges, fan-out 10, tickets and clearing launch / this, recent policy, uniform ids: 65537 queries 22.6 /
 // 13.4, 10^5 27.8 / 15.7, 2 * 10^5 37.0 / 25.3, 2^18 - 1 36.9 / 29.2; power-law ids 26.7 / 17.8, 32.5 / 20.5, 40.8 / 28.7, 38.0 / 30.5; uniform
 // policy, power-law ids 38.8 / 32.0, 49.3 / 38.9, 66.8 / 58.0, 77.9 / 66.4; prefix layout, recent 32.4 / 23.5, 37.4 / 25.5, 44.7 /
 // 32.6, 41.2 / 35.5 (the second figures without tiles that make room).  Both forms in one kernel, chosen at run time, cost the large batches of the prefix layout 1 to 4 %.
 constexpr int kTotalBits = 16;                        // a tile's total is below 2^16
-constexpr int kTagShift = kTotalBits + 1;             // between them: the tile has left its dense rows to the last one
-constexpr uint64_t kDeferredBit = uint64_t(1) << kTotalBits;
+constexpr int kTagShift = kTotalBits + 4;
+constexpr uint64_t kDeferredBit = uint64_t(1) << kTotalBits;          // made room: its dense rows are to be written
+constexpr uint64_t kAskedBit = kDeferredBit << 1;                     // others wait for it to see to noted tiles
+constexpr uint64_t kStartedBit = kDeferredBit << 2, kPublishedBit = kDeferredBit << 3;
 
 // Tile t's word is status[t].
 struct TaggedChain {
+    struct Call {            // what only a tile that makes room or was asked needs
+        int64_t queries;
+        int64_t *end, *total_out;
+        uint32_t* err_flag;
+    };
     ScanWorkspace* ws;
-    uint64_t tag;
-    int32_t* s_more;         // LDS: 1 if tiles have left their dense rows to this one, the last
-    bool last_wg;            // the workgroup of the last tile
-    bool again = false;      // which samples other tiles again
-    int64_t last_tile = 0;
-    __device__ __forceinline__ void start(bool is_last_tile, int32_t* more) {
-        last_wg = is_last_tile;
-        s_more = more;
-    }
-    // for every tile of a workgroup
-    __device__ __forceinline__ void use(void* scan_ws, uint64_t launch_tag) {
+    uint64_t tag, old = 0;   // old: what the tile's word held (one lane)
+    int32_t* s_todo;         // LDS, 0 before: what is left to do when the tile is done
+    bool again = false;      // sampling a noted tile
+    enum Todo : int32_t { kAsked = 1, kMakeRoom = 2 };
+    // for every tile of a workgroup, inside the loop: the compiler waits before a loop for what was requested before it
+    __device__ __forceinline__ void begin(void* scan_ws, uint64_t launch_tag, int64_t tile) {
         ws = static_cast<ScanWorkspace*>(scan_ws);
         tag = launch_tag;
+        if (!again && threadIdx.x == 0)
+            old = __hip_atomic_exchange(&ws->status[tile], tag << kTagShift | kStartedBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ __forceinline__ void publish(int64_t tile, int32_t total) const {
+    // before this wave's sums are counted in
+    __device__ __forceinline__ void begun() const {
+        if (!again && threadIdx.x == 0) keep_request();
+    }
+    // by one lane
+    __device__ __forceinline__ void publish(int64_t tile, int32_t total) {
         if (again) return;
-        __hip_atomic_store(&ws->status[tile], tag << kTagShift | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        old = __hip_atomic_exchange(&ws->status[tile], tag << kTagShift | kStartedBit | kPublishedBit | (uint64_t)total, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT);
     }
-    // what an error word holds after a wait of this launch ran out
-    __device__ __forceinline__ uint32_t mark() const { return (uint32_t)tag | 1u; }
-    // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.  -1: the tile has
-    // waited for long enough and leaves its dense rows to the last one.  It says so before its last look: either that look finds
-    // what was missing, or the last tile, which goes on once nothing is missing, finds the note.
-    __device__ __forceinline__ int64_t exclusive(uint32_t* err_flag, int64_t tile, int lane, int defer_spins) const {
+    // Sum of the totals of all tiles before `tile` (called by one whole wave, whose lane 0 has published): four words per lane in
+    // flight.  -1: the tile has waited for long enough, writes no dense rows, and is noted by next().
+    __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins) const {
         int64_t sum = 0;
         int spins = 0;
-        bool noted = false;
         for (int64_t t0 = 0; t0 < tile; t0 += 4 * kChainWave) {
             uint64_t w[4];
             while (true) {
-                bool ready = true;
+                bool ready = true, started = true;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int64_t t = t0 + i * kChainWave + lane;
-                    w[i] = tag << kTagShift;
+                    w[i] = tag << kTagShift | kStartedBit | kPublishedBit;
                     if (t < tile) w[i] = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) ready = ready && w[i] >> kTagShift == tag;
-                if (!__ballot(!ready)) break;
-                if (noted) return -1;
-                if (++spins > kSpinLimit) {
-                    if (lane == 0) atomicExch(err_flag, mark());
-                    __threadfence();
-                    return 0;
+                for (int i = 0; i < 4; ++i) {
+                    ready = ready && published(w[i]);
+                    started = started && w[i] >> kTagShift == tag && (w[i] & kStartedBit);
                 }
-                if (!last_wg && spins > defer_spins) {
-                    if (lane == 0) {
-                        __hip_atomic_fetch_or(&ws->status[tile], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        __threadfence();
-                        __hip_atomic_store(&ws->deferred, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    __threadfence();
-                    __builtin_amdgcn_wave_barrier();      // no lane looks before the note is made
-                    noted = true;
-                    continue;
+                if (!__ballot(!ready)) break;
+                if (++spins > (defer_spins < 0 || __ballot(!started) ? defer_spins : kSpinLimit)) {
+                    if (lane == 0) *s_todo = kMakeRoom;
+                    return -1;
                 }
                 if (spins < 16) __builtin_amdgcn_s_sleep(2);
                 else __builtin_amdgcn_s_sleep(16);
@@ -171,47 +172,109 @@ struct TaggedChain {
             sum += v;
         }
         for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kChainWave);
+        if (!again && lane == 0) keep_request();
         return sum;
     }
-    // The end of the launch, by one lane that knows that every tile has published: true if a wait of this launch ran out.
-    // An error word that holds anything else is made 0 (it held whatever the workspace did).
-    __device__ __forceinline__ bool close(uint32_t* err_flag) const {
-        __threadfence();
-        const uint64_t left = __hip_atomic_load(&ws->deferred, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool bad = __hip_atomic_load(err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mark();
-        if (left == tag && !bad) *s_more = 1;
-        if (!bad) __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return bad;
+    // The end of the call, by the lane that writes it.
+    __device__ __forceinline__ void close(uint32_t* err_flag) const {
+        __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // After a tile, by the whole workgroup: true if there is another one for it to sample, again and now with its dense rows.
-    // One wave looks for it: a tile's note may come between two waves' looks (it then writes its rows itself), and the waves
-    // of a workgroup must go on with one tile.  s_tile, s_arrived: in LDS, of the tile that is done.
-    __device__ __forceinline__ bool next(int64_t& tile, int64_t* s_tile, int32_t* s_arrived, int lane) {
-        if (!last_wg) return false;
+    // One wave looks for it: other workgroups take tiles too, and the waves of one must go on with the same.  s_tile, s_arrived: in
+    // LDS, of the tile that is done; call(): the Call.
+    template <class GetCall>
+    __device__ __forceinline__ bool next(int64_t& tile, int32_t per_tile, int64_t* s_tile, int32_t* s_arrived, int lane, const GetCall& call) {
+        if (!__builtin_amdgcn_readfirstlane(*s_todo)) return false;
         __syncthreads();
-        const int64_t last = again ? last_tile : tile;
         if (threadIdx.x < kChainWave) {
-            uint64_t found = 0;
-            int64_t t0 = again ? tile + 1 : 0;
-            if (!*s_more) t0 = last;
-            for (; t0 < last; t0 += kChainWave) {
-                uint64_t w = 0;
-                if (t0 + lane < last) w = __hip_atomic_load(&ws->status[t0 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                found = __ballot(w >> kTagShift == tag && (w & kDeferredBit));
-                if (found) break;
+            const Call c = call();
+            bool asked = *s_todo == kAsked;
+            if (!asked) {
+                note(tile, per_tile, lane, c);
+                asked = !ask_nearest(tile, lane);
             }
+            const int64_t t = asked ? take(again ? tile : 0, per_tile, lane, c) : -1;
             if (lane == 0) {
-                *s_tile = found ? t0 + __builtin_ctzll(found) : -1;
+                *s_tile = t;
                 *s_arrived = 0;
+                *s_todo = kAsked;
             }
         }
         __syncthreads();
-        const int64_t t = *s_tile;
-        if (__builtin_amdgcn_readfirstlane((int)(t < 0))) return false;
-        last_tile = last;
+        const int t = __builtin_amdgcn_readfirstlane((int)*s_tile);      // (a tile's number has 31 bits: grid.x)
+        if (t < 0) return false;
         again = true;
         tile = t;
         return true;
+    }
+
+   private:
+    __device__ __forceinline__ bool published(uint64_t w) const { return w >> kTagShift == tag && (w & kPublishedBit); }
+    // (the word of a tile that was asked before it started, too)
+    __device__ __forceinline__ void keep_request() const {
+        if (old >> kTagShift == tag && (old & kAskedBit)) *s_todo = kAsked;
+    }
+    // these by one whole wave
+    __device__ __forceinline__ void note(int64_t tile, int32_t per_tile, int lane, const Call& c) const {
+        if (lane == 0) {
+            if ((tile + 1) * per_tile >= c.queries) {
+                __hip_atomic_store(c.err_flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(c.end, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (c.total_out) __hip_atomic_store(c.total_out, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __threadfence();      // (whoever samples the tile again overwrites these)
+            __hip_atomic_fetch_or(&ws->status[tile], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __threadfence();
+        __builtin_amdgcn_wave_barrier();      // no lane looks for missing tiles before the note is made
+    }
+    // false if tile t has published
+    __device__ __forceinline__ bool ask(int64_t t, int lane) const {
+        int asked = 0;
+        if (lane == 0) {
+            uint64_t w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (!asked && !published(w)) {
+                const uint64_t with = (w >> kTagShift == tag ? w : tag << kTagShift) | kAskedBit;
+                asked = __hip_atomic_compare_exchange_strong(&ws->status[t], &w, with, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        return __builtin_amdgcn_readfirstlane(asked) != 0;
+    }
+    // false if no tile before `tile` is missing
+    __device__ __forceinline__ bool ask_nearest(int64_t tile, int lane) const {
+        for (int64_t end = tile; end > 0;) {
+            const int64_t t = end - 1 - lane;
+            uint64_t w = tag << kTagShift | kPublishedBit;
+            if (t >= 0) w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t missing = __ballot(!published(w));
+            if (!missing) end -= kChainWave;
+            else if (ask(end - 1 - __builtin_ctzll(missing), lane)) return true;
+        }
+        return false;
+    }
+    // A noted tile from `from` on, to be sampled again; -1: none before the first missing tile.
+    __device__ __forceinline__ int64_t take(int64_t from, int32_t per_tile, int lane, const Call& c) const {
+        for (int64_t t0 = from; t0 * per_tile < c.queries;) {
+            const int64_t t = t0 + lane;
+            uint64_t w = tag << kTagShift | kPublishedBit;
+            if (t * per_tile < c.queries) w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t missing = __ballot(!published(w));
+            const uint64_t noted = __ballot((w & kDeferredBit) != 0) & (missing ? (missing & -missing) - 1 : ~0ull);
+            if (noted) {
+                const int64_t found = t0 + __builtin_ctzll(noted);
+                int taken = 0;
+                if (lane == 0) {
+                    taken = (__hip_atomic_fetch_and(&ws->status[found], ~kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kDeferredBit) != 0;
+                    if (taken) __hip_atomic_fetch_add(&ws->sampled_again, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (__builtin_amdgcn_readfirstlane(taken)) return found;
+            } else if (missing) {
+                return -1;
+            } else {
+                t0 += kChainWave;
+            }
+        }
+        return -1;
     }
 };
 

@@ -440,6 +440,11 @@ __device__ __forceinline__ const SampleArgs& arguments_anew() {
     return *(const SampleArgs*)p;
 }
 
+__device__ __forceinline__ TaggedChain::Call call_of(const SampleArgs& p) {
+    const int64_t Q = p.Q_dev ? min(p.Q, *p.Q_dev) : p.Q;
+    return TaggedChain::Call{Q, &p.rowptr[Q], p.total_out, p.err_flag};
+}
+
 // How a kernel numbers its tiles and learns the dense entries of the tiles before one.
 enum Scan : int {
     kNoScan,      // padded rows only
@@ -451,12 +456,12 @@ struct TileChain {
     static constexpr bool kTagged = SCAN == kTags;
     TaggedChain tags;
     int64_t tile;
-    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t Q, int64_t* s_tile_base, int32_t* s_arrived, int32_t* s_more) {
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived, int32_t* s_todo) {
         if (threadIdx.x == 0) *s_arrived = 0;
         if (kTagged) {
             tile = (int64_t)blockIdx.x + p.first_ticket;
-            if (threadIdx.x == 0) *s_more = 0;
-            tags.start((tile + 1) * blockDim.x >= Q, s_more);
+            if (threadIdx.x == 0) *s_todo = 0;
+            tags.s_todo = s_todo;
             __syncthreads();
         } else {
             if (threadIdx.x == 0) *s_tile_base = (int64_t)atomicAdd(&static_cast<ScanWorkspace*>(p.scan_ws)->ticket, 1u);
@@ -466,24 +471,28 @@ struct TileChain {
         }
     }
     // for every tile of a workgroup
-    __device__ __forceinline__ void use(const SampleArgs& p) {
-        if (kTagged) tags.use(p.scan_ws, p.chain_tag);
+    __device__ __forceinline__ void begin(const SampleArgs& p) {
+        if (kTagged) tags.begin(p.scan_ws, p.chain_tag, tile);
+    }
+    // once what the wave's queries are has been read
+    __device__ __forceinline__ void begun() const {
+        if (kTagged) tags.begun();
     }
     __device__ __forceinline__ ScanWorkspace* ws(const SampleArgs& p) const { return static_cast<ScanWorkspace*>(p.scan_ws); }
     // one wave, at once, so that later tiles can look past this one
-    __device__ __forceinline__ void publish_total(const SampleArgs& p, int32_t total, int lane) const {
+    __device__ __forceinline__ void publish_total(const SampleArgs& p, int32_t total, int lane) {
         if (lane != 0) return;
         if (kTagged) tags.publish(tile, total);
         else if (tile > 0) __hip_atomic_store(&ws(p)->status[tile], kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // by the whole workgroup, after a tile: true if it has another one to sample
-    __device__ __forceinline__ bool next(int64_t* s_tile_base, int32_t* s_arrived, int lane) {
+    __device__ __forceinline__ bool next(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_arrived, int lane) {
         if (!kTagged) return false;
-        return tags.next(tile, s_tile_base, s_arrived, lane);
+        return tags.next(tile, (int32_t)blockDim.x, s_tile_base, s_arrived, lane, [&]() { return call_of(p); });
     }
     // one wave: the dense entries of the tiles before this one; -1 (kTags): the tile writes no dense rows
     __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
-        if (kTagged) return tags.exclusive(p.err_flag, tile, lane, p.defer_spins);
+        if (kTagged) return tags.exclusive(tile, lane, p.defer_spins);
         const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane) : 0;
         if (lane == 0)
             __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -491,7 +500,10 @@ struct TileChain {
     }
     // by the last query's lane, whose tile has looked back over every other one: true if any wait ran into its bound
     __device__ __forceinline__ bool failed(const SampleArgs& p) const {
-        if (kTagged) return tags.close(p.err_flag);
+        if (kTagged) {
+            tags.close(p.err_flag);
+            return false;
+        }
         __threadfence();
         return __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     }
@@ -500,10 +512,11 @@ struct TileChain {
 template <>
 struct TileChain<kNoScan> {
     int64_t tile;
-    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t, int64_t*, int32_t*, int32_t*)
+    __device__ __forceinline__ TileChain(const SampleArgs& p, int64_t*, int32_t*, int32_t*)
         : tile(p.xcd_remap ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) {}
-    __device__ __forceinline__ void use(const SampleArgs&) {}
-    __device__ __forceinline__ bool next(int64_t*, int32_t*, int) const { return false; }
+    __device__ __forceinline__ void begin(const SampleArgs&) {}
+    __device__ __forceinline__ void begun() const {}
+    __device__ __forceinline__ bool next(const SampleArgs&, int64_t*, int32_t*, int) const { return false; }
 };
 
 // Output stage of a fused kernel: chained scan over the workgroup tiles for the dense offsets, padded rows, dense rows and
@@ -513,7 +526,7 @@ struct TileChain<kNoScan> {
 // order measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
 template <bool CHAIN_FIRST, class Chain, class Load>
 __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_wave_sum, int32_t* s_arrived,
-                                             const Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
+                                             Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
                                              uint32_t f_mul, const Load& load) {
     const int32_t f = p.fanout;
     const int32_t inc = wave_inclusive_scan(k, lane);

@@ -53,7 +53,7 @@ struct SampleArgs {
     int32_t keep_nodes;    // node lines are likely to be read again soon: no non-temporal hint on them
     int32_t wide_offsets;  // edge array has 2^31 or more entries: 64-bit positions in LDS
     int32_t first_ticket;  // 0; tests of the chained scan's bounded wait pass 1: tile 0 then never exists
-    int32_t defer_spins;   // small grids: rounds of waiting after which a tile leaves its dense rows to the last one (kDeferSpins; tests: 0)
+    int32_t defer_spins;   // small grids: rounds of waiting for a tile that has not started (kDeferSpins; tests: -1, for any tile)
     int32_t scan_ready;    // scan_ws is as this launch needs it (multi-hop: one clearing launch for all hops that need it)
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
     uint64_t chain_tag;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)

@@ -66,7 +66,7 @@ tns_sample_kernel(const SampleArgs args, const int32_t stride, const uint32_t f_
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;      // fused: waves of the tile that have finished their searches
-    __shared__ int32_t s_more;
+    __shared__ int32_t s_todo;
     int lane = threadIdx.x & (kWave - 1), wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
@@ -80,7 +80,7 @@ tns_sample_kernel(const SampleArgs args, const int32_t stride, const uint32_t f_
         }
         return;
     }
-    TileChain<SCAN> tc(args, Q, &s_tile_base, &s_arrived, &s_more);
+    TileChain<SCAN> tc(args, &s_tile_base, &s_arrived, &s_todo);
     if (FUSED && tc.tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
 sample_tile:
     if (SCAN == kTags) {
@@ -91,7 +91,7 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.use(p);
+    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -122,6 +122,7 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
+    tc.begun();
     // the node's 128-byte line: header + the records of up to 7 blocks, newest first
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -463,7 +464,7 @@ sample_tile:
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
-    if (tc.next(&s_tile_base, &s_arrived, lane)) goto sample_tile;
+    if (tc.next(p, &s_tile_base, &s_arrived, lane)) goto sample_tile;
 }
 
 // ---- padding removal -------------------------------------------------------------------

@@ -29,7 +29,7 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;
-    __shared__ int32_t s_more;
+    __shared__ int32_t s_todo;
     int lane = threadIdx.x & (kWave - 1), wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
@@ -43,7 +43,7 @@ __global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUN
         }
         return;
     }
-    TileChain<SCAN> tc(args, Q, &s_tile_base, &s_arrived, &s_more);
+    TileChain<SCAN> tc(args, &s_tile_base, &s_arrived, &s_todo);
     if (FUSED && tc.tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
 sample_tile:
     if (SCAN == kTags) {
@@ -54,7 +54,7 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.use(p);
+    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -79,6 +79,7 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
+    tc.begun();
     // ---- node lines: eight lanes per line, handed over through LDS ------------------------------------
     uint32_t w[3 * kInlineSlots];     // the eight edge slots of the node's own line
     uint32_t h_degree, h_meta, h_ext0, h_ext12, h_fence0, h_fence1, h_fence2, h_dir;   // the node entry
@@ -276,7 +277,7 @@ sample_tile:
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
-    if (tc.next(&s_tile_base, &s_arrived, lane)) goto sample_tile;
+    if (tc.next(p, &s_tile_base, &s_arrived, lane)) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, bool FUSED>

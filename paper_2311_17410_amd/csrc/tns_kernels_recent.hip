@@ -49,7 +49,7 @@ constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes 
 // block i or an older one.  Top byte of `lo`: filled slots; of `hi`: 1 if the row holds an entry per slot.
 struct SlotHead { uint32_t lo, hi; };
 
-// Registers: small grids up to 128 and some scratch, because the workgroup of the last tile may sample others again (a loop around
+// Registers: small grids up to 128 and some scratch, because a workgroup may sample others' tiles again (a loop around
 // the kernel; they have one or two waves per SIMD, four at most).  Otherwise, fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
 // positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
 // all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
@@ -61,7 +61,7 @@ tns_sample_recent_kernel(const SampleArgs args, const int32_t stride, const uint
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[16];
     __shared__ int32_t s_arrived;      // fused: waves of the tile that have finished their searches
-    __shared__ int32_t s_more;
+    __shared__ int32_t s_todo;
     int lane = threadIdx.x & (kWave - 1), wave = wave_uniform((int32_t)(threadIdx.x >> 6));
     const int waves_per_wg = blockDim.x >> 6;
 
@@ -75,7 +75,7 @@ tns_sample_recent_kernel(const SampleArgs args, const int32_t stride, const uint
         }
         return;
     }
-    TileChain<SCAN> tc(args, Q, &s_tile_base, &s_arrived, &s_more);
+    TileChain<SCAN> tc(args, &s_tile_base, &s_arrived, &s_todo);
     if (FUSED && tc.tile * blockDim.x >= Q) return;      // (tests whose tiles start at 1)
 sample_tile:
     if (SCAN == kTags) {
@@ -86,7 +86,7 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.use(p);
+    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -119,6 +119,7 @@ sample_tile:
     bool ok = have && (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
     if (p.inst_rowptr) ok = ok && inst < p.num_instances;
     const uint32_t node = ok ? (uint32_t)(inst * p.num_nodes + v) : ~0u;      // the target's entry in the node table (a table of 2^32 lines does not exist)
+    tc.begun();
     // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
     u32x4 P[8];
     {
@@ -439,7 +440,7 @@ sample_tile:
         }
     }
     if (q < Q && p.out_count) __builtin_nontemporal_store(k, &p.out_count[q]);
-    if (tc.next(&s_tile_base, &s_arrived, lane)) goto sample_tile;
+    if (tc.next(p, &s_tile_base, &s_arrived, lane)) goto sample_tile;
 }
 
 template <bool PREFIX, bool INCL, typename pos_t, bool FUSED>

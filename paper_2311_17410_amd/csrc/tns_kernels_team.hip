@@ -19,8 +19,7 @@
 //             The flag is read here and not on the host: a captured call may be replayed after a deletion.
 // What bounds it is the chain of dependent reads (query, node, search, edge, look-back).  Its tiles tag what they publish
 // instead of having the scan state cleared by a launch before it and tickets taken (TaggedChain): 1024 queries 11.9 -> 8.5 us
-// per call, two hops from 600 and 4000 roots 17.3 -> 15.2 and 27.6 -> 24.5 (14.7 and 23.0 if every tile waited for as long as it takes,
-// which launches on several streams could do for good: TaggedChain).  Measured beside the kernels with a query per
+// per call, two hops from 600 and 4000 roots 17.2 -> 13.9 and 27.6 -> 23.4.  Measured beside the kernels with a query per
 // lane: see the rule in launch_sample.
 #include <type_traits>
 
@@ -75,7 +74,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     constexpr int kTileQueries = kTileWaves * kTeamsPerWave * CH;
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[kTileWaves];
-    __shared__ int32_t s_arrived, s_more;
+    __shared__ int32_t s_arrived, s_todo;
     __shared__ int32_t s_seq[kTileWaves][CH][kTeamsPerWave][ROUNDS * kTeam];      // nodes with deleted edges: the slots' edges
     int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int32_t f = args.fanout;
@@ -90,14 +89,14 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     }
     int64_t tile = (int64_t)blockIdx.x + args.first_ticket;
     if (tile * kTileQueries >= Q) return;      // (tests whose tiles start at 1)
-    if (threadIdx.x == 0) s_arrived = s_more = 0;
+    if (threadIdx.x == 0) s_arrived = s_todo = 0;
     __syncthreads();
     TaggedChain chain;
-    chain.start((tile + 1) * kTileQueries >= Q, &s_more);
+    chain.s_todo = &s_todo;
 sample_tile:
     new_tile(lane, wave);
     const SampleArgs& p = arguments_anew();
-    chain.use(p.scan_ws, p.chain_tag);
+    chain.begin(p.scan_ws, p.chain_tag, tile);
     const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
     // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
     const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
@@ -173,6 +172,7 @@ sample_tile:
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
+    chain.begun();
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -398,7 +398,7 @@ sample_tile:
 
     // ---- outputs --------------------------------------------------------------------------------
     if (is_last) {
-        const int64_t excl = chain.exclusive(p.err_flag, tile, lane, p.defer_spins);
+        const int64_t excl = chain.exclusive(tile, lane, p.defer_spins);
         if (lane == 0) s_tile_base = excl;
     }
     if (p.out_nbr) {
@@ -419,7 +419,7 @@ sample_tile:
     }
     lds_barrier();
     int64_t wave_row = s_tile_base;
-    const bool dense = wave_row >= 0;      // (or the last tile's workgroup writes them)
+    const bool dense = wave_row >= 0;      // (or another workgroup writes them)
     for (int i = 0; i < wave; ++i) wave_row += s_wave_sum[i];
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
@@ -431,9 +431,8 @@ sample_tile:
         if (j == 0) {
             p.rowptr[q] = row;
             if (q == Q - 1) {
-                // The last query's tile has looked back over every other tile.  If any wait ran into its bound the
-                // dense rows are not valid: the total then reads 0, so that a hop chained to this one has no queries.
-                const int64_t tot = chain.close(p.err_flag) ? 0 : row + k[u];
+                const int64_t tot = row + k[u];
+                chain.close(p.err_flag);
                 p.rowptr[Q] = tot;
                 if (p.total_out) *p.total_out = tot;
             }
@@ -448,7 +447,7 @@ sample_tile:
             }
         }
     }
-    if (chain.next(tile, &s_tile_base, &s_arrived, lane)) goto sample_tile;
+    if (chain.next(tile, kTileQueries, &s_tile_base, &s_arrived, lane, [&]() { return call_of(p); })) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, int CH, int ROUNDS>

@@ -12,6 +12,7 @@ extern "C" TNS_API void tns_test_cache_no_wait(tns_cache* cache);
 // reports the time-out and the dense outputs are not valid.
 #define TNS_TEST_FLAG_LOST_TILE 64
 
-// Batches without tickets: from now on a tile of this plan's calls that does not find the totals before it at its first look leaves its
-// dense rows to the last one.  The results are what they always are.
+// Batches without tickets: from now on a tile of this plan's calls that does not find the totals before it at its first look makes
+// room, also where the missing tiles have started.  The results are what they always are.  The 64-bit word at byte 8 of the
+// workspace counts the tiles that were sampled again.
 extern "C" TNS_API void tns_test_defer(tns_plan* plan);

@@ -52,7 +52,7 @@ struct Group {
     std::vector<Fiber> lane;
     int live = 0;
     int64_t base;                  // the program's LDS
-    int32_t wave_sum[kWaves], arrived, more;
+    int32_t wave_sum[kWaves], arrived, todo;
 };
 inline Fiber* me;
 inline jmp_buf scheduler;

@@ -207,8 +207,8 @@ def test_a_tile_that_never_reports(B, Q):
 @pytest.mark.parametrize("policy", [0, 1])
 @pytest.mark.parametrize("Q,fanout,instances", [(1, 10, 1), (130, 3, 1), (4000, 64, 1), (16_500, 10, 1), (30_001, 20, 1), (40_000, 5, 3), (100_000, 10, 1), (60_000, 64, 1),
                                                 ((1 << 18) - 1, 10, 1)])
-def test_tiles_that_leave_their_dense_rows_to_the_last(B, oracle_lib, policy, Q, fanout, instances, layout):
-    # a tile that does not find the totals before it at once makes room; the last tile's workgroup samples it again
+def test_tiles_that_leave_their_dense_rows_to_another(B, oracle_lib, policy, Q, fanout, instances, layout):
+    # a tile that does not find the totals before it at once makes room; another one's workgroup samples it again
     import ctypes
 
     import torch
@@ -234,10 +234,14 @@ def test_tiles_that_leave_their_dense_rows_to_the_last(B, oracle_lib, policy, Q,
     for i in range(4):
         for n in ("rowptr", "cmp_eid", "count", "eid"):
             out[n].fill_(-3)
+        if i == 0:
+            out["workspace"][8:16].zero_()
         plan.run(*args, out=out)
         torch.cuda.synchronize()
         assert not plan.status(out["workspace"])
         assert_same(results(out, Q, fanout), ref, oracle_lib, f"call {i}")
+    again = int(out["workspace"][8:16].cpu().numpy().view(np.int64)[0])      # tiles sampled again in four calls
+    assert again > 0 if Q >= 30_000 else again >= 0, again
     plan.close()
 
 
