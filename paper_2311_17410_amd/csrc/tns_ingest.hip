@@ -592,9 +592,6 @@ constexpr int kFastMaxTiles = 512;
 constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^21 edges
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
 constexpr int kPlanThreads = 512;                       // k_fast_plan: one sorted position per thread, 512 per tile
-// Most tiles that go without tickets: a quarter of the two per compute unit that the chip holds at once.  XCDs start the workgroups
-// of two queues in either order, and a process has four hardware queues: launches that fit side by side cannot hold one another up.
-constexpr int kPlanResident = 128;
 // Batches planned and applied by one workgroup (k_small_batch).  us per batch with the sampling of its events, with it / with
 // the same in two launches and a bitonic sort, which above this size was slower than the five kernels (3000 edges over
 // 2^18 nodes 73.2 / 51.9 us without the sampling): 600 edges over 2^18 nodes 46 / 56, 2000 over 2^18 57 / 68, 2000 over 2^16
@@ -881,9 +878,9 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     __shared__ int32_t s_heads[kWaves], s_end;
     __shared__ int32_t s_start[kPlanThreads + 1];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    // tiles are numbered in the order workgroups start or, where they are few enough, as the workgroups are (a ticket is an atomic
-    // on one word, 18 ns each)
-    if (t == 0) s_tile = plan_tiles <= kPlanResident ? (int64_t)blockIdx.x : (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
+    // tiles are numbered in the order workgroups start: other work can hold an XCD for any time, and a tile must not wait for one
+    // that has not started (a ticket is an atomic on one word, 18 ns each)
+    if (t == 0) s_tile = (int64_t)atomicAdd(&scans.ws[0]->ticket, 1u);
     __syncthreads();
     const int64_t tile = s_tile, p0 = tile * kPlanThreads, p = p0 + t;
     const uint64_t k = p < a.m ? key[p] : 0, before = p > 0 && p < a.m ? key[p - 1] : 0;

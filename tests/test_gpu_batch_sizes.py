@@ -93,8 +93,8 @@ def test_ingestion_batches_around_the_small_plan(B, oracle_lib, batch, nodes):
 
 
 @pytest.mark.parametrize("batch", [(1 << 16) - 1, 1 << 16, (1 << 16) + 1, (1 << 18) - 1, 1 << 18, (1 << 18) + 1])
-def test_ingestion_batches_around_the_plan_without_tickets(B, oracle_lib, batch):
-    # 128, 129, 512 and 513 tiles of sorted positions, the first without tickets; a node of a tenth of every batch spans dozens of them
+def test_ingestion_batches_of_many_plan_tiles(B, oracle_lib, batch):
+    # 128, 129, 512 and 513 tiles of sorted positions; a node of a tenth of every batch spans dozens of them
     import torch
     rng = np.random.default_rng(batch)
     n, nodes = 2 * batch, 30_000
