@@ -793,12 +793,12 @@ static int fill_sample_args(tns_plan* plan, int64_t Q, const int32_t* d_targets,
     a.fanout = plan->cfg.fanout;
     a.policy = plan->cfg.policy;
     a.inclusive_end = plan->cfg.inclusive_end;
-    // A node line is read with the non-temporal hint unless other queries will come back to it: it should not push edge lines out of
-    // the caches.  They do where an instance's table is at most half of the chip's L2, and where degrees are skewed, which long
-    // lists show: a directory of at least a sixteenth of the nodes.  Hint / none, us: 256 graphs of 4096 nodes, windowed 1498 / 1345;
-    // power-law ids, 2^17 nodes 229 / 222, 2^18 553 / 521, 2^19 1183 / 1093 (uniform policy 1807 / 1745), 3 * 10^6 2747 / 2499; uniform ids,
-    // 2^17 nodes 185 / 180, 2^18 363 / 367, 2^19 722 / 766, 2^20 1439 / 1499.
-    a.keep_nodes = plan->cfg.num_nodes <= (int64_t(1) << 17) || a.num_dir * 16 >= plan->cfg.num_nodes * plan->cfg.num_instances ? 1 : 0;
+    if (!plan->pstore) {
+        int64_t blocks = 0;
+        for (int32_t i = 0; i < plan->cfg.num_instances && plan->cfg.num_nodes > tns::kSmallTable; ++i)
+            blocks += plan->dev ? plan->dev->totals[(size_t)i].blocks : plan->store->totals(i).blocks;
+        a.keep_nodes = tns::node_lines_stay(plan->cfg.num_nodes, plan->cfg.num_nodes * plan->cfg.num_instances, a.num_dir, blocks) ? 1 : 0;
+    }
     a.xcd_remap = (plan->cfg.flags & TNS_FLAG_NO_XCD_REMAP) ? 0 : 1;
     a.defer_spins = plan->defer_spins;
     a.first_ticket = (plan->cfg.flags & TNS_TEST_FLAG_LOST_TILE) ? 1 : 0;
