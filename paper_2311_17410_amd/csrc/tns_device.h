@@ -604,9 +604,9 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
     }
 }
 
-// Launches `grid` workgroups of a kernel with a query per lane in the form that the batch asks for.
+// Launches `grid` workgroups, of `tile` queries each, of a kernel with a query per lane in the form that the batch asks for.
 template <bool FUSED, class Launch>
-hipError_t launch_tiles(const SampleArgs& a, int64_t grid, hipStream_t stream, const Launch& launch) {
+hipError_t launch_tiles(const SampleArgs& a, int64_t grid, int64_t tile, hipStream_t stream, const Launch& launch) {
     SampleArgs b = a;
     if (!FUSED) {
         if (grid > 0) launch(std::integral_constant<int, kNoScan>{}, b);
@@ -615,6 +615,8 @@ hipError_t launch_tiles(const SampleArgs& a, int64_t grid, hipStream_t stream, c
     if constexpr (FUSED) {
         if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
         if (grid > 0 && a.Q <= tagged_queries(a.fanout)) {
+            // (sixteen waves and 64 slots would not fit; the LDS of a wave's rows keeps such workgroups smaller)
+            if (tile * a.fanout >= (int64_t(1) << kTotalBits)) return hipErrorInvalidValue;
             const hipError_t e = ready_tags(b, grid, stream);
             if (e != hipSuccess) return e;
             launch(std::integral_constant<int, kTags>{}, b);

@@ -454,7 +454,7 @@ sample_tile:
 
     auto load = [&](GatherRegs& g, int32_t it0) { gather_load<pos_t, POLICY == 1>(g, p, f_mul, stride, w_pos, lane, it0, k); };
     if constexpr (FUSED) {
-        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+        fused_output<false>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         wave_lds_sync();
         GatherRegs g;
@@ -609,7 +609,7 @@ hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((tns_sample_kernel<POLICY, INCL, pos_t, COUNT, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds,
                            stream, b, stride, slot_multiplier(a.fanout), (uint32_t)chunk);
     };
-    return launch_tiles<FUSED>(a, grid, stream, launch);
+    return launch_tiles<FUSED>(a, grid, per_wg, stream, launch);
 }
 
 }  // namespace

@@ -268,7 +268,7 @@ sample_tile:
         gather_load<pos_t, POLICY == 1>(g, p, f_mul, rs * 4 / (int32_t)sizeof(pos_t), w_pos, lane, it0, k);
     };
     if constexpr (FUSED) {
-        fused_output<POLICY == 0>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+        fused_output<false>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
@@ -302,7 +302,7 @@ hipError_t launch_prefix_t(const SampleArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((tns_sample_prefix_kernel<POLICY, INCL, pos_t, COUNT, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave),
                            lds, stream, b, rs, slot_multiplier(f), gshift, (uint32_t)chunk);
     };
-    return launch_tiles<FUSED>(a, grid, stream, launch);
+    return launch_tiles<FUSED>(a, grid, per_wg, stream, launch);
 }
 
 }  // namespace

@@ -196,7 +196,9 @@ sample_tile:
             const int32_t size = rec_size(r);
             cnt[j] = in ? size : 0;
             end_slot[j] = (pos_t)(rec_off(r) + size);
-            // (of a block's slots, the first and the last one lie on different sides of a time inside it)
+            // What block() does, written out: called here it takes 76 registers instead of 68 without the scan, a wave per SIMD, and 97
+            // instead of 89 with tickets and 64-bit positions.  (Of a block's slots, the first and the last one lie on different
+            // sides of a time inside it.)
             if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_lo = 1; w.d_n = size - 2; end_block = j; }
             if (in && w.tb > r.t_min) { b_off = rec_off(r); b_lo = 1; b_n = size - 2; start_block = j; newer = whole; }
             whole += in && before_end(r.t_max) ? size : 0;
@@ -473,7 +475,7 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((tns_sample_recent_kernel<PREFIX, INCL, pos_t, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b,
                            stride, slot_multiplier(a.fanout), (uint32_t)chunk);
     };
-    return launch_tiles<FUSED>(a, grid, stream, launch);
+    return launch_tiles<FUSED>(a, grid, per_wg, stream, launch);
 }
 
 }  // namespace
