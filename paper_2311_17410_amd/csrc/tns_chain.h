@@ -24,7 +24,9 @@ struct ScanWorkspace {
     uint32_t ticket;
     uint32_t error;
     uint64_t sampled_again;   // tagged chain: tiles, counted on from whatever this held (read by tests)
-    uint32_t pad[60];
+    uint64_t failed;          // tagged chain: the tag of a launch in which a wait ran out
+    uint32_t noted;           // tagged chain: half the tag of a launch in which a tile has made room
+    uint32_t pad[57];
     uint64_t status[1];   // [number of tiles]
 };
 
@@ -86,61 +88,58 @@ __device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_
 // are taken at 18 ns each (14 us for the 782 tiles of 10^5 queries).  Here a tile's word carries a tag next to the total, and
 // a word with another tag has not been written yet, whatever the workspace held before.  The host draws a tag anew for every
 // launch.  A captured launch is replayed with the tag it has, over words that the replay before may have left, so that there the
-// state is cleared by a launch of its own (may_be_replayed).  Memory that by chance holds the tag of a launch: one word in 2^44.
+// state is cleared by a launch of its own (may_be_replayed).  Memory that by chance holds the tag of a launch: one word in 2^46.
 //
 // Every tile reads the totals of all tiles before it, four words per lane at a time; there are no prefixes to wait for.  Tiles
 // are numbered as the workgroups are, and a tile may find that one before it has not even started: other work can hold an XCD for
 // any time, and waiting tiles of two launches could each fill an XCD that the other one's earlier tiles need.  So a tile waits for
 // tiles that have started, which publish without waiting for anything, and no more than about two milliseconds (kDeferSpins,
 // hundreds of times what a tile takes) for one that has not.  Then it makes room: it leaves its dense rows out, notes that in its
-// word, and asks the nearest missing tile, in that tile's word, to see to it.  What a word held is what publishing it returns, so that
-// either the request is seen, or whoever asks sees that there is nothing to wait for any more.  A workgroup that was asked has either
-// made room itself and asked a tile further back, or nothing is missing before its tile and before those that asked it: it
-// samples the noted tiles up to the first missing one again, beside others that do the same.  The last tile, if it makes room,
-// first leaves the end of the call as it would be if a tile never reported.  What that can cost: 10^5 queries over power-law ids with
-// 770 of their tiles sampled again, most of them by one workgroup, took 5.5 ms (7 us a tile) instead of 17 us.
-// us per call, 2^21 edges, fan-out 10, tickets and clearing launch / this, recent policy, uniform ids: 65537 queries 22.6 /
-// 13.4, 10^5 27.8 / 15.7, 2 * 10^5 37.0 / 25.3, 2^18 - 1 36.9 / 29.2; power-law ids 26.7 / 17.8, 32.5 / 20.5, 40.8 / 28.7, 38.0 / 30.5; uniform
-// policy, power-law ids 38.8 / 32.0, 49.3 / 38.9, 66.8 / 58.0, 77.9 / 66.4; prefix layout, recent 32.4 / 23.5, 37.4 / 25.5, 44.7 /
-// 32.6, 41.2 / 35.5 (the second figures without tiles that make room).  Both forms in one kernel, chosen at run time, cost the large batches of the prefix layout 1 to 4 %.
+// word and the launch's mark in the workspace's head.  Every tile says that it has started before it reads the head, so that whoever
+// starts after the note sees the mark.  Workgroups that have made room or seen the mark look, when their own tile is done, for
+// noted tiles and sample them again, beside one another, up to the first tile that has not started: that one will see the mark.
+// The last tile, if it makes room, first leaves the end of the call as it would be if a tile never reported.
+// What that can cost: 10^5 queries over power-law ids with 775 of their tiles sampled again, most of them by one workgroup, took
+// 6.2 ms (8 us a tile) instead of 25 us.
+// us per call, 2^21 edges, fan-out 10, tickets and clearing launch / this, 65537, 10^5, 2 * 10^5 and 2^18 - 1 queries: recent policy,
+// uniform ids 22.2 / 15.2, 27.9 / 19.6, 37.4 / 30.4, 37.0 / 35.5, power-law ids 26.9 / 20.9, 32.9 / 24.9, 41.1 / 34.5, 38.2 / 36.9; uniform
+// policy, power-law ids 39.3 / 33.2, 49.7 / 39.6, 68.5 / 58.2, 77.9 / 65.2; prefix layout, uniform ids, recent 32.3 / 14.4, 38.1 / 17.1,
+// 44.9 / 28.5, 41.8 / 32.8, uniform policy 30.6 / 21.3, 36.3 / 23.5, 44.7 / 31.8, 44.7 / 34.7.  Both forms in one kernel, chosen at run time, cost
+// the large batches of the prefix layout 1 to 4 %.
 constexpr int kTotalBits = 16;                        // a tile's total is below 2^16
-constexpr int kTagShift = kTotalBits + 4;
-constexpr uint64_t kDeferredBit = uint64_t(1) << kTotalBits;          // made room: its dense rows are to be written
-constexpr uint64_t kAskedBit = kDeferredBit << 1;                     // others wait for it to see to noted tiles
-constexpr uint64_t kStartedBit = kDeferredBit << 2, kPublishedBit = kDeferredBit << 3;
+constexpr int kTagShift = kTotalBits + 2;
+constexpr uint64_t kNotedBit = uint64_t(1) << kTotalBits;             // made room: its dense rows are to be written
+constexpr uint64_t kPublishedBit = kNotedBit << 1;                    // (started, but not published: the tag alone)
 
 // Tile t's word is status[t].
 struct TaggedChain {
-    struct Call {            // what only a tile that makes room or was asked needs
+    struct Call {            // what only a tile that makes room or has others to see to needs
         int64_t queries;
         int64_t *end, *total_out;
         uint32_t* err_flag;
     };
     ScanWorkspace* ws;
-    uint64_t tag, old = 0;   // old: what the tile's word held (one lane)
+    uint64_t tag;
     int32_t* s_todo;         // LDS, 0 before: what is left to do when the tile is done
     bool again = false;      // sampling a noted tile
-    enum Todo : int32_t { kAsked = 1, kMakeRoom = 2 };
-    // for every tile of a workgroup, inside the loop: the compiler waits before a loop for what was requested before it
+    enum Todo : int32_t { kSeeToNoted = 1, kMakeRoom = 2 };
+    // for every tile of a workgroup
     __device__ __forceinline__ void begin(void* scan_ws, uint64_t launch_tag, int64_t tile) {
         ws = static_cast<ScanWorkspace*>(scan_ws);
         tag = launch_tag;
-        if (!again && threadIdx.x == 0)
-            old = __hip_atomic_exchange(&ws->status[tile], tag << kTagShift | kStartedBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!again && threadIdx.x == 0) __hip_atomic_store(&ws->status[tile], tag << kTagShift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // before this wave's sums are counted in
-    __device__ __forceinline__ void begun() const {
-        if (!again && threadIdx.x == 0) keep_request();
-    }
+    // before a wave's sums are counted in: the tile's start is known to all before its total is, and before its workgroup reads the head
+    __device__ __forceinline__ void begun() const { wait_for_stores(); }
     // by one lane
-    __device__ __forceinline__ void publish(int64_t tile, int32_t total) {
+    __device__ __forceinline__ void publish(int64_t tile, int32_t total) const {
         if (again) return;
-        old = __hip_atomic_exchange(&ws->status[tile], tag << kTagShift | kStartedBit | kPublishedBit | (uint64_t)total, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ws->status[tile], tag << kTagShift | kPublishedBit | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // Sum of the totals of all tiles before `tile` (called by one whole wave, whose lane 0 has published): four words per lane in
-    // flight.  -1: the tile has waited for long enough, writes no dense rows, and is noted by next().
+    // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.  -1: the tile has
+    // waited for long enough, writes no dense rows, and is noted by next().
     __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins) const {
+        const uint32_t noted = __hip_atomic_load(&ws->noted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int64_t sum = 0;
         int spins = 0;
         for (int64_t t0 = 0; t0 < tile; t0 += 4 * kChainWave) {
@@ -150,34 +149,41 @@ struct TaggedChain {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int64_t t = t0 + i * kChainWave + lane;
-                    w[i] = tag << kTagShift | kStartedBit | kPublishedBit;
+                    w[i] = tag << kTagShift | kPublishedBit;
                     if (t < tile) w[i] = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     ready = ready && published(w[i]);
-                    started = started && w[i] >> kTagShift == tag && (w[i] & kStartedBit);
+                    started = started && w[i] >> kTagShift == tag;
                 }
                 if (!__ballot(!ready)) break;
-                if (++spins > (defer_spins < 0 || __ballot(!started) ? defer_spins : kSpinLimit)) {
-                    if (lane == 0) *s_todo = kMakeRoom;
-                    return -1;
-                }
-                if (spins < 16) __builtin_amdgcn_s_sleep(2);
+                const bool wait = defer_spins >= 0 && !__ballot(!started);
+                if (++spins > (wait ? kSpinLimit : defer_spins)) {
+                    if (!wait) {
+                        wait_for_stores();      // the total, before another wave notes
+                        if (lane == 0) *s_todo = kMakeRoom;
+                        return -1;
+                    }
+                    if (spins > kSpinLimit + 1) return 0;
+                    fail(lane);      // and a last look: what publishes after it closes a call that has failed
+                } else if (spins < 16) __builtin_amdgcn_s_sleep(2);
                 else __builtin_amdgcn_s_sleep(16);
             }
             int64_t v = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & (kDeferredBit - 1ull));
+            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & (kNotedBit - 1ull));
             sum += v;
         }
         for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kChainWave);
-        if (!again && lane == 0) keep_request();
+        if (lane == 0 && noted == (uint32_t)tag) *s_todo = kSeeToNoted;
         return sum;
     }
-    // The end of the call, by the lane that writes it.
-    __device__ __forceinline__ void close(uint32_t* err_flag) const {
-        __hip_atomic_store(err_flag, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The end of the call, by the lane that writes it, all tiles having published: true if a wait of this launch ran out.
+    __device__ __forceinline__ bool close(uint32_t* err_flag) const {
+        const bool bad = __hip_atomic_load(&ws->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+        __hip_atomic_store(err_flag, bad ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return bad;
     }
     // After a tile, by the whole workgroup: true if there is another one for it to sample, again and now with its dense rows.
     // One wave looks for it: other workgroups take tiles too, and the waves of one must go on with the same.  s_tile, s_arrived: in
@@ -188,16 +194,12 @@ struct TaggedChain {
         __syncthreads();
         if (threadIdx.x < kChainWave) {
             const Call c = call();
-            bool asked = *s_todo == kAsked;
-            if (!asked) {
-                note(tile, per_tile, lane, c);
-                asked = !ask_nearest(tile, lane);
-            }
-            const int64_t t = asked ? take(again ? tile : 0, per_tile, lane, c) : -1;
+            if (*s_todo == kMakeRoom) note(tile, per_tile, lane, c);
+            const int64_t t = take(again ? tile : 0, per_tile, lane, c);
             if (lane == 0) {
                 *s_tile = t;
                 *s_arrived = 0;
-                *s_todo = kAsked;
+                *s_todo = kSeeToNoted;
             }
         }
         __syncthreads();
@@ -209,12 +211,17 @@ struct TaggedChain {
     }
 
    private:
-    __device__ __forceinline__ bool published(uint64_t w) const { return w >> kTagShift == tag && (w & kPublishedBit); }
-    // (the word of a tile that was asked before it started, too)
-    __device__ __forceinline__ void keep_request() const {
-        if (old >> kTagShift == tag && (old & kAskedBit)) *s_todo = kAsked;
+    __device__ __forceinline__ static void wait_for_stores() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0): as a rule nothing is on its way where this is called
+        asm volatile("" ::: "memory");
     }
+    __device__ __forceinline__ bool published(uint64_t w) const { return w >> kTagShift == tag && (w & kPublishedBit); }
     // these by one whole wave
+    __device__ __forceinline__ void fail(int lane) const {
+        if (lane == 0) __hip_atomic_store(&ws->failed, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+    }
     __device__ __forceinline__ void note(int64_t tile, int32_t per_tile, int lane, const Call& c) const {
         if (lane == 0) {
             if ((tile + 1) * per_tile >= c.queries) {
@@ -223,55 +230,37 @@ struct TaggedChain {
                 if (c.total_out) __hip_atomic_store(c.total_out, (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __threadfence();      // (whoever samples the tile again overwrites these)
-            __hip_atomic_fetch_or(&ws->status[tile], kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_or(&ws->status[tile], kNotedBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence();
+            __hip_atomic_store(&ws->noted, (uint32_t)tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __threadfence();
         __builtin_amdgcn_wave_barrier();      // no lane looks for missing tiles before the note is made
     }
-    // false if tile t has published
-    __device__ __forceinline__ bool ask(int64_t t, int lane) const {
-        int asked = 0;
-        if (lane == 0) {
-            uint64_t w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while (!asked && !published(w)) {
-                const uint64_t with = (w >> kTagShift == tag ? w : tag << kTagShift) | kAskedBit;
-                asked = __hip_atomic_compare_exchange_strong(&ws->status[t], &w, with, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        return __builtin_amdgcn_readfirstlane(asked) != 0;
-    }
-    // false if no tile before `tile` is missing
-    __device__ __forceinline__ bool ask_nearest(int64_t tile, int lane) const {
-        for (int64_t end = tile; end > 0;) {
-            const int64_t t = end - 1 - lane;
-            uint64_t w = tag << kTagShift | kPublishedBit;
-            if (t >= 0) w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t missing = __ballot(!published(w));
-            if (!missing) end -= kChainWave;
-            else if (ask(end - 1 - __builtin_ctzll(missing), lane)) return true;
-        }
-        return false;
-    }
-    // A noted tile from `from` on, to be sampled again; -1: none before the first missing tile.
+    // A noted tile from `from` on, to be sampled again; -1: none before the first tile that has not started, or a wait ran out.
     __device__ __forceinline__ int64_t take(int64_t from, int32_t per_tile, int lane, const Call& c) const {
+        int spins = 0;
         for (int64_t t0 = from; t0 * per_tile < c.queries;) {
             const int64_t t = t0 + lane;
             uint64_t w = tag << kTagShift | kPublishedBit;
             if (t * per_tile < c.queries) w = __hip_atomic_load(&ws->status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint64_t missing = __ballot(!published(w));
-            const uint64_t noted = __ballot((w & kDeferredBit) != 0) & (missing ? (missing & -missing) - 1 : ~0ull);
+            const uint64_t first = missing & -missing;
+            const uint64_t noted = __ballot((w & kNotedBit) != 0) & (first - 1);      // (none missing: all lanes)
             if (noted) {
                 const int64_t found = t0 + __builtin_ctzll(noted);
                 int taken = 0;
                 if (lane == 0) {
-                    taken = (__hip_atomic_fetch_and(&ws->status[found], ~kDeferredBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kDeferredBit) != 0;
+                    taken = (__hip_atomic_fetch_and(&ws->status[found], ~kNotedBit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kNotedBit) != 0;
                     if (taken) __hip_atomic_fetch_add(&ws->sampled_again, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 if (__builtin_amdgcn_readfirstlane(taken)) return found;
-            } else if (missing) {
-                return -1;
-            } else {
+            } else if (!missing) {
                 t0 += kChainWave;
+            } else {
+                if (first & __ballot(w >> kTagShift != tag) || ++spins > kSpinLimit + 1) return -1;
+                if (spins > kSpinLimit) fail(lane);
+                else __builtin_amdgcn_s_sleep(16);
             }
         }
         return -1;

@@ -128,7 +128,8 @@ template <class Qual>
 __device__ __forceinline__ void narrow4(int32_t& lo, int32_t& n, int32_t rest, const Qual& qual) {
     while (n > rest) {
         const int32_t i1 = n >> 2, i2 = n >> 1, i3 = (int32_t)((3 * (int64_t)n) >> 2);
-        const bool b1 = qual(lo + i1), b2 = qual(lo + i2), b3 = qual(lo + i3);
+        int32_t b1 = qual(lo + i1), b2 = qual(lo + i2), b3 = qual(lo + i3);
+        asm("" : "+v"(b1), "+v"(b2), "+v"(b3));      // (the compiler would read one after the other, each where it is first needed)
         const int32_t skip = b3 ? i3 + 1 : (b2 ? i2 + 1 : (b1 ? i1 + 1 : 0));
         const int32_t end = !b1 ? i1 : (!b2 ? i2 : (!b3 ? i3 : n));
         lo += skip;
@@ -474,7 +475,7 @@ struct TileChain {
     __device__ __forceinline__ void begin(const SampleArgs& p) {
         if (kTagged) tags.begin(p.scan_ws, p.chain_tag, tile);
     }
-    // once what the wave's queries are has been read
+    // before the wave's sum is counted in
     __device__ __forceinline__ void begun() const {
         if (kTagged) tags.begun();
     }
@@ -500,10 +501,7 @@ struct TileChain {
     }
     // by the last query's lane, whose tile has looked back over every other one: true if any wait ran into its bound
     __device__ __forceinline__ bool failed(const SampleArgs& p) const {
-        if (kTagged) {
-            tags.close(p.err_flag);
-            return false;
-        }
+        if (kTagged) return tags.close(p.err_flag);
         __threadfence();
         return __hip_atomic_load(p.err_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     }
@@ -530,6 +528,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
                                              uint32_t f_mul, const Load& load) {
     const int32_t f = p.fanout;
     const int32_t inc = wave_inclusive_scan(k, lane);
+    tc.begun();
     auto chain = [&](int32_t wg_total) {
         const int64_t excl = tc.look_back(p, wg_total, lane);
         if (lane == 0) *s_tile_base = excl;

@@ -38,6 +38,8 @@ __global__ void __launch_bounds__(256) tns_scan_init(ScanWorkspace* ws, int64_t 
     if (i == 0) {
         ws->ticket = first_ticket;
         ws->error = 0;
+        ws->noted = 0;
+        ws->failed = 0;
         if (Q_dev && *Q_dev < Q) Q = *Q_dev;
         if (Q <= 0) {          // no query will write the end of rowptr
             rowptr0[0] = 0;
@@ -91,7 +93,6 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -122,7 +123,7 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
-    tc.begun();
+    tc.begin(p);
     // the node's 128-byte line: header + the records of up to 7 blocks, newest first
     uint4 hd = make_uint4(0u, 0u, 0u, 0u);
     uint4 L[kInlineBlocks];
@@ -236,8 +237,8 @@ sample_tile:
                     if (in && !before_end(r.t_max)) { w.d_off = rec_off(r); w.d_n = rec_size(r); end_block = j; }
                     if (in && w.tb > r.t_min) { b_off = rec_off(r); b_n = rec_size(r); start_block = j; }
                 }
-                narrow4(w.d_lo, w.d_n, 0, [&](int32_t i) { return before_end(time_at<pos_t>(p.edges, w.d_off + i)); });
-                narrow4(b_lo, b_n, 0, [&](int32_t i) { return time_at<pos_t>(p.edges, b_off + i) < w.tb; });
+                narrow4(w.d_lo, w.d_n, 0, [&](int32_t i) { return before_end(time_at<pos_t>(w.edges, w.d_off + i)); });
+                narrow4(b_lo, b_n, 0, [&](int32_t i) { return time_at<pos_t>(w.edges, b_off + i) < w.tb; });
                 const int32_t c = count_flat(w.d_lo);
                 w.k = min(c, f);
                 fill_flat(c, w.k);
@@ -290,7 +291,7 @@ sample_tile:
                                 pos = w.template first_not_before<STRICT>(off, rec_size(r), x);
                             } else {
                                 int32_t n = rec_size(r) - 1;          // the newest edge is not before x
-                                narrow4(pos, n, 0, [&](int32_t i) { return before(time_at<pos_t>(p.edges, off + i)); });
+                                narrow4(pos, n, 0, [&](int32_t i) { return before(time_at<pos_t>(w.edges, off + i)); });
                             }
                         }
                         return (int64_t)cum[lo] + pos;
@@ -435,7 +436,7 @@ sample_tile:
     if (COUNT && POLICY == 0 && w.d_off >= 0) {
         // the slots of the window's last block that the search left open
         int32_t h = w.d_lo;
-        for (int32_t i = 0; i < w.d_n; ++i) h += before_end(time_at<pos_t>(p.edges, w.d_off + w.d_lo + i)) ? 1 : 0;
+        for (int32_t i = 0; i < w.d_n; ++i) h += before_end(time_at<pos_t>(w.edges, w.d_off + w.d_lo + i)) ? 1 : 0;
         k = min(f, h + w.k);
     }
     if (COUNT) {

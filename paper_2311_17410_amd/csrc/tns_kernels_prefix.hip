@@ -19,9 +19,9 @@ constexpr int kMaxFastFanout = kSlotsPerLine;
 __device__ __forceinline__ int ceil_log2_outcomes(int n) { return n <= 0 ? 0 : 32 - __clz(n); }   // probes of a binary search over n sorted items
 
 // Uniform policy: workgroups of at most eight waves, three of them per compute unit (80 registers; at 85, with two of
-// them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459).
+// them, 2^22 queries took 447 us windowed and 478 without a window instead of 405 and 459); small grids have two at most.
 template <int POLICY, bool INCL, typename pos_t, bool COUNT, int SCAN>
-__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs args, const int32_t rs, const uint32_t f_mul,
+__global__ void __launch_bounds__(POLICY == 1 ? 512 : 1024, POLICY == 1 && !COUNT && SCAN != kTags ? 6 : 4) tns_sample_prefix_kernel(const SampleArgs args, const int32_t rs, const uint32_t f_mul,
                                                                  const int32_t gshift, const uint32_t chunk) {
     constexpr bool FUSED = SCAN != kNoScan;
     static_assert(POLICY == 1 || (COUNT && !FUSED), "the recent policy is sampled by tns_sample_recent_kernel");
@@ -54,7 +54,6 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -79,7 +78,7 @@ sample_tile:
         }
         if (ok) nidx = nbase + v;
     }
-    tc.begun();
+    tc.begin(p);
     // ---- node lines: eight lanes per line, handed over through LDS ------------------------------------
     uint32_t w[3 * kInlineSlots];     // the eight edge slots of the node's own line
     uint32_t h_degree, h_meta, h_ext0, h_ext12, h_fence0, h_fence1, h_fence2, h_dir;   // the node entry

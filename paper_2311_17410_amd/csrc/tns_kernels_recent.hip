@@ -86,7 +86,6 @@ sample_tile:
         if constexpr (SCAN == kTags) return arguments_anew();
         else return args;
     }();
-    tc.begin(p);
     const int64_t tile = SCAN == kTags ? wave_uniform(tc.tile) : tc.tile;
     const int64_t q0 = (tile * waves_per_wg + wave) * kWave;
     const int64_t q = q0 + lane;
@@ -119,7 +118,7 @@ sample_tile:
     bool ok = have && (uint32_t)v < (uint64_t)p.num_nodes && !(w.te != w.te) && !(w.tb != w.tb);
     if (p.inst_rowptr) ok = ok && inst < p.num_instances;
     const uint32_t node = ok ? (uint32_t)(inst * p.num_nodes + v) : ~0u;      // the target's entry in the node table (a table of 2^32 lines does not exist)
-    tc.begun();
+    tc.begin(p);
     // ---- the node's line: entry and the records of up to seven blocks, newest first -------------------
     u32x4 P[8];
     {

@@ -172,7 +172,6 @@ sample_tile:
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
     }
     any_long = __ballot(any_long) != 0;
-    chain.begun();
 
     // ---- the window [L, R) in a node's sequence of edges --------------------------------------
     // index of the first edge with ts >= x (STRICT: ts > x)
@@ -313,6 +312,7 @@ sample_tile:
         excl_in_wave[u] = wave_total + (lane >= 16 ? k0 : 0) + (lane >= 32 ? k1 : 0) + (lane >= 48 ? k2 : 0);
         wave_total += k0 + k1 + k2 + k3;
     }
+    chain.begun();
     int is_last = 0;
     if (lane == 0) {
         s_wave_sum[wave] = wave_total;
@@ -431,8 +431,8 @@ sample_tile:
         if (j == 0) {
             p.rowptr[q] = row;
             if (q == Q - 1) {
-                const int64_t tot = row + k[u];
-                chain.close(p.err_flag);
+                // (a call in which a wait ran out: 0, so that a hop chained to this one has no queries)
+                const int64_t tot = chain.close(p.err_flag) ? 0 : row + k[u];
                 p.rowptr[Q] = tot;
                 if (p.total_out) *p.total_out = tot;
             }

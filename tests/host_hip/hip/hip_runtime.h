@@ -1,6 +1,7 @@
 // What csrc/tns_chain.h needs of the HIP runtime, for the host: workgroups of two waves run as fibers, one per lane, of one
-// thread.  A random scheduler (seeded, so that a run can be repeated) decides at every access to global memory, which lane goes
-// on; cross-lane operations and barriers wait for the lanes that take part.
+// thread.  A random scheduler (seeded, so that a run can be repeated) decides at every access to global memory which lane goes
+// on; cross-lane operations and barriers wait for the lanes that take part.  What a lane stores reaches the others some time later,
+// stores to different places in any order, or when the lane waits for its stores.
 #pragma once
 #include <setjmp.h>
 #include <ucontext.h>
@@ -8,6 +9,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <memory>
 #include <random>
 #include <vector>
@@ -55,6 +57,28 @@ struct Group {
     int32_t wave_sum[kWaves], arrived, todo;
 };
 inline Fiber* me;
+struct Stored {                    // and not yet seen by others
+    Fiber* by;
+    void* at;
+    uint64_t value;
+    int bytes;
+};
+inline std::vector<Stored> on_their_way;
+inline void arrive(size_t i) {
+    const Stored s = on_their_way[i];
+    on_their_way.erase(on_their_way.begin() + (long)i);
+    std::memcpy(s.at, &s.value, (size_t)s.bytes);
+}
+inline size_t first_of_place(size_t i) {
+    for (size_t j = 0; j < i; ++j)
+        if (on_their_way[j].by == on_their_way[i].by && on_their_way[j].at == on_their_way[i].at) return j;
+    return i;
+}
+inline void wait_for_stores(const void* at = nullptr) {        // of this lane (to one place)
+    for (size_t i = 0; i < on_their_way.size();)
+        if (on_their_way[i].by == me && (!at || on_their_way[i].at == at)) arrive(i);
+        else ++i;
+}
 inline jmp_buf scheduler;
 inline void pause() {
     if (!_setjmp(me->at)) _longjmp(scheduler, 1);
@@ -146,7 +170,11 @@ bool run(int groups, int resident, std::mt19937& rng, const Program& program) {
             }
             ++running;
         }
-        if (running == 0) return true;
+        if (running == 0) {
+            while (!on_their_way.empty()) arrive(0);
+            return true;
+        }
+        if (!on_their_way.empty() && rng() % 32 == 0) arrive(first_of_place(rng() % on_their_way.size()));
         struct Choice { Group* g; int w; };
         static std::vector<Choice> can;
         can.clear();
@@ -161,6 +189,7 @@ bool run(int groups, int resident, std::mt19937& rng, const Program& program) {
                     }
         }
         if (can.empty()) {
+            if (!on_their_way.empty()) { arrive(0); continue; }
             if (begun < groups && running < resident) continue;
             return false;
         }
@@ -177,18 +206,25 @@ bool run(int groups, int resident, std::mt19937& rng, const Program& program) {
     }
     return false;
 }
-template <class T, class V> void store(T* p, V v) { pause(); *p = (T)v; }
-template <class T> T load(const T* p) { pause(); return *p; }
-template <class T, class V> T exchange(T* p, V v) { pause(); T o = *p; *p = (T)v; return o; }
-template <class T, class V> T fetch_or(T* p, V v) { pause(); T o = *p; *p |= (T)v; return o; }
-template <class T, class V> T fetch_and(T* p, V v) { pause(); T o = *p; *p &= (T)v; return o; }
-template <class T, class V> T fetch_add(T* p, V v) { pause(); T o = *p; *p += (T)v; return o; }
-template <class T, class V> bool compare_exchange(T* p, T* expected, V v) {
+template <class T, class V> void store(T* p, V v) {
     pause();
-    if (*p == *expected) { *p = (T)v; return true; }
-    *expected = *p;
-    return false;
+    Stored s{me, p, 0, (int)sizeof(T)};
+    const T value = (T)v;
+    std::memcpy(&s.value, &value, sizeof(T));
+    on_their_way.push_back(s);
 }
+template <class T> T load(const T* p) {
+    pause();
+    T v = *p;
+    for (const Stored& s : on_their_way)
+        if (s.by == me && s.at == p) std::memcpy(&v, &s.value, sizeof(T));
+    return v;
+}
+template <class T> void before_change(T* p) { pause(); wait_for_stores(p); }
+template <class T, class V> T exchange(T* p, V v) { before_change(p); T o = *p; *p = (T)v; return o; }
+template <class T, class V> T fetch_or(T* p, V v) { before_change(p); T o = *p; *p |= (T)v; return o; }
+template <class T, class V> T fetch_and(T* p, V v) { before_change(p); T o = *p; *p &= (T)v; return o; }
+template <class T, class V> T fetch_add(T* p, V v) { before_change(p); T o = *p; *p += (T)v; return o; }
 }  // namespace sim
 
 #define threadIdx (sim::me->tid)
@@ -198,13 +234,13 @@ template <class T, class V> bool compare_exchange(T* p, T* expected, V v) {
 #define __hip_atomic_fetch_or(p, v, o, s) sim::fetch_or(p, v)
 #define __hip_atomic_fetch_and(p, v, o, s) sim::fetch_and(p, v)
 #define __hip_atomic_fetch_add(p, v, o, s) sim::fetch_add(p, v)
-#define __hip_atomic_compare_exchange_strong(p, e, v, o, o2, s) sim::compare_exchange(p, e, v)
 inline uint32_t atomicExch(uint32_t* p, uint32_t v) { return sim::exchange(p, v); }
-inline void __threadfence() {}
+inline void __threadfence() { sim::wait_for_stores(); }
 inline void __syncthreads() { sim::meet(sim::me->group->all); }
 inline uint64_t __ballot(bool p) { return sim::ballot(p); }
 template <class T> T __shfl(T v, int src, int) { return sim::from_lane(v, src); }
 template <class T> T __shfl_xor(T v, int d, int) { return sim::from_lane(v, (int)(sim::me->tid.x % sim::kLanes) ^ d); }
 #define __builtin_amdgcn_readfirstlane(v) sim::from_lane((int)(v), 0)
 #define __builtin_amdgcn_s_sleep(n) sim::pause()
+#define __builtin_amdgcn_s_waitcnt(n) sim::wait_for_stores()
 #define __builtin_amdgcn_wave_barrier() (void)sim::among_lanes(0)

@@ -51,8 +51,7 @@ static int try_once(uint32_t seed) {
                 for (int w = 0; w < wave; ++w) at += g.wave_sum[w];
                 if (lane == 0) row[tile * sim::kWaves + wave] = at;
                 if (lane == 0 && wave == sim::kWaves - 1 && tile == tiles - 1) {
-                    chain.close(&err);
-                    end = total_out = at + count[tile * sim::kWaves + wave];
+                    end = total_out = chain.close(&err) ? 0 : at + count[tile * sim::kWaves + wave];
                 }
             }
         } while (chain.next(tile, per_tile, &g.base, &g.arrived, lane, [&]() { return TaggedChain::Call{queries, &end, &total_out, &err}; }));
