@@ -25,8 +25,11 @@ import sys
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 PROBE_BYTES = 1 << 30
 
-_SAMPLE = re.compile(r"tns_sample(_prefix)?_kernel<(\d), (true|false), (int|long), (true|false), (true|false)>")
-_RECENT = re.compile(r"tns_sample_recent_kernel<(true|false), (int|long), (true|false)>")
+# the last argument: 0 padded rows only, 1 and 2 with the padding removal (large and small grids); before there were small
+# grids, false and true, and no argument for the layout in the recent kernel
+_SAMPLE = re.compile(r"tns_sample(_prefix)?_kernel<(\d), (true|false), (int|long), (true|false), (true|false|\d)>")
+_RECENT = re.compile(r"tns_sample_recent_kernel<(?:(true|false), )?(true|false), (int|long), (true|false|\d)>")
+_NOT_FUSED = ("false", "0")
 _PROBE = re.compile(r"tns_probe_kernel<(\d), (true|false)>")
 
 
@@ -66,11 +69,13 @@ def short_name(kernel: str):
         layout = "prefix" if m.group(1) else "blocks"
         policy = "recent" if m.group(2) == "0" else "uniform"
         name = f"tns_sample{m.group(1) or ''}_kernel<{m.group(2)},{m.group(3)},{m.group(4)},{m.group(5)},{m.group(6)}>"
-        fused_step = m.group(5) == "false" and m.group(6) == "true"
+        fused_step = m.group(5) == "false" and m.group(6) not in _NOT_FUSED
         return name, (f"{policy}:{layout}" if fused_step else None)
     m = _RECENT.search(kernel)
     if m:
-        return f"tns_sample_recent_kernel<{m.group(1)},{m.group(2)},{m.group(3)}>", ("recent:blocks" if m.group(3) == "true" else None)
+        layout = "prefix" if m.group(1) == "true" else "blocks"
+        name = ",".join(g for g in m.groups() if g is not None)
+        return f"tns_sample_recent_kernel<{name}>", (f"recent:{layout}" if m.group(4) not in _NOT_FUSED else None)
     m = _PROBE.search(kernel)
     if m:
         return f"tns_probe_kernel<{m.group(1)},{m.group(2)}>", None
@@ -168,8 +173,9 @@ def main(argv=None) -> int:
              f"  python3 -m paper_2311_17410_amd.traffic --kt gpurun_out/prof/kt --fetch gpurun_out/prof/fetch --write gpurun_out/prof/write "
              f"--workload {args.workload} --json profiles/traffic.json --summary profiles/{os.path.basename(args.summary)}", "",
              "Template arguments of the sampling kernels: <policy (0 recent, 1 uniform), inclusive window end, position type,",
-             "counting pass (byte model), padding removal fused>; of tns_sample_recent_kernel (default layout, recent policy):",
-             "<inclusive window end, position type, padding removal fused>.  <p,false,int,false,true> and <false,int,true> are the timed steps.", "",
+             "counting pass (byte model), form>; of tns_sample_recent_kernel (recent policy): <prefix layout, inclusive window end,",
+             "position type, form>.  Form: 0 padded rows only, 1 padding removal fused, 2 the same for small grids.  <1,false,int,false,1>,",
+             "<false,false,int,1> and <true,false,int,1> are the timed steps.", "",
              "kernel trace (ms per dispatch): name, dispatches, avg, min, max"]
     for k in sorted(trace):
         v = trace[k]

@@ -2,6 +2,8 @@
 per fused sampling kernel, and the staleness stamp that bench.py relies on (hand-made CSVs of the profiler's layout)."""
 import json
 import os
+import re
+import subprocess
 
 from paper_2311_17410_amd import traffic as T
 
@@ -58,6 +60,25 @@ def test_entries_calibration_and_stamp(tmp_path):
     doc["source_hash"] = "0" * 16
     out_json.write_text(json.dumps(doc))
     assert T.lookup(str(out_json), "C5:recent:blocks")["stale"] is True
+
+
+def test_the_kernels_names_as_they_are(tmp_path):
+    # every sampling kernel of the built library, as the profiler prints it; the steps with the padding removal are the entries
+    names = {}
+    lib = os.path.join(os.path.dirname(T.CSRC), "libtns.so")
+    for m in re.finditer(rb"_ZN3tns12_GLOBAL__N_1\d+tns_sample_(?:recent_|prefix_)?kernelI[A-Za-z0-9]*EEvNS_10SampleArgsE[a-z]*", open(lib, "rb").read()):
+        names[m.group(0).decode()] = None
+    assert names
+    plain = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True, check=True).stdout.split("\n")
+    keys = {}
+    for name in plain:
+        got, key = T.short_name(name)
+        assert "<" in got, name
+        keys.setdefault(key, set()).add(got)
+    assert {k for k in keys if k} == {"recent:blocks", "recent:prefix", "uniform:blocks", "uniform:prefix"}
+    assert {"tns_sample_recent_kernel<false,false,int,1>", "tns_sample_recent_kernel<false,false,int,2>"} <= keys["recent:blocks"]
+    assert "tns_sample_recent_kernel<true,false,int,1>" in keys["recent:prefix"] and "tns_sample_recent_kernel<false,false,int,0>" in keys[None]
+    assert "tns_sample_kernel<1,false,int,false,1>" in keys["uniform:blocks"] and "tns_sample_kernel<1,false,int,true,0>" in keys[None]
 
 
 def test_committed_traffic_json_has_the_four_c5_entries():
