@@ -657,11 +657,11 @@ hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     if (a.prefix_layout) return launch_sample_prefix(a, stream);
     // Small batches go to the kernel with sixteen lanes per query: up to one workgroup of it per compute unit, or two where
     // every lane of a team has a slot to gather.  us per call with that kernel / with a query per lane over 2^21 edges, both
-    // without tickets and clearing launch: recent policy, fan-out 10, uniform ids, 16384 queries 9.4 / 9.5 (the host's 9.2),
-    // 32768 10.6 / 10.8, 49152 14.8 / 11.8, 65536 15.1 / 12.9, power-law ids 9.4 / 13.7, 14.8 / 15.2, 21.6 / 16.1, 22.3 / 17.3; fan-out 64,
-    // 65536 27.8 / 33.0 and 46.4 / 40.2.  Uniform policy, fan-out 10, uniform ids 9.2 / 11.7, 11.6 / 12.8, 16.2 / 14.1, 16.4 / 15.5,
-    // power-law ids 10.2 / 21.6, 17.5 / 25.2, 24.9 / 29.2, 25.7 / 32.3; fan-out 5, 32768 11.1 / 10.6 and 16.4 / 18.6, 65536
-    // 16.0 / 12.2 and 23.6 / 23.3.
+    // without tickets and with the loop over tiles that made room: recent policy, fan-out 10, uniform ids, 16384 queries 9.8 / 11.3
+    // (the host's 9.4), 32768 10.6 / 12.6, 49152 14.8 / 13.8, 65536 15.2 / 15.1, power-law ids 9.5 / 16.3, 14.5 / 17.5, 21.1 / 18.9,
+    // 21.6 / 20.0; fan-out 64, 32768 14.5 / 28.9 and 24.8 / 41.0, 65536 29.4 / 33.9 and 47.8 / 47.3.  Uniform policy, fan-out 10, uniform ids
+    // 9.7 / 12.3, 11.6 / 13.3, 16.0 / 14.7, 16.9 / 15.8, power-law ids 10.2 / 22.8, 18.2 / 25.9, 25.8 / 29.8, 26.4 / 33.0; fan-out 5,
+    // 32768 11.3 / 10.7 and 16.5 / 18.6, 65536 16.4 / 12.3 and 24.0 / 23.0.
     const int64_t team_max_queries = int64_t(1) << ((a.policy == 0 ? a.fanout <= 32 : a.fanout < 8) ? 15 : 16);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;

@@ -49,9 +49,11 @@ constexpr uint32_t kFlagBytes = 0x00404040u;                       // the bytes 
 // block i or an older one.  Top byte of `lo`: filled slots; of `hi`: 1 if the row holds an entry per slot.
 struct SlotHead { uint32_t lo, hi; };
 
-// Registers: small grids up to 128 and some scratch, because a workgroup may sample others' tiles again (a loop around
-// the kernel; they have one or two waves per SIMD, four at most).  Otherwise, fused 81 to 83, so that a compute unit holds one tile of sixteen waves; without the scan 70 to 72 with 32-bit
-// positions, seven waves per SIMD, and 80 with 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
+// Registers: small grids 127 or 128 and 32 to 72 bytes of scratch, because a workgroup may sample others' tiles again (a loop around
+// the kernel; they have one or two waves per SIMD, four at most).  Otherwise nothing is spilled but 44 bytes in the prefix layout's
+// form with 64-bit positions and without the scan.  With tickets 82 to 86 (64-bit positions 89 to 100), so that a compute unit holds
+// one tile of sixteen waves; without the scan 68 with 32-bit positions, seven waves per SIMD (prefix layout 76, six), and 80 with
+// 64-bit ones, six.  The kernel before this one kept seven there too, and was slower
 // all the same: 2^20 queries over power-law ids, edge data on the host, unbounded windows 1.40 -> 1.34 ms, windowed 2.15 -> 1.40.
 template <bool PREFIX, bool INCL, typename pos_t, int SCAN>
 __global__ void __launch_bounds__(SCAN ? 1024 : 256, SCAN ? 4 : 6)

@@ -469,9 +469,11 @@ template <int POLICY, bool INCL>
 hipError_t launch_team_p(const SampleArgs& a, hipStream_t stream) {
     constexpr int kAllRounds = 4;
     static_assert(kAllRounds * kTeam >= TNS_MAX_FANOUT, "rounds cover the largest fan-out");
-    // Queries per team: one while the batch gives a compute unit no more than one workgroup (16384 queries: 12.5 us
-    // against 13.2 with two per team, power-law ids 14.3 / 17.9), two beyond (32768: 15.6 against 18.9, 65536: 23.6 /
-    // 30.7, both with tickets).
+    // Queries per team: one while the batch gives a compute unit no more than one workgroup, two beyond.  us per call with one / two,
+    // 2^21 edges, uniform and power-law ids: recent policy, fan-out 10, 16384 queries 9.8 / 10.3 and 9.5 / 14.3; fan-out 64, 32768
+    // 17.0 / 14.5 and 27.8 / 24.8, 65536 33.0 / 29.4 and 54.2 / 47.8; uniform policy, fan-out 10, 16384 9.7 / 11.0 and 10.2 / 16.2, 65536
+    // 19.0 / 16.9 and 27.2 / 26.4.  The line was drawn while tiles took tickets (32768 queries 18.9 / 15.6); without them one per
+    // team is the faster form there too up to fan-out 16 (9.9 / 10.6 and 13.1 / 14.5, uniform policy 10.3 / 11.6 and 14.6 / 18.2).
     const bool one = a.Q <= kComputeUnits * (int64_t)(kTileWaves * kTeamsPerWave);
     if (a.fanout > kTeam) return one ? launch_team_t<POLICY, INCL, 1, kAllRounds>(a, stream) : launch_team_t<POLICY, INCL, 2, kAllRounds>(a, stream);
     return one ? launch_team_t<POLICY, INCL, 1, 1>(a, stream) : launch_team_t<POLICY, INCL, 2, 1>(a, stream);

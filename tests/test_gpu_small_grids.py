@@ -267,3 +267,34 @@ def test_four_streams(B, oracle_lib, policy):
         assert not plan.status(o["workspace"])
         assert_same(results(o, Q, fanout), oracle_sample(oracle_lib, wl, t, None, e, None, fanout, policy, 0, 6, adjs=adjs), oracle_lib, "streams")
     plan.close()
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_small_calls_beside_large_ones(B, oracle_lib, policy, layout):
+    # calls without tickets on two streams while two others keep the chip full with calls of many tiles: workgroups of the small
+    # calls start late and in any order
+    import torch
+    fanout, streams = 10, [torch.cuda.Stream() for _ in range(4)]
+    st, wl, plan = store(B, fanout, policy)
+    adjs = [oracle_lib.Adjacency(st.num_nodes, st.src, st.dst, st.ts)]
+    sizes = [1 << 21, 1 << 21, 100_000, 4000]
+    queries = [W.random_queries(60 + i, st, q) for i, q in enumerate(sizes)]
+    on_device = [(torch.from_numpy(t).cuda(), torch.from_numpy(e).cuda()) for t, _, e in queries]
+    outs = [plan.run(t, None, e) for t, e in on_device]
+    torch.cuda.synchronize()
+    kept = [o["cmp_eid"][:int(o["rowptr"][-1].item())].clone() for o in outs]
+    for o in outs:
+        for n in ("rowptr", "cmp_eid", "count"):
+            o[n].fill_(-3)
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for s, (t, e), o in zip(streams, on_device, outs):
+            with torch.cuda.stream(s):
+                plan.run(t, None, e, out=o)
+    torch.cuda.synchronize()
+    for o, want in zip(outs, kept):
+        assert not plan.status(o["workspace"])
+        assert int(o["rowptr"][-1].item()) == want.numel() and torch.equal(o["cmp_eid"][:want.numel()], want)
+    for (t, _, e), o in list(zip(queries, outs))[2:]:
+        assert_same(results(o, len(t), fanout), oracle_sample(oracle_lib, wl, t, None, e, None, fanout, policy, 0, 6, adjs=adjs), oracle_lib, "small")
+    plan.close()
