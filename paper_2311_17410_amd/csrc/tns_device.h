@@ -293,6 +293,10 @@ struct Walk {
     }
 };
 
+// Around the loads of one of two branches that differ in the non-temporal hint alone: without it the compiler takes the loads of both
+// for the same and makes one of them, without the hint.
+__device__ __forceinline__ void keep_apart() { asm volatile("" ::: "memory"); }
+
 // Ordering between LDS writes and reads of the SAME wave (rows are wave-private): the hardware
 // executes a wave's LDS operations in order, so only the compiler must not reorder them.
 __device__ __forceinline__ void wave_lds_sync() {

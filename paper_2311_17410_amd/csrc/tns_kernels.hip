@@ -143,9 +143,11 @@ sample_tile:
             for (int i = 0; i < 8; ++i)
                 if (src[i] >= 0) R[i] = *(reinterpret_cast<const u32x4*>(p.nodes + src[i]) + piece);
         } else {
+            keep_apart();
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (src[i] >= 0) R[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.nodes + src[i]) + piece);
+            keep_apart();
         }
         u32x4 P[8];
         // through LDS in three rounds of 24, 24 and 16 queries (3 KiB of staging); 16-byte pieces are

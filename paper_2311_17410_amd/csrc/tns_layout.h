@@ -174,11 +174,12 @@ static_assert(sizeof(StoreLine) == 128, "a line is 128 bytes");
 // A node line is read with the non-temporal hint unless other queries will come back to it: it should not push edge lines out of the
 // caches.  They do where an instance's table is at most half of the chip's L2, and where degrees are skewed, which a directory of
 // at least a sixteenth of the nodes shows if the mean list is one that a node line holds; longer ones fill a directory of any
-// degrees.  Hint / none, us: 256 graphs of 4096 nodes, windowed 1498 / 1345; power-law ids, 2^17 nodes 229 / 222, 2^18 553 / 521, 2^19
-// 1183 / 1093 (uniform policy 1807 / 1745), 3 * 10^6 2747 / 2499; uniform ids, 2^17 nodes 185 / 180, 2^18 363 / 367, 2^19 722 / 766,
-// 2^20 1439 / 1499.  A hundred edges a node, uniform policy, 2^22 queries: power-law ids, 2^18 nodes (4.6 blocks a list) 1225 / 1204,
-// 2^20 (5.5) 1638 / 1612; uniform ids, 2^18 (12.1) 1313 / 1322, 2^20 (14.7) 1472 / 1478, 48 edges (8.2) 1013 / 1021; the recent policy within
-// half a percent either way.
+// degrees.  Hint / none, us, recent policy and uniform policy: 256 graphs of 4096 nodes, windowed 1500 / 1346 and 1680 / 1417; power-law
+// ids, 2^18 nodes 568 / 519 and 915 / 855, 2^19 1205 / 1093 and 1944 / 1811, 2^20 2480 / 2320 and 4424 / 4123; uniform ids, 2^17 nodes 189 /
+// 183 and 221 / 213, 2^18 362 / 367 and 421 / 403, 2^19 714 / 755 and 843 / 857, 2^20 1431 / 1490 and 1704 / 1743, 2^21 2966 / 2954 and
+// 3422 / 3455, 2^22 6215 / 6191 and 6953 / 6993, 2^20 windowed 1341 / 1425 and 1582 / 1639 (a query per edge each).  A hundred
+// edges a node, uniform policy, 2^22 queries: power-law ids, 2^18 nodes (4.6 blocks a list) 1225 / 1204, 2^20 (5.5) 1638 / 1612; uniform
+// ids, 2^18 (12.1) 1313 / 1322, 2^20 (14.7) 1472 / 1478, 48 edges (8.2) 1013 / 1021.
 constexpr int64_t kSmallTable = int64_t(1) << 17;       // nodes
 inline bool node_lines_stay(int64_t nodes_per_instance, int64_t nodes, int64_t num_dir, int64_t num_blocks) {
     return nodes_per_instance <= kSmallTable || (num_dir * 16 >= nodes && num_blocks <= nodes * kInlineBlocks);
