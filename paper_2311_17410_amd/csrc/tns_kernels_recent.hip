@@ -480,7 +480,11 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((tns_sample_recent_kernel<PREFIX, INCL, pos_t, decltype(scan)::value>), dim3((unsigned)grid), dim3(waves * kWave), lds, stream, b,
                            stride, slot_multiplier(a.fanout), (uint32_t)chunk);
     };
-    return launch_tiles<FUSED>(a, grid, per_wg, stream, launch);
+    // Padded rows only over the prefix layout: tiles in the order of the workgroups.  With a contiguous range of tiles per XCD, us: 2^22
+    // queries 267 -> 296, 2^24 1086 -> 1204, 2^26 4297 -> 4798 (the kernel before the one with block tables, with ranges, 316, 1052 and 4308).
+    SampleArgs b = a;
+    if (PREFIX && !FUSED) b.xcd_remap = 0;
+    return launch_tiles<FUSED>(b, grid, per_wg, stream, launch);
 }
 
 }  // namespace
