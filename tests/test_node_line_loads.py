@@ -37,5 +37,7 @@ def test_node_lines_are_read_both_ways(tmp_path):
     recent = {n: v for n, v in loads.items() if re.search(r"tns_sample_recent_kernelILb0E.*Li[01]EEEv", n)}      # default layout, no small grids
     uniform = {n: v for n, v in loads.items() if re.search(r"tns_sample_kernelILi1E.*Lb0ELi\dEEEv", n)}
     assert len(recent) == 8 and len(uniform) == 12, sorted(loads)
-    for name, (hint, plain) in {**recent, **uniform}.items():
+    for name, (hint, plain) in recent.items():
         assert hint >= 8 and plain >= 8, (name, hint, plain)
+    for name, (hint, plain) in uniform.items():      # (one of the eight is the same in both branches, which measured faster)
+        assert hint >= 7 and plain >= 8, (name, hint, plain)
