@@ -255,7 +255,7 @@ def side_config(B, torch, W, name: str, layout: str, steps: int):
         e1.record()
         torch.cuda.synchronize()
         row["ms_per_step_100_back_to_back"] = e0.elapsed_time(e1) / 100
-        row["note"] = "launch-bound: two launches per step (scan state clear + fused kernel)"
+        row["note"] = "launches per step: one up to 2^18 queries, beyond that two (scan state clear + fused kernel)"
     r.close()
     return row
 
@@ -330,7 +330,7 @@ def main() -> int:
         total_k = int(r.out["rowptr"][-1].item())
         assert total_k == bm["n_edges"], (total_k, bm["n_edges"])
         ms = sum(ev) / len(ev)
-        kname = "tns_sample_prefix_kernel" if layout == "prefix" else ("tns_sample_recent_kernel" if args.policy == "recent" else "tns_sample_kernel")
+        kname = "tns_sample_recent_kernel" if args.policy == "recent" else ("tns_sample_prefix_kernel" if layout == "prefix" else "tns_sample_kernel")
         kname += " (padding removal fused)" if args.placement == "hbm" else " + tns_compact kernels"
         key = f"{wl.name}:{args.policy}:{layout}"
         tr = measured_traffic(key) if plain else None
