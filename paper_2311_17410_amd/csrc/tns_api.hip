@@ -756,7 +756,7 @@ static int check_compact_args(int64_t Q, const void* rowptr, const void* a, cons
     if (!rowptr) return fail(TNS_EINVAL, "null d_rowptr");
     if (Q > 0 && n_cmp != 3) return fail(TNS_EINVAL, "pass all four compaction outputs or none");
     if (!ws) return fail(TNS_EINVAL, "compaction needs a workspace");
-    if (ws_bytes < tns::compact_workspace_bytes(Q)) return fail(TNS_ESIZE, "workspace smaller than tns_workspace()");
+    if (ws_bytes < tns::compact_workspace_least(Q)) return fail(TNS_ESIZE, "workspace smaller than tns_workspace()");
     if (reinterpret_cast<uintptr_t>(ws) & 255) return fail(TNS_EINVAL, "workspace must be 256-byte aligned");
     return TNS_OK;
 }
@@ -844,7 +844,7 @@ static int run_impl(tns_plan* plan, int64_t Q, const int32_t* d_targets, const f
     DeviceGuard guard(plan->cfg.device);
     if (guard.error() != hipSuccess) return fail_hip(guard.error(), "selecting the plan's device");
     if (static_scratch && want_cmp) {
-        if (Q > kStaticMaxQueries || tns::compact_workspace_bytes(Q) > kStaticScratchBytes)
+        if (Q > kStaticMaxQueries || tns::compact_workspace_least(Q) > kStaticScratchBytes)
             return fail(TNS_ESIZE, "tns_run_static serves at most 2^24 queries per call");
         if ((rc = static_scratch_of(plan->cfg.device, &d_workspace))) return rc;
         workspace_bytes = kStaticScratchBytes;
@@ -867,6 +867,7 @@ static int run_impl(tns_plan* plan, int64_t Q, const int32_t* d_targets, const f
         return fail(TNS_EINVAL, "this plan removes the padding in a step of its own (edge data on the host, or deleted edges) and needs the padded outputs");
     if (fuse) {
         a.scan_ws = d_workspace;
+        a.scan_states = tns::tile_states(workspace_bytes);
         a.rowptr = d_rowptr;
         a.cmp_nbr = d_cmp_nbr;
         a.cmp_eid = d_cmp_eid;
@@ -937,6 +938,15 @@ size_t khop_header_bytes(int32_t num_hops, int32_t num_instances) {
     const size_t per_hop = (size_t)(num_instances + 2) * sizeof(int64_t);
     return ((size_t)num_hops * per_hop + 255) & ~size_t(255);
 }
+// one chained-scan region per hop, so that a single launch can clear them all before the first hop
+size_t khop_scan_bytes(int32_t num_hops, const int64_t* caps, size_t (*region)(int64_t)) {
+    size_t scan = 0;
+    for (int h = 0; h < num_hops; ++h) scan += region(caps[h]);
+    return scan;
+}
+size_t khop_workspace(int32_t num_hops, const int64_t* caps, int32_t num_instances, size_t (*region)(int64_t)) {
+    return kStatusBytes + khop_scan_bytes(num_hops, caps, region) + khop_header_bytes(num_hops, num_instances);
+}
 }  // namespace
 
 int tns_workspace_khop(const tns_plan* plan, int32_t num_hops, const int32_t* fanouts, int64_t Q, size_t* bytes) {
@@ -945,10 +955,7 @@ int tns_workspace_khop(const tns_plan* plan, int32_t num_hops, const int32_t* fa
     if (num_hops < 1 || num_hops > kMaxHops) return fail(TNS_EINVAL, "num_hops must be in [1, 8]");
     int64_t caps[kMaxHops];
     if (!khop_caps(num_hops, fanouts, Q, caps)) return fail(TNS_ESIZE, "fan-out out of range or more than 2^36 queries in a hop");
-    // one chained-scan region per hop, so that a single launch can clear them all before the first hop
-    size_t scan = 0;
-    for (int h = 0; h < num_hops; ++h) scan += tns::compact_workspace_bytes(caps[h]);
-    *bytes = kStatusBytes + scan + khop_header_bytes(num_hops, plan->cfg.num_instances);
+    *bytes = khop_workspace(num_hops, caps, plan->cfg.num_instances, tns::compact_workspace_bytes);
     return TNS_OK;
 }
 
@@ -964,11 +971,11 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
     if (std::isnan(delta) || delta < 0) return fail(TNS_EINVAL, "delta must be >= 0 (or +infinity)");
     int64_t caps[kMaxHops];
     if (Q < 0 || !khop_caps(num_hops, fanouts, Q, caps)) return fail(TNS_ESIZE, "fan-out out of range or more than 2^36 queries in a hop");
-    size_t need = 0;
-    int rc = tns_workspace_khop(plan, num_hops, fanouts, Q, &need);
-    if (rc) return rc;
     if (!d_workspace) return fail(TNS_EINVAL, "null workspace");
-    if (workspace_bytes < need) return fail(TNS_ESIZE, "workspace smaller than tns_workspace_khop()");
+    // (a workspace of the size that does without the states of smaller tiles will do)
+    const auto region = workspace_bytes < khop_workspace(num_hops, caps, plan->cfg.num_instances, tns::compact_workspace_bytes) ? tns::compact_workspace_least
+                                                                                                                               : tns::compact_workspace_bytes;
+    if (workspace_bytes < khop_workspace(num_hops, caps, plan->cfg.num_instances, region)) return fail(TNS_ESIZE, "workspace smaller than tns_workspace_khop()");
     if (reinterpret_cast<uintptr_t>(d_workspace) & 255) return fail(TNS_EINVAL, "workspace must be 256-byte aligned");
     for (int h = 0; h < num_hops; ++h) {
         const tns_hop_buffers& b = hops[h];
@@ -978,7 +985,8 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
             return fail(TNS_EINVAL, "null buffer in hops[]");
     }
     tns::SampleArgs a;
-    if ((rc = fill_sample_args(plan, Q, d_targets, d_t_start, d_t_end, d_inst_rowptr, query_id_base, a))) return rc;
+    const int rc = fill_sample_args(plan, Q, d_targets, d_t_start, d_t_end, d_inst_rowptr, query_id_base, a);
+    if (rc) return rc;
 
     DeviceGuard guard(plan->cfg.device);
     if (guard.error() != hipSuccess) return fail_hip(guard.error(), "selecting the plan's device");
@@ -987,8 +995,7 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
     // workspace: the status word (second 32-bit word, as in tns_run's workspace), one chained-scan region per
     // hop, then per hop the dense total and the instance offsets of the next hop
     unsigned char* scan_ws = static_cast<unsigned char*>(d_workspace) + kStatusBytes;
-    size_t scan = 0;
-    for (int h = 0; h < num_hops; ++h) scan += tns::compact_workspace_bytes(caps[h]);
+    const size_t scan = khop_scan_bytes(num_hops, caps, region);
     int64_t* header = reinterpret_cast<int64_t*>(scan_ws + scan);
     // One launch clears the regions of the hops that cannot do without: all of them in a call that may be replayed, otherwise those
     // from the first on that is too large (hops do not get smaller); with the status word if that is the first hop, which otherwise
@@ -998,7 +1005,7 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
         while (first_cleared < num_hops && caps[first_cleared] <= tns::tagged_queries(fanouts[first_cleared])) ++first_cleared;
     if (first_cleared < num_hops) {
         unsigned char* from = scan_ws;
-        for (int h = 0; h < first_cleared; ++h) from += tns::compact_workspace_bytes(caps[h]);
+        for (int h = 0; h < first_cleared; ++h) from += region(caps[h]);
         if (first_cleared == 0) from = static_cast<unsigned char*>(d_workspace);
         const hipError_t e = tns::launch_scan_clear(from, (size_t)(scan_ws + scan - from), stream);
         if (e != hipSuccess) return fail_hip(e, "clearing the chained-scan workspace");
@@ -1018,7 +1025,8 @@ int tns_run_khop(tns_plan* plan, int32_t num_hops, const int32_t* fanouts, float
         a.total_out = total;
         a.scan_ws = scan_ws;                                    // sampling with the padding removal fused in
         a.scan_ready = Q > 0 ? 1 : 0;                           // cleared above where it has to be
-        scan_ws += tns::compact_workspace_bytes(caps[h]);
+        a.scan_states = tns::tile_states(region(caps[h]));
+        scan_ws += region(caps[h]);
         a.rowptr = b.rowptr;
         a.cmp_nbr = b.cmp_nbr;
         a.cmp_eid = b.cmp_eid;

@@ -137,10 +137,18 @@ struct TaggedChain {
         __hip_atomic_store(&ws->status[tile], tag << kTagShift | kPublishedBit | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.  -1: the tile has
-    // waited for long enough, writes no dense rows, and is noted by next().
+    // waited for long enough, writes no dense rows, and is noted by next().  sum_of(v): the sum over the wave; such a call has less
+    // than 2^31 dense entries.
     __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins) const {
+        return exclusive(tile, lane, defer_spins, [](int32_t v) {
+            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kChainWave);
+            return v;
+        });
+    }
+    template <class Sum>
+    __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins, const Sum& sum_of) const {
         const uint32_t noted = __hip_atomic_load(&ws->noted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int64_t sum = 0;
+        int32_t sum = 0;
         int spins = 0;
         for (int64_t t0 = 0; t0 < tile; t0 += 4 * kChainWave) {
             uint64_t w[4];
@@ -170,12 +178,10 @@ struct TaggedChain {
                 } else if (spins < 16) __builtin_amdgcn_s_sleep(2);
                 else __builtin_amdgcn_s_sleep(16);
             }
-            int64_t v = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v += (int64_t)(w[i] & (kNotedBit - 1ull));
-            sum += v;
+            for (int i = 0; i < 4; ++i) sum += (int32_t)(w[i] & (kNotedBit - 1ull));
         }
-        for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kChainWave);
+        sum = sum_of(sum);
         if (lane == 0 && noted == (uint32_t)tag) *s_todo = kSeeToNoted;
         return sum;
     }

@@ -44,14 +44,31 @@ __device__ __forceinline__ uint64_t pick_rank(uint64_t seed, int64_t qid, int32_
     return ((z >> 32) * c) >> 32;
 }
 
-__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t u = __shfl_up(v, d, kWave);
-        if (lane >= d) v += u;
-    }
-    return v;
+// Moves inside a row of sixteen lanes are part of a vector instruction (DPP); a shuffle is a round trip through the LDS unit, some
+// sixty cycles each, and what waits for a shuffle waits for all of it.  Called by the whole wave.
+template <int LANE>
+__device__ __forceinline__ int32_t row_read(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + LANE, 0xf, 0xf, true); }      // of lane LANE of the row
+template <int BY>
+__device__ __forceinline__ int32_t row_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x110 + BY, 0xf, 0xf, true); }          // of the lane BY below, 0 at the row's begin
+
+__device__ __forceinline__ int32_t row_inclusive_scan(int32_t v) {
+    v += row_up<1>(v);
+    v += row_up<2>(v);
+    v += row_up<4>(v);
+    return v + row_up<8>(v);
 }
+__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v) {
+    v = row_inclusive_scan(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);            // rows 1 and 3: what the row before them has in its last lane
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // rows 2 and 3: what lane 31 has
+}
+// Sum over the first n of the workgroup's waves (at most sixteen), whose own sums lie in LDS: a value per lane and one LDS access, where
+// a loop over the waves waits for one access after the other.
+__device__ __forceinline__ int32_t sum_of_waves(const int32_t* s_wave_sum, int n, int lane) {
+    const int w = lane & 15, v = s_wave_sum[w];
+    return __builtin_amdgcn_readlane(row_inclusive_scan(w < n ? v : 0), 15);
+}
+__device__ __forceinline__ int32_t wave_sum(int32_t v) { return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kWave - 1); }
 
 // Instance of query q, one of the wave's 64 consecutive queries from q0 on: instance b owns queries rowptr[b] ..
 // rowptr[b + 1] - 1.  The wave finds the instance of its first query together, 64 probes a round (two dependent reads
@@ -497,7 +514,7 @@ struct TileChain {
     }
     // one wave: the dense entries of the tiles before this one; -1 (kTags): the tile writes no dense rows
     __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
-        if (kTagged) return tags.exclusive(tile, lane, p.defer_spins);
+        if (kTagged) return tags.exclusive(tile, lane, p.defer_spins, [](int32_t v) { return wave_sum(v); });
         const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane) : 0;
         if (lane == 0)
             __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -531,7 +548,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
                                              Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
                                              uint32_t f_mul, const Load& load) {
     const int32_t f = p.fanout;
-    const int32_t inc = wave_inclusive_scan(k, lane);
+    const int32_t inc = wave_inclusive_scan(k);
     tc.begun();
     auto chain = [&](int32_t wg_total) {
         const int64_t excl = tc.look_back(p, wg_total, lane);
@@ -550,8 +567,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         }
     };
     auto row_of_wave = [&]() {
-        int32_t off = 0;
-        for (int i = 0; i < wave; ++i) off += s_wave_sum[i];
+        const int32_t off = sum_of_waves(s_wave_sum, wave, lane);
         const int64_t base = *s_tile_base;
         return wave_uniform(Chain::kTagged && base < 0 ? base : base + off);
     };
@@ -572,7 +588,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         int32_t wg_total = 0;
         if (is_last) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
+            wg_total = sum_of_waves(s_wave_sum, waves_per_wg, lane);
             tc.publish_total(p, wg_total, lane);
         }
         wave_lds_sync();      // what the load reads from LDS was written by this wave's own lanes
@@ -590,8 +606,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         if (lane == kWave - 1) s_wave_sum[wave] = inc;
         __syncthreads();
         if (wave == 0) {
-            int32_t wg_total = 0;
-            for (int i = 0; i < waves_per_wg; ++i) wg_total += s_wave_sum[i];
+            const int32_t wg_total = sum_of_waves(s_wave_sum, waves_per_wg, lane);
             tc.publish_total(p, wg_total, lane);
             chain(wg_total);
         }

@@ -33,6 +33,7 @@ struct SampleArgs {
     // non-null: also remove the padding in the same pass (chained scan over workgroups);
     // scan_ws is the caller's workspace, rowptr / cmp_* the dense outputs
     void* scan_ws;
+    int64_t scan_states;     // tile states that it holds
     int64_t* rowptr;
     int32_t* cmp_nbr;
     int32_t* cmp_eid;
@@ -76,9 +77,16 @@ struct CompactArgs {
     void* workspace;
 };
 
+constexpr size_t kScanHeader = 256;         // of a scan workspace, before the tile states
+constexpr int64_t kSmallTile = 16, kMostSmallTiles = 512;      // queries of the smallest tiles; most such tiles of a call
 constexpr int kCompactTile = 1024;  // queries per compaction tile
 
+// What a call with Q queries needs, and what it is asked to bring: room for the states of smaller tiles where the batch is small
+// (tns_kernels_team.hip).
+size_t compact_workspace_least(int64_t Q);
 size_t compact_workspace_bytes(int64_t Q);
+// tile states in a workspace of that size
+int64_t tile_states(size_t bytes);
 
 // Both only enqueue kernels on `stream`; they return the first launch error.
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream);

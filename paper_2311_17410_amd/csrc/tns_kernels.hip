@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(256) tns_count_tile_sums(const int32_t* __rest
         if (q < Q) v += count[q];
     }
     const int lane = threadIdx.x & 63;
-    v = wave_inclusive_scan(v, lane);
+    v = wave_inclusive_scan(v);
     if (lane == 63) s_w[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
@@ -505,7 +505,7 @@ __global__ void __launch_bounds__(1024) tns_scan_tile_sums(const int32_t* __rest
     for (int64_t base = 0; base < num_tiles; base += 1024) {
         const int64_t i = base + threadIdx.x;
         const int32_t v = i < num_tiles ? tile_sums[i] : 0;
-        const int32_t inc = wave_inclusive_scan(v, lane);
+        const int32_t inc = wave_inclusive_scan(v);
         if (lane == 63) s_w[wave] = inc;
         __syncthreads();
         int32_t wave_off = 0, all = 0;
@@ -548,7 +548,7 @@ __global__ void __launch_bounds__(256) tns_compact_scatter(const CompactArgs a, 
         c[i] = q < Q ? a.count[q] : 0;
         sum += c[i];
     }
-    const int32_t inc = wave_inclusive_scan(sum, lane);
+    const int32_t inc = wave_inclusive_scan(sum);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
     int32_t excl = inc - sum;
@@ -617,15 +617,22 @@ hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-size_t compact_workspace_bytes(int64_t Q) {
+size_t compact_workspace_least(int64_t Q) {
     // enough for either use: tile sums + offsets of the stand-alone compaction, or the ticket
     // and one state per 64-query wave (the smallest workgroup) of the fused chained scan
     const int64_t tiles = (Q + kCompactTile - 1) / kCompactTile;
     const size_t sums = ((size_t)tiles * sizeof(int32_t) + 255) & ~size_t(255);
     const size_t offs = ((size_t)tiles * sizeof(int64_t) + 255) & ~size_t(255);
-    const size_t fused = 256 + (size_t)((Q + kWave - 1) / kWave + 1) * sizeof(uint64_t);
+    const size_t fused = kScanHeader + (size_t)((Q + kWave - 1) / kWave + 1) * sizeof(uint64_t);
     return std::max(sums + offs + 256, (fused + 255) & ~size_t(255));
 }
+
+size_t compact_workspace_bytes(int64_t Q) {
+    const int64_t small_tiles = std::min<int64_t>((Q + kSmallTile - 1) / kSmallTile, kMostSmallTiles);
+    return std::max(compact_workspace_least(Q), (kScanHeader + (size_t)(small_tiles + 1) * sizeof(uint64_t) + 255) & ~size_t(255));
+}
+
+int64_t tile_states(size_t bytes) { return bytes < kScanHeader ? 0 : (int64_t)((bytes - kScanHeader) / sizeof(uint64_t)); }
 
 hipError_t launch_scan_init(const SampleArgs& a, int64_t num_tiles, hipStream_t stream) {
     const unsigned init_grid = (unsigned)std::max<int64_t>(1, (num_tiles + 255) / 256);
@@ -657,13 +664,12 @@ hipError_t ready_tags(SampleArgs& a, int64_t tiles, hipStream_t stream) {
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     if (a.prefix_layout) return launch_sample_prefix(a, stream);
-    // Small batches go to the kernel with sixteen lanes per query: up to one workgroup of it per compute unit, or two where
-    // every lane of a team has a slot to gather.  us per call with that kernel / with a query per lane over 2^21 edges, both
-    // without tickets and with the loop over tiles that made room: recent policy, fan-out 10, uniform ids, 16384 queries 9.8 / 11.3
-    // (the host's 9.4), 32768 10.6 / 12.6, 49152 14.8 / 13.8, 65536 15.2 / 15.1, power-law ids 9.5 / 16.3, 14.5 / 17.5, 21.1 / 18.9,
-    // 21.6 / 20.0; fan-out 64, 32768 14.5 / 28.9 and 24.8 / 41.0, 65536 29.4 / 33.9 and 47.8 / 47.3.  Uniform policy, fan-out 10, uniform ids
-    // 9.7 / 12.3, 11.6 / 13.3, 16.0 / 14.7, 16.9 / 15.8, power-law ids 10.2 / 22.8, 18.2 / 25.9, 25.8 / 29.8, 26.4 / 33.0; fan-out 5,
-    // 32768 11.3 / 10.7 and 16.5 / 18.6, 65536 16.4 / 12.3 and 24.0 / 23.0.
+    // Small batches go to the kernel with sixteen lanes per query: up to what the chip holds of it at once, or twice that where
+    // every lane of a team has a slot to gather.  us of that kernel / of the one with a query per lane, 2^21 edges: recent
+    // policy, fan-out 10, uniform ids, 20000 queries 8.6 / 11.6, 32768 9.3 / 12.0, 49152 13.7 / 13.1, 65536 14.2 / 14.3, power-law ids 11.4 / 16.6,
+    // 12.0 / 17.1, 16.8 / 17.9, 19.4 / 19.3; fan-out 20, 32768 11.5 / 17.0 and 15.9 / 21.9, 40000 19.4 / 17.9 and 27.9 / 22.9; fan-out 64,
+    // 65536 26.6 / 32.7 and 43.3 / 41.7.  Uniform policy, fan-out 10, uniform ids 9.0 / 12.6, 9.9 / 13.2, 14.5 / 14.6, 15.2 / 15.7, power-law ids
+    // 12.7 / 24.6, 13.7 / 26.0, 20.8 / 29.4, 24.2 / 32.4; fan-out 5, 32768 9.3 / 10.8 and 12.9 / 19.2, 65536 14.6 / 11.8 and 21.8 / 23.3.
     const int64_t team_max_queries = int64_t(1) << ((a.policy == 0 ? a.fanout <= 32 : a.fanout < 8) ? 15 : 16);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;

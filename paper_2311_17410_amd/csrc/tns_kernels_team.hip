@@ -17,10 +17,14 @@
 //             other.
 //   deleted   a node whose flags say that edges of it are deleted has its candidates looked at, sixteen side by side.
 //             The flag is read here and not on the host: a captured call may be replayed after a deletion.
-// What bounds it is the chain of dependent reads (query, node, search, edge, look-back).  Its tiles tag what they publish
-// instead of having the scan state cleared by a launch before it and tickets taken (TaggedChain): 1024 queries 11.9 -> 8.5 us
-// per call, two hops from 600 and 4000 roots 17.2 -> 13.9 and 27.6 -> 23.4.  Measured beside the kernels with a query per
-// lane: see the rule in launch_sample.
+// What bounds it is the chain of dependent reads (query, node, search, edge, look-back) and, between them, the instructions of the
+// waves that share a SIMD.  Its tiles tag what they publish instead of having the scan state cleared by a launch before it and
+// tickets taken (TaggedChain).  A team is a row of sixteen lanes, so that what it shares moves within vector instructions (row_read,
+// row_up) and not through the LDS unit, the waves' sums are added up side by side, a block's position is divided by the slots per
+// line once, and small batches take small workgroups (launch_team_t).  The kernel, us: 1024 queries over 2^10 edges 7.6 -> 5.9, two
+// hops from 600 roots 7.0 + 7.5 -> 5.9 + 6.3, from 4000 under the uniform policy 8.2 + 16.0 -> 6.0 + 13.0; per call 14.2 -> 12.1 and
+// 23.7 -> 19.7.  Measured beside the kernels with a query per lane: see the rule in launch_sample.
+#include <algorithm>
 #include <type_traits>
 
 #include "../../include/tns.h"
@@ -33,7 +37,8 @@ namespace {
 constexpr int kTeam = 16;
 constexpr int kTeamsPerWave = kWave / kTeam;
 constexpr int64_t kComputeUnits = 256;
-constexpr int kTileWaves = 16;       // 64 queries per workgroup at least: the workspace holds one tile state per 64 queries
+constexpr int kTileWaves = 16, kFewWaves = 4;      // of the largest workgroups (every workspace holds a tile state per 64 queries) and the smallest
+constexpr int64_t kFewQueries = 512;               // up to so many the smallest workgroups are not the best
 
 // For each of CH independent ranges: number of leading items of [0, n) for which qual(u, i) holds (the items for which
 // it holds come first), found by the team together: sixteen probes a round, the rounds of all ranges side by side.
@@ -71,7 +76,7 @@ __device__ __forceinline__ void team_partition(int32_t (&n)[CH], int32_t (&lo)[C
 // CH: queries per team, all steps of which run side by side; ROUNDS: of sixteen slots
 template <int POLICY, bool INCL, int CH, int ROUNDS>
 __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) tns_sample_team_kernel(const SampleArgs args) {
-    constexpr int kTileQueries = kTileWaves * kTeamsPerWave * CH;
+    const int tile_waves = (int)(blockDim.x >> 6), tile_queries = tile_waves * kTeamsPerWave * CH;
     __shared__ int64_t s_tile_base;
     __shared__ int32_t s_wave_sum[kTileWaves];
     __shared__ int32_t s_arrived, s_todo;
@@ -80,7 +85,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
     const int32_t f = args.fanout;
     const int64_t Q = args.Q_dev ? min(args.Q, *args.Q_dev) : args.Q;
     // later hops are launched for the most queries they can have: workgroups beyond the actual number leave at once
-    if ((int64_t)blockIdx.x * kTileQueries >= Q) {
+    if ((int64_t)blockIdx.x * tile_queries >= Q) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {      // no query will write the end of rowptr
             args.rowptr[0] = 0;
             if (args.total_out) *args.total_out = 0;
@@ -88,7 +93,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, CH * ROUNDS <= 2 ? 8 : 4) 
         return;
     }
     int64_t tile = (int64_t)blockIdx.x + args.first_ticket;
-    if (tile * kTileQueries >= Q) return;      // (tests whose tiles start at 1)
+    if (tile * tile_queries >= Q) return;      // (tests whose tiles start at 1)
     if (threadIdx.x == 0) s_arrived = s_todo = 0;
     __syncthreads();
     TaggedChain chain;
@@ -99,7 +104,7 @@ sample_tile:
     chain.begin(p.scan_ws, p.chain_tag, tile);
     const int j = lane & (kTeam - 1), team0 = lane & ~(kTeam - 1);
     // a wave's queries are consecutive: team t of the wave has q0 + u * 4 + t
-    const int64_t q0 = tile * kTileQueries + wave * (kTeamsPerWave * CH) + (lane >> 4);
+    const int64_t q0 = tile * tile_queries + wave * (kTeamsPerWave * CH) + (lane >> 4);
 
     // ---- the queries and their nodes ---------------------------------------------------------
     float te[CH], tb[CH];
@@ -147,9 +152,9 @@ sample_tile:
     bool any_long = false;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
-        int32_t nb = __shfl((int)piece[u].x, team0, kWave);
-        dline[u] = (uint32_t)__shfl((int)piece[u].z, team0, kWave);
-        const int32_t flags = __shfl((int)piece[u].w, team0, kWave);
+        int32_t nb = row_read<0>((int)piece[u].x);
+        dline[u] = (uint32_t)row_read<0>((int)piece[u].z);
+        const int32_t flags = row_read<0>((int)piece[u].w);
         if (flags & 1) nb = 0;                                                       // deleted node: no blocks
         if (nb > kInlineBlocks && (int64_t)dline[u] * kDirAlign + nb > p.num_dir) nb = 0;
         nb_in[u] = nb > kInlineBlocks ? 0 : nb;
@@ -161,12 +166,9 @@ sample_tile:
         rec[u].off_lo = (uint32_t)__shfl((int)piece[u].z, src, kWave);
         rec[u].size_hi = (uint32_t)__shfl((int)piece[u].w, src, kWave);
         const int32_t size = j < nb_in[u] ? rec_size(rec[u]) : 0;
-        cum[u] = size;
-#pragma unroll
-        for (int d = 1; d < 8; d <<= 1) {
-            const int32_t w = __shfl_up(cum[u], d, kTeam);
-            if (j >= d) cum[u] += w;
-        }
+        cum[u] = size + row_up<1>(size);
+        cum[u] += row_up<2>(cum[u]);
+        cum[u] += row_up<4>(cum[u]);
         cum[u] = j == kTeam - 1 ? flags : cum[u] - size;
         piv[u] = 0;
         if (nb_long[u] > 0) piv[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + min(j * ((nb_long[u] + kTeam - 1) / kTeam), nb_long[u] - 1)];
@@ -179,7 +181,8 @@ sample_tile:
         constexpr bool STRICT = decltype(strict)::value;
         auto before = [&](int u, float t) { return STRICT ? t <= x[u] : t < x[u]; };
         int32_t b[CH], n[CH], base[CH], size[CH], pos[CH];
-        int64_t off[CH];
+        const uint32_t* edges[CH];      // of the block that the search goes through
+        uint32_t edges_at[CH];
 #pragma unroll
         for (int u = 0; u < CH; ++u) b[u] = __popcll((__ballot(j < nb_in[u] && before(u, rec[u].t_max)) >> team0) & 0xffffull);
         if (any_long) {
@@ -205,11 +208,13 @@ sample_tile:
                 base[u] = (int32_t)p.dir_cum[(int64_t)dline[u] * kDirAlign + bb];
             }
             size[u] = rec_size(r);
-            off[u] = rec_off(r);
+            const BlockWords words(r);
+            edges[u] = p.edges + words.base;
+            edges_at[u] = words.at;
             // the block's newest edge is not before x: one item less to search
             n[u] = (b[u] < nb && before(u, r.t_min)) ? size[u] - 1 : 0;
         }
-        team_partition<CH>(n, pos, lane, [&](int u, int32_t i) { return before(u, __uint_as_float(p.edges[slot_word(off[u] + i)])); });
+        team_partition<CH>(n, pos, lane, [&](int u, int32_t i) { return before(u, __uint_as_float(edges[u][words_behind(edges_at[u] + (uint32_t)i)])); });
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
             const int32_t nb = nb_in[u] + nb_long[u];
@@ -308,7 +313,7 @@ sample_tile:
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         k[u] = min(c[u], f);
-        const int32_t k0 = __shfl(k[u], 0, kWave), k1 = __shfl(k[u], 16, kWave), k2 = __shfl(k[u], 32, kWave), k3 = __shfl(k[u], 48, kWave);
+        const int32_t k0 = wave_read(k[u], 0), k1 = wave_read(k[u], 16), k2 = wave_read(k[u], 32), k3 = wave_read(k[u], 48);
         excl_in_wave[u] = wave_total + (lane >= 16 ? k0 : 0) + (lane >= 32 ? k1 : 0) + (lane >= 48 ? k2 : 0);
         wave_total += k0 + k1 + k2 + k3;
     }
@@ -317,14 +322,14 @@ sample_tile:
     if (lane == 0) {
         s_wave_sum[wave] = wave_total;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        is_last = __hip_atomic_fetch_add(&s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == kTileWaves - 1;
+        is_last = __hip_atomic_fetch_add(&s_arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == tile_waves - 1;
     }
-    is_last = __shfl(is_last, 0, kWave);
+    is_last = wave_uniform(is_last);
     int32_t wg_total = 0;
     if (is_last) {
         // the wave that arrives last publishes the tile total at once, so that later tiles can look past this one
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-        for (int i = 0; i < kTileWaves; ++i) wg_total += s_wave_sum[i];
+        wg_total = sum_of_waves(s_wave_sum, tile_waves, lane);
         if (lane == 0) chain.publish(tile, wg_total);
     }
 
@@ -347,11 +352,18 @@ sample_tile:
             g[u] = R[u] - 1 - slot_no;                // newest first; so too when all candidates are taken
             if (POLICY == 1 && slot_no < k[u] && c[u] > f)
                 g[u] = L[u] + (int32_t)pick_rank(p.seed, p.qid_base + q0 + u * kTeamsPerWave, f, slot_no, (uint64_t)c[u]);
-            if (any_holes && (__shfl(cum[u], team0 + kTeam - 1, kWave) & 2)) g[u] = s_seq[wave][u][lane >> 4][slot_no];
+            if (any_holes && (row_read<kTeam - 1>(cum[u]) & 2)) g[u] = s_seq[wave][u][lane >> 4][slot_no];
             // newest inline block that starts at or before g
             int32_t b = -1;
-#pragma unroll
-            for (int t = 0; t < kInlineBlocks; ++t) b += (t < nb_in[u] && __shfl(cum[u], team0 + t, kWave) <= g[u]) ? 1 : 0;
+            auto from = [&](auto t) { b += t.value < nb_in[u] && row_read<t.value>(cum[u]) <= g[u] ? 1 : 0; };
+            from(std::integral_constant<int, 0>{});
+            from(std::integral_constant<int, 1>{});
+            from(std::integral_constant<int, 2>{});
+            from(std::integral_constant<int, 3>{});
+            from(std::integral_constant<int, 4>{});
+            from(std::integral_constant<int, 5>{});
+            from(std::integral_constant<int, 6>{});
+            static_assert(kInlineBlocks == 7, "every block of a node line");
             const int src = team0 + max(b, 0);
             rb[u].off_lo = (uint32_t)__shfl((int)rec[u].off_lo, src, kWave);
             rb[u].size_hi = (uint32_t)__shfl((int)rec[u].size_hi, src, kWave);
@@ -393,12 +405,15 @@ sample_tile:
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u)
-            if (slot_no < k[u]) e[u][r] = *reinterpret_cast<const Edge*>(p.edges + slot_word(rec_off(rb[u]) + (g[u] - cb[u])));
+            if (slot_no < k[u]) {
+                const BlockWords words(rb[u]);
+                e[u][r] = *reinterpret_cast<const Edge*>(p.edges + words.base + words.words_to(g[u] - cb[u]));
+            }
     }
 
     // ---- outputs --------------------------------------------------------------------------------
     if (is_last) {
-        const int64_t excl = chain.exclusive(tile, lane, p.defer_spins);
+        const int64_t excl = chain.exclusive(tile, lane, p.defer_spins, [](int32_t v) { return wave_sum(v); });
         if (lane == 0) s_tile_base = excl;
     }
     if (p.out_nbr) {
@@ -418,9 +433,8 @@ sample_tile:
         }
     }
     lds_barrier();
-    int64_t wave_row = s_tile_base;
-    const bool dense = wave_row >= 0;      // (or another workgroup writes them)
-    for (int i = 0; i < wave; ++i) wave_row += s_wave_sum[i];
+    const int64_t tile_row = s_tile_base, wave_row = tile_row + sum_of_waves(s_wave_sum, wave, lane);
+    const bool dense = tile_row >= 0;      // (or another workgroup writes them)
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         const int64_t q = q0 + u * kTeamsPerWave;
@@ -447,21 +461,28 @@ sample_tile:
             }
         }
     }
-    if (chain.next(tile, kTileQueries, &s_tile_base, &s_arrived, lane, [&]() { return call_of(p); })) goto sample_tile;
+    if (chain.next(tile, tile_queries, &s_tile_base, &s_arrived, lane, [&]() { return call_of(p); })) goto sample_tile;
 }
 
 template <int POLICY, bool INCL, int CH, int ROUNDS>
 hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
-    constexpr int64_t kTileQueries = kTileWaves * kTeamsPerWave * CH;
-    static_assert(kTileQueries * ROUNDS * kTeam < (1 << kTotalBits), "a tile's total lies below the tag");
-    const int64_t grid = (a.Q + kTileQueries - 1) / kTileQueries;
+    static_assert(kTileWaves * kTeamsPerWave * CH * ROUNDS * kTeam < (1 << kTotalBits), "a tile's total lies below the tag");
+    // Workgroups as small as leave no more of them than compute units, if the workspace has room for the states of their tiles:
+    // sixteen waves of one workgroup issue four to a SIMD in step, and what a step costs is then mostly their turns.  us, 16 / 8 / 4
+    // waves, uniform ids and recent policy, the others alike: 600 queries 7.0 / 6.2 / 6.3, 1000 6.6 / 5.9 / 5.8, 4000 6.5 / 6.5 / 6.1, 8000
+    // 6.7 / 6.2 / 6.7, 16000 7.1 / 7.4 / 7.1; 100 queries 5.7 / 5.6 / 6.2 and over power-law ids 6.7 / 6.5 / 7.3.
+    auto tiles = [&](int waves) { return (a.Q + waves * kTeamsPerWave * CH - 1) / (waves * kTeamsPerWave * CH); };
+    static_assert(kFewWaves * kTeamsPerWave >= kSmallTile, "the workspace has room for the states of the smallest tiles");
+    int waves = a.Q <= kFewQueries ? 2 * kFewWaves : kFewWaves;
+    while (waves < kTileWaves && (tiles(waves) > std::min(kComputeUnits, kMostSmallTiles) || tiles(waves) >= a.scan_states)) waves *= 2;
+    const int64_t grid = tiles(waves);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (grid <= 0) return a.scan_ready ? hipGetLastError() : launch_scan_init(a, 1, stream);
     SampleArgs b = a;
     if (!b.err_flag) b.err_flag = &static_cast<ScanWorkspace*>(a.scan_ws)->error;
     const hipError_t e = ready_tags(b, grid, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((tns_sample_team_kernel<POLICY, INCL, CH, ROUNDS>), dim3((unsigned)grid), dim3(kTileWaves * kWave), 0, stream, b);
+    hipLaunchKernelGGL((tns_sample_team_kernel<POLICY, INCL, CH, ROUNDS>), dim3((unsigned)grid), dim3(waves * kWave), 0, stream, b);
     return hipGetLastError();
 }
 
@@ -469,12 +490,12 @@ template <int POLICY, bool INCL>
 hipError_t launch_team_p(const SampleArgs& a, hipStream_t stream) {
     constexpr int kAllRounds = 4;
     static_assert(kAllRounds * kTeam >= TNS_MAX_FANOUT, "rounds cover the largest fan-out");
-    // Queries per team: one while the batch gives a compute unit no more than one workgroup, two beyond.  us per call with one / two,
-    // 2^21 edges, uniform and power-law ids: recent policy, fan-out 10, 16384 queries 9.8 / 10.3 and 9.5 / 14.3; fan-out 64, 32768
-    // 17.0 / 14.5 and 27.8 / 24.8, 65536 33.0 / 29.4 and 54.2 / 47.8; uniform policy, fan-out 10, 16384 9.7 / 11.0 and 10.2 / 16.2, 65536
-    // 19.0 / 16.9 and 27.2 / 26.4.  The line was drawn while tiles took tickets (32768 queries 18.9 / 15.6); without them one per
-    // team is the faster form there too up to fan-out 16 (9.9 / 10.6 and 13.1 / 14.5, uniform policy 10.3 / 11.6 and 14.6 / 18.2).
-    const bool one = a.Q <= kComputeUnits * (int64_t)(kTileWaves * kTeamsPerWave);
+    // Queries per team: one while that many fit the chip side by side, or one and a half times as many where the slots are one round;
+    // two beyond.  us with one / two, 2^21 edges, uniform and power-law ids: recent policy, fan-out 10, 20000 queries 8.6 / 9.4 and 11.4 /
+    // 12.5, 32768 9.3 / 10.1 and 12.0 / 13.7, 49152 13.7 / 14.0 and 16.8 / 19.1, 65536 16.5 / 14.2 and 20.8 / 19.4; fan-out 64, 10000 8.1 / 10.7
+    // and 12.6 / 19.2, 20000 14.5 / 11.4 and 22.9 / 21.1; uniform policy, fan-out 10, 49152 14.5 / 14.9 and 20.8 / 22.3, 65536 17.3 / 15.2 and
+    // 25.0 / 24.2; fan-out 64, 10000 8.4 / 11.4 and 16.9 / 25.1, 20000 14.7 / 11.8 and 32.6 / 29.0.
+    const bool one = a.Q <= kComputeUnits * (int64_t)(kTileWaves * kTeamsPerWave) * (a.fanout > kTeam ? 1 : 3);
     if (a.fanout > kTeam) return one ? launch_team_t<POLICY, INCL, 1, kAllRounds>(a, stream) : launch_team_t<POLICY, INCL, 2, kAllRounds>(a, stream);
     return one ? launch_team_t<POLICY, INCL, 1, 1>(a, stream) : launch_team_t<POLICY, INCL, 2, 1>(a, stream);
 }

@@ -91,6 +91,24 @@ TNS_HD int64_t slot_word(int64_t s) {
     return line * 32 + (s - line * kSlotsPerLine) * 3;
 }
 
+// words from the begin of a line to a slot that many slots behind it
+TNS_HD uint32_t words_behind(uint32_t slots) { return 3u * slots + 2u * (slots / (uint32_t)kSlotsPerLine); }
+
+// The edges of a block, for addresses of many of its slots: slot i lies at word `base` + words_to(i), below 2^32 words behind it.
+// One division of the block's 39-bit slot index by the slots per line, as 2^32 = 10 * 429496729 + 6, and one of 32 bits per slot;
+// slot_word takes a 64-bit one per slot, about thirty instructions.
+struct BlockWords {
+    uint64_t base;      // of the line with the block's first slot
+    uint32_t at;        // the first slot's position there
+    TNS_HD explicit BlockWords(const BlockRec& r) {
+        const uint32_t lo = r.off_lo, hi = (r.size_hi >> 24) & 0x7fu, q = lo / (uint32_t)kSlotsPerLine;
+        const uint32_t t = lo - q * (uint32_t)kSlotsPerLine + hi * 6u, tq = (t * 205u) >> 11;      // t <= 771; t / kSlotsPerLine
+        base = ((uint64_t)hi * 429496729u + q + tq) * 32u;
+        at = t - tq * (uint32_t)kSlotsPerLine;
+    }
+    TNS_HD uint32_t words_to(int32_t i) const { return words_behind(at + (uint32_t)i); }      // i: up to 2^24
+};
+
 // Search request of the sampling kernel for the recent policy: up to sixteen consecutive slots whose timestamps are
 // compared with one time by as many lanes.
 struct alignas(16) SearchRequest {
