@@ -9,11 +9,11 @@
 
 #include "tns_chain.h"
 #include "tns_kernels.h"
+#include "tns_lanes.h"
 
 namespace tns {
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kXcds = 8;
 
 // Workgroup -> tile mapping that gives each XCD (own L2) one contiguous range of tiles; the
@@ -43,32 +43,6 @@ __device__ __forceinline__ uint64_t pick_rank(uint64_t seed, int64_t qid, int32_
     z ^= z >> 31;
     return ((z >> 32) * c) >> 32;
 }
-
-// Moves inside a row of sixteen lanes are part of a vector instruction (DPP); a shuffle is a round trip through the LDS unit, some
-// sixty cycles each, and what waits for a shuffle waits for all of it.  Called by the whole wave.
-template <int LANE>
-__device__ __forceinline__ int32_t row_read(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + LANE, 0xf, 0xf, true); }      // of lane LANE of the row
-template <int BY>
-__device__ __forceinline__ int32_t row_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x110 + BY, 0xf, 0xf, true); }          // of the lane BY below, 0 at the row's begin
-
-__device__ __forceinline__ int32_t row_inclusive_scan(int32_t v) {
-    v += row_up<1>(v);
-    v += row_up<2>(v);
-    v += row_up<4>(v);
-    return v + row_up<8>(v);
-}
-__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v) {
-    v = row_inclusive_scan(v);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);            // rows 1 and 3: what the row before them has in its last lane
-    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // rows 2 and 3: what lane 31 has
-}
-// Sum over the first n of the workgroup's waves (at most sixteen), whose own sums lie in LDS: a value per lane and one LDS access, where
-// a loop over the waves waits for one access after the other.
-__device__ __forceinline__ int32_t sum_of_waves(const int32_t* s_wave_sum, int n, int lane) {
-    const int w = lane & 15, v = s_wave_sum[w];
-    return __builtin_amdgcn_readlane(row_inclusive_scan(w < n ? v : 0), 15);
-}
-__device__ __forceinline__ int32_t wave_sum(int32_t v) { return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kWave - 1); }
 
 // Instance of query q, one of the wave's 64 consecutive queries from q0 on: instance b owns queries rowptr[b] ..
 // rowptr[b + 1] - 1.  The wave finds the instance of its first query together, 64 probes a round (two dependent reads

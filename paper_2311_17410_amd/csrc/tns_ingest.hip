@@ -15,6 +15,7 @@
 // and made room in the pools.
 #include "tns_ingest.h"
 #include "tns_chain.h"
+#include "tns_lanes.h"
 
 #include <algorithm>
 
@@ -23,7 +24,6 @@
 namespace tns {
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kThreads = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanTile = kThreads * kScanPer;
@@ -40,11 +40,6 @@ static_assert(sizeof(SegPlan) == 32, "32 bytes per segment");
 
 __device__ __forceinline__ void report(IngestStatus* st, int status, int64_t pos) {
     atomicMin(&st->err_word, ((unsigned long long)pos << 8) | (unsigned long long)(-status));
-}
-
-__device__ __forceinline__ int64_t wave_sum64(int64_t v) {
-    for (int d = 32; d >= 1; d >>= 1) v += (int64_t)__shfl_xor((long long)v, d, kWave);
-    return v;
 }
 
 __global__ void __launch_bounds__(64) k_status_reset(IngestStatus* st) {
@@ -75,15 +70,6 @@ __global__ void __launch_bounds__(kThreads) k_scan64_sums(const int64_t* __restr
     if (threadIdx.x == 0) sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 }
 
-__device__ __forceinline__ int64_t wave_inclusive64(int64_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t u = (int64_t)__shfl_up((long long)v, d, kWave);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
-
 // one workgroup: exclusive scan of the tile sums in place, total to *total_out
 __global__ void __launch_bounds__(1024) k_scan64_top(int64_t* __restrict__ sums, int64_t nb, int64_t* __restrict__ total_out) {
     __shared__ int64_t s_w[16];
@@ -94,7 +80,7 @@ __global__ void __launch_bounds__(1024) k_scan64_top(int64_t* __restrict__ sums,
     for (int64_t base = 0; base < nb; base += 1024) {
         const int64_t i = base + threadIdx.x;
         const int64_t v = i < nb ? sums[i] : 0;
-        const int64_t inc = wave_inclusive64(v, lane);
+        const int64_t inc = wave_inclusive_scan64(v);
         if (lane == kWave - 1) s_w[wave] = inc;
         __syncthreads();
         int64_t off = 0, all = 0;
@@ -125,7 +111,7 @@ __global__ void __launch_bounds__(kThreads) k_scan64_apply(const int64_t* in, in
         v[i] = base + i < n ? in[base + i] : 0;
         s += v[i];
     }
-    const int64_t inc = wave_inclusive64(s, lane);
+    const int64_t inc = wave_inclusive_scan64(s);
     if (lane == kWave - 1) s_w[wave] = inc;
     __syncthreads();
     int64_t run = sums[blockIdx.x] + (inc - s);
@@ -316,20 +302,24 @@ struct SegNode {
     NodeAux ax;
     float t_first;
 };
-__device__ __forceinline__ void load_segment_node(const IngestArgs& a, uint32_t v, uint32_t first, SegNode& n) {
+__device__ __forceinline__ void load_node(const IngestArgs& a, uint32_t v, SegNode& n) {
     if ((uint64_t)v >= (uint64_t)a.num_nodes) return;      // out-of-range ids were reported with the keys
     const int64_t nidx = a.node_base + v;
     n.h = *reinterpret_cast<const uint4*>(&a.nodes[nidx]);
     n.r0 = *(reinterpret_cast<const uint4*>(&a.nodes[nidx]) + 1);
     n.ax = a.aux[nidx];
-    n.t_first = a.ts[first];
+}
+__device__ __forceinline__ void load_segment_node(const IngestArgs& a, uint32_t v, uint32_t first, SegNode& n) {
+    load_node(a, v, n);
+    if ((uint64_t)v < (uint64_t)a.num_nodes) n.t_first = a.ts[first];
 }
 
 // What one segment (the batch's edges p0..p1 of one source node, sorted) needs: how many edges the tail block
 // still takes, the new blocks' capacity and number, the edge lines and directory records to reserve.
-// v: the node, mm: the number of edges.
+// v: the node, mm: the number of edges, too_old(): called where the node has a later edge than the segment's first.
+template <class TooOld>
 __device__ __forceinline__ void plan_segment(const IngestArgs& a, uint32_t v, const SegNode& n, int64_t mm, SegPlan& P, int64_t& lines,
-                                             int64_t& dirs, int64_t& blocks, int64_t& slots) {
+                                             int64_t& dirs, int64_t& blocks, int64_t& slots, const TooOld& too_old) {
     if ((uint64_t)v >= (uint64_t)a.num_nodes) return;
     const int64_t nidx = a.node_base + v;
     const uint4 h = n.h, r0 = n.r0;
@@ -345,7 +335,7 @@ __device__ __forceinline__ void plan_segment(const IngestArgs& a, uint32_t v, co
         } else {
             tr = *tail_of(a, nd, nidx);
         }
-        if (t_first < tr.t_max) report(a.status, TNS_EORDER, a.m + (int64_t)v);
+        if (t_first < tr.t_max) too_old();
         room = ax.tail_cap - rec_size(tr);
         P.tail_slot = rec_off(tr) + rec_size(tr);
     }
@@ -408,7 +398,8 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
             const int32_t p0 = seg_start[s];
             SegNode n{};
             load_segment_node(a, (uint32_t)(key[p0] >> 32), val[p0], n);
-            plan_segment(a, (uint32_t)(key[p0] >> 32), n, seg_start[s + 1] - p0, P, lines, dirs, blocks, slots);
+            plan_segment(a, (uint32_t)(key[p0] >> 32), n, seg_start[s + 1] - p0, P, lines, dirs, blocks, slots,
+                         [&]() { report(a.status, TNS_EORDER, a.m + (int64_t)(key[p0] >> 32)); });
             plan[s] = P;
         }
         need_lines[s] = lines;
@@ -416,6 +407,10 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
     }
     add_block_totals(a.status, blocks, slots);
 }
+
+// Loads of these values are requested together: the compiler would otherwise request one, wait for it, and use its register for the next.
+__device__ __forceinline__ void side_by_side(int32_t& a, int32_t& b, int32_t& c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
+__device__ __forceinline__ void side_by_side(uint32_t& a, uint32_t& b, uint32_t& c, int64_t& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
 
 // A planned batch as the apply phase reads it, left in memory by the planning kernels.
 struct PlannedBatch {
@@ -428,68 +423,88 @@ struct PlannedBatch {
     const int64_t* __restrict__ dir_base;
     __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(key[p] >> 32); }
     __device__ __forceinline__ uint32_t position(int64_t p) const { return val[p]; }
-    __device__ __forceinline__ int64_t segment(int64_t p) const { return head_excl[p] + (is_head(key, p) ? 1 : 0) - 1; }
+    __device__ __forceinline__ float time(const IngestArgs& a, int64_t p) const { return a.ts[val[p]]; }
+    __device__ __forceinline__ void positions(int32_t (&p)[3]) const {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) p[i] = (int32_t)val[p[i]];
+        side_by_side(p[0], p[1], p[2]);
+    }
+    __device__ __forceinline__ float time_at(const IngestArgs& a, int32_t position) const { return a.ts[position]; }
 };
 
-// One thread per segment: tail record, new block records, node entry, builder state.
+// One thread per segment: tail record, new block records, node entry, builder state.  n: the node as it was when the segment was planned.
+// Everything is read before the first store: a load behind stores is only waited for together with them.
+struct SegTimes { float tail, first, last; };      // of the last edge for the tail block; of the first new block's first and last
 template <class Batch>
-__device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, int64_t s) {
-    const SegPlan P = b.plan[s];
-    const int32_t p0 = b.seg_start[s], p1 = b.seg_start[s + 1];
+__device__ __forceinline__ SegTimes segment_times(const IngestArgs& a, const Batch& b, const SegPlan& P, int32_t p0, int32_t p1) {
+    const int32_t fresh = min(p0 + P.take, p1 - 1);
+    int32_t at[3] = {p0 + max(P.take, 1) - 1, fresh, P.cap < p1 - fresh ? max(fresh + P.cap - 1, p0) : p1 - 1};
+    b.positions(at);
+    return SegTimes{b.time_at(a, at[0]), b.time_at(a, at[1]), b.time_at(a, at[2])};
+}
+template <class Batch>
+__device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, int64_t s, const SegPlan& P, int32_t p0, int32_t p1, int64_t nidx,
+                                           const SegNode& n, const SegTimes& times) {
     const int64_t mm = p1 - p0;
-    const int64_t nidx = a.node_base + b.source(p0);
     NodeLine* N = &a.nodes[nidx];
-    NodeAux ax = a.aux[nidx];
-    const int32_t nb = N->nblocks;
+    const int32_t nb = (int32_t)n.h.x;
+    const int64_t degree_before = (int32_t)n.h.y, after = (int64_t)nb + P.nbn;
+    uint32_t dir_line = n.h.z;
+    BlockRec tail;                         // inline list: its newest block
+    tail.t_min = __uint_as_float(n.r0.x); tail.t_max = __uint_as_float(n.r0.y); tail.off_lo = n.r0.z; tail.size_hi = n.r0.w;
     if (P.take > 0) {
-        BlockRec* tr = nb <= kInlineBlocks ? &N->rec[0] : &a.dir[(int64_t)N->dir_line * kDirAlign + nb - 1];
-        const BlockRec o = *tr;
-        *tr = make_rec(o.t_min, a.ts[b.position(p0 + P.take - 1)], rec_off(o), rec_size(o) + P.take, rec_tombstones(o));
+        BlockRec* tr = nb <= kInlineBlocks ? &N->rec[0] : &a.dir[(int64_t)dir_line * kDirAlign + nb - 1];
+        BlockRec o = tail;
+        if (nb > kInlineBlocks) o = *tr;
+        o = make_rec(o.t_min, times.tail, rec_off(o), rec_size(o) + P.take, rec_tombstones(o));
+        tail = o;
+        *tr = o;
     }
-    const int64_t degree_before = N->degree;
-    N->degree += (int32_t)mm;
     if (P.nbn > 0) {
+        NodeAux ax = n.ax;
         const int64_t lines = lines_of_blocks(P.cap, P.nbn, P.k0);
         const int64_t line0 = a.used_lines + b.lines_base[s];
         if (line0 + lines > a.cap_lines) { atomicOr(&a.status->internal, 1u); return; }
-        const int64_t after = (int64_t)nb + P.nbn;
         const int64_t rest = mm - P.take;
         BlockRec* run = nullptr;
         if (after > kInlineBlocks) {
             if (after > ax.dir_cap) {
-                const int64_t n = dir_run_for(after, ax.dir_cap);
+                const int64_t room = dir_run_for(after, ax.dir_cap);
                 const int64_t start = a.used_dir + b.dir_base[s];
-                if (start + n > a.cap_dir) { atomicOr(&a.status->internal, 2u); return; }
+                if (start + room > a.cap_dir) { atomicOr(&a.status->internal, 2u); return; }
                 BlockRec* dst = a.dir + start;
                 uint32_t* dcum = a.dir_cum + start;
                 if (nb <= kInlineBlocks) {
                     uint32_t before = 0;
-                    for (int j = 0; j < nb; ++j) {                                       // oldest first
-                        const BlockRec o = N->rec[nb - 1 - j];
-                        dst[j] = o;
-                        dcum[j] = before;
+                    for (int j = nb - 1; j >= 0; --j) {                                  // oldest first
+                        const BlockRec o = j > 0 ? N->rec[j] : tail;
+                        dst[nb - 1 - j] = o;
+                        dcum[nb - 1 - j] = before;
                         before += (uint32_t)rec_size(o);
                     }
                 } else {
-                    const BlockRec* old = a.dir + (int64_t)N->dir_line * kDirAlign;
-                    const uint32_t* ocum = a.dir_cum + (int64_t)N->dir_line * kDirAlign;
+                    const BlockRec* old = a.dir + (int64_t)dir_line * kDirAlign;
+                    const uint32_t* ocum = a.dir_cum + (int64_t)dir_line * kDirAlign;
                     for (int32_t j = 0; j < nb; ++j) {
                         dst[j] = old[j];
                         dcum[j] = ocum[j];
                     }
                 }
-                N->dir_line = (uint32_t)(start / kDirAlign);
-                ax.dir_cap = (int32_t)n;
+                dir_line = (uint32_t)(start / kDirAlign);
+                ax.dir_cap = (int32_t)room;
             }
-            run = a.dir + (int64_t)N->dir_line * kDirAlign;
+            run = a.dir + (int64_t)dir_line * kDirAlign;
         } else {
-            for (int j = nb - 1; j >= 0; --j) N->rec[j + P.nbn] = N->rec[j];            // newest first: make room in front
+            for (int j = nb - 1; j > 0; --j) N->rec[j + P.nbn] = N->rec[j];              // newest first: room in front
+            if (nb > 0) N->rec[P.nbn] = tail;
         }
-        uint32_t* run_cum = run ? a.dir_cum + (int64_t)N->dir_line * kDirAlign : nullptr;
+        uint32_t* run_cum = run ? a.dir_cum + (int64_t)dir_line * kDirAlign : nullptr;
         for (int32_t j = 0; j < P.nbn; ++j) {
             const int64_t first = (int64_t)p0 + P.take + (int64_t)j * P.cap;
             const int64_t size = min((int64_t)P.cap, rest - (int64_t)j * P.cap);
-            const BlockRec r = make_rec(a.ts[b.position(first)], a.ts[b.position(first + size - 1)], block_slot(P, line0, j), (int32_t)size);
+            float t_min = times.first, t_max = times.last;
+            if (j > 0) { t_min = b.time(a, first); t_max = b.time(a, first + size - 1); }
+            const BlockRec r = make_rec(t_min, t_max, block_slot(P, line0, j), (int32_t)size);
             if (run) {
                 run[nb + j] = r;
                 run_cum[nb + j] = (uint32_t)(degree_before + P.take + (int64_t)j * P.cap);   // edges in the older blocks
@@ -497,7 +512,6 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, 
                 N->rec[P.nbn - 1 - j] = r;
             }
         }
-        N->nblocks = (int32_t)after;
         ax.tail_cap = P.cap;
         if (P.cap < kSlotsPerLine) {
             const int32_t per_line = kSlotsPerLine / P.cap, rem = P.nbn - P.k0;
@@ -508,8 +522,11 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, 
                 ax.slab_used += P.nbn * P.cap;
             }
         }
+        a.aux[nidx] = ax;
     }
-    a.aux[nidx] = ax;
+    N->nblocks = (int32_t)after;
+    N->degree = (int32_t)(degree_before + mm);
+    N->dir_line = dir_line;
 }
 
 // The record made ready for the next batch (`internal` stays: it is reported by the next read-back).
@@ -527,20 +544,19 @@ __device__ __forceinline__ void ready_status(IngestStatus* st) {
 // One thread per edge (sorted position): what is stored, and its slot from the segment's plan.
 struct EdgeWords { uint32_t ts, nbr, eid; };
 __device__ __forceinline__ EdgeWords load_edge(const IngestArgs& a, uint32_t e) {
-    return EdgeWords{__float_as_uint(a.ts[e]), (uint32_t)a.dst[e], (uint32_t)(a.eid ? a.eid[e] : (int32_t)(a.eid_base + (int64_t)e))};
+    const int32_t* const ids = a.eid ? a.eid : a.dst;      // (no load sits in a branch)
+    const uint32_t id = (uint32_t)ids[e];
+    return EdgeWords{__float_as_uint(a.ts[e]), (uint32_t)a.dst[e], a.eid ? id : (uint32_t)(int32_t)(a.eid_base + (int64_t)e)};
 }
-template <class Batch>
-__device__ __forceinline__ void apply_edge(const IngestArgs& a, const Batch& b, int64_t p, const EdgeWords& edge) {
-    const int64_t s = b.segment(p);
-    const SegPlan P = b.plan[s];
-    const int64_t r = p - b.seg_start[s];
+// r: the edge's number in its segment; lines_base: the segment's
+__device__ __forceinline__ void apply_edge(const IngestArgs& a, const SegPlan& P, int64_t r, int64_t lines_base, const EdgeWords& edge) {
     int64_t slot;
     if (r < P.take) {
         slot = P.tail_slot + r;
     } else {
         const int64_t rr = r - P.take;
         const int32_t j = (int32_t)((uint32_t)rr / (uint32_t)P.cap);      // both below 2^24
-        slot = block_slot(P, a.used_lines + b.lines_base[s], j) + (rr - (int64_t)j * P.cap);
+        slot = block_slot(P, a.used_lines + lines_base, j) + (rr - (int64_t)j * P.cap);
     }
     if (slot / kSlotsPerLine >= a.cap_lines) { atomicOr(&a.status->internal, 4u); return; }
     const int64_t w = slot_word(slot);
@@ -558,12 +574,29 @@ __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const Pl
     // the node part first: it is the longer chain of dependent reads
     if (blockIdx.x < node_blocks) {
         const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-        if (s < num_segments) apply_node(a, b, s);
+        if (s < num_segments) {
+            const SegPlan P = b.plan[s];
+            const int32_t p0 = b.seg_start[s], p1 = b.seg_start[s + 1];
+            const int64_t nidx = a.node_base + b.source(p0);
+            SegNode n;
+            n.h = *reinterpret_cast<const uint4*>(&a.nodes[nidx]);
+            n.r0 = *(reinterpret_cast<const uint4*>(&a.nodes[nidx]) + 1);
+            n.ax = a.aux[nidx];
+            apply_node(a, b, s, P, p0, p1, nidx, n, segment_times(a, b, P, p0, p1));
+        }
     } else {
         const int64_t p = (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x;
         // (the host has read the record or has a copy of it: the next plan needs no launch of its own for it)
         if (p == 0) ready_status(a.status);
-        if (p < a.m) apply_edge(a, b, p, load_edge(a, b.position(p)));
+        if (p < a.m) {
+            uint32_t e = b.position(p), own = b.source(p), before = b.source(p > 0 ? p - 1 : 0);
+            int64_t seg = b.head_excl[p];
+            side_by_side(e, own, before, seg);
+            if (p > 0 && own == before) --seg;
+            const SegPlan P = b.plan[seg];
+            const int64_t r = p - b.seg_start[seg], lines_base = b.lines_base[seg];
+            apply_edge(a, P, r, lines_base, load_edge(a, e));
+        }
     }
 }
 
@@ -603,12 +636,7 @@ constexpr uint32_t kInternalScan = 8u;                  // IngestStatus::interna
 template <int WAVES = kThreads / kWave>
 __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* s_wave /* [WAVES] */, int64_t& total) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    int64_t inc = v;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t u = (int64_t)__shfl_up((long long)inc, d, kWave);
-        if (lane >= d) inc += u;
-    }
+    const int64_t inc = wave_inclusive_scan64(v);
     if (lane == kWave - 1) s_wave[wave] = inc;
     __syncthreads();
     int64_t off = 0;
@@ -916,17 +944,14 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     __syncthreads();
     SegPlan P{};
     int64_t lines = 0, dirs = 0, blocks = 0, slots = 0;
-    if (head) plan_segment(a, (uint32_t)(k >> 32), node, s_start[local + 1] - p, P, lines, dirs, blocks, slots);
+    if (head) plan_segment(a, (uint32_t)(k >> 32), node, s_start[local + 1] - p, P, lines, dirs, blocks, slots,
+                           [&]() { report(a.status, TNS_EORDER, a.m + (int64_t)(k >> 32)); });
     // exclusive sums of the scans' values over the workgroup
     int64_t v[kPlanScans] = {((int64_t)(head ? 1 : 0) << 32) | blocks, lines, dirs, slots}, total[kPlanScans];
 #pragma unroll
     for (int i = 0; i < kPlanScans; ++i) {
         const int64_t own = v[i];
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int64_t u = (int64_t)__shfl_up((long long)v[i], d, kWave);
-            if (lane >= d) v[i] += u;
-        }
+        v[i] = wave_inclusive_scan64(own);
         if (lane == kWave - 1) s_sum[i][wave] = v[i];
         v[i] -= own;
     }
@@ -977,54 +1002,34 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     }
 }
 
-// Two exclusive scans over the workgroup side by side.
-template <int WAVES>
-__device__ __forceinline__ void block_exclusive_scan2(int64_t (&v)[2], int64_t (*s_wave)[WAVES] /* [2][WAVES] */, int64_t (&total)[2]) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    int64_t own[2] = {v[0], v[1]};
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t u0 = (int64_t)__shfl_up((long long)v[0], d, kWave), u1 = (int64_t)__shfl_up((long long)v[1], d, kWave);
-        if (lane >= d) { v[0] += u0; v[1] += u1; }
-    }
-    if (lane == kWave - 1) { s_wave[0][wave] = v[0]; s_wave[1][wave] = v[1]; }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        // lane w of every wave adds up the waves: a value per lane instead of a loop over all of them
-        int64_t x = lane < WAVES ? s_wave[i][lane] : 0;
-        int64_t before = lane < wave ? x : 0;
-        for (int d = WAVES / 2; d >= 1; d >>= 1) {
-            x += (int64_t)__shfl_xor((long long)x, d, kWave);
-            before += (int64_t)__shfl_xor((long long)before, d, kWave);
-        }
-        total[i] = (int64_t)__shfl((long long)x, 0, kWave);
-        v[i] += (int64_t)__shfl((long long)before, 0, kWave) - own[i];
-    }
-    __syncthreads();
-}
-
 // A batch of at most kSmallBatch edges (a mini-batch of a stream), planned and applied by one workgroup: such a batch
-// spends its time in dependent launches otherwise.  Everything between the batch and the store stays in LDS; the record goes
-// to the host while the store is being changed.  Sorted by (source, arrival) with a stable radix sort, six bits a pass: a
-// wave ranks 128 keys with ballots, and the 64 x 16 counts of a pass are one per thread for its scan.  As a bitonic network of
-// 66 steps the sort took 13.5 of 28 us, and the apply phase was a launch of its own (64 batches of 2000 power-law edges, each
-// sampled, into a new store: 3.80 -> 3.09 ms).  Every thread has two edges and up to two segments; their reads are requested together,
-// before the loops that use them one after the other, and the edges' words while the nodes are changed (the same: 2.86 -> 2.66 ms).
+// spends its time in dependent launches otherwise.  Everything between the batch and the store stays in LDS, the batch's times and
+// errors among it; the record goes to the host while the store is being changed.  Sorted by (source, arrival) with a stable radix
+// sort, up to nine bits a pass: a wave ranks 128 keys with ballots, and the counts of a pass are scanned by all threads.
+// What bounds it is one workgroup's chain of steps: keys, passes, segments, plans, record, nodes, edges.  So a thread's two edges and
+// two segments have their reads requested together and what the plan has read of a node is kept for its change; sums over lanes are
+// vector instructions and not shuffles.  Batch of 2000 power-law edges over 2^16 nodes, us from the start: sorted 8.0 -> 7.6, planned 14.4 ->
+// 13.9, record on its way 17.1 -> 15.2, done 26.4 -> 22.4, in a stream of batches 25.9 -> 21.1; before that, as a bitonic network of 66 steps, the sort alone took 13.5.
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave, kSmallItems = (int)kSmallBatch / kSmallThreads;
-constexpr int kSmallDigit = 6, kSmallBins = 1 << kSmallDigit;
+constexpr int kSender = kSmallThreads - kWave;                             // whose wave has fewest segments: hands the record over
+constexpr int kSmallDigitLeast = 6, kSmallDigitMost = 9;                 // bits a pass (six: a count per thread)
 struct SmallShared {
     uint64_t key[kSmallBatch];           // sorted: source in the high word, batch position in the low one
-    SegPlan plan[kSmallBatch];
+    float ts[kSmallBatch];               // by batch position
+    union {
+        SegPlan plan[kSmallBatch];
+        int32_t count[(1 << kSmallDigitMost) * (kSmallWaves + 1)];      // of a sorting pass: [digit][wave], a word of padding per digit
+    };
     int64_t lines_base[kSmallBatch], dir_base[kSmallBatch];
     int32_t seg_start[kSmallBatch + 1];
     int32_t seg_of[kSmallBatch];
-    int32_t count[kSmallBins * (kSmallWaves + 1)];      // [digit][wave], a word of padding per digit
-    int64_t wave[2][kSmallWaves];
+    int64_t wave[4][kSmallWaves];        // edge lines, directory records, blocks, slots
     int32_t wave32[kSmallWaves];
-    unsigned long long totals[2];
+    unsigned long long err_word;         // as in IngestStatus
+    uint32_t unsorted;
     int32_t go;
 };
+static_assert(sizeof(SmallShared) <= 160 << 10, "one workgroup's LDS");
 struct SmallBatch {                      // as PlannedBatch, in LDS
     const SmallShared& sh;
     const SegPlan* plan;
@@ -1034,21 +1039,32 @@ struct SmallBatch {                      // as PlannedBatch, in LDS
         : sh(x), plan(x.plan), seg_start(x.seg_start), lines_base(x.lines_base), dir_base(x.dir_base) {}
     __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(sh.key[p] >> 32); }
     __device__ __forceinline__ uint32_t position(int64_t p) const { return (uint32_t)sh.key[p]; }
-    __device__ __forceinline__ int64_t segment(int64_t p) const { return sh.seg_of[p]; }
+    __device__ __forceinline__ float time(const IngestArgs&, int64_t p) const { return sh.ts[position(p)]; }
+    __device__ __forceinline__ void positions(int32_t (&p)[3]) const {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) p[i] = (int32_t)position(p[i]);
+    }
+    __device__ __forceinline__ float time_at(const IngestArgs&, int32_t position) const { return sh.ts[position]; }
 };
 
-__global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs a, int bits, uint64_t* __restrict__ key,
+// digit: bits a pass
+__global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs a, int bits, int digit, uint64_t* __restrict__ key,
                                                                uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
                                                                int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
                                                                int64_t* __restrict__ lines_base, int64_t* __restrict__ dir_base) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     SmallShared& sh = *reinterpret_cast<SmallShared*>(s_raw);
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, m = (int)a.m;
-    if (t < 2) sh.totals[t] = 0;
     // a wave owns kSmallItems * 64 consecutive keys, item by item; the items' reads are requested together
     uint64_t k[kSmallItems];
     int32_t v[kSmallItems], e[kSmallItems], touched[2 * kSmallItems];
     float ts[kSmallItems], before[kSmallItems];
+    IngestStatus rec{};
+    if (t == kSender) {
+        sh.err_word = ~0ull;
+        sh.unsorted = 0;
+        rec.internal = a.status->internal;         // (what earlier launches have left; this batch's own errors are in LDS)
+    }
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int i = min((wave * kSmallItems + j) * kWave + lane, m - 1);
@@ -1057,6 +1073,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
         before[j] = a.ts[i > 0 ? i - 1 : 0];
         e[j] = a.eid ? a.eid[i] : 0;
     }
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         // brings the node's entry and builder state into the L2 while the keys are sorted
@@ -1064,62 +1081,77 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
         touched[2 * j] = a.nodes[nidx].nblocks;
         touched[2 * j + 1] = a.aux[nidx].tail_cap;
     }
+    auto report_here = [&](int status, int64_t pos) { atomicMin(&sh.err_word, ((unsigned long long)pos << 8) | (unsigned long long)(-status)); };
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int i = (wave * kSmallItems + j) * kWave + lane;
         k[j] = ~0ull;                    // beyond the batch: last in every pass
         if (i < m) {
-            if ((uint64_t)(uint32_t)v[j] >= (uint64_t)a.num_nodes) report(a.status, TNS_ERANGE, i);
-            else if (ts[j] != ts[j]) report(a.status, TNS_EORDER, i);
-            else if (e[j] < 0) report(a.status, TNS_EINVAL, i);
-            if (i > 0 && before[j] > ts[j]) atomicOr(&a.status->unsorted, 1u);
+            if ((uint64_t)(uint32_t)v[j] >= (uint64_t)a.num_nodes) report_here(TNS_ERANGE, i);
+            else if (ts[j] != ts[j]) report_here(TNS_EORDER, i);
+            else if (e[j] < 0) report_here(TNS_EINVAL, i);
+            if (i > 0 && before[j] > ts[j]) sh.unsorted = 1;
             k[j] = ((uint64_t)(uint32_t)v[j] << 32) | (uint32_t)i;
+            sh.ts[i] = ts[j];
         }
     }
+    const int bins = 1 << digit, per = bins * kSmallWaves / kSmallThreads;      // counts per thread
+    uint32_t to[kSmallItems];
 #pragma unroll 1
-    for (int shift = 0; shift < bits; shift += kSmallDigit) {
+    for (int shift = 0; shift < bits; shift += digit) {
         // rank among the wave's equal digits: those of earlier items, then those of lower lanes
-        sh.count[lane * (kSmallWaves + 1) + wave] = 0;
+        for (int i = lane; i < bins; i += kWave) sh.count[i * (kSmallWaves + 1) + wave] = 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         uint32_t d[kSmallItems], rank[kSmallItems];
+        uint64_t same[kSmallItems];
 #pragma unroll
         for (int j = 0; j < kSmallItems; ++j) {
-            d[j] = (uint32_t)(k[j] >> (32 + shift)) & (uint32_t)(kSmallBins - 1);
-            uint64_t same = ~0ull;
+            d[j] = (uint32_t)(k[j] >> (32 + shift)) & (uint32_t)(bins - 1);
+            same[j] = ~0ull;
+        }
+        for (int b = 0; b < digit; ++b) {
 #pragma unroll
-            for (int b = 0; b < kSmallDigit; ++b) {
+            for (int j = 0; j < kSmallItems; ++j) {
                 const bool bit = (d[j] >> b) & 1u;
                 const uint64_t bal = __ballot(bit);
-                same &= bit ? bal : ~bal;
+                same[j] &= bit ? bal : ~bal;
             }
+        }
+#pragma unroll
+        for (int j = 0; j < kSmallItems; ++j) {
             int32_t* const c = &sh.count[d[j] * (kSmallWaves + 1) + wave];
-            const uint32_t earlier = (uint32_t)*c;
-            rank[j] = earlier + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            const uint32_t earlier = (uint32_t)*c, lower = (uint32_t)__popcll(same[j] & ((1ull << lane) - 1ull));
+            rank[j] = earlier + lower;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if ((same & ((1ull << lane) - 1ull)) == 0) *c = (int32_t)(earlier + (uint32_t)__popcll(same));
+            if (lower == 0) *c = (int32_t)(earlier + (uint32_t)__popcll(same[j]));
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
-        // exclusive scan of the counts, digit by digit and wave by wave: one per thread
-        int32_t* const mine = &sh.count[(t / kSmallWaves) * (kSmallWaves + 1) + (t % kSmallWaves)];
-        const int32_t own = *mine;
-        int32_t inc = own;
-#pragma unroll
-        for (int x = 1; x < kWave; x <<= 1) {
-            const int32_t u = __shfl_up(inc, x, kWave);
-            if (lane >= x) inc += u;
+        // exclusive scan of the counts, digit by digit and wave by wave: `per` consecutive ones per thread
+        int32_t own = 0;
+        for (int i = 0; i < per; ++i) {
+            const int c = t * per + i;
+            own += sh.count[c / kSmallWaves * (kSmallWaves + 1) + c % kSmallWaves];
         }
+        const int32_t inc = wave_inclusive_scan(own);
         if (lane == kWave - 1) sh.wave32[wave] = inc;
         __syncthreads();
-        int32_t before = lane < wave ? sh.wave32[lane & (kSmallWaves - 1)] : 0;
-        for (int x = kSmallWaves / 2; x >= 1; x >>= 1) before += __shfl_xor(before, x, kWave);
-        *mine = __shfl(before, 0, kWave) + inc - own;
+        int32_t run = sum_of_waves(sh.wave32, wave, lane) + inc - own;
+        for (int i = 0; i < per; ++i) {
+            const int c = t * per + i;
+            int32_t* const at = &sh.count[c / kSmallWaves * (kSmallWaves + 1) + c % kSmallWaves];
+            const int32_t n = *at;
+            *at = run;
+            run += n;
+        }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kSmallItems; ++j) sh.key[(uint32_t)sh.count[d[j] * (kSmallWaves + 1) + wave] + rank[j]] = k[j];
+        for (int j = 0; j < kSmallItems; ++j) to[j] = (uint32_t)sh.count[d[j] * (kSmallWaves + 1) + wave] + rank[j];
+#pragma unroll
+        for (int j = 0; j < kSmallItems; ++j) sh.key[to[j]] = k[j];
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kSmallItems; ++j) k[j] = sh.key[(wave * kSmallItems + j) * kWave + lane];
@@ -1133,18 +1165,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int p = (wave * kSmallItems + j) * kWave + lane;
-        h[j] = p < m && (p == 0 || (uint32_t)(sh.key[p - 1] >> 32) != (uint32_t)(k[j] >> 32)) ? 1 : 0;
+        h[j] = p < m && (p == 0 || (uint32_t)(sh.key[max(p - 1, 0)] >> 32) != (uint32_t)(k[j] >> 32)) ? 1 : 0;
         heads[j] = __ballot(h[j]);
         in_wave += __popcll(heads[j]);
     }
     if (lane == 0) sh.wave32[wave] = in_wave;
     __syncthreads();
-    int32_t run = 0, nseg = 0;
-    for (int w = 0; w < kSmallWaves; ++w) {
-        const int32_t c = sh.wave32[w];
-        if (w < wave) run += c;
-        nseg += c;
-    }
+    int32_t run = sum_of_waves(sh.wave32, wave, lane);
+    const int32_t nseg = sum_of_waves(sh.wave32, kSmallWaves, lane);
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int p = (wave * kSmallItems + j) * kWave + lane;
@@ -1158,84 +1186,91 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
     }
     __syncthreads();
     // plans, 1024 segments at a time (a loop, not unrolled: the program is fetched once from a cold instruction cache,
-    // and its length is part of what this kernel costs)
-    int64_t all[2] = {0, 0}, blocks = 0, slots = 0;
-    SegNode node[kSmallItems] = {};      // requested for all of them first
+    // and its length is part of what this kernel costs); what is read of all the nodes is requested first
+    SegNode node[kSmallItems] = {};
 #pragma unroll
     for (int j = 0; j < kSmallItems; ++j) {
         const int sgm = t + j * kSmallThreads;
         if (sgm < nseg) {
             const uint64_t k0 = sh.key[sh.seg_start[sgm]];
-            load_segment_node(a, (uint32_t)(k0 >> 32), (uint32_t)k0, node[j]);
+            load_node(a, (uint32_t)(k0 >> 32), node[j]);
+            node[j].t_first = sh.ts[(uint32_t)k0];
         }
     }
-    static_assert(kSmallItems == 2, "the loop takes the next node's place");
+    static_assert(kSmallItems == 2, "the loops take one node or the other");
+    EdgeWords edge[kSmallItems] = {};      // on their way while the nodes are planned
+#pragma unroll
+    for (int j = 0; j < kSmallItems; ++j)
+        if (t + j * kSmallThreads < m) edge[j] = load_edge(a, (uint32_t)sh.key[t + j * kSmallThreads]);
+    int64_t all[4] = {0, 0, 0, 0};
 #pragma unroll 1
     for (int sgm = t; sgm - t < nseg; sgm += kSmallThreads) {
-        int64_t need[2] = {0, 0}, tot[2], b = 0, sl = 0;
+        int64_t need[4] = {0, 0, 0, 0};
         if (sgm < nseg) {
+            const SegNode n = sgm == t ? node[0] : node[1];
             const int p0 = sh.seg_start[sgm];
-            const uint64_t k0 = sh.key[p0];
+            const uint32_t source = (uint32_t)(sh.key[p0] >> 32);
             SegPlan P{};
-            plan_segment(a, (uint32_t)(k0 >> 32), node[0], sh.seg_start[sgm + 1] - p0, P, need[0], need[1], b, sl);
+            plan_segment(a, source, n, sh.seg_start[sgm + 1] - p0, P, need[0], need[1], need[2], need[3],
+                         [&]() { report_here(TNS_EORDER, a.m + (int64_t)source); });
             sh.plan[sgm] = P;
         }
-        blocks += b;
-        slots += sl;
-        block_exclusive_scan2<kSmallWaves>(need, sh.wave, tot);
-        if (sgm < nseg) {
-            sh.lines_base[sgm] = all[0] + need[0];
-            sh.dir_base[sgm] = all[1] + need[1];
+        const bool some = __ballot(sgm < nseg) != 0;        // (waves without a segment leave the sums out)
+        int64_t inc[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (some) inc[i] = wave_inclusive_scan64(need[i]);
+            if (lane == kWave - 1) sh.wave[i][wave] = inc[i];
         }
-        all[0] += tot[0];
-        all[1] += tot[1];
-        node[0] = node[1];
+        __syncthreads();
+        if (some) {
+            const int64_t lines_before = sum_of_waves64(sh.wave[0], wave, lane), dir_before = sum_of_waves64(sh.wave[1], wave, lane);
+            if (sgm < nseg) {
+                sh.lines_base[sgm] = all[0] + lines_before + inc[0] - need[0];
+                sh.dir_base[sgm] = all[1] + dir_before + inc[1] - need[1];
+            }
+        }
+        if (wave == kSmallWaves - 1 || sgm - t + kSmallThreads < nseg) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) all[i] += sum_of_waves64(sh.wave[i], kSmallWaves, lane);      // (for the next segments, and the record)
+        }
+        __syncthreads();
     }
-    blocks = wave_sum64(blocks);
-    slots = wave_sum64(slots);
-    if (lane == 0) {
-        atomicAdd(&sh.totals[0], (unsigned long long)blocks);
-        atomicAdd(&sh.totals[1], (unsigned long long)slots);
-    }
-    wait_for_memory();               // every thread's reports have been performed
-    __syncthreads();
-    IngestStatus rec;
-    if (t == 0) {
-        rec = load_status(a.status);
+    if (t == kSender) {
+        rec.err_word = sh.err_word;
+        rec.unsorted = sh.unsorted;
         rec.num_segments = nseg;
         rec.total_lines = all[0];
         rec.total_dir = all[1];
-        rec.new_blocks = sh.totals[0];
-        rec.new_slots = sh.totals[1];
+        rec.new_blocks = (unsigned long long)all[2];
+        rec.new_slots = (unsigned long long)all[3];
         sh.go = a.host_status && ingest_may_apply(rec, a) ? 1 : 0;
     }
     __syncthreads();
     const bool go = sh.go != 0;
-    if (t == 0) {
+    if (t == kSender) {
         IngestStatus* st = a.status;
         if (go) {
             ready_status(st);
         } else {
-            st->num_segments = rec.num_segments;
-            st->total_lines = rec.total_lines;
-            st->total_dir = rec.total_dir;
-            st->new_blocks = rec.new_blocks;
-            st->new_slots = rec.new_slots;
+            *st = rec;
             __threadfence();
         }
         if (a.host_status) send_to_host(a, rec);
     }
     const SmallBatch batch(sh);
     if (go) {
-        EdgeWords edge[kSmallItems] = {};      // on their way while the nodes are changed
-#pragma unroll
-        for (int j = 0; j < kSmallItems; ++j)
-            if (t + j * kSmallThreads < m) edge[j] = load_edge(a, batch.position(t + j * kSmallThreads));
 #pragma unroll 1
-        for (int s = t; s < nseg; s += kSmallThreads) apply_node(a, batch, s);
+        for (int s = t; s < nseg; s += kSmallThreads) {
+            const SegNode n = s == t ? node[0] : node[1];
+            const SegPlan P = sh.plan[s];
+            const int32_t p0 = sh.seg_start[s], p1 = sh.seg_start[s + 1];
+            apply_node(a, batch, s, P, p0, p1, a.node_base + batch.source(p0), n, segment_times(a, batch, P, p0, p1));
+        }
 #pragma unroll 1
         for (int p = t; p < m; p += kSmallThreads) {
-            apply_edge(a, batch, p, edge[0]);
+            const int32_t sgm = sh.seg_of[p];
+            apply_edge(a, sh.plan[sgm], p - sh.seg_start[sgm], sh.lines_base[sgm], edge[0]);
             edge[0] = edge[1];
         }
     } else {
@@ -1425,7 +1460,8 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
     IngestArgs a = args;
     a.go = c.sums;
     if (a.m <= kSmallBatch) {
-        hipLaunchKernelGGL(k_small_batch, dim3(1), dim3(kSmallThreads), sizeof(SmallShared), stream, a, 2 * bits, c.keyA, c.valA, c.head_excl,
+        const int passes = (2 * bits + kSmallDigitMost - 1) / kSmallDigitMost, digit = std::max(kSmallDigitLeast, (2 * bits + passes - 1) / passes);
+        hipLaunchKernelGGL(k_small_batch, dim3(1), dim3(kSmallThreads), sizeof(SmallShared), stream, a, 2 * bits, digit, c.keyA, c.valA, c.head_excl,
                            c.seg_start, c.plan, c.lines_base, c.dir_base);
         return hipGetLastError();
     }
