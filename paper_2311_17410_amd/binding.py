@@ -48,6 +48,9 @@ class tns_hop_buffers(C.Structure):
     _fields_ = [(n, C.c_void_p) for n in ("nbr", "eid", "ts", "count", "rowptr", "cmp_nbr", "cmp_eid", "cmp_ts")]
 
 
+_HOP_FIELDS = [name for name, _ in tns_hop_buffers._fields_]
+
+
 class TnsError(RuntimeError):
     def __init__(self, status: int, where: str):
         L = lib()
@@ -199,10 +202,10 @@ def tns_run(plan, Q: int, d_targets: int, d_t_start: int, d_t_end: int, d_inst_r
             d_cmp_eid: int = 0, d_cmp_ts: int = 0, d_workspace: int = 0, workspace_bytes: int = 0,
             hip_stream: int = 0) -> None:
     """All d_* arguments are raw device addresses (e.g. ``tensor.data_ptr()``), 0 for NULL."""
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_run(plan, Q, vp(d_targets), vp(d_t_start), vp(d_t_end), vp(d_inst_rowptr), query_id_base,
-                         vp(d_out_nbr), vp(d_out_eid), vp(d_out_ts), vp(d_out_count), vp(d_rowptr), vp(d_cmp_nbr),
-                         vp(d_cmp_eid), vp(d_cmp_ts), vp(d_workspace), workspace_bytes, vp(hip_stream)), "tns_run")
+    # (here and below: the declared argument types make pointers of the integers; an object for each cost 2 us of a call that took 8.5)
+    _check(lib().tns_run(plan, Q, d_targets or None, d_t_start or None, d_t_end or None, d_inst_rowptr or None, query_id_base,
+                         d_out_nbr or None, d_out_eid or None, d_out_ts or None, d_out_count or None, d_rowptr or None, d_cmp_nbr or None,
+                         d_cmp_eid or None, d_cmp_ts or None, d_workspace or None, workspace_bytes, hip_stream or None), "tns_run")
 
 
 def tns_run_status(plan, d_workspace: int = 0, hip_stream: int = 0) -> bool:
@@ -218,10 +221,9 @@ def tns_run_static(plan, Q: int, d_targets: int, d_t_start: int, d_t_end: int, d
                    d_out_nbr: int, d_out_eid: int, d_out_ts: int, d_out_count: int, d_rowptr: int, d_cmp_nbr: int,
                    d_cmp_eid: int, d_cmp_ts: int, hip_stream: int = 0) -> None:
     """tns_run with padding removal on the library's static scratch (no workspace argument)."""
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_run_static(plan, Q, vp(d_targets), vp(d_t_start), vp(d_t_end), vp(d_inst_rowptr), query_id_base,
-                                vp(d_out_nbr), vp(d_out_eid), vp(d_out_ts), vp(d_out_count), vp(d_rowptr), vp(d_cmp_nbr),
-                                vp(d_cmp_eid), vp(d_cmp_ts), vp(hip_stream)), "tns_run_static")
+    _check(lib().tns_run_static(plan, Q, d_targets or None, d_t_start or None, d_t_end or None, d_inst_rowptr or None, query_id_base,
+                                d_out_nbr or None, d_out_eid or None, d_out_ts or None, d_out_count or None, d_rowptr or None, d_cmp_nbr or None,
+                                d_cmp_eid or None, d_cmp_ts or None, hip_stream or None), "tns_run_static")
 
 
 def tns_workspace_khop(plan, fanouts, Q: int) -> int:
@@ -234,31 +236,25 @@ def tns_workspace_khop(plan, fanouts, Q: int) -> int:
 def tns_run_khop(plan, fanouts, delta: float, Q: int, d_targets: int, d_t_start: int, d_t_end: int, d_inst_rowptr: int,
                  query_id_base: int, hops, d_workspace: int, workspace_bytes: int, hip_stream: int = 0) -> None:
     """hops: one dict per hop with the raw device addresses nbr, eid, ts, count, rowptr, cmp_nbr, cmp_eid, cmp_ts."""
-    vp = lambda x: C.c_void_p(x or None)
     fo = (C.c_int32 * len(fanouts))(*fanouts)
-    hb = (tns_hop_buffers * len(hops))()
-    for i, h in enumerate(hops):
-        for name, _ in tns_hop_buffers._fields_:
-            setattr(hb[i], name, h[name] or None)
-    _check(lib().tns_run_khop(plan, len(fanouts), fo, delta, Q, vp(d_targets), vp(d_t_start), vp(d_t_end),
-                              vp(d_inst_rowptr), query_id_base, hb, vp(d_workspace), workspace_bytes, vp(hip_stream)),
+    hb = (tns_hop_buffers * len(hops))(*[tns_hop_buffers(*[h[name] or None for name in _HOP_FIELDS]) for h in hops])
+    _check(lib().tns_run_khop(plan, len(fanouts), fo, delta, Q, d_targets or None, d_t_start or None, d_t_end or None,
+                              d_inst_rowptr or None, query_id_base, hb, d_workspace or None, workspace_bytes, hip_stream or None),
            "tns_run_khop")
 
 
 def tns_compact(plan, Q: int, d_out_nbr: int, d_out_eid: int, d_out_ts: int, d_out_count: int, d_rowptr: int,
                 d_cmp_nbr: int, d_cmp_eid: int, d_cmp_ts: int, d_workspace: int, workspace_bytes: int,
                 hip_stream: int = 0) -> None:
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_compact(plan, Q, vp(d_out_nbr), vp(d_out_eid), vp(d_out_ts), vp(d_out_count), vp(d_rowptr),
-                             vp(d_cmp_nbr), vp(d_cmp_eid), vp(d_cmp_ts), vp(d_workspace), workspace_bytes,
-                             vp(hip_stream)), "tns_compact")
+    _check(lib().tns_compact(plan, Q, d_out_nbr or None, d_out_eid or None, d_out_ts or None, d_out_count or None, d_rowptr or None,
+                             d_cmp_nbr or None, d_cmp_eid or None, d_cmp_ts or None, d_workspace or None, workspace_bytes,
+                             hip_stream or None), "tns_compact")
 
 
 def tns_traffic_model(plan, Q: int, d_targets: int, d_t_start: int, d_t_end: int, d_inst_rowptr: int,
                       query_id_base: int, d_counters: int, hip_stream: int = 0) -> None:
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_traffic_model(plan, Q, vp(d_targets), vp(d_t_start), vp(d_t_end), vp(d_inst_rowptr),
-                                   query_id_base, vp(d_counters), vp(hip_stream)), "tns_traffic_model")
+    _check(lib().tns_traffic_model(plan, Q, d_targets or None, d_t_start or None, d_t_end or None, d_inst_rowptr or None,
+                                   query_id_base, d_counters or None, hip_stream or None), "tns_traffic_model")
 
 
 def tns_stats(plan, instance: int = -1) -> dict:
@@ -283,14 +279,12 @@ def tns_node_blocks(plan, instance: int, node: int) -> dict:
 
 def tns_hbm_probe(mode: int, nontemporal: bool, d_dst: int, d_src: int, nbytes: int, hip_stream: int = 0) -> None:
     """Streaming kernel of known traffic: mode 0 copy, 1 read, 2 write (raw device addresses)."""
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_hbm_probe(mode, 1 if nontemporal else 0, vp(d_dst), vp(d_src), nbytes, vp(hip_stream)), "tns_hbm_probe")
+    _check(lib().tns_hbm_probe(mode, 1 if nontemporal else 0, d_dst or None, d_src or None, nbytes, hip_stream or None), "tns_hbm_probe")
 
 
 def tns_hbm_probe_mix(nontemporal: bool, d_dst: int, write_bytes: int, d_src: int, read_bytes: int, hip_stream: int = 0) -> None:
     """Streaming kernel that reads read_bytes and writes write_bytes, evenly interleaved (measurement aid)."""
-    vp = lambda x: C.c_void_p(x or None)
-    _check(lib().tns_hbm_probe_mix(1 if nontemporal else 0, vp(d_dst), write_bytes, vp(d_src), read_bytes, vp(hip_stream)),
+    _check(lib().tns_hbm_probe_mix(1 if nontemporal else 0, d_dst or None, write_bytes, d_src or None, read_bytes, hip_stream or None),
            "tns_hbm_probe_mix")
 
 
@@ -333,10 +327,9 @@ class Plan:
                 raise ValueError("batch arrays must be contiguous 1-d tensors of the right dtype on the plan's device")
             if t.numel() != src.numel():
                 raise ValueError("src, dst, ts (and eid) must have the same length")
-        with torch.cuda.device(self.device):
-            tns_add_edges_device(self._h, instance, src.data_ptr(), dst.data_ptr(), ts.data_ptr(),
-                                 None if eid is None else eid.data_ptr(), src.numel(),
-                                 torch.cuda.current_stream().cuda_stream)
+        tns_add_edges_device(self._h, instance, src.data_ptr(), dst.data_ptr(), ts.data_ptr(),
+                             None if eid is None else eid.data_ptr(), src.numel(),
+                             torch.cuda.current_stream(self.device).cuda_stream)      # (the library selects the device)
 
     def add_stream(self, stream, instance: int = 0):
         """Ingest a workloads.Stream batch by batch, as the paper's continuous-learning setting does."""
@@ -378,12 +371,11 @@ class Plan:
         if out is None:
             out = self.alloc_outputs(Q, compact)
         p = lambda t: 0 if t is None else t.data_ptr()
-        with torch.cuda.device(self.device):
-            stream = torch.cuda.current_stream().cuda_stream
-            tns_run(self._h, Q, p(targets), p(t_start), p(t_end), p(inst_rowptr), query_id_base,
-                    p(out.get("nbr")), p(out.get("eid")), p(out.get("ts")), p(out.get("count")),
-                    p(out.get("rowptr")), p(out.get("cmp_nbr")), p(out.get("cmp_eid")), p(out.get("cmp_ts")),
-                    p(out.get("workspace")), 0 if out.get("workspace") is None else out["workspace"].numel(), stream)
+        ws = out.get("workspace")
+        tns_run(self._h, Q, p(targets), p(t_start), p(t_end), p(inst_rowptr), query_id_base,
+                p(out.get("nbr")), p(out.get("eid")), p(out.get("ts")), p(out.get("count")),
+                p(out.get("rowptr")), p(out.get("cmp_nbr")), p(out.get("cmp_eid")), p(out.get("cmp_ts")),
+                p(ws), 0 if ws is None else ws.numel(), torch.cuda.current_stream(self.device).cuda_stream)
         return out
 
     def status(self, workspace=None) -> bool:

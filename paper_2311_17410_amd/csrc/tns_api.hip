@@ -93,10 +93,10 @@ public:
         return hipMalloc(p, bytes);
     }
 
-    // memory of the current device, in use by work queued there at most
-    void release(void* p, size_t bytes) {
+    // memory of the current device, in use by work queued there at most; idle: the device has been waited for since it was used last
+    void release(void* p, size_t bytes, bool idle) {
         int dev = 0;
-        if (bytes > kHold || hipGetDevice(&dev) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+        if (bytes > kHold || hipGetDevice(&dev) != hipSuccess || (!idle && hipDeviceSynchronize() != hipSuccess)) {
             (void)hipFree(p);
             return;
         }
@@ -153,6 +153,69 @@ private:
     size_t held_ = 0;
 };
 
+// Page-locked host records of destroyed device-built stores, kept for the next one on the same device: at most kRecords of 128 bytes
+// each, given back by tns_destroy(NULL).  (hipHostMalloc and hipHostFree are some 30 us each: with them, with a wait for the device
+// per array and with the device's record from hipMalloc a store of seven arrays took 111 us to close, now 26.)
+class RecordPool {
+public:
+    struct Record {
+        tns::IngestStatus* host = nullptr;      // followed by a sequence word
+        tns::IngestStatus* dev = nullptr;       // the same memory as the device addresses it
+        int device = 0;
+    };
+    static constexpr size_t kRecords = 16;
+    hipError_t take(Record* r) {
+        hipError_t e = hipGetDevice(&r->device);
+        if (e != hipSuccess) return e;
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            for (size_t i = 0; i < count_; ++i) {
+                if (kept_[i].device != r->device) continue;
+                *r = kept_[i];
+                kept_[i] = kept_[--count_];
+                return hipSuccess;
+            }
+        }
+        e = hipHostMalloc(reinterpret_cast<void**>(&r->host), 2 * sizeof(tns::IngestStatus), hipHostMallocMapped | hipHostMallocCoherent);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&r->dev), r->host, 0);
+        if (e != hipSuccess && r->host) {
+            (void)hipHostFree(r->host);
+            *r = Record{};
+        }
+        return e;
+    }
+    // nothing is on its way to it
+    void release(const Record& r) {
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            if (count_ < kRecords) {
+                kept_[count_++] = r;
+                return;
+            }
+        }
+        (void)hipHostFree(r.host);
+    }
+    void give_back() {
+        Record r;
+        do {
+            r = Record{};
+            std::lock_guard<std::mutex> lock(mutex_);
+            if (count_) r = kept_[--count_];
+        } while (r.host && hipHostFree(r.host) == hipSuccess);
+    }
+
+private:
+    std::mutex mutex_;
+    Record kept_[kRecords];
+    size_t count_ = 0;
+};
+
+RecordPool& record_pool() {
+    alignas(RecordPool) static unsigned char room[sizeof(RecordPool)];
+    static RecordPool* pool = new (room) RecordPool();      // never destroyed, as the device memory's
+    return *pool;
+}
+
 DevicePool& device_pool() {
     alignas(DevicePool) static unsigned char room[sizeof(DevicePool)];
     static DevicePool* pool = new (room) DevicePool();      // never destroyed: the HIP runtime may be gone by then
@@ -179,12 +242,12 @@ struct DeviceArray {
         return on_host ? hipHostMalloc(reinterpret_cast<void**>(p), *got, hipHostMallocMapped | hipHostMallocPortable)
                        : device_pool().take(reinterpret_cast<void**>(p), *got, got);
     }
-    void free_block(T* p, size_t size) const {
+    void free_block(T* p, size_t size, bool idle = false) const {
         if (on_host) (void)hipHostFree(p);
-        else device_pool().release(p, size);
+        else device_pool().release(p, size, idle);
     }
-    void release() {
-        if (ptr) free_block(ptr, bytes);
+    void release(bool idle = false) {
+        if (ptr) free_block(ptr, bytes, idle);
         ptr = nullptr;
         cap = used = 0;
         bytes = 0;
@@ -195,7 +258,9 @@ struct DeviceArray {
 struct DeviceStore {
     DeviceArray<tns::NodeAux> aux;
     DeviceArray<unsigned char> ws;              // scratch of the ingestion kernels, grown on demand
-    tns::IngestStatus* d_status = nullptr;
+    DeviceArray<tns::IngestStatus> status;
+    tns::IngestStatus* d_status = nullptr;      // status.ptr, once the store exists
+    RecordPool::Record record;
     tns::IngestStatus* h_status = nullptr;      // page-locked landing place of the status read-backs, followed by a
                                                 // sequence word; the device can write both (mapped, coherent)
     tns::IngestStatus* h_status_dev = nullptr;  // the same memory as the device addresses it
@@ -316,22 +381,20 @@ int ensure_device_store(tns_plan* plan, hipStream_t stream) {
     if ((rc = grow_device(plan->d_edges, 1024, 4096, stream, "allocating edge data"))) return rc;
     hipError_t e = hipMemsetAsync(plan->d_nodes.ptr, 0, (size_t)total_nodes * sizeof(tns::NodeLine), stream);
     if (e == hipSuccess) e = hipMemsetAsync(ds.aux.ptr, 0, (size_t)total_nodes * sizeof(tns::NodeAux), stream);
-    tns::IngestStatus* st = nullptr;
-    if (e == hipSuccess) e = tns::device_malloc(reinterpret_cast<void**>(&st), sizeof(tns::IngestStatus));
+    if (e == hipSuccess && !ds.status.ptr) e = ds.status.alloc(&ds.status.ptr, 1, &ds.status.bytes);
+    tns::IngestStatus* const st = ds.status.ptr;
     if (e == hipSuccess && !ds.h_status) {
-        e = hipHostMalloc(reinterpret_cast<void**>(&ds.h_status), 2 * sizeof(tns::IngestStatus), hipHostMallocMapped | hipHostMallocCoherent);
+        e = record_pool().take(&ds.record);
         if (e == hipSuccess) {
+            ds.h_status = ds.record.host;
+            ds.h_status_dev = ds.record.dev;
             std::memset(ds.h_status, 0, 2 * sizeof(tns::IngestStatus));
-            e = hipHostGetDevicePointer(reinterpret_cast<void**>(&ds.h_status_dev), ds.h_status, 0);
         }
     }
     if (e == hipSuccess) e = hipMemsetAsync(st, 0, sizeof(tns::IngestStatus), stream);
     if (e == hipSuccess) e = tns::ingest_status_reset(st, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-        if (st) (void)hipFree(st);
-        return fail_hip(e, "initialising the device store");
-    }
+    if (e != hipSuccess) return fail_hip(e, "initialising the device store");
     plan->d_nodes.used = total_nodes;
     ds.aux.used = total_nodes;
     ds.d_status = st;
@@ -1219,20 +1282,22 @@ int tns_destroy(tns_plan* plan) {
     g_err.clear();
     if (!plan) {
         device_pool().give_back(std::chrono::steady_clock::time_point::max(), -1);
+        record_pool().give_back();
         return TNS_OK;
     }
     if (plan->d_nodes.ptr || plan->d_dir.ptr || plan->d_edges.ptr || plan->d_lines.ptr) {
         DeviceGuard guard(plan->cfg.device);
-        plan->d_lines.release();
-        plan->d_nodes.release();
-        plan->d_dir.release();
-        plan->d_dir_cum.release();
-        plan->d_edges.release();
+        const bool idle = hipDeviceSynchronize() == hipSuccess;      // one wait for all of it
+        plan->d_lines.release(idle);
+        plan->d_nodes.release(idle);
+        plan->d_dir.release(idle);
+        plan->d_dir_cum.release(idle);
+        plan->d_edges.release(idle);
         if (plan->dev) {
-            plan->dev->aux.release();
-            plan->dev->ws.release();
-            if (plan->dev->d_status) (void)hipFree(plan->dev->d_status);
-            if (plan->dev->h_status) (void)hipHostFree(plan->dev->h_status);
+            plan->dev->aux.release(idle);
+            plan->dev->ws.release(idle);
+            plan->dev->status.release(idle);
+            if (plan->dev->h_status) idle ? record_pool().release(plan->dev->record) : (void)hipHostFree(plan->dev->h_status);
         }
     }
     delete plan;
