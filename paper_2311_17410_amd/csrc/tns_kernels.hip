@@ -601,9 +601,7 @@ hipError_t launch_sample_t(const SampleArgs& a, hipStream_t stream) {
     // tile finish far apart (searches and picks) and wait for each other before the dense copy, so small tiles win (C5:
     // 36.5 ms with 16 waves, 32.6 with 8, 31.3 with 4, 34.1 with 2).
     int waves = (int)std::min<size_t>(4, std::max<size_t>(1, (62u << 10) / chunk));
-    // small batches: smaller workgroups, so that the queries spread over the compute units instead of
-    // queueing at the address units of a few
-    while (waves > 1 && (a.Q + (int64_t)waves * kWave - 1) / ((int64_t)waves * kWave) < 512) waves >>= 1;
+    waves = workgroup_waves(a.Q, a.fanout, waves, FUSED);
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;

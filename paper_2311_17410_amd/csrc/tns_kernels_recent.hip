@@ -469,9 +469,7 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
         for (int n = four - 1; n >= 1; --n)
             if (resident(n) * 4 >= resident(four) * 5 && resident(n) > resident(waves)) waves = n;
     }
-    // small batches: smaller workgroups, so that the queries spread over the compute units instead of queueing at the
-    // address units of a few
-    while (waves > 1 && (a.Q + (int64_t)waves * kWave - 1) / ((int64_t)waves * kWave) < 512) waves >>= 1;
+    waves = workgroup_waves(a.Q, a.fanout, waves, FUSED);
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
