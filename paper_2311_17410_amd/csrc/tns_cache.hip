@@ -14,6 +14,7 @@
 #include "../../include/tns_cache.h"
 #include "tns_chain.h"
 #include "tns_internal.h"
+#include "tns_lanes.h"
 #include "tns_test_hooks.h"
 
 using tns::DeviceGuard;
@@ -253,23 +254,6 @@ __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, 
 // (2) exclusive scan of the tile sums by one workgroup, (3) per tile: the flags again, a local scan,
 // and the functor's emit() with the number of flagged elements before each one.  No flag array.
 
-__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t u = __shfl_up(v, d, kWave);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
-__device__ __forceinline__ int64_t wave_inclusive_scan64(int64_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t u = (int64_t)__shfl_up((long long)v, d, kWave);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
-
 constexpr int kPerThread = kScanTile / 256;
 
 template <class F>
@@ -281,7 +265,7 @@ __global__ void __launch_bounds__(256) k_flag_tile_sums(const F f, int64_t n, in
     for (int i = 0; i < kPerThread; ++i)
         if (base + i < n) v += f.count(base + i);
     const int lane = threadIdx.x & 63;
-    v = wave_inclusive_scan64(v, lane);
+    v = tns::wave_inclusive_scan64(v);
     if (lane == 63) s_w[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
@@ -298,7 +282,7 @@ __global__ void __launch_bounds__(1024) k_flag_scan_sums(const F f, int64_t* __r
     for (int64_t base = 0; base < num_tiles; base += 1024) {
         const int64_t i = base + threadIdx.x;
         const int64_t v = i < num_tiles ? sums[i] : 0;
-        const int64_t inc = wave_inclusive_scan64(v, lane);
+        const int64_t inc = tns::wave_inclusive_scan64(v);
         if (lane == 63) s_w[wave] = inc;
         __syncthreads();
         int64_t wave_off = 0, all = 0;
@@ -339,7 +323,7 @@ __device__ __forceinline__ void flag_collect_body(const F& f, int64_t n, const i
             }
             part += v[0] + v[1] + v[2] + v[3];
         }
-        part = wave_inclusive_scan64(part, lane);
+        part = tns::wave_inclusive_scan64(part);
         if (lane == 63) s_t[wave] = part;
     }
     int64_t c[kPerThread], sum = 0;
@@ -348,7 +332,7 @@ __device__ __forceinline__ void flag_collect_body(const F& f, int64_t n, const i
         c[i] = base + i < n ? f.count(base + i) : 0;
         sum += c[i];
     }
-    const int64_t inc = wave_inclusive_scan64(sum, lane);
+    const int64_t inc = tns::wave_inclusive_scan64(sum);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
     if (FOLD) tile_off = s_t[0] + s_t[1] + s_t[2] + s_t[3];
@@ -417,7 +401,7 @@ __device__ __forceinline__ SelState select_pick(Ctl* ctl, int pass /* 1..kPasses
     }
 #pragma unroll
     for (int i = 0; i < kBinsPerThread; ++i) mine += h[i];
-    int32_t inc = wave_inclusive_scan(mine, lane);
+    int32_t inc = tns::wave_inclusive_scan(mine);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();
     for (int w = 0; w < wave; ++w) inc += s_w[w];
@@ -527,7 +511,7 @@ __global__ void __launch_bounds__(256) k_victims_tile_sums(const Victims f, Ctl*
             if (base + i < n) v += f.count_with(base + i, st.prefix);
     }
     const int lane = threadIdx.x & 63;
-    v = wave_inclusive_scan64(v, lane);
+    v = tns::wave_inclusive_scan64(v);
     if (lane == 63) s_w[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) sums[blockIdx.x] = s_w[0] + s_w[1] + s_w[2] + s_w[3];
@@ -634,7 +618,7 @@ __device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, t
         if (lane == 0 && tile > 0)
             __hip_atomic_store(&chain->status[tile], tns::kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int64_t excl = 0;
-        if (tile > 0 && !(wait && tns::lookback(chain, tile, lane, excl))) excl = -1;
+        if (tile > 0 && !(wait && tns::lookback(chain, tile, lane, excl, [](int64_t v) { return tns::wave_sum64(v); }))) excl = -1;
         if (lane == 0) {
             s_excl = excl;
             if (excl >= 0) publish(excl);

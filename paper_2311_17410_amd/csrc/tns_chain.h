@@ -37,8 +37,9 @@ __device__ __forceinline__ int64_t shfl64(int64_t v, int src) {
 }
 
 // Sum of the totals of all tiles before `tile` (called by one whole wave).  False if a tile had not reported after
-// kSpinLimit polls: `excl` is then too small.
-__device__ __forceinline__ bool lookback(ScanWorkspace* ws, int64_t tile, int lane, int64_t& excl) {
+// kSpinLimit polls: `excl` is then too small.  sum_of(v): the sum over the wave.
+template <class Sum>
+__device__ __forceinline__ bool lookback(ScanWorkspace* ws, int64_t tile, int lane, int64_t& excl, const Sum& sum_of) {
     excl = 0;
     int64_t idx = tile - 1;
     int spins = 0;
@@ -62,9 +63,7 @@ __device__ __forceinline__ bool lookback(ScanWorkspace* ws, int64_t tile, int la
             __builtin_amdgcn_s_sleep(16);      // ~0.4 us between polls: late tiles are late by microseconds
             continue;
         }
-        int64_t v = (lane <= first) ? (int64_t)(st & ~kStMask) : 0;
-        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kChainWave);
-        excl += v;
+        excl += sum_of((lane <= first) ? (int64_t)(st & ~kStMask) : 0);
         if (first < kChainWave) return true;
         idx -= kChainWave;
         fresh = true;
@@ -73,9 +72,10 @@ __device__ __forceinline__ bool lookback(ScanWorkspace* ws, int64_t tile, int la
 
 // The same for a scan that cannot do without the tiles before this one: a wait that runs out is reported in *err_flag,
 // before this tile publishes anything, so that whoever builds on its (wrong) prefix can see the flag.
-__device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_t* err_flag, int64_t tile, int lane) {
+template <class Sum>
+__device__ __forceinline__ int64_t lookback_exclusive(ScanWorkspace* ws, uint32_t* err_flag, int64_t tile, int lane, const Sum& sum_of) {
     int64_t excl;
-    if (!lookback(ws, tile, lane, excl)) {
+    if (!lookback(ws, tile, lane, excl, sum_of)) {
         if (lane == 0) atomicExch(err_flag, 1u);
         __threadfence();
     }

@@ -490,7 +490,7 @@ struct TileChain {
     // one wave: the dense entries of the tiles before this one; -1 (kTags): the tile writes no dense rows
     __device__ __forceinline__ int64_t look_back(const SampleArgs& p, int32_t total, int lane) const {
         if (kTagged) return tags.exclusive(tile, lane, p.defer_spins, [](int32_t v) { return wave_sum(v); });
-        const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane) : 0;
+        const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane, [](int64_t v) { return wave_sum64(v); }) : 0;
         if (lane == 0)
             __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return excl;

@@ -620,7 +620,9 @@ __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const Pl
 constexpr int kFastTileMax = 4096;
 inline int fast_tile_keys(int64_t m) { return m <= (int64_t(1) << 17) ? 1024 : (m <= (int64_t(1) << 18) ? 2048 : kFastTileMax); }
 constexpr int kScatThreads = 512;                       // the radix passes: 8 waves x 8 keys per lane on the same tiles
+constexpr int kScatRows = 13;                            // rows of the table that a thread has in flight
 constexpr int kScatGroups = 4;                          // parts of the table of tile histograms that are added up side by side
+__host__ __device__ constexpr int scatter_groups(int bins) { return kScatThreads / (bins / 4) < 1 ? 1 : (kScatThreads / (bins / 4) < kScatGroups ? kScatThreads / (bins / 4) : kScatGroups); }
 constexpr int kFastMaxTiles = 512;
 constexpr int64_t kFastMaxBatch = (int64_t)kFastTileMax * kFastMaxTiles;   // 2^21 edges
 constexpr int kFastMaxBits = 12;                        // bits per digit: two digits cover 2^24 nodes
@@ -658,7 +660,7 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* s_wa
 __device__ __forceinline__ int64_t chain_wave(ScanWorkspace* ws, IngestStatus* st, int64_t tile, int64_t total, int lane) {
     if (lane == 0 && tile > 0)
         __hip_atomic_store(&ws->status[tile], kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int64_t excl = tile > 0 ? lookback_exclusive(ws, &ws->error, tile, lane) : 0;
+    const int64_t excl = tile > 0 ? lookback_exclusive(ws, &ws->error, tile, lane, [](int64_t v) { return wave_sum64(v); }) : 0;
     if (lane == 0) {
         __hip_atomic_store(&ws->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__hip_atomic_load(&ws->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(&st->internal, kInternalScan);
@@ -771,7 +773,10 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
     const int bins = 1 << bits;
     uint32_t* s_off = smem;                     // [bins]  position of the tile's first key of each digit
     uint32_t* s_cnt = smem + bins;              // [waves][bins]
-    __shared__ int64_t s_wave[kScatThreads / kWave];
+    // [2][groups][bins]  parts of the table's sums; with the most bins in the waves' rows, for which there is no more LDS
+    const bool apart = bins < 1 << kFastMaxBits;
+    uint32_t* s_part = apart ? s_cnt + (size_t)(kScatThreads / kWave) * bins : s_cnt;
+    __shared__ int32_t s_wave[16];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
     const int tile = blockIdx.x;
     const uint32_t mask = (uint32_t)(bins - 1);
@@ -788,20 +793,26 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
         v_[j] = vin[i];
     }
     // keys with this digit in earlier tiles, and in all tiles.  A thread adds up four digits (16-byte loads) of every
-    // group-th tile, eight rows in flight: the rows come from the L2, and with all 49 rows of a batch of 100 K to itself a
-    // thread spent seven round trips here (16.5 us a pass, 11.2 in the second, which counts nothing for a next one).
-    const int quads = bins / 4, groups = min(kScatGroups, max(1, kScatThreads / quads));
-    uint32_t* const part_before = s_cnt;                       // [groups][bins] each, in the waves' rows for now
-    uint32_t* const part_all = s_cnt + (size_t)groups * bins;
+    // group-th tile, thirteen rows in flight: the rows come from the L2, and with all 98 rows of a batch of 100 K to itself a
+    // thread would spend eight round trips here.  The counts' rows are cleared meanwhile.  (A pass of 10^5 edges, mean of both:
+    // 11.8 -> 10.7 us with these, of which the table 3, its sums 1, ranks 1.3, and the keys' places 4 in the first pass, whose counts for
+    // the second are atomics, and 1.4 in the second.)
+    const int quads = bins / 4, groups = scatter_groups(bins);
+    uint32_t* const part_before = s_part;                      // [groups][bins] each
+    uint32_t* const part_all = s_part + (size_t)groups * bins;
+    auto clear_counts = [&]() {
+        for (int i = t; i < bins * (kScatThreads / kWave) / 4; i += kScatThreads) reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0, 0, 0, 0);
+    };
+    if (apart) clear_counts();
     for (int x = t; x < quads * groups; x += kScatThreads) {
         const int q = x % quads, grp = x / quads;
         uint4 before = make_uint4(0, 0, 0, 0), all = make_uint4(0, 0, 0, 0);
-        for (int r0 = grp; r0 < tiles; r0 += 8 * groups) {
-            uint4 c[8];
+        for (int r0 = grp; r0 < tiles; r0 += kScatRows * groups) {
+            uint4 c[kScatRows];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) c[u] = *reinterpret_cast<const uint4*>(hist + (size_t)min(r0 + u * groups, tiles - 1) * bins + 4 * q);
+            for (int u = 0; u < kScatRows; ++u) c[u] = *reinterpret_cast<const uint4*>(hist + (size_t)min(r0 + u * groups, tiles - 1) * bins + 4 * q);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < kScatRows; ++u) {
                 const int r = r0 + u * groups;
                 if (r < tiles) { all.x += c[u].x; all.y += c[u].y; all.z += c[u].z; all.w += c[u].w; }
                 if (r < tile) { before.x += c[u].x; before.y += c[u].y; before.z += c[u].z; before.w += c[u].w; }
@@ -813,7 +824,7 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
     __syncthreads();
     // thread t owns `per` consecutive digits
     const int per = bins >= kScatThreads ? bins / kScatThreads : 1;
-    int64_t mine = 0;
+    int32_t mine = 0;
     for (int i = 0; i < per; ++i) {
         const int b = t * per + i;
         if (b >= bins) break;
@@ -824,21 +835,24 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
         }
         s_off[b] = before;
         part_all[b] = all;             // the first group's: this thread's alone from here on
-        mine += all;
+        mine += (int32_t)all;
     }
-    int64_t total;
-    int64_t run = block_exclusive_scan<kScatThreads / kWave>(mine, s_wave, total);       // keys with a smaller digit than this thread's first
+    const int32_t inc = wave_inclusive_scan(mine);
+    if (lane == kWave - 1) s_wave[wave] = inc;
+    __syncthreads();
+    uint32_t run = (uint32_t)(sum_of_waves(s_wave, wave, lane) + inc - mine);       // keys with a smaller digit than this thread's first
     for (int k = 0; k < per; ++k) {
         const int b = t * per + k;
         if (b >= bins) break;
         const uint32_t all = part_all[b];
-        s_off[b] += (uint32_t)run;
+        s_off[b] += run;
         run += all;
     }
-    __syncthreads();
-    for (int i = t; i < bins * (kScatThreads / kWave); i += kScatThreads) s_cnt[i] = 0;
-    __syncthreads();
-
+    if (!apart) {
+        __syncthreads();
+        clear_counts();
+        __syncthreads();
+    }
     uint32_t* my_cnt = s_cnt + (size_t)wave * bins;
 #pragma unroll
     for (int j = 0; j < kScatItems; ++j) {
@@ -1466,7 +1480,7 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
         return hipGetLastError();
     }
     const int bins = 1 << bits;
-    const size_t lds = (size_t)bins * 4 * (1 + kScatThreads / kWave);
+    const size_t lds = (size_t)bins * 4 * (1 + kScatThreads / kWave + (bins < 1 << kFastMaxBits ? 2 * scatter_groups(bins) : 0));
 #define TNS_FAST_SORT(TILE)                                                                                                          \
     do {                                                                                                                             \
         hipLaunchKernelGGL((k_fast_keys<TILE>), dim3((unsigned)c.fast_tiles), dim3(kThreads), (size_t)bins * 4, stream, a, c.keyA,  \
