@@ -179,6 +179,11 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
 // consecutive rows 281 -> 272, any of 2^24 rows 380 -> 370: of what a copy reaches, the rest is rows that begin and end inside
 // lines and lie anywhere.
 constexpr int kGatherUnroll = 8;
+// In the launch with the update a thread moves half as many pieces of 16 bytes: its workgroups have 1024 threads, and with eight pieces
+// 66600 rows of 172 floats are 350 workgroups, of which a third of the compute units got two and took twice as long (gather done at
+// 22 us, half of it at 10).  us per fetch with 8 / 4 / 3 / 2: 66600 rows 33.5 / 31.4 / 31.5 / 32.8, 200000 71.2 / 67.1 / 67.2 / 71.5, 16000 as
+// before; pieces of 4 bytes, 66600 rows of 173 floats, 38.0 / 41.6 / 45.9 / 54.1.
+__host__ __device__ constexpr int update_unroll(int vec) { return vec == 4 ? 4 : kGatherUnroll; }
 
 // Row of piece t where a row has `per_row` of them, for t < 2^31: floor(t / per_row) = t * mul >> shift, with mul =
 // ceil(2^shift / per_row) and 2^(shift - 31) >= per_row, so that the product's error stays below 1 / per_row.
@@ -194,39 +199,39 @@ RowOf row_of(int32_t per_row) {
 }
 constexpr int64_t kGatherPieces = int64_t(1) << 31;       // of one launch
 
-template <int VEC, int THREADS>
+template <int VEC, int THREADS, int UNROLL>
 __device__ __forceinline__ void gather_body(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                             uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
                                             const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid, uint32_t nb) {
     const uint32_t stride = nb * THREADS;
     const uint32_t t0 = bid * THREADS + threadIdx.x;
-    uint32_t col[kGatherUnroll];
-    int32_t id[kGatherUnroll], s[kGatherUnroll];
+    uint32_t col[UNROLL];
+    int32_t id[UNROLL], s[UNROLL];
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const uint32_t t = min(t0 + (uint32_t)u * stride, total - 1);      // clamped: no load sits in a branch
         const uint32_t b = row(t);
         col[u] = (t - b * row.per_row) * VEC;
         id[u] = ids[b];
     }
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const bool in_range = id[u] >= 0 && id[u] < num_ids;
         s[u] = slot_of[in_range ? id[u] : 0];
         if (!in_range) s[u] = -2;                                         // -1: not cached, -2: id out of range
     }
     // the output is touched once (non-temporal); the cached rows are what should stay in the L2
     typedef float vec_t __attribute__((ext_vector_type(VEC)));
-    vec_t v[kGatherUnroll];
+    vec_t v[UNROLL];
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const float* const from = s[u] >= 0 ? rows : store;
         const uint32_t r = s[u] >= 0 ? (uint32_t)s[u] : (s[u] == -1 ? (uint32_t)id[u] : 0u);
         v[u] = *reinterpret_cast<const vec_t*>(from + ((uint64_t)r * (uint32_t)dim + col[u]));
     }
     // Every row piece has arrived before the first store is issued (what a copy reaches in the two orders: tns_probe.hip).
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         float x = v[u][0];
         asm volatile("" : "+v"(x));         // (the compiler would otherwise move the first load into the branch of its store)
         v[u][0] = x;
@@ -235,7 +240,7 @@ __device__ __forceinline__ void gather_body(const float* __restrict__ rows, cons
     __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0) only
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < kGatherUnroll; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
         const uint32_t t = t0 + (uint32_t)u * stride;
         if (s[u] == -2) v[u] = vec_t(0.f);
         if (t < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out) + t);
@@ -246,7 +251,7 @@ template <int VEC>
 __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                                 uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
                                                 const int32_t* __restrict__ slot_of, float* __restrict__ out) {
-    gather_body<VEC, 256>(rows, store, dim, total, row, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
+    gather_body<VEC, 256, kGatherUnroll>(rows, store, dim, total, row, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
 }
 
 // ---- compaction of flagged elements in three launches -------------------------------------------
@@ -760,7 +765,7 @@ __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const 
                                                       uint32_t pieces, const RowOf row, int64_t num_ids, float* __restrict__ out) {
     __shared__ uint32_t s_ticket;
     if ((int64_t)blockIdx.x >= tiles) {
-        gather_body<GATHER, kOneGroup>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out, blockIdx.x - (uint32_t)tiles,
+        gather_body<GATHER, kOneGroup, update_unroll(GATHER)>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out, blockIdx.x - (uint32_t)tiles,
                                        gridDim.x - (uint32_t)tiles);
         return;
     }
@@ -1008,7 +1013,8 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
     hipLaunchKernelGGL(k_lookup, dim3((unsigned)tiles_b), dim3(256), 0, us, st, policy, N, B, d_ids, w.slots, d_hit, w.ctl,
                        one_launch ? w.chain : nullptr, cache->first_ticket);
     if (one_launch) {
-        const int64_t gather_blocks = blocks_for((pieces + kGatherUnroll - 1) / kGatherUnroll, kOneGroup);
+        const int unroll = update_unroll(vec4 ? 4 : 1);
+        const int64_t gather_blocks = blocks_for((pieces + unroll - 1) / unroll, kOneGroup);
         auto update = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_b + gather_blocks)), dim3(kOneGroup), 0, us, st, nf, B, tiles_b, w.chain, w.victims,
                                store, dim, (uint32_t)pieces, row, N, d_out);
