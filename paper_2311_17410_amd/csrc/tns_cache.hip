@@ -171,9 +171,9 @@ __global__ void __launch_bounds__(256) k_lookup(const CacheState c, int policy, 
 }
 
 // out[b] = cached row or row of the backing store; VEC floats per thread, rows stay coalesced
-// The slot comes from the id map directly (the threads of a row read the same two words), so the gather does not
+// The slot comes from the id map directly, so the gather does not
 // wait for the lookup kernel, which records the accesses for the update beside it.  A thread moves kGatherUnroll
-// pieces, one grid width apart: the kernel is a copy, and a copy on this machine is bound by how much each compute unit has
+// pieces, one workgroup's width apart: the kernel is a copy, and a copy on this machine is bound by how much each compute unit has
 // in flight.  The row of a piece is found by a multiplication; with 64-bit divisions eight pieces took 849 vector
 // instructions and 90 registers (five waves per SIMD), now 233 and 61 (eight).  2^20 rows of 172 floats: Zipf ids 353 -> 342 us,
 // consecutive rows 281 -> 272, any of 2^24 rows 380 -> 370: of what a copy reaches, the rest is rows that begin and end inside
@@ -199,27 +199,11 @@ RowOf row_of(int32_t per_row) {
 }
 constexpr int64_t kGatherPieces = int64_t(1) << 31;       // of one launch
 
+// The pieces of a thread, THREADS apart from t0 on: from cached row s[u], from the store's row id[u] (s[u] = -1), or zeros (s[u] = -2).
 template <int VEC, int THREADS, int UNROLL>
-__device__ __forceinline__ void gather_body(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
-                                            uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
-                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid, uint32_t nb) {
-    const uint32_t stride = nb * THREADS;
-    const uint32_t t0 = bid * THREADS + threadIdx.x;
-    uint32_t col[UNROLL];
-    int32_t id[UNROLL], s[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const uint32_t t = min(t0 + (uint32_t)u * stride, total - 1);      // clamped: no load sits in a branch
-        const uint32_t b = row(t);
-        col[u] = (t - b * row.per_row) * VEC;
-        id[u] = ids[b];
-    }
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const bool in_range = id[u] >= 0 && id[u] < num_ids;
-        s[u] = slot_of[in_range ? id[u] : 0];
-        if (!in_range) s[u] = -2;                                         // -1: not cached, -2: id out of range
-    }
+__device__ __forceinline__ void move_pieces(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim, uint32_t total,
+                                            uint32_t t0, const uint32_t (&col)[UNROLL], const int32_t (&id)[UNROLL], const int32_t (&s)[UNROLL],
+                                            float* __restrict__ out) {
     // the output is touched once (non-temporal); the cached rows are what should stay in the L2
     typedef float vec_t __attribute__((ext_vector_type(VEC)));
     vec_t v[UNROLL];
@@ -241,17 +225,85 @@ __device__ __forceinline__ void gather_body(const float* __restrict__ rows, cons
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-        const uint32_t t = t0 + (uint32_t)u * stride;
+        const uint32_t t = t0 + (uint32_t)u * THREADS;
         if (s[u] == -2) v[u] = vec_t(0.f);
         if (t < total) __builtin_nontemporal_store(v[u], reinterpret_cast<vec_t*>(out) + t);
     }
+}
+
+// slots of ids: -1: not cached, -2: id out of range
+template <int N>
+__device__ __forceinline__ void look_up(const int32_t (&id)[N], int32_t (&s)[N], int64_t num_ids, const int32_t* __restrict__ slot_of, int n = N) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        if (u >= n) break;
+        const bool in_range = id[u] >= 0 && id[u] < num_ids;
+        s[u] = slot_of[in_range ? id[u] : 0];
+        if (!in_range) s[u] = -2;
+    }
+}
+
+// A workgroup's pieces are consecutive, so that a row is read and written by one compute unit, or two.  In k_gather its rows are
+// looked up once each and handed over in LDS.  us per fetch with pieces a grid width apart / consecutive / consecutive and
+// handed over: 2^20 rows of 172 floats, LFU 371 / 369 / 363, of 128 224 / 218 / 217, of 32 149 / 145 / 146, of 173 (pieces of 4 bytes) 324 /
+// 309 / 295.  In k_update, whose workgroups are four times as large, handing over costs more than it gives: 66600 rows of 172 27.6 /
+// 27.9 / 28.2, of 173 29.8 / 29.9 / 31.6, 300000 of 172 95.4 / 94.3 / 96.8.
+template <int VEC, int THREADS, int UNROLL>
+__device__ __forceinline__ void gather_each(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
+                                            uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
+                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid) {
+    const uint32_t t0 = bid * (THREADS * UNROLL) + threadIdx.x;
+    uint32_t col[UNROLL];
+    int32_t id[UNROLL], s[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t t = min(t0 + (uint32_t)u * THREADS, total - 1);      // clamped: no load sits in a branch
+        const uint32_t b = row(t);
+        col[u] = (t - b * row.per_row) * VEC;
+        id[u] = ids[b];
+    }
+    look_up(id, s, num_ids, slot_of);
+    move_pieces<VEC, THREADS, UNROLL>(rows, store, dim, total, t0, col, id, s, out);
+}
+template <int VEC, int THREADS, int UNROLL>
+__device__ __forceinline__ void gather_rows(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
+                                            uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
+                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid) {
+    constexpr uint32_t kPieces = THREADS * UNROLL;
+    __shared__ int32_t s_from[kPieces];         // the slot of a row, -1 - id if it is not cached, INT_MIN if the id is out of range
+    const uint32_t first = bid * kPieces, t0 = first + threadIdx.x;
+    const uint32_t r0 = row(first), n = row(min(first + kPieces, total) - 1) - r0 + 1;     // rows of the workgroup, at most kPieces
+    const int rounds = (int)((n + THREADS - 1) / THREADS);
+    uint32_t col[UNROLL];
+    int32_t id[UNROLL], s[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        if (u >= rounds) break;                                 // uniform
+        id[u] = ids[r0 + min((uint32_t)u * THREADS + threadIdx.x, n - 1)];
+    }
+    look_up(id, s, num_ids, slot_of, rounds);
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t i = (uint32_t)u * THREADS + threadIdx.x;
+        if (i < n) s_from[i] = s[u] >= 0 ? s[u] : (s[u] == -1 ? -1 - id[u] : INT_MIN);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t t = min(t0 + (uint32_t)u * THREADS, total - 1), b = row(t);
+        col[u] = (t - b * row.per_row) * VEC;
+        const int32_t from = s_from[b - r0];
+        id[u] = -1 - from;
+        s[u] = from >= 0 ? from : (from == INT_MIN ? -2 : -1);
+    }
+    move_pieces<VEC, THREADS, UNROLL>(rows, store, dim, total, t0, col, id, s, out);
 }
 
 template <int VEC>
 __global__ void __launch_bounds__(256) k_gather(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                                 uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
                                                 const int32_t* __restrict__ slot_of, float* __restrict__ out) {
-    gather_body<VEC, 256, kGatherUnroll>(rows, store, dim, total, row, num_ids, ids, slot_of, out, blockIdx.x, gridDim.x);
+    gather_rows<VEC, 256, kGatherUnroll>(rows, store, dim, total, row, num_ids, ids, slot_of, out, blockIdx.x);
 }
 
 // ---- compaction of flagged elements in three launches -------------------------------------------
@@ -765,8 +817,8 @@ __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const 
                                                       uint32_t pieces, const RowOf row, int64_t num_ids, float* __restrict__ out) {
     __shared__ uint32_t s_ticket;
     if ((int64_t)blockIdx.x >= tiles) {
-        gather_body<GATHER, kOneGroup, update_unroll(GATHER)>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out, blockIdx.x - (uint32_t)tiles,
-                                       gridDim.x - (uint32_t)tiles);
+        gather_each<GATHER, kOneGroup, update_unroll(GATHER)>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out,
+                                                              blockIdx.x - (uint32_t)tiles);
         return;
     }
     // tiles are numbered in the order workgroups start, so that a tile only waits for tiles that have started

@@ -229,3 +229,17 @@ def test_rows_gathered_beside_lookup_and_update(KB, rows):
     # 43 pieces a row: 2^20 pieces end inside row 24385
     rng = np.random.default_rng(rows)
     run_sequence(KB, CO.LRU, 60_000, 2000, 172, 0.2, [rng.zipf(1.1, rows) % 60_000 for _ in range(3)], 8)[0].close()
+
+
+@pytest.mark.parametrize("dim,b", [(1, 1), (1, 2047), (1, 2048), (1, 2049), (3, 683), (4, 2049), (8, 1025), (12, 100_001), (172, 48), (172, 5000),
+                                   (2049, 3)])
+def test_rows_of_a_workgroup_looked_up_once(KB, dim, b):
+    # more than 65536 entries: the rows are moved by a launch of their own, 2048 pieces a workgroup, so that there are rows that fill,
+    # span and share workgroups, and as many rows as pieces
+    rng = np.random.default_rng(b)
+    n, cap = 70_000 if dim <= 172 else 65_600, 65_537
+    batches = [rng.integers(0, n, b) for _ in range(3)]
+    batches[1][rng.integers(0, b, 1 + b // 9)] = rng.choice([-1, n, 2 ** 31 - 1], 1 + b // 9)
+    batches[2] = batches[0]
+    gpu, *_ = run_sequence(KB, CO.LRU, n, cap, dim, 0.2, batches, 4, check_state_every=3)
+    gpu.close()
