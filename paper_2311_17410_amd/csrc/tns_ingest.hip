@@ -135,6 +135,13 @@ hipError_t exclusive_scan64(const int64_t* in, int64_t* out, int64_t n, int64_t*
 
 // Key = (source id, order-preserving image of the timestamp); the value is the batch position.
 // -0.0 and +0.0 compare equal, so both take the key of +0.0 and keep their arrival order.
+__device__ __forceinline__ uint64_t key_of(int32_t v, float t) {
+    uint32_t u = t == 0.0f ? 0u : __float_as_uint(t);
+    u ^= (u >> 31) ? 0xffffffffu : 0x80000000u;
+    return ((uint64_t)(uint32_t)v << 32) | u;
+}
+constexpr uint32_t kZeroTime = 0x80000000u;              // low word of a key: a time of either sign
+__device__ __forceinline__ float time_of_key(uint32_t u) { return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xffffffffu)); }
 __global__ void __launch_bounds__(kThreads) k_keys(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= a.m) return;
@@ -144,9 +151,7 @@ __global__ void __launch_bounds__(kThreads) k_keys(const IngestArgs a, uint64_t*
     else if (t != t) report(a.status, TNS_EORDER, i);
     else if (a.eid && a.eid[i] < 0) report(a.status, TNS_EINVAL, i);
     if (i > 0 && a.ts[i - 1] > t) atomicOr(&a.status->unsorted, 1u);
-    uint32_t u = t == 0.0f ? 0u : __float_as_uint(t);
-    u ^= (u >> 31) ? 0xffffffffu : 0x80000000u;
-    key[i] = ((uint64_t)(uint32_t)v << 32) | u;
+    key[i] = key_of(v, t);
     val[i] = (uint32_t)i;
 }
 
@@ -387,7 +392,7 @@ __device__ __forceinline__ void add_block_totals(IngestStatus* st, int64_t block
 }
 
 __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uint64_t* __restrict__ key, const uint32_t* __restrict__ val,
-                                                   const int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
+                                                   const int32_t* __restrict__ seg_start, uint32_t* __restrict__ seg_src, SegPlan* __restrict__ plan,
                                                    int64_t* __restrict__ need_lines, int64_t* __restrict__ need_dir) {
     const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     int64_t blocks = 0, slots = 0;
@@ -400,6 +405,7 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
             load_segment_node(a, (uint32_t)(key[p0] >> 32), val[p0], n);
             plan_segment(a, (uint32_t)(key[p0] >> 32), n, seg_start[s + 1] - p0, P, lines, dirs, blocks, slots,
                          [&]() { report(a.status, TNS_EORDER, a.m + (int64_t)(key[p0] >> 32)); });
+            seg_src[s] = (uint32_t)(key[p0] >> 32);
             plan[s] = P;
         }
         need_lines[s] = lines;
@@ -410,41 +416,58 @@ __global__ void __launch_bounds__(kThreads) k_plan(const IngestArgs a, const uin
 
 // Loads of these values are requested together: the compiler would otherwise request one, wait for it, and use its register for the next.
 __device__ __forceinline__ void side_by_side(int32_t& a, int32_t& b, int32_t& c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
-__device__ __forceinline__ void side_by_side(uint32_t& a, uint32_t& b, uint32_t& c, int64_t& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+
+struct SegTimes { float tail, first, last; };      // of the last edge for the tail block; of the first new block's first and last
 
 // A planned batch as the apply phase reads it, left in memory by the planning kernels.
 struct PlannedBatch {
+    static constexpr bool kAhead = true;
     const uint64_t* __restrict__ key;         // sorted: source in the high word
     const uint32_t* __restrict__ val;         // batch position
     const int64_t* __restrict__ head_excl;    // segment heads before a position
     const int32_t* __restrict__ seg_start;
+    const uint32_t* __restrict__ seg_src;     // source of a segment
     const SegPlan* __restrict__ plan;
     const int64_t* __restrict__ lines_base;
     const int64_t* __restrict__ dir_base;
     __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(key[p] >> 32); }
     __device__ __forceinline__ uint32_t position(int64_t p) const { return val[p]; }
-    __device__ __forceinline__ float time(const IngestArgs& a, int64_t p) const { return a.ts[val[p]]; }
-    __device__ __forceinline__ void positions(int32_t (&p)[3]) const {
+    // a time lies in its key, but for the sign of a zero
+    __device__ __forceinline__ float time_in(const IngestArgs& a, uint32_t u, int64_t p) const { return u == kZeroTime ? a.ts[val[p]] : time_of_key(u); }
+    __device__ __forceinline__ float time(const IngestArgs& a, int64_t p) const { return time_in(a, (uint32_t)key[p], p); }
+    __device__ __forceinline__ SegTimes times(const IngestArgs& a, const int32_t (&p)[3]) const {
+        int32_t u[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) p[i] = (int32_t)val[p[i]];
-        side_by_side(p[0], p[1], p[2]);
+        for (int i = 0; i < 3; ++i) u[i] = (int32_t)(uint32_t)key[p[i]];
+        side_by_side(u[0], u[1], u[2]);
+        return SegTimes{time_in(a, (uint32_t)u[0], p[0]), time_in(a, (uint32_t)u[1], p[1]), time_in(a, (uint32_t)u[2], p[2])};
     }
-    __device__ __forceinline__ float time_at(const IngestArgs& a, int32_t position) const { return a.ts[position]; }
 };
 
 // One thread per segment: tail record, new block records, node entry, builder state.  n: the node as it was when the segment was planned.
 // Everything is read before the first store: a load behind stores is only waited for together with them.
-struct SegTimes { float tail, first, last; };      // of the last edge for the tail block; of the first new block's first and last
 template <class Batch>
 __device__ __forceinline__ SegTimes segment_times(const IngestArgs& a, const Batch& b, const SegPlan& P, int32_t p0, int32_t p1) {
     const int32_t fresh = min(p0 + P.take, p1 - 1);
-    int32_t at[3] = {p0 + max(P.take, 1) - 1, fresh, P.cap < p1 - fresh ? max(fresh + P.cap - 1, p0) : p1 - 1};
-    b.positions(at);
-    return SegTimes{b.time_at(a, at[0]), b.time_at(a, at[1]), b.time_at(a, at[2])};
+    const int32_t at[3] = {p0 + max(P.take, 1) - 1, fresh, P.cap < p1 - fresh ? max(fresh + P.cap - 1, p0) : p1 - 1};
+    return b.times(a, at);
 }
+// The records of a node's inline list behind its newest, read with the entry (Batch::kAhead): moving them one by one is a round trip
+// each, and so is copying a directory run.  k_apply in batches of 3 * 10^5 edges over 2^20 nodes, us a batch with the sampling 197.6 ->
+// 192; not in k_small_batch, whose program would get longer than the round trips cost (2000 edges 33.7 -> 36).
+typedef uint32_t rec_words __attribute__((ext_vector_type(4)));
+struct OlderRecs { rec_words r[kInlineBlocks - 1]; };
+__device__ __forceinline__ OlderRecs load_older(const NodeLine* N) {
+    OlderRecs o;
+#pragma unroll
+    for (int j = 0; j < kInlineBlocks - 1; ++j) o.r[j] = *(reinterpret_cast<const rec_words*>(N) + 2 + j);
+    return o;
+}
+static_assert(sizeof(NodeLine) == 16 + kInlineBlocks * 16, "a header and the inline records, 16 bytes each");
+constexpr int kCopyAhead = 8;          // directory records in flight per thread
 template <class Batch>
 __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, int64_t s, const SegPlan& P, int32_t p0, int32_t p1, int64_t nidx,
-                                           const SegNode& n, const SegTimes& times) {
+                                           const SegNode& n, const OlderRecs& older, const SegTimes& times) {
     const int64_t mm = p1 - p0;
     NodeLine* N = &a.nodes[nidx];
     const int32_t nb = (int32_t)n.h.x;
@@ -474,17 +497,46 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, 
                 if (start + room > a.cap_dir) { atomicOr(&a.status->internal, 2u); return; }
                 BlockRec* dst = a.dir + start;
                 uint32_t* dcum = a.dir_cum + start;
-                if (nb <= kInlineBlocks) {
-                    uint32_t before = 0;
-                    for (int j = nb - 1; j >= 0; --j) {                                  // oldest first
+                const BlockRec* old = a.dir + (int64_t)dir_line * kDirAlign;
+                const uint32_t* ocum = a.dir_cum + (int64_t)dir_line * kDirAlign;
+                uint32_t before = 0;
+                if (nb <= kInlineBlocks && Batch::kAhead) {
+#pragma unroll
+                    for (int j = kInlineBlocks - 1; j >= 0; --j) {                       // oldest first
+                        const rec_words newest = {__float_as_uint(tail.t_min), __float_as_uint(tail.t_max), tail.off_lo, tail.size_hi};
+                        const rec_words o = j > 0 ? older.r[j > 0 ? j - 1 : 0] : newest;
+                        if (j < nb) {
+                            *reinterpret_cast<rec_words*>(&dst[nb - 1 - j]) = o;
+                            dcum[nb - 1 - j] = before;
+                            before += o.w & 0xffffffu;       // rec_size()
+                        }
+                    }
+                } else if (nb <= kInlineBlocks) {
+                    for (int j = nb - 1; j >= 0; --j) {
                         const BlockRec o = j > 0 ? N->rec[j] : tail;
                         dst[nb - 1 - j] = o;
                         dcum[nb - 1 - j] = before;
                         before += (uint32_t)rec_size(o);
                     }
+                } else if (Batch::kAhead) {
+#pragma unroll 1
+                    for (int32_t j0 = 0; j0 < nb; j0 += kCopyAhead) {
+                        rec_words o[kCopyAhead];
+                        uint32_t c[kCopyAhead];
+#pragma unroll
+                        for (int u = 0; u < kCopyAhead; ++u) {
+                            o[u] = *reinterpret_cast<const rec_words*>(&old[min(j0 + u, nb - 1)]);
+                            c[u] = ocum[min(j0 + u, nb - 1)];
+                        }
+#pragma unroll
+                        for (int u = 0; u < kCopyAhead; ++u) {
+                            if (j0 + u < nb) {
+                                *reinterpret_cast<rec_words*>(&dst[j0 + u]) = o[u];
+                                dcum[j0 + u] = c[u];
+                            }
+                        }
+                    }
                 } else {
-                    const BlockRec* old = a.dir + (int64_t)dir_line * kDirAlign;
-                    const uint32_t* ocum = a.dir_cum + (int64_t)dir_line * kDirAlign;
                     for (int32_t j = 0; j < nb; ++j) {
                         dst[j] = old[j];
                         dcum[j] = ocum[j];
@@ -495,7 +547,14 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, 
             }
             run = a.dir + (int64_t)dir_line * kDirAlign;
         } else {
-            for (int j = nb - 1; j > 0; --j) N->rec[j + P.nbn] = N->rec[j];              // newest first: room in front
+            // newest first: room in front
+            if (Batch::kAhead) {
+#pragma unroll
+                for (int j = 1; j < kInlineBlocks; ++j)
+                    if (j < nb) *reinterpret_cast<rec_words*>(&N->rec[j + P.nbn]) = older.r[j - 1];
+            } else {
+                for (int j = nb - 1; j > 0; --j) N->rec[j + P.nbn] = N->rec[j];
+            }
             if (nb > 0) N->rec[P.nbn] = tail;
         }
         uint32_t* run_cum = run ? a.dir_cum + (int64_t)dir_line * kDirAlign : nullptr;
@@ -567,31 +626,38 @@ __device__ __forceinline__ void apply_edge(const IngestArgs& a, const SegPlan& P
 
 // Both in one launch: an edge's slot follows from the plan alone, so the two parts do not depend on each other.
 // (100 K edges: 14.4 us against 7.8 + 10.2 and the gap between the two launches.)
+// What bounds it is the chain of dependent reads: the plan's word to go ahead, the segment, its node and times.  The first two are
+// requested together, a segment's source has an array of its own, and a time is read from its key; likewise in k_fast_plan, and
+// the keys are made by the first sorting pass, not written for it.  us a batch with the sampling of its events: 10^4 edges over 2^16 nodes
+// 45.5 -> 43.3, 10^5 over 2^18 71.5 -> 69.9, over 2^20 power-law ids 120 -> 115, 3 * 10^5 over 2^20 201 -> 198.
 __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const PlannedBatch b, int64_t num_segments, unsigned node_blocks,
                                                     const int64_t* __restrict__ go) {
-    if (go) num_segments = *go;          // queued before the host has seen the plan
-    if (num_segments <= 0) return;
+    // (clamped and requested beside the number of segments, which a launch queued before the host has seen the plan reads)
+    int64_t limit = go ? *go : num_segments;
     // the node part first: it is the longer chain of dependent reads
     if (blockIdx.x < node_blocks) {
-        const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-        if (s < num_segments) {
-            const SegPlan P = b.plan[s];
-            const int32_t p0 = b.seg_start[s], p1 = b.seg_start[s + 1];
-            const int64_t nidx = a.node_base + b.source(p0);
+        const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x, at = min(s, a.m - 1);
+        SegPlan P = b.plan[at];
+        int32_t p0 = b.seg_start[at], p1 = b.seg_start[at + 1];
+        uint32_t source = b.seg_src[at];
+        asm volatile("" : "+v"(limit), "+v"(P.tail_slot), "+v"(P.take), "+v"(p0), "+v"(p1), "+v"(source));
+        if (s < limit) {
+            const int64_t nidx = a.node_base + source;
             SegNode n;
             n.h = *reinterpret_cast<const uint4*>(&a.nodes[nidx]);
             n.r0 = *(reinterpret_cast<const uint4*>(&a.nodes[nidx]) + 1);
             n.ax = a.aux[nidx];
-            apply_node(a, b, s, P, p0, p1, nidx, n, segment_times(a, b, P, p0, p1));
+            apply_node(a, b, s, P, p0, p1, nidx, n, load_older(&a.nodes[nidx]), segment_times(a, b, P, p0, p1));
         }
     } else {
-        const int64_t p = (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x;
+        const int64_t p = (int64_t)(blockIdx.x - node_blocks) * kThreads + threadIdx.x, at = min(p, a.m - 1);
+        uint32_t e = b.position(at), own = b.source(at), before = b.source(at > 0 ? at - 1 : 0);
+        int64_t seg = b.head_excl[at];
+        asm volatile("" : "+v"(limit), "+v"(e), "+v"(own), "+v"(before), "+v"(seg));
+        if (limit <= 0) return;
         // (the host has read the record or has a copy of it: the next plan needs no launch of its own for it)
         if (p == 0) ready_status(a.status);
         if (p < a.m) {
-            uint32_t e = b.position(p), own = b.source(p), before = b.source(p > 0 ? p - 1 : 0);
-            int64_t seg = b.head_excl[p];
-            side_by_side(e, own, before, seg);
             if (p > 0 && own == before) --seg;
             const SegPlan P = b.plan[seg];
             const int64_t r = p - b.seg_start[seg], lines_base = b.lines_base[seg];
@@ -605,7 +671,7 @@ __global__ void __launch_bounds__(kThreads) k_apply(const IngestArgs a, const Pl
 // A batch of the size streams are ingested in (the paper's 100 K edges) spends its time in launches,
 // not in memory traffic, so the planning phase above (about 40 dependent launches) is cut to four
 // for batches that fit kFastMaxBatch and arrive in time order, the usual case for a stream:
-//   k_fast_keys      validation, keys, and every tile's histogram of the first digit;
+//   k_fast_keys      validation, and every tile's histogram of the first digit;
 //   k_fast_scatter   x 2: stable radix pass over one half of the source id's bits.  Every tile adds
 //                    up the histograms of the tiles before it by itself (at most kFastMaxTiles rows, read
 //                    from the L2), so a pass needs no separate scan launch and no tile waits for another;
@@ -704,9 +770,8 @@ constexpr int kPlanScans = 4;
 struct PlanScans { ScanWorkspace* ws[kPlanScans]; };      // of k_fast_plan
 
 template <int TILE>
-__global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint64_t* __restrict__ key, uint32_t* __restrict__ val,
-                                                        uint32_t* __restrict__ hist1, uint32_t* __restrict__ hist2, int bits,
-                                                        const PlanScans scans, int plan_tiles) {
+__global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint32_t* __restrict__ hist1,
+                                                        uint32_t* __restrict__ hist2, int bits, const PlanScans scans, int plan_tiles) {
     extern __shared__ uint32_t s_hist[];     // [bins]
     const int bins = 1 << bits;
     for (int b = threadIdx.x; b < bins; b += kThreads) s_hist[b] = 0;
@@ -733,10 +798,6 @@ __global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint
         else if (t != t) report(a.status, TNS_EORDER, i);
         else if (e_[j] < 0) report(a.status, TNS_EINVAL, i);
         if (i > 0 && tp_[j] > t) atomicOr(&a.status->unsorted, 1u);
-        uint32_t u = t == 0.0f ? 0u : __float_as_uint(t);
-        u ^= (u >> 31) ? 0xffffffffu : 0x80000000u;
-        key[i] = ((uint64_t)(uint32_t)v << 32) | u;
-        val[i] = (uint32_t)i;
         atomicAdd(&s_hist[(uint32_t)v & (uint32_t)(bins - 1)], 1u);
     }
     __syncthreads();
@@ -764,8 +825,9 @@ __global__ void __launch_bounds__(kThreads) k_fast_keys(const IngestArgs a, uint
 // consecutive keys of the tile and takes them 64 at a time in order, so "earlier in the tile" is
 // (wave, item, lane) order; a key's rank among equal digits is the count of its wave so far plus its rank
 // among the lanes of the current item (ballots over the digit's bits).
-template <int TILE>
-__global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+// The first pass makes its keys from the batch.
+template <int TILE, bool FIRST>
+__global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const IngestArgs a, const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
                                                            uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, int64_t m,
                                                            int shift, int bits, int tiles, const uint32_t* __restrict__ hist,
                                                            uint32_t* __restrict__ hist_next, int shift_next) {
@@ -789,8 +851,13 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
 #pragma unroll
     for (int j = 0; j < kScatItems; ++j) {
         const int64_t i = min(wbase + (int64_t)j * kWave + lane, m - 1);   // clamped: no load sits in a branch
-        k_[j] = kin[i];
-        v_[j] = vin[i];
+        if (FIRST) {
+            k_[j] = ((uint64_t)(uint32_t)a.src[i] << 32) | __float_as_uint(a.ts[i]);
+            v_[j] = (uint32_t)i;
+        } else {
+            k_[j] = kin[i];
+            v_[j] = vin[i];
+        }
     }
     // keys with this digit in earlier tiles, and in all tiles.  A thread adds up four digits (16-byte loads) of every
     // group-th tile, thirteen rows in flight: the rows come from the L2, and with all 98 rows of a batch of 100 K to itself a
@@ -893,9 +960,9 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
         const uint32_t d = (uint32_t)(k_[j] >> shift) & mask;
         const uint32_t pos = s_off[d] + my_cnt[d] + r_[j];
         if ((int64_t)pos < m) {                 // always true for consistent histograms; keeps a bad one in bounds
-            kout[pos] = k_[j];
+            kout[pos] = FIRST ? key_of((int32_t)(k_[j] >> 32), __uint_as_float((uint32_t)k_[j])) : k_[j];
             vout[pos] = v_[j];
-            if (hist_next) atomicAdd(&hist_next[(size_t)(pos / TILE) * bins + ((uint32_t)(k_[j] >> shift_next) & mask)], 1u);
+            if (FIRST) atomicAdd(&hist_next[(size_t)(pos / TILE) * bins + ((uint32_t)(k_[j] >> shift_next) & mask)], 1u);
         }
     }
 }
@@ -911,8 +978,8 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const uint64_t* _
 // the table of tile histograms read four rows side by side (k_fast_scatter); with the nodes requested before the segments' lengths
 // are known and the apply kernel's edges requested beside their segments, 2860 -> 2570 together with the sampling's smaller launches.
 __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, const uint64_t* __restrict__ key,
-                                                            const uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
-                                                            int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
+                                                            int64_t* __restrict__ head_excl, int32_t* __restrict__ seg_start,
+                                                            uint32_t* __restrict__ seg_src, SegPlan* __restrict__ plan,
                                                             int64_t* __restrict__ lines_base, int64_t* __restrict__ dir_base,
                                                             const PlanScans scans, int plan_tiles) {
     constexpr int kWaves = kPlanThreads / kWave;
@@ -928,7 +995,10 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     const uint64_t k = p < a.m ? key[p] : 0, before = p > 0 && p < a.m ? key[p - 1] : 0;
     const bool head = p < a.m && (p == 0 || (uint32_t)(k >> 32) != (uint32_t)(before >> 32));
     SegNode node{};
-    if (head) load_segment_node(a, (uint32_t)(k >> 32), val[p], node);
+    if (head) {
+        load_node(a, (uint32_t)(k >> 32), node);
+        node.t_first = time_of_key((uint32_t)k);       // (only compared: a zero's sign does not matter)
+    }
     if (wave == kWaves - 1) {
         // where the tile's last segment ends: beyond the tile by at most a batch, found 64 positions at a time
         int64_t lo = min(p0 + kPlanThreads, a.m), n = a.m - lo;
@@ -992,6 +1062,7 @@ __global__ void __launch_bounds__(kPlanThreads) k_fast_plan(const IngestArgs a, 
     // (after a chained scan's time-out the sums are short and nothing is applied: the stores stay within the batch)
     if (head && seg < a.m) {
         seg_start[seg] = (int32_t)p;
+        seg_src[seg] = (uint32_t)(k >> 32);
         plan[seg] = P;
         lines_base[seg] = v[1] + s_excl[1];
         dir_base[seg] = v[2] + s_excl[2];
@@ -1045,6 +1116,7 @@ struct SmallShared {
 };
 static_assert(sizeof(SmallShared) <= 160 << 10, "one workgroup's LDS");
 struct SmallBatch {                      // as PlannedBatch, in LDS
+    static constexpr bool kAhead = false;
     const SmallShared& sh;
     const SegPlan* plan;
     const int32_t* seg_start;
@@ -1054,18 +1126,17 @@ struct SmallBatch {                      // as PlannedBatch, in LDS
     __device__ __forceinline__ uint32_t source(int64_t p) const { return (uint32_t)(sh.key[p] >> 32); }
     __device__ __forceinline__ uint32_t position(int64_t p) const { return (uint32_t)sh.key[p]; }
     __device__ __forceinline__ float time(const IngestArgs&, int64_t p) const { return sh.ts[position(p)]; }
-    __device__ __forceinline__ void positions(int32_t (&p)[3]) const {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) p[i] = (int32_t)position(p[i]);
+    __device__ __forceinline__ SegTimes times(const IngestArgs& a, const int32_t (&p)[3]) const {
+        return SegTimes{time(a, p[0]), time(a, p[1]), time(a, p[2])};
     }
-    __device__ __forceinline__ float time_at(const IngestArgs&, int32_t position) const { return sh.ts[position]; }
 };
 
 // digit: bits a pass
 __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs a, int bits, int digit, uint64_t* __restrict__ key,
                                                                uint32_t* __restrict__ val, int64_t* __restrict__ head_excl,
-                                                               int32_t* __restrict__ seg_start, SegPlan* __restrict__ plan,
-                                                               int64_t* __restrict__ lines_base, int64_t* __restrict__ dir_base) {
+                                                               int32_t* __restrict__ seg_start, uint32_t* __restrict__ seg_src,
+                                                               SegPlan* __restrict__ plan, int64_t* __restrict__ lines_base,
+                                                               int64_t* __restrict__ dir_base) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     SmallShared& sh = *reinterpret_cast<SmallShared*>(s_raw);
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, m = (int)a.m;
@@ -1279,7 +1350,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
             const SegNode n = s == t ? node[0] : node[1];
             const SegPlan P = sh.plan[s];
             const int32_t p0 = sh.seg_start[s], p1 = sh.seg_start[s + 1];
-            apply_node(a, batch, s, P, p0, p1, a.node_base + batch.source(p0), n, segment_times(a, batch, P, p0, p1));
+            const int64_t nidx = a.node_base + batch.source(p0);
+            apply_node(a, batch, s, P, p0, p1, nidx, n, OlderRecs{}, segment_times(a, batch, P, p0, p1));
         }
 #pragma unroll 1
         for (int p = t; p < m; p += kSmallThreads) {
@@ -1291,7 +1363,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
         // an error, a batch out of order, pools without room: the host decides, and a later launch finds the plan in memory
 #pragma unroll 1
         for (int p = t; p < m; p += kSmallThreads) {
-            key[p] = sh.key[p];
+            key[p] = key_of((int32_t)batch.source(p), batch.time(a, p));
             val[p] = batch.position(p);
             head_excl[p] = sh.seg_of[p] + ((p == sh.seg_start[sh.seg_of[p]]) ? 0 : 1);
         }
@@ -1299,6 +1371,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_batch(const IngestArgs 
         for (int s = t; s < nseg; s += kSmallThreads) {
             plan[s] = sh.plan[s];
             seg_start[s] = sh.seg_start[s];
+            seg_src[s] = batch.source(sh.seg_start[s]);
             lines_base[s] = sh.lines_base[s];
             dir_base[s] = sh.dir_base[s];
             if (s == nseg - 1) seg_start[nseg] = m;
@@ -1364,6 +1437,7 @@ struct Carve {
     uint32_t *valA, *valB, *hist;
     int64_t *head_excl, *lines_base, *dir_base, *sums;
     int32_t* seg_start;
+    uint32_t* seg_src;
     SegPlan* plan;
     int64_t chunk;
     int nblk;
@@ -1393,6 +1467,7 @@ Carve carve(void* ws, int64_t m) {
     c.dir_base = reinterpret_cast<int64_t*>(take(mm * 8));
     c.sums = reinterpret_cast<int64_t*>(take(((mm + kScanTile - 1) / kScanTile + 1) * 8));
     c.seg_start = reinterpret_cast<int32_t*>(take((mm + 1) * 4));
+    c.seg_src = reinterpret_cast<uint32_t*>(take(mm * 4));
     c.plan = reinterpret_cast<SegPlan*>(take(mm * sizeof(SegPlan)));
     if (m <= kFastMaxBatch) {
         c.fast_tiles = (int)((mm + fast_tile_keys(m) - 1) / fast_tile_keys(m));
@@ -1449,7 +1524,7 @@ hipError_t ingest_plan(const IngestArgs& a, hipStream_t stream) {
     hipError_t e = exclusive_scan64(c.head_excl, c.head_excl, m, c.sums, &a.status->num_segments, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_seg_start, dim3(grid_for(m)), dim3(kThreads), 0, stream, kin, m, c.head_excl, c.seg_start);
-    hipLaunchKernelGGL(k_plan, dim3(grid_for(m)), dim3(kThreads), 0, stream, a, kin, vin, c.seg_start, c.plan, c.lines_base,
+    hipLaunchKernelGGL(k_plan, dim3(grid_for(m)), dim3(kThreads), 0, stream, a, kin, vin, c.seg_start, c.seg_src, c.plan, c.lines_base,
                        c.dir_base);
     e = exclusive_scan64(c.lines_base, c.lines_base, m, c.sums, &a.status->total_lines, stream);
     if (e != hipSuccess) return e;
@@ -1476,19 +1551,19 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
     if (a.m <= kSmallBatch) {
         const int passes = (2 * bits + kSmallDigitMost - 1) / kSmallDigitMost, digit = std::max(kSmallDigitLeast, (2 * bits + passes - 1) / passes);
         hipLaunchKernelGGL(k_small_batch, dim3(1), dim3(kSmallThreads), sizeof(SmallShared), stream, a, 2 * bits, digit, c.keyA, c.valA, c.head_excl,
-                           c.seg_start, c.plan, c.lines_base, c.dir_base);
+                           c.seg_start, c.seg_src, c.plan, c.lines_base, c.dir_base);
         return hipGetLastError();
     }
     const int bins = 1 << bits;
     const size_t lds = (size_t)bins * 4 * (1 + kScatThreads / kWave + (bins < 1 << kFastMaxBits ? 2 * scatter_groups(bins) : 0));
 #define TNS_FAST_SORT(TILE)                                                                                                          \
     do {                                                                                                                             \
-        hipLaunchKernelGGL((k_fast_keys<TILE>), dim3((unsigned)c.fast_tiles), dim3(kThreads), (size_t)bins * 4, stream, a, c.keyA,  \
-                           c.valA, c.tile_hist[0], c.tile_hist[1], bits, c.scans, c.plan_tiles);                                     \
-        hipLaunchKernelGGL((k_fast_scatter<TILE>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, c.keyA, c.valA,    \
-                           c.keyB, c.valB, a.m, 32, bits, c.fast_tiles, c.tile_hist[0], c.tile_hist[1], 32 + bits);                  \
-        hipLaunchKernelGGL((k_fast_scatter<TILE>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, c.keyB, c.valB,    \
-                           c.keyA, c.valA, a.m, 32 + bits, bits, c.fast_tiles, c.tile_hist[1], (uint32_t*)nullptr, 0);               \
+        hipLaunchKernelGGL((k_fast_keys<TILE>), dim3((unsigned)c.fast_tiles), dim3(kThreads), (size_t)bins * 4, stream, a,          \
+                           c.tile_hist[0], c.tile_hist[1], bits, c.scans, c.plan_tiles);                                             \
+        hipLaunchKernelGGL((k_fast_scatter<TILE, true>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, a,           \
+                           (const uint64_t*)nullptr, (const uint32_t*)nullptr, c.keyB, c.valB, a.m, 32, bits, c.fast_tiles, c.tile_hist[0], c.tile_hist[1], 32 + bits);                  \
+        hipLaunchKernelGGL((k_fast_scatter<TILE, false>), dim3((unsigned)c.fast_tiles), dim3(kScatThreads), lds, stream, a, c.keyB,   \
+                           c.valB, c.keyA, c.valA, a.m, 32 + bits, bits, c.fast_tiles, c.tile_hist[1], (uint32_t*)nullptr, 0);               \
     } while (0)
     switch (fast_tile_keys(a.m)) {
         case 1024: TNS_FAST_SORT(1024); break;
@@ -1496,8 +1571,8 @@ hipError_t ingest_plan_fast(const IngestArgs& args, hipStream_t stream) {
         default: TNS_FAST_SORT(kFastTileMax); break;
     }
 #undef TNS_FAST_SORT
-    hipLaunchKernelGGL(k_fast_plan, dim3((unsigned)c.plan_tiles), dim3(kPlanThreads), 0, stream, a, c.keyA, c.valA, c.head_excl, c.seg_start,
-                       c.plan, c.lines_base, c.dir_base, c.scans, c.plan_tiles);
+    hipLaunchKernelGGL(k_fast_plan, dim3((unsigned)c.plan_tiles), dim3(kPlanThreads), 0, stream, a, c.keyA, c.head_excl, c.seg_start,
+                       c.seg_src, c.plan, c.lines_base, c.dir_base, c.scans, c.plan_tiles);
     return hipGetLastError();
 }
 
@@ -1509,7 +1584,7 @@ hipError_t ingest_apply(const IngestArgs& a, int64_t num_segments, bool fast, hi
     const uint32_t* val = in_b ? c.valB : c.valA;
     if (num_segments <= 0 && a.m <= kSmallBatch) return hipSuccess;          // k_small_batch has applied the batch, or may not
     const unsigned node_blocks = grid_for(num_segments > 0 ? num_segments : a.m);
-    const PlannedBatch b{key, val, c.head_excl, c.seg_start, c.plan, c.lines_base, c.dir_base};
+    const PlannedBatch b{key, val, c.head_excl, c.seg_start, c.seg_src, c.plan, c.lines_base, c.dir_base};
     hipLaunchKernelGGL(k_apply, dim3(node_blocks + grid_for(a.m)), dim3(kThreads), 0, stream, a, b, num_segments, node_blocks,
                        num_segments > 0 ? nullptr : c.sums);
     return hipGetLastError();

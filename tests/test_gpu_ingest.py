@@ -74,6 +74,30 @@ def test_block_structure_matches_structural_oracle(B, oracle_lib, sizing, tau, b
     plan.close()
 
 
+@pytest.mark.parametrize("sizing,batch,batches", [(0, 2049, 44), (1, 2100, 3), (2, 4097, 40)])
+def test_lists_that_move_and_zeros_of_either_sign(B, oracle_lib, sizing, batch, batches):
+    # batches of the pipeline of several kernels, few nodes: lists go from the entry to the directory and from run to run (16, 32, 64
+    # records, copied eight at a time), and a block's times keep the sign of a zero
+    g = np.random.Generator(np.random.PCG64(batch))
+    n, nodes = batch * batches, 37
+    src, dst = g.integers(0, nodes, n).astype(np.int32), g.integers(0, nodes, n).astype(np.int32)
+    ts = np.repeat(np.arange(batches) // 4 - 2, batch).astype(np.float32)       # whole batches of equal times
+    zero = ts == 0
+    ts[zero] = np.where(g.integers(0, 2, zero.sum()) == 1, np.float32(0.0), np.float32(-0.0))
+    plan = B.Plan(nodes, 10, block_threshold=48, sizing=sizing, flags=B.TNS_FLAG_DEVICE_INGEST)
+    for lo in range(0, n, batch):
+        plan.add_edges_device(*(to_dev(a[lo:lo + batch], t) for a, t in ((src, np.int32), (dst, np.int32), (ts, np.float32))))
+    bs = oracle_lib.BlockStore(nodes, 48, sizing)
+    bs.add_stream(src, dst, ts, batch)
+    ref = bs.blocks()
+    for v in range(nodes):
+        got, mine = plan.node_blocks(v), ref["node"] == v
+        assert np.array_equal(got["cap"], ref["cap"][mine]) and np.array_equal(got["size"], ref["size"][mine]), v
+        for name in ("t_min", "t_max"):
+            assert np.array_equal(np.float32(got[name]).view(np.int32), np.float32(ref[name][mine]).view(np.int32)), (v, name)
+    plan.close()
+
+
 @pytest.mark.parametrize("policy", [0, 1])
 def test_ties_and_unsorted_batches(B, oracle_lib, policy):
     # many equal timestamps; inside every batch the arrival order is shuffled, so the device has to
