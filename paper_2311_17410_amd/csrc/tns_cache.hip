@@ -599,12 +599,18 @@ __global__ void __launch_bounds__(256) k_newids_collect_hist0(const NewIds f, in
 // instruction per SIMD every four cycles, so 44 scores per thread make the instructions per score what counts: the victims are
 // stored in 2.5 us where the equal ones are all taken or all left, by one comparison; with both compared for
 // every score and counted in a pass of their own they took 9.  Time stamps, batch of 66600 of which 8388 are replaced: new ids
-// known at 8 us, threshold at 15, victims stored at 18.
+// known at 8 us, threshold at 15, victims stored at 18; since then the lowest score is found, and under LRU the eight lowest
+// values are counted (kNear), before the tile waits for the others.
 // 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO, one cache again and again: 66600 ids 71 / 74 / 61 -> 34 / 36 / 32, 16000 ids 67 / 67 / 60
 // -> 22 / 19 / 16, 600 ids 69 / 67 / 60 -> 16 / 15 / 13.  Three caches in turn, so that their rows come from memory: 66600 ids
 // 83 / 84 / 65 -> 41 / 44 / 40.
 constexpr int kOneGroup = 1024, kOneGroupWaves = kOneGroup / kWave;
 constexpr int kItems = 64, kItemStep = 8;                         // scores per thread, and per uniform branch
+// LRU: values from the lowest on that are counted at once while new ids are awaited, if these come from enough tiles for the wait to be
+// long.  us per fetch without / with: 52 K entries, 34000 ids of 100 floats 32.1 / 30.5, 50000 34.1 / 32.9; 42 K, 66600 of 172 32.7 / 31.2; 10 K, 150000
+// of 32 26.1 / 24.6.  In all batches: 52 K entries, 600 ids 15.0 / 17.5, 10000 16.1 / 19.8.  Under LFU, where the lowest value alone
+// often has enough entries, 34000 ids 25.6 / 28.4.
+constexpr int kNear = 8, kNearTiles = 32;
 // Where the line lies: a large gather saturates the memory, and the chain of dependent reads of the tiles beside it then
 // takes longer than the short launches do on a stream of their own.  Us per fetch, LRU / LFU / FIFO, this form and the
 // other: 262144 rows of 172 floats (11 M pieces of 16 bytes) 97 / 118 / 97 and 116 / 132 / 102, 524288 rows (23 M) 174 / 214 / 171 and
@@ -653,7 +659,10 @@ __device__ __forceinline__ int32_t count_below(const uint32_t (&key)[kItems], in
 // Returns their number up to and including this tile.  What a tile learns from the chained scan it could count by itself, and
 // does so if the tiles before it have not reported within the bound of its wait (or `wait` is false, in tests): every update
 // is made, however late a tile is.
-__device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile, bool wait) {
+// meanwhile(): what the workgroup does before it waits.
+template <class Meanwhile>
+__device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, tns::ScanWorkspace* chain, int64_t tile, bool wait,
+                                                   const Meanwhile& meanwhile) {
     __shared__ int32_t s_w[kOneGroupWaves];
     __shared__ int64_t s_excl;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -671,9 +680,10 @@ __device__ __forceinline__ int64_t new_ids_of_tile(const NewIds& f, int64_t B, t
     auto publish = [&](int64_t before_tile) {
         __hip_atomic_store(&chain->status[tile], tns::kStPrefix | (uint64_t)(before_tile + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    if (threadIdx.x == 0 && tile > 0)
+        __hip_atomic_store(&chain->status[tile], tns::kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    meanwhile();
     if (wave == 0) {
-        if (lane == 0 && tile > 0)
-            __hip_atomic_store(&chain->status[tile], tns::kStTotal | (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int64_t excl = 0;
         if (tile > 0 && !(wait && tns::lookback(chain, tile, lane, excl, [](int64_t v) { return tns::wave_sum64(v); }))) excl = -1;
         if (lane == 0) {
@@ -712,6 +722,7 @@ __device__ __forceinline__ void last_tile(const CacheState& c, const NewIds& f, 
                                           int32_t* __restrict__ victims, bool wait) {
     __shared__ int32_t s_cnt[2][kOneGroupWaves];
     __shared__ uint32_t s_min[kOneGroupWaves];
+    __shared__ int32_t s_near[kNear][kOneGroupWaves];
     __shared__ int32_t s_below[kOneGroupWaves], s_equal[kOneGroupWaves];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     // a wave holds `items` times 64 consecutive scores: the lanes of a ballot are in slot order
@@ -732,24 +743,64 @@ __device__ __forceinline__ void last_tile(const CacheState& c, const NewIds& f, 
 #pragma unroll
         for (int i = i0; i < i0 + kItemStep; ++i) key[i] = base + i * kWave < C ? score_key((int32_t)key[i], now) : ~0u;
     }
-    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait);
+    uint32_t lowest = ~0u;
+    const bool near = tile >= kNearTiles && now != 0;
+    int32_t near_all[kNear] = {}, near_own[kNear] = {};      // keys below lowest + 1 + j: all of them, this wave's
+    auto count_near = [&]() {
+#pragma unroll
+        for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+            if (i0 >= items) continue;
+#pragma unroll
+            for (int i = i0; i < i0 + kItemStep; ++i) lowest = min(lowest, key[i]);
+        }
+        for (int d = kWave / 2; d >= 1; d >>= 1) lowest = min(lowest, (uint32_t)__shfl_xor((int)lowest, d, kWave));
+        if (lane == 0) s_min[wave] = lowest;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kOneGroupWaves; ++w) lowest = min(lowest, s_min[w]);
+        lowest = (uint32_t)__builtin_amdgcn_readfirstlane((int)lowest);
+        if (!near) return;
+        // a byte per value and thread (at most kItems), then sixteen bits per wave
+        uint32_t low = 0, high = 0;
+#pragma unroll
+        for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
+            if (i0 >= items) continue;
+#pragma unroll
+            for (int i = i0; i < i0 + kItemStep; ++i) {
+                const uint32_t d = key[i] - lowest, one = 1u << ((8 * d) & 31u);
+                low += d < 4 ? one : 0u;
+                high += d - 4 < 4 ? one : 0u;
+            }
+        }
+        const uint32_t even = 0x00ff00ffu;
+        const uint32_t pair[4] = {(uint32_t)tns::wave_sum((int)(low & even)), (uint32_t)tns::wave_sum((int)((low >> 8) & even)),
+                                  (uint32_t)tns::wave_sum((int)(high & even)), (uint32_t)tns::wave_sum((int)((high >> 8) & even))};
+        int32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < kNear; ++j) {
+            n += (int32_t)((pair[j / 4 * 2 + (j & 1)] >> (j & 2 ? 16 : 0)) & 0xffffu);
+            near_own[j] = n;
+            if (lane == 0) s_near[j][wave] = n;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kNear; ++j) near_all[j] = tns::sum_of_waves(s_near[j], kOneGroupWaves, lane);
+    };
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait, count_near);
     const int32_t m = __builtin_amdgcn_readfirstlane(entries_to_replace(f, n_unique));
     if (m <= 0) return;
-    uint32_t lowest = ~0u;
-#pragma unroll
-    for (int i0 = 0; i0 < kItems; i0 += kItemStep) {
-        if (i0 >= items) continue;
-#pragma unroll
-        for (int i = i0; i < i0 + kItemStep; ++i) lowest = min(lowest, key[i]);
-    }
-    for (int d = kWave / 2; d >= 1; d >>= 1) lowest = min(lowest, (uint32_t)__shfl_xor((int)lowest, d, kWave));
-    if (lane == 0) s_min[wave] = lowest;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kOneGroupWaves; ++w) lowest = min(lowest, s_min[w]);
     // the m-th lowest key is in [lo, hi); below lo lie below_lo keys, of_lo of them this wave's, and of_hi of this wave's below hi
-    uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lowest), hi = 1ull << 32, step = 1;
+    uint64_t lo = lowest, hi = 1ull << 32, step = 1;
     int32_t below_lo = 0, of_lo = 0, of_hi = max(min(C - wave * items * kWave, items * kWave), 0);
+    if (near && lowest < ~0u - kNear) {      // (no place beyond the last entry was counted)
+#pragma unroll
+        for (int j = 0; j < kNear; ++j) {
+            if (hi != 1ull << 32) continue;
+            if (near_all[j] >= m) { hi = (uint64_t)lowest + 1 + j; of_hi = near_own[j]; }
+            else { lo = (uint64_t)lowest + 1 + j; below_lo = near_all[j]; of_lo = near_own[j]; }
+        }
+        step = 2 * kNear;
+    }
     int round = 0;
     while (hi - lo > 1) {
         const bool rising = hi == 1ull << 32 && lo + step < hi;      // (at most sixteen times, then never again)
@@ -830,7 +881,7 @@ __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const 
         last_tile(c, f, B, chain, tile, victims, wait);
         return;
     }
-    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait);
+    const int64_t n_unique = new_ids_of_tile(f, B, chain, tile, wait, []() {});
     if (!SELECT && tile == tiles - 1) {
         const int32_t m = entries_to_replace(f, n_unique);
         if (threadIdx.x == 0) fifo_advance(c.capacity, c.ring, f.ctl, m);

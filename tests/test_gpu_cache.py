@@ -197,6 +197,31 @@ def test_victims_among_scores_of_any_size(KB, policy, cap):
         gpu.close()
 
 
+@pytest.mark.parametrize("b", [32 * 1024, 32 * 1024 + 1])
+@pytest.mark.parametrize("cap,lo,hi", [(300, -3, 0), (8193, -8, 0), (40_001, -9, 0), (40_001, -2, 0), (65_536, -1, 0), (65_536, -40, 0),
+                                       (65_536, 2 ** 31 - 8, 2 ** 31 - 1), (57_345, 2 ** 31 - 20, 2 ** 31 - 9), (4097, -(2 ** 31), -(2 ** 31) + 9)])
+def test_values_counted_while_ids_are_awaited(KB, b, cap, lo, hi):
+    # from 33 tiles of ids on the eight lowest scores are counted beforehand: thresholds inside and beyond them, one value held by
+    # every entry, values so high that places beyond the last entry are next to them
+    import torch
+    dev = torch.device("cuda", 0)
+    rng = np.random.default_rng(cap)
+    n, dim = 200_000, 2
+    store = rng.standard_normal((n, dim)).astype(np.float32)
+    d_store = torch.from_numpy(store).to(dev)
+    for lam in (0.001, 0.2, 0.9, 1.0):
+        ref, gpu = CO.VectorCache(n, cap, dim, CO.LRU, lam), KB.Cache(n, cap, dim, CO.LRU, lam)
+        ref.score[:] = rng.integers(lo, hi, cap)
+        gpu.restore(dict(id_of=ref.id_of, score=ref.score, rows=ref.data, ring=0))
+        ids = rng.integers(0, n, b).astype(np.int32)
+        out, hit = gpu.fetch(torch.from_numpy(ids).to(dev), d_store)
+        r_out, r_hit = ref.fetch(ids, store)
+        assert np.array_equal(out.cpu().numpy(), r_out) and np.array_equal(hit.cpu().numpy().astype(bool), r_hit), lam
+        st = gpu.save()
+        assert np.array_equal(st["id_of"], ref.id_of) and np.array_equal(st["score"], ref.score), lam
+        gpu.close()
+
+
 @pytest.mark.parametrize("policy", [CO.LRU, CO.LFU, CO.FIFO])
 def test_tiles_that_do_not_hear_from_one_another(KB, policy):
     # the update of a batch numbers its missed ids with a chained scan over tiles of 1024 ids; no tile of this cache waits for
