@@ -39,7 +39,7 @@ int hipHostGetDevicePointer(void **d, void *h, unsigned flags) { (void)flags; *d
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *stream) { (void)kind; (void)stream; memcpy(d, s, n); return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return 0; }
 int hipMemsetAsync(void *d, int v, size_t n, void *stream) { (void)stream; memset(d, v, n); return 0; }
-int hipGetSymbolAddress(void **p, const void *symbol) { static uint8_t scratch[4 << 20]; (void)symbol; *p = scratch; return 0; }
+int hipGetSymbolAddress(void **p, const void *symbol) { static _Alignas(256) uint8_t scratch[4 << 20]; (void)symbol; *p = scratch; return 0; }
 int hipLaunchKernel(const void *f, uint64_t gxy, uint32_t gz, uint64_t bxy, uint32_t bz, void **args, size_t lds, void *stream) {
     (void)f; (void)gxy; (void)gz; (void)bxy; (void)bz; (void)args; (void)lds; (void)stream;
     ++launches;

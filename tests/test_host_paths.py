@@ -121,3 +121,37 @@ def launches(capture):
     return m - n, fake.fake_launches() - m
 assert launches(0) == (1, 2) and launches(1) == (2, 3) and launches(2) == (2, 3) and launches(0) == (1, 2)
 """)
+
+
+def test_device_addresses_are_integers(run):
+    # bytes, strings, arrays and pointer objects are no device addresses: a kernel would follow them into host memory
+    run("""
+p = B.Plan(1000, 10)
+B.tns_commit(p.handle)
+hop = dict.fromkeys([n for n, _ in B.tns_hop_buffers._fields_], 256)
+calls = [(B.tns_run, [p.handle, 100, 256, 0, 256, 0, 0, 256, 256, 256, 256, 256, 256, 256, 256, 256, 1 << 20, 0]),
+         (B.tns_run_static, [p.handle, 100, 256, 0, 256, 0, 0, 256, 256, 256, 256, 256, 256, 256, 256, 0]),
+         (B.tns_run_khop, [p.handle, [10], 1.0, 100, 256, 0, 256, 0, 0, [hop], 256, 1 << 20, 0]),
+         (B.tns_compact, [p.handle, 100, 256, 256, 256, 256, 256, 256, 256, 256, 256, 1 << 20, 0]),
+         (B.tns_traffic_model, [p.handle, 100, 256, 0, 256, 0, 0, 256, 0]),
+         (B.tns_hbm_probe, [0, False, 256, 512, 128, 0]), (B.tns_hbm_probe_mix, [False, 256, 128, 512, 128, 0])]
+for call, args in calls:
+    call(*args)
+    # addresses, and what may be one: not the numbers of hops and queries, the window length, nor the flag
+    first = next(i for i, a in enumerate(args) if type(a) is int and a >= 256)
+    for i in [i for i in range(first, len(args)) if type(args[i]) is int and args[i] in (256, 512)] + [len(args) - 1]:
+        for other in (b"12345678", "12345678", C.create_string_buffer(8), C.c_void_p(256), (C.c_int64 * 2)(1, 2), 1.5):
+            try:
+                call(*args[:i], other, *args[i + 1:])
+            except (TypeError, C.ArgumentError):
+                continue
+            raise SystemExit(f"{call.__name__} takes {other!r} as argument {i}")
+for name in hop:
+    for other in (b"12345678", "12345678", C.create_string_buffer(8)):
+        try:
+            B.tns_run_khop(p.handle, [10], 1.0, 100, 256, 0, 256, 0, 0, [{**hop, name: other}], 256, 1 << 20, 0)
+        except TypeError:
+            continue
+        raise SystemExit(f"{name} takes {other!r}")
+B.tns_run(p.handle, 100, 256, None, 256, None, 0, 256, 256, 256, 256, 256, 256, 256, 256, 256, 1 << 20, None)      # NULL either way
+""")
