@@ -700,25 +700,6 @@ constexpr int kPlanThreads = 512;                       // k_fast_plan: one sort
 constexpr int64_t kSmallBatch = 2048;
 constexpr uint32_t kInternalScan = 8u;                  // IngestStatus::internal: a chained scan's bounded wait ran out
 
-
-template <int WAVES = kThreads / kWave>
-__device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* s_wave /* [WAVES] */, int64_t& total) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int64_t inc = wave_inclusive_scan64(v);
-    if (lane == kWave - 1) s_wave[wave] = inc;
-    __syncthreads();
-    int64_t off = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        const int64_t t = s_wave[w];
-        if (w < wave) off += t;
-        total += t;
-    }
-    __syncthreads();
-    return off + inc - v;
-}
-
 // Tile index in launch order, and the sum of the totals of the tiles before it: one chained-scan step of a
 // workgroup.  `total` is the tile's own sum; the inclusive prefix is published for the tiles after it.
 // Called by one whole wave; lane 0 holds the result.  A bounded wait that runs out marks the scan's own error
