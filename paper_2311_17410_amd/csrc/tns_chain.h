@@ -139,12 +139,6 @@ struct TaggedChain {
     // Sum of the totals of all tiles before `tile` (called by one whole wave): four words per lane in flight.  -1: the tile has
     // waited for long enough, writes no dense rows, and is noted by next().  sum_of(v): the sum over the wave; such a call has less
     // than 2^31 dense entries.
-    __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins) const {
-        return exclusive(tile, lane, defer_spins, [](int32_t v) {
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kChainWave);
-            return v;
-        });
-    }
     template <class Sum>
     __device__ __forceinline__ int64_t exclusive(int64_t tile, int lane, int defer_spins, const Sum& sum_of) const {
         const uint32_t noted = __hip_atomic_load(&ws->noted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

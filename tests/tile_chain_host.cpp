@@ -42,7 +42,10 @@ static int try_once(uint32_t seed) {
             if (last) {
                 for (int w = 0; w < sim::kWaves; ++w) total += g.wave_sum[w];
                 if (lane == 0) chain.publish(tile, total);
-                const int64_t before = chain.exclusive(tile, lane, spins);
+                const int64_t before = chain.exclusive(tile, lane, spins, [](int32_t v) {
+                    for (int d = sim::kLanes / 2; d >= 1; d >>= 1) v += __shfl_xor(v, d, sim::kLanes);
+                    return v;
+                });
                 if (lane == 0) g.base = before;
             }
             __syncthreads();
