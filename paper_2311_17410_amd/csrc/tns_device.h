@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "../../include/tns.h"
 #include "tns_chain.h"
 #include "tns_kernels.h"
 #include "tns_lanes.h"
@@ -448,6 +449,13 @@ enum Scan : int {
     kTickets,     // tiles numbered in the order workgroups start: a tile only ever waits for tiles that have started
     kTags,        // small grids (TaggedChain)
 };
+// Dense entries of the largest call without tickets, whatever its fan-out.
+constexpr int64_t most_tagged_entries() {
+    int64_t most = 0;
+    for (int32_t f = 1; f <= TNS_MAX_FANOUT; ++f) most = std::max(most, tagged_queries(f) * f);
+    return most;
+}
+static_assert(most_tagged_entries() < int64_t(1) << 31, "TaggedChain::exclusive adds up in 32 bits");
 template <int SCAN>
 struct TileChain {
     static constexpr bool kTagged = SCAN == kTags;

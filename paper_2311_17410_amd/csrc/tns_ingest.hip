@@ -885,6 +885,7 @@ __global__ void __launch_bounds__(kScatThreads) k_fast_scatter(const IngestArgs 
         part_all[b] = all;             // the first group's: this thread's alone from here on
         mine += (int32_t)all;
     }
+    static_assert(kFastMaxBatch < int64_t(1) << 31, "numbers of keys are 32-bit");
     const int32_t inc = wave_inclusive_scan(mine);
     if (lane == kWave - 1) s_wave[wave] = inc;
     __syncthreads();

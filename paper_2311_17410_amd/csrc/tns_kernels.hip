@@ -668,6 +668,7 @@ hipError_t launch_sample(const SampleArgs& a, hipStream_t stream) {
     // 12.0 / 17.1, 16.8 / 17.9, 19.4 / 19.3; fan-out 20, 32768 11.5 / 17.0 and 15.9 / 21.9, 40000 19.4 / 17.9 and 27.9 / 22.9; fan-out 64,
     // 65536 26.6 / 32.7 and 43.3 / 41.7.  Uniform policy, fan-out 10, uniform ids 9.0 / 12.6, 9.9 / 13.2, 14.5 / 14.6, 15.2 / 15.7, power-law ids
     // 12.7 / 24.6, 13.7 / 26.0, 20.8 / 29.4, 24.2 / 32.4; fan-out 5, 32768 9.3 / 10.8 and 12.9 / 19.2, 65536 14.6 / 11.8 and 21.8 / 23.3.
+    static_assert(int64_t(1) << 16 <= tagged_queries(TNS_MAX_FANOUT), "its calls are calls without tickets");
     const int64_t team_max_queries = int64_t(1) << ((a.policy == 0 ? a.fanout <= 32 : a.fanout < 8) ? 15 : 16);
     if (a.scan_ws && !a.counters && a.Q <= team_max_queries) return launch_sample_team(a, stream);
     const bool incl = a.inclusive_end != 0;
