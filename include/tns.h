@@ -187,7 +187,7 @@ TNS_API int tns_delete_nodes(tns_plan *plan, int32_t instance, const int32_t *no
 TNS_API int tns_commit(tns_plan *plan, void *hip_stream);
 
 /* Bytes of DEVICE workspace for tns_run with Q queries when the padding removal of section 5 is requested
-   (scan state of that step; the first 256 bytes hold the step's status word, see tns_run_status).  Below 2^15 queries that is
+   (scan state of that step; the first 256 bytes hold the step's status word, see tns_run_status).  Below 2^14 queries that can be
    more than the step needs at the least, which is accepted too: one state of 8 bytes per 64 queries is; the rest is
    room for the states of smaller, faster workgroups. */
 TNS_API int tns_workspace(const tns_plan *plan, int64_t Q, size_t *bytes);

@@ -78,7 +78,7 @@ struct CompactArgs {
 };
 
 constexpr size_t kScanHeader = 256;         // of a scan workspace, before the tile states
-constexpr int64_t kSmallTile = 16, kMostSmallTiles = 512;      // queries of the smallest tiles; most such tiles of a call
+constexpr int64_t kSmallTile = 16, kMostSmallTiles = 256;      // queries of the smallest tiles; most tiles of a call that are made small
 constexpr int kCompactTile = 1024;  // queries per compaction tile
 
 // What a call with Q queries needs, and what it is asked to bring: room for the states of smaller tiles where the batch is small

@@ -626,6 +626,7 @@ size_t compact_workspace_least(int64_t Q) {
 }
 
 size_t compact_workspace_bytes(int64_t Q) {
+    // (also where this batch's tiles are larger: a smaller batch in the same workspace uses them all)
     const int64_t small_tiles = std::min<int64_t>((Q + kSmallTile - 1) / kSmallTile, kMostSmallTiles);
     return std::max(compact_workspace_least(Q), (kScanHeader + (size_t)(small_tiles + 1) * sizeof(uint64_t) + 255) & ~size_t(255));
 }

@@ -472,9 +472,9 @@ hipError_t launch_team_t(const SampleArgs& a, hipStream_t stream) {
     // waves, uniform ids and recent policy, the others alike: 600 queries 7.0 / 6.2 / 6.3, 1000 6.6 / 5.9 / 5.8, 4000 6.5 / 6.5 / 6.1, 8000
     // 6.7 / 6.2 / 6.7, 16000 7.1 / 7.4 / 7.1; 100 queries 5.7 / 5.6 / 6.2 and over power-law ids 6.7 / 6.5 / 7.3.
     auto tiles = [&](int waves) { return (a.Q + waves * kTeamsPerWave * CH - 1) / (waves * kTeamsPerWave * CH); };
-    static_assert(kFewWaves * kTeamsPerWave >= kSmallTile, "the workspace has room for the states of the smallest tiles");
+    static_assert(kFewWaves * kTeamsPerWave == kSmallTile && kMostSmallTiles == kComputeUnits, "the workspace has room for the states of the smallest tiles");
     int waves = a.Q <= kFewQueries ? 2 * kFewWaves : kFewWaves;
-    while (waves < kTileWaves && (tiles(waves) > std::min(kComputeUnits, kMostSmallTiles) || tiles(waves) >= a.scan_states)) waves *= 2;
+    while (waves < kTileWaves && (tiles(waves) > kComputeUnits || tiles(waves) >= a.scan_states)) waves *= 2;
     const int64_t grid = tiles(waves);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     if (grid <= 0) return a.scan_ready ? hipGetLastError() : launch_scan_init(a, 1, stream);

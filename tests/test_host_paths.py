@@ -155,3 +155,30 @@ for name in hop:
         raise SystemExit(f"{name} takes {other!r}")
 B.tns_run(p.handle, 100, 256, None, 256, None, 0, 256, 256, 256, 256, 256, 256, 256, 256, 256, 1 << 20, None)      # NULL either way
 """)
+
+
+@pytest.mark.parametrize("policy,fanout", [(0, 10), (1, 64)])
+def test_the_workspace_holds_the_states_of_the_tiles_and_no_more(run, policy, fanout):
+    # a batch's tiles are as small with the workspace that tns_workspace asks for as with any larger one; where it asks for more than
+    # the least, so does some batch of that size or smaller in the same workspace, and more queries never need less
+    run(f"""
+p = B.Plan(1000, {fanout}, policy={policy})
+B.tns_commit(p.handle)
+def grid(Q, size):
+    B.tns_run(p.handle, Q, 256, 0, 256, 0, 0, 256, 256, 256, 256, 256, 256, 256, 256, 256, size, 0)
+    return fake.fake_grid()
+def least(Q):
+    up = lambda n: (n + 255) // 256 * 256
+    tiles = (Q + 1023) // 1024
+    return max(up(4 * tiles) + up(8 * tiles) + 256, up(256 + 8 * ((Q + 63) // 64 + 1)))
+before, more = 0, 0
+for Q in list(range(1, 1100)) + [m + d for m in range(2048, 40_000, 512) for d in (-1, 0, 1)]:
+    size = B.tns_workspace(p.handle, Q)
+    assert size >= before and size >= least(Q), Q
+    before = size
+    assert grid(Q, size) == grid(Q, size + (1 << 20)), Q
+    if size > least(Q):
+        more = Q
+        assert any(grid(q, size) > grid(q, size - 256) for q in (Q, 4096) if q <= Q), Q
+assert 8192 < more < 1 << 14, more
+""")
