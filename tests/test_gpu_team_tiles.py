@@ -91,21 +91,3 @@ def test_hops_with_either_workspace(oracle_lib, policy):
                 assert torch.equal(g[k][:total], h[k][:total])
             n = total
     plan.close()
-
-
-def test_words_of_a_block():
-    """Where a block's slots lie, from one division per block, against a division per slot: every position in a line and every part of
-    the 39-bit slot index (the header's arithmetic, written out)."""
-    rng = np.random.default_rng(1)
-    off = np.concatenate([np.arange(0, 3000), (np.arange(1, 128)[:, None] * (1 << 32) + np.arange(-20, 20)).ravel(), rng.integers(0, 1 << 39, 20000)]).astype(np.uint64)
-    i = rng.integers(0, 1 << 24, off.size).astype(np.uint64)
-    lo, hi = off & np.uint64(0xffffffff), off >> np.uint64(32)
-    q = lo // np.uint64(10)
-    t = lo - q * np.uint64(10) + hi * np.uint64(6)
-    assert t.max() <= 771
-    tq = (t * np.uint64(205)) >> np.uint64(11)
-    base, at = (hi * np.uint64(429496729) + q + tq) * np.uint64(32), t - tq * np.uint64(10)
-    u = at + i
-    got = base + np.uint64(3) * u + np.uint64(2) * (u // np.uint64(10))
-    s = off + i
-    assert np.array_equal(got, s // np.uint64(10) * np.uint64(32) + s % np.uint64(10) * np.uint64(3))
