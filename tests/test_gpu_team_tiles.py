@@ -42,10 +42,10 @@ def test_tiles_of_small_batches(oracle_lib, policy, fanout):
         rowptr, cn, ce, ct = oracle_lib.compact(part)
         for size in (B.tns_workspace(plan.handle, Q), least(Q)):
             out = {k: torch.full_like(t, -7 if t.dtype != torch.uint8 else 255) for k, t in plan.alloc_outputs(Q).items()}
-            out["workspace"] = torch.full((size,), 255, dtype=torch.uint8, device="cuda")
-            guard = torch.full((4096,), 171, dtype=torch.uint8, device="cuda")      # right behind it, as a rule
+            room = torch.full((size + 4096,), 171, dtype=torch.uint8, device="cuda")      # what lies behind the workspace stays as it is
+            out["workspace"] = room[:size]
             plan.run(*(t[:Q] for t in dq), out=out)
-            assert not plan.status(out["workspace"]) and bool((guard == 171).all())
+            assert not plan.status(out["workspace"]) and bool((room[size:] == 171).all()), (Q, size)
             assert np.array_equal(out["rowptr"].cpu().numpy(), rowptr), (Q, size)
             assert np.array_equal(out["count"].cpu().numpy(), part.count), (Q, size)
             for name, want in (("cmp_nbr", cn), ("cmp_eid", ce), ("cmp_ts", ct)):
@@ -73,21 +73,26 @@ def test_hops_with_either_workspace(oracle_lib, policy):
         dt, de = torch.from_numpy(t).cuda(), torch.from_numpy(e).cuda()
         hops, ws = plan.run_khop([10, 10], dt, None, de)
         got = [{k: h[k].clone() for k in ("rowptr", "cmp_nbr", "cmp_eid", "cmp_ts")} for h in hops]
+        keys = ("nbr", "eid", "ts", "count", "rowptr", "cmp_nbr", "cmp_eid", "cmp_ts")
         small = 256 + least(Q) + least(10 * Q) + (2 * 3 * 8 + 255) // 256 * 256
         assert small <= ws.numel()
-        again = torch.full((small,), 255, dtype=torch.uint8, device="cuda")
-        keys = ("nbr", "eid", "ts", "count", "rowptr", "cmp_nbr", "cmp_eid", "cmp_ts")
-        for h in hops:
-            for k in keys:
-                h[k].fill_(-7)
-        B.tns_run_khop(plan.handle, [10, 10], float("inf"), Q, dt.data_ptr(), 0, de.data_ptr(), 0, 0,
-                       [{k: h[k].data_ptr() for k in keys} for h in hops], again.data_ptr(), small, torch.cuda.current_stream().cuda_stream)
-        torch.cuda.synchronize()
-        n = Q
-        for g, h in zip(got, hops):
-            total = int(g["rowptr"][n])
-            assert torch.equal(g["rowptr"][:n + 1], h["rowptr"][:n + 1])
-            for k in ("cmp_nbr", "cmp_eid", "cmp_ts"):
-                assert torch.equal(g[k][:total], h[k][:total])
-            n = total
+        for size in (small, B.tns_workspace_khop(plan.handle, [10, 10], Q)):
+            again = torch.full((size + 4096,), 171, dtype=torch.uint8, device="cuda")
+            for h in hops:
+                for k in keys:
+                    h[k].fill_(-7)
+            B.tns_run_khop(plan.handle, [10, 10], float("inf"), Q, dt.data_ptr(), 0, de.data_ptr(), 0, 0,
+                           [{k: h[k].data_ptr() for k in keys} for h in hops], again.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert bool((again[size:] == 171).all()), (Q, size)
+            n = Q
+            for g, h in zip(got, hops):
+                total = int(g["rowptr"][n])
+                assert torch.equal(g["rowptr"][:n + 1], h["rowptr"][:n + 1])
+                for k in ("cmp_nbr", "cmp_eid", "cmp_ts"):
+                    assert torch.equal(g[k][:total], h[k][:total])
+                n = total
+        with pytest.raises(B.TnsError):
+            B.tns_run_khop(plan.handle, [10, 10], float("inf"), Q, dt.data_ptr(), 0, de.data_ptr(), 0, 0,
+                           [{k: h[k].data_ptr() for k in keys} for h in hops], again.data_ptr(), small - 256, torch.cuda.current_stream().cuda_stream)
     plan.close()
