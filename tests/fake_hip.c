@@ -7,13 +7,16 @@
 #include <string.h>
 
 static size_t used, limit = (size_t)1 << 40;
-static int allocations, launches, capturing;
+static int allocations, launches, capturing, host_allocations, host_blocks, unsynchronized;
 static uint64_t grid_xy;                        /* of the latest launch */
 struct head { size_t bytes, pad[31]; };
 
 void fake_set_limit(size_t bytes) { limit = bytes; }
 size_t fake_used(void) { return used; }
 int fake_allocations(void) { return allocations; }
+int fake_host_allocations(void) { return host_allocations; }
+int fake_host_blocks(void) { return host_blocks; }      /* page-locked, not freed */
+void fake_fail_synchronize(int on) { unsynchronized = on; }
 int fake_launches(void) { return launches; }
 unsigned fake_grid(void) { return (unsigned)grid_xy; }
 
@@ -33,8 +36,14 @@ int hipFree(void *p) {
     if (p) { used -= h->bytes; free(h); }
     return 0;
 }
-int hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; return (*p = calloc(1, n)) ? 0 : 2; }
-int hipHostFree(void *p) { free(p); return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned flags) {
+    (void)flags;
+    if (!(*p = calloc(1, n))) return 2;
+    ++host_allocations;
+    ++host_blocks;
+    return 0;
+}
+int hipHostFree(void *p) { if (p) --host_blocks; free(p); return 0; }
 int hipHostGetDevicePointer(void **d, void *h, unsigned flags) { (void)flags; *d = h; return 0; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *stream) { (void)kind; (void)stream; memcpy(d, s, n); return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return 0; }
@@ -58,7 +67,7 @@ int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int d) { return d == 0 ? 0 : 101; }      /* hipErrorInvalidDevice */
 int hipGetLastError(void) { return 0; }
 const char *hipGetErrorString(int e) { return e == 2 ? "out of memory" : "error"; }
-int hipDeviceSynchronize(void) { return 0; }
+int hipDeviceSynchronize(void) { return unsynchronized ? 906 : 0; }
 int hipStreamSynchronize(void *s) { (void)s; return 0; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = NULL; return 0; }
 int hipStreamDestroy(void *s) { (void)s; return 0; }

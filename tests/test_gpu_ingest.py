@@ -95,6 +95,14 @@ def test_lists_that_move_and_zeros_of_either_sign(B, oracle_lib, sizing, batch, 
         assert np.array_equal(got["cap"], ref["cap"][mine]) and np.array_equal(got["size"], ref["size"][mine]), v
         for name in ("t_min", "t_max"):
             assert np.array_equal(np.float32(got[name]).view(np.int32), np.float32(ref[name][mine]).view(np.int32)), (v, name)
+    # and sampling over what has moved: the runs' slots and running edge counts, with few queries (a team of lanes each) and many
+    st = W.Stream(nodes, src, dst, ts, batch)
+    for queries in (500, 70_000):
+        targets, t_start, t_end = W.random_queries(queries, st, queries)
+        for policy, start in ((0, None), (0, t_start), (1, None), (1, t_start)):
+            plan.set_sampler(10, policy, 0, 4)
+            assert_same(gpu_sample(plan, targets, start, t_end), oracle_sample(oracle_lib, wl_of(st), targets, start, t_end, None, 10, policy, 0, 4),
+                        oracle_lib, f"queries={queries} policy={policy} windowed={start is not None}")
     plan.close()
 
 
@@ -240,10 +248,12 @@ def test_large_batches_through_both_pipelines(B, oracle_lib, batch):
     adj.close()
 
 
-@pytest.mark.parametrize("nodes", [1, 2, 63, 64, 65, 4095, 4096, 4097, (1 << 18) - 1, 1 << 18])
+@pytest.mark.parametrize("nodes", [1, 2, 63, 64, 65, 255, 256, 257, 511, 512, 513, 4095, 4096, 4097, (1 << 16) + 1, (1 << 18) - 1, 1 << 18, (1 << 18) + 1,
+                                   1 << 20, (1 << 20) + 1, 1 << 24])
 def test_one_workgroup_batches_at_digit_and_wave_boundaries(B, oracle_lib, nodes):
-    # batches sorted six bits of the node id at a time, 128 keys a wave: ids that are all ones in every digit (where the
-    # keys beyond the batch sort too), sizes around the waves' and the workgroup's, growth of the pools in between
+    # batches sorted six to nine bits of the node id at a time (one pass up to 2^8 nodes, two up to 2^18, three of seven or eight bits
+    # above), 128 keys a wave: ids that are all ones in every digit (where the keys beyond the batch sort too), sizes around the
+    # waves' and the workgroup's, growth of the pools in between
     rng = np.random.default_rng(nodes)
     sizes = [1, 2, 63, 64, 65, 127, 128, 129, 1023, 1024, 1025, 2047, 2048, 2048, 7]
     n = sum(sizes)
@@ -265,6 +275,7 @@ def test_one_workgroup_batches_at_digit_and_wave_boundaries(B, oracle_lib, nodes
         assert got[name] == ref[name], name
     st = W.Stream(nodes, src, dst, ts, n)
     targets, t_start, t_end = W.random_queries(6, st, 3000)
+    targets[::2] = rng.choice(src, len(targets[::2]))      # (nodes that have edges)
     wl = wl_of(st)
     assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl, targets, t_start, t_end, None, 10, 0, 0, 0),
                 oracle_lib, f"nodes={nodes}")
@@ -297,3 +308,24 @@ def test_segments_across_tiles_of_the_plan(B, oracle_lib, shift):
         assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl, targets, t_start, t_end, None, 10, policy, 0, 4),
                     oracle_lib, f"policy={policy}")
     plan.close()
+
+
+def test_stores_opened_closed_and_opened_again(B, oracle_lib):
+    # what a closed store leaves (device memory, the page-locked record that batches report to) serves the next ones, up to sixteen
+    # records: eighteen stores at once, their batches in turn, twice over, the kept memory given back in between
+    streams = [W.tiny_stream(100 + i, 3000 + 2500 * (i % 2), 29 + i, 1500) for i in range(18)]      # (mini-batches, and larger ones)
+    for again in range(3):
+        plans = [B.Plan(st.num_nodes, 10, block_threshold=16, flags=B.TNS_FLAG_DEVICE_INGEST) for st in streams]
+        for lo in range(0, 6000, 3000 if again == 1 else 1500):
+            for st, plan in zip(streams, plans):
+                part = slice(lo, min(lo + (3000 if again == 1 else 1500), st.n))
+                if part.start < st.n:
+                    plan.add_edges_device(to_dev(st.src[part], np.int32), to_dev(st.dst[part], np.int32), to_dev(st.ts[part], np.float32))
+        for i, (st, plan) in enumerate(zip(streams, plans)):
+            targets, t_start, t_end = W.random_queries(again, st, 500)
+            assert_same(gpu_sample(plan, targets, t_start, t_end), oracle_sample(oracle_lib, wl_of(st), targets, t_start, t_end, None, 10, 0, 0, 0),
+                        oracle_lib, f"store {i}, time {again}")
+            assert plan.stats()["num_edges"] == st.n
+            plan.close()
+        if again == 1:
+            B.tns_destroy(None)

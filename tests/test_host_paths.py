@@ -182,3 +182,29 @@ for Q in list(range(1, 1100)) + [m + d for m in range(2048, 40_000, 512) for d i
         assert any(grid(q, size) > grid(q, size - 256) for q in (Q, 4096) if q <= Q), Q
 assert 8192 < more < 1 << 14, more
 """)
+
+
+def test_records_kept_for_the_next_stores(run):
+    # a device-built store's page-locked record is kept when the store is closed, sixteen at most, and given back with the rest
+    run("""
+def stores(n): return [plan_of(1) for _ in range(n)]
+first = stores(20)
+assert fake.fake_host_allocations() == fake.fake_host_blocks() == 20
+for p in first: p.close()
+assert fake.fake_host_blocks() == 16                      # four freed
+again = stores(18)
+assert fake.fake_host_allocations() == 22 and fake.fake_host_blocks() == 18      # sixteen of them kept ones
+again[0].close()
+B.tns_destroy(None)
+assert fake.fake_host_blocks() == 17                      # the kept one; those in use stay
+again[0] = plan_of(1)
+for p in again: p.close()
+assert fake.fake_host_blocks() == 16
+B.tns_destroy(None)
+assert fake.fake_host_blocks() == 0 and fake.fake_used() == 0
+p = plan_of(1)
+fake.fake_fail_synchronize(1)                             # work that may still write to it: not kept
+p.close()
+fake.fake_fail_synchronize(0)
+assert fake.fake_host_blocks() == 0 and fake.fake_used() == 0
+""")
