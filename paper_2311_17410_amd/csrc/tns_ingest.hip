@@ -513,7 +513,8 @@ __device__ __forceinline__ void apply_node(const IngestArgs& a, const Batch& b, 
                     }
                 } else if (nb <= kInlineBlocks) {
                     for (int j = nb - 1; j >= 0; --j) {
-                        const BlockRec o = j > 0 ? N->rec[j] : tail;
+                        BlockRec o = tail;
+                        if (j > 0) o = N->rec[j];      // (a choice of one of the two would be one of addresses, with `tail` in memory)
                         dst[nb - 1 - j] = o;
                         dcum[nb - 1 - j] = before;
                         before += (uint32_t)rec_size(o);
