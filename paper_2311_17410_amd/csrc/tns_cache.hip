@@ -612,10 +612,12 @@ constexpr int kItems = 64, kItemStep = 8;                         // scores per 
 // often has enough entries, 34000 ids 25.6 / 28.4.
 constexpr int kNear = 8, kNearTiles = 32;
 // Where the line lies: a large gather saturates the memory, and the chain of dependent reads of the tiles beside it then
-// takes longer than the short launches do on a stream of their own.  Us per fetch, LRU / LFU / FIFO, this form and the
-// other: 262144 rows of 172 floats (11 M pieces of 16 bytes) 97 / 118 / 97 and 116 / 132 / 102, 524288 rows (23 M) 174 / 214 / 171 and
-// 169 / 194 / 162; rows of 173 floats, LRU, 66600 (12 M pieces of 4 bytes) 47 and 71, 262144 (45 M) 151 and 119; 2^20 rows of
-// 32 floats (8 M) 96 and 113.
+// takes longer than the short launches do on a stream of their own.  It was drawn where the two forms met at pieces of 16 bytes, when a
+// thread of this one moved eight; with four they meet further up.  42 K entries, us per fetch, LRU / LFU / FIFO, this form and the other:
+// rows of 172 floats, 262144 (11 M pieces of 16 bytes) 81 / 106 / 81 and 114 / 127 / 95, 390000 (17 M) 114 / 151 / 116 and 141 / 166 / 124, 524288 (23 M)
+// 149 / 198 / 149 and 169 / 206 / 153; 2^20 rows of 32 floats (8 M) 81 / 179 / 86 and 104 / 196 / 88, of 64 (17 M) 128 / 224 / 132 and 150 / 221 / 133; rows of
+// 173 floats, 66600 (12 M pieces of 4 bytes) 33 / 37 / 29 and 74 / 76 / 59, 97000 (17 M) 41 / 48 / 37 and 74 / 76 / 61, 180000 (31 M) 72 / 85 / 63 and 92 / 98 /
+// 74, 262144 (45 M) 103 / 123 / 89 and 105 / 121 / 88.
 constexpr int64_t kGatherWithin = int64_t(1) << 24, kOneLaunchIds = int64_t(1) << 20;
 constexpr uint32_t kNoWait = 1u << 31;                            // bit of the tickets of tiles that do not wait for one another (tests)
 constexpr int64_t kOneGroupEntries = (int64_t)kOneGroup * kItems;

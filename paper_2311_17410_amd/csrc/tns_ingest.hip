@@ -453,8 +453,11 @@ __device__ __forceinline__ SegTimes segment_times(const IngestArgs& a, const Bat
     return b.times(a, at);
 }
 // The records of a node's inline list behind its newest, read with the entry (Batch::kAhead): moving them one by one is a round trip
-// each, and so is copying a directory run.  k_apply in batches of 3 * 10^5 edges over 2^20 nodes, us a batch with the sampling 197.6 ->
-// 192; not in k_small_batch, whose program would get longer than the round trips cost (2000 edges 33.7 -> 36).
+// each, and so is copying a directory run.  It takes k_apply from 60 registers to 85, edges' threads too, eight waves per SIMD to five: us a batch
+// without / with, 3 * 10^5 edges over 2^20 nodes 131.9 / 129.3, the others the same within what runs differ by: 10^4 over 2^16 37.8 / 37.6, 10^5
+// over 2^18 51.3 / 51.5, over 2^20 power-law ids 74.9 / 73.1, 2^20 over 2^20 365 / 362, 2^21 over 2^20 666 / 672, over 2^22 938 / 944, 2^22 over 2^22
+// 1960 / 1970, 2^24 - 1 over 2^22 4616 / 4660.  Not in k_small_batch, whose program would get longer than the round trips cost (2000 edges
+// 33.7 -> 36).
 typedef uint32_t rec_words __attribute__((ext_vector_type(4)));
 struct OlderRecs { rec_words r[kInlineBlocks - 1]; };
 __device__ __forceinline__ OlderRecs load_older(const NodeLine* N) {

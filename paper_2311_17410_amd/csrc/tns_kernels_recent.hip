@@ -456,7 +456,10 @@ hipError_t launch_recent_t(const SampleArgs& a, hipStream_t stream) {
     // per wave: the table, the requests and their results; at least the 4 KiB in which the node lines are staged first
     const size_t chunk = std::max<size_t>((((size_t)kWave * stride * sizeof(pos_t) + 15) & ~size_t(15)) + 2 * kWave * (sizeof(SearchRequest) + 1), 4096);
     // The fused variant uses large workgroups: one chained-scan step per 1024 queries keeps the rate at which tiles publish
-    // their totals low enough for the look-back to keep up.
+    // their totals low enough for the look-back to keep up.  The registers would let ten waves each of two workgroups share a compute unit, so
+    // that one tile's searches fill the other's waits: with tickets, us with 16 / 10 / 8 waves, prefix layout, 10^6 queries 94.8 / 101.5 /
+    // 103.1, windowed 86.7 / 93.5 / 104.3, 2^22 339 / 350 / 357; two hops from 2^20 roots 393 / 395 / 478; 256 graphs 1327 / 1428 / 1535; blocks, 10^6
+    // 116 / 120 / 124, power-law ids 120 / 131 / 164, 2^24 1413 / 1601 / 1609.
     constexpr size_t kLds = 159u << 10;
     int waves = FUSED ? 16 : 4;
     while (waves > 1 && (size_t)waves * chunk > kLds) --waves;
