@@ -500,10 +500,7 @@ struct TileChain {
         if (kTagged) return tags.exclusive(tile, lane, p.defer_spins, [](int32_t v) { return wave_sum(v); });
         // (with tickets the sums stay shuffles: as vector instructions, us, 10^6 queries over the prefix layout 99.9 -> 100.0, where the
         // kernel before took 99.1 to 99.6, two hops from 2^20 roots 399 -> 402)
-        const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane, [](int64_t v) {
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-            return v;
-        }) : 0;
+        const int64_t excl = tile > 0 ? lookback_exclusive(ws(p), p.err_flag, tile, lane, Shuffles{}) : 0;
         if (lane == 0)
             __hip_atomic_store(&ws(p)->status[tile], kStPrefix | (uint64_t)(excl + total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return excl;
