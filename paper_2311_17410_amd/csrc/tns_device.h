@@ -530,13 +530,27 @@ struct TileChain<kNoScan> {
 // order measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
 // Sums over the wave and over the waves as vector instructions, not as shuffles and a loop: with tickets, us with those / with these, prefix
 // layout, 10^6 queries 94.6 / 94.0, windowed 87.9 / 86.7, 2^22 343 / 340, uniform policy 115.0 / 115.6; two hops from 2^20 roots 402 / 393, 256
-// graphs 1346 / 1333; blocks, 10^6 118.1 / 117.1, 2^22 367 / 363, 2^24 1426 / 1421.
-template <bool CHAIN_FIRST, class Chain, class Load>
+// graphs 1346 / 1333; blocks, 10^6 118.1 / 117.1, 2^22 367 / 363, 2^24 1426 / 1421 (all three sums).
+// SHUFFLED_SCAN: the scan over the wave as shuffles all the same (recent policy, blocks, tickets): as vector instructions C5, 2^28 queries,
+// takes 25.83 ms instead of 25.75, runs within 0.01 of one another.  It is not for every size: 256 graphs 1341 with shuffles and 1333
+// without, 2^22 queries 366 and 363, 10^6 over power-law ids 121.1 and 120.3, 2^25 and 2^26 the same; but with both forms in the kernel, chosen
+// by the number of queries, C5 takes 25.89.  Over the prefix layout (C5 22.03 / 21.89) and under the uniform policy (28.19 / 28.13) vector
+// instructions are the faster form there too.
+template <bool CHAIN_FIRST, bool SHUFFLED_SCAN, class Chain, class Load>
 __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_wave_sum, int32_t* s_arrived,
                                              Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
                                              uint32_t f_mul, const Load& load) {
     const int32_t f = p.fanout;
-    const int32_t inc = wave_inclusive_scan(k);
+    int32_t inc = k;
+    if (SHUFFLED_SCAN) {
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int32_t u = __shfl_up(inc, d, kWave);
+            if (lane >= d) inc += u;
+        }
+    } else {
+        inc = wave_inclusive_scan(k);
+    }
     tc.begun();
     auto chain = [&](int32_t wg_total) {
         const int64_t excl = tc.look_back(p, wg_total, lane);
