@@ -601,9 +601,9 @@ __global__ void __launch_bounds__(256) k_newids_collect_hist0(const NewIds f, in
 // every score and counted in a pass of their own they took 9.  Time stamps, batch of 66600 of which 8388 are replaced: new ids
 // known at 8 us, threshold at 15, victims stored at 18; since then the lowest score is found, and under LRU the eight lowest
 // values are counted (kNear), before the tile waits for the others.
-// 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO, one cache again and again: 66600 ids 71 / 74 / 61 -> 34 / 36 / 32, 16000 ids 67 / 67 / 60
-// -> 22 / 19 / 16, 600 ids 69 / 67 / 60 -> 16 / 15 / 13.  Three caches in turn, so that their rows come from memory: 66600 ids
-// 83 / 84 / 65 -> 41 / 44 / 40.
+// 42 K entries, rows of 172 floats, us per fetch, LRU / LFU / FIFO, one cache again and again: 66600 ids 71 / 74 / 61 -> 31 / 35 / 28, 16000 ids 67 / 67 / 60
+// -> 21 / 18 / 17, 600 ids 69 / 67 / 60 -> 16 / 16 / 16, which is what a call from Python takes.  Three caches in turn, so that their rows come from
+// memory: 66600 ids 83 / 84 / 65 -> 34 / 38 / 33.
 constexpr int kOneGroup = 1024, kOneGroupWaves = kOneGroup / kWave;
 constexpr int kItems = 64, kItemStep = 8;                         // scores per thread, and per uniform branch
 // LRU: values from the lowest on that are counted at once while new ids are awaited, if these come from enough tiles for the wait to be
