@@ -33,7 +33,6 @@ struct SampleArgs {
     // non-null: also remove the padding in the same pass (chained scan over workgroups);
     // scan_ws is the caller's workspace, rowptr / cmp_* the dense outputs
     void* scan_ws;
-    int64_t scan_states;     // tile states that it holds
     int64_t* rowptr;
     int32_t* cmp_nbr;
     int32_t* cmp_eid;
@@ -59,7 +58,14 @@ struct SampleArgs {
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
     uint64_t chain_tag;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)
     uint32_t* err_flag;    // where a chained scan whose bounded wait ran out reports it (null: the error word of scan_ws)
+    // Read by the host alone, and last: between scan_ws and rowptr it moved what the kernels request together, which cost the large batches
+    // of the prefix layout, with the data of several calls in turn, us: 10^6 queries 102.2 -> 104.4, 7 * 10^5 76.7 -> 78.0, 2^22 352.7 -> 355.9,
+    // two hops from 2^20 roots 397 -> 398.7, 256 graphs 1336 -> 1339 (but the uniform policy, 10^6 queries, 123.6 -> 121.5).
+    int64_t scan_states;     // tile states that scan_ws holds
 };
+
+static_assert(offsetof(SampleArgs, rowptr) == offsetof(SampleArgs, scan_ws) + sizeof(void*) && offsetof(SampleArgs, scan_states) == sizeof(SampleArgs) - sizeof(int64_t),
+              "the kernels' arguments lie side by side");
 
 struct CompactArgs {
     const int32_t* nbr;
