@@ -37,12 +37,6 @@ struct SampleArgs {
     int32_t* cmp_nbr;
     int32_t* cmp_eid;
     float* cmp_ts;
-    // Tile states that scan_ws holds: read by the host alone, but where it lies moves what the kernels request together from their
-    // arguments.  Large batches, data of several calls in turn, us, without it / between scan_ws and rowptr / here / at the end: recent
-    // policy, prefix layout, 10^6 queries 102.3 / 104.4 / 102.8 / 102.4, 7 * 10^5 76.9 / 78.1 / 76.8 / 76.7, 2^22 356 / 357 / 355 / 354, two hops from 2^20
-    // roots 405 / 398 / 398 / 397, 256 graphs 1341 / 1337 / 1342 / 1337; uniform policy, prefix layout, 10^6 124.2 / 124.1 / 121.5 / 123.8, blocks 153.2 /
-    // 152.0 / 151.2 / 153.4, power-law ids 2^23 1755 / 1753 / 1753 / 1759.  (Without it the sums in the output stage are shuffles.)
-    int64_t scan_states;
     int64_t Q;               // number of queries, or an upper bound of it when Q_dev is set
     const int64_t* Q_dev;    // may be null; device-resident number of queries (hops after the first)
     int64_t* total_out;      // may be null; fused variant: also receives the dense total (rowptr[Q])
@@ -64,10 +58,14 @@ struct SampleArgs {
     int32_t prefix_layout; // the store is in the prefix layout: `edges` is the one array of lines, node v's line is line v
     uint64_t chain_tag;    // small grids: what tells this launch's tile states from older ones (TaggedChain in tns_chain.h)
     uint32_t* err_flag;    // where a chained scan whose bounded wait ran out reports it (null: the error word of scan_ws)
+    // Tile states that scan_ws holds: read by the host alone, and last, because where it lies moves what the kernels request together from
+    // their arguments.  Between scan_ws and rowptr / behind cmp_ts / here, large batches, data of several calls in turn, us: recent policy,
+    // prefix layout, 10^6 queries 104.4 / 102.8 / 102.4, 2^22 357 / 355 / 354; uniform policy, 10^6 queries, fan-out 10, prefix layout 124.1 /
+    // 121.5 / 123.8, blocks 152.0 / 151.2 / 153.4.  Behind cmp_ts / here, fan-out 32 over power-law ids, 2 * 10^5 queries 163 / 152, 330000 262 / 234.
+    int64_t scan_states;
 };
 
-static_assert(offsetof(SampleArgs, rowptr) == offsetof(SampleArgs, scan_ws) + sizeof(void*) && offsetof(SampleArgs, Q) == offsetof(SampleArgs, scan_states) + sizeof(int64_t),
-              "the place of scan_states");
+static_assert(offsetof(SampleArgs, scan_states) == sizeof(SampleArgs) - sizeof(int64_t), "what kernels read lies side by side");
 
 struct CompactArgs {
     const int32_t* nbr;
