@@ -528,21 +528,25 @@ struct TileChain<kNoScan> {
 // CHAIN_FIRST (recent policy): the look-back reads come before the wave's padded stores (a load result can only be waited
 // for together with every store issued before it, and a store takes microseconds to be taken).  Uniform policy: the other
 // order measured faster (C5 step 31.2 against 36.6 ms; its waves reach this point far apart).
-// Sums over the wave and over the waves as vector instructions, not as shuffles and a loop: with tickets, us with those / with these, prefix
-// layout, 10^6 queries 94.6 / 94.0, windowed 87.9 / 86.7, 2^22 343 / 340, uniform policy 115.0 / 115.6; two hops from 2^20 roots 402 / 393, 256
-// graphs 1346 / 1333; blocks, 10^6 118.1 / 117.1, 2^22 367 / 363, 2^24 1426 / 1421 (all three sums).
-// SHUFFLED_SCAN: the scan over the wave as shuffles all the same (recent policy, blocks, tickets): as vector instructions C5, 2^28 queries,
-// takes 25.83 ms instead of 25.75, runs within 0.01 of one another.  It is not for every size: 256 graphs 1341 with shuffles and 1333
-// without, 2^22 queries 366 and 363, 10^6 over power-law ids 121.1 and 120.3, 2^25 and 2^26 the same; but with both forms in the kernel, chosen
-// by the number of queries, C5 takes 25.89.  Over the prefix layout (C5 22.03 / 21.89) and under the uniform policy (28.19 / 28.13) vector
-// instructions are the faster form there too.
-template <bool CHAIN_FIRST, bool SHUFFLED_SCAN, class Chain, class Load>
+// Sums over the wave and over the waves are vector instructions, not shuffles and loops, but where that measured slower.
+//   kVectorSums: us with shuffles / with these, tickets, recent policy, prefix layout, 10^6 queries 94.6 / 94.0, windowed 87.9 / 86.7, 2^22
+//   343 / 340; two hops from 2^20 roots 402 / 393
+//   kShuffledScan, recent policy over blocks with tickets: the scan over the wave.  C5, 2^28 queries, 25.75 with it and 25.83 ms without, runs
+//   within 0.01 of one another.  It is not for every size: 256 graphs 1341 with it and 1333 without, 2^22 queries 366 and 363, 2^25 and 2^26 the
+//   same; but with both forms in the kernel, chosen by the number of queries, C5 takes 25.89
+//   kLargeShuffled, uniform policy over the prefix layout without tickets: all of them with fan-outs that are gathered in batches.
+//   Power-law ids, vector / this, fan-out 20, 4000 queries 61.8 / 59.8, 33000 69.7 / 67.5, fan-out 32 86.4 / 82.8, 95.4 / 92.1, fan-out 64 148 / 140, 162 / 155
+//   kShuffled, the same with tickets: all of them.  Uniform ids, vector / this, fan-out 64, 180000 queries 87.6 / 80.0, 520000 189 / 165, 2 * 10^6
+//   593 / 552, fan-out 32 57.6 / 55.1, 120 / 116, 356 / 337; fan-out 10 the same, C5 24.13 / 24.34 ms; chosen by the fan-out as without tickets
+//   they are as slow as vector instructions
+enum Sums : int { kVectorSums, kShuffledScan, kLargeShuffled, kShuffled };
+template <bool CHAIN_FIRST, Sums SUMS, class Chain, class Load>
 __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_tile_base, int32_t* s_wave_sum, int32_t* s_arrived,
                                              Chain& tc, int wave, int waves_per_wg, int lane, int64_t q0, int64_t Q, int32_t k,
                                              uint32_t f_mul, const Load& load) {
     const int32_t f = p.fanout;
     int32_t inc = k;
-    if (SHUFFLED_SCAN) {
+    if (SUMS == kShuffledScan || SUMS == kShuffled || (SUMS == kLargeShuffled && f > kGatherChunk)) {
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
             const int32_t u = __shfl_up(inc, d, kWave);
@@ -568,11 +572,18 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
             }
         }
     };
-    auto row_of_wave = [&]() {
-        const int32_t off = sum_of_waves(s_wave_sum, wave, lane);
+    auto row_of_wave = [&](int32_t off) {
         const int64_t base = *s_tile_base;
         return wave_uniform(Chain::kTagged && base < 0 ? base : base + off);
     };
+    auto sum_before = [&](auto vector, int n) {      // of the first n waves
+        if (decltype(vector)::value) return sum_of_waves(s_wave_sum, n, lane);
+        int32_t sum = 0;
+        for (int i = 0; i < n; ++i) sum += s_wave_sum[i];
+        return sum;
+    };
+    constexpr std::integral_constant<bool, SUMS != kShuffled> small{};
+    constexpr std::integral_constant<bool, SUMS != kShuffled && SUMS != kLargeShuffled> large{};
     GatherRegs g;
     if (f <= kGatherChunk) {
         // No barrier between a wave's searches and its gather (the lines the searches fetched are then still in the L2): the
@@ -590,7 +601,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         int32_t wg_total = 0;
         if (is_last) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            wg_total = sum_of_waves(s_wave_sum, waves_per_wg, lane);
+            wg_total = sum_before(small, waves_per_wg);
             tc.publish_total(p, wg_total, lane);
         }
         wave_lds_sync();      // what the load reads from LDS was written by this wave's own lanes
@@ -599,7 +610,7 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         store_padded(g, p, lane, 0, q0, Q);
         if (!CHAIN_FIRST && is_last) chain(wg_total);
         lds_barrier();
-        const int64_t row0 = row_of_wave();
+        const int64_t row0 = row_of_wave(sum_before(small, wave));
         if (Chain::kTagged && row0 < 0) return;
         write_rowptr(row0);
         store_dense(g, p, f_mul, lane, 0, row0, inc - k);
@@ -608,12 +619,12 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
         if (lane == kWave - 1) s_wave_sum[wave] = inc;
         __syncthreads();
         if (wave == 0) {
-            const int32_t wg_total = sum_of_waves(s_wave_sum, waves_per_wg, lane);
+            const int32_t wg_total = sum_before(large, waves_per_wg);
             tc.publish_total(p, wg_total, lane);
             chain(wg_total);
         }
         __syncthreads();
-        const int64_t row0 = row_of_wave();
+        const int64_t row0 = row_of_wave(sum_before(large, wave));
         const bool dense = !Chain::kTagged || row0 >= 0;
         if (dense) write_rowptr(row0);
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {

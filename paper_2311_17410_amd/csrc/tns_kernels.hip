@@ -457,7 +457,7 @@ sample_tile:
 
     auto load = [&](GatherRegs& g, int32_t it0) { gather_load<pos_t, POLICY == 1>(g, p, f_mul, stride, w_pos, lane, it0, k); };
     if constexpr (FUSED) {
-        fused_output<false, false>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+        fused_output<false, kVectorSums>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         wave_lds_sync();
         GatherRegs g;

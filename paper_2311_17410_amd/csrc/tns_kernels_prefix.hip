@@ -267,7 +267,7 @@ sample_tile:
         gather_load<pos_t, POLICY == 1>(g, p, f_mul, rs * 4 / (int32_t)sizeof(pos_t), w_pos, lane, it0, k);
     };
     if constexpr (FUSED) {
-        fused_output<false, false>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+        fused_output<false, SCAN == kTickets ? kShuffled : kLargeShuffled>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {

@@ -438,7 +438,7 @@ sample_tile:
         }
     };
     if constexpr (FUSED) {
-        fused_output<true, !PREFIX && SCAN == kTickets>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
+        fused_output<true, !PREFIX && SCAN == kTickets ? kShuffledScan : kVectorSums>(p, &s_tile_base, s_wave_sum, &s_arrived, tc, wave, waves_per_wg, lane, q0, Q, k, f_mul, load);
     } else {
         GatherRegs g;
         for (int32_t it0 = 0; it0 < f; it0 += kGatherChunk) {
