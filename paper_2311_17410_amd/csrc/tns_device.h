@@ -637,21 +637,27 @@ __device__ __forceinline__ void fused_output(const SampleArgs& p, int64_t* s_til
 
 // Waves per workgroup of a kernel with a query per lane, `most` or fewer by halves, so that a small batch's queries spread over the compute
 // units instead of queueing at the address units of a few.
-//   sampling alone: at least 512 workgroups; with tickets: at least one per compute unit (fewer, larger tiles: a shorter chain), with
-//   larger fan-outs a quarter more of the largest, whose last ones would have the chip to themselves.  us with 512 / this: 400000
-//   queries 50.5 / 45.1, power-law ids 58.2 / 54.3, prefix layout 48.9 / 43.6 and 58.2 / 53.9; fan-out 20, 200000 queries 43.1 / 36.5, 47.6 / 41.5,
-//   42.3 / 36.3, 47.4 / 41.2; 300000 with 256 of the largest 57.9 instead of 56.6 and 70.3 instead of 66.6
+//   sampling alone, and under the uniform policy over the prefix layout (prefix_uniform) with fan-outs above 12: at least 512 workgroups.
+//   33000 queries, fan-out 20 / 32 / 64 over power-law ids, 129 workgroups of four waves 70.5 / 97.0 / 164, 516 of one 67.5 / 92.1 / 155
+//   with tickets: at least one per compute unit (fewer, larger tiles: a shorter chain), of the largest a quarter more, with
+//   larger fan-outs three quarters, whose last ones would have the chip to themselves.  us with 512 / this: 400000
+//   queries 58.7 / 55.5, power-law ids 59.9 / 56.6, prefix layout 54.2 / 49.7 and 59.9 / 55.5; fan-out 20, 200000 queries 43.1 / 36.5, 47.6 / 41.5,
+//   42.3 / 36.3, 47.4 / 41.2.  Between one per compute unit and these lines, the largest / half of it: 270000 queries 45.3 / 44.3, 55.1 / 52.1, 44.4 / 43.5,
+//   53.7 / 52.2, 315000 48.5 / 48.5, 55.0 / 53.6, 44.3 / 45.2, 53.9 / 53.3; fan-out 20, 330000 81.5 / 77.0, 85.5 / 82.3, 65.3 / 65.4, 75.1 / 73.7, 400000
+//   89.6 / 89.5, 100.8 / 100.4, 73.2 / 75.4, 82.3 / 83.4
 //   without tickets, one round of workgroups: what counts is how many waves the fullest compute unit has, and the fewest tiles with
 //   which that is not a third more than it could be; with sixteen waves a workgroup fills a compute unit, so some are left free.
 //   us with 512 / this, recent policy, uniform and power-law ids, prefix layout likewise: 40000 queries 12.9 / 12.5, 17.4 / 17.1, 13.2 / 12.3,
 //   17.8 / 16.9; 65536 14.8 / 13.7, 19.4 / 18.3, 14.6 / 13.2, 18.9 / 17.5; 10^5 17.9 / 17.3, 21.8 / 21.1, 16.9 / 16.5, 20.6 / 19.9; 2 * 10^5 28.6 / 27.9,
 //   31.8 / 31.5, 24.6 / 23.7, 28.4 / 28.1; 2^17, 150000 and 2^18 the same within 2 %
-inline int workgroup_waves(int64_t Q, int32_t f, int most, bool fused) {
+inline int workgroup_waves(int64_t Q, int32_t f, int most, bool fused, bool prefix_uniform = false) {
     constexpr int64_t kUnits = 256;
     auto tiles = [&](int w) { return (Q + (int64_t)w * kWave - 1) / ((int64_t)w * kWave); };
     int waves = most;
-    if (!fused || Q > tagged_queries(f)) {
-        while (waves > 1 && tiles(waves) < (!fused ? 512 : (waves == most && f > 12 ? kUnits + kUnits / 4 : kUnits))) waves >>= 1;
+    const bool spread = !fused || (prefix_uniform && f > 12);
+    if (spread || Q > tagged_queries(f)) {
+        const int64_t of_largest = kUnits + (f > 12 ? 3 * kUnits / 4 : kUnits / 4);
+        while (waves > 1 && tiles(waves) < (spread ? 2 * kUnits : (waves == most ? of_largest : kUnits))) waves >>= 1;
         return waves;
     }
     auto fullest = [&](int w) { return w * ((tiles(w) + kUnits - 1) / kUnits); };

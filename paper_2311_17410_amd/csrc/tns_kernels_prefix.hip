@@ -291,7 +291,7 @@ hipError_t launch_prefix_t(const SampleArgs& a, hipStream_t stream) {
     // 6.91 / 7.83 ms with 4 / 8 / 16 waves).  Without the scan small workgroups come and go more evenly.
     int waves = FUSED ? 8 : 2;
     while (waves > 1 && (size_t)waves * chunk > (size_t)(159u << 10)) --waves;      // LDS of a workgroup: 160 KiB
-    waves = workgroup_waves(a.Q, a.fanout, waves, FUSED);
+    waves = workgroup_waves(a.Q, a.fanout, waves, FUSED, true);
     const int64_t per_wg = (int64_t)waves * kWave;
     const int64_t grid = (a.Q + per_wg - 1) / per_wg;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -9,12 +9,13 @@ from test_host_paths import run  # noqa: F401
 # layout's flag, policy, fan-out, whether the padding is removed, and the lines: the first batch size beyond it, waves per workgroup on
 # either side
 LINES = [
-    (0, 0, 10, True, [(65_537, 4, 2), (81_921, 2, 8), (131_073, 8, 4), (180_225, 4, 16), (229_377, 16, 8), (262_145, 8, 16)]),
-    (0, 0, 20, True, [(65_537, 4, 2), (81_921, 2, 8), (326_657, 8, 16)]),
-    (0, 0, 64, True, [(65_537, 2, 4)]),
+    (0, 0, 10, True, [(65_537, 4, 2), (81_921, 2, 8), (131_073, 8, 4), (180_225, 4, 16), (229_377, 16, 8), (326_657, 8, 16)]),
+    (0, 0, 20, True, [(65_537, 4, 2), (81_921, 2, 8), (457_729, 8, 16)]),
+    (0, 0, 64, True, [(65_537, 2, 4), (228_865, 4, 8)]),
     (0, 1, 10, True, [(49_153, 1, 2), (81_921, 2, 4)]),
-    (128, 0, 10, True, [(16_385, 1, 2), (32_769, 2, 4), (65_537, 4, 2), (81_921, 2, 8), (131_073, 8, 4), (180_225, 4, 16), (229_377, 16, 8), (262_145, 8, 16)]),
+    (128, 0, 10, True, [(16_385, 1, 2), (32_769, 2, 4), (65_537, 4, 2), (81_921, 2, 8), (131_073, 8, 4), (180_225, 4, 16), (229_377, 16, 8), (326_657, 8, 16)]),
     (128, 1, 10, True, [(16_385, 1, 2), (32_769, 2, 4), (65_537, 4, 2), (81_921, 2, 8), (131_073, 8, 4), (180_225, 4, 8)]),
+    (128, 1, 20, True, [(65_409, 1, 2), (130_817, 2, 4), (261_633, 4, 8)]),
     (0, 0, 10, False, [(65_409, 1, 2), (130_817, 2, 4)]),
     (128, 1, 20, False, [(65_409, 1, 2)]),
 ]
