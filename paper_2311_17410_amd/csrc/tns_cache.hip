@@ -247,12 +247,14 @@ __device__ __forceinline__ void look_up(const int32_t (&id)[N], int32_t (&s)[N],
 // looked up once each and handed over in LDS.  us per fetch with pieces a grid width apart / consecutive / consecutive and
 // handed over: 2^20 rows of 172 floats, LFU 371 / 369 / 363, of 128 224 / 218 / 217, of 32 149 / 145 / 146, of 173 (pieces of 4 bytes) 324 /
 // 309 / 295.  In k_update, whose workgroups are four times as large, handing over costs more than it gives: 66600 rows of 172 27.6 /
-// 27.9 / 28.2, of 173 29.8 / 29.9 / 31.6, 300000 of 172 95.4 / 94.3 / 96.8.
+// 27.9 / 28.2, of 173 29.8 / 29.9 / 31.6, 300000 of 172 95.4 / 94.3 / 96.8.  There a workgroup takes `chunk` pieces, as many as the others: with
+// 8192 for every one but the last, two workgroups shared 10^4 rows of one float as four to one (LFU 18.8 -> 21.0 us, FIFO 19.7 -> 23.4).
 template <int VEC, int THREADS, int UNROLL>
 __device__ __forceinline__ void gather_each(const float* __restrict__ rows, const float* __restrict__ store, int32_t dim,
                                             uint32_t total, const RowOf row, int64_t num_ids, const int32_t* __restrict__ ids,
-                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid) {
-    const uint32_t t0 = bid * (THREADS * UNROLL) + threadIdx.x;
+                                            const int32_t* __restrict__ slot_of, float* __restrict__ out, uint32_t bid, uint32_t chunk) {
+    const uint32_t t0 = bid * chunk + threadIdx.x;
+    total = min(total, (bid + 1) * chunk);
     uint32_t col[UNROLL];
     int32_t id[UNROLL], s[UNROLL];
 #pragma unroll
@@ -867,11 +869,11 @@ __global__ void k_fifo_advance(int64_t capacity, int64_t* ring, Ctl* ctl) { fifo
 template <bool SELECT, int GATHER>
 __global__ void __launch_bounds__(kOneGroup) k_update(const CacheState c, const NewIds f, int64_t B, int64_t tiles, tns::ScanWorkspace* chain,
                                                       int32_t* __restrict__ victims, const float* __restrict__ store, int32_t dim,
-                                                      uint32_t pieces, const RowOf row, int64_t num_ids, float* __restrict__ out) {
+                                                      uint32_t pieces, uint32_t chunk, const RowOf row, int64_t num_ids, float* __restrict__ out) {
     __shared__ uint32_t s_ticket;
     if ((int64_t)blockIdx.x >= tiles) {
         gather_each<GATHER, kOneGroup, update_unroll(GATHER)>(c.rows, store, dim, pieces, row, num_ids, f.ids, c.slot_of, out,
-                                                              blockIdx.x - (uint32_t)tiles);
+                                                              blockIdx.x - (uint32_t)tiles, chunk);
         return;
     }
     // tiles are numbered in the order workgroups start, so that a tile only waits for tiles that have started
@@ -1120,9 +1122,10 @@ int tns_cache_fetch(tns_cache* cache, int64_t B, const int32_t* d_ids, const flo
     if (one_launch) {
         const int unroll = update_unroll(vec4 ? 4 : 1);
         const int64_t gather_blocks = blocks_for((pieces + unroll - 1) / unroll, kOneGroup);
+        const int64_t chunk = (pieces + gather_blocks * kOneGroup - 1) / (gather_blocks * kOneGroup) * kOneGroup;      // at most kOneGroup * unroll
         auto update = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles_b + gather_blocks)), dim3(kOneGroup), 0, us, st, nf, B, tiles_b, w.chain, w.victims,
-                               store, dim, (uint32_t)pieces, row, N, d_out);
+                               store, dim, (uint32_t)pieces, (uint32_t)chunk, row, N, d_out);
         };
         if (policy == TNS_CACHE_FIFO) vec4 ? update(k_update<false, 4>) : update(k_update<false, 1>);
         else vec4 ? update(k_update<true, 4>) : update(k_update<true, 1>);

@@ -268,3 +268,14 @@ def test_rows_of_a_workgroup_looked_up_once(KB, dim, b):
     batches[2] = batches[0]
     gpu, *_ = run_sequence(KB, CO.LRU, n, cap, dim, 0.2, batches, 4, check_state_every=3)
     gpu.close()
+
+
+@pytest.mark.parametrize("dim,b", [(1, 8191), (1, 8192), (1, 8193), (1, 10_000), (1, 16_385), (3, 5462), (4, 4097), (4, 12_289), (8, 2049), (173, 95)])
+def test_pieces_shared_out_evenly_beside_the_update(KB, dim, b):
+    # a cache of up to 65536 entries: the rows are moved beside the update, by as few workgroups as there are thousands of pieces, eight (or
+    # four of 16 bytes) a thread, and each takes as many of them as the others: batches that fill one workgroup, and a few pieces more
+    rng = np.random.default_rng(b)
+    for policy in (CO.LRU, CO.FIFO):
+        batches = [rng.integers(0, 70_000, b) for _ in range(3)]
+        batches[1][rng.integers(0, b, 5)] = [-1, 70_000, 2 ** 31 - 1, 0, 69_999]
+        run_sequence(KB, policy, 70_000, 3000, dim, 0.2, batches, 4, check_state_every=3)[0].close()
